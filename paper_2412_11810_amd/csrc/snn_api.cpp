@@ -212,6 +212,22 @@ size_t work_bytes(const NetDev &n, int chunk_len) {
   return bwd > fwd ? bwd : fwd;
 }
 
+// Steps of the adjoint pass per pipeline stage that a training step aims at (where the budget allows chunks of that
+// length).  A stage costs its launches and prologues once, whatever its length; the layers run one tile apart, so
+// L - 1 tiles of filling and draining come on top of the T steps: the sum is least at sqrt(T * o / (L - 1)) with o the
+// stage's fixed cost in steps.  Measured: o = 16 for layers whose recurrence stays inside a compute unit (about 1 us
+// per step against 15 us per stage), 4 for the chip-wide recurrences of layers up to 1024 neurons (5-14 us per step,
+// weights loaded again in every launch).  Wider layers are bound by throughput, a stage with fewer jobs is shorter, so
+// filling costs next to nothing there: 64 steps, where the inter-layer products reach their large tiles (batch 32).
+int bwd_tile_target(const NetDev &n, int T) {
+  int nmax = 0;
+  for (int l = 0; l < n.L; ++l) nmax = std::max(nmax, n.N[l]);
+  if (n.L == 1) return SNN_BWD_TILE;
+  if (nmax > 1024) return 64;
+  const double o = nmax <= 256 ? 16.0 : 4.0;
+  return std::max(16, std::min(SNN_BWD_TILE, (int)std::sqrt((double)T * o / (n.L - 1))));
+}
+
 // tile shape of the dense weight-gradient contraction: wide tiles when the network's matrices fill the chip with them
 bool dw_wide_tiles(const NetDev &n) {
   int tiles4 = ((n.N[n.L - 1] + 63) / 64) * ((n.n_out + 63) / 64);
@@ -1542,10 +1558,12 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
   }
   // every tile of the adjoint pass in order (their time ranges are fixed by the schedule): the head of a
   // tile (du_t, the top layer's product) is computed one stage early
+  // (layers in a pipeline: shorter tiles than the workspace would allow, see bwd_tile_target)
+  const int tile_len = pipelined ? bwd_tile_target(n, T) : SNN_BWD_TILE;
   std::vector<BwdPipe::NextTile> all_tiles;
   for (const SchedOp &o : ops)
     if (o.op == OP_BACKWARD)
-      for (int t1 = o.a; t1 >= o.b; t1 -= SNN_BWD_TILE) all_tiles.push_back({std::max(o.b - 1, t1 - SNN_BWD_TILE), t1});
+      for (int t1 = o.a; t1 >= o.b; t1 -= tile_len) all_tiles.push_back({std::max(o.b - 1, t1 - tile_len), t1});
   size_t tile_no = 0;
   auto buf_of = [&](size_t i) { return chunk0 + (size_t)(refwd2_ordinal[i] % p.n_chunk_bufs) * p.chunk_len * slot; };
   // Looks past op index `from` for the next `want` REFWD2 ops that can be started early: nothing between here
@@ -1710,12 +1728,12 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
         break;
       }
       case OP_BACKWARD: {
-        // long spans (Standard: the whole sequence) are walked in tiles of SNN_BWD_TILE steps so that
-        // the per-tile scratch stays small; neither the adjoint recurrence (carried state) nor the
+        // long spans (Standard: the whole sequence) are walked in tiles of at most SNN_BWD_TILE steps so that
+        // the per-tile scratch stays small and the layers' pipeline fills quickly; neither the adjoint recurrence (carried state) nor the
         // weight-gradient accumulation (continued per element) depends on where the cuts fall
         const int base = strategy == SNN_STANDARD ? 0 : chunk_base;
-        for (int t1 = op.a; t1 >= op.b; t1 -= SNN_BWD_TILE) {
-          const int t0 = std::max(op.b - 1, t1 - SNN_BWD_TILE);
+        for (int t1 = op.a; t1 >= op.b; t1 -= tile_len) {
+          const int t0 = std::max(op.b - 1, t1 - tile_len);
           const BwdTile tile{t0, t1, base, 0, chunk, nullptr};
           PreJobs pre{};
           if (prefetch && t1 == op.a) { // once per chunk, with its first tile
@@ -1823,6 +1841,23 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
         p.keep_from = keep_from;
         p.n_cache_slots = std::max(p.C, T - keep_from);
       }
+    }
+  }
+  // Chunks of several fine intervals where what is left of the budget holds them (Chunk, Double, Hierarchical): the
+  // backward pass then walks longer chunks from every m-th checkpoint.  Short intervals make it a series of launches
+  // that are too small for the chip (a chunk of 10 steps of three 1024-wide layers costs 10 launches of 5-140 us, most
+  // of the adjoint ones weight prologue); the results do not depend on where chunks are cut.  Hierarchical keeps its
+  // batches: the same span of time per transfer, so m divides nb_local.
+  if (c->bwd_pipeline && (strategy == SNN_CHUNK || strategy == SNN_DOUBLE || strategy == SNN_HIER)) {
+    const int target = bwd_tile_target(n, T), span = strategy == SNN_CHUNK ? T : strategy == SNN_DOUBLE ? p.C : p.C * p.F;
+    for (int m = std::min(target / p.F, (span + p.F - 1) / p.F); m > 1; --m) {
+      if (strategy == SNN_HIER && p.C % m != 0) continue;
+      Plan q;
+      if (!snn_make_plan((int)strategy, T, strategy == SNN_HIER ? p.C / m : p.C, std::min(p.F * m, std::min(span, T)), &q)) continue;
+      q.n_chunk_bufs = p.n_chunk_bufs; q.n_cache_slots = p.n_cache_slots; q.keep_from = p.keep_from;
+      if (budget && (size_t)q.local_slots() * Ms + work_bytes(n, q.chunk_len) + spike_bytes(n, T, ring) > budget) continue;
+      p = q;
+      break;
     }
   }
   const size_t need_states = (size_t)p.local_slots() * Ms;
