@@ -13,6 +13,8 @@
 //     ascending) that does not depend on where chunk boundaries fall;
 //   * no floating-point atomics anywhere.
 #include "snn_internal.h"
+#include <algorithm>
+#include <cmath>
 #include <stdlib.h>
 #include <type_traits>
 #include <string.h>
@@ -2504,6 +2506,13 @@ k_adj_rec_rows(NetDev net, AdjJobs jobs, float *__restrict__ carry, int list_all
 // then finishes row r for the four batch elements and writes dv_t as one float4 into the exchange buffer
 // [parity][batch group][N][4]; a counting barrier per (job, batch group) -- the batch groups never wait for each
 // other -- and every workgroup reloads its group's slice into LDS.  Bounded spin and error flag as in k_adj_rec_ws.
+// Under a surrogate window (net.win > 0) a row is evaluated only if the potential of at least one of the four batch
+// elements is inside it -- the potentials of the wavefront's rows are in its lanes anyway, a ballot gives the set of
+// rows to visit, the potentials of the next step are loaded a step ahead so that its first row can still be requested
+// early -- and a neuron outside the window gets dv_t = alpha dv_{t+1}, whatever the sums are.
+// CH: groups of 64 entries requested per row.  Every group costs its LDS read and four FMAs per lane whether the row
+// has entries there or not, so the launcher takes the smallest instance that holds nearly every row in one pass.
+template <int CH>
 __global__ void __launch_bounds__(1024)
 k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, unsigned *bar, unsigned *err,
                unsigned spin_limit, int n_rb, int n_bg, int xg_stride, int lds_n) {
@@ -2592,7 +2601,8 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
   group_barrier();
   // Entries of a row through buffer loads whose range is the row: lane + 64 i past the end reads 0 (weight 0, column
   // 0) with no address arithmetic or compare in the vector unit.
-  constexpr int CH = 14, CH2 = 2; // groups of 64 entries per pass (both even: group k always meets accumulator k & 1)
+  static_assert(CH % 2 == 0, "group k always meets accumulator k & 1");
+  constexpr int CH2 = 2; // groups per further pass of a longer row (even as well)
   struct Row { float w[CH]; uint32_t c[CH]; };
   // (weight and index of an entry come as one 8-byte load from the packed copy of the rows, NetDev::csr_pk)
   auto fetch = [&](Row &r, uint32_t e0, uint32_t e1) {
@@ -2608,9 +2618,8 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
   // one row: its entries sit in `r` (requested a row ago); each pair of registers is reloaded with the next row's
   // entries right after its products, so one row buffer serves both rows
   Row r;
-  auto do_row = [&](int q) {
+  auto do_row = [&](int q, int qn) { // qn: the row after it (after the last one: the first row of the next step)
     const uint32_t e0 = __builtin_amdgcn_readlane(m0, q), e1 = __builtin_amdgcn_readlane(m1, q);
-    const int qn = q + 1 < nr ? q + 1 : 0; // after the last row: the first row of the next step
     const uint32_t n0 = __builtin_amdgcn_readlane(m0, qn), n1 = __builtin_amdgcn_readlane(m1, qn);
     const __amdgpu_buffer_rsrc_t np =
         __builtin_amdgcn_make_buffer_rsrc((void *)(pk + n0), 0, (int)((n1 - n0) * sizeof(uint64_t)), 0x00027000);
@@ -2659,23 +2668,53 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
                                     wave_sum_lane63(a0[2] + a1[2]), wave_sum_lane63(a0[3] + a1[3]));
     if (lane == 63) sums[q] = sum4; // read back by lane q of this wavefront when the step's rows are done
   };
-  if (nr > 0) fetch(r, __builtin_amdgcn_readlane(m0, 0), __builtin_amdgcn_readlane(m1, 0));
   const size_t slot_stride = (size_t)B * SN;
+  const bool windowed = net.win > 0.0f;
+  auto load_v = [&](int t, float (&v)[4]) {
+    const float *vr = vbuf + (size_t)(t - t_base - 1) * slot_stride + (size_t)(4 * bg) * SN + off + j;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = lane < nr && 4 * bg + c < B ? vr[(size_t)c * SN] : 0.0f;
+  };
+  auto inside = [&](float v) { return !windowed || fabsf(v - net.theta) < net.win; };
+  auto rows_to_visit = [&](const float (&v)[4]) -> uint64_t {
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) any |= 4 * bg + c < B && inside(v[c]);
+    return __ballot(lane < nr && any);
+  };
+  const uint64_t all_rows = nr >= 64 ? ~0ull : (1ull << nr) - 1ull;
+  float vt[4];
+  load_v(t1, vt);
+  uint64_t visit = windowed ? rows_to_visit(vt) : all_rows;
+  if (visit) {
+    const int q = __builtin_ctzll(visit);
+    fetch(r, __builtin_amdgcn_readlane(m0, q), __builtin_amdgcn_readlane(m1, q));
+  }
   unsigned step = 0;
   for (int t = t1; t > t0; --t, ++step) {
     const int wr = (int)(step & 1u);
     const size_t slot = (size_t)(t - t_base - 1);
-    float vt[4] = {0.0f, 0.0f, 0.0f, 0.0f}, upv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (lane < nr) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (4 * bg + c < B) {
-          vt[c] = vbuf[slot * slot_stride + (size_t)(4 * bg + c) * SN + off + j];
-          upv[c] = up[(slot * B + 4 * bg + c) * ldu + j];
-        }
-    }
-    for (int q = 0; q < nr; ++q) do_row(q);
     const bool last = t == t0 + 1;
+    float upv[4], vn[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) upv[c] = lane < nr && 4 * bg + c < B ? up[(slot * B + 4 * bg + c) * ldu + j] : 0.0f;
+    load_v(last ? t : t - 1, vn);
+    const bool skipped = visit == 0; // then nobody has requested the first row of the next step
+    while (visit) {
+      const int q = __builtin_ctzll(visit);
+      visit &= visit - 1;
+      if (!visit) {
+        const uint64_t next = windowed ? rows_to_visit(vn) : all_rows;
+        do_row(q, next ? __builtin_ctzll(next) : q);
+      } else {
+        do_row(q, __builtin_ctzll(visit));
+      }
+    }
+    visit = windowed ? rows_to_visit(vn) : all_rows;
+    if (skipped && visit) {
+      const int q = __builtin_ctzll(visit);
+      fetch(r, __builtin_amdgcn_readlane(m0, q), __builtin_amdgcn_readlane(m1, q));
+    }
     if (lane < nr) {
       const float4 dn4 = xs[j], my4 = sums[lane];
       const float dn[4] = {dn4.x, dn4.y, dn4.z, dn4.w}, mys[4] = {my4.x, my4.y, my4.z, my4.w};
@@ -2684,7 +2723,8 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
       for (int c = 0; c < 4; ++c) {
         const bool ok = 4 * bg + c < B;
         const float ds = (mys[c] + upv[c]) - net.theta * dn[c];
-        const float dvt = fmaf(ds, surrogate(net, vt[c]), net.alpha * dn[c]);
+        const float leak = net.alpha * dn[c];
+        const float dvt = inside(vt[c]) ? fmaf(ds, surrogate(net, vt[c]), leak) : leak;
         dv[c] = ok ? dvt : 0.0f;
         if (ok) {
           vbuf[slot * slot_stride + (size_t)(4 * bg + c) * SN + off + j] = dvt;
@@ -2695,6 +2735,8 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
         *reinterpret_cast<float4 *>(xq + (((size_t)wr * n_bg + bg) * N + j) * 4) = make_float4(dv[0], dv[1], dv[2], dv[3]);
     }
     if (last) break; // nobody reads the exchange buffer after the last step
+#pragma unroll
+    for (int c = 0; c < 4; ++c) vt[c] = vn[c];
     group_barrier();
     const uint32_t xbase = (uint32_t)((((size_t)wr * n_bg + bg) * N) * 4 * sizeof(float));
     for (int i0 = 0; i0 < N; i0 += 8 * 1024) {
@@ -4211,12 +4253,17 @@ static int adj_csrw_resident() {
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) != hipSuccess) return 0;
     const size_t lds = ((size_t)8192 + 16 * 64) * 4 * sizeof(float); // the widest layer the library takes + the row sums
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_csrw), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds) != hipSuccess)
-      return 0;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_adj_rec_csrw, 1024, lds) != hipSuccess) return 0;
-    cached[device] = per_cu * prop.multiProcessorCount;
+    int least = 1 << 20;
+    const void *const inst[] = {reinterpret_cast<const void *>(k_adj_rec_csrw<4>), reinterpret_cast<const void *>(k_adj_rec_csrw<8>),
+                                reinterpret_cast<const void *>(k_adj_rec_csrw<14>)};
+    for (const void *f : inst) {
+      int per_cu = 0;
+      if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 1024, lds) != hipSuccess)
+        return 0;
+      least = per_cu < least ? per_cu : least;
+    }
+    cached[device] = least * prop.multiProcessorCount;
     if (cached[device] <= 0) cached[device] = -1;
   }
   return cached[device] > 0 ? cached[device] : 0;
@@ -4232,6 +4279,16 @@ static bool adj_csrw_ok(const NetDev &net, int l, const WsArgs &ws) {
   if ((net.sel_adjoint != 0 && net.sel_adjoint < 6) || !net.csr_sub[l] || N <= 1024 || N > 8192 || B > 64 || !ws.xg) return false;
   if ((size_t)8 * ((B + 3) / 4) * N > (size_t)ws.xg_stride) return false;
   return adj_csrw_row_blocks(net, 1, N) > 0;
+}
+// Groups of 64 entries per row that k_adj_rec_csrw requests at once: the mean row of the longest job plus four times
+// the deviation of a random mask; longer rows take further passes.
+static int adj_csrw_groups(const NetDev &net, const AdjJobs &jobs) {
+  double most = 0.0;
+  for (int k = 0; k < jobs.count; ++k) {
+    const double mean = (double)net.csr_nnz[jobs.j[k].l] / net.N[jobs.j[k].l];
+    most = std::max(most, mean + 4.0 * std::sqrt(mean));
+  }
+  return most <= 4 * 64 ? 4 : most <= 8 * 64 ? 8 : 14;
 }
 // SNN_WS_KERNEL=stream keeps wide layers on the one-workgroup-per-batch-element kernel
 static bool adj_wide_ok(const NetDev &net, int l, const WsArgs &ws) {
@@ -4305,9 +4362,13 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
     const AdjJob &jb = jobs.j[i];
     const int l = jb.l, N = net.N[l];
     if (N <= 256 || taken[i]) continue;
-    // Event-driven rows under a surrogate window: layers wider than 1024 (the streamed kernels pay for every row
-    // of the matrix every step), or wherever the hook asks (3: listed rows, 4: the same kernel listing every row)
-    if (net.sel_adjoint == 3 || net.sel_adjoint == 4 || (net.sel_adjoint == 0 && net.win > 0.0f && N > 1024)) {
+    // Event-driven rows under a surrogate window: layers wider than 1024 whose matrix has no compressed rows (the
+    // streamed kernels pay for every row of the matrix every step; over compressed rows the chip-wide kernel skips
+    // rows itself and gives the same bits: 512-2x2048 at 10 % density, batch 16, window 0.5, 2000 steps: 123 -> 78 ms per
+    // training step), or wherever the hook asks (3: listed rows, 4: the same kernel
+    // listing every row)
+    if (net.sel_adjoint == 3 || net.sel_adjoint == 4 ||
+        (net.sel_adjoint == 0 && net.win > 0.0f && N > 1024 && !adj_csrw_ok(net, l, ws))) {
       AdjJobs grp{};
       for (int k = i; k < jobs.count; ++k)
         if (!taken[k] && net.N[jobs.j[k].l] == N) {
@@ -4406,7 +4467,9 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
       if (n_rb <= 0) return hipErrorInvalidValue;
       hipError_t e = launch_fill_zero(ws.bar, (size_t)64 * SNN_MAXL * sizeof(unsigned), s);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(k_adj_rec_csrw, dim3(grp.count * n_rb * n_bg), dim3(1024), ((size_t)n_max + 16 * 64) * 4 * sizeof(float),
+      const int groups = adj_csrw_groups(net, grp);
+      const auto kern = groups == 4 ? k_adj_rec_csrw<4> : groups == 8 ? k_adj_rec_csrw<8> : k_adj_rec_csrw<14>;
+      hipLaunchKernelGGL(kern, dim3(grp.count * n_rb * n_bg), dim3(1024), ((size_t)n_max + 16 * 64) * 4 * sizeof(float),
                          s, net, grp, carry, ws.xg, ws.bar, ws.err, ws.spin_limit, n_rb, n_bg, ws.xg_stride, n_max);
     } else if (adj_wide_ok(net, l, ws)) {
       taken[i] = true;

@@ -1074,6 +1074,36 @@ def test_event_driven_adjoint_under_the_surrogate_window(hidden, B, T, density, 
     assert all(0.0 < x < 0.5 for x in inside)
 
 
+@pytest.mark.parametrize("hidden,B,T,density,window", [
+    ((1100,), 5, 14, 0.1, 0.3),        # rows of 110 entries (4 groups of 64), a ragged batch group
+    ((2048, 1030), 9, 10, 0.2, 0.5),   # 410 and 206 entries (8 groups), two jobs, three batch groups
+    ((1536,), 4, 12, 0.5, 0.4),        # 768 entries (14 groups)
+    ((1088,), 3, 12, 0.15, 0.002),     # hardly any neuron inside: wavefronts and steps without a row to visit
+    ((1088,), 6, 12, 0.15, 50.0)])     # every neuron inside
+def test_chip_wide_adjoint_skips_rows_outside_the_window(hidden, B, T, density, window, monkeypatch):
+    """Masked layers above 1024 neurons run the chip-wide kernel over compressed rows under a window too: rows of which
+    no batch element of the group is inside are not evaluated, in instances for different row lengths.  A row is summed
+    in the order of the rows kernel, so the gradients must be that kernel's bits."""
+    w = synth.Workload("csrw_win_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=0.8,
+                       rec_density=density, seed=81 + B)
+    d = synth.generate(w)
+    got = {}
+    for mode in (None, "rows", "rows_all"):
+        monkeypatch.delenv("SNN_WS_KERNEL", raising=False)
+        if mode:
+            monkeypatch.setenv("SNN_WS_KERNEL", mode)
+        net = snn.from_workload(w, d, surr_window=window)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            net.snn_bptt(snn.SNN_DOUBLE, 8, 3)
+            got[mode] = _gpu_grads(net, len(hidden))
+            net.snn_bptt(snn.SNN_DOUBLE, 8, 3)  # the replayed graph
+            assert _identical(_gpu_grads(net, len(hidden)), got[mode]), mode
+        finally:
+            net.snn_destroy()
+    assert _identical(got[None], got["rows"]) and _identical(got[None], got["rows_all"])
+
+
 @pytest.mark.parametrize("hidden,B,T,tier_env,strategies", [
     ((256, 256), 4, 3000, "direct", [(2, 100, 0), (3, 200, 20)]),
     ((200, 300), 3, 2600, "dma", [(3, 150, 30), (2, 64, 0)]),
