@@ -620,6 +620,7 @@ struct CsrGroup { // the entries of U consecutive rows that fall into the wavefr
 };
 typedef __attribute__((address_space(3))) float lds_float;
 typedef unsigned int csr_u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int csr_u32x4 __attribute__((ext_vector_type(4)));
 // Requests the entries of rows q .. q + U - 1 of a block (positions and counts one row per lane in p0 / nn; q is a
 // constant after unrolling).  One 8-byte load per row from the packed copy (NetDev::csr_pk) through one descriptor
 // over the whole array: no scalar descriptor arithmetic per row (the compute unit's one scalar unit is what eight
@@ -1609,6 +1610,21 @@ __device__ __forceinline__ float surrogate(const NetDev &net, float v) {
   return (net.win > 0.0f && !(x < net.win)) ? 0.0f : g;
 }
 
+// Values that say by themselves that they have arrived: what travels between the workgroups of a chip-wide recurrence
+// is the complement of a float's bits, so that 0 -- what the launcher fills the exchange buffer with -- stands for
+// "not there yet" (the one float whose complement is 0, a NaN that no operation produces, travels as another NaN).
+// Values are 4 bytes and polled in loads of any width; there is no barrier: one store and one load round trip per
+// step, where a counting barrier has store, wait, atomic, poll and load.  The buffer holds four steps (step & 3):
+// in step s a thread writes its values, then clears the entries that it wrote in step s - 2.  Those have been read:
+// to get here its workgroup has read everyone's values of step s - 1, and who wrote those had read step s - 2.  And
+// the cleared entries are in memory (vmcnt(0)) before the thread writes its values of step s + 1, so who has read
+// those and looks for values of step s + 2 cannot meet the old ones.
+static __device__ __forceinline__ uint32_t xenc(float v) {
+  const uint32_t e = ~__float_as_uint(v);
+  return e != 0u ? e : ~0x7fc00000u;
+}
+static __device__ __forceinline__ float xdec(uint32_t e) { return __uint_as_float(~e); }
+
 // Recurrent part, layers of up to H*KH neurons: the recurrent matrix stays in registers for the
 // whole chunk.  Thread (jj, h) keeps W_rec[j][h*KH .. h*KH+KH) for the R postsynaptic rows
 // j = jj, jj + NJR, ..., jj + (R-1)*NJR (H threads per row, each a slice of the reduction; partial sums
@@ -2504,8 +2520,10 @@ k_adj_rec_rows(NetDev net, AdjJobs jobs, float *__restrict__ carry, int list_all
 // same bits as that kernel listing every row -- with all entries of the next row requested before the products of
 // the current one (the first row of the next step before the step's barrier: the matrix does not change).  Lane r
 // then finishes row r for the four batch elements and writes dv_t as one float4 into the exchange buffer
-// [parity][batch group][N][4]; a counting barrier per (job, batch group) -- the batch groups never wait for each
-// other -- and every workgroup reloads its group's slice into LDS.  Bounded spin and error flag as in k_adj_rec_ws.
+// [step & 3][batch group][N][4] (values encoded by xenc, see there: no barrier, the batch groups never wait for each
+// other), from where every workgroup reloads its group's slice into LDS: against a counting barrier per step two layers
+// of 2048 neurons go from 10.2 to about 6 us per step, four of 8192 from 115 to 112.  Polling is bounded and raises *err; the
+// counting barrier (bounded like k_adj_rec_ws's) is only met once, before the first step.
 // Under a surrogate window (net.win > 0) a row is evaluated only if the potential of at least one of the four batch
 // elements is inside it -- the potentials of the wavefront's rows are in its lanes anyway, a ballot gives the set of
 // rows to visit, the potentials of the next step are loaded a step ahead so that its first row can still be requested
@@ -2557,9 +2575,9 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
     m0 = sub[(size_t)j * nsub1];
     m1 = sub[(size_t)j * nsub1 + nsub1 - 1];
   }
-  float *xq = xg + (size_t)jq * xg_stride; // [2][n_bg][N][4]
+  float *xq = xg + (size_t)jq * xg_stride; // [4][n_bg][N][4]
   const __amdgpu_buffer_rsrc_t xres =
-      __builtin_amdgcn_make_buffer_rsrc((void *)xq, 0, (int)((size_t)2 * n_bg * N * 4 * sizeof(float)), 0x00027000);
+      __builtin_amdgcn_make_buffer_rsrc((void *)xq, 0, (int)((size_t)4 * n_bg * N * 4 * sizeof(float)), 0x00027000);
   unsigned *cnt = bar + 64 * jq + bg;
   bool dead = false;
   unsigned arrivals = 0;
@@ -2692,7 +2710,6 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
   }
   unsigned step = 0;
   for (int t = t1; t > t0; --t, ++step) {
-    const int wr = (int)(step & 1u);
     const size_t slot = (size_t)(t - t_base - 1);
     const bool last = t == t0 + 1;
     float upv[4], vn[4];
@@ -2731,27 +2748,57 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
           if (last) carry[(size_t)(4 * bg + c) * (SN + O) + off + j] = dvt; // dv_{t0+1}: every workgroup its own rows
         }
       }
-      if (!last)
-        *reinterpret_cast<float4 *>(xq + (((size_t)wr * n_bg + bg) * N + j) * 4) = make_float4(dv[0], dv[1], dv[2], dv[3]);
+      if (!last) {
+        const auto entry = [&](unsigned s) { return (uint32_t)((((size_t)(s & 3u) * n_bg + bg) * N + j) * 16u); };
+        __builtin_amdgcn_raw_buffer_store_b128(csr_u32x4{xenc(dv[0]), xenc(dv[1]), xenc(dv[2]), xenc(dv[3])}, xres, entry(step), 0, 17);
+        // nobody reads the values of two steps ago any more
+        __builtin_amdgcn_raw_buffer_store_b128(csr_u32x4{0u, 0u, 0u, 0u}, xres, entry(step + 2u), 0, 17); // sc0 sc1
+      }
     }
     if (last) break; // nobody reads the exchange buffer after the last step
 #pragma unroll
     for (int c = 0; c < 4; ++c) vt[c] = vn[c];
-    group_barrier();
-    const uint32_t xbase = (uint32_t)((((size_t)wr * n_bg + bg) * N) * 4 * sizeof(float));
-    for (int i0 = 0; i0 < N; i0 += 8 * 1024) {
-      float4 r[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u * 1024 + tid, ic = i < N ? i : N - 1;
-        r[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(xres, xbase + (uint32_t)ic * 16u, 0, 17)); // sc0 sc1
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u * 1024 + tid;
-        if (i < N) xs[i] = r[u];
-      }
+    __syncthreads(); // every wavefront has read its dv_{t+1} from LDS
+    // dv_t of the whole layer: a lane asks again only for entries that have not arrived
+    const uint32_t xbase = (uint32_t)((((size_t)(step & 3u) * n_bg + bg) * N) * 4 * sizeof(float));
+    if (spin_limit == 0u && !dead) { // only ever set by a test of this path: give up at once, arrived or not
+      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      dead = true;
     }
+    constexpr int UN = 4;
+    for (int i0 = tid; i0 < N; i0 += UN * 1024) {
+      csr_u32x4 x[UN];
+      uint32_t open = 0u;
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        x[u] = csr_u32x4{0u, 0u, 0u, 0u};
+        if (i0 + u * 1024 < N) open |= 1u << u;
+      }
+      const uint32_t mine = open;
+      unsigned spins = 0;
+      for (;;) {
+        asm volatile("" ::: "memory"); // every round reads again
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+          if (open >> u & 1u)
+            x[u] = __builtin_amdgcn_raw_buffer_load_b128(xres, xbase + (uint32_t)(i0 + u * 1024) * 16u, 0, 17); // sc0 sc1
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+          if (x[u].x != 0u && x[u].y != 0u && x[u].z != 0u && x[u].w != 0u) open &= ~(1u << u);
+        if (open == 0u || dead) break;
+        if (++spins > spin_limit / 8u ||
+            ((spins & 15u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          dead = true; // keep going to the end of the chunk, never wait again
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+        if (mine >> u & 1u) xs[i0 + u * 1024] = make_float4(xdec(x[u].x), xdec(x[u].y), xdec(x[u].z), xdec(x[u].w));
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the cleared entries are in memory before the next values go out
     __syncthreads();
   }
 }
@@ -4277,16 +4324,16 @@ static int adj_csrw_row_blocks(const NetDev &net, int count, int n_max) {
 static bool adj_csrw_ok(const NetDev &net, int l, const WsArgs &ws) {
   const int N = net.N[l], B = net.B;
   if ((net.sel_adjoint != 0 && net.sel_adjoint < 6) || !net.csr_sub[l] || N <= 1024 || N > 8192 || B > 64 || !ws.xg) return false;
-  if ((size_t)8 * ((B + 3) / 4) * N > (size_t)ws.xg_stride) return false;
+  if ((size_t)16 * ((B + 3) / 4) * N > (size_t)ws.xg_stride) return false;
   return adj_csrw_row_blocks(net, 1, N) > 0;
 }
-// Groups of 64 entries per row that k_adj_rec_csrw requests at once: the mean row of the longest job plus four times
+// Groups of 64 entries per row that k_adj_rec_csrw requests at once: the mean row of the longest job plus three times
 // the deviation of a random mask; longer rows take further passes.
 static int adj_csrw_groups(const NetDev &net, const AdjJobs &jobs) {
   double most = 0.0;
   for (int k = 0; k < jobs.count; ++k) {
     const double mean = (double)net.csr_nnz[jobs.j[k].l] / net.N[jobs.j[k].l];
-    most = std::max(most, mean + 4.0 * std::sqrt(mean));
+    most = std::max(most, mean + 3.0 * std::sqrt(mean));
   }
   return most <= 4 * 64 ? 4 : most <= 8 * 64 ? 8 : 14;
 }
@@ -4364,7 +4411,7 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
     if (N <= 256 || taken[i]) continue;
     // Event-driven rows under a surrogate window: layers wider than 1024 whose matrix has no compressed rows (the
     // streamed kernels pay for every row of the matrix every step; over compressed rows the chip-wide kernel skips
-    // rows itself and gives the same bits: 512-2x2048 at 10 % density, batch 16, window 0.5, 2000 steps: 123 -> 78 ms per
+    // rows itself and gives the same bits: 512-2x2048 at 10 % density, batch 16, window 0.5, 2000 steps: 123 -> 69 ms per
     // training step), or wherever the hook asks (3: listed rows, 4: the same kernel
     // listing every row)
     if (net.sel_adjoint == 3 || net.sel_adjoint == 4 ||
@@ -4465,7 +4512,9 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
       }
       const int n_bg = (B + 3) / 4, n_rb = adj_csrw_row_blocks(net, grp.count, n_max);
       if (n_rb <= 0) return hipErrorInvalidValue;
+      // counters and the jobs' exchange entries (which lie behind the counters and the error flag) start from zero
       hipError_t e = launch_fill_zero(ws.bar, (size_t)64 * SNN_MAXL * sizeof(unsigned), s);
+      if (e == hipSuccess) e = launch_fill_zero(ws.xg, (size_t)grp.count * ws.xg_stride * sizeof(float), s);
       if (e != hipSuccess) return e;
       const int groups = adj_csrw_groups(net, grp);
       const auto kern = groups == 4 ? k_adj_rec_csrw<4> : groups == 8 ? k_adj_rec_csrw<8> : k_adj_rec_csrw<14>;
