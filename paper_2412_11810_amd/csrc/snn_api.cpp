@@ -513,10 +513,10 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       // one exchange buffer and one set of 64 counters per job of a launch (layers of equal width that are one
       // tile apart share a launch), one error flag
       const size_t n_bar = (size_t)64 * SNN_MAXL + 16; // counters + error flag, padded to a multiple of 64 bytes
-      // (the kernel for layers wider than 1024 pads the batch to whole blocks of 16: 1, 2 or 4 of them)
-      const size_t bp = nmax > 1024 && B <= 64 ? (size_t)((B + 15) / 16 == 3 ? 4 : (B + 15) / 16) * 16 : (size_t)B;
-      const size_t xg_stride = ((size_t)4 * bp * nmax + 15) & ~(size_t)15; // [2][B][N] entries of 8 bytes (value + step tag)
-      // (+ 16 KB: readers of the tagged exchange address a row padded to 1024 entries of 8 bytes)
+      // (the batch in whole groups of 16; the kernel for layers wider than 1024 takes 1, 2 or 4 of them)
+      const size_t bp = nmax > 1024 && B <= 64 ? (size_t)((B + 15) / 16 == 3 ? 4 : (B + 15) / 16) * 16 : (size_t)((B + 15) / 16) * 16;
+      const size_t xg_stride = ((size_t)4 * bp * nmax + 15) & ~(size_t)15; // four steps of values in flight
+      // (+ 16 KB: the forward pass's exchange of spike words shares the buffer)
       const size_t bytes = n_bar * sizeof(unsigned) + (size_t)SNN_MAXL * xg_stride * 4 + 16384;
       void *blk = uncached_block(cfg->device, bytes);
       if (!blk) return fail(c, SNN_E_HIP, "uncached device allocation failed");
@@ -527,6 +527,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       c->ws.err = c->ws.bar + 64 * SNN_MAXL;
       c->ws.max_groups = ws_max_resident_groups(cfg->device);
       c->ws.max_groups_m = ws_max_resident_groups_mfma(cfg->device);
+      if (nmax > 1024) c->ws.max_groups_m8 = ws_max_resident_groups_mfma8(cfg->device);
       c->ws.spin_limit = 4000000u; // ~1 s of polling: far beyond any real wait
       if (const char *e = std::getenv("SNN_WS_SPIN_LIMIT")) c->ws.spin_limit = (unsigned)std::strtoul(e, nullptr, 10);
       adjoint_prepare(n, c->ws);

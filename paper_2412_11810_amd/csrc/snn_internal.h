@@ -150,12 +150,13 @@ hipError_t launch_loss(const double *readout, const int32_t *labels, int B, int 
 // Exchange buffer, barrier counters and error flag of the chip-wide weight-stationary recurrent
 // kernel (see k_adj_rec_ws); xg == NULL disables that kernel.
 struct WsArgs {
-  float *xg;           // SNN_MAXL x [2][B][max N_l], one per job of a launch
+  float *xg;           // SNN_MAXL x [4][B in whole groups of 16][max N_l], one per job of a launch
   int xg_stride;       // floats between the exchange buffers of two jobs
   unsigned *bar;       // SNN_MAXL x [64] counters, zeroed before every launch
   unsigned *err;       // raised if a barrier gave up waiting
   int max_groups;      // workgroups of that kernel that can be resident at once
   int max_groups_m;    // the same for its matrix-core version
+  int max_groups_m8;   // ... and for that one's instances for layers of 1025..2048 neurons
   unsigned spin_limit; // barrier polls before giving up
 };
 // One recurrence of the adjoint pass: layer l over steps t1, ..., t0+1 of a tile whose states sit in vbuf.
@@ -177,6 +178,7 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
                                const SpanHook *hook = nullptr);
 int ws_max_resident_groups(int device);
 int ws_max_resident_groups_mfma(int device);
+int ws_max_resident_groups_mfma8(int device);
 void adjoint_prepare(const NetDev &net, const WsArgs &ws); // occupancy queries of the wide-layer kernel, at init
 // dW[j][:] += sum over t = t1..t0+1 (descending), b ascending, of pre-spike(t - lag, b, j) * post(t, b, :)
 // where post(t) sits at slot (t - t_base - 1) of postbuf with row stride post_stride (floats per batch

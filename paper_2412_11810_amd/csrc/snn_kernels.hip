@@ -1889,13 +1889,17 @@ k_adj_rec_ws(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, uns
 }
 
 // The same chip-wide recurrence on the matrix cores.  Workgroup (js, bg) owns 32 postsynaptic rows x 16 batch
-// elements; wavefront q takes a quarter of the reduction range and, for each of the two 16-row blocks, keeps its
+// elements; wavefront q takes one of KS parts of the reduction range and, for each of the two 16-row blocks, keeps its
 // part of W_rec in registers as the A operands of NK K-steps (v_mfma_f32_16x16x4: A[i][k] in lane i + 16k).  The
 // B operand of a K-step is dv_{t+1} of 4 presynaptic neurons x 16 batch elements, read from LDS (batch-minor, so
 // the 64 lanes read 64 consecutive floats).  Per step a wavefront issues 2 NK MFMAs on two independent
 // accumulators and one LDS read per K-step, where the VALU version reads every dv value of 8 batch elements
-// once per thread and is bound by the LDS (about twice the time).  The four partial sums are combined in a
-// fixed order; exchange and barrier are those of k_adj_rec_ws.
+// once per thread and is bound by the LDS (about twice the time).  The KS partial sums are combined in a
+// fixed order.  KS = 4 up to 1024 neurons, 8 (two wavefronts per SIMD, 256 registers each) up to 2048.
+// Exchange: [step & 3][batch group][N][16], values encoded by xenc (no barrier, see there).  What a step costs beyond
+// its products is that every workgroup reads the N x 16 values of its group from uncached memory: they lie as LDS
+// wants them, 4 bytes each (with a step tag beside every
+// value, 8 bytes, three layers of 1024 neurons at batch 64 took 14.2 us per step, now 9.6; two of 512 at batch 16 5.7, now 5.1).
 // With NG = 2 a workgroup serves two batch groups of 16 with the same registers of W_rec, half a step apart: while
 // the values one group has just stored travel through the exchange buffer, the matrix cores work on the other
 // group, and the two round trips of a step no longer add to its products.  Half as many workgroups per layer also
@@ -1903,9 +1907,9 @@ k_adj_rec_ws(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, uns
 // With RH = 2 a workgroup has eight wavefronts and owns 64 rows (wavefront w: rows 32 (w / 4) .., quarter w % 4 of
 // the reduction range; two wavefronts per SIMD, 256 registers each): half as many workgroups read a batch group's
 // dv_t from the exchange buffer, which is what a step costs.
-template <int NK, int NG, int RH> // K-steps per wavefront and row block (padded width 16 NK); batch groups and 32-row halves per workgroup
-__global__ void __launch_bounds__(256 * RH) __attribute__((amdgpu_waves_per_eu(RH, RH))) // the weights must stay in registers
-k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, unsigned *bar, unsigned *err, int G_w,
+template <int NK, int NG, int RH, int KS = 4> // K-steps per wavefront and row block (padded width 4 KS NK); batch groups and 32-row halves per workgroup; parts of the reduction range
+__global__ void __launch_bounds__(64 * KS * RH) __attribute__((amdgpu_waves_per_eu(KS * RH / 4, KS * RH / 4))) // the weights must stay in registers
+k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, unsigned *err, int G_w,
               unsigned spin_limit, int blocks_per_job, int xg_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int jq = blockIdx.x / blocks_per_job, vb = blockIdx.x % blocks_per_job;
@@ -1913,74 +1917,89 @@ k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, un
   const int l = jb.l, t0 = jb.t0, t1 = jb.t1, t_base = jb.t_base, carry_init = jb.carry_init;
   float *__restrict__ vbuf = jb.vbuf;
   const float *__restrict__ up = jb.up;
-  // exchange entries: dv_t in the low half, the step count (from 1; the buffer is cleared before every launch)
-  // in the high half -- a reader polls the values it needs until they all carry the tag of the step
-  uint64_t *xq = reinterpret_cast<uint64_t *>(xg + (size_t)jq * xg_stride); // [2][B][N]
-  (void)bar;
   const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, O = net.n_out, ldu = N;
-  constexpr int NT = 256 * RH;
-  const int tid = threadIdx.x, lane = tid & 63, wv = (tid >> 6) & 3, rh = tid >> 8, li = lane & 15, lk = lane >> 4;
+  constexpr int NT = 64 * KS * RH;
+  const int tid = threadIdx.x, lane = tid & 63, wv = (tid >> 6) % KS, rh = (tid >> 6) / KS, li = lane & 15, lk = lane >> 4;
   const int bg = vb % G_w, js = vb / G_w; // G_w workgroups of NG batch groups each per 32 RH rows
   const int j0 = js * 32 * RH, jw = j0 + 32 * rh; // first row of the workgroup, of the wavefront
-  constexpr int NP = 16 * NK;                          // padded reduction length (>= N)
+  if (j0 >= N) return; // a job of a narrower layer than the widest of the launch: nobody waits for this workgroup
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(xg + (size_t)jq * xg_stride), 0, (int)((size_t)xg_stride * sizeof(float)), 0x00027000); // [4][G_w NG][N][16]
+  constexpr int NP = 4 * KS * NK;                      // padded reduction length (>= N)
   float *xs_all = (float *)smem;                       // [NG][NP][16]  dv_{t+1}, batch-minor
-  float *part_all = xs_all + (size_t)NG * NP * 16;     // [NG][RH][4][32][16]
+  float *part_all = xs_all + (size_t)NG * NP * 16;     // [NG][RH][KS][32][16]
 
-  // A operands: a[rb][s] = W_rec[j0 + 16 rb + li][4 NK wv + 4 s + lk].  Every load unconditional, from a clamped
-  // address, zeroed with an integer mask afterwards (a select lets the compiler put each load under its condition).
+  // dv_{t1+1} of the batch groups.  Here and below every load is unconditional, from a clamped address, and zeroed with
+  // an integer mask afterwards (a select lets the compiler put each load under its condition).
+  for (int g = 0; g < NG; ++g) {
+    const int b0 = (bg * NG + g) * 16;
+    constexpr int NR = 16; // of NP * 16 / NT values per thread, at a time
+    static_assert(NP * 16 / NT % NR == 0, "whole rounds");
+    for (int i0 = tid; i0 < NP * 16; i0 += NR * NT) {
+      float cv[NR];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int i = i0 + NT * r, n = i >> 4, bb = i & 15;
+        cv[r] = carry[(size_t)(b0 + bb < B ? b0 + bb : B - 1) * (SN + O) + off + (n < N ? n : N - 1)];
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int i = i0 + NT * r, n = i >> 4, bb = i & 15;
+        xs_all[(size_t)g * NP * 16 + i] =
+            __uint_as_float(__float_as_uint(cv[r]) & (0u - (uint32_t)(!carry_init && n < N && b0 + bb < B)));
+      }
+    }
+  }
+  // A operands: a[rb][s] = W_rec[j0 + 16 rb + li][4 NK wv + 4 s + lk]
   float a[2][NK];
+  const __amdgpu_buffer_rsrc_t wres =
+      __builtin_amdgcn_make_buffer_rsrc((void *)net.W_recT[l], 0, (int)((size_t)N * N * sizeof(float)), 0x00027000);
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
     const int j = jw + 16 * rb + li, jc = j < N ? j : N - 1;
 #pragma unroll
     for (int q = 0; q < NK; ++q) {
       const int n = 4 * NK * wv + 4 * q + lk, nc = n < N ? n : N - 1;
-      a[rb][q] = net.W_recT[l][(size_t)nc * N + jc]; // = W_rec[j][n]
+      a[rb][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, (uint32_t)(nc * N + jc) * 4u, 0, 0)); // = W_rec[j][n]
+      if (q % 16 == 15) __builtin_amdgcn_sched_barrier(0); // no more addresses at a time than the registers hold
     }
+  }
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+    const int j = jw + 16 * rb + li;
 #pragma unroll
     for (int q = 0; q < NK; ++q)
       a[rb][q] = __uint_as_float(__float_as_uint(a[rb][q]) & (0u - (uint32_t)(j < N && 4 * NK * wv + 4 * q + lk < N)));
   }
-  // dv_{t1+1} of the batch groups
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    const int b0 = (bg * NG + g) * 16;
-    float cv[NK / RH];
-#pragma unroll
-    for (int r = 0; r < NK / RH; ++r) {
-      const int i = tid + NT * r, n = i >> 4, bb = i & 15;
-      cv[r] = carry[(size_t)(b0 + bb < B ? b0 + bb : B - 1) * (SN + O) + off + (n < N ? n : N - 1)];
-    }
-#pragma unroll
-    for (int r = 0; r < NK / RH; ++r) {
-      const int i = tid + NT * r, n = i >> 4, bb = i & 15;
-      xs_all[(size_t)g * NP * 16 + i] =
-          __uint_as_float(__float_as_uint(cv[r]) & (0u - (uint32_t)(!carry_init && n < N && b0 + bb < B)));
-    }
-  }
   __syncthreads();
-  // finalising role: 32 RH x 16 (row, batch element) pairs per group, two per thread
-  int fj[2], fbb[2];
+  // finalising role: 32 RH x 16 (row, batch element) pairs per group, NE per thread
+  constexpr int NE = 8 / KS;
+  int fj[NE], fbb[NE];
+  float dprev[NG][NE]; // dv_{t+1} of the pairs
 #pragma unroll
-  for (int e = 0; e < 2; ++e) {
+  for (int e = 0; e < NE; ++e) {
     const int pidx = tid + NT * e;
     fj[e] = j0 + (pidx >> 4);
     fbb[e] = pidx & 15;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) dprev[g][e] = fj[e] < NP ? xs_all[((size_t)g * NP + fj[e]) * 16 + fbb[e]] : 0.0f;
   }
   const size_t slot_stride = (size_t)B * SN;
+  // byte offset of the values of a step and a group of this workgroup in the exchange buffer
+  auto x_base = [&](int g, unsigned step) { return (uint32_t)(((size_t)(step & 3u) * (G_w * NG) + bg * NG + g) * N * 64u); };
   bool dead = false;
-  // one step of one batch group: products, the sum of the four partial results, the recurrence, the exchange stores
+  // one step of one batch group: products, the sum of the partial results, the recurrence, the exchange stores
   auto compute = [&](int g, unsigned step, int t) {
     const int b0 = (bg * NG + g) * 16;
-    float *xs = xs_all + (size_t)g * NP * 16, *part = part_all + (size_t)g * RH * 4 * 32 * 16;
+    float *xs = xs_all + (size_t)g * NP * 16, *part = part_all + (size_t)g * RH * KS * 32 * 16;
     const size_t slot = (size_t)(t - t_base - 1);
-    float vt[2] = {0.0f, 0.0f}, upv[2] = {0.0f, 0.0f};
+    float vt[NE], upv[NE];
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-      if (fj[e] < N && b0 + fbb[e] < B) {
-        vt[e] = vbuf[slot * slot_stride + (size_t)(b0 + fbb[e]) * SN + off + fj[e]];
-        upv[e] = up[(slot * B + b0 + fbb[e]) * ldu + fj[e]];
-      }
+    for (int e = 0; e < NE; ++e) {
+      const bool ok = fj[e] < N && b0 + fbb[e] < B;
+      vt[e] = ok ? vbuf[slot * slot_stride + (size_t)(b0 + fbb[e]) * SN + off + fj[e]] : 0.0f;
+      upv[e] = ok ? up[(slot * B + b0 + fbb[e]) * ldu + fj[e]] : 0.0f;
+    }
     v4f acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
     const float *xb = xs + (size_t)(4 * NK * wv + lk) * 16 + li;
 #pragma unroll
@@ -1992,58 +2011,59 @@ k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, un
     // D[4 lk + r][li]: row 4 lk + r of the block, batch element li
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      part[((size_t)(4 * rh + wv) * 32 + 4 * lk + r) * 16 + li] = acc0[r];
-      part[((size_t)(4 * rh + wv) * 32 + 16 + 4 * lk + r) * 16 + li] = acc1[r];
+      part[((size_t)(KS * rh + wv) * 32 + 4 * lk + r) * 16 + li] = acc0[r];
+      part[((size_t)(KS * rh + wv) * 32 + 16 + 4 * lk + r) * 16 + li] = acc1[r];
     }
-    __syncthreads();
-    const int par = step & 1;
+    __syncthreads(); // from here on nobody reads dv_{t+1} of this group in LDS
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-      if (fj[e] < N && b0 + fbb[e] < B) {
+    for (int e = 0; e < NE; ++e)
+      if (fj[e] < N) {
         const int fr = (fj[e] - j0) & 31, fh = (fj[e] - j0) >> 5, fb = b0 + fbb[e];
-        float sacc = part[((size_t)(4 * fh) * 32 + fr) * 16 + fbb[e]];
+        float sacc = part[((size_t)(KS * fh) * 32 + fr) * 16 + fbb[e]];
 #pragma unroll
-        for (int k = 1; k < 4; ++k) sacc = sacc + part[((size_t)(4 * fh + k) * 32 + fr) * 16 + fbb[e]];
-        const float dn = xs[(size_t)fj[e] * 16 + fbb[e]];
+        for (int k = 1; k < KS; ++k) sacc = sacc + part[((size_t)(KS * fh + k) * 32 + fr) * 16 + fbb[e]];
+        const float dn = dprev[g][e];
         const float ds = (sacc + upv[e]) - net.theta * dn;
-        const float dvt = fmaf(ds, surrogate(net, vt[e]), net.alpha * dn);
-        vbuf[slot * slot_stride + (size_t)fb * SN + off + fj[e]] = dvt;
-        __hip_atomic_store(&xq[((size_t)par * B + fb) * N + fj[e]],
-                           ((uint64_t)(step + 1u) << 32) | (uint64_t)__float_as_uint(dvt), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        const float dvt = fb < B ? fmaf(ds, surrogate(net, vt[e]), net.alpha * dn) : 0.0f;
+        if (fb < B) vbuf[slot * slot_stride + (size_t)fb * SN + off + fj[e]] = dvt;
+        dprev[g][e] = dvt;
+        const uint32_t at = (uint32_t)(fj[e] * 16 + fbb[e]) * 4u;
+        __builtin_amdgcn_raw_buffer_store_b32(xenc(dvt), xres, x_base(g, step) + at, 0, 17); // sc0 sc1
+        __builtin_amdgcn_raw_buffer_store_b32(0u, xres, x_base(g, step + 2u) + at, 0, 17);  // nobody reads these any more
       }
   };
-  // dv_t of the whole layer for one batch group -> LDS.  No barrier: the values themselves say when they have
-  // arrived.  One store and one load round trip per step instead of store, wait, atomic, poll, load.  The polling
-  // is bounded like the barrier of k_adj_rec_ws: a thread that gives up raises *err, and from then on nobody waits.
+  // dv_t of the whole layer for one batch group -> LDS; a lane asks again only for values that have not arrived.  The
+  // polling is bounded like the barrier of k_adj_rec_ws: a thread that gives up raises *err, and from then on nobody
+  // waits.
   auto poll = [&](int g, unsigned step) {
-    const int b0 = (bg * NG + g) * 16, par = step & 1;
-    float *xs = xs_all + (size_t)g * NP * 16;
-    // thread -> batch element tid / (16 RH), columns tid % (16 RH) + 16 RH i: all loads of a round issued before
-    // the first use.  One base address for all of them, the column in the constant offset: entries past the layer's
-    // width read whatever follows (the buffer has 16 KB of slack behind its last row) and are neither waited for
-    // nor used.
-    constexpr int NB = 16 * RH, NE = NK / RH; // lanes along the row, entries per thread
-    const int bb = tid / NB, nb = tid % NB;
-    const uint64_t *src = xq + ((size_t)par * B + (b0 + bb < B ? b0 + bb : B - 1)) * N + nb;
-    const uint32_t want = step + 1u;
+    float4 *xs = reinterpret_cast<float4 *>(xs_all + (size_t)g * NP * 16);
+    const uint32_t base = x_base(g, step);
     if (spin_limit == 0u && !dead) { // only ever set by a test of this path: give up at once, arrived or not
       __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       dead = true;
     }
-    constexpr int CH = RH == 2 ? NE / 2 : (NE < 32 ? NE : 32); // values polled at a time: a round that comes too early is read again
+    constexpr int NL = NP * 4 / NT, UN = NL < 8 ? NL : 8; // 16-byte loads per thread, in flight at a time
 #pragma unroll
-    for (int c = 0; c < NE; c += CH) {
-      uint64_t r[CH];
+    for (int c = 0; c < NL; c += UN) {
+      csr_u32x4 x[UN];
+      uint32_t open = 0u;
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        x[u] = csr_u32x4{0u, 0u, 0u, 0u};
+        if (tid + NT * (c + u) < 4 * N) open |= 1u << u;
+      }
+      const uint32_t mine = open;
       unsigned spins = 0;
       for (;;) {
-        uint32_t bad = 0;
+        asm volatile("" ::: "memory"); // every round reads again
 #pragma unroll
-        for (int i = 0; i < CH; ++i) // agent-scope loads: never served from this compute unit's L1
-          r[i] = __hip_atomic_load(&src[NB * (c + i)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int u = 0; u < UN; ++u)
+          if (open >> u & 1u)
+            x[u] = __builtin_amdgcn_raw_buffer_load_b128(xres, base + (uint32_t)(tid + NT * (c + u)) * 16u, 0, 17); // sc0 sc1
 #pragma unroll
-        for (int i = 0; i < CH; ++i) bad |= ((uint32_t)(r[i] >> 32) ^ want) & (0u - (uint32_t)(nb + NB * (c + i) < N));
-        if (bad == 0u || dead) break;
+        for (int u = 0; u < UN; ++u)
+          if (x[u].x != 0u && x[u].y != 0u && x[u].z != 0u && x[u].w != 0u) open &= ~(1u << u);
+        if (open == 0u || dead) break;
         if (++spins > spin_limit / 8u ||
             ((spins & 15u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
           __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2053,11 +2073,10 @@ k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, un
         __builtin_amdgcn_s_sleep(1);
       }
 #pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        const int n = nb + NB * (c + i);
-        xs[(size_t)n * 16 + bb] = __uint_as_float((uint32_t)r[i] & (0u - (uint32_t)(n < N && b0 + bb < B)));
-      }
+      for (int u = 0; u < UN; ++u)
+        if (mine >> u & 1u) xs[tid + NT * (c + u)] = make_float4(xdec(x[u].x), xdec(x[u].y), xdec(x[u].z), xdec(x[u].w));
     }
+    __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the cleared entries are in memory before the next values go out
   };
   unsigned step = 0;
   for (int t = t1; t > t0; --t, ++step) {
@@ -2069,22 +2088,19 @@ k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, un
       __syncthreads();
       compute(1, step, t);
     }
-    __syncthreads(); // every thread has read its dv_{t+1} of the first group from LDS
-    poll(0, step);
+    // the values of the last step stay with their owners; a launch of one step waits all the same: everyone has read
+    // the carry when its values arrive, and only then may it be overwritten below
+    if (t > t0 + 1 || step == 0u) poll(0, step);
     __syncthreads();
   }
-  if (NG == 2) {
-    poll(1, step - 1u);
-    __syncthreads();
-  }
+  if (NG == 2 && step == 1u) poll(1, 0u);
   // carry out dv_{t0+1}: every workgroup writes its own rows
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     const int b0 = (bg * NG + g) * 16;
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-      if (fj[e] < N && b0 + fbb[e] < B)
-        carry[(size_t)(b0 + fbb[e]) * (SN + O) + off + fj[e]] = xs_all[(size_t)g * NP * 16 + (size_t)fj[e] * 16 + fbb[e]];
+    for (int e = 0; e < NE; ++e)
+      if (fj[e] < N && b0 + fbb[e] < B) carry[(size_t)(b0 + fbb[e]) * (SN + O) + off + fj[e]] = dprev[g][e];
   }
 }
 
@@ -2522,7 +2538,7 @@ k_adj_rec_rows(NetDev net, AdjJobs jobs, float *__restrict__ carry, int list_all
 // then finishes row r for the four batch elements and writes dv_t as one float4 into the exchange buffer
 // [step & 3][batch group][N][4] (values encoded by xenc, see there: no barrier, the batch groups never wait for each
 // other), from where every workgroup reloads its group's slice into LDS: against a counting barrier per step two layers
-// of 2048 neurons go from 10.2 to about 6 us per step, four of 8192 from 115 to 112.  Polling is bounded and raises *err; the
+// of 2048 neurons (batch 16, window 0.5) go from 10.2 to 5.2 us per step, four of 8192 (batch 32) from 124 to 118.  Polling is bounded and raises *err; the
 // counting barrier (bounded like k_adj_rec_ws's) is only met once, before the first step.
 // Under a surrogate window (net.win > 0) a row is evaluated only if the potential of at least one of the four batch
 // elements is inside it -- the potentials of the wavefront's rows are in its lanes anyway, a ballot gives the set of
@@ -4327,6 +4343,17 @@ static bool adj_csrw_ok(const NetDev &net, int l, const WsArgs &ws) {
   if ((size_t)16 * ((B + 3) / 4) * N > (size_t)ws.xg_stride) return false;
   return adj_csrw_row_blocks(net, 1, N) > 0;
 }
+// K-steps per wavefront of k_adj_rec_wsm by layer width: fixed by the width alone, since the reduction range is cut there
+static int wsm_size_class(int N) { return N <= 512 ? 32 : N <= 1024 ? 64 : N <= 1536 ? 48 : 64; }
+// Layers of 1025..2048 neurons whose matrix is dense-stored: its parts fit the registers of the chip, one workgroup per
+// compute unit, as long as the layer has no more of them than can be resident at once.  300-1500-1100
+// at batch 24, T = 150: 45.2 ms per step with one workgroup per batch element streaming the matrix (k_adj_rec_stream, what
+// widths that are no multiple of 64 ran), 7.8 so.
+static bool adj_wsm_wide_ok(const NetDev &net, int l, const WsArgs &ws) {
+  const int N = net.N[l], B = net.B;
+  if (net.sel_adjoint == 2 || N <= 1024 || N > 2048 || !ws.xg || adj_csrw_ok(net, l, ws)) return false;
+  return ((N + 31) / 32) * ((B + 15) / 16) <= ws.max_groups_m8;
+}
 // Groups of 64 entries per row that k_adj_rec_csrw requests at once: the mean row of the longest job plus three times
 // the deviation of a random mask; longer rows take further passes.
 static int adj_csrw_groups(const NetDev &net, const AdjJobs &jobs) {
@@ -4431,51 +4458,65 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
       hipLaunchKernelGGL(k_adj_rec_rows, dim3(B, grp.count), dim3(1024), lds, s, net, grp, carry, net.sel_adjoint == 4 ? 1 : 0);
       continue;
     }
-    if (N <= 1024 && ws.xg && ws_use_mfma(net) && (B + 15) / 16 <= 64 && ((N + 31) / 32) * ((B + 15) / 16) <= ws.max_groups_m) {
+    const bool wsm_wide = N > 1024; // 8 parts of the reduction range
+    if (ws.xg && ws_use_mfma(net) && (wsm_wide ? adj_wsm_wide_ok(net, l, ws)
+                                               : (B + 15) / 16 <= 64 && ((N + 31) / 32) * ((B + 15) / 16) <= ws.max_groups_m)) {
       // matrix-core version: workgroup = 32 rows x 16 batch elements, or x 2 groups of 16 half a step apart (two
       // groups per workgroup double the products a workgroup runs one after the other per step and halve the
       // workgroups per layer; only where net.sel_adjoint == 8 asks and the batch has an even number of groups;
       // 7 keeps 32 rows and one group per workgroup).
-      const int G_b = (B + 15) / 16;
+      const int G_b = (B + 15) / 16, limit = wsm_wide ? ws.max_groups_m8 : ws.max_groups_m;
+      // Layers of one size class (the same padded reduction range, which fixes the order of a sum) share a launch as
+      // far as all their workgroups can be resident at once
+      const int NK = wsm_size_class(N);
+      AdjJobs cls{};
+      int cls_at[SNN_MAXL], n_max = 0;
+      for (int k = i; k < jobs.count; ++k) {
+        const int Nk = net.N[jobs.j[k].l];
+        if (taken[k] || Nk <= 256 || (Nk > 1024) != wsm_wide || wsm_size_class(Nk) != NK) continue;
+        if (wsm_wide ? !adj_wsm_wide_ok(net, jobs.j[k].l, ws) : ((Nk + 31) / 32) * G_b > limit) continue;
+        cls_at[cls.count] = k;
+        cls.j[cls.count++] = jobs.j[k];
+        n_max = Nk > n_max ? Nk : n_max;
+      }
       // Workgroups of eight wavefronts and 64 rows (RH = 2) halve the workgroups per layer as well, and with them
       // the reads of the exchange buffer, at one batch group per workgroup: measured faster than two groups where
       // the stage's layers do not fit one launch otherwise (configuration 2: 147 against 171 ms per step), slower
       // where they do (configuration 3: 36 against 28 ms: few workgroups, each with twice the products per step).
       // net.sel_adjoint == 9 forces them.
-      int cnt = 0;
-      for (int k = i; k < jobs.count; ++k)
-        if (!taken[k] && net.N[jobs.j[k].l] == N) ++cnt;
-      const int per1 = ((N + 31) / 32) * G_b, cap1 = ws.max_groups_m / per1;
+      const int cap1 = limit / (((n_max + 31) / 32) * G_b);
       const bool plain = net.sel_adjoint == 7 || net.sel_adjoint == 8;
-      const int RH = (net.sel_adjoint == 9 || (!plain && cap1 >= 1 && cnt > cap1)) ? 2 : 1;
-      const int NG = (G_b % 2 == 0 && net.sel_adjoint == 8) ? 2 : 1;
-      const int G_w = G_b / NG, n_slices = (N + 32 * RH - 1) / (32 * RH), bpj = n_slices * G_w;
-      const int NK = N <= 512 ? 32 : 64;
-      const size_t lds = (size_t)NG * ((size_t)16 * NK * 16 + RH * 4 * 32 * 16) * sizeof(float);
+      const int RH = !wsm_wide && (net.sel_adjoint == 9 || (!plain && cap1 >= 1 && cls.count > cap1)) ? 2 : 1;
+      const int NG = !wsm_wide && G_b % 2 == 0 && net.sel_adjoint == 8 ? 2 : 1;
+      const int KS = wsm_wide ? 8 : 4;
+      const int G_w = G_b / NG, bpj = (n_max + 32 * RH - 1) / (32 * RH) * G_w;
+      const size_t lds = (size_t)NG * ((size_t)4 * KS * NK * 16 + RH * KS * 32 * 16) * sizeof(float);
       AdjJobs grp{};
-      for (int k = i; k < jobs.count; ++k)
-        if (!taken[k] && net.N[jobs.j[k].l] == N && (grp.count + 1) * bpj <= ws.max_groups_m) {
-          grp.j[grp.count++] = jobs.j[k];
-          taken[k] = true;
+      for (int k = 0; k < cls.count; ++k)
+        if (grp.count == 0 || (grp.count + 1) * bpj <= limit) {
+          grp.j[grp.count++] = cls.j[k];
+          taken[cls_at[k]] = true;
         }
-      // tags of the exchange entries start from zero in every launch
+      // the exchange entries start from zero in every launch
       hipError_t e = launch_fill_zero(ws.xg, (size_t)grp.count * ws.xg_stride * sizeof(float), s);
       if (e != hipSuccess) return e;
-      const dim3 grid(bpj * grp.count), block(256 * RH);
-#define WSM_CASE(NK_, NG_, RH_)                                                                                         \
+      const dim3 grid(bpj * grp.count), block(64 * KS * RH);
+#define WSM_CASE(NK_, NG_, RH_, KS_)                                                                                    \
   {                                                                                                                     \
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_wsm<NK_, NG_, RH_>),                               \
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_wsm<NK_, NG_, RH_, KS_>),                          \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                      \
     if (e != hipSuccess) return e;                                                                                      \
-    hipLaunchKernelGGL((k_adj_rec_wsm<NK_, NG_, RH_>), grid, block, lds, s, net, grp, carry, ws.xg, ws.bar, ws.err,     \
-                       G_w, ws.spin_limit, bpj, ws.xg_stride);                                                          \
+    hipLaunchKernelGGL((k_adj_rec_wsm<NK_, NG_, RH_, KS_>), grid, block, lds, s, net, grp, carry, ws.xg, ws.err, G_w,   \
+                       ws.spin_limit, bpj, ws.xg_stride);                                                               \
   }
-      if (RH == 2) {
-        if (NK == 32) WSM_CASE(32, 1, 2) else WSM_CASE(64, 1, 2)
+      if (wsm_wide) {
+        if (NK == 48) WSM_CASE(48, 1, 1, 8) else WSM_CASE(64, 1, 1, 8)
+      } else if (RH == 2) {
+        if (NK == 32) WSM_CASE(32, 1, 2, 4) else WSM_CASE(64, 1, 2, 4)
       } else if (NK == 32) {
-        if (NG == 1) WSM_CASE(32, 1, 1) else WSM_CASE(32, 2, 1)
+        if (NG == 1) WSM_CASE(32, 1, 1, 4) else WSM_CASE(32, 2, 1, 4)
       } else {
-        if (NG == 1) WSM_CASE(64, 1, 1) else WSM_CASE(64, 2, 1)
+        if (NG == 1) WSM_CASE(64, 1, 1, 4) else WSM_CASE(64, 2, 1, 4)
       }
 #undef WSM_CASE
     } else if (N <= 1024 && ws.xg && (B + 7) / 8 <= 64 && ((N + 31) / 32) * ((B + 7) / 8) <= ws.max_groups) {
@@ -4555,6 +4596,18 @@ int ws_max_resident_groups_mfma(int device) {
                           (int)lds) != hipSuccess)
     return 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_adj_rec_wsm<64, 2, 1>, 256, lds) != hipSuccess) return 0;
+  return per_cu * prop.multiProcessorCount;
+}
+
+int ws_max_resident_groups_mfma8(int device) { // the instances for layers of 1025..2048 neurons
+  hipDeviceProp_t prop;
+  if (hipGetDeviceProperties(&prop, device) != hipSuccess) return 0;
+  int per_cu = 0;
+  const size_t lds = ((size_t)2048 * 16 + 8 * 32 * 16) * sizeof(float);
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_wsm<64, 1, 1, 8>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)lds) != hipSuccess)
+    return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_adj_rec_wsm<64, 1, 1, 8>, 512, lds) != hipSuccess) return 0;
   return per_cu * prop.multiProcessorCount;
 }
 

@@ -301,6 +301,32 @@ def test_chip_wide_adjoint_two_batch_groups_per_workgroup(hidden, B, T, monkeypa
     monkeypatch.delenv("SNN_WS_KERNEL")
 
 
+@pytest.mark.parametrize("hidden,B,T", [
+    ((1025,), 3, 9),                   # one row in the last workgroup, a ragged batch group
+    ((1500, 1100), 20, 10),            # both of the 1536 class in one launch, surplus workgroups of the narrower one
+    ((1537, 1536), 17, 7),             # the two classes
+    ((2048,), 64, 5), ((2047,), 16, 1),  # one workgroup per compute unit; a single step
+    ((1000, 700, 300), 18, 11)])       # 513..1024 neurons: two widths in one launch beside another class
+def test_chip_wide_adjoint_any_width_up_to_2048(hidden, B, T, monkeypatch):
+    """Dense-stored recurrent matrices of up to 2048 neurons stay in the registers of the chip, whatever the width; layers
+    of one size class share a launch.  Against the oracle and the kernel with one workgroup per batch element, bit-identical
+    between strategies (chunks of one step among them)."""
+    w = synth.Workload("wsm_" + "x".join(map(str, hidden)), 40, hidden, 7, T=T, B=B, p_in=0.1, gain=0.6, seed=91 + B)
+    first, _ = _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 1), (snn.SNN_DOUBLE, min(T, 6), 1 if T == 1 else 3)],
+                            nthreads=8, check_states=False)
+    monkeypatch.setenv("SNN_WS_KERNEL", "stream")
+    net = snn.from_workload(w, d := synth.generate(w))
+    try:
+        net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+        net.snn_bptt(snn.SNN_STANDARD, 0, 0)
+        other = _gpu_grads(net, len(hidden))
+    finally:
+        net.snn_destroy()
+    flat = lambda g: list(g[0]) + list(g[1]) + [g[2]]
+    for a, b in zip(flat(first), flat(other)):  # sums of 1025..2048 products in two orders: a few 1e-7 of the largest
+        assert float(np.max(np.abs(a - b))) <= 2e-5 * (float(np.max(np.abs(b))) or 1.0)
+
+
 @pytest.mark.parametrize("hidden,B,T", [((1088,), 5, 14), ((1152, 1088), 20, 10), ((1088,), 40, 8), ((4096,), 3, 9)])
 def test_streamed_chip_wide_adjoint(hidden, B, T, monkeypatch):
     """Layers wider than 1024 neurons: the recurrence of the adjoint streams W_rec once per step for the whole
