@@ -1899,7 +1899,7 @@ k_adj_rec_ws(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, uns
 // Exchange: [step & 3][batch group][N][16], values encoded by xenc (no barrier, see there).  What a step costs beyond
 // its products is that every workgroup reads the N x 16 values of its group from uncached memory: they lie as LDS
 // wants them, 4 bytes each (with a step tag beside every
-// value, 8 bytes, three layers of 1024 neurons at batch 64 took 14.2 us per step, now 9.6; two of 512 at batch 16 5.7, now 5.1).
+// value, 8 bytes, three layers of 1024 neurons at batch 64 took 14.2 us per step, now 9.1; two of 512 at batch 16 5.7, now 4.8).
 // With NG = 2 a workgroup serves two batch groups of 16 with the same registers of W_rec, half a step apart: while
 // the values one group has just stored travel through the exchange buffer, the matrix cores work on the other
 // group, and the two round trips of a step no longer add to its products.  Half as many workgroups per layer also
@@ -1988,18 +1988,26 @@ k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, un
   // byte offset of the values of a step and a group of this workgroup in the exchange buffer
   auto x_base = [&](int g, unsigned step) { return (uint32_t)(((size_t)(step & 3u) * (G_w * NG) + bg * NG + g) * N * 64u); };
   bool dead = false;
+  // v_t and the inter-layer product of the pairs: requested a step ahead, behind the exchange stores, so that they arrive
+  // while the exchange is polled
+  float vt[NG][NE], upv[NG][NE];
+  auto load_operands = [&](int g, int t) {
+    const size_t slot = (size_t)(t - t_base - 1);
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int fb = (bg * NG + g) * 16 + fbb[e];
+      const bool ok = fj[e] < N && fb < B;
+      vt[g][e] = ok ? vbuf[slot * slot_stride + (size_t)fb * SN + off + fj[e]] : 0.0f;
+      upv[g][e] = ok ? up[(slot * B + fb) * ldu + fj[e]] : 0.0f;
+    }
+  };
+#pragma unroll
+  for (int g = 0; g < NG; ++g) load_operands(g, t1);
   // one step of one batch group: products, the sum of the partial results, the recurrence, the exchange stores
   auto compute = [&](int g, unsigned step, int t) {
     const int b0 = (bg * NG + g) * 16;
     float *xs = xs_all + (size_t)g * NP * 16, *part = part_all + (size_t)g * RH * KS * 32 * 16;
     const size_t slot = (size_t)(t - t_base - 1);
-    float vt[NE], upv[NE];
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const bool ok = fj[e] < N && b0 + fbb[e] < B;
-      vt[e] = ok ? vbuf[slot * slot_stride + (size_t)(b0 + fbb[e]) * SN + off + fj[e]] : 0.0f;
-      upv[e] = ok ? up[(slot * B + b0 + fbb[e]) * ldu + fj[e]] : 0.0f;
-    }
     v4f acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
     const float *xb = xs + (size_t)(4 * NK * wv + lk) * 16 + li;
 #pragma unroll
@@ -2023,14 +2031,15 @@ k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, un
 #pragma unroll
         for (int k = 1; k < KS; ++k) sacc = sacc + part[((size_t)(KS * fh + k) * 32 + fr) * 16 + fbb[e]];
         const float dn = dprev[g][e];
-        const float ds = (sacc + upv[e]) - net.theta * dn;
-        const float dvt = fb < B ? fmaf(ds, surrogate(net, vt[e]), net.alpha * dn) : 0.0f;
+        const float ds = (sacc + upv[g][e]) - net.theta * dn;
+        const float dvt = fb < B ? fmaf(ds, surrogate(net, vt[g][e]), net.alpha * dn) : 0.0f;
         if (fb < B) vbuf[slot * slot_stride + (size_t)fb * SN + off + fj[e]] = dvt;
         dprev[g][e] = dvt;
         const uint32_t at = (uint32_t)(fj[e] * 16 + fbb[e]) * 4u;
         __builtin_amdgcn_raw_buffer_store_b32(xenc(dvt), xres, x_base(g, step) + at, 0, 17); // sc0 sc1
         __builtin_amdgcn_raw_buffer_store_b32(0u, xres, x_base(g, step + 2u) + at, 0, 17);  // nobody reads these any more
       }
+    load_operands(g, t - 1 > t0 ? t - 1 : t);
   };
   // dv_t of the whole layer for one batch group -> LDS; a lane asks again only for values that have not arrived.  The
   // polling is bounded like the barrier of k_adj_rec_ws: a thread that gives up raises *err, and from then on nobody
