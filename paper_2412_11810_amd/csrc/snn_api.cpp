@@ -259,69 +259,38 @@ void free_csr(snn_ctx *c, int l) {
 }
 
 // Compressed rows of a masked recurrent matrix (layout: NetDev::csr_sub).  An entry exists where the mask says a
-// synapse exists, whatever its weight; its order inside a row is the ascending postsynaptic index.  Built on the
-// host (one pass over the matrix), uploaded once; the stream is idle when this is called.
-snn_status build_csr(snn_ctx *c, int l, const float *w, const uint8_t *mask) {
+// synapse exists, whatever its weight; its order inside a row is the ascending postsynaptic index.  Built on the GPU
+// from the context's own copies of mask and weights; the arrays stay while the number of synapses does (a training loop
+// that hands over new weights under the same mask).  A matrix that cannot be compressed is left without the form.
+snn_status build_csr(snn_ctx *c, int l) {
   const int N = c->net.N[l], nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
-  const size_t ne = (size_t)N * N;
-  std::vector<float> wh;
-  std::vector<uint8_t> mh;
-  if (is_device_ptr(w)) { wh.resize(ne); HIPCHK(c, hipMemcpy(wh.data(), w, ne * 4, hipMemcpyDeviceToHost)); w = wh.data(); }
-  if (is_device_ptr(mask)) { mh.resize(ne); HIPCHK(c, hipMemcpy(mh.data(), mask, ne, hipMemcpyDeviceToHost)); mask = mh.data(); }
-  size_t nnz = 0;
-  for (size_t i = 0; i < ne; ++i) nnz += mask[i] != 0;
-  if (nnz > 0x1FF00000ull) return fail(c, SNN_E_INVAL, "recurrent matrix has too many synapses for 32-bit byte offsets of its entries");
-  std::vector<uint32_t> sub((size_t)N * (nsub + 1));
-  std::vector<uint16_t> col(nnz + 1);
-  std::vector<float> val(nnz + 1);
-  size_t p = 0;
-  for (int j = 0; j < N; ++j) {
-    const uint8_t *mr = mask + (size_t)j * N;
-    const float *wr = w + (size_t)j * N;
-    uint32_t *sr = sub.data() + (size_t)j * (nsub + 1);
-    for (int r = 0; r < nsub; ++r) {
-      sr[r] = (uint32_t)p;
-      const int n1 = std::min(N, (r + 1) * SNN_CSR_SUBW);
-      for (int n = r * SNN_CSR_SUBW; n < n1; ++n)
-        if (mr[n]) { col[p] = (uint16_t)n; val[p] = wr[n]; ++p; }
-    }
-    sr[nsub] = (uint32_t)p;
+  unsigned long long *out = c->counters; // at least two words
+  unsigned long long found[2] = {0, 0};
+  hipError_t e = hipSuccess;
+  if (!c->csr_sub[l]) e = hipMalloc(&c->csr_sub[l], (size_t)N * (nsub + 1) * 4);
+  if (e == hipSuccess) e = launch_csr_count(c->rec_mask[l], N, c->csr_sub[l], out, c->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(found, out, sizeof found, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  const size_t nnz = (size_t)found[0];
+  if (e == hipSuccess && nnz > 0x1FF00000ull) {
+    free_csr(c, l);
+    return fail(c, SNN_E_INVAL, "recurrent matrix has too many synapses for 32-bit byte offsets of its entries");
   }
-  // k_dw_csr: a wavefront owns 16 consecutive rows of a block of 256 and keeps 64 entries per row and sub-range in
-  // registers, up to 64 more per wavefront (and per row) in LDS
-  bool dw_ok = true;
-  for (int j0 = 0; j0 < N && dw_ok; j0 += 16)
-    for (int r = 0; r < nsub && dw_ok; ++r) {
-      uint32_t extra = 0;
-      for (int j = j0; j < std::min(N, j0 + 16); ++j) {
-        const uint32_t *sr = sub.data() + (size_t)j * (nsub + 1);
-        const uint32_t n = sr[r + 1] - sr[r];
-        if (n > 64) extra += n - 64;
-      }
-      if (extra > 64) dw_ok = false;
-    }
-  free_csr(c, l);
-  HIPCHK(c, hipMalloc(&c->acc_csr[l], (nnz + 1) * sizeof(double)));
-  c->csr_dw_ok[l] = dw_ok;
-  HIPCHK(c, hipMalloc(&c->csr_sub[l], sub.size() * 4));
-  HIPCHK(c, hipMalloc(&c->csr_col[l], col.size() * 2));
-  HIPCHK(c, hipMalloc(&c->csr_val[l], val.size() * 4));
-  HIPCHK(c, hipMemcpy(c->csr_sub[l], sub.data(), sub.size() * 4, hipMemcpyHostToDevice));
-  HIPCHK(c, hipMemcpy(c->csr_col[l], col.data(), col.size() * 2, hipMemcpyHostToDevice));
-  HIPCHK(c, hipMemcpy(c->csr_val[l], val.data(), val.size() * 4, hipMemcpyHostToDevice));
-  {
-    // packed copy for the gather (layout: NetDev::csr_pk)
-    std::vector<uint64_t> pk(nnz + (size_t)nsub * 64);
-    for (size_t e = 0; e < nnz; ++e) {
-      uint32_t bits;
-      memcpy(&bits, &val[e], 4);
-      pk[e] = (uint64_t)bits | ((uint64_t)col[e] << 32);
-    }
-    for (int r = 0; r < nsub; ++r)
-      for (int k = 0; k < 64; ++k) pk[nnz + (size_t)r * 64 + k] = (uint64_t)((r + 1) * SNN_CSR_SUBW + k) << 32;
-    HIPCHK(c, hipMalloc(&c->csr_pk[l], pk.size() * 8));
-    HIPCHK(c, hipMemcpy(c->csr_pk[l], pk.data(), pk.size() * 8, hipMemcpyHostToDevice));
+  if (e == hipSuccess && (!c->csr_pk[l] || c->csr_nnz[l] != nnz)) {
+    (void)hipFree(c->csr_col[l]); (void)hipFree(c->csr_val[l]); (void)hipFree(c->csr_pk[l]); (void)hipFree(c->acc_csr[l]);
+    c->csr_col[l] = nullptr; c->csr_val[l] = nullptr; c->csr_pk[l] = nullptr; c->acc_csr[l] = nullptr;
+    e = hipMalloc(&c->csr_col[l], (nnz + 1) * 2);
+    if (e == hipSuccess) e = hipMalloc(&c->csr_val[l], (nnz + 1) * 4);
+    if (e == hipSuccess) e = hipMalloc(&c->acc_csr[l], (nnz + 1) * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc(&c->csr_pk[l], (nnz + (size_t)nsub * 64) * 8);
   }
+  if (e == hipSuccess)
+    e = launch_csr_fill(c->rec_mask[l], c->W_rec[l], N, (uint32_t)nnz, c->csr_sub[l], c->csr_col[l], c->csr_val[l], c->csr_pk[l], c->stream);
+  if (e != hipSuccess) {
+    free_csr(c, l);
+    return fail(c, SNN_E_HIP, std::string("compressed rows: ") + hipGetErrorString(e));
+  }
+  c->csr_dw_ok[l] = found[1] == 0;
   c->csr_nnz[l] = nnz;
   return SNN_OK;
 }
@@ -610,14 +579,15 @@ snn_status snn_set_weights(snn_ctx *c, int kind, int layer, const float *w, cons
     c->graph_exec = nullptr;
   }
   const size_t ne = (size_t)rows * cols;
+  // mask and weights of the compressed rows may have been produced on the caller's default stream (see snn_bind_inputs)
+  if (mask && c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr));
   HIPCHK(c, hipMemcpyAsync(dst, w, ne * 4, hipMemcpyDefault, c->stream));
   HIPCHK(c, launch_transpose(dst, dstT, rows, cols, c->stream));
   if (kind == SNN_W_REC) {
     if (mask) {
       if (!c->rec_mask[layer]) HIPCHK(c, hipMalloc(&c->rec_mask[layer], ne));
       HIPCHK(c, hipMemcpyAsync(c->rec_mask[layer], mask, ne, hipMemcpyDefault, c->stream));
-      HIPCHK(c, hipStreamSynchronize(c->stream));
-      const snn_status rs = build_csr(c, layer, w, mask);
+      const snn_status rs = build_csr(c, layer);
       if (rs != SNN_OK) return rs;
     } else if (c->rec_mask[layer]) {
       HIPCHK(c, hipStreamSynchronize(c->stream));

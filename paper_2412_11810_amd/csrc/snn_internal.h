@@ -240,6 +240,11 @@ hipError_t launch_bwd_stage(const NetDev &net, const AdjJobs &jobs, float *carry
                             const float *g, PreJobs pre, hipStream_t s, const SpanHook *hook = nullptr);
 hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, const SpanHook *hook = nullptr);
 hipError_t launch_transpose(const float *src, float *dst, int rows, int cols, hipStream_t s);
+// Compressed rows of a masked recurrent matrix, in two parts: counts and row ends into sub, {synapses, sub-ranges that are
+// too full for k_dw_csr} into out (device); then, with the arrays sized for them, positions and entries.
+hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, hipStream_t s);
+hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t nnz, uint32_t *sub, uint16_t *col, float *val,
+                           uint64_t *pk, hipStream_t s);
 hipError_t launch_finish_grad(const double *acc, const uint8_t *mask_or_null, float *dW, size_t n, hipStream_t s);
 // The same for accumulators kept per existing synapse (compressed-row order): dW = 0 where no synapse exists.
 hipError_t launch_finish_grad_csr(const double *acc, const uint32_t *csr_sub, const uint16_t *csr_col, int N, float *dW,

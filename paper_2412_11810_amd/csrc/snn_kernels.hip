@@ -3556,6 +3556,112 @@ __global__ void k_transpose(const float *__restrict__ src, float *__restrict__ d
 }
 
 // fp64 accumulator -> fp32 gradient; a masked matrix has a gradient only where a synapse exists
+// Compressed rows of a masked recurrent matrix (layout: NetDev::csr_sub), built from the mask and the weights in HBM: one
+// pass over the mask counts, a scan over the rows places them, a second pass writes the entries.  Reads 2 N^2 mask bytes
+// and the weights once: bound by memory and launches (2048^2 at 10 % density: 22 us in three
+// launches; copying matrix and mask to the host and back and one pass there took 7.5 ms).
+// One workgroup per row, one wavefront per sub-range of SNN_CSR_SUBW postsynaptic neurons at a time.
+__global__ void __launch_bounds__(256)
+k_csr_count(const uint8_t *__restrict__ mask, int N, int nsub, uint32_t *__restrict__ sub) {
+  __shared__ uint32_t total[4];
+  const int j = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+  const uint8_t *mr = mask + (size_t)j * N;
+  uint32_t sum = 0;
+  for (int r = wave; r < nsub; r += 4) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < SNN_CSR_SUBW / WAVE; ++i) {
+      const int n = r * SNN_CSR_SUBW + i * WAVE + lane;
+      c += (uint32_t)__popcll(__ballot(n < N && mr[n < N ? n : 0] != 0));
+    }
+    if (lane == 0) sub[(size_t)j * (nsub + 1) + r] = c;
+    sum += c;
+  }
+  if (lane == 0) total[wave] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) sub[(size_t)j * (nsub + 1) + nsub] = total[0] + total[1] + total[2] + total[3];
+}
+// The row totals become the end of every row; out[0]: synapses, out[1]: sub-ranges in which 16 consecutive rows (the share
+// of a wavefront of k_dw_csr) have more than 64 entries beyond the 64 per row that it keeps in registers.
+__global__ void __launch_bounds__(1024)
+k_csr_scan(int N, int nsub, uint32_t *__restrict__ sub, unsigned long long *__restrict__ out) {
+  __shared__ unsigned long long wsum[16], bad[16];
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  unsigned long long nbad = 0;
+  for (int i = tid; i < (N + 15) / 16 * nsub; i += 1024) {
+    const int r = i % nsub, j0 = i / nsub * 16, j1 = j0 + 16 < N ? j0 + 16 : N;
+    uint32_t extra = 0;
+    for (int j = j0; j < j1; ++j) {
+      const uint32_t n = sub[(size_t)j * (nsub + 1) + r];
+      extra += n > 64u ? n - 64u : 0u;
+    }
+    nbad += extra > 64u;
+  }
+  for (int d = 1; d < WAVE; d <<= 1) nbad += __shfl_xor(nbad, d);
+  if (lane == 0) bad[wave] = nbad;
+  unsigned long long before = 0;
+  for (int j0 = 0; j0 < N; j0 += 1024) {
+    const int j = j0 + tid;
+    uint32_t *e = sub + (size_t)(j < N ? j : N - 1) * (nsub + 1) + nsub;
+    unsigned long long x = j < N ? *e : 0u;
+    for (int d = 1; d < WAVE; d <<= 1) {
+      const unsigned long long y = __shfl_up(x, d);
+      if (lane >= d) x += y;
+    }
+    if (lane == WAVE - 1) wsum[wave] = x;
+    __syncthreads();
+    unsigned long long all = 0;
+    for (int q = 0; q < 16; ++q) {
+      x += q < wave ? wsum[q] : 0ull;
+      all += wsum[q];
+    }
+    if (j < N) *e = (uint32_t)(before + x);
+    before += all;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    unsigned long long b = 0;
+    for (int q = 0; q < 16; ++q) b += bad[q];
+    out[0] = before;
+    out[1] = b;
+  }
+}
+__global__ void __launch_bounds__(256)
+k_csr_fill(const uint8_t *__restrict__ mask, const float *__restrict__ W, int N, int nsub, uint32_t nnz,
+           uint32_t *__restrict__ sub, uint16_t *__restrict__ col, float *__restrict__ val, uint64_t *__restrict__ pk) {
+  __shared__ uint32_t cnt[128]; // sub-ranges of a row: at most 65535 / 512 rounded up
+  const int j = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+  if ((int)threadIdx.x < nsub) cnt[threadIdx.x] = sub[(size_t)j * (nsub + 1) + threadIdx.x];
+  __syncthreads();
+  const uint32_t row0 = j > 0 ? sub[(size_t)(j - 1) * (nsub + 1) + nsub] : 0u;
+  const uint8_t *mr = mask + (size_t)j * N;
+  const float *wr = W + (size_t)j * N;
+  for (int r = wave; r < nsub; r += 4) {
+    uint32_t p = row0;
+    for (int q = 0; q < r; ++q) p += cnt[q];
+    if (lane == 0) sub[(size_t)j * (nsub + 1) + r] = p;
+#pragma unroll
+    for (int i = 0; i < SNN_CSR_SUBW / WAVE; ++i) {
+      const int n = r * SNN_CSR_SUBW + i * WAVE + lane;
+      const bool on = n < N && mr[n < N ? n : 0] != 0;
+      const uint64_t m = __ballot(on);
+      if (on) {
+        const uint32_t e = p + (uint32_t)__popcll(m & lanemask_lt());
+        const float w = wr[n];
+        col[e] = (uint16_t)n;
+        val[e] = w;
+        pk[e] = (uint64_t)__float_as_uint(w) | (uint64_t)(uint32_t)n << 32;
+      }
+      p += (uint32_t)__popcll(m);
+    }
+  }
+  if (j == 0) { // the entries behind the last one
+    for (int i = threadIdx.x; i < nsub * 64; i += 256)
+      pk[(size_t)nnz + i] = (uint64_t)((i / 64 + 1) * SNN_CSR_SUBW + i % 64) << 32;
+    if (threadIdx.x == 0) { col[nnz] = 0; val[nnz] = 0.0f; }
+  }
+}
+
 __global__ void k_finish_grad(const double *__restrict__ acc, const uint8_t *__restrict__ mask, float *__restrict__ dW,
                               size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -4877,6 +4983,19 @@ hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, cons
 
 hipError_t launch_transpose(const float *src, float *dst, int rows, int cols, hipStream_t s) {
   hipLaunchKernelGGL(k_transpose, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(32, 8), 0, s, src, dst, rows, cols);
+  return hipGetLastError();
+}
+
+hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, hipStream_t s) {
+  const int nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
+  hipLaunchKernelGGL(k_csr_count, dim3(N), dim3(256), 0, s, mask, N, nsub, sub);
+  hipLaunchKernelGGL(k_csr_scan, dim3(1), dim3(1024), 0, s, N, nsub, sub, out);
+  return hipGetLastError();
+}
+hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t nnz, uint32_t *sub, uint16_t *col, float *val,
+                           uint64_t *pk, hipStream_t s) {
+  const int nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
+  hipLaunchKernelGGL(k_csr_fill, dim3(N), dim3(256), 0, s, mask, W, N, nsub, nnz, sub, col, val, pk);
   return hipGetLastError();
 }
 

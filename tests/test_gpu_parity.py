@@ -1010,6 +1010,43 @@ def test_weight_gradients_over_compressed_rows(hidden, B, T, density, monkeypatc
     monkeypatch.delenv("SNN_DW")
 
 
+@pytest.mark.parametrize("N,host", [(300, True), (512, False), (513, True), (1100, False), (1100, True)])
+def test_compressed_rows_follow_the_mask(N, host, monkeypatch):
+    """The compressed rows are built on the GPU whenever a mask is handed over: rows without and with every synapse, a last
+    sub-range of one neuron, another mask with as many synapses in the same context (its arrays are kept), one with more,
+    no mask, and one again.  Each time the spikes and gradients of a context that walks the dense-stored rows."""
+    import torch
+    rng = np.random.default_rng(5 + N)
+    w = synth.Workload("csr_build", 40, (N,), 6, T=9, B=3, p_in=0.1, gain=0.8, seed=7)
+    d = synth.generate(w)
+    first = (rng.random((N, N)) < 0.2).astype(np.uint8)
+    first[0] = 0
+    first[N // 2] = 1
+    first[N - 1] = 0
+    first[:, N - 1] = 1
+    masks = [first, np.ascontiguousarray(first[::-1, ::-1]), (rng.random((N, N)) < 0.6).astype(np.uint8), None, first]
+    monkeypatch.setenv("SNN_WS_KERNEL", "chip")  # the same order of summation in the adjoint of both
+    got = {}
+    for csr in ("1", "0"):
+        monkeypatch.setenv("SNN_CSR", csr)
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            for k, m in enumerate(masks):
+                wr = d["W_rec"][0] * (1 + k) / 2 * (m if m is not None else 1)
+                if host:
+                    net.snn_set_weights(snn.SNN_W_REC, 0, np.ascontiguousarray(wr, dtype=np.float32), m)
+                else:
+                    net.snn_set_weights(snn.SNN_W_REC, 0, torch.tensor(wr, dtype=torch.float32, device="cuda"),
+                                        None if m is None else torch.tensor(m, device="cuda"))
+                net.snn_bptt(snn.SNN_DOUBLE, 8, 3)
+                got[csr, k] = _gpu_grads(net, 1), net.snn_get_spikes(0, w.T)
+        finally:
+            net.snn_destroy()
+    for k in range(len(masks)):
+        assert np.array_equal(got["1", k][1], got["0", k][1]) and _identical(got["1", k][0], got["0", k][0]), k
+
+
 @pytest.mark.parametrize("hidden,B,T,density,window", [
     ((2048,), 5, 14, 0.1, 0.0),        # one job, a ragged batch group (5 = 4 + 1)
     ((1536, 1100), 3, 12, 0.3, 0.0),   # two jobs of different widths in one launch, ragged row blocks
