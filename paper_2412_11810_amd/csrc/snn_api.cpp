@@ -638,16 +638,36 @@ snn_status snn_bind_inputs(snn_ctx *c, const uint8_t *in_spikes, const int32_t *
   return SNN_OK;
 }
 
-// Tile boundaries of a forward pass over (t0, t1]: at most SNN_FWD_TILE steps per tile, and a
-// boundary at every multiple of `seg` (the coarse checkpoints of the host tier).
-static std::vector<int> tile_bounds(int t0, int t1, int seg) {
+// Steps per tile that a forward pass over T steps aims at.  The layers run two tiles apart: n tiles are n + 2 (L - 1)
+// sequential launches one after the other (one tile: L), each of T / n steps and a fixed cost of o steps.  Measured: o = 16
+// up to 4096 neurons (1-20 us per step; 700-3x1024, T = 500: 48 steps best; 300-1500-1100, T = 150: 8.2 ms per training step
+// with 64, 7.6 with 24-50; 700-2x256, T = 1000: 64 best; 244-3x2112, T = 29: 1.6 ms in one tile, 1.8 in two), 3 for wider
+// layers (100 us per step; 1024-4x8192, T = 512: 263 ms with 64, 254 with 16; T = 200 in segments of 50: 198 with 50, 179
+// with 17).
+static int fwd_tile_target(const NetDev &n, int T) {
+  int nmax = 0;
+  for (int l = 0; l < n.L; ++l) nmax = std::max(nmax, n.N[l]);
+  const double o = nmax <= 4096 ? 16.0 : 3.0;
+  int best = SNN_FWD_TILE;
+  double least = 0.0;
+  for (int len = SNN_FWD_TILE; len >= 16; --len) {
+    const int tiles = (T + len - 1) / len;
+    const double cost = (tiles == 1 ? n.L : tiles + 2 * (n.L - 1)) * ((double)T / tiles + o);
+    if (len == SNN_FWD_TILE || cost < least) { least = cost; best = len; }
+  }
+  return best;
+}
+
+// Tile boundaries of a forward pass over (t0, t1]: a boundary at every multiple of `seg` (the coarse checkpoints of the
+// host tier), and between two of them as many equal tiles as the target length asks for.
+static std::vector<int> tile_bounds(const NetDev &n, int t0, int t1, int seg) {
+  const int target = fwd_tile_target(n, t1 - t0);
   std::vector<int> b{t0};
   for (int a = t0; a < t1;) {
-    int e = std::min(a + SNN_FWD_TILE, t1);
-    const int next_seg = (a / seg + 1) * seg;
-    if (next_seg < e) e = next_seg;
-    b.push_back(e);
-    a = e;
+    const int end = std::min(t1, (a / seg + 1) * seg);
+    const int tiles = (end - a + target - 1) / target;
+    for (int k = 1, from = a; k <= tiles; ++k) b.push_back(from + (int)((long long)(end - from) * k / tiles));
+    a = end;
   }
   return b;
 }
@@ -703,7 +723,7 @@ static snn_status forward_only(snn_ctx *c, float *traj_or_null, float *work_or_n
     work = c->dubuf;
   }
   HIPCHK(c, launch_fill_zero(c->cur_state, c->Ms(), c->stream));
-  std::vector<int> bounds = tile_bounds(0, c->T_bound, c->T_bound);
+  std::vector<int> bounds = tile_bounds(n, 0, c->T_bound, c->T_bound);
   HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, st, c->readout, 1, work, c->stream, nullptr, nullptr, &c->ws));
   HIPCHK(c, launch_loss(c->readout, c->labels, n.B, n.n_out, c->T_bound, c->ubar, c->g, c->loss_dev, c->stream));
   c->T_spikes = c->T_bound;
@@ -1375,12 +1395,12 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
   HIPCHK(c, launch_fill_zero(c->cur_state, Ms, s)); // x_0
   if (strategy == SNN_STANDARD) {
     StoreSpec sp{chunk0, slot, 0, 1, 0, T, 0};
-    const std::vector<int> bounds = tile_bounds(0, T, T);
+    const std::vector<int> bounds = tile_bounds(n, 0, T, T);
     HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, sp, c->readout, 1, c->dubuf, s, &hk, nullptr, &c->ws));
   } else if (strategy == SNN_CHUNK) {
     HIPCHK(c, launch_fill_zero(lckpt, Ms, s)); // x_0
     StoreSpec sp{lckpt, slot, 0, p.F, 1, T - 1, 0};
-    const std::vector<int> bounds = tile_bounds(0, T, T);
+    const std::vector<int> bounds = tile_bounds(n, 0, T, T);
     HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, sp, c->readout, 1, c->dubuf, s, &hk, nullptr, &c->ws));
   } else if (strategy == SNN_HIER) {
     // Checkpoint k = x_{kF} goes to slot k mod 2*nb_local of a ring of two batches.  When every layer
@@ -1428,7 +1448,7 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
     HIPCHK(c, launch_fill_zero(lckpt, Ms, s)); // x_0 = checkpoint 0
     StoreSpec sp{lckpt, slot, 0, p.F, 1, T - 1, RB * NL};
     const FwdCallbacks cb{&hier, &Hier::done};
-    const std::vector<int> bounds = tile_bounds(0, T, p.F);
+    const std::vector<int> bounds = tile_bounds(n, 0, T, p.F);
     HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, sp, c->readout, 1, c->dubuf, s, &hk, &cb, &c->ws));
   } else if (direct) {
     // x_0 lives in host slot 0 (zeroed on the host); the sequential kernels store x_{KC} into host slot K
@@ -1438,7 +1458,7 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
       sp.cur_from = p.keep_from;
       cache_a = p.keep_from; cache_b = T;
     }
-    const std::vector<int> bounds = tile_bounds(0, T, T); // no host-side work at the checkpoints: full tiles
+    const std::vector<int> bounds = tile_bounds(n, 0, T, T); // no host-side work at the checkpoints: full tiles
     HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, sp, c->readout, 1, c->dubuf, s, &hk, R > 0 ? &cb_spk : nullptr, &c->ws));
     st.n_d2h += p.n_remote - 1;
     st.d2h_bytes += (int64_t)(p.n_remote - 1) * (int64_t)Ms;
@@ -1482,7 +1502,7 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
     }
     const FwdCallbacks cb{&snap, &Snap::done};
     so.inner = &cb;
-    const std::vector<int> bounds = tile_bounds(0, T, p.C);
+    const std::vector<int> bounds = tile_bounds(n, 0, T, p.C);
     HIPCHK(c, snap.reserve(0)); // nothing to wait for yet; marks checkpoint 1 as reserved
     StoreSpec sp{stage, slot, 0, p.C, 1, T - 1, p.n_stage_slots}; // x_{KC} -> staging slot K % n_stage
     if (ccache && p.keep_from >= 0) { // the currents of the last coarse segment(s) stay for the backward pass
