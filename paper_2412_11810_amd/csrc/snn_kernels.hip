@@ -489,8 +489,8 @@ k_layer_seq_gather(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpe
 
 // The same sequential part with the neurons of a layer spread over S workgroups per batch element (one workgroup
 // per batch element leaves most of the chip idle and is bound by what one compute unit can load: every active
-// weight row passes through its L1).  Workgroup (b, sl) owns the columns [sl N/S, (sl+1) N/S) -- whole 64-bit spike
-// words -- and gathers its part of the active rows of W_rec; sums per neuron are the same ascending sums.  After
+// weight row passes through its L1).  Workgroup (b, sl) owns ceil(Wd / S) whole 64-bit spike words of columns (the last
+// ones of a layer may own fewer, or none and leave) and gathers its part of the active rows of W_rec; sums per neuron are the same ascending sums.  After
 // the threshold it writes its spike words to the stored bitmask and, as two 8-byte entries per word (32 spike bits
 // in the low half, the step count of this launch in the high half), to an exchange buffer in uncached device
 // memory that is cleared before every launch and double-buffered by the parity of the step.  There is no barrier:
@@ -499,7 +499,7 @@ k_layer_seq_gather(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpe
 // the list of active rows.
 template <int NPT>
 __global__ void __launch_bounds__(512)
-k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec st, int S, uint64_t *xw,
+k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec st, int S, uint64_t *xw, int wd_max,
                       unsigned *err, unsigned spin_limit) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int jq = blockIdx.y;
@@ -508,13 +508,14 @@ k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, Store
   const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, Wd = net.Wd[l + 1];
   const int b = (int)blockIdx.x / S, sl = (int)blockIdx.x % S;
   const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
-  const int Ns = N / S, c0 = sl * Ns, w0 = c0 >> 6; // own columns and their first word
+  const int ws = (Wd + S - 1) / S, w0 = sl * ws, c0 = w0 << 6; // own words, first word and column
+  if (w0 >= Wd) return;
   uint64_t *words = (uint64_t *)smem;       // [Wd]  whole layer
   int *cnt = (int *)(words + Wd);           // [1] (+3 pad)
   uint32_t *offs = (uint32_t *)(cnt + 4);   // [N + 4] byte offsets of the active rows
   uint64_t *mbase = net.mask[l + 1] + (size_t)b * Wd;
   const size_t mstride = (size_t)B * Wd;
-  uint64_t *xb = xw + (size_t)(jq * B + b) * 4 * Wd; // [2][2 Wd] tagged half-words
+  uint64_t *xb = xw + (size_t)(jq * B + b) * 4 * wd_max; // [2][2 Wd] tagged half-words
   const uint32_t n4 = (uint32_t)N * 4u;
   // descriptor over the whole matrix, shifted to this slice's first column
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
@@ -522,6 +523,8 @@ k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, Store
   uint32_t coff[NPT];
 #pragma unroll
   for (int k = 0; k < NPT; ++k) coff[k] = (uint32_t)(tid + k * nt) * 4u;
+  // whether word k of the wavefront's exists and is this workgroup's (uniform per wavefront)
+  auto own = [&](int k) { const int w = (tid + k * nt) >> 6; return w < ws && w0 + w < Wd; };
   if (tid == 0) *cnt = 0;
   for (int i = tid; i < Wd; i += nt) words[i] = mbase[mrow_of(net, l + 1, t0) * mstride + i];
   __syncthreads();
@@ -530,8 +533,8 @@ k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, Store
 #pragma unroll
   for (int k = 0; k < NPT; ++k) {
     const int n = c0 + tid + k * nt;
-    v[k] = state[(size_t)b * SN + off + n];
-    if ((words[n >> 6] >> lane) & 1ull) sp |= 1u << k;
+    v[k] = n < N ? state[(size_t)b * SN + off + n] : 0.0f;
+    if (own(k) && ((words[n >> 6] >> lane) & 1ull)) sp |= 1u << k;
   }
   expand_offsets(words, Wd, offs, cnt, tid, nt, n4);
   __syncthreads();
@@ -547,7 +550,7 @@ k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, Store
     const float *irow = iin + (size_t)(t - 1 - t_tile) * istride + (size_t)b * N + c0;
     float in_t[NPT];
 #pragma unroll
-    for (int k = 0; k < NPT; ++k) in_t[k] = irow[tid + k * nt];
+    for (int k = 0; k < NPT; ++k) in_t[k] = own(k) && c0 + tid + k * nt < N ? irow[tid + k * nt] : 0.0f;
     float a_rec[NPT];
     gather1<NPT>(wres, coff, offs, *cnt, a_rec);
     uint64_t *xdst = xb + (size_t)(step & 1u) * 2 * Wd;
@@ -556,15 +559,17 @@ k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, Store
 #pragma unroll
     for (int k = 0; k < NPT; ++k) {
       const int nl = tid + k * nt, widx = w0 + (nl >> 6);
+      const bool in = c0 + nl < N;
+      if (!own(k)) continue;
       float a = net.alpha * v[k];
       if ((sp >> k) & 1u) a = a - net.theta;
       const float it = in_t[k] + a_rec[k];
       const float vn = a + it;
       v[k] = vn;
-      if (st.cur && t > st.cur_from) st.cur[(size_t)(t - st.cur_from - 1) * st.slot_stride + (size_t)b * SN + off + c0 + nl] = it;
-      const uint64_t word = __ballot(vn > net.theta);
+      if (st.cur && t > st.cur_from && in) st.cur[(size_t)(t - st.cur_from - 1) * st.slot_stride + (size_t)b * SN + off + c0 + nl] = it;
+      const uint64_t word = __ballot(in && vn > net.theta);
       if ((word >> lane) & 1ull) spn |= 1u << k;
-      if (store_slot >= 0) st.base[(size_t)store_slot * st.slot_stride + (size_t)b * SN + off + c0 + nl] = vn;
+      if (store_slot >= 0 && in) st.base[(size_t)store_slot * st.slot_stride + (size_t)b * SN + off + c0 + nl] = vn;
       if (lane == 0) mbase[mrow_of(net, l + 1, t) * mstride + widx] = word;
       if (lane < 2)
         __hip_atomic_store(&xdst[2 * widx + lane], tag | (uint64_t)(uint32_t)(word >> (32 * lane)), __ATOMIC_RELAXED,
@@ -597,7 +602,8 @@ k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, Store
     __syncthreads();
   }
 #pragma unroll
-  for (int k = 0; k < NPT; ++k) state[(size_t)b * SN + off + c0 + tid + k * nt] = v[k];
+  for (int k = 0; k < NPT; ++k)
+    if (own(k) && c0 + tid + k * nt < N) state[(size_t)b * SN + off + c0 + tid + k * nt] = v[k];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -728,15 +734,15 @@ static __device__ __forceinline__ void csr_gather_wave(const uint16_t *list, int
   }
 }
 
-// The sliced sequential part for a layer whose recurrent matrix has compressed rows (widths that are multiples
-// of 4 SNN_CSR_SUBW).  Workgroup (b, sl) owns 4 SNN_CSR_SUBW columns, wavefront w the sub-range 4 sl + w: it
+// The sliced sequential part for a layer whose recurrent matrix has compressed rows.  Workgroup (b, sl) owns
+// 4 SNN_CSR_SUBW columns, wavefront w the sub-range 4 sl + w (at the end of a layer partly or wholly past its width): it
 // walks the compressed rows of the neurons that fired in the previous step (csr_gather_wave, accumulators in LDS,
 // cleared by their owner at the start of the step) and moves 1/10 of the bytes of the dense-stored walk when
 // 90 % of the synapses do not exist.  Thread (w, lane) then owns the columns 64 k + lane of its wavefront's
 // sub-range for the LIF update, so a ballot is a whole spike word.  Exchange of the spike words between the
 // workgroups of a batch element, polling and time-out exactly as in k_layer_seq_gather_sl.
 static __device__ __forceinline__ void layer_seq_csr_sl_body(const NetDev &net, const SeqJobs &jobs, float *__restrict__ state,
-                                                             const StoreSpec &st, int S, uint64_t *xw, unsigned *err,
+                                                             const StoreSpec &st, int S, uint64_t *xw, int wd_max, unsigned *err,
                                                              unsigned spin_limit, unsigned char *smem, int bx, int jq) {
   constexpr int NPT = SNN_CSR_SUBW / WAVE, NS = 4 * SNN_CSR_SUBW;
   const int l = jobs.j[jq].l, t0 = jobs.j[jq].t0, t1 = jobs.j[jq].t1, t_tile = jobs.j[jq].t_tile;
@@ -745,7 +751,9 @@ static __device__ __forceinline__ void layer_seq_csr_sl_body(const NetDev &net, 
   const int b = bx / S, sl = bx % S;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c0 = sl * NS + wave * SNN_CSR_SUBW, w0 = c0 >> 6; // own wavefront's first column and its spike word
-  const int nsub1 = N / SNN_CSR_SUBW + 1, r = sl * 4 + wave;
+  if (sl * NS >= N) return; // a narrower layer than the widest of the launch
+  const int nsub1 = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW + 1, r = sl * 4 + wave;
+  const bool has = c0 < N; // the wavefront's sub-range exists
   uint64_t *words = (uint64_t *)smem;                    // [Wd]  whole layer
   int *cnt = (int *)(words + Wd);                        // [1] (+3 pad)
   float *acc = (float *)(cnt + 4);                       // [4][SNN_CSR_ACCW]
@@ -753,7 +761,7 @@ static __device__ __forceinline__ void layer_seq_csr_sl_body(const NetDev &net, 
   float *acc_w = acc + wave * SNN_CSR_ACCW;
   uint64_t *mbase = net.mask[l + 1] + (size_t)b * Wd;
   const size_t mstride = (size_t)B * Wd;
-  uint64_t *xb = xw + (size_t)(jq * B + b) * 4 * Wd; // [2][2 Wd] tagged half-words
+  uint64_t *xb = xw + (size_t)(jq * B + b) * 4 * wd_max; // [2][2 Wd] tagged half-words
   const uint32_t *__restrict__ sub = net.csr_sub[l];
   if (tid == 0) *cnt = 0;
   for (int i = tid; i < Wd; i += 256) words[i] = mbase[mrow_of(net, l + 1, t0) * mstride + i];
@@ -762,8 +770,8 @@ static __device__ __forceinline__ void layer_seq_csr_sl_body(const NetDev &net, 
   uint32_t sp = 0;
 #pragma unroll
   for (int k = 0; k < NPT; ++k) {
-    v[k] = state[(size_t)b * SN + off + c0 + 64 * k + lane];
-    if ((words[w0 + k] >> lane) & 1ull) sp |= 1u << k;
+    v[k] = c0 + 64 * k + lane < N ? state[(size_t)b * SN + off + c0 + 64 * k + lane] : 0.0f;
+    if (w0 + k < Wd && ((words[w0 + k] >> lane) & 1ull)) sp |= 1u << k;
   }
   expand_all(words, Wd, list, cnt, tid, 256);
   __syncthreads();
@@ -780,10 +788,10 @@ static __device__ __forceinline__ void layer_seq_csr_sl_body(const NetDev &net, 
     float in_t[NPT];
 #pragma unroll
     for (int k = 0; k < NPT; ++k) {
-      in_t[k] = irow[64 * k + lane];
+      in_t[k] = c0 + 64 * k + lane < N ? irow[64 * k + lane] : 0.0f;
       acc_w[64 * k + lane] = 0.0f;
     }
-    csr_gather_wave(list, *cnt, sub, nsub1, r, net.csr_pk[l], net.csr_nnz[l], acc_w, lane);
+    if (has) csr_gather_wave(list, *cnt, sub, nsub1, r, net.csr_pk[l], net.csr_nnz[l], acc_w, lane);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); // the adds of this wavefront have landed before it reads the sums
     uint64_t *xdst = xb + (size_t)(step & 1u) * 2 * Wd;
     const uint64_t tag = (uint64_t)(step + 1u) << 32;
@@ -791,16 +799,18 @@ static __device__ __forceinline__ void layer_seq_csr_sl_body(const NetDev &net, 
 #pragma unroll
     for (int k = 0; k < NPT; ++k) {
       const int widx = w0 + k;
+      const bool in = c0 + 64 * k + lane < N;
+      if (widx >= Wd) continue;
       const float a_rec = acc_w[64 * k + lane];
       float a = net.alpha * v[k];
       if ((sp >> k) & 1u) a = a - net.theta;
       const float it = in_t[k] + a_rec;
       const float vn = a + it;
       v[k] = vn;
-      if (st.cur && t > st.cur_from) st.cur[(size_t)(t - st.cur_from - 1) * st.slot_stride + (size_t)b * SN + off + c0 + 64 * k + lane] = it;
-      const uint64_t word = __ballot(vn > net.theta);
+      if (st.cur && t > st.cur_from && in) st.cur[(size_t)(t - st.cur_from - 1) * st.slot_stride + (size_t)b * SN + off + c0 + 64 * k + lane] = it;
+      const uint64_t word = __ballot(in && vn > net.theta);
       if ((word >> lane) & 1ull) spn |= 1u << k;
-      if (store_slot >= 0) st.base[(size_t)store_slot * st.slot_stride + (size_t)b * SN + off + c0 + 64 * k + lane] = vn;
+      if (store_slot >= 0 && in) st.base[(size_t)store_slot * st.slot_stride + (size_t)b * SN + off + c0 + 64 * k + lane] = vn;
       if (lane == 0) mbase[mrow_of(net, l + 1, t) * mstride + widx] = word;
       if (lane < 2)
         __hip_atomic_store(&xdst[2 * widx + lane], tag | (uint64_t)(uint32_t)(word >> (32 * lane)), __ATOMIC_RELAXED,
@@ -834,14 +844,15 @@ static __device__ __forceinline__ void layer_seq_csr_sl_body(const NetDev &net, 
     __syncthreads();
   }
 #pragma unroll
-  for (int k = 0; k < NPT; ++k) state[(size_t)b * SN + off + c0 + 64 * k + lane] = v[k];
+  for (int k = 0; k < NPT; ++k)
+    if (c0 + 64 * k + lane < N) state[(size_t)b * SN + off + c0 + 64 * k + lane] = v[k];
 }
 
 __global__ void __launch_bounds__(256)
-k_layer_seq_csr_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec st, int S, uint64_t *xw,
+k_layer_seq_csr_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec st, int S, uint64_t *xw, int wd_max,
                    unsigned *err, unsigned spin_limit) {
   extern __shared__ __align__(16) unsigned char smem[];
-  layer_seq_csr_sl_body(net, jobs, state, st, S, xw, err, spin_limit, smem, (int)blockIdx.x, (int)blockIdx.y);
+  layer_seq_csr_sl_body(net, jobs, state, st, S, xw, wd_max, err, spin_limit, smem, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 // A4: u_t = beta u_{t-1} + I_out,t ; usum += u_t over the steps of a tile (fp64 state: ubar feeds a
@@ -1255,13 +1266,13 @@ k_currents_dense(NetDev net, CurJobs jobs, int ws) {
 // current workgroup, which their exchange of spike words needs -- and one of the current kernel, which keeps the
 // matrix cores as busy with one wavefront per SIMD as with two.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
-k_fwd_stage_csr(NetDev net, SeqJobs sj, float *__restrict__ state, StoreSpec st, int S, uint64_t *xw, unsigned *err,
+k_fwd_stage_csr(NetDev net, SeqJobs sj, float *__restrict__ state, StoreSpec st, int S, uint64_t *xw, int wd_max, unsigned *err,
                 unsigned spin_limit, CurJobs cj, int n_seq_x, int cur_gx) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n_seq = n_seq_x * sj.count;
   if ((int)blockIdx.x < n_seq) {
     __builtin_amdgcn_s_setprio(3); // the chain goes first wherever both have an instruction ready
-    layer_seq_csr_sl_body(net, sj, state, st, S, xw, err, spin_limit, smem, (int)blockIdx.x % n_seq_x, (int)blockIdx.x / n_seq_x);
+    layer_seq_csr_sl_body(net, sj, state, st, S, xw, wd_max, err, spin_limit, smem, (int)blockIdx.x % n_seq_x, (int)blockIdx.x / n_seq_x);
   } else {
     const int i = (int)blockIdx.x - n_seq;
     currents_dense_body<SNN_DENSE_MB_, 0>(net, cj.j[i / cur_gx], i % cur_gx,
@@ -3977,9 +3988,11 @@ static hipError_t launch_fwd_stage(const NetDev &net, const SeqJobs &sj, float *
 static size_t seq_gather_lds(const NetDev &net);
 template <int NPT>
 static int seq_sl_resident(int device, size_t lds, int threads) {
-  static int cached[16][9] = {}; // per device and block size / 64
-  if (device < 0 || device >= 16 || threads < 64 || threads > 512) return 0;
-  int &c = cached[device][threads / 64];
+  static int cached[16][9][10] = {}; // per device, block size / 64 and LDS in steps of 16 KB
+  if (device < 0 || device >= 16 || threads < 64 || threads > 512 || lds > 160 * 1024) return 0;
+  const size_t step = lds ? (lds - 1) >> 14 : 0;
+  lds = (step + 1) << 14;
+  int &c = cached[device][threads / 64][step];
   if (!c) {
     hipDeviceProp_t prop;
     int per_cu = 0;
@@ -3991,34 +4004,37 @@ static int seq_sl_resident(int device, size_t lds, int threads) {
 }
 // Slices per batch element for the sequential part of layers wider than 256 neurons (1: one workgroup per batch
 // element).  All workgroups of a launch must be resident at once (they wait for each other), every wide layer may
-// have a job in the same launch, a slice is whole spike words and a whole number of rounds of its block, and the
-// exchange buffer of the chip-wide kernels must hold the entries of every (job, batch element).  Used from 2048
-// neurons (a single compute unit's L1 then bounds the step).  SNN_SEQ_SLICES=1 turns it off, =2, 4, 8 asks for
-// that many at any width.
+// have a job in the same launch, a slice is whole spike words, and the exchange buffer of the chip-wide kernels must
+// hold the entries of every (job, batch element).  Used where a layer is wider than 1024 neurons: a single compute unit's
+// L1 then bounds the step, and its threads own four and more neurons each.  Against one
+// workgroup per batch element, which widths that are no multiple of 1024 or differ between layers ran: 300-1500-1100, batch
+// 24, T = 150: 7.5 -> 5.1 ms per training step; 244-3x2112, batch 15, T = 29, forward pass: 1.62 -> 0.97; 3x7808 at 20 %
+// density, batch 13, T = 135: 227 -> 123 per training step.  SNN_SEQ_SLICES=1 turns it off,
+// =2, 4, 8 asks for that many at any width.
 static int seq_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws, int *npt, int *threads) {
   if (!ws || !ws->xg || ga.count < 1) return 1;
   const int forced = net.sel_slices;
   if (forced == 1) return 1;
-  const int N = net.N[ga.j[0].l], Wd = net.Wd[ga.j[0].l + 1];
-  int n_wide = 0;
+  int n_wide = 0, N = 0, Wd = 0;
   for (int l = 0; l < net.L; ++l) n_wide += net.N[l] > 256;
-  for (int i = 0; i < ga.count; ++i)
-    if (net.N[ga.j[i].l] != N) return 1;
+  for (int i = 0; i < ga.count; ++i) {
+    N = net.N[ga.j[i].l] > N ? net.N[ga.j[i].l] : N;
+    Wd = net.Wd[ga.j[i].l + 1] > Wd ? net.Wd[ga.j[i].l + 1] : Wd;
+  }
   // narrower layers: measured slower with slices at 512 and 1024 neurons (a wavefront walks every active row whatever
   // the number of columns its workgroup owns, and that walk, not the compute unit's L1, is what takes the time)
-  if (!forced && N < 2048) return 1;
+  if (!forced && N <= 1024) return 1;
   if ((size_t)n_wide * net.B * 4 * Wd * sizeof(uint64_t) > (size_t)ws->xg_stride * SNN_MAXL * sizeof(float)) return 1;
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess) return 1;
   const size_t lds = seq_gather_lds(net);
   for (int S = 8; S >= 2; S /= 2) {
     if (forced && S != forced) continue;
-    if (N % (64 * S) != 0) continue;
-    const int Ns = N / S;
+    const int words = (Wd + S - 1) / S; // of a slice: up to eight wavefronts, p words each
     int p = 1;
-    while (Ns / p > 512) p *= 2;
-    if (p > 16 || Ns % (64 * p) != 0) continue;
-    const int th = Ns / p;
+    while ((words + p - 1) / p > 8) p *= 2;
+    if (p > 16) continue;
+    const int th = 64 * ((words + p - 1) / p);
     int resident = 0;
     switch (p) {
       case 1: resident = seq_sl_resident<1>(device, lds, th); break;
@@ -4036,9 +4052,9 @@ static int seq_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws, in
   return 1;
 }
 
-// The compressed-row version of the sliced sequential part: every job's layer has compressed rows, the same width
-// (a multiple of 4 SNN_CSR_SUBW), all workgroups of the launch are resident at once and the exchange buffer holds
-// the entries of every (job, batch element).  Returns the slices per batch element, 0 if it cannot run.
+// The compressed-row version of the sliced sequential part: every job's layer is wider than 1024 neurons and has
+// compressed rows, all workgroups of the launch are resident at once and the exchange buffer holds the entries of every
+// (job, batch element).  Returns the slices per batch element of the widest job, 0 if it cannot run.
 static size_t seq_csr_lds(int N, int Wd) {
   return (size_t)Wd * 8 + 16 + (size_t)4 * SNN_CSR_SUBW * 4 + (size_t)((N + 7) & ~7) * 2 + (size_t)4 * 64 * 4;
 }
@@ -4075,25 +4091,31 @@ static int seq_csr_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws
   if (!ws || !ws->xg || ga.count < 1 || net.sel_slices == 1) return 0;
   // The walk over compressed rows pays per presynaptic spike and per synapse that exists: it runs where the
   // context's firing-rate policy has picked the gather over compressed rows for the recompute or, at higher
-  // activity, for this walk alone (cur_pol 1, 3, 4), or wherever the hook asks.
+  // activity, for this walk alone (cur_pol 1, 3, 4), or wherever the hook asks.  Before any rate is known (a context's
+  // first step, or one that only runs forward passes): where that policy would pick it at every activity, i.e. matrices
+  // of 32 MB and more at a density of at most 1/8.
+  int N = 0, Wd = 0;
+  for (int i = 0; i < ga.count; ++i) {
+    const int l = ga.j[i].l;
+    N = net.N[l] > N ? net.N[l] : N;
+    Wd = net.Wd[l + 1] > Wd ? net.Wd[l + 1] : Wd;
+    if (net.N[l] <= 1024 || (need_rows && !net.csr_sub[l])) return 0;
+  }
   if (need_rows && net.sel_csr != 2) {
     if (net.sel_csr == 1) return 0;
     for (int i = 0; i < ga.count; ++i) {
-      const int pol = net.cur_pol[1][ga.j[i].l];
-      if (pol != 1 && pol != 3 && pol != 4) return 0;
+      const int l = ga.j[i].l, pol = net.cur_pol[1][l];
+      const bool always = (size_t)N * N * sizeof(float) >= ((size_t)32 << 20) && (size_t)net.csr_nnz[l] * 8 <= (size_t)net.N[l] * net.N[l];
+      if (pol != 1 && pol != 3 && pol != 4 && !(pol == 0 && always)) return 0;
     }
   }
-  const int N = net.N[ga.j[0].l], Wd = net.Wd[ga.j[0].l + 1];
-  if (N % (4 * SNN_CSR_SUBW) != 0) return 0;
   int n_wide = 0;
   for (int l = 0; l < net.L; ++l) n_wide += net.N[l] > 256;
-  for (int i = 0; i < ga.count; ++i)
-    if (net.N[ga.j[i].l] != N || (need_rows && !net.csr_sub[ga.j[i].l])) return 0;
   if ((size_t)n_wide * net.B * 4 * Wd * sizeof(uint64_t) > (size_t)ws->xg_stride * SNN_MAXL * sizeof(float)) return 0;
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess) return 0;
   // LDS of the widest layer the kernel can meet on this device (the occupancy is queried once, outside any capture)
-  const int S = N / (4 * SNN_CSR_SUBW);
+  const int S = (N + 4 * SNN_CSR_SUBW - 1) / (4 * SNN_CSR_SUBW);
   if (S * net.B * n_wide > seq_csr_resident(device, seq_csr_lds(8192, 128))) return 0;
   return S;
 }
@@ -4186,7 +4208,11 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
         ro_first = false;
       }
     } else {
-      int npt_sl = 0, th_sl = 0;
+      int npt_sl = 0, th_sl = 0, wd_max = 0, n_max = 0; // words and neurons of the stage's widest event-driven layer
+      for (int i = 0; i < ga.count; ++i) {
+        wd_max = net.Wd[ga.j[i].l + 1] > wd_max ? net.Wd[ga.j[i].l + 1] : wd_max;
+        n_max = net.N[ga.j[i].l] > n_max ? net.N[ga.j[i].l] : n_max;
+      }
       const int S_csr = ga.count ? seq_csr_slices(net, ga, ws) : 0;
       const int S = (ga.count && !S_csr) ? seq_slices(net, ga, ws, &npt_sl, &th_sl) : 1;
       // Wide layers over compressed rows: the dense feed-forward currents for the next stage ride in the launch
@@ -4219,10 +4245,9 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
       }
       if (S_csr) {
         // tags of the exchange entries start from zero in every launch
-        e = launch_fill_zero(ws->xg, (size_t)ga.count * B * 4 * net.Wd[ga.j[0].l + 1] * sizeof(uint64_t), s);
+        e = launch_fill_zero(ws->xg, (size_t)ga.count * B * 4 * wd_max * sizeof(uint64_t), s);
         if (e != hipSuccess) return e;
-        const int Nc = net.N[ga.j[0].l];
-        const size_t lds_seq = seq_csr_lds(Nc, net.Wd[ga.j[0].l + 1]);
+        const size_t lds_seq = seq_csr_lds(n_max, wd_max);
         if (cj_fused.count) {
           unsigned gx = 0;
           for (int i = 0; i < cj_fused.count; ++i) {
@@ -4232,21 +4257,21 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
           }
           const size_t lds = lds_seq > SNN_FWD_STAGE_CSR_LDS ? lds_seq : SNN_FWD_STAGE_CSR_LDS;
           hipLaunchKernelGGL(k_fwd_stage_csr, dim3(B * S_csr * ga.count + gx * cj_fused.count), dim3(256), lds, s, net, ga, state,
-                             st, S_csr, reinterpret_cast<uint64_t *>(ws->xg), ws->err, ws->spin_limit, cj_fused, B * S_csr, (int)gx);
+                             st, S_csr, reinterpret_cast<uint64_t *>(ws->xg), wd_max, ws->err, ws->spin_limit, cj_fused, B * S_csr, (int)gx);
         } else {
           hipLaunchKernelGGL(k_layer_seq_csr_sl, dim3(B * S_csr, ga.count), dim3(256), lds_seq, s,
-                             net, ga, state, st, S_csr, reinterpret_cast<uint64_t *>(ws->xg), ws->err, ws->spin_limit);
+                             net, ga, state, st, S_csr, reinterpret_cast<uint64_t *>(ws->xg), wd_max, ws->err, ws->spin_limit);
         }
       } else if (ga.count && S > 1) {
         // tags of the exchange entries start from zero in every launch
-        e = launch_fill_zero(ws->xg, (size_t)ga.count * B * 4 * net.Wd[ga.j[0].l + 1] * sizeof(uint64_t), s);
+        e = launch_fill_zero(ws->xg, (size_t)ga.count * B * 4 * wd_max * sizeof(uint64_t), s);
         if (e != hipSuccess) return e;
         const size_t lds = seq_gather_lds(net);
         const dim3 grid(B * S, ga.count), block(th_sl);
         uint64_t *xw = reinterpret_cast<uint64_t *>(ws->xg);
 #define SEQ_CASE(NPT_)                                                                                         \
   case NPT_:                                                                                                    \
-    hipLaunchKernelGGL((k_layer_seq_gather_sl<NPT_>), grid, block, lds, s, net, ga, state, st, S, xw,          \
+    hipLaunchKernelGGL((k_layer_seq_gather_sl<NPT_>), grid, block, lds, s, net, ga, state, st, S, xw, wd_max,  \
                        ws->err, ws->spin_limit);                                                                \
     break;
         switch (npt_sl) {

@@ -351,6 +351,43 @@ def test_streamed_chip_wide_adjoint(hidden, B, T, monkeypatch):
         assert float(np.max(np.abs(a - b))) <= 1e-4 * scale
 
 
+@pytest.mark.parametrize("hidden,B,T,density,csr", [
+    ((1025,), 3, 70, 1.0, None),           # one neuron in the last spike word
+    ((1500, 1100), 5, 40, 1.0, None),      # two widths in one launch
+    ((2112, 300), 4, 30, 0.2, "0"),        # a narrow layer beside it
+    ((1030, 4100, 2600), 2, 24, 0.1, "1"),  # compressed rows: three numbers of slices in one launch, empty wavefronts
+    ((3000,), 3, 20, 0.1, None)])          # the walk a context takes before it knows a firing rate
+def test_sliced_sequential_forward_at_any_width(hidden, B, T, density, csr, monkeypatch):
+    """The sequential forward part of layers above 1024 neurons is spread over several workgroups per batch element at any
+    width, dense-stored or over compressed rows: spikes, potentials and gradients of the unsliced walk (SNN_SEQ_SLICES=1)
+    and of the oracle."""
+    w = synth.Workload("sl_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=0.5, rec_density=density,
+                       seed=101 + B)
+    d = synth.generate(w)
+    L = len(hidden)
+    if csr is not None:
+        monkeypatch.setenv("SNN_CSR", csr)
+    got = {}
+    for slices in (None, "1"):
+        if slices:
+            monkeypatch.setenv("SNN_SEQ_SLICES", slices)
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            states = net.snn_debug_states(w.T)
+            net.snn_bptt(snn.SNN_DOUBLE, 8, 3)
+            net.snn_bptt(snn.SNN_DOUBLE, 8, 3)
+            got[slices] = _gpu_grads(net, L), [net.snn_get_spikes(l, w.T) for l in range(L)], states
+        finally:
+            net.snn_destroy()
+    monkeypatch.delenv("SNN_SEQ_SLICES")
+    assert _identical(got[None][0], got["1"][0])
+    for a, b in zip(got[None][1], got["1"][1]):
+        assert np.array_equal(a, b)
+    assert np.array_equal(got[None][2], got["1"][2])
+    _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
+
+
 @pytest.mark.parametrize("hidden,B,T,force", [((2048, 2048), 3, 80, "0"), ((3072,), 3, 70, "0"), ((4096, 4096), 2, 20, "0"),
                                               ((512, 512), 5, 150, "8"), ((384,), 4, 100, "2")])
 def test_sliced_sequential_forward_is_bitwise_neutral(hidden, B, T, force, monkeypatch):
