@@ -1334,12 +1334,15 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
   float *ccache = p.n_cache_slots ? stage + (size_t)p.n_stage_slots * slot : nullptr; // currents of a coarse segment
   int cache_a = -1, cache_b = -1; // ccache holds the currents of steps (cache_a, cache_b], slot t - cache_a - 1
 
+  ZeroJobs clear{}; // everything that starts from zero, in one launch before the forward pass
   for (int l = 0; l < L; ++l) {
-    HIPCHK(c, launch_fill_zero(c->acc_in[l], (size_t)pre_of(n, l) * n.N[l] * 8, s));
-    if (dw_rec_csr(c, l)) HIPCHK(c, launch_fill_zero(c->acc_csr[l], c->csr_nnz[l] * 8, s));
-    else HIPCHK(c, launch_fill_zero(c->acc_rec[l], (size_t)n.N[l] * n.N[l] * 8, s));
+    clear.add(c->acc_in[l], (size_t)pre_of(n, l) * n.N[l] * 8);
+    if (dw_rec_csr(c, l)) clear.add(c->acc_csr[l], c->csr_nnz[l] * 8);
+    else clear.add(c->acc_rec[l], (size_t)n.N[l] * n.N[l] * 8);
   }
-  HIPCHK(c, launch_fill_zero(c->acc_out, (size_t)n.N[L - 1] * O * 8, s));
+  clear.add(c->acc_out, (size_t)n.N[L - 1] * O * 8);
+  clear.add(c->cur_state, Ms);                                                          // x_0
+  if (strategy == SNN_CHUNK || strategy == SNN_HIER) clear.add(lckpt, Ms);              // x_0 = checkpoint 0
 
   // events for the host tier
   const int n_load_ev = strategy == SNN_HIER ? p.n_local_ckpt / p.C : 2; // load slots (HIER: ring positions)
@@ -1379,9 +1382,9 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
       ev_spk[i] = tm.get(); ev_spk_go[i] = tm.get();
       if (!ev_spk[i] || !ev_spk_go[i]) return fail(c, SNN_E_HIP, "hipEventCreate failed");
     }
-    HIPCHK(c, launch_fill_zero(c->counters, 8 * (SNN_MAXL + 1), s));
+    clear.add(c->counters, 8 * (SNN_MAXL + 1));
     // step 0 of every hidden layer (all silent) sits at ring row 0
-    for (int l = 1; l <= L; ++l) HIPCHK(c, launch_fill_zero(c->mask_ring[l], (size_t)B * n.Wd[l] * 8, s));
+    for (int l = 1; l <= L; ++l) clear.add(c->mask_ring[l], (size_t)B * n.Wd[l] * 8);
     if (!remote) { // the copy stream joins this step also when the states take the direct tier
       ev_fork = tm.get(); ev_join = tm.get();
       if (!ev_fork || !ev_join) return fail(c, SNN_E_HIP, "hipEventCreate failed");
@@ -1392,13 +1395,12 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
   const FwdCallbacks cb_spk{&so, &SpikeOff::done};
 
   // ---- forward ------------------------------------------------------------------------------
-  HIPCHK(c, launch_fill_zero(c->cur_state, Ms, s)); // x_0
+  HIPCHK(c, launch_fill_zero_jobs(clear, s));
   if (strategy == SNN_STANDARD) {
     StoreSpec sp{chunk0, slot, 0, 1, 0, T, 0};
     const std::vector<int> bounds = tile_bounds(n, 0, T, T);
     HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, sp, c->readout, 1, c->dubuf, s, &hk, nullptr, &c->ws));
   } else if (strategy == SNN_CHUNK) {
-    HIPCHK(c, launch_fill_zero(lckpt, Ms, s)); // x_0
     StoreSpec sp{lckpt, slot, 0, p.F, 1, T - 1, 0};
     const std::vector<int> bounds = tile_bounds(n, 0, T, T);
     HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, sp, c->readout, 1, c->dubuf, s, &hk, nullptr, &c->ws));
@@ -1445,7 +1447,6 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
       hier.ready.push_back(tm.get()); hier.freed.push_back(tm.get()); hier.busy.push_back(0);
       if (!hier.ready.back() || !hier.freed.back()) return fail(c, SNN_E_HIP, "hipEventCreate failed");
     }
-    HIPCHK(c, launch_fill_zero(lckpt, Ms, s)); // x_0 = checkpoint 0
     StoreSpec sp{lckpt, slot, 0, p.F, 1, T - 1, RB * NL};
     const FwdCallbacks cb{&hier, &Hier::done};
     const std::vector<int> bounds = tile_bounds(n, 0, T, p.F);
@@ -1766,12 +1767,14 @@ static snn_status enqueue_step(snn_ctx *c, const Plan &p, snn_stats &st, Timer &
     const snn_status rs = pipe.flush();
     if (rs != SNN_OK) return rs;
   }
+  FinishJobs fin{};
   for (int l = 0; l < L; ++l) {
-    HIPCHK(c, launch_finish_grad(c->acc_in[l], nullptr, c->dW_in[l], (size_t)pre_of(n, l) * n.N[l], s));
+    fin.j[fin.count++] = FinishJob{c->acc_in[l], nullptr, c->dW_in[l], (size_t)pre_of(n, l) * n.N[l], 0u};
     if (dw_rec_csr(c, l)) HIPCHK(c, launch_finish_grad_csr(c->acc_csr[l], n.csr_sub[l], n.csr_col[l], n.N[l], c->dW_rec[l], s));
-    else HIPCHK(c, launch_finish_grad(c->acc_rec[l], c->rec_mask[l], c->dW_rec[l], (size_t)n.N[l] * n.N[l], s));
+    else fin.j[fin.count++] = FinishJob{c->acc_rec[l], c->rec_mask[l], c->dW_rec[l], (size_t)n.N[l] * n.N[l], 0u};
   }
-  HIPCHK(c, launch_finish_grad(c->acc_out, nullptr, c->dW_out, (size_t)n.N[L - 1] * O, s));
+  fin.j[fin.count++] = FinishJob{c->acc_out, nullptr, c->dW_out, (size_t)n.N[L - 1] * O, 0u};
+  HIPCHK(c, launch_finish_grads(fin, s));
   if (remote || R > 0) { // join the copy stream back
     HIPCHK(c, hipEventRecord(ev_join, cs));
     HIPCHK(c, hipStreamWaitEvent(s, ev_join, 0));

@@ -245,7 +245,10 @@ hipError_t launch_transpose(const float *src, float *dst, int rows, int cols, hi
 hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, hipStream_t s);
 hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t nnz, uint32_t *sub, uint16_t *col, float *val,
                            uint64_t *pk, hipStream_t s);
-hipError_t launch_finish_grad(const double *acc, const uint8_t *mask_or_null, float *dW, size_t n, hipStream_t s);
+// dW = the accumulators rounded to fp32, zero where a mask says so, for every matrix of a step in one launch
+struct FinishJob { const double *acc; const uint8_t *mask; float *dW; size_t n; unsigned first; }; // first: set by the launcher
+struct FinishJobs { FinishJob j[2 * SNN_MAXL + 1]; int count; };
+hipError_t launch_finish_grads(FinishJobs jobs, hipStream_t s);
 // The same for accumulators kept per existing synapse (compressed-row order): dW = 0 where no synapse exists.
 hipError_t launch_finish_grad_csr(const double *acc, const uint32_t *csr_sub, const uint16_t *csr_col, int N, float *dW,
                                   hipStream_t s);
@@ -253,6 +256,13 @@ hipError_t launch_unpack_spikes(const uint64_t *mask, int words, int N, int T, i
                                 hipStream_t s);
 hipError_t launch_count_spikes(const uint64_t *mask, size_t n_words, unsigned long long *count, hipStream_t s);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
+struct ZeroJob { void *p; size_t bytes; unsigned first; }; // first: set by the launcher
+struct ZeroJobs {
+  ZeroJob j[3 * SNN_MAXL + 5];
+  int count;
+  void add(void *p, size_t bytes) { if (bytes) j[count++] = ZeroJob{p, bytes, 0u}; }
+};
+hipError_t launch_fill_zero_jobs(ZeroJobs jobs, hipStream_t s);
 hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 bool snn_kernel_shape_ok(const NetDev &net, char *why, size_t why_len);
 

@@ -3700,10 +3700,19 @@ k_csr_fill(const uint8_t *__restrict__ mask, const float *__restrict__ W, int N,
   }
 }
 
-__global__ void k_finish_grad(const double *__restrict__ acc, const uint8_t *__restrict__ mask, float *__restrict__ dW,
-                              size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dW[i] = (mask && !mask[i]) ? 0.0f : (float)acc[i];
+// Gradients of every matrix with dense accumulators in one launch: a small network's step is a chain of launches, and the
+// matrices of a large one fill the chip either way.
+#define FIN_PER_BLOCK 1024
+__global__ void __launch_bounds__(256) k_finish_grads(FinishJobs jobs) {
+  int k = 0;
+  while (k + 1 < jobs.count && blockIdx.x >= jobs.j[k + 1].first) ++k;
+  const FinishJob &jb = jobs.j[k];
+  const size_t i0 = (size_t)(blockIdx.x - jb.first) * FIN_PER_BLOCK + threadIdx.x;
+#pragma unroll
+  for (int r = 0; r < FIN_PER_BLOCK / 256; ++r) {
+    const size_t i = i0 + 256 * r;
+    if (i < jb.n) jb.dW[i] = (jb.mask && !jb.mask[i]) ? 0.0f : (float)jb.acc[i];
+  }
 }
 
 __global__ void k_unpack(const uint64_t *__restrict__ mask, int words, int N, size_t TB, uint8_t *__restrict__ dst) {
@@ -3729,6 +3738,18 @@ __global__ void __launch_bounds__(256) k_copy(const float4 *__restrict__ src, fl
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) dst[i] = src[i];
 }
 
+// Several buffers in one launch, whole 16 bytes at a time (the buffers are allocations of their own or start at a multiple of
+// 16 bytes in one; what is left behind the last whole 16 bytes word by word).
+__global__ void __launch_bounds__(256) k_zero_jobs(ZeroJobs jobs) {
+  int k = 0;
+  while (k + 1 < jobs.count && blockIdx.x >= jobs.j[k + 1].first) ++k;
+  const ZeroJob &jb = jobs.j[k];
+  const unsigned nb = (k + 1 < jobs.count ? jobs.j[k + 1].first : gridDim.x) - jb.first;
+  const size_t stride = (size_t)nb * 256, i0 = (size_t)(blockIdx.x - jb.first) * 256 + threadIdx.x;
+  const size_t whole = ((uintptr_t)jb.p & 15) ? 0 : jb.bytes / 16;
+  for (size_t i = i0; i < whole; i += stride) reinterpret_cast<uint4 *>(jb.p)[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (size_t i = whole * 4 + i0; i < jb.bytes / 4; i += stride) reinterpret_cast<uint32_t *>(jb.p)[i] = 0u;
+}
 __global__ void k_zero(uint32_t *p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
@@ -5066,8 +5087,25 @@ hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t 
   return hipGetLastError();
 }
 
-hipError_t launch_finish_grad(const double *acc, const uint8_t *mask, float *dW, size_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_finish_grad, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, acc, mask, dW, n);
+hipError_t launch_finish_grads(FinishJobs jobs, hipStream_t s) {
+  unsigned blocks = 0;
+  for (int k = 0; k < jobs.count; ++k) {
+    jobs.j[k].first = blocks;
+    blocks += (unsigned)((jobs.j[k].n + FIN_PER_BLOCK - 1) / FIN_PER_BLOCK);
+  }
+  if (blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_finish_grads, dim3(blocks), dim3(256), 0, s, jobs);
+  return hipGetLastError();
+}
+hipError_t launch_fill_zero_jobs(ZeroJobs jobs, hipStream_t s) {
+  unsigned blocks = 0;
+  for (int k = 0; k < jobs.count; ++k) {
+    jobs.j[k].first = blocks;
+    const size_t want = (jobs.j[k].bytes + 256 * 16 * 4 - 1) / (256 * 16 * 4); // four rounds per thread up to 1024 workgroups
+    blocks += want < 1 ? 1u : want > 1024 ? 1024u : (unsigned)want;
+  }
+  if (blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_zero_jobs, dim3(blocks), dim3(256), 0, s, jobs);
   return hipGetLastError();
 }
 
