@@ -1593,7 +1593,15 @@ k_up_gemm(const float *__restrict__ A, int lda, const float *__restrict__ W, int
   up_gemm_body<WM, WN, BM, BN>(A, lda, W, K, N, C, ldc, M, (int)blockIdx.x, (int)blockIdx.y);
 }
 // Matrices from 2048 x 2048: 128 x 128 tiles (a rule on the layer's shape only, like the one for small matrices).
-static __host__ __device__ __forceinline__ bool up_gemm_big(int N, int K) { return N >= 2048 && K >= 2048; }
+// Tile of a product in front of a large matrix (0: 64 x 64, 1: 128 x 128, 2: 256 x 256): the largest that still gives nearly
+// every compute unit a workgroup.  256 from 192 of them (M = 1600, N = K = 8192: 2263 us, 128: 2362; M = 2048: 54 against 58 ms
+// per step at 1024-4x8192, T = 512; 256 x 128 with 8 wavefronts: 56), 128 from 256 (M = 1024, N = K = 2048, which has 128 of
+// them: 178 us, 64: 94).  The operations per element of the result are the same for every tile, so the choice may look at M.
+static int up_gemm_tile(int M, int N, int K) {
+  if (N < 2048 || K < 2048) return 0;
+  const auto tiles = [&](int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
+  return N >= 4096 && tiles(256) >= 192 ? 2 : tiles(128) >= 256 ? 1 : 0;
+}
 
 __device__ __forceinline__ void up_gemm16_body(const float *__restrict__ A, int lda, const float *__restrict__ W, int K,
                                                int N, float *__restrict__ C, int ldc, int M, int vblock) {
@@ -4433,8 +4441,8 @@ static hipError_t launch_up_gemm(const float *A, int lda, const float *W, int K,
   if (aligned16 && (size_t)N * K <= 65536) {
     const int tiles = ((M + 15) / 16) * ((N + 15) / 16);
     hipLaunchKernelGGL(k_up_gemm16, dim3((tiles + 3) / 4), dim3(256), 0, s, A, lda, W, K, N, C, N, M);
-  } else if (up_gemm_big(N, K)) {
-    if (N >= 4096 && M >= 2048)
+  } else if (const int tile = up_gemm_tile(M, N, K)) {
+    if (tile == 2)
       hipLaunchKernelGGL((k_up_gemm<4, 4, 2, 2>), dim3((M + 255) / 256, (N + 255) / 256), dim3(1024), 0, s, A, lda, W, K, N, C, N, M);
     else
       hipLaunchKernelGGL((k_up_gemm<2, 2, 2, 2>), dim3((M + 127) / 128, (N + 127) / 128), dim3(256), 0, s, A, lda, W, K, N, C, N, M);
@@ -5010,7 +5018,7 @@ static void plan_gemm(GemmJob *gj) {
     gj->kind = 0;
     gj->tiles_m = (gj->M + 15) / 16;
     gj->n_blocks = (gj->tiles_m * ((gj->N + 15) / 16) + 3) / 4;
-  } else if (up_gemm_big(gj->N, gj->K)) {
+  } else if (up_gemm_tile(gj->M, gj->N, gj->K)) {
     gj->kind = 2;
     gj->tiles_m = (gj->M + 127) / 128;
     gj->n_blocks = gj->tiles_m * ((gj->N + 127) / 128);
@@ -5039,10 +5047,7 @@ hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, cons
       // products of large matrices fill the chip by themselves and want the registers of the 128 x 128 tiles:
       // launches of their own, the fused launch keeps the rest
       const GemmJob &gj = ij.g[q];
-      // 256 x 256 tiles (16 wavefronts) where they still give a workgroup to every compute unit, else 128 x 128:
-      // 54 against 58 ms per step at configuration 4, T = 512 (256 x 128 with 8 wavefronts: 56; with 4: 62).  The
-      // operations per element of C are the same for every tile shape, so this choice may look at M.
-      if (gj.N >= 4096 && gj.M >= 2048)
+      if (up_gemm_tile(gj.M, gj.N, gj.K) == 2)
         hipLaunchKernelGGL((k_up_gemm<4, 4, 2, 2>), dim3((gj.M + 255) / 256, (gj.N + 255) / 256), dim3(1024), 0, s, gj.A, gj.lda,
                            gj.W, gj.K, gj.N, gj.C, gj.N, gj.M);
       else
