@@ -13,6 +13,7 @@
 //     ascending) that does not depend on where chunk boundaries fall;
 //   * no floating-point atomics anywhere.
 #include "snn_internal.h"
+#include "snn_split.h"
 #include <algorithm>
 #include <cmath>
 #include <stdlib.h>
@@ -1665,6 +1666,8 @@ __device__ __forceinline__ float surrogate(const NetDev &net, float v) {
 // to get here its workgroup has read everyone's values of step s - 1, and who wrote those had read step s - 2.  And
 // the cleared entries are in memory (vmcnt(0)) before the thread writes its values of step s + 1, so who has read
 // those and looks for values of step s + 2 cannot meet the old ones.
+// Whoever reads must therefore also write: a workgroup without values of its own is waited for by nobody, so it
+// leaves before the first step.
 static __device__ __forceinline__ uint32_t xenc(float v) {
   const uint32_t e = ~__float_as_uint(v);
   return e != 0u ? e : ~0x7fc00000u;
@@ -2628,6 +2631,8 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
   float *__restrict__ vbuf = jb.vbuf;
   const float *__restrict__ up = jb.up;
   const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, O = net.n_out, ldu = N;
+  const int n_act = csrw_active_blocks(N, n_rb); // row blocks that own rows: who reads the exchange also writes it
+  if (rb >= n_act) return;
   const uint32_t *__restrict__ sub = net.csr_sub[l];
   const uint16_t *__restrict__ col = net.csr_col[l];
   const float *__restrict__ val = net.csr_val[l];
@@ -2635,7 +2640,7 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
   const int nsub1 = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW + 1;
   // rows: the workgroup's [rb R, rb R + R), the wavefront's nr <= 64 consecutive ones from jw0; lane r keeps the
   // position of row jw0 + r
-  const int R = (N + n_rb - 1) / n_rb, nrw = (R + 15) / 16;
+  const int R = csrw_block_rows(N, n_rb), nrw = csrw_wave_rows(N, n_rb);
   const int row_end = (rb + 1) * R < N ? (rb + 1) * R : N;
   const int jw0 = rb * R + wave * nrw;
   const int jw1 = jw0 + nrw < row_end ? jw0 + nrw : row_end;
@@ -2657,7 +2662,7 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0)
     __syncthreads();
-    arrivals += (unsigned)n_rb;
+    arrivals += (unsigned)n_act;
     if (tid == 0 && !dead) {
       __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned spins = 0;
@@ -4545,7 +4550,7 @@ static int adj_csrw_resident() {
 static int adj_csrw_row_blocks(const NetDev &net, int count, int n_max) {
   const int n_bg = (net.B + 3) / 4;
   const int n_rb = (adj_csrw_resident() / (n_bg * count)) & ~7; // a multiple of 8: whole row blocks per die
-  if (n_rb < 8 || (n_max + n_rb - 1) / n_rb > 1024) return 0;   // a wavefront keeps the positions of at most 64 rows
+  if (n_rb < 8 || csrw_wave_rows(n_max, n_rb) > 64) return 0;   // a wavefront keeps the positions of at most 64 rows
   return n_rb;
 }
 static bool adj_csrw_ok(const NetDev &net, int l, const WsArgs &ws) {
