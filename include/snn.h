@@ -170,8 +170,16 @@ snn_status snn_forward_noalloc(snn_ctx *ctx, const uint8_t *in_spikes, const int
  *   T_Double's second recomputation then costs scans only) and, for networks whose layers all have more than 256
  *   neurons, as many further slots as the budget leaves, in whole coarse segments from the end of the
  *   sequence, in which the forward pass leaves the currents it computed, so that those segments' currents are
- *   not recomputed at all (without a budget: the last segment only).  Gradients are the same bit for bit
- *   either way, and stats reports what was allocated and how many steps' currents were recomputed. */
+ *   not recomputed at all (without a budget: the last segment only).  What is then left lets CHUNK, DOUBLE and HIER
+ *   walk the backward pass in chunks of several fine intervals, from every m-th checkpoint: m is the largest number
+ *   that fits whose chunk is no longer than the library's target (64 steps for networks with a layer above 1024
+ *   neurons, 256 for a single layer, between 16 and 256 with the square root of T otherwise) or, for DOUBLE, than a
+ *   coarse interval; for HIER m divides nb_local, and a transfer moves nb_local / m checkpoints over the same span of
+ *   time.  A budget of exactly snn_bytes_required runs the intervals asked for in the bytes it says.  Without a budget
+ *   the state storage of such a call can be m times that of the asked intervals with the chunk buffers above; where
+ *   the device has no room for it, a smaller m is taken, in the end the intervals asked for.  Gradients are the same
+ *   bit for bit either way, and stats reports the plan that ran: what was allocated, the checkpoints moved, and how
+ *   many steps' currents were recomputed. */
 snn_status snn_bptt(snn_ctx *ctx, snn_strategy strategy, int32_t coarse_interval, int32_t fine_interval,
                     size_t hbm_budget_bytes, snn_stats *stats_or_null);
 
@@ -218,7 +226,7 @@ snn_status snn_debug_currents(snn_ctx *ctx, const uint8_t *const *hidden, int32_
  * needed): M_s times the state count of eq. M_Base / M_Standard / M_Remote / M_Hier / M_Double plus the staging
  * slots of the host tier, plus the spike bitmasks and the per-chunk workspace.  Returns 0 for invalid arguments
  * and for shapes snn_init refuses.  Equals stats.bytes_states + bytes_spikes +
- * bytes_workspace of a call whose budget is exactly this number. */
+ * bytes_workspace of a call whose budget is exactly this number; a smaller budget is refused (SNN_E_BUDGET). */
 size_t snn_bytes_required(const snn_config *cfg, snn_strategy strategy, int32_t T, int32_t coarse_interval,
                           int32_t fine_interval);
 /* Number of M_s-sized state slots of that plan held in HBM (the paper's closed forms plus the
@@ -260,6 +268,9 @@ void snn_destroy(snn_ctx *ctx);
  *     SNN_RF_CACHE=0             Double: never keep a coarse segment's currents between its two recompute passes
  *     SNN_KEEP_CURRENTS=0        Double: the forward pass never leaves the currents of the last coarse segments in
  *                                that cache (default: as many whole segments as the budget has room for)
+ *     SNN_CHUNK_SPAN=0           the backward pass walks chunks of one fine interval, never of several
+ *     SNN_STATES_MAX=n           chunks of several fine intervals only below n bytes of state storage, as if the
+ *                                device had no room for more
  *     SNN_DW_CSR=0               tiled weight gradients of masked recurrent matrices over the dense tile, not per
  *                                existing synapse
  *     SNN_GRAPH=0                no HIP-graph replay of the training step

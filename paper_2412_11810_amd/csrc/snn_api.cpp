@@ -94,6 +94,8 @@ struct snn_ctx {
   bool rate_driven = false;     // some weight matrix is far beyond the L2: the current kernel follows the firing rates
   bool rf_cache = true;         // SNN_RF_CACHE=0: Double never keeps a segment's currents between its two recompute passes
   bool keep_currents = true;    // SNN_KEEP_CURRENTS=0: the forward pass never leaves currents in that cache
+  bool chunk_spans = true;      // SNN_CHUNK_SPAN=0: the backward pass walks chunks of one fine interval, as asked for
+  size_t states_max = ~(size_t)0; // chunks of several intervals: least state storage the device had no room for (SNN_STATES_MAX)
   std::string err;
   size_t Ms() const { return (size_t)cfg.batch * net.SN * sizeof(float); }
 };
@@ -407,6 +409,8 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
   if (const char *e = std::getenv("SNN_RF_CACHE")) c->rf_cache = std::strcmp(e, "0") != 0;
   if (const char *e = std::getenv("SNN_KEEP_CURRENTS")) c->keep_currents = std::strcmp(e, "0") != 0;
   if (const char *e = std::getenv("SNN_DW_CSR")) c->dw_csr = std::strcmp(e, "0") != 0;
+  if (const char *e = std::getenv("SNN_CHUNK_SPAN")) c->chunk_spans = std::strcmp(e, "0") != 0;
+  if (const char *e = std::getenv("SNN_STATES_MAX")) c->states_max = (size_t)std::strtoull(e, nullptr, 10);
   read_kernel_hooks(c);
   char buf[256];
   if (!snn_kernel_shape_ok(c->net, buf, sizeof buf)) return fail(c, SNN_E_INVAL, buf);
@@ -681,6 +685,23 @@ static snn_status ensure_work(snn_ctx *c, size_t bytes) {
   HIPCHK(c, hipMalloc(&c->dubuf, bytes));
   c->dubuf_bytes = bytes;
   return SNN_OK;
+}
+
+// State storage of a training step and its workspace, grown on demand.
+static snn_status ensure_states(snn_ctx *c, size_t states, size_t work) {
+  if (c->arena_bytes < states) {
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (c->arena) HIPCHK(c, hipFree(c->arena));
+    c->arena = nullptr; c->arena_bytes = 0;
+    const hipError_t e = hipMalloc(&c->arena, states);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      c->arena = nullptr;
+      return fail(c, SNN_E_HIP, std::string("state storage: ") + hipGetErrorString(e));
+    }
+    c->arena_bytes = states;
+  }
+  return ensure_work(c, work);
 }
 
 // The whole-sequence spike arrays in HBM, which the forward-only pass and the accessors work on.  A context with
@@ -1794,6 +1815,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   const int L = n.L;
   const size_t Ms = c->Ms();
   const int ring = spike_ring_steps(c->cfg, (int)strategy, T, p.C); // > 0: the hidden spike bitmasks live on the host tier
+  const int asked_slots = p.local_slots();
   // One chunk buffer per layer lets the adjoint pass run its layers one chunk apart (see BwdPipe).  The extra
   // (L - 1) * chunk_len state slots are taken only if the budget has room for them; the results are the same
   // bit for bit either way.
@@ -1838,44 +1860,47 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
       }
     }
   }
+  const size_t need_spikes = spike_bytes(n, T, ring);
+  const size_t need_asked = (size_t)p.local_slots() * Ms + work_bytes(n, p.chunk_len) + need_spikes;
+  if (budget && need_asked > budget) {
+    char buf[200];
+    snprintf(buf, sizeof buf, "needs %zu B of HBM activation memory (%d state slots), budget is %zu B", need_asked,
+             p.local_slots(), budget);
+    return fail(c, SNN_E_BUDGET, buf);
+  }
+  HIPCHK(c, hipSetDevice(c->cfg.device));
+  hipStream_t s = c->stream;
+  // ---- storage (before anything is queued or recorded) -----------------------------------------
   // Chunks of several fine intervals where what is left of the budget holds them (Chunk, Double, Hierarchical): the
   // backward pass then walks longer chunks from every m-th checkpoint.  Short intervals make it a series of launches
   // that are too small for the chip (a chunk of 10 steps of three 1024-wide layers costs 10 launches of 5-140 us, most
   // of the adjoint ones weight prologue); the results do not depend on where chunks are cut.  Hierarchical keeps its
-  // batches: the same span of time per transfer, so m divides nb_local.
-  if (c->bwd_pipeline && (strategy == SNN_CHUNK || strategy == SNN_DOUBLE || strategy == SNN_HIER)) {
+  // batches: the same span of time per transfer, so m divides nb_local.  Fewer checkpoints can make such a plan the
+  // smaller one: under a budget it is taken only from the asked intervals' own size on, so that a budget of exactly
+  // snn_bytes_required is used up by the plan it was computed for.  What the device has no room for is not taken.
+  if (c->bwd_pipeline && c->chunk_spans && (strategy == SNN_CHUNK || strategy == SNN_DOUBLE || strategy == SNN_HIER)) {
     const int target = bwd_tile_target(n, T), span = strategy == SNN_CHUNK ? T : strategy == SNN_DOUBLE ? p.C : p.C * p.F;
     for (int m = std::min(target / p.F, (span + p.F - 1) / p.F); m > 1; --m) {
       if (strategy == SNN_HIER && p.C % m != 0) continue;
       Plan q;
       if (!snn_make_plan((int)strategy, T, strategy == SNN_HIER ? p.C / m : p.C, std::min(p.F * m, std::min(span, T)), &q)) continue;
       q.n_chunk_bufs = p.n_chunk_bufs; q.n_cache_slots = p.n_cache_slots; q.keep_from = p.keep_from;
-      if (budget && (size_t)q.local_slots() * Ms + work_bytes(n, q.chunk_len) + spike_bytes(n, T, ring) > budget) continue;
+      const size_t states = (size_t)q.local_slots() * Ms, work = work_bytes(n, q.chunk_len);
+      if (budget && (q.local_slots() < asked_slots || states + work + need_spikes > budget)) continue;
+      if (states >= c->states_max) continue;
+      if (ensure_states(c, states, work) != SNN_OK) { // not tried again at every call
+        (void)hipGetLastError();
+        c->states_max = states;
+        continue;
+      }
       p = q;
       break;
     }
   }
   const size_t need_states = (size_t)p.local_slots() * Ms;
   const size_t need_work = work_bytes(n, p.chunk_len);
-  const size_t need_spikes = spike_bytes(n, T, ring);
-  if (budget && need_states + need_work + need_spikes > budget) {
-    char buf[200];
-    snprintf(buf, sizeof buf, "needs %zu B of HBM activation memory (%d state slots), budget is %zu B",
-             need_states + need_work + need_spikes, p.local_slots(), budget);
-    return fail(c, SNN_E_BUDGET, buf);
-  }
-  HIPCHK(c, hipSetDevice(c->cfg.device));
-  hipStream_t s = c->stream;
-  // ---- storage (before anything is queued or recorded) -----------------------------------------
-  if (c->arena_bytes < need_states) {
-    HIPCHK(c, hipStreamSynchronize(s));
-    if (c->arena) HIPCHK(c, hipFree(c->arena));
-    c->arena = nullptr; c->arena_bytes = 0;
-    HIPCHK(c, hipMalloc(&c->arena, need_states));
-    c->arena_bytes = need_states;
-  }
   {
-    snn_status rs = ensure_work(c, need_work);
+    snn_status rs = ensure_states(c, need_states, need_work);
     if (rs != SNN_OK) return rs;
   }
   const size_t need_host = (size_t)p.n_remote * Ms;

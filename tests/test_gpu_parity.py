@@ -537,6 +537,62 @@ def test_budget_and_argument_errors():
     net.snn_destroy()
 
 
+@pytest.mark.parametrize("strat,hidden,C,F", [(snn.SNN_CHUNK, (64,), 0, 7), (snn.SNN_CHUNK, (48, 300), 0, 10),
+                                              (snn.SNN_DOUBLE, (40,), 200, 3), (snn.SNN_HIER, (50, 30), 6, 4)])
+def test_chunks_of_several_intervals_respect_the_budget(strat, hidden, C, F, monkeypatch):
+    """Longer chunks than asked for are an extra: a budget below snn_bytes_required is refused also where they would fit
+    into it (fewer checkpoints), that very budget is used up by the intervals asked for, more room gives chunks in
+    between, and without a budget or room on the device what is left runs.  The same gradients each time."""
+    T = 1000
+    w = synth.Workload("spans_" + "x".join(map(str, hidden)), 30, hidden, 6, T=T, B=2, p_in=0.1, gain=0.8, seed=17)
+    d = synth.generate(w)
+    L, Ms = len(hidden), 4 * w.B * sum(hidden)
+
+    def run(budget, env=()):
+        for k, v in env:
+            monkeypatch.setenv(k, v)
+        net = snn.from_workload(w, d)
+        for k, _ in env:
+            monkeypatch.delenv(k)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], T)
+            st = net.snn_bptt(strat, C, F, budget)
+            grads = _gpu_grads(net, L)
+            net.snn_bptt(strat, C, F, budget, want_stats=False)  # recorded and replayed
+            assert _identical(_gpu_grads(net, L), grads)
+            return st, grads
+        finally:
+            net.snn_destroy()
+
+    total = lambda st: st.bytes_states + st.bytes_spikes + st.bytes_workspace
+    cfg = snn.make_config(w.n_in, list(hidden), w.n_out, T, w.B)
+    need, slots = snn.snn_bytes_required(cfg, strat, T, C, F), snn.snn_state_slots(strat, T, C, F)[0]
+    for less in (1, Ms, (slots - snn.snn_state_slots(strat, T, C, 2 * F)[0]) * Ms):
+        if 0 < less < need:
+            with pytest.raises(snn.SnnError) as e:
+                run(need - less)
+            assert e.value.status == snn.SNN_E_BUDGET
+    st, ref = run(need)
+    assert total(st) == need and st.local_state_slots == slots
+    asked, g = run(0, [("SNN_CHUNK_SPAN", "0")])
+    assert _identical(g, ref)
+    seen = [asked.local_state_slots]
+    for room in (need + 40 * Ms, need + 2000 * Ms, 0):
+        st, g = run(room)
+        assert _identical(g, ref) and (room == 0 or need <= total(st) <= room)
+        seen.append(st.local_state_slots)
+        if strat == snn.SNN_CHUNK and L == 1:  # one buffer: the plan of chunks of m F steps, m as large as fits
+            plans = [(snn.snn_state_slots(strat, T, 0, m * F)[0], snn.snn_bytes_required(cfg, strat, T, 0, m * F))
+                     for m in range(1, 256 // F + 1)]
+            assert st.local_state_slots == [k for k, b in plans if k >= slots and (room == 0 or b <= room)][-1]
+    assert seen[-1] > seen[0]
+    # a device with no room for any longer chunk, and for some
+    st, g = run(0, [("SNN_STATES_MAX", "1")])
+    assert _identical(g, ref) and st.local_state_slots == asked.local_state_slots
+    st, g = run(0, [("SNN_STATES_MAX", str(seen[-1] * Ms))])
+    assert _identical(g, ref) and st.local_state_slots < seen[-1]
+
+
 def test_graph_replay_follows_a_change_of_the_recurrent_mask():
     """A recorded training step holds the pointers it was recorded with, the recurrent mask among them.  Setting
     weights (with a mask, then without) between replays must give what an eager step gives, bit for bit: masked
