@@ -583,8 +583,8 @@ snn_status snn_set_weights(snn_ctx *c, int kind, int layer, const float *w, cons
     c->graph_exec = nullptr;
   }
   const size_t ne = (size_t)rows * cols;
-  // mask and weights of the compressed rows may have been produced on the caller's default stream (see snn_bind_inputs)
-  if (mask && c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr));
+  // weights and mask may have been produced on the caller's default stream (see snn_bind_inputs)
+  if (c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr));
   HIPCHK(c, hipMemcpyAsync(dst, w, ne * 4, hipMemcpyDefault, c->stream));
   HIPCHK(c, launch_transpose(dst, dstT, rows, cols, c->stream));
   if (kind == SNN_W_REC) {

@@ -668,6 +668,45 @@ def test_shorter_sequence_in_same_context_and_device_inputs():
     net.snn_destroy()
 
 
+def _busy(torch):
+    """Some tens of milliseconds of work on torch's default stream."""
+    a = torch.ones((4096, 4096), device="cuda")
+    for _ in range(40):
+        a = (a @ a).clamp_(0.0, 1.0)
+    return a
+
+
+def test_weights_still_being_written_on_the_default_stream():
+    """An optimiser's update queued on the default stream just before snn_set_weights is what the context gets, for every
+    kind of matrix, with a mask or without one: the library's own stream does not wait for the default stream by itself."""
+    torch = pytest.importorskip("torch")
+    w = synth.Workload("late_30-70-40-6", 30, (70, 40), 6, T=30, B=3, p_in=0.2, gain=0.9, rec_density=0.5, seed=19)
+    d = synth.generate(w)
+    dev = lambda a: torch.tensor(a, device="cuda")
+    mask = dev(d["rec_mask"][1].astype(np.uint8))
+    for kind, layer, key, m in ((snn.SNN_W_IN, 1, "W_in", None), (snn.SNN_W_REC, 0, "W_rec", None),
+                                (snn.SNN_W_REC, 1, "W_rec", mask), (snn.SNN_W_OUT, 0, "W_out", None)):
+        new = d[key] if key == "W_out" else d[key][layer]
+        got = []
+        for late in (False, True):
+            net = snn.from_workload(w, d)
+            try:
+                buf, target = torch.zeros(new.shape, device="cuda"), dev(1.5 * new.astype(np.float32))
+                torch.cuda.synchronize()
+                if late:
+                    keep = _busy(torch)
+                buf.copy_(target)
+                if not late:
+                    torch.cuda.synchronize()
+                net.snn_set_weights(kind, layer, buf, m)
+                net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+                net.snn_bptt(snn.SNN_STANDARD)
+                got.append((_gpu_grads(net, 2), net.snn_get_readout()[0]))
+            finally:
+                net.snn_destroy()
+        assert _identical(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1]), (kind, layer)
+
+
 def test_graph_replay_matches_eager():
     """snn_bptt without statistics replays a recorded HIP graph.  Every replay must give exactly what
     the eager (instrumented) call gives, also after other work ran in between and after the plan changed."""
