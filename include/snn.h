@@ -26,7 +26,8 @@
  *
  * Conventions.  Every function returns an snn_status (0 = success) unless noted;
  * nothing throws or aborts.  Pointers marked "host or device" may be either (the
- * library asks the HIP runtime which).  The caller owns every buffer it passes and
+ * library asks the HIP runtime which); a context on a stream of the library's own waits for
+ * the device's default stream before it touches them.  The caller owns every buffer it passes and
  * keeps it alive for the duration of the call.  All calls on one context must come
  * from one thread at a time.  All functions return after the work they queued on the
  * context's stream (and on the library's private copy stream) has completed.

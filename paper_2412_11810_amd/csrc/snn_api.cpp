@@ -842,6 +842,7 @@ snn_status snn_get_state(snn_ctx *c, int layer, int32_t t, float *dst) {
   if (c->T_spikes < 1) return fail(c, SNN_E_STATE, "no forward pass since the inputs were bound");
   if (t < 1 || t > c->T_spikes) return fail(c, SNN_E_INVAL, "t outside 1..T");
   HIPCHK(c, hipSetDevice(c->cfg.device));
+  if (c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr)); // dst: as in snn_grads
   read_kernel_hooks(c);
   {
     const snn_status rm = ensure_full_masks(c);
@@ -900,6 +901,7 @@ snn_status snn_get_readout(snn_ctx *c, float *ubar, float *loss) {
 snn_status snn_debug_copy(snn_ctx *c, const void *src, void *dst, size_t bytes) {
   if (!c || !src || !dst) return fail(c, SNN_E_INVAL, "null argument");
   HIPCHK(c, hipSetDevice(c->cfg.device));
+  if (c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr)); // src and dst: as in snn_set_weights and snn_grads
   HIPCHK(c, launch_copy(src, dst, bytes, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return SNN_OK;
@@ -974,6 +976,8 @@ snn_status snn_grads(snn_ctx *c, int kind, int layer, float *dst, size_t n_elems
   } else return fail(c, SNN_E_INVAL, "bad tensor kind/layer");
   if (ne != n_elems) return fail(c, SNN_E_INVAL, "n_elems does not match the tensor");
   HIPCHK(c, hipSetDevice(c->cfg.device));
+  // work queued on the caller's default stream may still read what dst held (see snn_bind_inputs)
+  if (c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr));
   HIPCHK(c, hipMemcpyAsync(dst, src, ne * 4, hipMemcpyDefault, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return SNN_OK;

@@ -707,6 +707,39 @@ def test_weights_still_being_written_on_the_default_stream():
         assert _identical(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1]), (kind, layer)
 
 
+def test_gradients_still_being_read_on_the_default_stream():
+    """Gradients accumulated over two steps through one buffer: the addition of the first step's values, still queued on the
+    default stream when snn_grads (or snn_get_state) writes the second step's into the buffer, must see the first step's."""
+    import ctypes
+    torch = pytest.importorskip("torch")
+    w = synth.Workload("accum_30-70-6", 30, (70,), 6, T=30, B=3, p_in=0.2, gain=0.9, seed=29)
+    d = synth.generate(w)
+    net = snn.from_workload(w, d)
+    lib = snn.lib()
+    calls = {"grads": (70 * 70, lambda p: lib.snn_grads(net._h, snn.SNN_W_REC, 0, p, 70 * 70)),
+             "state": (w.B * 70, lambda p: lib.snn_get_state(net._h, 0, w.T, p))}
+    try:
+        for name, (n, call) in calls.items():
+            got = []
+            for late in (False, True):
+                buf, total = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+                for x in (d["in_spikes"], np.ascontiguousarray(1 - d["in_spikes"])):
+                    net.snn_bind_inputs(x, d["labels"], w.T)
+                    net.snn_bptt(snn.SNN_STANDARD)
+                    if late:  # (after the calls above, which wait by themselves)
+                        keep = _busy(torch)
+                    total += buf  # of the step before
+                    if not late:
+                        torch.cuda.synchronize()
+                    assert call(ctypes.c_void_p(buf.data_ptr())) == snn.SNN_OK
+                total += buf
+                torch.cuda.synchronize()
+                got.append(total.cpu().numpy())
+            assert np.array_equal(got[0], got[1]) and got[0].any(), name
+    finally:
+        net.snn_destroy()
+
+
 def test_graph_replay_matches_eager():
     """snn_bptt without statistics replays a recorded HIP graph.  Every replay must give exactly what
     the eager (instrumented) call gives, also after other work ran in between and after the plan changed."""
