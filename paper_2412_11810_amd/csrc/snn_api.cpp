@@ -539,8 +539,7 @@ void snn_destroy(snn_ctx *c) {
   for (int l = 0; l < SNN_MAXL; ++l) {
     (void)hipFree(c->W_in[l]); (void)hipFree(c->W_inT[l]); (void)hipFree(c->W_recT[l]);
     (void)hipFree(c->dW_in[l]); (void)hipFree(c->dW_rec[l]); (void)hipFree(c->rec_mask[l]);
-    (void)hipFree(c->csr_sub[l]); (void)hipFree(c->csr_col[l]); (void)hipFree(c->csr_val[l]);
-    (void)hipFree(c->csr_pk[l]);
+    free_csr(c, l);
     (void)hipFree(c->acc_in[l]); (void)hipFree(c->acc_rec[l]);
   }
   for (int l = 0; l <= SNN_MAXL; ++l) { (void)hipFree(c->mask_full[l]); (void)hipFree(c->mask_ring[l]); }
