@@ -10,6 +10,7 @@ if ROOT not in sys.path:
 
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (runs the HIP library)")
+    config.addinivalue_line("markers", "library_chunks: lets the library walk chunks of several intervals (its default)")
 
 
 @pytest.fixture(scope="session", autouse=True)

@@ -3,6 +3,8 @@
 Bar: spike trains bit-exact (mismatches tolerated only at steps where the oracle's |v - theta| < 1e-5;
 they are counted and printed -- with the shared summation order the expected count is 0); fp32
 gradients within 1e-4 of max|grad| per tensor; all GPU strategies bit-identical to each other."""
+import os
+
 import numpy as np
 import pytest
 
@@ -14,6 +16,15 @@ pytestmark = pytest.mark.gpu
 snn = pytest.importorskip("paper_2412_11810_amd")
 
 GRAD_TOL = 1e-4
+
+
+@pytest.fixture(autouse=True)
+def _intervals_as_asked(request, monkeypatch):
+    """The tests name short intervals to cross many chunk boundaries in few steps.  With room to spare the library walks
+    chunks of several intervals instead, often the whole of a short sequence: that is left to the tests marked
+    library_chunks and to a pass of its own in _full_parity."""
+    if not request.node.get_closest_marker("library_chunks"):
+        monkeypatch.setenv("SNN_CHUNK_SPAN", "0")
 
 
 def _oracle(w, d, **kw):
@@ -110,9 +121,22 @@ def _full_parity(w, strategies, nthreads=8, check_states=True, window=0.0, probe
             assert st.fwd_steps == w.T and st.bwd_steps == w.T
             rates = [float(ref.spikes[l].mean()) for l in range(len(w.n_hidden))]
             assert np.allclose(list(st.firing_rate)[:len(rates)], rates, atol=1e-6)
-        return first, ref
     finally:
         net.snn_destroy()
+    # the same intervals with the library's chunks of several of them
+    spans = os.environ.pop("SNN_CHUNK_SPAN", None)
+    net = snn.from_workload(w, d, surr_window=window)
+    try:
+        net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+        for strat, C, F in strategies:
+            if strat in (snn.SNN_CHUNK, snn.SNN_DOUBLE, snn.SNN_HIER):
+                net.snn_bptt(strat, C, F)
+                assert _identical(_gpu_grads(net, len(w.n_hidden)), first), f"{w.name} strat={strat} C={C} F={F}: longer chunks"
+    finally:
+        net.snn_destroy()
+        if spans is not None:
+            os.environ["SNN_CHUNK_SPAN"] = spans
+    return first, ref
 
 
 def test_hand_trace_on_gpu():
@@ -327,12 +351,15 @@ def test_chip_wide_adjoint_any_width_up_to_2048(hidden, B, T, monkeypatch):
         assert float(np.max(np.abs(a - b))) <= 2e-5 * (float(np.max(np.abs(b))) or 1.0)
 
 
-@pytest.mark.parametrize("hidden,B,T", [((1088,), 5, 14), ((1152, 1088), 20, 10), ((1088,), 40, 8), ((4096,), 3, 9)])
+@pytest.mark.parametrize("hidden,B,T", [((1088,), 5, 14), ((1152, 1088), 20, 10), ((1088,), 40, 8), ((4096,), 3, 9),
+                                        ((2112,), 5, 14), ((2176, 2112), 20, 10), ((2112,), 40, 8), ((4096,), 20, 9),
+                                        ((4096,), 33, 8)])
 def test_streamed_chip_wide_adjoint(hidden, B, T, monkeypatch):
-    """Layers wider than 1024 neurons: the recurrence of the adjoint streams W_rec once per step for the whole
-    batch (matrix cores, workgroups of 16 or 32 rows, batch in 1, 2 or 4 blocks of 16, a reduction range that is
-    not a multiple of the prefetch ring).  Against the oracle, bit-identical between strategies, and within the
-    tolerance of the one-workgroup-per-batch-element kernel it replaces."""
+    """Dense-stored layers wider than 2048 neurons whose width is a multiple of 64: the recurrence of the adjoint streams
+    W_rec once per step for the whole batch (matrix cores, workgroups of 16 rows or, from 4096 neurons, 32, batch in 1, 2
+    or 4 blocks of 16, a reduction range that is not a multiple of the prefetch ring).  Narrower ones (1088, 1152) keep
+    the matrix in registers.  Against the oracle, bit-identical between strategies, and within the tolerance of the
+    one-workgroup-per-batch-element kernel."""
     w = synth.Workload("wide_" + "x".join(map(str, hidden)), 40, hidden, 7, T=T, B=B, p_in=0.1, seed=31 + B)
     first, _ = _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 4), (snn.SNN_DOUBLE, 8, 3)], nthreads=4)
     monkeypatch.setenv("SNN_WS_KERNEL", "stream")
@@ -391,7 +418,7 @@ def test_sliced_sequential_forward_at_any_width(hidden, B, T, density, csr, monk
 @pytest.mark.parametrize("hidden,B,T,force", [((2048, 2048), 3, 80, "0"), ((3072,), 3, 70, "0"), ((4096, 4096), 2, 20, "0"),
                                               ((512, 512), 5, 150, "8"), ((384,), 4, 100, "2")])
 def test_sliced_sequential_forward_is_bitwise_neutral(hidden, B, T, force, monkeypatch):
-    """Layers of 2048 neurons and more (narrower ones when SNN_SEQ_SLICES asks for it: 64-thread and 192-thread
+    """Layers of more than 1024 neurons (narrower ones when SNN_SEQ_SLICES asks for it: 64-thread and 192-thread
     workgroups): the sequential part of the forward pass spreads the neurons
     of a batch element over several workgroups that exchange their spike words every step.  Spike trains, membrane
     potentials and gradients must be the very bits of the one-workgroup-per-batch-element kernel, and match the
@@ -492,6 +519,7 @@ def test_config3_width_reduced_length():
     _full_parity(w, [(snn.SNN_CHUNK, 0, 27), (snn.SNN_DOUBLE, 316, 18)], nthreads=4, check_states=False)
 
 
+@pytest.mark.library_chunks
 def test_budget_and_argument_errors():
     w = synth.config(0)
     d = synth.generate(w)
@@ -537,6 +565,7 @@ def test_budget_and_argument_errors():
     net.snn_destroy()
 
 
+@pytest.mark.library_chunks
 @pytest.mark.parametrize("strat,hidden,C,F", [(snn.SNN_CHUNK, (64,), 0, 7), (snn.SNN_CHUNK, (48, 300), 0, 10),
                                               (snn.SNN_DOUBLE, (40,), 200, 3), (snn.SNN_HIER, (50, 30), 6, 4)])
 def test_chunks_of_several_intervals_respect_the_budget(strat, hidden, C, F, monkeypatch):
@@ -627,6 +656,7 @@ def test_graph_replay_follows_a_change_of_the_recurrent_mask():
         net.snn_destroy()
 
 
+@pytest.mark.library_chunks
 def test_suggested_intervals_train_within_the_budget():
     """Intervals picked by snn_suggest_intervals for a budget: the step runs inside that budget and gives the
     gradients of full storage bit for bit."""
@@ -915,14 +945,13 @@ def test_event_driven_step_of_narrow_layers_is_bitwise_neutral(monkeypatch):
     _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 7)], nthreads=2)
 
 
-@pytest.mark.parametrize("width,density", [(512, 1.0), (2048, 1.0), (1088, 1.0), (2048, 0.2)])
+@pytest.mark.parametrize("width,density", [(512, 1.0), (2048, 1.0), (1088, 1.0), (2048, 0.2), (2112, 1.0)])
 def test_barrier_timeout_is_reported_not_hung(monkeypatch, width, density):
-    """The chip-wide adjoint kernels of wide layers (weights in registers up to 1024 neurons, streamed
-    above, over compressed rows for a masked matrix) and the sliced sequential part of their forward pass (widths from 2048 that are multiples of 1024)
-    synchronise their workgroups with a counting barrier
-    that polls a bounded number of times.  With the limit forced to zero from the host every workgroup
-    gives up at its first barrier: all kernels still run to completion, and snn_bptt reports the
-    failure instead of returning gradients.  A context created afterwards works normally."""
+    """The chip-wide adjoint kernels of wide layers (weights in registers up to 2048 neurons, streamed above, over
+    compressed rows for a masked matrix above 1024) and the sliced sequential part of the forward pass above 1024 neurons
+    wait for each other's values, or in a counting barrier, in loops that poll a bounded number of times.  With the limit
+    forced to zero from the host every workgroup gives up at its first wait: all kernels still run to completion, and
+    snn_bptt reports the failure instead of returning gradients.  A context created afterwards works normally."""
     w = synth.Workload(f"wide_24-{width}-6", 24, (width,), 6, T=12, B=4, p_in=0.1, rec_density=density, seed=11)
     d = synth.generate(w)
     monkeypatch.setenv("SNN_WS_SPIN_LIMIT", "0")
@@ -1060,17 +1089,20 @@ def _full_size_properties(idx, strategies, budget, prefix):
         net.snn_destroy()
 
 
+@pytest.mark.library_chunks
 def test_config2_full_size_properties():
     """Configuration 2 (700 -> 3x1024 -> 20, T = 10 000, batch 64) under its 8 GB budget: Double(100, 10)
     as the configuration says, Chunk(100) and Remote(100) for comparison."""
     _full_size_properties(2, [(snn.SNN_DOUBLE, 100, 10), (snn.SNN_CHUNK, 0, 100), (snn.SNN_REMOTE, 100, 0)], 8 * 10**9, 150)
 
 
+@pytest.mark.library_chunks
 def test_config3_full_size_properties():
     """Configuration 3 (128 -> 2x512 -> 10, T = 100 000, batch 16) under its 4 GB budget: Double(316, 18)."""
     _full_size_properties(3, [(snn.SNN_DOUBLE, 316, 18), (snn.SNN_CHUNK, 0, 316)], 4 * 10**9, 1500)
 
 
+@pytest.mark.library_chunks
 def test_config4_full_size_properties():
     """Configuration 4 (1024 -> 4x8192 -> 100, T = 5000, batch 32, recurrent matrices 90 % zero) as the benchmark
     times it: Double(512, 64) under the 32 GB budget (the forward pass's currents kept, stage launches over compressed
@@ -1093,7 +1125,7 @@ def test_config4_widths_short():
                                                      ((1536,), 2, 16, 0.9, 0.5)])
 def test_compressed_rows_of_masked_matrices_are_bitwise_neutral(hidden, B, T, density, gain, monkeypatch):
     """A masked recurrent matrix is also kept as compressed rows (only the synapses that exist), and the kernels
-    that gather its rows walk those (recompute; from 2048 neurons also the sequential part of the forward pass).
+    that gather its rows walk those (recompute; above 1024 neurons also the sequential part of the forward pass).
     Adding +0.0f where no synapse exists changes nothing, so spike trains, membrane potentials -- the forward
     pass's and the recomputed ones -- and gradients must be the very bits of the dense-stored walk (SNN_CSR=0), and
     match the oracle.  Widths: one sub-range, several, a ragged last one, a row with more than 64 entries in a
@@ -1241,11 +1273,11 @@ def test_compressed_rows_follow_the_mask(N, host, monkeypatch):
     ((4096, 4096), 8, 10, 0.1, 0.0),   # two batch groups
     ((2048,), 2, 9, 0.9, 0.0),         # rows of ~1840 entries: more than one pass of 14 x 64
     ((2048, 256), 6, 12, 0.2, 0.0),    # a narrow layer beside it (weights in registers)
-    ((3072,), 4, 10, 0.15, 0.5)])      # under a surrogate window, forced (the library would list rows)
+    ((3072,), 4, 10, 0.15, 0.5)])      # under a surrogate window
 def test_chip_wide_adjoint_over_compressed_rows(hidden, B, T, density, window, monkeypatch):
     """Wide layers (more than 1024 neurons) with a masked recurrent matrix run the adjoint recurrence chip-wide over
     the compressed rows: four batch elements per workgroup with their dv_{t+1} in LDS, rows dealt to wavefronts,
-    a barrier per batch group and step.  A row is summed in the order of the rows kernel (lane-strided, two
+    an exchange per batch group and step.  A row is summed in the order of the rows kernel (lane-strided, two
     accumulators, butterfly), so the gradients must be the very bits of that kernel evaluating every row
     (SNN_WS_KERNEL=rows_all); they must agree with the dense-stored chip-wide kernel (SNN_CSR=0) within the gradient
     tolerance, and match the oracle under every strategy."""
