@@ -1161,8 +1161,9 @@ struct SpikeOff {
       }
     }
     if (layer == n.L - 1) {
-      // everything that reads rows up to the START of the tile the top layer just finished has been queued
-      // (the readout currents of a tile are computed one stage after the top layer's sequential part)
+      // Every recurrent part that reads rows up to the START of the tile the top layer just finished has been queued.
+      // The readout currents of up to SNN_FWD_TILE steps more may still be due: they read the top layer's rows, which
+      // stay in the ring until that layer itself is R (more than 1600) steps further, on this stream as well.
       e = q.issue_upto(q.top_prev_end);
       if (e != hipSuccess) return e;
       q.top_prev_end = t_end;

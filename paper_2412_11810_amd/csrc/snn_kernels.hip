@@ -1593,7 +1593,6 @@ k_up_gemm(const float *__restrict__ A, int lda, const float *__restrict__ W, int
           int ldc, int M) {
   up_gemm_body<WM, WN, BM, BN>(A, lda, W, K, N, C, ldc, M, (int)blockIdx.x, (int)blockIdx.y);
 }
-// Matrices from 2048 x 2048: 128 x 128 tiles (a rule on the layer's shape only, like the one for small matrices).
 // Tile of a product in front of a large matrix (0: 64 x 64, 1: 128 x 128, 2: 256 x 256): the largest that still gives nearly
 // every compute unit a workgroup.  256 from 192 of them (M = 1600, N = K = 8192: 2263 us, 128: 2362; M = 2048: 54 against 58 ms
 // per step at 1024-4x8192, T = 512; 256 x 128 with 8 wavefronts: 56), 128 from 256 (M = 1024, N = K = 2048, which has 128 of
@@ -2592,7 +2591,7 @@ k_adj_rec_rows(NetDev net, AdjJobs jobs, float *__restrict__ carry, int list_all
 // wavefronts in contiguous runs; a wavefront evaluates a row like k_adj_rec_rows does -- entries lane-strided, two
 // accumulators taking alternate groups of 64 entries, then wave_sum over the lanes: the same order, so the
 // same bits as that kernel listing every row -- with all entries of the next row requested before the products of
-// the current one (the first row of the next step before the step's barrier: the matrix does not change).  Lane r
+// the current one (the first row of the next step before the step's exchange: the matrix does not change).  Lane r
 // then finishes row r for the four batch elements and writes dv_t as one float4 into the exchange buffer
 // [step & 3][batch group][N][4] (values encoded by xenc, see there: no barrier, the batch groups never wait for each
 // other), from where every workgroup reloads its group's slice into LDS: against a counting barrier per step two layers
@@ -3606,7 +3605,6 @@ __global__ void k_transpose(const float *__restrict__ src, float *__restrict__ d
     if (x < rows && y + i < cols) dst[(size_t)(y + i) * rows + x] = tile[threadIdx.x][threadIdx.y + i];
 }
 
-// fp64 accumulator -> fp32 gradient; a masked matrix has a gradient only where a synapse exists
 // Compressed rows of a masked recurrent matrix (layout: NetDev::csr_sub), built from the mask and the weights in HBM: one
 // pass over the mask counts, a scan over the rows places them, a second pass writes the entries.  Reads 2 N^2 mask bytes
 // and the weights once: bound by memory and launches (2048^2 at 10 % density: 22 us in three
@@ -3713,7 +3711,8 @@ k_csr_fill(const uint8_t *__restrict__ mask, const float *__restrict__ W, int N,
   }
 }
 
-// Gradients of every matrix with dense accumulators in one launch: a small network's step is a chain of launches, and the
+// fp64 accumulator -> fp32 gradient; a masked matrix has a gradient only where a synapse exists.  Every matrix with dense
+// accumulators in one launch: a small network's step is a chain of launches, and the
 // matrices of a large one fill the chip either way.
 #define FIN_PER_BLOCK 1024
 __global__ void __launch_bounds__(256) k_finish_grads(FinishJobs jobs) {
@@ -4154,7 +4153,8 @@ static int seq_csr_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws
   // context's firing-rate policy has picked the gather over compressed rows for the recompute or, at higher
   // activity, for this walk alone (cur_pol 1, 3, 4), or wherever the hook asks.  Before any rate is known (a context's
   // first step, or one that only runs forward passes): where that policy would pick it at every activity, i.e. matrices
-  // of 32 MB and more at a density of at most 1/8.
+  // of 32 MB and more at a density of at most 1/8.  The launch's widest layer decides about the size: its jobs share one
+  // kernel, and the other choice would send that layer's matrix through the dense-stored walk as well.
   int N = 0, Wd = 0;
   for (int i = 0; i < ga.count; ++i) {
     const int l = ga.j[i].l;
@@ -4440,8 +4440,9 @@ hipError_t launch_loss(const double *readout, const int32_t *labels, int B, int 
 
 static hipError_t launch_up_gemm(const float *A, int lda, const float *W, int K, int N, float *C, int M,
                                  hipStream_t s) {
-  // The choice of kernel may depend on the layer's shape and on alignments that are the same for every
-  // tile (lda % 4 == 0 makes the alignment of A independent of the slot it starts at), never on M.
+  // Which of the two kernels runs may depend on the layer's shape and on alignments that are the same for every time
+  // tile (lda % 4 == 0 makes the alignment of A independent of the slot it starts at), never on M: they add in different
+  // orders.  The tile of the LDS kernel may depend on M: every tile adds in the same order (see up_gemm_tile).
   const bool aligned16 = K % 16 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
   if (aligned16 && (size_t)N * K <= 65536) {
     const int tiles = ((M + 15) / 16) * ((N + 15) / 16);
@@ -5015,8 +5016,7 @@ hipError_t launch_bwd_stage(const NetDev &net, const AdjJobs &jobs, float *carry
   return hipGetLastError();
 }
 
-// Fills kind / n_blocks / tiles_m of an inter-layer product by the same rule as launch_up_gemm (shapes and
-// tile-independent alignments only).
+// Fills kind / n_blocks / tiles_m of an inter-layer product by the same rules as launch_up_gemm.
 static void plan_gemm(GemmJob *gj) {
   const bool aligned16 = gj->K % 16 == 0 && gj->lda % 4 == 0 && ((uintptr_t)gj->A & 15) == 0 && ((uintptr_t)gj->W & 15) == 0;
   if (aligned16 && (size_t)gj->N * gj->K <= 65536) {
