@@ -252,6 +252,8 @@ def main():
     y = torch.from_numpy(d["labels"]).to(dev)
     if args.host_inputs:  # the library copies them to the device inside snn_bind_inputs, every step
         x, y = d["in_spikes"], d["labels"]
+    if args.sweep:  # the study is about chunks as long as asked for
+        os.environ["SNN_CHUNK_SPAN"] = "0"
     net = snn.from_workload(w, d, surr_window=args.surr_window, spike_tier=args.spike_tier)  # stream = None: the library runs on a stream of its own
     params = dict(STRATEGY_PARAMS[args.config])
     if args.coarse >= 0 or args.fine >= 0:
@@ -410,14 +412,22 @@ def main():
     C, F = params[args.strategy]
     slots, rslots = snn.snn_state_slots(SID[args.strategy], w.T, C, F)
     sched = snn.snn_schedule(SID[args.strategy], w.T, C, F)
-    n_bwd = max(1, sum(-(-(o[1] - o[2] + 1) // 256) for o in sched if o[0] == "BACKWARD"))  # adjoint tiles of <= 256 steps
+    # adjoint tiles, as long as the library's target (chunks as asked for: with room the library walks several in one)
+    L, nmax = len(w.n_hidden), max(w.n_hidden)
+    bwd_tile = 256 if L == 1 else 64 if nmax > 1024 else max(16, min(256, int((w.T * (16.0 if nmax <= 256 else 4.0) / (L - 1)) ** 0.5)))
+    n_bwd = max(1, sum(-(-(o[1] - o[2] + 1) // bwd_tile) for o in sched if o[0] == "BACKWARD"))
     Ms = 4 * w.B * w.neurons
     tier = os.environ.get("SNN_HOST_TIER", "")
     host_direct = args.strategy in ("remote", "double") and tier != "dma" and (tier == "direct" or Ms <= (1 << 20))
     seg = C if (args.strategy in ("remote", "double") and not host_direct) else (F if args.strategy == "hier" else w.T)
-    n_tiles = sum(-(-(min(a + seg, w.T) - a) // 64) for a in range(0, w.T, seg))   # forward tiles of <= 64 steps
+    # forward tiles: the length whose launches cost least, 64 steps unless another is clearly better (the library's rule)
+    fwd_cost = {n: (L if -(-w.T // n) == 1 else -(-w.T // n) + 2 * (L - 1)) * (w.T / -(-w.T // n) + (16.0 if nmax <= 4096 else 3.0))
+                for n in range(64, 15, -1)}
+    fwd_tile = min(fwd_cost, key=fwd_cost.get)
+    if fwd_cost[fwd_tile] >= 0.985 * fwd_cost[64]:
+        fwd_tile = 64
+    n_tiles = sum(-(-(min(a + seg, w.T) - a) // fwd_tile) for a in range(0, w.T, seg))
     n_rec = sum(1 for o in sched if o[0] == "REFWD2") + sum(-(-(o[2] - o[1]) // max(F, 1)) for o in sched if o[0] == "REFWD1")
-    L = len(w.n_hidden)
     big = any(4.0 * max(pn, n) * n >= (32 << 20) for pn, n in zip([w.n_in] + list(w.n_hidden[:-1]), w.n_hidden))
     dw_env = os.environ.get("SNN_DW", "")
     # (the library's rule: always for matrices of 32 MB and more; for other networks with layers wider than 256 below
@@ -436,13 +446,14 @@ def main():
     ms = {"fwd_seq": st.ms_fwd_seq, "fwd_currents": st.ms_fwd_currents, "recompute": st.ms_recompute, "scan": st.ms_scan,
           "adjoint": st.ms_adjoint, "up_gemm": st.ms_up_gemm, "dw": st.ms_dw, "bwd_stage": st.ms_bwd_stage,
           "fwd_stage": st.ms_fwd_stage, "bwd_inter": 0.0}
-    # adjoint recurrence of layers wider than 1024: event-driven rows under a surrogate window, chip-wide over the
-    # compressed rows for a masked matrix (all layers of a pipeline stage in one launch), else chip-wide over the
-    # dense-stored matrix (one launch per layer and tile)
+    # adjoint recurrence of layers wider than 1024: chip-wide over the compressed rows for a masked matrix (all layers of
+    # a pipeline stage in one launch, also under a surrogate window); for a dense-stored one event-driven rows under a
+    # window, else the matrix in registers up to 2048 neurons and streamed above (one launch per layer and tile)
     ws_env = os.environ.get("SNN_WS_KERNEL", "")
-    adj_kernel = ("k_adj_rec_rows" if (args.surr_window > 0 and ws_env in ("", "rows", "rows_all")) or ws_env in ("rows", "rows_all") else
-                  "k_adj_rec_csrw" if (w.rec_density < 1.0 and w.B <= 64 and os.environ.get("SNN_CSR", "") != "0" and ws_env in ("", "csrw")) else
-                  "k_adj_rec_wide")
+    masked_rows = w.rec_density < 1.0 and w.B <= 64 and os.environ.get("SNN_CSR", "") != "0" and ws_env in ("", "csrw")
+    adj_kernel = ("k_adj_rec_rows" if ws_env in ("rows", "rows_all") or (args.surr_window > 0 and ws_env == "" and not masked_rows) else
+                  "k_adj_rec_csrw" if masked_rows else
+                  "k_adj_rec_wsm" if nmax <= 2048 and ws_env != "stream" else "k_adj_rec_wide")
     # inter-layer products of matrices from 2048 x 2048: one launch of the 128 x 128-tile kernel per product
     gemm_big = L > 1 and min(w.n_hidden) >= 2048
     # launches of each kind's main kernel per step (layers that share a width and a pipeline stage share a launch)
@@ -481,9 +492,9 @@ def main():
     # more, firing rate x density below 0.01 in every layer)
     csr_env = os.environ.get("SNN_CSR", "")
     csr_pol = big and w.rec_density < 1.0 and max(rates) * w.rec_density < 0.01 and np.mean(rates) >= 0.035
-    csr_fwd = w.rec_density < 1.0 and all(n % 2048 == 0 for n in w.n_hidden) and (csr_env == "1" or (csr_env == "" and (csr_pol or (big and np.mean(rates) < 0.035))))
+    csr_fwd = w.rec_density < 1.0 and min(w.n_hidden) > 1024 and (csr_env == "1" or (csr_env == "" and (csr_pol or (big and np.mean(rates) < 0.035))))
     kernel_of = {"fwd_seq": ("k_layer_seq_gather" if os.environ.get("SNN_SEQ_KERNEL", "") == "gather" else "k_layer_seq_rs") if not wide else ("k_layer_seq_csr_sl" if csr_fwd else
-                            ("k_layer_seq_gather_sl" if max(w.n_hidden) >= 2048 and max(w.n_hidden) % 1024 == 0 else "k_layer_seq_gather")),
+                            ("k_layer_seq_gather_sl" if nmax > 1024 else "k_layer_seq_gather")),
                  # (matrices of 32 MB and more: the dense matrix-core version from 3.5 % presynaptic activity, below it
                  # the event-by-event gather k_currents, with k_currents_csr for masked recurrent matrices)
                  "fwd_currents": ("k_currents_dense<4,0>" if np.mean(rates) >= 0.035 else "k_currents") if big else "k_currents_mfma",
