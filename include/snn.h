@@ -177,8 +177,9 @@ snn_status snn_forward_noalloc(snn_ctx *ctx, const uint8_t *in_spikes, const int
  *   neurons, 256 for a single layer, between 16 and 256 with the square root of T otherwise) or, for DOUBLE, than a
  *   coarse interval; for HIER m divides nb_local, and a transfer moves nb_local / m checkpoints over the same span of
  *   time.  A budget of exactly snn_bytes_required runs the intervals asked for in the bytes it says.  Without a budget
- *   the state storage of such a call can be m times that of the asked intervals with the chunk buffers above; where
- *   the device has no room for it, a smaller m is taken, in the end the intervals asked for.  Gradients are the same
+ *   the state storage of such a call can be m times that of the asked intervals with the chunk buffers above, up to an
+ *   eighth of the device's memory; where the device has no room for it, a smaller m is taken, in the end the intervals
+ *   asked for.  Gradients are the same
  *   bit for bit either way, and stats reports the plan that ran: what was allocated, the checkpoints moved, and how
  *   many steps' currents were recomputed. */
 snn_status snn_bptt(snn_ctx *ctx, snn_strategy strategy, int32_t coarse_interval, int32_t fine_interval,

@@ -95,7 +95,9 @@ struct snn_ctx {
   bool rf_cache = true;         // SNN_RF_CACHE=0: Double never keeps a segment's currents between its two recompute passes
   bool keep_currents = true;    // SNN_KEEP_CURRENTS=0: the forward pass never leaves currents in that cache
   bool chunk_spans = true;      // SNN_CHUNK_SPAN=0: the backward pass walks chunks of one fine interval, as asked for
-  size_t states_max = ~(size_t)0; // chunks of several intervals: least state storage the device had no room for (SNN_STATES_MAX)
+  // chunks of several intervals: the least state storage the device had no room for (SNN_STATES_MAX), and what they may
+  // take without a budget (an eighth of the device's memory: the rest is the caller's)
+  size_t states_max = ~(size_t)0, states_unasked = 0;
   std::string err;
   size_t Ms() const { return (size_t)cfg.batch * net.SN * sizeof(float); }
 };
@@ -418,6 +420,11 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
   HIPCHK(c, hipGetDeviceCount(&ndev));
   if (cfg->device < 0 || cfg->device >= ndev) return fail(c, SNN_E_INVAL, "no such device");
   HIPCHK(c, hipSetDevice(cfg->device));
+  {
+    size_t free_b = 0, total_b = 0;
+    HIPCHK(c, hipMemGetInfo(&free_b, &total_b));
+    c->states_unasked = total_b / 8;
+  }
   c->stream = (hipStream_t)cfg->stream;
   if (!c->stream) {
     // the legacy default stream cannot be recorded into a graph: work runs on a stream of the library's
@@ -1891,9 +1898,10 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
       q.n_chunk_bufs = p.n_chunk_bufs; q.n_cache_slots = p.n_cache_slots; q.keep_from = p.keep_from;
       const size_t states = (size_t)q.local_slots() * Ms, work = work_bytes(n, q.chunk_len);
       if (budget && (q.local_slots() < asked_slots || states + work + need_spikes > budget)) continue;
-      if (states >= c->states_max) continue;
+      if (states >= c->states_max || (!budget && states > c->states_unasked)) continue;
       if (ensure_states(c, states, work) != SNN_OK) { // not tried again at every call
         (void)hipGetLastError();
+        c->err.clear(); // the call goes on
         c->states_max = states;
         continue;
       }
