@@ -199,7 +199,7 @@ void read_kernel_hooks(snn_ctx *c) {
     n.sel_currents = !std::strcmp(e, "gather") ? 1 : !std::strcmp(e, "mfma") ? 2 : !std::strcmp(e, "dense") ? 3 : 0;
   if (const char *e = std::getenv("SNN_WS_KERNEL"))
     n.sel_adjoint = !std::strcmp(e, "valu") ? 1 : !std::strcmp(e, "stream") ? 2 : !std::strcmp(e, "rows") ? 3 :
-                    !std::strcmp(e, "rows_all") ? 4 : !std::strcmp(e, "chip") ? 5 : !std::strcmp(e, "csrw") ? 6 : !std::strcmp(e, "single") ? 7 : !std::strcmp(e, "pair") ? 8 : !std::strcmp(e, "rows64") ? 9 : 0;
+                    !std::strcmp(e, "rows_all") ? 4 : !std::strcmp(e, "chip") ? 5 : !std::strcmp(e, "csrw") ? 6 : !std::strcmp(e, "single") ? 7 : !std::strcmp(e, "pair") ? 8 : !std::strcmp(e, "rows64") ? 9 : !std::strcmp(e, "uncached") ? 10 : 0;
   if (const char *e = std::getenv("SNN_SEQ_SLICES")) {
     const int v = std::atoi(e);
     n.sel_slices = (v == 1 || v == 2 || v == 4 || v == 8) ? (unsigned char)v : 0;
@@ -495,7 +495,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       const size_t n_bar = (size_t)64 * SNN_MAXL + 16; // counters + error flag, padded to a multiple of 64 bytes
       // (the batch in whole groups of 16; the kernel for layers wider than 1024 takes 1, 2 or 4 of them)
       const size_t bp = nmax > 1024 && B <= 64 ? (size_t)((B + 15) / 16 == 3 ? 4 : (B + 15) / 16) * 16 : (size_t)((B + 15) / 16) * 16;
-      const size_t xg_stride = ((size_t)4 * bp * nmax + 15) & ~(size_t)15; // four steps of values in flight
+      const size_t xg_stride = ((size_t)4 * bp * ((nmax + 3) & ~3) + 15) & ~(size_t)15; // four steps of values in flight, whole 16 bytes
       // (+ 16 KB: the forward pass's exchange of spike words shares the buffer)
       const size_t bytes = n_bar * sizeof(unsigned) + (size_t)SNN_MAXL * xg_stride * 4 + 16384;
       void *blk = uncached_block(cfg->device, bytes);
@@ -504,6 +504,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       c->ws.xg = (float *)((char *)blk + n_bar * sizeof(unsigned));
       c->ws.xg_stride = (int)xg_stride;
       HIPCHK(c, hipMemsetAsync(c->ws.bar, 0, n_bar * sizeof(unsigned), c->stream));
+      HIPCHK(c, hipMalloc(&c->ws.xl, (size_t)SNN_MAXL * xg_stride * 4));
       c->ws.err = c->ws.bar + 64 * SNN_MAXL;
       c->ws.max_groups = ws_max_resident_groups(cfg->device);
       c->ws.max_groups_m = ws_max_resident_groups_mfma(cfg->device);
@@ -554,7 +555,8 @@ void snn_destroy(snn_ctx *c) {
   (void)hipFree(c->W_out); (void)hipFree(c->W_outT); (void)hipFree(c->dW_out); (void)hipFree(c->acc_out);
   (void)hipFree(c->labels); (void)hipFree(c->readout); (void)hipFree(c->ubar); (void)hipFree(c->g);
   (void)hipFree(c->loss_dev); (void)hipFree(c->carry); (void)hipFree(c->cur_state);
-  if (c->ws.bar) uncached_release(c->cfg.device, c->ws.bar); (void)hipFree(c->counters);
+  if (c->ws.bar) uncached_release(c->cfg.device, c->ws.bar);
+  (void)hipFree(c->ws.xl); (void)hipFree(c->counters);
   (void)hipFree(c->arena); (void)hipFree(c->dubuf);
   if (c->host_ckpt) (void)hipHostFree(c->host_ckpt);
   if (c->host_small) (void)hipHostFree(c->host_small);

@@ -59,7 +59,8 @@ struct NetDev {
   // chip-wide kernels over the dense-stored matrix, also under a surrogate window, 6 the chip-wide kernel over
   // compressed rows also under a surrogate window, 7 the matrix-core version of the chip-wide recurrence with one
   // batch group per workgroup (never two half a step apart), 8 the same with two groups wherever the batch has an
-  // even number of groups, 9 the same with workgroups of 64 rows and one group.
+  // even number of groups, 9 the same with workgroups of 64 rows and one group, 10 the library's choice, but never with
+  // the exchange inside one die.
   // sel_slices: workgroups per batch element in the sequential part of wide layers (1, 2, 4 or 8).
   unsigned char sel_currents, sel_adjoint, sel_slices;
   unsigned char no_fwd_fuse; // 1: the dense currents of wide layers never ride in the launch of the sequential parts
@@ -151,6 +152,7 @@ hipError_t launch_loss(const double *readout, const int32_t *labels, int B, int 
 // kernel (see k_adj_rec_ws); xg == NULL disables that kernel.
 struct WsArgs {
   float *xg;           // SNN_MAXL x [4][B in whole groups of 16][max N_l], one per job of a launch
+  float *xl;           // the same in ordinary memory, for workgroups that share a die (NULL: never used)
   int xg_stride;       // floats between the exchange buffers of two jobs
   unsigned *bar;       // SNN_MAXL x [64] counters, zeroed before every launch
   unsigned *err;       // raised if a barrier gave up waiting

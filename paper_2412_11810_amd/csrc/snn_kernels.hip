@@ -1673,6 +1673,45 @@ static __device__ __forceinline__ uint32_t xenc(float v) {
 }
 static __device__ __forceinline__ float xdec(uint32_t e) { return __uint_as_float(~e); }
 
+// Exchange inside one die.  A value travels between two workgroups in 0.59 us through uncached memory and in 0.22 us
+// through the L2 of a die that both run on (ordinary memory, plain store, load that passes the L1 by), and the reads of
+// what the others have written, 16 to 64 KB per workgroup and step, come at the L2's rate.  The launchers put the
+// workgroups that exchange with each other at block indices that are equal modulo 8, which the hardware deals to
+// one die; whether it did is established here, once per launch: every workgroup of the unit posts the number of its die in
+// uncached memory (zero before the launch) and reads those of all the others.  All see the same numbers, so all decide alike.
+// Called by every thread of the workgroup, n <= 64.
+static __device__ __forceinline__ unsigned die_id() {
+  unsigned r;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(r));
+  return r & 15u;
+}
+static __device__ __forceinline__ bool unit_on_one_die(unsigned *posts, int me, int n, unsigned *err, unsigned spin_limit, bool *dead) {
+  __shared__ int s_one_die;
+  const unsigned mine = die_id() + 1u;
+  if (threadIdx.x == 0) __hip_atomic_store(&posts[me], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x < WAVE) {
+    const int i = (int)threadIdx.x;
+    unsigned got = mine, spins = 0;
+    bool late = false;
+    if (i < n)
+      while ((got = __hip_atomic_load(&posts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u || spin_limit == 0u) {
+        if (++spins > spin_limit ||
+            ((spins & 63u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          late = true;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    const bool gave_up = __ballot(late) != 0ull, one = __ballot(got != mine) == 0ull;
+    if (i == 0) s_one_die = gave_up ? 2 : one ? 1 : 0;
+  }
+  __syncthreads();
+  const int r = s_one_die;
+  if (r == 2) *dead = true; // keep going, never wait again
+  return r == 1;
+}
+
 // Recurrent part, layers of up to H*KH neurons: the recurrent matrix stays in registers for the
 // whole chunk.  Thread (jj, h) keeps W_rec[j][h*KH .. h*KH+KH) for the R postsynaptic rows
 // j = jj, jj + NJR, ..., jj + (R-1)*NJR (H threads per row, each a slice of the reduction; partial sums
@@ -1936,228 +1975,285 @@ k_adj_rec_ws(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, uns
   if (fin) carry[(size_t)fb * (SN + O) + off + fj] = xs[(size_t)fj * 8 + fbb];
 }
 
-// The same chip-wide recurrence on the matrix cores.  Workgroup (js, bg) owns 32 postsynaptic rows x 16 batch
-// elements; wavefront q takes one of KS parts of the reduction range and, for each of the two 16-row blocks, keeps its
-// part of W_rec in registers as the A operands of NK K-steps (v_mfma_f32_16x16x4: A[i][k] in lane i + 16k).  The
-// B operand of a K-step is dv_{t+1} of 4 presynaptic neurons x 16 batch elements, read from LDS (batch-minor, so
-// the 64 lanes read 64 consecutive floats).  Per step a wavefront issues 2 NK MFMAs on two independent
-// accumulators and one LDS read per K-step, where the VALU version reads every dv value of 8 batch elements
-// once per thread and is bound by the LDS (about twice the time).  The KS partial sums are combined in a
-// fixed order.  KS = 4 up to 1024 neurons, 8 (two wavefronts per SIMD, 256 registers each) up to 2048.
-// Exchange: [step & 3][batch group][N][16], values encoded by xenc (no barrier, see there).  What a step costs beyond
-// its products is that every workgroup reads the N x 16 values of its group from uncached memory: they lie as LDS
-// wants them, 4 bytes each (with a step tag beside every
-// value, 8 bytes, three layers of 1024 neurons at batch 64 took 14.2 us per step, now 9.1; two of 512 at batch 16 5.7, now 4.8).
+// The same chip-wide recurrence on the matrix cores.  Workgroup (js, bg) owns 16 RB RH postsynaptic rows x 16 batch
+// elements; wavefront q takes one of KS parts of the reduction range and, for each of its RB blocks of 16 rows, keeps its
+// part of W_rec in registers as the A operands of NK K-steps (v_mfma_f32_16x16x4: A[i][k] in lane i + 16k).  K-step c of
+// a group of four takes the presynaptic neurons 16 Q + 4 k + c, so that the B operands of a group, dv_{t+1} of 16
+// neurons x 16 batch elements, are one 16-byte LDS read per lane (rows of one batch element, 4 floats apart in their
+// banks: no conflicts).  Even and odd groups add to accumulators of their own (a K-step that waits for the one before it
+// costs a third more), then the KS partial sums are combined; the order of a sum depends on the padded width alone, so every
+// RB, RH and NG gives the same bits.  KS = 4 up to 1024 neurons, 8 (two wavefronts per SIMD, 256 registers each) up to 2048.
+// Exchange: [step & 3][batch group][16][NX], NX = N rounded up to 4, values encoded by xenc (no barrier, see there).
+// What bounds a step is the chain products -> sum -> store -> arrival at the others -> LDS -> products, so nothing
+// else is on it: v_t and the inter-layer product of a step are requested, the dv_t of the step before it stored and the
+// exchange entries of the step before that cleared at the beginning of a step, while the products run (a poll waits for
+// every older access as well: with them behind the exchange stores the poll took 1.5 us longer), the surrogate
+// derivative is formed there too, rows run along the lanes in every access to memory, and the exchange goes through the
+// L2 of one die where the units fit (unit_on_one_die).  Two layers of 512 neurons at batch 16: 4.8 -> 2.1 us per step
+// (2.5 with 32 rows per workgroup), three of 1024 at batch 64: 9.1 -> 6.5, of which 3.4 are the products of 64 rows.
 // With NG = 2 a workgroup serves two batch groups of 16 with the same registers of W_rec, half a step apart: while
 // the values one group has just stored travel through the exchange buffer, the matrix cores work on the other
-// group, and the two round trips of a step no longer add to its products.  Half as many workgroups per layer also
-// lets more layers of a pipeline stage share a launch.  The operations per element are those of NG = 1.
-// With RH = 2 a workgroup has eight wavefronts and owns 64 rows (wavefront w: rows 32 (w / 4) .., quarter w % 4 of
-// the reduction range; two wavefronts per SIMD, 256 registers each): half as many workgroups read a batch group's
-// dv_t from the exchange buffer, which is what a step costs.
-template <int NK, int NG, int RH, int KS = 4> // K-steps per wavefront and row block (padded width 4 KS NK); batch groups and 32-row halves per workgroup; parts of the reduction range
+// group.  With RH = 2 a workgroup has eight wavefronts and owns twice the rows (wavefront w: half w / 4, quarter w % 4 of
+// the reduction range; two wavefronts per SIMD, 256 registers each): half as many workgroups per layer.
+template <int NK, int NG, int RH, int KS = 4, int RB = 2> // K-steps per wavefront and row block (padded width 4 KS NK); batch groups and halves of 16 RB rows per workgroup; parts of the reduction range
 __global__ void __launch_bounds__(64 * KS * RH) __attribute__((amdgpu_waves_per_eu(KS * RH / 4, KS * RH / 4))) // the weights must stay in registers
-k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, unsigned *err, int G_w,
-              unsigned spin_limit, int blocks_per_job, int xg_stride) {
+k_adj_rec_wsm(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, float *xl, unsigned *posts, unsigned *err, int G_w,
+              unsigned spin_limit, int slices, int n_units, int xg_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int jq = blockIdx.x / blocks_per_job, vb = blockIdx.x % blocks_per_job;
+  constexpr int NT = 64 * KS * RH, ROWS = 16 * RB * RH, NP = 4 * KS * NK; // threads; rows of the workgroup; padded reduction length (>= N)
+  constexpr int XP = NP + 4, PP = 16 * RB + 4;                            // floats per batch element: dv in LDS, partial sums of a wavefront
+  // unit: a job and a group of G_w; its `slices` workgroups exchange with each other.  n_units > 0: unit u at block
+  // indices equal to u modulo 8, i.e. on one die
+  int unit, js;
+  if (n_units > 0) {
+    const int k = (int)blockIdx.x >> 3;
+    unit = ((int)blockIdx.x & 7) + 8 * (k / slices);
+    js = k % slices;
+    if (unit >= n_units) return;
+  } else {
+    unit = (int)blockIdx.x / (slices * G_w) * G_w + (int)blockIdx.x % G_w;
+    js = (int)blockIdx.x % (slices * G_w) / G_w;
+  }
+  const int jq = unit / G_w, bg = unit % G_w; // G_w units of NG batch groups each per job
   const AdjJob &jb = jobs.j[jq];
   const int l = jb.l, t0 = jb.t0, t1 = jb.t1, t_base = jb.t_base, carry_init = jb.carry_init;
-  float *__restrict__ vbuf = jb.vbuf;
-  const float *__restrict__ up = jb.up;
   const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, O = net.n_out, ldu = N;
-  constexpr int NT = 64 * KS * RH;
   const int tid = threadIdx.x, lane = tid & 63, wv = (tid >> 6) % KS, rh = (tid >> 6) / KS, li = lane & 15, lk = lane >> 4;
-  const int bg = vb % G_w, js = vb / G_w; // G_w workgroups of NG batch groups each per 32 RH rows
-  const int j0 = js * 32 * RH, jw = j0 + 32 * rh; // first row of the workgroup, of the wavefront
+  const int j0 = js * ROWS, jw = j0 + 16 * RB * rh; // first row of the workgroup, of the wavefront
   if (j0 >= N) return; // a job of a narrower layer than the widest of the launch: nobody waits for this workgroup
-  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)(xg + (size_t)jq * xg_stride), 0, (int)((size_t)xg_stride * sizeof(float)), 0x00027000); // [4][G_w NG][N][16]
-  constexpr int NP = 4 * KS * NK;                      // padded reduction length (>= N)
-  float *xs_all = (float *)smem;                       // [NG][NP][16]  dv_{t+1}, batch-minor
-  float *part_all = xs_all + (size_t)NG * NP * 16;     // [NG][RH][KS][32][16]
+  const int NX = (N + 3) & ~3;
+  float *xs_all = (float *)smem;                        // [NG][16][XP]  dv_{t+1}
+  float *part_all = xs_all + (size_t)NG * 16 * XP;      // [NG][RH][KS][16][PP]
 
-  // dv_{t1+1} of the batch groups.  Here and below every load is unconditional, from a clamped address, and zeroed with
-  // an integer mask afterwards (a select lets the compiler put each load under its condition).
+  // A operands: a[rb][4 Q + c] = W_rec[jw + 16 rb + li][4 NK wv + 16 Q + 4 lk + c].  Here and below every load is
+  // unconditional, from a clamped address, and zeroed with an integer mask afterwards (a select lets the compiler put each
+  // load under its condition); what a 16-byte load takes beyond the end of its row is masked, beyond the matrix reads 0.
+  float a[RB][NK];
+  {
+    const __amdgpu_buffer_rsrc_t wres =
+        __builtin_amdgcn_make_buffer_rsrc((void *)net.W_rec[l], 0, (int)((size_t)N * N * sizeof(float)), 0x00027000);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int j = jw + 16 * rb + li, jc = j < N ? j : N - 1;
+#pragma unroll
+      for (int q = 0; q < NK; q += 4) {
+        const int n = 4 * NK * wv + 4 * q + 4 * lk, nc = n < N ? n : N - 1;
+        const csr_u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(wres, (uint32_t)(jc * N + nc) * 4u, 0, 0);
+        a[rb][q] = __uint_as_float(w.x);
+        a[rb][q + 1] = __uint_as_float(w.y);
+        a[rb][q + 2] = __uint_as_float(w.z);
+        a[rb][q + 3] = __uint_as_float(w.w);
+        if (q % 16 == 12) __builtin_amdgcn_sched_barrier(0); // no more addresses at a time than the registers hold
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int q = 0; q < NK; ++q) {
+        const int n = 4 * NK * wv + 4 * (q & ~3) + 4 * lk + (q & 3);
+        a[rb][q] = __uint_as_float(__float_as_uint(a[rb][q]) & (0u - (uint32_t)(jw + 16 * rb + li < N && n < N)));
+      }
+  }
+  // dv_{t1+1} of the batch groups: thread -> batch element tid / LB, 4 floats at a time along the neurons
+  constexpr int LB = NT / 16, NL = NP / 4 / LB; // threads per batch element; 16-byte pieces per thread
+  static_assert(NP / 4 % LB == 0, "whole rounds");
+  const int xbb = tid / LB, xn = 4 * (tid % LB); // this thread's batch element and first neuron of a round
   for (int g = 0; g < NG; ++g) {
-    const int b0 = (bg * NG + g) * 16;
-    constexpr int NR = 16; // of NP * 16 / NT values per thread, at a time
-    static_assert(NP * 16 / NT % NR == 0, "whole rounds");
-    for (int i0 = tid; i0 < NP * 16; i0 += NR * NT) {
-      float cv[NR];
+    const int fb = (bg * NG + g) * 16 + xbb;
+    const float *cp = carry + (size_t)(fb < B ? fb : B - 1) * (SN + O) + off;
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int i = i0 + NT * r, n = i >> 4, bb = i & 15;
-        cv[r] = carry[(size_t)(b0 + bb < B ? b0 + bb : B - 1) * (SN + O) + off + (n < N ? n : N - 1)];
+    for (int u = 0; u < NL; ++u) {
+      float v[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int n = xn + 4 * LB * u + c;
+        v[c] = cp[n < N ? n : N - 1];
       }
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int i = i0 + NT * r, n = i >> 4, bb = i & 15;
-        xs_all[(size_t)g * NP * 16 + i] =
-            __uint_as_float(__float_as_uint(cv[r]) & (0u - (uint32_t)(!carry_init && n < N && b0 + bb < B)));
+      for (int c = 0; c < 4; ++c) {
+        const int n = xn + 4 * LB * u + c;
+        xs_all[((size_t)g * 16 + xbb) * XP + n] = __uint_as_float(__float_as_uint(v[c]) & (0u - (uint32_t)(!carry_init && n < N && fb < B)));
       }
     }
   }
-  // A operands: a[rb][s] = W_rec[j0 + 16 rb + li][4 NK wv + 4 s + lk]
-  float a[2][NK];
-  const __amdgpu_buffer_rsrc_t wres =
-      __builtin_amdgcn_make_buffer_rsrc((void *)net.W_recT[l], 0, (int)((size_t)N * N * sizeof(float)), 0x00027000);
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int j = jw + 16 * rb + li, jc = j < N ? j : N - 1;
-#pragma unroll
-    for (int q = 0; q < NK; ++q) {
-      const int n = 4 * NK * wv + 4 * q + lk, nc = n < N ? n : N - 1;
-      a[rb][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, (uint32_t)(nc * N + jc) * 4u, 0, 0)); // = W_rec[j][n]
-      if (q % 16 == 15) __builtin_amdgcn_sched_barrier(0); // no more addresses at a time than the registers hold
-    }
-  }
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int j = jw + 16 * rb + li;
-#pragma unroll
-    for (int q = 0; q < NK; ++q)
-      a[rb][q] = __uint_as_float(__float_as_uint(a[rb][q]) & (0u - (uint32_t)(j < N && 4 * NK * wv + 4 * q + lk < N)));
-  }
+  bool dead = false;
+  const bool local = n_units > 0 && unit_on_one_die(posts + unit * slices, js, (N + ROWS - 1) / ROWS, err, spin_limit, &dead);
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((local ? xl : xg) + (size_t)jq * xg_stride), 0, (int)((size_t)xg_stride * sizeof(float)), 0x00027000); // [4][G_w NG][16][NX]
   __syncthreads();
-  // finalising role: 32 RH x 16 (row, batch element) pairs per group, NE per thread
-  constexpr int NE = 8 / KS;
-  int fj[NE], fbb[NE];
-  float dprev[NG][NE]; // dv_{t+1} of the pairs
+  // finalising role: ROWS x 16 (row, batch element) pairs per group, NE per thread, rows along the lanes
+  constexpr int NE = ROWS * 16 / NT;
+  int fr[NE], fbb[NE];
+  bool fin[NG][NE];                  // the pair exists
+  uint32_t xo[NE];                   // byte offset of its exchange entry (none: beyond the buffer, where stores are dropped)
+  uint32_t iv[NG][NE], iu[NG][NE];   // its place in a slot of states, in a step of the inter-layer product
+  float dprev[NG][NE];               // dv_{t+1} of the pairs
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
     const int pidx = tid + NT * e;
-    fj[e] = j0 + (pidx >> 4);
-    fbb[e] = pidx & 15;
+    fr[e] = pidx % ROWS;
+    fbb[e] = pidx / ROWS;
+    const int j = j0 + fr[e], jc = j < N ? j : N - 1;
+    xo[e] = j < NX ? (uint32_t)(fbb[e] * NX + j) * 4u : 0x80000000u;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) dprev[g][e] = fj[e] < NP ? xs_all[((size_t)g * NP + fj[e]) * 16 + fbb[e]] : 0.0f;
+    for (int g = 0; g < NG; ++g) {
+      const int fb = (bg * NG + g) * 16 + fbb[e], fc = fb < B ? fb : B - 1;
+      fin[g][e] = j < N && fb < B;
+      iv[g][e] = (uint32_t)(fc * SN + off + jc);
+      iu[g][e] = (uint32_t)(fc * ldu + jc);
+      dprev[g][e] = j < NP ? xs_all[((size_t)g * 16 + fbb[e]) * XP + j] : 0.0f;
+    }
   }
-  const size_t slot_stride = (size_t)B * SN;
+  const size_t slot_stride = (size_t)B * SN, up_stride = (size_t)B * ldu;
   // byte offset of the values of a step and a group of this workgroup in the exchange buffer
-  auto x_base = [&](int g, unsigned step) { return (uint32_t)(((size_t)(step & 3u) * (G_w * NG) + bg * NG + g) * N * 64u); };
-  bool dead = false;
-  // v_t and the inter-layer product of the pairs: requested a step ahead, behind the exchange stores, so that they arrive
-  // while the exchange is polled
-  float vt[NG][NE], upv[NG][NE];
-  auto load_operands = [&](int g, int t) {
-    const size_t slot = (size_t)(t - t_base - 1);
+  auto x_base = [&](int g, unsigned step) { return (uint32_t)(((step & 3u) * (uint32_t)(G_w * NG) + (uint32_t)(bg * NG + g)) * (uint32_t)NX * 64u); };
+  float vt[NG][NE], upv[NG][NE]; // of the step: potential, inter-layer product
+  auto load_operands = [&](int g, int t, float (&v)[NE], float (&u)[NE]) {
+    const float *vr = jb.vbuf + (size_t)(t - t_base - 1) * slot_stride, *ur = jb.up + (size_t)(t - t_base - 1) * up_stride;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
-      const int fb = (bg * NG + g) * 16 + fbb[e];
-      const bool ok = fj[e] < N && fb < B;
-      vt[g][e] = ok ? vbuf[slot * slot_stride + (size_t)fb * SN + off + fj[e]] : 0.0f;
-      upv[g][e] = ok ? up[(slot * B + fb) * ldu + fj[e]] : 0.0f;
+      v[e] = vr[iv[g][e]];
+      u[e] = ur[iu[g][e]];
     }
   };
 #pragma unroll
-  for (int g = 0; g < NG; ++g) load_operands(g, t1);
-  // one step of one batch group: products, the sum of the partial results, the recurrence, the exchange stores
-  auto compute = [&](int g, unsigned step, int t) {
-    const int b0 = (bg * NG + g) * 16;
-    float *xs = xs_all + (size_t)g * NP * 16, *part = part_all + (size_t)g * RH * KS * 32 * 16;
-    const size_t slot = (size_t)(t - t_base - 1);
-    v4f acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
-    const float *xb = xs + (size_t)(4 * NK * wv + lk) * 16 + li;
-#pragma unroll
-    for (int q = 0; q < NK; ++q) {
-      const float x = xb[64 * q];
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][q], x, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1][q], x, acc1, 0, 0, 0);
-    }
-    // D[4 lk + r][li]: row 4 lk + r of the block, batch element li
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      part[((size_t)(KS * rh + wv) * 32 + 4 * lk + r) * 16 + li] = acc0[r];
-      part[((size_t)(KS * rh + wv) * 32 + 16 + 4 * lk + r) * 16 + li] = acc1[r];
-    }
-    __syncthreads(); // from here on nobody reads dv_{t+1} of this group in LDS
+  for (int g = 0; g < NG; ++g) load_operands(g, t1, vt[g], upv[g]);
+  auto store_dv = [&](int g, int t) {
+    float *vr = jb.vbuf + (size_t)(t - t_base - 1) * slot_stride;
 #pragma unroll
     for (int e = 0; e < NE; ++e)
-      if (fj[e] < N) {
-        const int fr = (fj[e] - j0) & 31, fh = (fj[e] - j0) >> 5, fb = b0 + fbb[e];
-        float sacc = part[((size_t)(KS * fh) * 32 + fr) * 16 + fbb[e]];
+      if (fin[g][e]) vr[iv[g][e]] = dprev[g][e];
+  };
+  // the time loop, once for the exchange inside a die (plain stores, loads with sc1) and once through uncached memory (sc0 sc1)
+  auto run = [&](auto local_c) {
+    constexpr int ST = decltype(local_c)::value ? 0 : 17, LD = decltype(local_c)::value ? 16 : 17;
+    // one step of one batch group, from the values of the step before it in LDS to the exchange stores
+    auto compute = [&](int g, unsigned step, int t) {
+      float *xs = xs_all + (size_t)g * 16 * XP, *part = part_all + (size_t)g * RH * KS * 16 * PP;
+      float vn[NE], un[NE], gs[NE];
+      load_operands(g, t - 1 > t0 ? t - 1 : t, vn, un);
 #pragma unroll
-        for (int k = 1; k < KS; ++k) sacc = sacc + part[((size_t)(KS * fh + k) * 32 + fr) * 16 + fbb[e]];
+      for (int e = 0; e < NE; ++e) {
+        gs[e] = surrogate(net, vt[g][e]);
+        asm volatile("" : "+v"(gs[e])); // formed here, not behind the products
+      }
+      if (step > 0u) {
+        store_dv(g, t + 1);
+        // everyone has read the values of the step before the last: who wrote the last one's had
+#pragma unroll
+        for (int e = 0; e < NE; ++e) __builtin_amdgcn_raw_buffer_store_b32(0u, xres, x_base(g, step - 2u) + xo[e], 0, ST);
+      }
+      v4f acc[RB][2];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[rb][0] = acc[rb][1] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+      const float4 *xb = reinterpret_cast<const float4 *>(xs + (size_t)li * XP + 4 * NK * wv + 4 * lk);
+#pragma unroll
+      for (int q = 0; q < NK; q += 4) {
+        const float4 x = xb[q];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb)
+            acc[rb][(q >> 2) & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rb][q + c], c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w,
+                                                                         acc[rb][(q >> 2) & 1], 0, 0, 0);
+      }
+      // D[4 lk + r][li]: row 4 lk + r of the block, batch element li
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const v4f s = acc[rb][0] + acc[rb][1];
+        *reinterpret_cast<v4f *>(part + ((size_t)(KS * rh + wv) * 16 + li) * PP + 16 * rb + 4 * lk) = s;
+      }
+      __syncthreads(); // from here on nobody reads dv_{t+1} of this group in LDS
+      const uint32_t base = x_base(g, step);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const float *pp = part + ((size_t)(KS * (fr[e] / (16 * RB))) * 16 + fbb[e]) * PP + fr[e] % (16 * RB);
+        float sacc = pp[0];
+#pragma unroll
+        for (int k = 1; k < KS; ++k) sacc = sacc + pp[(size_t)k * 16 * PP];
         const float dn = dprev[g][e];
         const float ds = (sacc + upv[g][e]) - net.theta * dn;
-        const float dvt = fb < B ? fmaf(ds, surrogate(net, vt[g][e]), net.alpha * dn) : 0.0f;
-        if (fb < B) vbuf[slot * slot_stride + (size_t)fb * SN + off + fj[e]] = dvt;
-        dprev[g][e] = dvt;
-        const uint32_t at = (uint32_t)(fj[e] * 16 + fbb[e]) * 4u;
-        __builtin_amdgcn_raw_buffer_store_b32(xenc(dvt), xres, x_base(g, step) + at, 0, 17); // sc0 sc1
-        __builtin_amdgcn_raw_buffer_store_b32(0u, xres, x_base(g, step + 2u) + at, 0, 17);  // nobody reads these any more
+        const float dvt = fmaf(ds, gs[e], net.alpha * dn);
+        dprev[g][e] = fin[g][e] ? dvt : 0.0f;
+        __builtin_amdgcn_raw_buffer_store_b32(xenc(dprev[g][e]), xres, base + xo[e], 0, ST);
       }
-    load_operands(g, t - 1 > t0 ? t - 1 : t);
-  };
-  // dv_t of the whole layer for one batch group -> LDS; a lane asks again only for values that have not arrived.  The
-  // polling is bounded like the barrier of k_adj_rec_ws: a thread that gives up raises *err, and from then on nobody
-  // waits.
-  auto poll = [&](int g, unsigned step) {
-    float4 *xs = reinterpret_cast<float4 *>(xs_all + (size_t)g * NP * 16);
-    const uint32_t base = x_base(g, step);
-    if (spin_limit == 0u && !dead) { // only ever set by a test of this path: give up at once, arrived or not
-      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      dead = true;
-    }
-    constexpr int NL = NP * 4 / NT, UN = NL < 8 ? NL : 8; // 16-byte loads per thread, in flight at a time
 #pragma unroll
-    for (int c = 0; c < NL; c += UN) {
-      csr_u32x4 x[UN];
-      uint32_t open = 0u;
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        x[u] = csr_u32x4{0u, 0u, 0u, 0u};
-        if (tid + NT * (c + u) < 4 * N) open |= 1u << u;
+      for (int e = 0; e < NE; ++e) {
+        vt[g][e] = vn[e];
+        upv[g][e] = un[e];
       }
-      const uint32_t mine = open;
-      unsigned spins = 0;
-      for (;;) {
-        asm volatile("" ::: "memory"); // every round reads again
+    };
+    // dv_t of the whole layer for one batch group -> LDS.  A wavefront asks again until everything it reads has arrived.
+    // Nothing is conditional per lane: a piece beyond the layer's width is the lane's first one again and goes to the four
+    // spare floats of its row.  The polling is bounded like the barrier of k_adj_rec_ws: a wavefront that gives up raises
+    // *err, and from then on nobody waits.
+    auto poll = [&](int g, unsigned step) {
+      float *xs = xs_all + ((size_t)g * 16 + xbb) * XP;
+      const uint32_t base = x_base(g, step) + (uint32_t)(xbb * NX) * 4u;
+      if (spin_limit == 0u && !dead) { // only ever set by a test of this path: give up at once, arrived or not
+        __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        dead = true;
+      }
+      constexpr int UN = NL < 8 ? NL : 8; // 16-byte loads per thread in flight at a time
 #pragma unroll
-        for (int u = 0; u < UN; ++u)
-          if (open >> u & 1u)
-            x[u] = __builtin_amdgcn_raw_buffer_load_b128(xres, base + (uint32_t)(tid + NT * (c + u)) * 16u, 0, 17); // sc0 sc1
+      for (int c = 0; c < NL; c += UN) {
+        csr_u32x4 x[UN];
+        for (unsigned spins = 0;;) {
+          asm volatile("" ::: "memory"); // every round reads again
 #pragma unroll
-        for (int u = 0; u < UN; ++u)
-          if (x[u].x != 0u && x[u].y != 0u && x[u].z != 0u && x[u].w != 0u) open &= ~(1u << u);
-        if (open == 0u || dead) break;
-        if (++spins > spin_limit / 8u ||
-            ((spins & 15u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-          __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          dead = true; // keep going to the end of the chunk, never wait again
-          break;
+          for (int u = 0; u < UN; ++u) {
+            const int n = xn + 4 * LB * (c + u);
+            x[u] = __builtin_amdgcn_raw_buffer_load_b128(xres, base + (uint32_t)(n < N ? n : xn) * 4u, 0, LD);
+          }
+          uint32_t least = ~0u; // 0: something has not arrived
+#pragma unroll
+          for (int u = 0; u < UN; ++u) {
+            least = min(min(least, x[u].x), x[u].y);
+            least = min(min(least, x[u].z), x[u].w);
+          }
+          if (__ballot(least == 0u) == 0ull || dead) break;
+          if (++spins > spin_limit / 8u ||
+              ((spins & 15u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+            __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            dead = true; // keep going to the end of the chunk, never wait again
+            break;
+          }
+          if (!decltype(local_c)::value) __builtin_amdgcn_s_sleep(1);
         }
-        __builtin_amdgcn_s_sleep(1);
-      }
 #pragma unroll
-      for (int u = 0; u < UN; ++u)
-        if (mine >> u & 1u) xs[tid + NT * (c + u)] = make_float4(xdec(x[u].x), xdec(x[u].y), xdec(x[u].z), xdec(x[u].w));
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the cleared entries are in memory before the next values go out
-  };
-  unsigned step = 0;
-  for (int t = t1; t > t0; --t, ++step) {
-    compute(0, step, t);
-    if (NG == 2) {
-      // the second group runs half a step behind: its values of the previous step have had the first group's
-      // products to arrive
-      if (step > 0u) poll(1, step - 1u);
+        for (int u = 0; u < UN; ++u) {
+          const int n = xn + 4 * LB * (c + u);
+          *reinterpret_cast<float4 *>(xs + (n < N ? n : NP)) = make_float4(xdec(x[u].x), xdec(x[u].y), xdec(x[u].z), xdec(x[u].w));
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the cleared entries are in memory before the next values go out
+    };
+    unsigned step = 0;
+    for (int t = t1; t > t0; --t, ++step) {
+      compute(0, step, t);
+      if (NG == 2) {
+        // the second group runs half a step behind: its values of the previous step have had the first group's
+        // products to arrive
+        if (step > 0u) poll(1, step - 1u);
+        __syncthreads();
+        compute(1, step, t);
+      }
+      // the values of the last step stay with their owners; a launch of one step waits all the same: everyone has read
+      // the carry when its values arrive, and only then may it be overwritten below
+      if (t > t0 + 1 || step == 0u) poll(0, step);
       __syncthreads();
-      compute(1, step, t);
     }
-    // the values of the last step stay with their owners; a launch of one step waits all the same: everyone has read
-    // the carry when its values arrive, and only then may it be overwritten below
-    if (t > t0 + 1 || step == 0u) poll(0, step);
-    __syncthreads();
-  }
-  if (NG == 2 && step == 1u) poll(1, 0u);
-  // carry out dv_{t0+1}: every workgroup writes its own rows
+    if (NG == 2 && step == 1u) poll(1, 0u);
+  };
+  if (local) run(std::true_type{});
+  else run(std::false_type{});
+  // dv_{t0+1}: to its slot and into the carry, every workgroup its own rows
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
-    const int b0 = (bg * NG + g) * 16;
+    store_dv(g, t0 + 1);
 #pragma unroll
     for (int e = 0; e < NE; ++e)
-      if (fj[e] < N && b0 + fbb[e] < B) carry[(size_t)(b0 + fbb[e]) * (SN + O) + off + fj[e]] = dprev[g][e];
+      if (fin[g][e]) carry[(size_t)((bg * NG + g) * 16 + fbb[e]) * (SN + O) + off + j0 + fr[e]] = dprev[g][e];
   }
 }
 
@@ -4482,6 +4578,9 @@ hipError_t launch_up_product(const NetDev &net, int l, int t0, int t1, int t_bas
 }
 
 static bool ws_use_mfma(const NetDev &net);
+static size_t wsm_lds(int NK, int NG, int RH, int KS, int RB) { // dynamic LDS of k_adj_rec_wsm
+  return (size_t)NG * 16 * ((size_t)4 * KS * NK + 4 + (size_t)RH * KS * (16 * RB + 4)) * sizeof(float);
+}
 
 // Chip-wide recurrence of a wide layer: geometry and launch.
 template <int RB, int NBB>
@@ -4706,34 +4805,51 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
       const int RH = !wsm_wide && (net.sel_adjoint == 9 || (!plain && cap1 >= 1 && cls.count > cap1)) ? 2 : 1;
       const int NG = !wsm_wide && G_b % 2 == 0 && net.sel_adjoint == 8 ? 2 : 1;
       const int KS = wsm_wide ? 8 : 4;
-      const int G_w = G_b / NG, bpj = (n_max + 32 * RH - 1) / (32 * RH) * G_w;
-      const size_t lds = (size_t)NG * ((size_t)4 * KS * NK * 16 + RH * KS * 32 * 16) * sizeof(float);
       AdjJobs grp{};
+      const int full = (n_max + 32 * RH - 1) / (32 * RH) * (G_b / NG);
       for (int k = 0; k < cls.count; ++k)
-        if (grp.count == 0 || (grp.count + 1) * bpj <= limit) {
+        if (grp.count == 0 || (grp.count + 1) * full <= limit) {
           grp.j[grp.count++] = cls.j[k];
           taken[cls_at[k]] = true;
         }
-      // the exchange entries start from zero in every launch
-      hipError_t e = launch_fill_zero(ws.xg, (size_t)grp.count * ws.xg_stride * sizeof(float), s);
+      // Units on one die each where every die has room for its share of them (an eighth of the chip's resident workgroups),
+      // and 16 rows per workgroup instead of 32 where it has room for those: half the products per step.  128-2x512, batch 16,
+      // T = 4000: 48.8 ms per training step through uncached memory, 39.9 by die, 37.9 with 16 rows.
+      const int G_w = G_b / NG, units = grp.count * G_w;
+      auto die_fits = [&](int rows) {
+        const int sl = (n_max + rows - 1) / rows, per_die = (units + 7) / 8 * sl;
+        return ws.xl && net.sel_adjoint != 10 && per_die <= limit / 8 && sl <= WAVE && 8 * per_die <= 64 * SNN_MAXL;
+      };
+      const bool by_die = die_fits(32 * RH);
+      const int RB = NK == 32 && NG == 1 && RH == 1 && net.sel_adjoint != 7 && die_fits(16) ? 1 : 2;
+      const int slices = (n_max + 16 * RB * RH - 1) / (16 * RB * RH);
+      const size_t lds = wsm_lds(NK, NG, RH, KS, RB);
+      // the exchange entries (and the posts of the dies) start from zero in every launch
+      ZeroJobs clear{};
+      clear.add(ws.xg, (size_t)grp.count * ws.xg_stride * sizeof(float));
+      if (by_die) {
+        clear.add(ws.xl, (size_t)grp.count * ws.xg_stride * sizeof(float));
+        clear.add(ws.bar, (size_t)units * slices * sizeof(unsigned));
+      }
+      hipError_t e = launch_fill_zero_jobs(clear, s);
       if (e != hipSuccess) return e;
-      const dim3 grid(bpj * grp.count), block(64 * KS * RH);
-#define WSM_CASE(NK_, NG_, RH_, KS_)                                                                                    \
+      const dim3 grid((by_die ? (units + 7) / 8 * 8 : units) * slices), block(64 * KS * RH);
+#define WSM_CASE(NK_, NG_, RH_, KS_, RB_)                                                                               \
   {                                                                                                                     \
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_wsm<NK_, NG_, RH_, KS_>),                          \
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_wsm<NK_, NG_, RH_, KS_, RB_>),                     \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                      \
     if (e != hipSuccess) return e;                                                                                      \
-    hipLaunchKernelGGL((k_adj_rec_wsm<NK_, NG_, RH_, KS_>), grid, block, lds, s, net, grp, carry, ws.xg, ws.err, G_w,   \
-                       ws.spin_limit, bpj, ws.xg_stride);                                                               \
+    hipLaunchKernelGGL((k_adj_rec_wsm<NK_, NG_, RH_, KS_, RB_>), grid, block, lds, s, net, grp, carry, ws.xg, ws.xl, ws.bar, \
+                       ws.err, G_w, ws.spin_limit, slices, by_die ? units : 0, ws.xg_stride);                           \
   }
       if (wsm_wide) {
-        if (NK == 48) WSM_CASE(48, 1, 1, 8) else WSM_CASE(64, 1, 1, 8)
+        if (NK == 48) WSM_CASE(48, 1, 1, 8, 2) else WSM_CASE(64, 1, 1, 8, 2)
       } else if (RH == 2) {
-        if (NK == 32) WSM_CASE(32, 1, 2, 4) else WSM_CASE(64, 1, 2, 4)
+        if (NK == 32) WSM_CASE(32, 1, 2, 4, 2) else WSM_CASE(64, 1, 2, 4, 2)
       } else if (NK == 32) {
-        if (NG == 1) WSM_CASE(32, 1, 1, 4) else WSM_CASE(32, 2, 1, 4)
+        if (RB == 1) WSM_CASE(32, 1, 1, 4, 1) else if (NG == 1) WSM_CASE(32, 1, 1, 4, 2) else WSM_CASE(32, 2, 1, 4, 2)
       } else {
-        if (NG == 1) WSM_CASE(64, 1, 1, 4) else WSM_CASE(64, 2, 1, 4)
+        if (NG == 1) WSM_CASE(64, 1, 1, 4, 2) else WSM_CASE(64, 2, 1, 4, 2)
       }
 #undef WSM_CASE
     } else if (N <= 1024 && ws.xg && (B + 7) / 8 <= 64 && ((N + 31) / 32) * ((B + 7) / 8) <= ws.max_groups) {
@@ -4808,7 +4924,7 @@ int ws_max_resident_groups_mfma(int device) {
   if (hipGetDeviceProperties(&prop, device) != hipSuccess) return 0;
   int per_cu = 0;
   // the version with two batch groups per workgroup has the larger LDS footprint and bounds both
-  const size_t lds = (size_t)2 * ((size_t)16 * 64 * 16 + 4 * 32 * 16) * sizeof(float);
+  const size_t lds = wsm_lds(64, 2, 1, 4, 2);
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_wsm<64, 2, 1>), hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)lds) != hipSuccess)
     return 0;
@@ -4820,7 +4936,7 @@ int ws_max_resident_groups_mfma8(int device) { // the instances for layers of 10
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) != hipSuccess) return 0;
   int per_cu = 0;
-  const size_t lds = ((size_t)2048 * 16 + 8 * 32 * 16) * sizeof(float);
+  const size_t lds = wsm_lds(64, 1, 1, 8, 2);
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_rec_wsm<64, 1, 1, 8>), hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)lds) != hipSuccess)
     return 0;

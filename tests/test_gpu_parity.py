@@ -326,6 +326,30 @@ def test_chip_wide_adjoint_two_batch_groups_per_workgroup(hidden, B, T, monkeypa
 
 
 @pytest.mark.parametrize("hidden,B,T", [
+    ((257,), 3, 7),                    # the narrowest: one value beyond 256, three spare columns of the exchange, one step per tile
+    ((512, 300), 16, 40),              # 16 rows per workgroup, two widths of a class, the narrower one's surplus workgroups
+    ((510,), 130, 6),                  # nine batch groups: more units than dies, 32 rows
+    ((1023, 640), 18, 9),              # the 1024 class, a ragged second batch group
+    ((1024, 1024, 1024), 64, 6)])      # 64 rows per workgroup, two units on a die
+def test_chip_wide_adjoint_inside_a_die(hidden, B, T, monkeypatch):
+    """Layers of 257..1024 neurons exchange through the L2 of one die where their units fit: against the oracle, and
+    bit-identical to the exchange through uncached memory (SNN_WS_KERNEL=uncached) and to 32 rows per workgroup (=single)."""
+    w = synth.Workload("die_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=0.6, seed=71 + B)
+    first, _ = _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 1)], nthreads=8, check_states=False)
+    d = synth.generate(w)
+    for mode in ("uncached", "single"):
+        monkeypatch.setenv("SNN_WS_KERNEL", mode)
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            net.snn_bptt(snn.SNN_STANDARD, 0, 0)
+            assert _identical(first, _gpu_grads(net, len(hidden))), mode
+        finally:
+            net.snn_destroy()
+    monkeypatch.delenv("SNN_WS_KERNEL")
+
+
+@pytest.mark.parametrize("hidden,B,T", [
     ((1025,), 3, 9),                   # one row in the last workgroup, a ragged batch group
     ((1500, 1100), 20, 10),            # both of the 1536 class in one launch, surplus workgroups of the narrower one
     ((1537, 1536), 17, 7),             # the two classes
