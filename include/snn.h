@@ -295,7 +295,8 @@ void snn_destroy(snn_ctx *ctx);
  *                                      never with its exchange inside one die
  *     SNN_CSR=0|1                      compressed rows of masked recurrent matrices never / wherever a kernel
  *                                      for them exists (default: where the firing-rate policy picks a gather)
- *     SNN_SEQ_SLICES=1|2|4|8           workgroups per batch element in the sequential part of wide layers
+ *     SNN_SEQ_SLICES=1|2|4|8           workgroups per batch element in the sequential part of wide layers, which then walk
+ *                                      the rows in memory (default up to 1024 neurons: slices of the matrix in LDS)
  *     SNN_FWD_FUSE=0                   wide layers over compressed rows: the dense currents for the next pipeline
  *                                      stage never ride in the launch of a stage's sequential parts
  *     SNN_SEQ_KERNEL=gather|rs         sequential forward part of layers of up to 256 neurons: event-driven gather

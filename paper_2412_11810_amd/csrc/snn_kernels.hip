@@ -23,6 +23,9 @@
 #define WAVE 64
 #define SNN_SEQ_GROUP 8 // steps whose per-step operands the sequential kernels load ahead in one go
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) float lds_float;
+typedef unsigned int csr_u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int csr_u32x4 __attribute__((ext_vector_type(4)));
 
 static __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 // Sum of x over the 64 lanes, the same bits in every lane (all lanes must be active): neighbours within quads
@@ -269,6 +272,45 @@ static __device__ __forceinline__ void gather1(__amdgpu_buffer_rsrc_t wres, cons
         for (int k = 0; k < NPT; ++k) acc[k] = acc[k] + (q + r0 + i < cnt ? w[r0 + i][k] : 0.0f);
     }
   }
+}
+
+// Exchange inside one die.  A value travels between two workgroups in 0.59 us through uncached memory and in 0.22 us
+// through the L2 of a die that both run on (ordinary memory, plain store, load that passes the L1 by), and the reads of
+// what the others have written, 16 to 64 KB per workgroup and step, come at the L2's rate.  The launchers put the
+// workgroups that exchange with each other at block indices that are equal modulo 8, which the hardware deals to
+// one die; whether it did is established here, once per launch: every workgroup of the unit posts the number of its die in
+// uncached memory (zero before the launch) and reads those of all the others.  All see the same numbers, so all decide alike.
+// Called by every thread of the workgroup, n <= 64.
+static __device__ __forceinline__ unsigned die_id() {
+  unsigned r;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(r));
+  return r & 15u;
+}
+static __device__ __forceinline__ bool unit_on_one_die(unsigned *posts, int me, int n, unsigned *err, unsigned spin_limit, bool *dead) {
+  __shared__ int s_one_die;
+  const unsigned mine = die_id() + 1u;
+  if (threadIdx.x == 0) __hip_atomic_store(&posts[me], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x < WAVE) {
+    const int i = (int)threadIdx.x;
+    unsigned got = mine, spins = 0;
+    bool late = false;
+    if (i < n)
+      while ((got = __hip_atomic_load(&posts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u || spin_limit == 0u) {
+        if (++spins > spin_limit ||
+            ((spins & 63u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          late = true;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    const bool gave_up = __ballot(late) != 0ull, one = __ballot(got != mine) == 0ull;
+    if (i == 0) s_one_die = gave_up ? 2 : one ? 1 : 0;
+  }
+  __syncthreads();
+  const int r = s_one_die;
+  if (r == 2) *dead = true; // keep going, never wait again
+  return r == 1;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -607,6 +649,246 @@ k_layer_seq_gather_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, Store
     if (own(k) && c0 + tid + k * nt < N) state[(size_t)b * SN + off + c0 + tid + k * nt] = v[k];
 }
 
+// Sequential part of layers of 257..1024 neurons.  One workgroup per batch element, walking the active rows of the matrix in
+// the L2, is bound by what one compute unit loads (two layers of 512 at 45 %: 470 KB per step, 5.3 us) or by its two barriers and
+// list (1024 at 5 %: 4.1 us).  Here a workgroup keeps LPB columns of W_rec for all presynaptic neurons in LDS (128 KB) for the
+// whole tile, and a wavefront owns them for 64 / LPB batch elements: no weight comes from memory in a step, no
+// barrier, wavefronts of different batch elements never wait for each other.  A step of a wavefront: the spike
+// words of its batch elements from the exchange, a list of the active rows in LDS (each lane the bits of LPB lanes' share in
+// ascending order), the walk over it (one 16-byte read for eight entries, then address, read, add per row; entries past the
+// end of the shorter list point at a row of zeros), the LIF update, the own spike bits with the number of the step to the exchange.
+// Spikes, states and currents of a step go to memory at the beginning of the next one, so that the polls, which wait
+// for every older access, do not meet them.  The `slices` workgroups of a unit (job, group of batch elements) exchange
+// through the L2 of one die (unit_on_one_die) or through uncached memory: two 32-bit halves per spike word, 8 bytes each with
+// the step as a tag, double-buffered by the parity of the step (who writes step s has read step s - 1 of all the others, who
+// had read step s - 2).
+// LPB = 64 up to 512 neurons, 32 up to 1024.  Per step: 128-2x512 at 45 %, batch 16: 5.3 -> 3.7 us (list
+// 0.3, walk 2.6: 24 cycles per row, most of them the issue of its one LDS read), 700-3x1024 at 5 %, batch 64: 4.1 -> 2.4.
+template <int LPB>
+__global__ void __launch_bounds__(1024)
+k_layer_seq_lds(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec st, uint64_t *xg, uint64_t *xl, unsigned *posts,
+                unsigned *err, unsigned spin_limit, int slices, int groups, int n_units, int h_max, int lcap) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int NBW = 64 / LPB, SB = LPB == 64 ? 8 : 32, LPH = 32 / SB; // batch elements per wavefront; bits per lane; lanes per half-word
+  const int k = (int)blockIdx.x >> 3, unit = ((int)blockIdx.x & 7) + 8 * (k / slices), js = k % slices;
+  if (unit >= n_units) return;
+  const int jq = unit / groups, gb = unit % groups;
+  const int l = jobs.j[jq].l, t0 = jobs.j[jq].t0, t1 = jobs.j[jq].t1, t_tile = jobs.j[jq].t_tile;
+  const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, Wd = net.Wd[l + 1], c0 = js * LPB;
+  if (c0 >= N) return; // a narrower layer than the widest of the launch
+  const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wave = tid >> 6;
+  const int q = lane / LPB, cl = lane % LPB; // batch element of the wavefront, column of the slice
+  const int b = (gb * (nt >> 6) + wave) * NBW + q, c = c0 + cl;
+  const bool bok = b < B, own = bok && c < N;
+  const int bc = bok ? b : B - 1, cc = c < N ? c : N - 1;
+  float *wl = (float *)smem;                                                                       // [N + 1][LPB], the last row zero
+  uint16_t *list = (uint16_t *)(wl + (size_t)(N + 1) * LPB) + (size_t)(wave * NBW + q) * lcap;     // [wavefronts][NBW][lcap]
+  {
+    // (16 bytes per load, up to 64 KB in flight; what a load takes beyond the end of its row is never used: no spike, no
+    // column there; beyond the matrix it reads 0)
+    const __amdgpu_buffer_rsrc_t wres =
+        __builtin_amdgcn_make_buffer_rsrc((void *)net.W_rec[l], 0, (int)((size_t)N * N * sizeof(float)), 0x00027000);
+    constexpr int UL = 16, TPR = LPB / 4;
+    const int cw = 4 * (tid % TPR), r0 = tid / TPR, rs = nt / TPR;
+    for (int r = r0; r < N; r += UL * rs) {
+      csr_u32x4 w[UL];
+#pragma unroll
+      for (int u = 0; u < UL; ++u)
+        w[u] = __builtin_amdgcn_raw_buffer_load_b128(wres, (uint32_t)((r + u * rs < N ? r + u * rs : N - 1) * N + c0 + cw) * 4u, 0, 0);
+#pragma unroll
+      for (int u = 0; u < UL; ++u)
+        if (r + u * rs < N) *reinterpret_cast<csr_u32x4 *>(wl + (size_t)(r + u * rs) * LPB + cw) = w[u];
+    }
+    if (tid < LPB) wl[(size_t)N * LPB + tid] = 0.0f;
+  }
+  bool dead = false;
+  const bool local = unit_on_one_die(posts + unit * slices, js, (N + LPB - 1) / LPB, err, spin_limit, &dead); // (a barrier: the weights are in)
+  if (__ballot(bok) == 0ull) return; // no batch element left for this wavefront
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)(local ? xl : xg), 0, (int)((size_t)(n_units / groups) * B * 2 * h_max * 8), 0x00027000);
+  // this lane's share of the spike words: SB bits from bit sb of half-word h on
+  const int h = cl / LPH, sb = cl % LPH * SB;
+  const int n_half = (N + 31) >> 5; // half-words with neurons (LPB = 32: each has its slice)
+  const bool need = bok && h < n_half;
+  const uint32_t xin = (uint32_t)(((size_t)(jq * B + bc) * 2) * h_max + (need ? h : 0)) * 8u, xpar = (uint32_t)h_max * 8u;
+  const uint32_t xout = (uint32_t)(((size_t)(jq * B + bc) * 2) * h_max + (c0 >> 5) + (LPB == 64 ? lane & 1 : 0)) * 8u;
+  const bool writer = bok && (LPB == 64 ? lane < 2 : cl == 0);
+  const bool half_left = LPB == 32 && writer && (c0 >> 5) + 1 == n_half && (n_half & 1); // the last word's upper half is nobody's
+  const size_t mstride = (size_t)B * Wd;
+  uint32_t *mask32 = reinterpret_cast<uint32_t *>(net.mask[l + 1]);
+  const size_t mh = (size_t)bc * 2 * Wd; // half-words in front of this batch element in a row
+  auto share = [&](uint32_t half) { return SB == 32 ? half : (half >> sb) & ((1u << (SB & 31)) - 1u); };
+  int mrow = (int)mrow_of(net, l + 1, t0);
+  const int ring = net.mring[l + 1];
+  uint32_t bits = need ? share(mask32[(size_t)mrow * 2 * mstride + mh + h]) : 0u; // the layer's spikes of the step before
+  bool sprev = own && ((mask32[(size_t)mrow * 2 * mstride + mh + (cc >> 5)] >> (cc & 31)) & 1u);
+  float v = state[(size_t)bc * SN + off + cc], it = 0.0f;
+  uint32_t mine = 0u; // writer: the half-word of the step
+  const float *icol = jobs.j[jq].iin + (size_t)bc * N + cc;
+  const size_t istride = (size_t)B * N;
+  const uint32_t lane_w = (uint32_t)(uintptr_t)(lds_float *)wl + (uint32_t)cl * 4u;
+  constexpr uint32_t ROWB = LPB * 4;
+  // the feed-forward currents of G steps, requested a group ahead and moved down one register per step
+  constexpr int G = SNN_SEQ_GROUP;
+  float ri[G], rn[G];
+  auto stage = [&](int t_lo) {
+#pragma unroll
+    for (int i = 0; i < G; ++i) rn[i] = icol[(size_t)((t_lo + 1 + i <= t1 ? t_lo + 1 + i : t1) - 1 - t_tile) * istride];
+  };
+  stage(t0);
+  StoreCursor sc;
+  sc.init(st, t0 + 1);
+  auto put_out = [&](int t) { // what step t leaves in memory
+    if (++mrow == ring) mrow = 0;
+    uint32_t *mp = mask32 + (size_t)mrow * 2 * mstride + mh + (c0 >> 5) + (LPB == 64 ? lane & 1 : 0);
+    if (writer) mp[0] = mine;
+    if (half_left) mp[1] = 0u;
+    const int sl = sc.slot(st, t);
+    sc.next(st);
+    if (own && sl >= 0) st.base[(size_t)sl * st.slot_stride + (size_t)b * SN + off + c] = v;
+    if (st.cur && t > st.cur_from && own) st.cur[(size_t)(t - st.cur_from - 1) * st.slot_stride + (size_t)b * SN + off + c] = it;
+  };
+  const uint32_t spare = (uint32_t)(lcap - 1) * 2u;
+  auto row = [&](uint32_t pair, auto hi) { // weight of this lane's column in the row named by one half of a pair of entries
+    uint32_t a;
+    if (decltype(hi)::value) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(a) : "v"(pair), "s"(ROWB), "v"(lane_w));
+    else asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(a) : "v"(pair), "s"(ROWB), "v"(lane_w));
+    return *(lds_float *)(uintptr_t)a;
+  };
+  auto rows8 = [&](const uint4 &e, float (&w)[8]) {
+    const uint32_t p[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      w[2 * i] = row(p[i], std::false_type{});
+      w[2 * i + 1] = row(p[i], std::true_type{});
+    }
+  };
+  auto run = [&](auto local_c) {
+    constexpr int ST = decltype(local_c)::value ? 0 : 17, LD = decltype(local_c)::value ? 16 : 17;
+    unsigned step = 0;
+    for (int t = t0 + 1; t <= t1; ++t, ++step) {
+      if (step % G == 0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) ri[i] = rn[i];
+        stage(t - 1 + G);
+      }
+      // ---- the active rows, ascending, and the sum over them ------------------------------------------
+      auto dpp_add = [](uint32_t x, auto ctrl, auto rows) {
+        return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+      };
+      using all = std::integral_constant<int, 0xF>;
+      float acc = 0.0f;
+      const auto pass = [&](uint32_t m) {
+        uint32_t x = (uint32_t)__popc(m);
+        const uint32_t n_own = x;
+        x = dpp_add(x, std::integral_constant<int, 0x111>{}, all{}); // row_shr 1, 2, 4, 8: running counts within 16 lanes
+        x = dpp_add(x, std::integral_constant<int, 0x112>{}, all{});
+        x = dpp_add(x, std::integral_constant<int, 0x114>{}, all{});
+        x = dpp_add(x, std::integral_constant<int, 0x118>{}, all{});
+        x = dpp_add(x, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{}); // row_bcast 15: rows 0 -> 1, 2 -> 3
+        if (LPB == 64) x = dpp_add(x, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{}); // row_bcast 31: -> rows 2, 3
+        const uint32_t n_lo = (uint32_t)__builtin_amdgcn_readlane((int)x, 31), n_hi = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+        const uint32_t n_max = LPB == 64 ? n_hi : (n_lo > n_hi ? n_lo : n_hi), n_mine = LPB == 64 ? n_hi : q ? n_hi : n_lo;
+        if (n_max == 0u) return;
+        const uint32_t n_pad = (n_max + 15u) & ~15u;
+        uint32_t at = (x - n_own) * 2u, left = m; // byte offset in the list of the next entry; bits to come
+        const uint32_t first = (uint32_t)(h * 32 + sb);
+        auto put = [&](uint32_t to, uint32_t entry) { *reinterpret_cast<uint16_t *>(reinterpret_cast<unsigned char *>(list) + to) = (uint16_t)entry; };
+        if (SB == 8) { // every bit in turn, what is not set to the spare entry at the list's end
+#pragma unroll
+          for (int i = 0; i < SB; ++i) {
+            const bool on = (m >> i) & 1u;
+            put(on ? at : spare, first + i);
+            at += on ? 2u : 0u;
+          }
+        } else { // the bits that are set, as long as any lane has one
+          while (__ballot(left != 0u) != 0ull) {
+            const bool on = left != 0u;
+            put(on ? at : spare, first + (uint32_t)__builtin_ctz(left | 0x80000000u));
+            left &= left - 1u;
+            at += 2u;
+          }
+        }
+        // rows of zeros up to the end of the longest list of the wavefront, and three groups more for the reads ahead
+        for (uint32_t i = n_mine + (uint32_t)cl; i < n_pad + 24u; i += LPB) list[i] = (uint16_t)N;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // (one wavefront's LDS accesses are carried out in order)
+        __builtin_amdgcn_wave_barrier();
+        // groups of eight rows, two per round: those of the next group are requested before this one's are added, the
+        // entries two groups ahead of their use
+        const uint4 *e8 = reinterpret_cast<const uint4 *>(list);
+        float wa[8], wb[8];
+        uint4 ea = e8[0], eb = e8[1];
+        rows8(ea, wa);
+        ea = e8[2];
+        uint32_t rounds = n_pad >> 4;
+        do {
+          rows8(eb, wb);
+          eb = e8[3];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc = acc + wa[u];
+          __builtin_amdgcn_sched_barrier(0);
+          rows8(ea, wa);
+          ea = e8[4];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc = acc + wb[u];
+          __builtin_amdgcn_sched_barrier(0);
+          e8 += 2;
+        } while (--rounds);
+        __builtin_amdgcn_wave_barrier();
+      };
+      // a list as long as the layer does not always fit: then a quarter of the neurons at a time
+      bool whole = true;
+      if (lcap < N + 40 + 8) {
+        uint32_t x = (uint32_t)__popc(bits);
+#pragma unroll
+        for (int o = 1; o < LPB; o <<= 1) x += __shfl_xor(x, o, WAVE);
+        whole = __ballot(x + 48u > (uint32_t)lcap) == 0ull;
+      }
+      if (whole) pass(bits);
+      else
+        for (int f = 0; f < 4; ++f) pass((h * 32 + sb) >> 8 == f ? bits : 0u);
+      // ---- LIF update, own spikes to the exchange ---------------------------------------------------------
+      float a = net.alpha * v;
+      if (sprev) a = a - net.theta;
+      it = ri[0] + acc;
+      v = a + it;
+      sprev = own && v > net.theta;
+      const uint64_t word = __ballot(sprev);
+      mine = (uint32_t)(word >> (LPB == 64 ? 32 * (lane & 1) : 32 * q));
+      const uint32_t par = (step & 1u) * xpar;
+      if (writer) __builtin_amdgcn_raw_buffer_store_b64(csr_u32x2{mine, step + 1u}, xres, xout + par, 0, ST);
+#pragma unroll
+      for (int i = 0; i + 1 < G; ++i) ri[i] = ri[i + 1];
+      if (t == t1) break; // the next tile reads the stored spike words
+      // ---- the layer's spikes of this step ------------------------------------------------------------------
+      if (spin_limit == 0u && !dead) { // only ever set by a test of this path: give up at once, arrived or not
+        __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        dead = true;
+      }
+      csr_u32x2 x;
+      for (unsigned spins = 0;;) {
+        asm volatile("" ::: "memory"); // every round reads again
+        x = __builtin_amdgcn_raw_buffer_load_b64(xres, xin + par, 0, LD);
+        if (__ballot(need && x.y != step + 1u) == 0ull || dead) break;
+        if (++spins > spin_limit ||
+            ((spins & 63u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          dead = true; // keep going to the end of the tile, never wait again
+          break;
+        }
+        if (!decltype(local_c)::value) __builtin_amdgcn_s_sleep(1);
+      }
+      bits = need ? share(x.x) : 0u;
+      put_out(t);
+    }
+    put_out(t1);
+  };
+  if (local) run(std::true_type{});
+  else run(std::false_type{});
+  if (own) state[(size_t)b * SN + off + c] = v;
+}
+
 // ------------------------------------------------------------------------------------------
 // A2 for masked recurrent matrices: the rows of active presynaptic neurons in compressed form (only the
 // synapses that exist).  A wavefront owns SNN_CSR_SUBW postsynaptic neurons and an accumulator for each in LDS.
@@ -625,9 +907,6 @@ struct CsrGroup { // the entries of U consecutive rows that fall into the wavefr
   uint32_t c[U];
   float v[U];
 };
-typedef __attribute__((address_space(3))) float lds_float;
-typedef unsigned int csr_u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int csr_u32x4 __attribute__((ext_vector_type(4)));
 // Requests the entries of rows q .. q + U - 1 of a block (positions and counts one row per lane in p0 / nn; q is a
 // constant after unrolling).  One 8-byte load per row from the packed copy (NetDev::csr_pk) through one descriptor
 // over the whole array: no scalar descriptor arithmetic per row (the compute unit's one scalar unit is what eight
@@ -1672,45 +1951,6 @@ static __device__ __forceinline__ uint32_t xenc(float v) {
   return e != 0u ? e : ~0x7fc00000u;
 }
 static __device__ __forceinline__ float xdec(uint32_t e) { return __uint_as_float(~e); }
-
-// Exchange inside one die.  A value travels between two workgroups in 0.59 us through uncached memory and in 0.22 us
-// through the L2 of a die that both run on (ordinary memory, plain store, load that passes the L1 by), and the reads of
-// what the others have written, 16 to 64 KB per workgroup and step, come at the L2's rate.  The launchers put the
-// workgroups that exchange with each other at block indices that are equal modulo 8, which the hardware deals to
-// one die; whether it did is established here, once per launch: every workgroup of the unit posts the number of its die in
-// uncached memory (zero before the launch) and reads those of all the others.  All see the same numbers, so all decide alike.
-// Called by every thread of the workgroup, n <= 64.
-static __device__ __forceinline__ unsigned die_id() {
-  unsigned r;
-  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(r));
-  return r & 15u;
-}
-static __device__ __forceinline__ bool unit_on_one_die(unsigned *posts, int me, int n, unsigned *err, unsigned spin_limit, bool *dead) {
-  __shared__ int s_one_die;
-  const unsigned mine = die_id() + 1u;
-  if (threadIdx.x == 0) __hip_atomic_store(&posts[me], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (threadIdx.x < WAVE) {
-    const int i = (int)threadIdx.x;
-    unsigned got = mine, spins = 0;
-    bool late = false;
-    if (i < n)
-      while ((got = __hip_atomic_load(&posts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u || spin_limit == 0u) {
-        if (++spins > spin_limit ||
-            ((spins & 63u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-          __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          late = true;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    const bool gave_up = __ballot(late) != 0ull, one = __ballot(got != mine) == 0ull;
-    if (i == 0) s_one_die = gave_up ? 2 : one ? 1 : 0;
-  }
-  __syncthreads();
-  const int r = s_one_die;
-  if (r == 2) *dead = true; // keep going, never wait again
-  return r == 1;
-}
 
 // Recurrent part, layers of up to H*KH neurons: the recurrent matrix stays in registers for the
 // whole chunk.  Thread (jj, h) keeps W_rec[j][h*KH .. h*KH+KH) for the R postsynaptic rows
@@ -4277,6 +4517,55 @@ static int seq_csr_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws
   return S;
 }
 
+// The sequential part of layers of 257..1024 neurons with the weights in LDS (k_layer_seq_lds): every job of the stage that
+// wide, units (job, group of batch elements) that fit the dies, one workgroup per compute unit, with as few wavefronts per
+// workgroup as that allows.  SNN_SEQ_SLICES asks for the walk through the L2 (1: unsliced).
+struct SeqLdsPlan { int lpb, waves, groups, slices, units, lcap; size_t lds; };
+static int seq_lds_die_slots(int device) { // workgroups of it that can be resident on a die
+  static int cached[16] = {};
+  if (device < 0 || device >= 16) return 0;
+  if (!cached[device]) {
+    hipDeviceProp_t prop;
+    int a = 0, b = 0;
+    if (hipGetDeviceProperties(&prop, device) != hipSuccess) return 0;
+    const size_t lds = SNN_LDS_PER_CU - 64;
+    for (const void *f : {reinterpret_cast<const void *>(k_layer_seq_lds<64>), reinterpret_cast<const void *>(k_layer_seq_lds<32>)})
+      if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_layer_seq_lds<64>, 1024, lds) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_layer_seq_lds<32>, 1024, lds) != hipSuccess) return 0;
+    cached[device] = a > 0 && b > 0 ? prop.multiProcessorCount / 8 : -1;
+  }
+  return cached[device] > 0 ? cached[device] : 0;
+}
+static bool seq_lds_plan(const NetDev &net, const SeqJobs &ga, const WsArgs *ws, SeqLdsPlan *p) {
+  if (!ws || !ws->xg || !ws->xl || ga.count < 1 || net.sel_slices != 0) return false;
+  int N = 0;
+  for (int i = 0; i < ga.count; ++i) {
+    const int n = net.N[ga.j[i].l];
+    if (n <= 256 || n > 1024) return false;
+    N = n > N ? n : N;
+  }
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return false;
+  const int slots = seq_lds_die_slots(device);
+  p->lpb = N <= 512 ? 64 : 32;
+  p->slices = (N + p->lpb - 1) / p->lpb;
+  if (p->slices > slots) return false;
+  const int per_wave = 64 / p->lpb, units_max = slots / p->slices * 8;
+  for (p->waves = 4; p->waves <= 16; p->waves *= 2) {
+    p->groups = (net.B + p->waves * per_wave - 1) / (p->waves * per_wave);
+    p->units = ga.count * p->groups;
+    if (p->units > units_max || p->units * p->slices > 64 * SNN_MAXL) continue;
+    const size_t weights = (size_t)(N + 1) * p->lpb * sizeof(float), lists = (size_t)p->waves * per_wave * sizeof(uint16_t);
+    const size_t room = (SNN_LDS_PER_CU - 64 - weights) / lists;
+    p->lcap = (int)((size_t)N + 48 < room ? (size_t)N + 56 : room) & ~7;
+    if (p->lcap < 256 + 48) continue; // a quarter of the widest layer, whole groups, the reads ahead, the spare entry
+    p->lds = weights + lists * p->lcap;
+    return true;
+  }
+  return false;
+}
+
 hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, float *state, const StoreSpec &st,
                           double *readout, int readout_init, float *work, hipStream_t s, const SpanHook *hook,
                           const FwdCallbacks *cb, const WsArgs *ws) {
@@ -4378,7 +4667,9 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
         n_max = net.N[ga.j[i].l] > n_max ? net.N[ga.j[i].l] : n_max;
       }
       const int S_csr = ga.count ? seq_csr_slices(net, ga, ws) : 0;
-      const int S = (ga.count && !S_csr) ? seq_slices(net, ga, ws, &npt_sl, &th_sl) : 1;
+      SeqLdsPlan lp{};
+      const bool in_lds = ga.count && !S_csr && seq_lds_plan(net, ga, ws, &lp);
+      const int S = (ga.count && !S_csr && !in_lds) ? seq_slices(net, ga, ws, &npt_sl, &th_sl) : 1;
       // Wide layers over compressed rows: the dense feed-forward currents for the next stage ride in the launch
       // of this stage's sequential parts (k_fwd_stage_csr) when all sequential workgroups fit beside one current
       // workgroup per compute unit; other current jobs (readout, matrices that fit the L2) go out on their own.
@@ -4426,6 +4717,23 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
           hipLaunchKernelGGL(k_layer_seq_csr_sl, dim3(B * S_csr, ga.count), dim3(256), lds_seq, s,
                              net, ga, state, st, S_csr, reinterpret_cast<uint64_t *>(ws->xg), wd_max, ws->err, ws->spin_limit);
         }
+      } else if (in_lds) {
+        // tags of the exchange entries and the posts of the dies start from zero in every launch
+        const size_t xbytes = (size_t)ga.count * B * 4 * wd_max * sizeof(uint64_t);
+        ZeroJobs clear{};
+        clear.add(ws->xg, xbytes);
+        clear.add(ws->xl, xbytes);
+        clear.add(ws->bar, (size_t)lp.units * lp.slices * sizeof(unsigned));
+        e = launch_fill_zero_jobs(clear, s);
+        if (e != hipSuccess) return e;
+        const dim3 grid((lp.units + 7) / 8 * 8 * lp.slices), block(64 * lp.waves);
+        uint64_t *xg = reinterpret_cast<uint64_t *>(ws->xg), *xl = reinterpret_cast<uint64_t *>(ws->xl);
+        if (lp.lpb == 64)
+          hipLaunchKernelGGL(k_layer_seq_lds<64>, grid, block, lp.lds, s, net, ga, state, st, xg, xl, ws->bar, ws->err, ws->spin_limit,
+                             lp.slices, lp.groups, lp.units, 2 * wd_max, lp.lcap);
+        else
+          hipLaunchKernelGGL(k_layer_seq_lds<32>, grid, block, lp.lds, s, net, ga, state, st, xg, xl, ws->bar, ws->err, ws->spin_limit,
+                             lp.slices, lp.groups, lp.units, 2 * wd_max, lp.lcap);
       } else if (ga.count && S > 1) {
         // tags of the exchange entries start from zero in every launch
         e = launch_fill_zero(ws->xg, (size_t)ga.count * B * 4 * wd_max * sizeof(uint64_t), s);
@@ -4711,6 +5019,8 @@ void adjoint_prepare(const NetDev &net, const WsArgs &ws) {
       int npt = 0, th = 0;
       (void)seq_slices(net, probe, &ws, &npt, &th);
       (void)seq_csr_slices(net, probe, &ws, false);
+      SeqLdsPlan lp{};
+      (void)seq_lds_plan(net, probe, &ws, &lp);
       int device = 0, n_cu = 0;
       if (hipGetDevice(&device) == hipSuccess) (void)fwd_stage_csr_per_cu(device, &n_cu);
     }

@@ -439,6 +439,43 @@ def test_sliced_sequential_forward_at_any_width(hidden, B, T, density, csr, monk
     _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
 
+@pytest.mark.parametrize("hidden,B,T,gain,tier", [
+    ((257,), 1, 70, 0.6, 0),                   # one neuron in the last slice; three idle wavefronts per workgroup
+    ((512, 300), 5, 130, 1.0, 0),              # two widths, a ragged group of batch elements, three tiles
+    ((513, 511), 9, 40, 0.7, 0),               # half-word slices, an odd number of them; a narrower layer in the wider class
+    ((1000,), 33, 20, 0.5, 0),
+    ((1024, 1024, 1024, 1024), 64, 12, 1.6, 0),  # sixteen wavefronts, lists shorter than the layer: a quarter of it at a time
+    ((640, 640), 3, 2200, 0.5, 1)])            # the ring of spike words
+def test_sequential_forward_with_the_weights_in_lds(hidden, B, T, gain, tier, monkeypatch):
+    """Layers of 257..1024 neurons keep a slice of W_rec in LDS and exchange spike words inside a die: spikes, potentials and
+    gradients of the walk through the L2 (SNN_SEQ_SLICES=1), and of the oracle where that is quick."""
+    w = synth.Workload("lds_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=gain, seed=131 + B)
+    d = synth.generate(w)
+    L = len(hidden)
+    got = {}
+    for slices in (None, "1"):
+        if slices:
+            monkeypatch.setenv("SNN_SEQ_SLICES", slices)
+        net = snn.from_workload(w, d, spike_tier=tier) if tier else snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            states = net.snn_debug_states(w.T) if T < 1000 else np.zeros(1)
+            net.snn_bptt(snn.SNN_DOUBLE, min(T, 20), 3)
+            got[slices] = _gpu_grads(net, L), [net.snn_get_spikes(l, w.T) for l in range(L)], states
+        finally:
+            net.snn_destroy()
+    monkeypatch.delenv("SNN_SEQ_SLICES")
+    assert _identical(got[None][0], got["1"][0])
+    for a, b in zip(got[None][1], got["1"][1]):
+        assert np.array_equal(a, b)
+        assert a.any()
+    assert np.array_equal(got[None][2], got["1"][2])
+    if gain > 1.5:
+        assert max(s.reshape(T, B, -1).sum(2).max() for s in got[None][1]) > 500, "no list was longer than the space for it"
+    if T * B * sum(hidden) < 400_000:
+        _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
+
+
 @pytest.mark.parametrize("hidden,B,T,force", [((2048, 2048), 3, 80, "0"), ((3072,), 3, 70, "0"), ((4096, 4096), 2, 20, "0"),
                                               ((512, 512), 5, 150, "8"), ((384,), 4, 100, "2")])
 def test_sliced_sequential_forward_is_bitwise_neutral(hidden, B, T, force, monkeypatch):
