@@ -71,26 +71,39 @@ static __device__ __forceinline__ size_t mrow_of(const NetDev &net, int li, int 
   return (size_t)(r > 0 ? t % r : t);
 }
 
-// acc = fma(x[lane n of the own 16-lane row], w[n], acc) for n = 0..15, one VOP2 instruction each:
-// the DPP row broadcast (row_newbcast:n) feeds lane n of every row to all 16 lanes of that row, so a
-// register whose lanes hold 16 consecutive operands replaces 16 scalar broadcasts.  The leading
-// s_nop covers the wait states a DPP read needs after a VALU write of its source or of EXEC (the
-// compiler does not see into the asm).  One accumulator: a strictly sequential chain.
+// acc = fma(x0[lane n of the own 16-lane row], wa[ba + n], acc) for n = 0..15, then x1 with wb[bb + n], one VOP2 instruction
+// each: the DPP row broadcast (row_newbcast:n) feeds lane n of every row to all 16 lanes of that row, so a register whose
+// lanes hold 16 consecutive operands replaces 16 scalar broadcasts.  The leading s_nop covers the wait states a DPP read
+// needs after a VALU write of its source (the compiler does not see into the asm).  One accumulator: a strictly
+// sequential chain, 4.9 cycles per term.
 #define DPP_BC(n) " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
-#define FMAC16_1(acc, x, w, b)                                                                              \
-  asm volatile("s_nop 4\n\t"                                                                                \
-               "v_fmac_f32_dpp %0, %1, %2" DPP_BC(0) "v_fmac_f32_dpp %0, %1, %3" DPP_BC(1)                  \
-               "v_fmac_f32_dpp %0, %1, %4" DPP_BC(2) "v_fmac_f32_dpp %0, %1, %5" DPP_BC(3)                  \
-               "v_fmac_f32_dpp %0, %1, %6" DPP_BC(4) "v_fmac_f32_dpp %0, %1, %7" DPP_BC(5)                  \
-               "v_fmac_f32_dpp %0, %1, %8" DPP_BC(6) "v_fmac_f32_dpp %0, %1, %9" DPP_BC(7)                  \
-               "v_fmac_f32_dpp %0, %1, %10" DPP_BC(8) "v_fmac_f32_dpp %0, %1, %11" DPP_BC(9)                \
-               "v_fmac_f32_dpp %0, %1, %12" DPP_BC(10) "v_fmac_f32_dpp %0, %1, %13" DPP_BC(11)              \
-               "v_fmac_f32_dpp %0, %1, %14" DPP_BC(12) "v_fmac_f32_dpp %0, %1, %15" DPP_BC(13)              \
-               "v_fmac_f32_dpp %0, %1, %16" DPP_BC(14) "v_fmac_f32_dpp %0, %1, %17" DPP_BC(15)              \
+#define FMAC32_1(acc, x0, x1, wa, ba, wb, bb)                                                               \
+  asm volatile("s_nop 1\n\t"                                                                                \
+               "v_fmac_f32_dpp %0, %1, %3" DPP_BC(0) "v_fmac_f32_dpp %0, %1, %4" DPP_BC(1)                 \
+               "v_fmac_f32_dpp %0, %1, %5" DPP_BC(2) "v_fmac_f32_dpp %0, %1, %6" DPP_BC(3)                 \
+               "v_fmac_f32_dpp %0, %1, %7" DPP_BC(4) "v_fmac_f32_dpp %0, %1, %8" DPP_BC(5)                 \
+               "v_fmac_f32_dpp %0, %1, %9" DPP_BC(6) "v_fmac_f32_dpp %0, %1, %10" DPP_BC(7)                \
+               "v_fmac_f32_dpp %0, %1, %11" DPP_BC(8) "v_fmac_f32_dpp %0, %1, %12" DPP_BC(9)               \
+               "v_fmac_f32_dpp %0, %1, %13" DPP_BC(10) "v_fmac_f32_dpp %0, %1, %14" DPP_BC(11)             \
+               "v_fmac_f32_dpp %0, %1, %15" DPP_BC(12) "v_fmac_f32_dpp %0, %1, %16" DPP_BC(13)             \
+               "v_fmac_f32_dpp %0, %1, %17" DPP_BC(14) "v_fmac_f32_dpp %0, %1, %18" DPP_BC(15)             \
+               "v_fmac_f32_dpp %0, %2, %19" DPP_BC(0) "v_fmac_f32_dpp %0, %2, %20" DPP_BC(1)               \
+               "v_fmac_f32_dpp %0, %2, %21" DPP_BC(2) "v_fmac_f32_dpp %0, %2, %22" DPP_BC(3)               \
+               "v_fmac_f32_dpp %0, %2, %23" DPP_BC(4) "v_fmac_f32_dpp %0, %2, %24" DPP_BC(5)               \
+               "v_fmac_f32_dpp %0, %2, %25" DPP_BC(6) "v_fmac_f32_dpp %0, %2, %26" DPP_BC(7)               \
+               "v_fmac_f32_dpp %0, %2, %27" DPP_BC(8) "v_fmac_f32_dpp %0, %2, %28" DPP_BC(9)               \
+               "v_fmac_f32_dpp %0, %2, %29" DPP_BC(10) "v_fmac_f32_dpp %0, %2, %30" DPP_BC(11)             \
+               "v_fmac_f32_dpp %0, %2, %31" DPP_BC(12) "v_fmac_f32_dpp %0, %2, %32" DPP_BC(13)             \
+               "v_fmac_f32_dpp %0, %2, %33" DPP_BC(14) "v_fmac_f32_dpp %0, %2, %34" DPP_BC(15)             \
                : "+v"(acc)                                                                                  \
-               : "v"(x), "v"(w[b + 0]), "v"(w[b + 1]), "v"(w[b + 2]), "v"(w[b + 3]), "v"(w[b + 4]),         \
-                 "v"(w[b + 5]), "v"(w[b + 6]), "v"(w[b + 7]), "v"(w[b + 8]), "v"(w[b + 9]), "v"(w[b + 10]), \
-                 "v"(w[b + 11]), "v"(w[b + 12]), "v"(w[b + 13]), "v"(w[b + 14]), "v"(w[b + 15]))
+               : "v"(x0), "v"(x1), "v"(wa[ba + 0]), "v"(wa[ba + 1]), "v"(wa[ba + 2]), "v"(wa[ba + 3]) \
+                 , "v"(wa[ba + 4]), "v"(wa[ba + 5]), "v"(wa[ba + 6]), "v"(wa[ba + 7]) \
+                 , "v"(wa[ba + 8]), "v"(wa[ba + 9]), "v"(wa[ba + 10]), "v"(wa[ba + 11]) \
+                 , "v"(wa[ba + 12]), "v"(wa[ba + 13]), "v"(wa[ba + 14]), "v"(wa[ba + 15]) \
+                 , "v"(wb[bb + 0]), "v"(wb[bb + 1]), "v"(wb[bb + 2]), "v"(wb[bb + 3]) \
+                 , "v"(wb[bb + 4]), "v"(wb[bb + 5]), "v"(wb[bb + 6]), "v"(wb[bb + 7]) \
+                 , "v"(wb[bb + 8]), "v"(wb[bb + 9]), "v"(wb[bb + 10]), "v"(wb[bb + 11]) \
+                 , "v"(wb[bb + 12]), "v"(wb[bb + 13]), "v"(wb[bb + 14]), "v"(wb[bb + 15]))
 
 // ------------------------------------------------------------------------------------------
 // A1 (inputs): byte spikes [T][B][n_in] -> bit words mask0[t+1][b][w] (row 0 = step 0 = zeros)
@@ -349,97 +362,177 @@ struct StoreCursor {
   }
 };
 
-// Sequential part, layers of up to NW neurons: the recurrent matrix stays in registers (thread i keeps
-// column i, W_rec[0..NW)[i]).  The previous step's spike words are shared through LDS; each lane turns
-// bits into 0.0f/1.0f (lane L of register g: spike 16g + L%16), a DPP row broadcast feeds spike j to
-// every lane and I_rec = fma(s_j, w_j, I_rec) runs over ascending j: fma(1, w, a) = a + w rounded once
-// and fma(0, w, a) = a, i.e. exactly the ascending sum over the active neurons.  One instruction per
-// presynaptic neuron, no memory traffic in the loop, one barrier per step.
+// Sequential part, layers of up to NW neurons (a multiple of 32): the recurrent matrix stays with the threads (thread i keeps
+// column i, W_rec[0..NW)[i]), as far as it goes in registers; 16 (NW = 224) or 48 (256) rows sit in LDS, four to a
+// 16-byte read, read into one set of 16 registers well ahead of their use -- the instructions of the chain reach 256
+// registers, and a weight parked beyond them (an accumulator register) costs a copy per step, as long as its own term.
+// A thread writes its spike as 0.0f / 1.0f to LDS; lane L of register g reads spike 16 g + L % 16 of the previous
+// step from there, a DPP row broadcast feeds spike j to every lane and I_rec = fma(s_j, w_j, I_rec) runs over ascending
+// j: fma(1, w, a) = a + w rounded once and fma(0, w, a) = a, i.e. exactly the ascending sum over the active neurons.
+// What bounds a step is that chain (4.9 cycles per presynaptic neuron), so nothing else is on it: the instance has the
+// layer's width rounded up to 32, what a step leaves in memory goes out at the beginning of the next one, steps and
+// slots are counted in scalar registers.  One barrier per step.  700-2x256, batch 32: 1.28 -> 0.9 us per step, of which
+// the weights' way into the registers, 64 steps apart, 0.22 -> 0.07.
+static __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <int NW> struct SeqRs {
+  static constexpr int lds_rows = NW > 224 ? 48 : NW > 208 ? 16 : 0;
+  static constexpr int lds_bytes = ((2 + SNN_SEQ_GROUP) * 256 + lds_rows * 256) * 4; // spikes, currents, rows
+  // sub-blocks of 16 presynaptic neurons whose rows sit in LDS: 3, 8 and 13
+  static constexpr bool in_lds(int s) { return s % 5 == 3 && s / 5 < lds_rows / 16; }
+  static constexpr int reg_at(int s) { // registers in front of sub-block s
+    int r = 0;
+    for (int k = 0; k < s; ++k) r += in_lds(k) ? 0 : 16;
+    return r;
+  }
+};
 template <int NW>
 __device__ __forceinline__ void layer_seq_rs_body(const NetDev &net, const SeqJob &jb, float *__restrict__ state,
-                                                  const StoreSpec &st, int b) {
-  constexpr int NWD = NW / 64;
-  __shared__ uint64_t sw[2][NWD];
-  __shared__ float ring[SNN_SEQ_GROUP][NW];
-  const int l = jb.l, t0 = jb.t0, t1 = jb.t1;
-  const int t_tile = jb.t_tile;
-  const float *__restrict__ iin = jb.iin;
-  const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, Wd = net.Wd[l + 1];
-  const int i = threadIdx.x, lane = lane_id(), wave = i >> 6;
+                                                  const StoreSpec &st, int b_in, unsigned char *smem) {
+  using C = SeqRs<NW>;
+  constexpr int NR = NW - C::lds_rows, G = SNN_SEQ_GROUP, NS = NW / 16;
+  float *sf = reinterpret_cast<float *>(smem), *ring = sf + 2 * 256;   // [2][256] spikes of a step; [G][256]
+  const int i = threadIdx.x, lane = lane_id(), wave = uniform(i >> 6);
+  if (wave >= (NW + 63) / 64) return; // a workgroup of a wider layer's size
+  const int l = uniform(jb.l), t0 = uniform(jb.t0), t1 = uniform(jb.t1), t_tile = uniform(jb.t_tile), b = uniform(b_in);
+  const int N = uniform(net.N[l]), off = uniform(net.off[l]), Wd = uniform(net.Wd[l + 1]), B = net.B, SN = net.SN;
   const bool own = i < N;
-  float w[NW];
+  const int ic = own ? i : N - 1;
+  float4 *wl = reinterpret_cast<float4 *>(ring + G * 256);             // [lds_rows / 4][256]
+  // (rows and columns past the layer's width read 0: beyond the end of the matrix; no load is conditional)
+  float w[NR];
+  {
+    const __amdgpu_buffer_rsrc_t wres =
+        __builtin_amdgcn_make_buffer_rsrc((void *)net.W_rec[l], 0, (int)((size_t)N * N * sizeof(float)), 0x00027000);
+    const uint32_t col = own ? (uint32_t)i * 4u : 0x80000000u, n4 = (uint32_t)N * 4u;
 #pragma unroll
-  for (int q = 0; q < NW; ++q) w[q] = (own && q < N) ? net.W_rec[l][(size_t)q * N + i] : 0.0f;
-  float v = own ? state[(size_t)b * SN + off + i] : 0.0f;
-  uint64_t *mrow = net.mask[l + 1] + (size_t)b * Wd + wave;
+    for (int s = 0; s < NS; ++s) {
+      float m[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) m[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, col, (uint32_t)(16 * s + r) * n4, 0));
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (!C::in_lds(s)) w[C::reg_at(s) + r] = m[r];
+      if (C::in_lds(s))
+#pragma unroll
+        for (int r = 0; r < 16; r += 4) wl[(4 * (s / 5) + r / 4) * 256 + i] = make_float4(m[r], m[r + 1], m[r + 2], m[r + 3]);
+    }
+  }
+  float v = state[(size_t)b * SN + off + ic];
   const size_t mstride = (size_t)B * Wd;
-  if (i < NWD) sw[0][i] = i < Wd ? net.mask[l + 1][mrow_of(net, l + 1, t0) * mstride + (size_t)b * Wd + i] : 0ull;
-  __syncthreads();
-  bool sprev = (sw[0][wave] >> lane) & 1ull;
-  int cur = 0;
-  const float *icol = iin + (size_t)b * N + i;
-  const size_t istride = (size_t)B * N;
+  uint64_t *const mbase = net.mask[l + 1] + (size_t)b * Wd + (wave < Wd ? wave : 0);
+  const int rlen = uniform(net.mring[l + 1]);
+  int mrow = uniform((int)mrow_of(net, l + 1, t0));
+  uint64_t *mp = mbase + (size_t)mrow * mstride;
+  const uint64_t w0 = wave < Wd ? *mp : 0ull;
+  bool sprev = own && ((w0 >> lane) & 1ull);
+  uint64_t word = 0ull;
+  sf[i] = sprev ? 1.0f : 0.0f;
   // The feed-forward currents of G steps are loaded one group ahead, parked in a thread-private
   // column of an LDS ring when their group starts (the only point that waits for them) and read
   // from there: no step waits on global memory.
-  constexpr int G = SNN_SEQ_GROUP;
+  const float *icol = jb.iin + (size_t)b * N;
+  const size_t istride = (size_t)B * N;
   float ri[G];
   auto stage_issue = [&](int t_lo) { // steps t_lo + 1 .. t_lo + G (steps past the end re-read the last one)
 #pragma unroll
     for (int k = 0; k < G; ++k) {
       const int t = t_lo + 1 + k <= t1 ? t_lo + 1 + k : t1;
-      ri[k] = icol[(size_t)(t - 1 - t_tile) * istride];
+      ri[k] = (icol + (size_t)(t - 1 - t_tile) * istride)[ic];
     }
   };
   // the weights are in registers from here on (otherwise the compiler, which cannot tell their loads
   // from the staged ones, would wait for every outstanding load before each block of FMAs)
   __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0)
-  if (own && t1 > t0) stage_issue(t0);
-  StoreCursor sc;
-  sc.init(st, t0 + 1);
-  for (int tg = t0; tg < t1; tg += G) {
-    if (own) {
-#pragma unroll
-      for (int k = 0; k < G; ++k) ring[k][i] = ri[k];
-      if (tg + G < t1) stage_issue(tg + G);
-    }
-    const int thi = tg + G < t1 ? tg + G : t1;
-    for (int t = tg + 1; t <= thi; ++t) {
-      const float in_t = own ? ring[t - tg - 1][i] : 0.0f;
-      // lane L of sb[g] holds spike 16g + L%16 of the previous step as 0.0f / 1.0f
-      // (one bit-field extract from the 32-bit half that holds the 16 spikes, one convert)
-      float sb[NW / 16];
-      const uint32_t *sw32 = reinterpret_cast<const uint32_t *>(sw[cur]);
-#pragma unroll
-      for (int g = 0; g < NW / 16; ++g)
-        sb[g] = (float)__builtin_amdgcn_ubfe(sw32[g >> 1], (uint32_t)(16 * (g & 1) + (lane & 15)), 1u);
-      float acc = 0.0f;
-#pragma unroll
-      for (int g = 0; g < NW / 16; ++g) FMAC16_1(acc, sb[g], w, 16 * g);
-      float a = net.alpha * v;
-      if (sprev) a = a - net.theta;
-      v = a + (in_t + acc);
-      sprev = own && v > net.theta;
-      const uint64_t word = __ballot(sprev);
-      if (lane == 0) {
-        sw[cur ^ 1][wave] = word;
-        if (wave < Wd) mrow[mrow_of(net, l + 1, t) * mstride] = word;
-      }
-      const int sl = sc.slot(st, t);
-      if (own && sl >= 0) st.base[(size_t)sl * st.slot_stride + (size_t)b * SN + off + i] = v;
-      sc.next(st);
-      __syncthreads();
-      cur ^= 1;
-    }
+  stage_issue(t0);
+  // the next step that stores its state, and its slot
+  int t_store = t1 + 1, slot = 0;
+  if (st.base) {
+    const int d = t0 + 1 - st.t_base, q = (d + st.interval - 1) / st.interval;
+    t_store = uniform(st.t_base + q * st.interval);
+    slot = uniform(q - 1 + st.slot0);
   }
+  auto put_out = [&](int t) { // what step t leaves in memory
+    mp += mstride;
+    if (++mrow == rlen) {
+      mrow = 0;
+      mp = mbase;
+    }
+    if (lane == 0 && wave < Wd) *mp = word;
+    if (t == t_store) {
+      if (t <= st.t_max && own)
+        (st.base + (size_t)(st.slot_mod > 0 ? slot % st.slot_mod : slot) * st.slot_stride + (size_t)b * SN + off)[i] = v;
+      t_store += st.interval;
+      ++slot;
+    }
+  };
+  __syncthreads();
+  int cur = 0;
+  for (int t = t0 + 1; t <= t1; ++t) {
+    const float *s16 = sf + cur + (lane & 15);
+    float x[NS], m[16];
+#pragma unroll
+    for (int g = 0; g < NS; ++g) x[g] = s16[16 * g];
+    auto lds_rows = [&](int s) {
+#pragma unroll
+      for (int r = 0; r < 16; r += 4) {
+        const float4 f = wl[(4 * (s / 5) + r / 4) * 256 + i];
+        m[r] = f.x; m[r + 1] = f.y; m[r + 2] = f.z; m[r + 3] = f.w;
+      }
+    };
+    if (C::lds_rows) lds_rows(3);
+    const int k = (t - t0 - 1) & (G - 1);
+    if (t > t0 + 1) put_out(t - 1);
+    if (k == 0) {
+#pragma unroll
+      for (int q = 0; q < G; ++q) ring[q * 256 + i] = ri[q];
+      if (t + G <= t1) stage_issue(t - 1 + G);
+    }
+    const float in_t = ring[k * 256 + i];
+    float acc = 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < NS; s += 2) {
+      if (C::in_lds(s)) FMAC32_1(acc, x[s], x[s + 1], m, 0, w, C::reg_at(s + 1));
+      else if (C::in_lds(s + 1)) FMAC32_1(acc, x[s], x[s + 1], w, C::reg_at(s), m, 0);
+      else FMAC32_1(acc, x[s], x[s + 1], w, C::reg_at(s), w, C::reg_at(s + 1));
+      const int done = C::in_lds(s) ? s : C::in_lds(s + 1) ? s + 1 : -1; // the next rows from LDS follow at once
+      if (done >= 0 && C::in_lds(done + 5)) {
+        __builtin_amdgcn_sched_barrier(0);
+        lds_rows(done + 5);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    float a = net.alpha * v;
+    if (sprev) a = a - net.theta;
+    v = a + (in_t + acc);
+    sprev = own && v > net.theta;
+    word = __ballot(sprev);
+    cur ^= 256;
+    sf[cur + i] = sprev ? 1.0f : 0.0f;
+    __syncthreads();
+  }
+  put_out(t1);
   if (own) state[(size_t)b * SN + off + i] = v;
+}
+// The instance for a layer's width, uniform per workgroup
+template <int NW>
+__device__ __forceinline__ void layer_seq_rs_any(const NetDev &net, const SeqJob &jb, float *__restrict__ state, const StoreSpec &st, int b,
+                                                 unsigned char *smem) {
+  const int N = uniform(net.N[uniform(jb.l)]);
+  if constexpr (NW > 32)
+    if (N <= NW - 32) {
+      layer_seq_rs_any<NW - 32>(net, jb, state, st, b, smem);
+      return;
+    }
+  layer_seq_rs_body<NW>(net, jb, state, st, b, smem);
 }
 
 // blockIdx.y selects the (layer, tile) this workgroup runs: the layers are pipelined, a few tiles apart
 template <int NW>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(NW)
 k_layer_seq_rs(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec st) {
-  layer_seq_rs_body<NW>(net, jobs.j[blockIdx.y], state, st, (int)blockIdx.x);
+  extern __shared__ __align__(16) unsigned char smem[];
+  layer_seq_rs_any<NW>(net, jobs.j[blockIdx.y], state, st, (int)blockIdx.x, smem);
 }
 
 // Sequential part, any layer width: event-driven.  The layer's spikes of the previous step are kept
@@ -1624,7 +1717,7 @@ k_fwd_stage(NetDev net, SeqJobs sj, float *__restrict__ state, StoreSpec st, Cur
   extern __shared__ __align__(16) unsigned char smem[];
   int v = (int)blockIdx.x; // every branch below is uniform per workgroup
   if (v < n_seq_blocks) {
-    layer_seq_rs_body<256>(net, sj.j[v / net.B], state, st, v % net.B);
+    layer_seq_rs_any<256>(net, sj.j[v / net.B], state, st, v % net.B, smem);
     return;
   }
   v -= n_seq_blocks;
@@ -4356,11 +4449,12 @@ static hipError_t launch_fwd_stage(const NetDev &net, const SeqJobs &sj, float *
   unsigned gx;
   int ws, lcap;
   currents_geometry(net, cj, &gx, &ws, &lcap);
-  // the sequential part holds ~8 KB of static LDS, the current part 8 KB; asking for 72 KB more puts the
-  // total above half of a compute unit's 160 KB, so every workgroup gets a compute unit of its own
+  // the current part holds 8 KB of static LDS, the sequential part 58 KB of the dynamic; 72 KB of that put the
+  // total at half of a compute unit's 160 KB, so every workgroup gets a compute unit of its own
   size_t lds = currents_lds(4, ws, lcap);
   if (lds + 17 * 1024 > SNN_LDS_PER_CU) return hipErrorInvalidValue; // the caller checks fwd_stage_fits first
-  if (lds < 72 * 1024) lds = 72 * 1024;
+  static_assert(SeqRs<256>::lds_bytes <= 72 * 1024, "");
+  if (lds < 73 * 1024) lds = 73 * 1024;
   const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void *>(k_fwd_stage),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (ea != hipSuccess) return ea;
@@ -4650,7 +4744,7 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
         if (e != hipSuccess) return e;
         if (rs.count) {
           hb(4);
-          hipLaunchKernelGGL((k_layer_seq_rs<256>), dim3(B, rs.count), dim3(256), 0, s, net, rs, state, st);
+          hipLaunchKernelGGL((k_layer_seq_rs<256>), dim3(B, rs.count), dim3(256), SeqRs<256>::lds_bytes, s, net, rs, state, st);
           he();
         }
         if (ro_pending.n) { scan_now(ro_pending); ro_pending = RoJob{}; }
@@ -4694,9 +4788,9 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
       if (e != hipSuccess) return e;
       hb(cj_fused.count ? 8 : 4);
       if (rs.count) {
-        if (nw <= 64) hipLaunchKernelGGL((k_layer_seq_rs<64>), dim3(B, rs.count), dim3(64), 0, s, net, rs, state, st);
-        else if (nw <= 128) hipLaunchKernelGGL((k_layer_seq_rs<128>), dim3(B, rs.count), dim3(128), 0, s, net, rs, state, st);
-        else hipLaunchKernelGGL((k_layer_seq_rs<256>), dim3(B, rs.count), dim3(256), 0, s, net, rs, state, st);
+        if (nw <= 64) hipLaunchKernelGGL((k_layer_seq_rs<64>), dim3(B, rs.count), dim3(64), SeqRs<64>::lds_bytes, s, net, rs, state, st);
+        else if (nw <= 128) hipLaunchKernelGGL((k_layer_seq_rs<128>), dim3(B, rs.count), dim3(128), SeqRs<128>::lds_bytes, s, net, rs, state, st);
+        else hipLaunchKernelGGL((k_layer_seq_rs<256>), dim3(B, rs.count), dim3(256), SeqRs<256>::lds_bytes, s, net, rs, state, st);
       }
       if (S_csr) {
         // tags of the exchange entries start from zero in every launch

@@ -439,6 +439,15 @@ def test_sliced_sequential_forward_at_any_width(hidden, B, T, density, csr, monk
     _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
 
+@pytest.mark.parametrize("hidden,T", [((1, 31, 33), 30), ((64, 65, 96), 70), ((127, 128, 129), 66), ((160, 191, 193), 30),
+                                      ((208, 224, 225), 70), ((241, 255, 256), 67)])
+def test_register_stationary_forward_widths(hidden, T):
+    """Layers of up to 256 neurons: an instance per 32 neurons, rows in LDS from 209 on, two widths of a class and narrower
+    layers beside them in one launch, tiles that are no multiple of eight steps: spikes, potentials, gradients of the oracle."""
+    w = synth.Workload("rs_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=3, p_in=0.1, gain=1.0, seed=151 + T)
+    _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 7), (snn.SNN_DOUBLE, 10, 3)], nthreads=3)
+
+
 @pytest.mark.parametrize("hidden,B,T,gain,tier", [
     ((257,), 1, 70, 0.6, 0),                   # one neuron in the last slice; three idle wavefronts per workgroup
     ((512, 300), 5, 130, 1.0, 0),              # two widths, a ragged group of batch elements, three tiles
