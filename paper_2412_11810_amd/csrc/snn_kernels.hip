@@ -2045,115 +2045,144 @@ static __device__ __forceinline__ uint32_t xenc(float v) {
 }
 static __device__ __forceinline__ float xdec(uint32_t e) { return __uint_as_float(~e); }
 
-// Recurrent part, layers of up to H*KH neurons: the recurrent matrix stays in registers for the
-// whole chunk.  Thread (jj, h) keeps W_rec[j][h*KH .. h*KH+KH) for the R postsynaptic rows
-// j = jj, jj + NJR, ..., jj + (R-1)*NJR (H threads per row, each a slice of the reduction; partial sums
-// combined in a fixed order).  dv_{t+1} is broadcast from LDS; every value read feeds R FMAs: the LDS
-// traffic that bounds this kernel (every thread re-reading its slice of dv) shrinks by R, while the
-// weights per thread stay R*KH.  No weight traffic and no waiting on global memory in the time loop
-// (operands staged G steps ahead), two barriers per step.  One workgroup per batch element,
-// H*NJR threads.
-template <int KH, int H, int R>
-__device__ __forceinline__ void adj_rec_rs_body(const NetDev &net, const AdjJob &jb, float *__restrict__ carry, int b) {
-  __shared__ __align__(16) float x[2][H * KH];
-  __shared__ float part[H][256];
-  __shared__ float ring[2 * SNN_SEQ_GROUP][256];
-  const int l = jb.l, t0 = jb.t0, t1 = jb.t1, t_base = jb.t_base, carry_init = jb.carry_init;
-  float *__restrict__ vbuf = jb.vbuf;
-  const float *__restrict__ up = jb.up;
-  const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, ldu = N;
-  const int NJR = blockDim.x / H, tid = threadIdx.x;
-  const int jj = tid % NJR, h = tid / NJR;
-  const int j = tid;                 // finalising role: the first R*NJR threads own one row each
-  const bool own = tid < R * NJR && j < N;
+// Recurrent part, layers of up to 32 KQ neurons: the recurrent matrix stays in registers for the whole chunk.  One workgroup
+// per batch element, KQ wavefronts of 32 postsynaptic rows each: lane (g, h) keeps four rows (4 g .. 4 g + 3 of the wavefront's)
+// and an eighth of the reduction range (the presynaptic neurons 32 q + 4 h + c), so that a wavefront reads dv_{t+1} in KQ
+// 16-byte LDS reads without conflicts, every value feeds four FMAs, and the eight partial sums of a row meet inside eight
+// neighbouring lanes (row-local moves, a fixed order) instead of through LDS and a second barrier.  Lane h < 4 of a
+// group then finishes row h.  Bound by the vector unit's instructions: 16 KQ FMAs per wavefront and step (1024 cycles at 256
+// neurons, two wavefronts per SIMD) and what surrounds them.  An instance per 32 neurons.  Per step: 200 neurons 0.85 -> 0.55 us; 256 neurons 0.80 ->
+// 0.73, where the weight-gradient tiles of the same launch bound the stage (85 of 94 us for 128 steps).
+template <int KQ>
+__device__ __forceinline__ void adj_rec_rs_body(const NetDev &net, const AdjJob &jb, float *__restrict__ carry, int b_in,
+                                                float (*x)[256], float (*ring)[256]) {
+  constexpr int G = SNN_SEQ_GROUP;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), h = lane & 7;
+  if (wave >= KQ) return; // a workgroup of a wider layer's size
+  const int l = uniform(jb.l), t0 = uniform(jb.t0), t1 = uniform(jb.t1), t_base = uniform(jb.t_base), carry_init = uniform(jb.carry_init), b = uniform(b_in);
+  const int N = uniform(net.N[l]), off = uniform(net.off[l]), B = net.B, SN = net.SN;
+  const int jr = 32 * wave + 4 * (lane >> 3); // first of this lane's rows
+  const int j = jr + (h & 3);                 // the row it finishes
+  const bool own = h < 4 && j < N;
+  const int jc = j < N ? j : N - 1;
   float *cb = carry + (size_t)b * (SN + net.n_out) + off;
-
-  float w[R][KH];
+  float w[4][KQ][4];
+  {
+    // (rows past the layer's width: beyond the end of the matrix, 0; what a 16-byte load takes beyond its row is masked)
+    const __amdgpu_buffer_rsrc_t wres =
+        __builtin_amdgcn_make_buffer_rsrc((void *)net.W_rec[l], 0, (int)((size_t)N * N * sizeof(float)), 0x00027000);
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int q = 0; q < KH; ++q) {
-      const int n = h * KH + q, jr = jj + r * NJR;
-      w[r][q] = (jr < N && n < N) ? net.W_recT[l][(size_t)n * N + jr] : 0.0f; // = W_rec[jr][n], coalesced over jj
-    }
-  for (int i = tid; i < H * KH; i += blockDim.x) {
+      for (int q = 0; q < KQ; ++q) {
+        const csr_u32x4 f = __builtin_amdgcn_raw_buffer_load_b128(wres, (uint32_t)((jr + r) * N + 32 * q + 4 * h) * 4u, 0, 0);
+        w[r][q][0] = __uint_as_float(f.x); w[r][q][1] = __uint_as_float(f.y);
+        w[r][q][2] = __uint_as_float(f.z); w[r][q][3] = __uint_as_float(f.w);
+      }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int q = 0; q < KQ; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          w[r][q][c] = __uint_as_float(__float_as_uint(w[r][q][c]) & (0u - (uint32_t)(32 * q + 4 * h + c < N)));
+  }
+  for (int i = tid; i < 32 * KQ; i += 64 * KQ) {
     x[0][i] = (i < N && !carry_init) ? cb[i] : 0.0f;
     x[1][i] = 0.0f;
   }
-  __syncthreads();
-  int cur = 0;
-  const size_t slot_stride = (size_t)B * SN;
+  const size_t slot_stride = (size_t)B * SN, up_stride = (size_t)B * N;
+  float *const vrow0 = jb.vbuf + (size_t)b * SN + off;
+  const float *const urow0 = jb.up + (size_t)b * N;
   // Operand staging.  A global load issued in one step and used in the next would put most of a
   // memory round trip into every step.  Instead the v_t and up_t of G steps are loaded into
-  // registers one group ahead (stage_issue), parked in a thread-private column of an LDS ring when
-  // their group starts (stage_park: the only point that waits for them, G steps after the issue),
-  // and read from there step by step.
-  constexpr int G = SNN_SEQ_GROUP;
-  float rv[G], ru[G];
+  // registers one group ahead (stage_issue), parked in an LDS ring when their group starts (the only point that waits for
+  // them, G steps after the issue), v_t as its surrogate derivative, and read from there step by step.  Both halves of the
+  // eight lanes work on it: h < 4 the first G / 2 steps of a group, the others the rest.
+  constexpr int GH = G / 2;
+  const int kh = h < 4 ? 0 : GH;
+  float rv[GH], ru[GH];
   auto stage_issue = [&](int t_hi) { // steps t_hi, t_hi - 1, ... (steps past the end re-read the last one)
 #pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int t = t_hi - k > t0 ? t_hi - k : t0 + 1;
-      rv[k] = vbuf[(size_t)(t - t_base - 1) * slot_stride + (size_t)b * SN + off + j];
-      ru[k] = up[((size_t)(t - t_base - 1) * B + b) * ldu + j];
+    for (int k = 0; k < GH; ++k) {
+      const size_t sa = (size_t)((t_hi - k > t0 ? t_hi - k : t0 + 1) - t_base - 1);
+      const size_t sb = (size_t)((t_hi - k - GH > t0 ? t_hi - k - GH : t0 + 1) - t_base - 1);
+      rv[k] = (kh ? vrow0 + sb * slot_stride : vrow0 + sa * slot_stride)[jc];
+      ru[k] = (kh ? urow0 + sb * up_stride : urow0 + sa * up_stride)[jc];
     }
   };
-  auto stage_park = [&]() {
+  __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the weights are in registers from here on
+  stage_issue(t1);
+  __syncthreads();
+  int cur = 0;
+  float dn = x[0][j < 32 * KQ ? j : 0]; // lanes h < 4
+  for (int t = t1; t > t0; --t) {
+    const int k = (t1 - t) & (G - 1);
+    const float4 *xs = reinterpret_cast<const float4 *>(x[cur]) + h;
+    float4 xv[KQ];
 #pragma unroll
-    for (int k = 0; k < G; ++k) {
-      ring[2 * k][j] = rv[k];
-      ring[2 * k + 1][j] = ru[k];
+    for (int q = 0; q < KQ; ++q) xv[q] = xs[8 * q];
+    if (k == 0) {
+#pragma unroll
+      for (int i = 0; i < GH; ++i) {
+        ring[2 * (i + kh)][j] = surrogate(net, rv[i]);
+        ring[2 * (i + kh) + 1][j] = ru[i];
+      }
+      if (t - G > t0) stage_issue(t - G);
     }
-  };
-  if (own) stage_issue(t1);
-  for (int tg = t1; tg > t0; tg -= G) {
+    const float gs = ring[2 * k][j], upv = ring[2 * k + 1][j];
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a[r] = fmaf(w[r][q][0], xv[q].x, a[r]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a[r] = fmaf(w[r][q][1], xv[q].y, a[r]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a[r] = fmaf(w[r][q][2], xv[q].z, a[r]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a[r] = fmaf(w[r][q][3], xv[q].w, a[r]);
+    }
+    // the sums over h: neighbours keep every other row, then pairs of neighbours, then lane h < 4 takes h + 4
+    auto dpp = [](float v, auto ctrl) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    using xor1 = std::integral_constant<int, 0xB1>; // quad_perm [1, 0, 3, 2]
+    using xor2 = std::integral_constant<int, 0x4E>; // quad_perm [2, 3, 0, 1]
+    const bool odd = h & 1, up2 = h & 2;
+    const float s0 = (odd ? a[1] : a[0]) + dpp(odd ? a[0] : a[1], xor1{}), s1 = (odd ? a[3] : a[2]) + dpp(odd ? a[2] : a[3], xor1{});
+    const float s2 = (up2 ? s1 : s0) + dpp(up2 ? s0 : s1, xor2{});
+    const float sacc = s2 + dpp(s2, std::integral_constant<int, 0x104>{}); // row_shl 4
+    const float ds = (sacc + upv) - net.theta * dn;
+    dn = fmaf(ds, gs, net.alpha * dn);
+    cur ^= 1;
     if (own) {
-      stage_park();
-      if (tg - G > t0) stage_issue(tg - G);
+      x[cur][j] = dn;
+      vrow0[(size_t)(t - t_base - 1) * slot_stride + j] = dn;
     }
-    const int tlo = tg - G > t0 ? tg - G : t0;
-    for (int t = tg; t > tlo; --t) {
-      const float4 *xs = reinterpret_cast<const float4 *>(&x[cur][h * KH]);
-      float a[R][4];
-#pragma unroll
-      for (int r = 0; r < R; ++r) a[r][0] = a[r][1] = a[r][2] = a[r][3] = 0.0f;
-#pragma unroll
-      for (int q = 0; q < KH / 4; ++q) {
-        const float4 xv = xs[q];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          a[r][0] = fmaf(w[r][4 * q + 0], xv.x, a[r][0]);
-          a[r][1] = fmaf(w[r][4 * q + 1], xv.y, a[r][1]);
-          a[r][2] = fmaf(w[r][4 * q + 2], xv.z, a[r][2]);
-          a[r][3] = fmaf(w[r][4 * q + 3], xv.w, a[r][3]);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) part[h][jj + r * NJR] = (a[r][0] + a[r][1]) + (a[r][2] + a[r][3]);
-      __syncthreads();
-      if (own) {
-        const float vt = ring[2 * (tg - t)][j], upv = ring[2 * (tg - t) + 1][j];
-        float sacc = part[0][j];
-#pragma unroll
-        for (int q = 1; q < H; ++q) sacc = sacc + part[q][j];
-        const float dn = x[cur][j];
-        const float ds = (sacc + upv) - net.theta * dn;
-        const float dvt = fmaf(ds, surrogate(net, vt), net.alpha * dn);
-        x[cur ^ 1][j] = dvt;
-        vbuf[(size_t)(t - t_base - 1) * slot_stride + (size_t)b * SN + off + j] = dvt;
-      }
-      __syncthreads();
-      cur ^= 1;
-    }
+    __syncthreads();
   }
-  if (own) cb[j] = x[cur][j];
+  if (own) cb[j] = dn;
+}
+// The instance for a layer's width, uniform per workgroup
+template <int KQ>
+__device__ __forceinline__ void adj_rec_rs_any(const NetDev &net, const AdjJob &jb, float *__restrict__ carry, int b, float (*x)[256],
+                                               float (*ring)[256]) {
+  if constexpr (KQ > 1)
+    if (uniform(net.N[uniform(jb.l)]) <= 32 * (KQ - 1)) {
+      adj_rec_rs_any<KQ - 1>(net, jb, carry, b, x, ring);
+      return;
+    }
+  adj_rec_rs_body<KQ>(net, jb, carry, b, x, ring);
 }
 
 // blockIdx.y selects the job: layers that are one tile apart in the layer pipeline share a launch
-template <int KH, int H, int R>
-__global__ void __launch_bounds__(512)
+template <int KQ>
+__global__ void __launch_bounds__(64 * KQ)
 k_adj_rec_rs(NetDev net, AdjJobs jobs, float *__restrict__ carry) {
-  adj_rec_rs_body<KH, H, R>(net, jobs.j[blockIdx.y], carry, blockIdx.x);
+  __shared__ __align__(16) float x[2][256];
+  __shared__ float ring[2 * SNN_SEQ_GROUP][256];
+  adj_rec_rs_any<KQ>(net, jobs.j[blockIdx.y], carry, (int)blockIdx.x, x, ring);
 }
 
 // Recurrent part, wide layers (N/8 weights per thread fit in registers, N <= 1024): the recurrent
@@ -3959,14 +3988,15 @@ k_finish_grad_csr(const double *__restrict__ acc, const uint32_t *__restrict__ s
 // compute units) leave most of the chip idle: the contraction fills it.  The register footprint of the
 // recurrence part keeps two workgroups from sharing a compute unit, so nothing competes with a recurrence
 // for issue slots.
-template <int KH, int H, int R>
 __global__ void __launch_bounds__(512)
 k_bwd_stage(NetDev net, AdjJobs jobs, float *__restrict__ carry, DwBatch batch, DuJob du, const float *__restrict__ g,
             PreJobs pre, int n_adj_blocks, int n_dw_blocks) {
   extern __shared__ __align__(16) unsigned char smem[];
   int v = (int)blockIdx.x; // every branch below is uniform per workgroup
   if (v < n_adj_blocks) {
-    adj_rec_rs_body<KH, H, R>(net, jobs.j[v / net.B], carry, v % net.B);
+    __shared__ __align__(16) float x[2][256];
+    __shared__ float ring[2 * SNN_SEQ_GROUP][256];
+    adj_rec_rs_any<8>(net, jobs.j[v / net.B], carry, v % net.B, x, ring);
     return;
   }
   v -= n_adj_blocks;
@@ -5130,26 +5160,20 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
   for (int i = 0; i < jobs.count; ++i)
     if (jobs.j[i].t1 <= jobs.j[i].t0 || jobs.j[i].l < 0 || jobs.j[i].l >= net.L) return hipErrorInvalidValue;
   if (hook) hook->begin(hook->ctx, 2);
-  // register-stationary layers of one size class go out together (blockIdx.y = job)
-  for (int cls = 0; cls < 2; ++cls) {
-    AdjJobs rs{};
-    int nthr = 0;
-    for (int i = 0; i < jobs.count; ++i) {
-      const int N = net.N[jobs.j[i].l];
-      if (N > 256 || (N <= 128) != (cls == 0)) continue;
-      const int nt = 2 * ((N + 63) & ~63); // H threads per R postsynaptic rows, H = 2R
-      if (nthr && nt != nthr) { // same class, different block size: a launch of its own
-        if (cls == 0) hipLaunchKernelGGL((k_adj_rec_rs<16, 8, 4>), dim3(B, rs.count), dim3(nthr), 0, s, net, rs, carry);
-        else hipLaunchKernelGGL((k_adj_rec_rs<32, 8, 4>), dim3(B, rs.count), dim3(nthr), 0, s, net, rs, carry);
-        rs.count = 0;
-      }
-      nthr = nt;
-      rs.j[rs.count++] = jobs.j[i];
-    }
-    if (rs.count) {
-      if (cls == 0) hipLaunchKernelGGL((k_adj_rec_rs<16, 8, 4>), dim3(B, rs.count), dim3(nthr), 0, s, net, rs, carry);
-      else hipLaunchKernelGGL((k_adj_rec_rs<32, 8, 4>), dim3(B, rs.count), dim3(nthr), 0, s, net, rs, carry);
-    }
+  // register-stationary layers go out together (blockIdx.y = job)
+  AdjJobs rs{};
+  int n_rs = 0;
+  for (int i = 0; i < jobs.count; ++i) {
+    const int N = net.N[jobs.j[i].l];
+    if (N > 256) continue;
+    n_rs = N > n_rs ? N : n_rs;
+    rs.j[rs.count++] = jobs.j[i];
+  }
+  if (rs.count) {
+    const dim3 grid(B, rs.count);
+    if (n_rs <= 64) hipLaunchKernelGGL(k_adj_rec_rs<2>, grid, dim3(128), 0, s, net, rs, carry);
+    else if (n_rs <= 128) hipLaunchKernelGGL(k_adj_rec_rs<4>, grid, dim3(256), 0, s, net, rs, carry);
+    else hipLaunchKernelGGL(k_adj_rec_rs<8>, grid, dim3(512), 0, s, net, rs, carry);
   }
   bool taken[SNN_MAXL] = {};
   for (int i = 0; i < jobs.count; ++i) {
@@ -5523,14 +5547,14 @@ hipError_t launch_bwd_stage(const NetDev &net, const AdjJobs &jobs, float *carry
     lds = lp > lds ? lp : lds;
   }
   {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_bwd_stage<32, 8, 4>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_bwd_stage),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
   const int n_adj = net.B * jobs.count;
   if (hook) hook->begin(hook->ctx, 7);
   const int grid = n_adj + du.n + total + pre.cur_gx * pre.cur.count + pre.n_scan;
-  hipLaunchKernelGGL((k_bwd_stage<32, 8, 4>), dim3(grid), dim3(512), lds, s, net, jobs, carry, batch, du, g, pre, n_adj,
+  hipLaunchKernelGGL(k_bwd_stage, dim3(grid), dim3(512), lds, s, net, jobs, carry, batch, du, g, pre, n_adj,
                      total);
   if (hook) hook->end(hook->ctx);
   return hipGetLastError();
