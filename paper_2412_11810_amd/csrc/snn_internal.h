@@ -111,13 +111,14 @@ hipError_t launch_pack_inputs(const uint8_t *in_spikes, uint64_t *mask0, int T, 
 // bounds[0..n_tiles], each at most SNN_FWD_TILE steps.  state: [B][SN], x_{bounds[0]} on entry,
 // x_{bounds[n_tiles]} on return.  work: scratch of SNN_FWD_TILE * B * (2 * SN + SNN_RO_TILES * n_out) floats.
 // layer_tile_done(layer, t_end) is called (on the host, in stream order) after the launch that
-// completes layer `layer` up to step t_end has been queued.
+// completes layer `layer` up to step t_end has been queued.  Either callback may be NULL.
 #define SNN_FWD_TILE 64
 #define SNN_FWD_LAG (2 * (SNN_MAXL - 1)) // tiles the lowest layer can be ahead of the top layer
 #define SNN_RO_TILES 8 // tiles of readout currents per launch of the readout scan
 struct FwdCallbacks {
   void *ctx;
   hipError_t (*layer_tile_done)(void *ctx, int layer, int t_end);
+  hipError_t (*tile_inputs)(void *ctx, int t0, int t1); // before the first launch that reads the inputs of steps t0+1..t1
 };
 // leaky readout over one tile of readout currents (n != 0: present; the launcher turns it into a workgroup count)
 struct RoJob { int n; const float *iout; int nsteps, init; };

@@ -4723,6 +4723,10 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
   for (int stage = 0; stage < n_tiles + 2 * L; ++stage) {
     // ---- parallel part: feed-forward currents for the next stage's sequential parts, readout currents ----
     CurJobs cj{};
+    if (cb && cb->tile_inputs && stage < n_tiles) {
+      const hipError_t ei = cb->tile_inputs(cb->ctx, bounds[stage], bounds[stage + 1]);
+      if (ei != hipSuccess) return ei;
+    }
     for (int l = 0; l < L; ++l) {
       const int k = stage - 2 * l;
       if (k < 0 || k >= n_tiles) continue;
@@ -4904,7 +4908,7 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (cb)
+    if (cb && cb->layer_tile_done)
       for (int l = 0; l < L; ++l) {
         const int k = stage - 2 * l - 1;
         if (k < 0 || k >= n_tiles) continue;

@@ -439,6 +439,31 @@ def test_sliced_sequential_forward_at_any_width(hidden, B, T, density, csr, monk
     _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
 
+@pytest.mark.parametrize("n_in,hidden,B,T", [(1000, (64,), 40, 300), (700, (256, 130), 33, 200), (37, (300,), 3, 9)])
+def test_inputs_from_host_memory_in_pieces(n_in, hidden, B, T):
+    """Spike trains in host memory are copied in pieces beside the forward pass (several pieces per tile, buffers used again;
+    one step that fills none): the same results as from the GPU, forward pass and training step."""
+    w = synth.Workload("pieces", n_in, hidden, 5, T=T, B=B, p_in=0.05, gain=0.6, seed=171 + B)
+    d = synth.generate(w)
+    import torch
+    dev = torch.device("cuda", 0)
+    x, y = torch.from_numpy(d["in_spikes"]).to(dev), torch.from_numpy(d["labels"]).to(dev)
+    net = snn.from_workload(w, d)
+    try:
+        got = []
+        for a, b in ((d["in_spikes"], d["labels"]), (x, y)):
+            loss = net.snn_forward(a, b, T)
+            spikes = [net.snn_get_spikes(l, T) for l in range(len(hidden))]
+            net.snn_bind_inputs(a, b, T)
+            net.snn_bptt(snn.SNN_CHUNK, 0, 16)
+            got.append((loss, spikes, net.snn_get_readout(), _gpu_grads(net, len(hidden))))
+        assert got[0][0] == got[1][0] and np.array_equal(got[0][2][0], got[1][2][0])
+        assert all(np.array_equal(a, b) for a, b in zip(got[0][1], got[1][1]))
+        assert _identical(got[0][3], got[1][3])
+    finally:
+        net.snn_destroy()
+
+
 @pytest.mark.parametrize("hidden,T", [((1, 31, 33), 30), ((64, 65, 96), 70), ((127, 128, 129), 66), ((160, 191, 193), 30),
                                       ((208, 224, 225), 70), ((241, 255, 256), 67)])
 def test_register_stationary_forward_widths(hidden, T):
