@@ -164,7 +164,9 @@ snn_status snn_forward_noalloc(snn_ctx *ctx, const uint8_t *in_spikes, const int
  *   fine ceil(sqrt T) for CHUNK: the square-root rules of the paper's Hyperparameter Study).
  *   hbm_budget_bytes caps activation storage (states + spike bitmasks + workspace); 0 = unlimited.
  *   snn_bytes_required is the least the strategy can run in (one chunk buffer: the paper's state
- *   count); below it -> SNN_E_BUDGET before anything is allocated.  With room to spare (or no budget)
+ *   count); below it -> SNN_E_BUDGET before anything is allocated.  Where the budget has room (or none is set), networks with a
+ *   layer above 256 neurons also keep lists of active neurons for 65 steps in the workspace (2 bytes per neuron, step and batch
+ *   element); stats counts them.  With room to spare (or no budget)
  *   the call takes up to n_layers + 2 more chunk buffers, which let the layers of the adjoint pass and
  *   the recompute of the next chunks overlap; DOUBLE then takes coarse_interval more state slots to keep the
  *   synaptic currents of a coarse segment between its two recompute passes (Section "Double Checkpointing":
@@ -282,7 +284,8 @@ void snn_destroy(snn_ctx *ctx);
  *     SNN_NO_WS=1                no chip-wide kernels (no exchange buffer is allocated)
  *     SNN_WS_SPIN_LIMIT=n        polls before a chip-wide kernel gives up waiting (0: at once; the error path)
  *   read at the start of every call that launches kernels:
- *     SNN_CURRENTS=gather|mfma|dense   kernel of the synaptic currents
+ *     SNN_CURRENTS=gather|mfma|dense   kernel of the synaptic currents (default for matrices below 32 MB in networks with a
+ *                                      layer above 256 neurons: lists of active neurons, up to 16 % activity)
  *     SNN_WS_KERNEL=valu|stream|rows|rows_all|chip|csrw|single|pair|rows64|uncached
  *                                      VALU version of the chip-wide adjoint recurrence / one workgroup per batch
  *                                      element streaming the transposed matrix / the event-driven rows kernel of

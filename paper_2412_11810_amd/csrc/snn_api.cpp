@@ -79,12 +79,12 @@ struct snn_ctx {
   // activation arena (HBM "local memory"), readout-adjoint tile, pinned host checkpoints
   float *arena = nullptr;
   size_t arena_bytes = 0;
-  float *dubuf = nullptr; // readout adjoints of a chunk, followed by the inter-layer product scratch
+  float *dubuf = nullptr; // readout adjoints of a chunk, followed by the inter-layer product scratch; at its end NetDev::lists
   size_t dubuf_bytes = 0;
   float *host_ckpt = nullptr;
   size_t host_bytes = 0;
   std::vector<hipEvent_t> ev_pool;
-  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache; } };
+  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; void *lists; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache && lists == o.lists; } };
   GraphKeyT graph_key{};
   hipGraphExec_t graph_exec = nullptr;
   bool graphs_enabled = true;   // SNN_GRAPH=0 turns graph replay off
@@ -486,7 +486,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
   HIPCHK(c, hipMalloc(&c->g, (size_t)B * O * 4));
   HIPCHK(c, hipMalloc(&c->loss_dev, 16));
   HIPCHK(c, hipMalloc(&c->carry, (size_t)B * (n.SN + O) * 4));
-  HIPCHK(c, hipMalloc(&c->cur_state, (size_t)B * n.SN * 4));
+  size_t xl_bytes = 0; // exchange inside a die: shares an allocation with cur_state
   {
     int nmax = 0;
     for (int l = 0; l < L; ++l) nmax = n.N[l] > nmax ? n.N[l] : nmax;
@@ -508,13 +508,18 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       c->ws.xg = (float *)((char *)blk + n_bar * sizeof(unsigned));
       c->ws.xg_stride = (int)xg_stride;
       HIPCHK(c, hipMemsetAsync(c->ws.bar, 0, n_bar * sizeof(unsigned), c->stream));
-      HIPCHK(c, hipMalloc(&c->ws.xl, (size_t)SNN_MAXL * xg_stride * 4));
+      xl_bytes = (size_t)L * xg_stride * 4; // (one job per layer at most in a launch)
       c->ws.err = c->ws.bar + 64 * SNN_MAXL;
       c->ws.max_groups = ws_max_resident_groups(cfg->device);
       c->ws.max_groups_m = ws_max_resident_groups_mfma(cfg->device);
       if (nmax > 1024) c->ws.max_groups_m8 = ws_max_resident_groups_mfma8(cfg->device);
       c->ws.spin_limit = 4000000u; // ~1 s of polling: far beyond any real wait
       if (const char *e = std::getenv("SNN_WS_SPIN_LIMIT")) c->ws.spin_limit = (unsigned)std::strtoul(e, nullptr, 10);
+    }
+    const size_t state = ((size_t)B * n.SN * 4 + 255) & ~(size_t)255;
+    HIPCHK(c, hipMalloc(&c->cur_state, state + xl_bytes));
+    if (xl_bytes) {
+      c->ws.xl = c->cur_state + state / 4;
       adjoint_prepare(n, c->ws);
     }
   }
@@ -560,7 +565,7 @@ void snn_destroy(snn_ctx *c) {
   (void)hipFree(c->labels); (void)hipFree(c->readout); (void)hipFree(c->ubar); (void)hipFree(c->g);
   (void)hipFree(c->loss_dev); (void)hipFree(c->carry); (void)hipFree(c->cur_state);
   if (c->ws.bar) uncached_release(c->cfg.device, c->ws.bar);
-  (void)hipFree(c->ws.xl); (void)hipFree(c->counters);
+  (void)hipFree(c->counters);
   (void)hipFree(c->arena); (void)hipFree(c->dubuf);
   if (c->host_ckpt) (void)hipHostFree(c->host_ckpt);
   (void)hipFree(c->in_stage);
@@ -753,6 +758,24 @@ static snn_status ensure_work(snn_ctx *c, size_t bytes) {
   return SNN_OK;
 }
 
+// Workspace of `bytes`, and behind it space for the lists of active neurons where `lists` says that this call may use them (they are
+// not part of what snn_bytes_required counts: a budget has room, or there is none) and the device has room for them.
+static size_t lists_bytes(const NetDev &n) { return (currents_lists_entries(n) * sizeof(uint16_t) + 255) & ~(size_t)255; }
+static snn_status ensure_work_lists(snn_ctx *c, size_t bytes, bool lists) {
+  const size_t extra = lists ? lists_bytes(c->net) : 0, work = (bytes + 255) & ~(size_t)255;
+  c->net.lists = nullptr;
+  c->net.lists_cap = currents_lists_entries(c->net);
+  if (extra) {
+    if (ensure_work(c, work + extra) == SNN_OK) {
+      c->net.lists = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(c->dubuf) + ((c->dubuf_bytes - extra) & ~(size_t)255));
+      return SNN_OK;
+    }
+    (void)hipGetLastError();
+    c->err.clear(); // the call goes without
+  }
+  return ensure_work(c, bytes);
+}
+
 // State storage of a training step and its workspace, grown on demand.
 static snn_status ensure_states(snn_ctx *c, size_t states, size_t work) {
   if (c->arena_bytes < states) {
@@ -798,6 +821,7 @@ static snn_status forward_only(snn_ctx *c, float *traj_or_null, float *work_or_n
     const snn_status rm = ensure_full_masks(c);
     if (rm != SNN_OK) return rm;
   }
+  c->net.lists = nullptr;
   const NetDev &n = c->net;
   StoreSpec st{};
   if (traj_or_null) {
@@ -806,7 +830,7 @@ static snn_status forward_only(snn_ctx *c, float *traj_or_null, float *work_or_n
   }
   float *work = work_or_null;
   if (!work) { // the caller brought no workspace: the context's own, grown on demand
-    snn_status rs = ensure_work(c, work_bytes(n, 1));
+    snn_status rs = ensure_work_lists(c, work_bytes(n, 1), true);
     if (rs != SNN_OK) return rs;
     work = c->dubuf;
   }
@@ -929,6 +953,7 @@ snn_status snn_get_state(snn_ctx *c, int layer, int32_t t, float *dst) {
   HIPCHK(c, hipSetDevice(c->cfg.device));
   if (c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr)); // dst: as in snn_grads
   read_kernel_hooks(c);
+  c->net.lists = nullptr;
   {
     const snn_status rm = ensure_full_masks(c);
     if (rm != SNN_OK) return rm;
@@ -998,6 +1023,7 @@ snn_status snn_debug_currents(snn_ctx *c, const uint8_t *const *hidden, int32_t 
   if (chunk < 1 || reps < 1) return fail(c, SNN_E_INVAL, "chunk and reps must be positive");
   HIPCHK(c, hipSetDevice(c->cfg.device));
   read_kernel_hooks(c);
+  c->net.lists = nullptr;
   {
     const snn_status rm = ensure_full_masks(c);
     if (rm != SNN_OK) return rm;
@@ -1103,6 +1129,9 @@ struct Timer {
 // presynaptic spike, the dense matrix-core version per presynaptic neuron; measured break-even about 3.5 %.
 // (weight gradients of 1024-wide layers, batch 64: tiled kernel 17 / 33 ms at 4.6 / 12 % activity, dense contraction 25.5)
 static constexpr double DW_TILE_MAX_ACTIVITY = 0.08;
+// (currents by lists, 512 -> 512 at batch 16: 33 us per launch at 47 %, matrix-core version 23 at any rate from 15 % on; lists cost
+// about 17 us + 35 us x rate)
+static constexpr double LISTS_MAX_ACTIVITY = 0.16;
 static snn_status update_current_policy(snn_ctx *c, int T, float *rates_out, bool hidden_counted) {
   const NetDev &n = c->net;
   const int L = n.L, B = n.B;
@@ -1127,6 +1156,7 @@ static snn_status update_current_policy(snn_ctx *c, int T, float *rates_out, boo
   }
   // weight gradients: measured break-even of the tiled event-driven kernel and the dense contraction
   if (c->dw_rate_driven) c->dw_tile = ev_re < DW_TILE_MAX_ACTIVITY * rows_re;
+  c->net.lists_off = ev_re < LISTS_MAX_ACTIVITY * rows_re ? 0 : 1;
   if (c->rate_driven) {
     // one choice for the whole network (jobs of one launch then stay in one launch)
     for (int l = 0; l < L; ++l) {
@@ -1994,6 +2024,12 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
     snn_status rs = ensure_states(c, need_states, need_work);
     if (rs != SNN_OK) return rs;
   }
+  // the lists of active neurons are part of the workspace where they are used, and only used where the budget has room
+  const size_t need_lists = lists_bytes(n);
+  {
+    const snn_status rs = ensure_work_lists(c, need_work, !budget || need_states + need_work + need_spikes + need_lists <= budget);
+    if (rs != SNN_OK) return rs;
+  }
   const size_t need_host = (size_t)p.n_remote * Ms;
   if (c->host_bytes < need_host) {
     HIPCHK(c, hipStreamSynchronize(s));
@@ -2041,7 +2077,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   }
 
   snn_stats st{};
-  st.bytes_states = (int64_t)need_states; st.bytes_spikes = (int64_t)need_spikes; st.bytes_workspace = (int64_t)need_work;
+  st.bytes_states = (int64_t)need_states; st.bytes_spikes = (int64_t)need_spikes; st.bytes_workspace = (int64_t)(need_work + (n.lists ? need_lists : 0));
   st.bytes_host = (int64_t)need_host; st.local_state_slots = p.local_slots(); st.remote_state_slots = p.n_remote;
   st.bytes_host_spikes = (int64_t)need_host_spk;
 
@@ -2052,10 +2088,10 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   if (use_graph) {
     unsigned long long pol = 0;
     for (int l = 0; l < L; ++l) pol = pol * 64 + c->net.cur_pol[0][l] * 16 + c->net.cur_pol[1][l] * 2 + c->net.seq_pol[l];
-    pol = pol * 2 + (c->dw_tile ? 1u : 0u);
+    pol = (pol * 2 + (c->dw_tile ? 1u : 0u)) * 2 + n.lists_off;
     const unsigned sel = (unsigned)n.sel_currents | (unsigned)n.sel_adjoint << 8 | (unsigned)n.sel_slices << 16 | (unsigned)n.sel_csr << 24 | (unsigned)n.sel_seq << 28 | (unsigned)n.no_fwd_fuse << 30;
     snn_ctx::GraphKeyT key{(int)strategy, T, p.C, p.F, p.n_chunk_bufs, c->arena, c->dubuf, c->host_ckpt, c->dw_event_driven, pol, sel,
-                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots};
+                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists};
     if (!c->graph_exec || !(key == c->graph_key)) {
       if (c->graph_exec) { (void)hipGraphExecDestroy(c->graph_exec); c->graph_exec = nullptr; }
       Timer tm{c, false};

@@ -67,6 +67,10 @@ struct NetDev {
   // Sequential forward part of layers of up to 256 neurons: sel_seq 1 forces the event-driven gather, 2 the
   // register-stationary chain, 0 follows seq_pol[l] (1: gather; set from the measured firing rates).
   unsigned char sel_seq, seq_pol[SNN_MAXL];
+  // Space for the lists of active neurons that k_currents_lists walks (NULL: the matrix-core kernels instead), in entries
+  uint16_t *lists;
+  size_t lists_cap;
+  unsigned char lists_off; // 1: the measured firing rates are above what the walk pays for (see LISTS_MAX_ACTIVITY)
   unsigned char sel_csr; // compressed rows of masked recurrent matrices: 1 never used (dense-stored walk everywhere),
                          // 2 used wherever a kernel for them exists, 0 the library's choice
 };
@@ -133,6 +137,8 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
 // Recompute pass over steps t0+1..t1 from state_in = x_{t0}, spikes read from the stored bitmasks:
 // currents of the whole range in parallel into buf (slot of x_t = t - t_base - 1), then a scan that
 // turns them into states in place (store_all) and/or writes x_{t1} to state_out.
+size_t currents_lists_entries(const NetDev &net); // of that space: SNN_LIST_STEPS steps of every layer; 0: never used
+#define SNN_LIST_STEPS 64
 hipError_t launch_recompute(const NetDev &net, int t0, int t1, const float *state_in, float *buf, int t_base,
                             size_t slot_stride, int store_all, float *state_out, hipStream_t s);
 // Part 1 of a recompute pass alone: the currents of steps t0+1..t1 of every layer into buf.
@@ -153,7 +159,7 @@ hipError_t launch_loss(const double *readout, const int32_t *labels, int B, int 
 // kernel (see k_adj_rec_ws); xg == NULL disables that kernel.
 struct WsArgs {
   float *xg;           // SNN_MAXL x [4][B in whole groups of 16][max N_l], one per job of a launch
-  float *xl;           // the same in ordinary memory, for workgroups that share a die (NULL: never used)
+  float *xl;           // the same for the network's layers in ordinary memory, for workgroups that share a die
   int xg_stride;       // floats between the exchange buffers of two jobs
   unsigned *bar;       // SNN_MAXL x [64] counters, zeroed before every launch
   unsigned *err;       // raised if a barrier gave up waiting

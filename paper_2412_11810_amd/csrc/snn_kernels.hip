@@ -23,10 +23,12 @@
 #define WAVE 64
 #define SNN_SEQ_GROUP 8 // steps whose per-step operands the sequential kernels load ahead in one go
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) float lds_float;
 typedef unsigned int csr_u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int csr_u32x4 __attribute__((ext_vector_type(4)));
 
+static __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 static __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 // Sum of x over the 64 lanes, the same bits in every lane (all lanes must be active): neighbours within quads
 // (xor 1, xor 2), the two quads of a half row, the two halves of a row of 16 -- row-local DPP moves, no LDS -- then
@@ -373,7 +375,6 @@ struct StoreCursor {
 // layer's width rounded up to 32, what a step leaves in memory goes out at the beginning of the next one, steps and
 // slots are counted in scalar registers.  One barrier per step.  700-2x256, batch 32: 1.28 -> 0.9 us per step, of which
 // the weights' way into the registers, 64 steps apart, 0.22 -> 0.07.
-static __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 template <int NW> struct SeqRs {
   static constexpr int lds_rows = NW > 224 ? 48 : NW > 208 ? 16 : 0;
   static constexpr int lds_bytes = ((2 + SNN_SEQ_GROUP) * 256 + lds_rows * 256) * 4; // spikes, currents, rows
@@ -1329,6 +1330,136 @@ k_currents(NetDev net, CurJobs jobs) {
 }
 
 // ------------------------------------------------------------------------------------------
+// A2 event by event, with the weights in LDS (matrices that fit the L2; networks with a layer above 256 neurons).  One list
+// of active presynaptic neurons per (t, b) row and layer is made once (k_spike_lists) and walked for every slice of
+// columns (k_currents_lists): a workgroup keeps 4 LPT columns for all presynaptic neurons in LDS (up to 150 KB) for as many rows as
+// it gets, LPT lanes share a row, a lane owns four columns: address, 16-byte read and four adds per active neuron, which
+// is what the event-driven method asks for -- the matrix-core version visits every neuron that is active in any of 16
+// rows (56 % of them at 5 % activity) and multiplies the other fifteen rows by zero.  Sums ascending from 0.0f: the same bits.
+// Bound by the LDS rate (4 rows of 64 bytes per 256-byte access meet the same banks now and then at LPT = 4).
+// 512-2x2048 at 5 %, batch 16, T = 2000: 11.5 -> 5.9 ms of currents per training step, 700-3x1024, batch 64, T = 500: 1.24 -> 0.77
+// per forward pass.  Above 16 % activity the matrix cores are faster (LISTS_MAX_ACTIVITY).
+// ------------------------------------------------------------------------------------------
+struct ListJob { const uint64_t *mask; int words, ring, t_first, rows, P, lc; uint16_t *lists; }; // rows = steps x B, from step t_first on
+struct ListJobs { ListJob j[SNN_MAXL + 1]; int count; };
+// A list: 8 entries of which the first is the number of groups of eight, then the groups -- the last one filled up with
+// P, which stands for no neuron -- then one group of P alone.
+__global__ void __launch_bounds__(256) k_spike_lists(ListJobs jobs, int B) {
+  const ListJob &jb = jobs.j[blockIdx.y];
+  const int row = (int)blockIdx.x * 4 + uniform((int)threadIdx.x >> 6), lane = lane_id();
+  if (row >= jb.rows) return;
+  const int t = jb.t_first + row / B, b = row % B;
+  const uint32_t *words = reinterpret_cast<const uint32_t *>(jb.mask + ((size_t)(jb.ring > 0 ? t % jb.ring : t) * B + b) * jb.words);
+  uint16_t *list = jb.lists + (size_t)row * jb.lc + 8;
+  uint32_t total = 0;
+  for (int h0 = 0; h0 < 2 * jb.words; h0 += WAVE) {
+    const int h = h0 + lane;
+    uint32_t m = h < 2 * jb.words ? words[h] : 0u;
+    uint32_t x = (uint32_t)__popc(m);
+    const uint32_t own = x;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
+    }
+    uint16_t *p = list + total + (x - own);
+    while (m) {
+      *p++ = (uint16_t)(h * 32 + __builtin_ctz(m));
+      m &= m - 1u;
+    }
+    total += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+  }
+  const uint32_t groups = (total + 7u) >> 3, end = groups * 8u + 8u;
+  if (total + (uint32_t)lane < end) list[total + lane] = (uint16_t)jb.P;
+  if (lane == 0) list[-8] = (uint16_t)groups;
+}
+struct LstJob { const float *W; const uint16_t *lists; float *out; size_t slot_stride; int P, N, lc, rows, mode, add, off, splits; };
+struct LstJobs { LstJob j[SNN_MAXL + 1]; int count; };
+template <int LPT> // lanes per row (four columns each)
+__global__ void __launch_bounds__(1024)
+k_currents_lists(LstJobs jobs, int B, int SN) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int CW = 4 * LPT, TBW = 64 / LPT;
+  constexpr uint32_t ROWB = CW * 4;
+  const LstJob &jb = jobs.j[blockIdx.y];
+  const int P = jb.P, N = jb.N, rows = jb.rows, splits = jb.splits;
+  const int sl = (int)blockIdx.x / splits, sp = (int)blockIdx.x % splits, c0 = sl * CW;
+  if (c0 >= N) return;
+  const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6);
+  float *wl = (float *)smem; // [P + 1][CW], the last row zero
+  {
+    // (what a 16-byte load takes beyond its row is never stored, beyond the matrix it reads 0)
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void *)jb.W, 0, (int)((size_t)P * N * sizeof(float)), 0x00027000);
+    constexpr int UL = 8, RS = 1024 / LPT;
+    const int cw = 4 * (tid % LPT), r0 = tid / LPT;
+    for (int r = r0; r < P; r += UL * RS) {
+      csr_u32x4 w[UL];
+#pragma unroll
+      for (int u = 0; u < UL; ++u)
+        w[u] = __builtin_amdgcn_raw_buffer_load_b128(wres, ((uint32_t)(r + u * RS < P ? r + u * RS : P - 1) * (uint32_t)N + (uint32_t)(c0 + cw)) * 4u, 0, 0);
+#pragma unroll
+      for (int u = 0; u < UL; ++u)
+        if (r + u * RS < P) *reinterpret_cast<csr_u32x4 *>(wl + (size_t)(r + u * RS) * CW + cw) = w[u];
+    }
+    if (tid < CW) wl[(size_t)P * CW + tid] = 0.0f;
+  }
+  __syncthreads();
+  const int g = lane / LPT, cl = 4 * (lane % LPT);
+  const uint32_t lane_w = (uint32_t)(uintptr_t)(lds_float *)wl + (uint32_t)cl * 4u;
+  typedef __attribute__((address_space(3))) v4f lds_v4f;
+  for (int p = sp; p * 16 * TBW < rows; p += splits) {
+    const int row = (p * 16 + wave) * TBW + g;
+    if (uniform((p * 16 + wave) * TBW) >= rows) break; // (rows only grow from here on)
+    const bool ok = row < rows;
+    const uint4 *list = reinterpret_cast<const uint4 *>(jb.lists + (size_t)(ok ? row : rows - 1) * jb.lc);
+    const uint32_t n = list[0].x & 0xFFFFu;
+    uint32_t nm = n;
+#pragma unroll
+    for (int o = LPT; o < WAVE; o <<= 1) {
+      const uint32_t y = (uint32_t)__shfl_xor((int)nm, o, WAVE);
+      nm = y > nm ? y : nm;
+    }
+    const int n_max = uniform((int)nm);
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto group = [&](int i) { return list[1 + ((uint32_t)i < n ? (uint32_t)i : n)]; };
+    auto walk = [&](const uint4 &e) {
+      const uint32_t pr[4] = {e.x, e.y, e.z, e.w};
+      v4f w[8];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        uint32_t a0, a1;
+        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(a0) : "v"(pr[k]), "s"(ROWB), "v"(lane_w));
+        asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(a1) : "v"(pr[k]), "s"(ROWB), "v"(lane_w));
+        w[2 * k] = *(lds_v4f *)(uintptr_t)a0;
+        w[2 * k + 1] = *(lds_v4f *)(uintptr_t)a1;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        acc.x = acc.x + w[k].x; acc.y = acc.y + w[k].y;
+        acc.z = acc.z + w[k].z; acc.w = acc.w + w[k].w;
+      }
+    };
+    uint4 ea = group(0), eb = group(1);
+    for (int i = 0; i < n_max; i += 2) {
+      const uint4 na = group(i + 2);
+      walk(ea);
+      ea = na;
+      if (i + 1 >= n_max) break;
+      const uint4 nb = group(i + 3);
+      walk(eb);
+      eb = nb;
+    }
+    if (!ok) continue;
+    float *dst = (jb.mode == 1 ? jb.out + (size_t)row * N
+                               : jb.out + (size_t)(row / B) * jb.slot_stride + (size_t)(row % B) * SN + jb.off) + c0 + cl;
+    const float v[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (c0 + cl + c < N) dst[c] = jb.add ? dst[c] + v[c] : v[c];
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // A2 on the matrix cores: currents of 16 (t, b) rows x 64 postsynaptic neurons per wavefront.
 // acc[row][col] = fma(s[row][k], W[k][col], acc[row][col]) for k ascending, one K = 1 MFMA
 // (v_mfma_f32_16x16x1, four 16x16 blocks sharing the A column) per presynaptic neuron k.  With
@@ -1958,7 +2089,6 @@ __device__ __forceinline__ void up_gemm_body(const float *__restrict__ A, int ld
 // layer shapes only, never on M, so every storage strategy sees the same arithmetic.
 //   lane layout (verified on the device): A[i][k] in lane i + 16k, B[k][j] in lane j + 16k,
 //   D[4*(lane/16) + r][lane%16] in register r.
-typedef float v4f __attribute__((ext_vector_type(4)));
 template <int WM, int WN, int BM = 1, int BN = 1>
 __global__ void __launch_bounds__(64 * WM * WN)
 k_up_gemm(const float *__restrict__ A, int lda, const float *__restrict__ W, int K, int N, float *__restrict__ C,
@@ -4389,6 +4519,131 @@ static hipError_t launch_currents(const NetDev &net, const CurJobs &jobs, hipStr
   if (e != hipSuccess) return e;
   return launch_currents_csr(net, cs, s);
 }
+// Entries per list: the number of groups, as many groups as a layer of P neurons can fill, one group of P alone.
+static int list_entries(int P) { return 8 + ((P + 7) & ~7) + 8; }
+static size_t list_lds(int P, int lpt) { return (size_t)(P + 1) * 4 * lpt * sizeof(float); }
+static int list_lanes(int P) { // the widest slice that fits the LDS
+  for (int lpt = 16; lpt >= 1; lpt /= 2)
+    if (list_lds(P, lpt) + 512 <= SNN_LDS_PER_CU) return lpt;
+  return 0;
+}
+static bool lists_ok(const NetDev &net) { // networks with a layer above 256 neurons and a matrix that fits the L2
+  int nmax = 0;
+  bool any = false;
+  for (int l = 0; l < net.L; ++l) {
+    nmax = net.N[l] > nmax ? net.N[l] : nmax;
+    const size_t p = (size_t)(l == 0 ? net.n_in : net.N[l - 1]);
+    any = any || p * net.N[l] * sizeof(float) < ((size_t)32 << 20);
+  }
+  return nmax > 256 && any;
+}
+size_t currents_lists_entries(const NetDev &net) {
+  if (!lists_ok(net)) return 0;
+  size_t n = 0;
+  for (int li = 0; li <= net.L; ++li) n += (size_t)(SNN_LIST_STEPS + 1) * net.B * list_entries(li == 0 ? net.n_in : net.N[li - 1]);
+  return n;
+}
+template <int LPT> static hipError_t launch_lists_t(const LstJobs &jobs, unsigned gx, size_t lds, int B, int SN, hipStream_t s) {
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_currents_lists<LPT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_currents_lists<LPT>, dim3(gx, jobs.count), dim3(1024), lds, s, jobs, B, SN);
+  return hipGetLastError();
+}
+static hipError_t launch_lists_walk(const NetDev &net, LstJobs jobs, hipStream_t s) {
+  // jobs of one slice width share a launch; a workgroup per compute unit, as many of them as rows and slices give
+  bool taken[SNN_MAXL + 1] = {};
+  for (int i = 0; i < jobs.count; ++i) {
+    if (taken[i]) continue;
+    const int lpt = list_lanes(jobs.j[i].P), per_pass = 16 * 64 / lpt;
+    LstJobs grp{};
+    size_t lds = 0;
+    long long units = 0;
+    for (int k = i; k < jobs.count; ++k)
+      if (!taken[k] && list_lanes(jobs.j[k].P) == lpt) {
+        taken[k] = true;
+        grp.j[grp.count++] = jobs.j[k];
+        lds = std::max(lds, list_lds(jobs.j[k].P, lpt));
+        units += (jobs.j[k].N + 4 * lpt - 1) / (4 * lpt);
+      }
+    unsigned gx = 0;
+    for (int k = 0; k < grp.count; ++k) {
+      LstJob &j = grp.j[k];
+      const int slices = (j.N + 4 * lpt - 1) / (4 * lpt), passes = (j.rows + per_pass - 1) / per_pass;
+      j.splits = std::max(1, std::min(passes, (int)(256 / units)));
+      gx = std::max(gx, (unsigned)(slices * j.splits));
+    }
+    hipError_t e;
+    switch (lpt) {
+      case 16: e = launch_lists_t<16>(grp, gx, lds, net.B, net.SN, s); break;
+      case 8: e = launch_lists_t<8>(grp, gx, lds, net.B, net.SN, s); break;
+      case 4: e = launch_lists_t<4>(grp, gx, lds, net.B, net.SN, s); break;
+      case 2: e = launch_lists_t<2>(grp, gx, lds, net.B, net.SN, s); break;
+      default: e = launch_lists_t<1>(grp, gx, lds, net.B, net.SN, s); break;
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+// Currents by walking lists (a readout job's lsel is the layer index of the spikes it reads, L), SNN_LIST_STEPS steps at a time: the lists of every layer that the jobs
+// read, then the feed-forward parts of all jobs, then the recurrent parts (mode 0), added to them.
+static hipError_t launch_currents_lists(const NetDev &net, CurJobs *jobs, hipStream_t s) {
+  if (!net.lists || net.lists_off || net.sel_currents != 0 || !lists_ok(net)) return hipSuccess;
+  CurJobs mine{}, rest{};
+  for (int i = 0; i < jobs->count; ++i) {
+    const CurJob &j = jobs->j[i];
+    const bool ok = list_lanes(j.lsel == 0 ? net.n_in : net.N[j.lsel - 1]) > 0 && (j.mode != 0 || list_lanes(net.N[j.lsel]) > 0);
+    CurJobs &dst = ok ? mine : rest;
+    dst.j[dst.count++] = j;
+  }
+  int most = 0;
+  for (int i = 0; i < mine.count; ++i) most = std::max(most, mine.j[i].nsteps);
+  const int B = net.B;
+  for (int a = 0; a < most; a += SNN_LIST_STEPS) {
+    ListJobs lj{};
+    uint16_t *at[SNN_MAXL + 1] = {};     // lists of layer index li
+    int first[SNN_MAXL + 1], last[SNN_MAXL + 1]; // steps first .. last
+    for (int li = 0; li <= net.L; ++li) { first[li] = 1 << 30; last[li] = -1; }
+    auto need = [&](int li, int f, int l) { first[li] = std::min(first[li], f); last[li] = std::max(last[li], l); };
+    for (int i = 0; i < mine.count; ++i) {
+      const CurJob &j = mine.j[i];
+      if (a >= j.nsteps) continue;
+      const int t0 = j.t0 + a, t1 = j.t0 + std::min(a + SNN_LIST_STEPS, j.nsteps);
+      need(j.lsel, t0 + 1, t1);
+      if (j.mode == 0) need(j.lsel + 1, t0, t1 - 1);
+    }
+    size_t used = 0;
+    int rows_max = 0;
+    for (int li = 0; li <= net.L; ++li)
+      if (last[li] >= first[li]) {
+        const int P = li == 0 ? net.n_in : net.N[li - 1], lc = list_entries(P), rows = (last[li] - first[li] + 1) * B;
+        at[li] = net.lists + used;
+        used += (size_t)rows * lc;
+        lj.j[lj.count++] = ListJob{net.mask[li], net.Wd[li], net.mring[li], first[li], rows, P, lc, at[li]};
+        rows_max = std::max(rows_max, rows);
+      }
+    if (used > net.lists_cap) return hipErrorInvalidValue; // (jobs of one launch cover the same steps of a layer, or of different layers)
+    hipLaunchKernelGGL(k_spike_lists, dim3((rows_max + 3) / 4, lj.count), dim3(256), 0, s, lj, B);
+    LstJobs in{}, rec{};
+    for (int i = 0; i < mine.count; ++i) {
+      const CurJob &j = mine.j[i];
+      if (a >= j.nsteps) continue;
+      const int n = std::min(SNN_LIST_STEPS, j.nsteps - a), t0 = j.t0 + a, l = j.lsel, Pi = l == 0 ? net.n_in : net.N[l - 1];
+      const bool ro = j.mode == 2;
+      const int N = ro ? net.n_out : net.N[l];
+      float *out = j.mode == 1 || ro ? j.out + (size_t)(t0 - j.t_base) * B * N : j.out + (size_t)(t0 - j.t_base) * j.slot_stride;
+      in.j[in.count++] = LstJob{ro ? net.W_out : net.W_in[l], at[l] + (size_t)(t0 + 1 - first[l]) * B * list_entries(Pi), out, j.slot_stride, Pi, N,
+                                list_entries(Pi), n * B, j.mode == 1 || ro ? 1 : 0, 0, ro ? 0 : net.off[l], 1};
+      if (j.mode == 0)
+        rec.j[rec.count++] = LstJob{net.W_rec[l], at[l + 1] + (size_t)(t0 - first[l + 1]) * B * list_entries(N), out, j.slot_stride, N, N,
+                                    list_entries(N), n * B, 0, 1, net.off[l], 1};
+    }
+    hipError_t e = launch_lists_walk(net, in, s);
+    if (e == hipSuccess && rec.count) e = launch_lists_walk(net, rec, s);
+    if (e != hipSuccess) return e;
+  }
+  *jobs = rest;
+  return hipSuccess;
+}
 static hipError_t launch_currents_plain(const NetDev &net, const CurJobs &jobs, hipStream_t s) {
   if (!currents_use_mfma(net)) return launch_currents_gather(net, jobs, s);
   CurJobs mf{}, dn{}, ga{};
@@ -4407,6 +4662,10 @@ static hipError_t launch_currents_plain(const NetDev &net, const CurJobs &jobs, 
     if (e != hipSuccess) return e;
   }
   if (!mf.count) return hipSuccess;
+  {
+    const hipError_t e = launch_currents_lists(net, &mf, s); // takes the jobs that it runs out of mf
+    if (e != hipSuccess || !mf.count) return e;
+  }
   unsigned gx;
   int ws, lcap;
   currents_geometry(net, mf, &gx, &ws, &lcap, 4);

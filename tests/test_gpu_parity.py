@@ -439,6 +439,39 @@ def test_sliced_sequential_forward_at_any_width(hidden, B, T, density, csr, monk
     _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
 
+@pytest.mark.parametrize("n_in,hidden,B,T,gain", [
+    (638, (257, 639), 3, 70, 0.3),     # 64-column slices up to 638 neurons, 32 above; two blocks of steps; odd widths
+    (1, (1278, 1279), 2, 20, 0.3),     # 16-column slices from 1279 on; one input channel
+    (2560, (300, 2559), 3, 20, 0.2),   # 8 columns
+    (4096, (260,), 5, 40, 0.5),        # 8 columns, 130 rows per launch
+    (40, (300, 300), 17, 66, 1.5),     # lists of nearly every neuron
+    (40, (5200, 300), 1, 10, 0.0)])    # 4 columns; no spike at all behind the input
+def test_currents_by_lists(n_in, hidden, B, T, gain, monkeypatch):
+    """Currents from lists of active neurons with the weights in LDS: the bits of the event-by-event gather
+    (SNN_CURRENTS=gather) in spikes, readout and gradients, under full storage and recomputation."""
+    w = synth.Workload("lists", n_in, hidden, 5, T=T, B=B, p_in=0.05, gain=gain, seed=191 + B)
+    d = synth.generate(w)
+    got = []
+    for mode in (None, "gather"):
+        if mode:
+            monkeypatch.setenv("SNN_CURRENTS", mode)
+        net = snn.from_workload(w, d)
+        try:
+            loss = net.snn_forward(d["in_spikes"], d["labels"], T)
+            spikes = [net.snn_get_spikes(l, T) for l in range(len(hidden))]
+            grads = []
+            for strategy, c, f in ((snn.SNN_STANDARD, 0, 0), (snn.SNN_DOUBLE, 10, 3)):
+                net.snn_bptt(strategy, c, f)
+                grads += list(sum((list(g) if isinstance(g, (list, tuple)) else [g] for g in _gpu_grads(net, len(hidden))), []))
+            got.append((loss, spikes, grads))
+        finally:
+            net.snn_destroy()
+    monkeypatch.delenv("SNN_CURRENTS")
+    assert got[0][0] == got[1][0]
+    assert all(np.array_equal(a, b) for a, b in zip(got[0][1], got[1][1]))
+    assert all(np.array_equal(a, b) for a, b in zip(got[0][2], got[1][2]))
+
+
 @pytest.mark.parametrize("n_in,hidden,B,T", [(1000, (64,), 40, 300), (700, (256, 130), 33, 200), (37, (300,), 3, 9)])
 def test_inputs_from_host_memory_in_pieces(n_in, hidden, B, T):
     """Spike trains in host memory are copied in pieces beside the forward pass (several pieces per tile, buffers used again;
@@ -455,7 +488,7 @@ def test_inputs_from_host_memory_in_pieces(n_in, hidden, B, T):
             loss = net.snn_forward(a, b, T)
             spikes = [net.snn_get_spikes(l, T) for l in range(len(hidden))]
             net.snn_bind_inputs(a, b, T)
-            net.snn_bptt(snn.SNN_CHUNK, 0, 16)
+            net.snn_bptt(snn.SNN_CHUNK, 0, min(T, 16))
             got.append((loss, spikes, net.snn_get_readout(), _gpu_grads(net, len(hidden))))
         assert got[0][0] == got[1][0] and np.array_equal(got[0][2][0], got[1][2][0])
         assert all(np.array_equal(a, b) for a, b in zip(got[0][1], got[1][1]))
