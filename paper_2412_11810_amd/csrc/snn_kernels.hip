@@ -3183,7 +3183,10 @@ k_adj_rec_rows(NetDev net, AdjJobs jobs, float *__restrict__ carry, int list_all
 // then finishes row r for the four batch elements and writes dv_t as one float4 into the exchange buffer
 // [step & 3][batch group][N][4] (values encoded by xenc, see there: no barrier, the batch groups never wait for each
 // other), from where every workgroup reloads its group's slice into LDS: against a counting barrier per step two layers
-// of 2048 neurons (batch 16, window 0.5) go from 10.2 to 5.2 us per step, four of 8192 (batch 32) from 124 to 118.  Polling is bounded and raises *err; the
+// of 2048 neurons (batch 16, window 0.5) go from 10.2 to 5.2 us per step, four of 8192 (batch 32) from 124 to 118.  Where the row
+// blocks of a (job, batch group) fit one die (by_die) they are placed there instead and exchange through its L2, if all of
+// them find themselves on the same one (unit_on_one_die): the same two layers of 2048, 5.0 -> 4.4 us per step; what is left there is the
+// 16-byte LDS reads at random entries.  Polling is bounded and raises *err; the
 // counting barrier (bounded like k_adj_rec_ws's) is only met once, before the first step.
 // Under a surrogate window (net.win > 0) a row is evaluated only if the potential of at least one of the four batch
 // elements is inside it -- the potentials of the wavefront's rows are in its lanes anyway, a ballot gives the set of
@@ -3193,8 +3196,8 @@ k_adj_rec_rows(NetDev net, AdjJobs jobs, float *__restrict__ carry, int list_all
 // has entries there or not, so the launcher takes the smallest instance that holds nearly every row in one pass.
 template <int CH>
 __global__ void __launch_bounds__(1024)
-k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, unsigned *bar, unsigned *err,
-               unsigned spin_limit, int n_rb, int n_bg, int xg_stride, int lds_n) {
+k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, float *xl, unsigned *posts, unsigned *bar,
+               unsigned *err, unsigned spin_limit, int n_rb, int n_bg, int by_die, int xg_stride, int lds_n) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_dead;
   float4 *xs = reinterpret_cast<float4 *>(smem); // [N]: dv_{t+1} of the group's four batch elements
@@ -3202,9 +3205,15 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
   float4 *sums = xs + lds_n + 64 * wave; // [16][64] behind the widest layer's slice: the row sums of a step, per wavefront
   if (tid == 0) s_dead = 0;
   // workgroups are dealt to the eight dies in turn: all batch groups of a (job, row block) onto one die
+  // (by_die: the row blocks of a (job, batch group) instead)
   const int G = jobs.count * n_rb;
   int g, bg;
-  if ((G & 7) == 0) {
+  if (by_die) {
+    const int k = (int)blockIdx.x >> 3, unit = ((int)blockIdx.x & 7) + 8 * (k / n_rb);
+    if (unit >= jobs.count * n_bg) return;
+    bg = unit % n_bg;
+    g = unit / n_bg * n_rb + k % n_rb;
+  } else if ((G & 7) == 0) {
     const int die = (int)blockIdx.x & 7, k = (int)blockIdx.x >> 3;
     g = die + 8 * (k / n_bg);
     bg = k % n_bg;
@@ -3238,11 +3247,12 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
     m0 = sub[(size_t)j * nsub1];
     m1 = sub[(size_t)j * nsub1 + nsub1 - 1];
   }
-  float *xq = xg + (size_t)jq * xg_stride; // [4][n_bg][N][4]
+  bool dead = false;
+  const bool local = by_die && unit_on_one_die(posts + (jq * n_bg + bg) * n_rb, rb, n_act, err, spin_limit, &dead);
+  float *xq = (local ? xl : xg) + (size_t)jq * xg_stride; // [4][n_bg][N][4]
   const __amdgpu_buffer_rsrc_t xres =
       __builtin_amdgcn_make_buffer_rsrc((void *)xq, 0, (int)((size_t)4 * n_bg * N * 4 * sizeof(float)), 0x00027000);
   unsigned *cnt = bar + 64 * jq + bg;
-  bool dead = false;
   unsigned arrivals = 0;
   auto group_barrier = [&]() {
     // see k_adj_rec_ws: every wave waits for its own stores, then one arrival per workgroup
@@ -3413,9 +3423,15 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
       }
       if (!last) {
         const auto entry = [&](unsigned s) { return (uint32_t)((((size_t)(s & 3u) * n_bg + bg) * N + j) * 16u); };
-        __builtin_amdgcn_raw_buffer_store_b128(csr_u32x4{xenc(dv[0]), xenc(dv[1]), xenc(dv[2]), xenc(dv[3])}, xres, entry(step), 0, 17);
-        // nobody reads the values of two steps ago any more
-        __builtin_amdgcn_raw_buffer_store_b128(csr_u32x4{0u, 0u, 0u, 0u}, xres, entry(step + 2u), 0, 17); // sc0 sc1
+        // (and nobody reads the values of two steps ago any more)
+        const csr_u32x4 coded{xenc(dv[0]), xenc(dv[1]), xenc(dv[2]), xenc(dv[3])}, clear{0u, 0u, 0u, 0u};
+        if (local) {
+          __builtin_amdgcn_raw_buffer_store_b128(coded, xres, entry(step), 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(clear, xres, entry(step + 2u), 0, 0);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b128(coded, xres, entry(step), 0, 17);
+          __builtin_amdgcn_raw_buffer_store_b128(clear, xres, entry(step + 2u), 0, 17);
+        }
       }
     }
     if (last) break; // nobody reads the exchange buffer after the last step
@@ -3428,38 +3444,35 @@ k_adj_rec_csrw(NetDev net, AdjJobs jobs, float *__restrict__ carry, float *xg, u
       __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       dead = true;
     }
-    constexpr int UN = 4;
-    for (int i0 = tid; i0 < N; i0 += UN * 1024) {
+    constexpr int UN = 2;
+    for (int i0 = tid; i0 - tid < N; i0 += UN * 1024) { // a wavefront asks until everything it reads has arrived
       csr_u32x4 x[UN];
-      uint32_t open = 0u;
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        x[u] = csr_u32x4{0u, 0u, 0u, 0u};
-        if (i0 + u * 1024 < N) open |= 1u << u;
-      }
-      const uint32_t mine = open;
-      unsigned spins = 0;
-      for (;;) {
+      for (unsigned spins = 0;;) {
         asm volatile("" ::: "memory"); // every round reads again
 #pragma unroll
-        for (int u = 0; u < UN; ++u)
-          if (open >> u & 1u)
-            x[u] = __builtin_amdgcn_raw_buffer_load_b128(xres, xbase + (uint32_t)(i0 + u * 1024) * 16u, 0, 17); // sc0 sc1
+        for (int u = 0; u < UN; ++u) { // (past the layer's width: its last neuron)
+          const uint32_t o = xbase + (uint32_t)min(i0 + u * 1024, N - 1) * 16u;
+          if (local) x[u] = __builtin_amdgcn_raw_buffer_load_b128(xres, o, 0, 16);
+          else x[u] = __builtin_amdgcn_raw_buffer_load_b128(xres, o, 0, 17);
+        }
+        uint32_t least = ~0u; // 0: something has not arrived
 #pragma unroll
-        for (int u = 0; u < UN; ++u)
-          if (x[u].x != 0u && x[u].y != 0u && x[u].z != 0u && x[u].w != 0u) open &= ~(1u << u);
-        if (open == 0u || dead) break;
+        for (int u = 0; u < UN; ++u) {
+          least = min(min(least, x[u].x), x[u].y);
+          least = min(min(least, x[u].z), x[u].w);
+        }
+        if (__ballot(least == 0u) == 0ull || dead) break;
         if (++spins > spin_limit / 8u ||
             ((spins & 15u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
           __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           dead = true; // keep going to the end of the chunk, never wait again
           break;
         }
-        __builtin_amdgcn_s_sleep(1);
+        if (!local) __builtin_amdgcn_s_sleep(1);
       }
 #pragma unroll
       for (int u = 0; u < UN; ++u)
-        if (mine >> u & 1u) xs[i0 + u * 1024] = make_float4(xdec(x[u].x), xdec(x[u].y), xdec(x[u].z), xdec(x[u].w));
+        if (i0 + u * 1024 < N) xs[i0 + u * 1024] = make_float4(xdec(x[u].x), xdec(x[u].y), xdec(x[u].z), xdec(x[u].w));
     }
     __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the cleared entries are in memory before the next values go out
     __syncthreads();
@@ -5578,13 +5591,26 @@ hipError_t launch_adjoint_jobs(const NetDev &net, const AdjJobs &jobs, float *ca
       const int n_bg = (B + 3) / 4, n_rb = adj_csrw_row_blocks(net, grp.count, n_max);
       if (n_rb <= 0) return hipErrorInvalidValue;
       // counters and the jobs' exchange entries (which lie behind the counters and the error flag) start from zero
-      hipError_t e = launch_fill_zero(ws.bar, (size_t)64 * SNN_MAXL * sizeof(unsigned), s);
-      if (e == hipSuccess) e = launch_fill_zero(ws.xg, (size_t)grp.count * ws.xg_stride * sizeof(float), s);
+      // The row blocks of a (job, batch group) on one die, to exchange through its L2, where there is room for them and the
+      // compressed rows fit that L2 as well: each die then streams them all.  Two layers of 2048 with 10 % of the synapses (3.4 MB a
+      // layer): 4.4 us per step against 5.0.  Larger ones keep all batch groups of a row block on a die, which reads each row once.
+      const int units = grp.count * n_bg, per_die = (units + 7) / 8 * n_rb;
+      bool by_die = ws.xl && per_die <= adj_csrw_resident() / 8 && n_rb <= WAVE && units * n_rb <= 4096 && net.sel_adjoint != 10;
+      for (int k = 0; k < grp.count; ++k) by_die = by_die && (size_t)net.csr_nnz[grp.j[k].l] * sizeof(uint64_t) <= ((size_t)4 << 20);
+      unsigned *posts = reinterpret_cast<unsigned *>(ws.xg + (size_t)SNN_MAXL * ws.xg_stride);
+      ZeroJobs clear{};
+      clear.add(ws.bar, (size_t)64 * SNN_MAXL * sizeof(unsigned));
+      clear.add(ws.xg, (size_t)grp.count * ws.xg_stride * sizeof(float));
+      if (by_die) {
+        clear.add(ws.xl, (size_t)grp.count * ws.xg_stride * sizeof(float));
+        clear.add(posts, (size_t)units * n_rb * sizeof(unsigned));
+      }
+      hipError_t e = launch_fill_zero_jobs(clear, s);
       if (e != hipSuccess) return e;
       const int groups = adj_csrw_groups(net, grp);
       const auto kern = groups == 4 ? k_adj_rec_csrw<4> : groups == 8 ? k_adj_rec_csrw<8> : k_adj_rec_csrw<14>;
-      hipLaunchKernelGGL(kern, dim3(grp.count * n_rb * n_bg), dim3(1024), ((size_t)n_max + 16 * 64) * 4 * sizeof(float),
-                         s, net, grp, carry, ws.xg, ws.bar, ws.err, ws.spin_limit, n_rb, n_bg, ws.xg_stride, n_max);
+      hipLaunchKernelGGL(kern, dim3(by_die ? 8 * per_die : grp.count * n_rb * n_bg), dim3(1024), ((size_t)n_max + 16 * 64) * 4 * sizeof(float),
+                         s, net, grp, carry, ws.xg, ws.xl, posts, ws.bar, ws.err, ws.spin_limit, n_rb, n_bg, by_die ? 1 : 0, ws.xg_stride, n_max);
     } else if (adj_wide_ok(net, l, ws)) {
       taken[i] = true;
       hipError_t e = launch_fill_zero(ws.bar, (size_t)64 * sizeof(unsigned), s);

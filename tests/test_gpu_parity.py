@@ -1444,6 +1444,33 @@ def test_chip_wide_adjoint_over_compressed_rows(hidden, B, T, density, window, m
         _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_DOUBLE, 8, 3), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
 
+@pytest.mark.parametrize("hidden,B,T,density,window", [
+    ((1025,), 5, 11, 0.3, 0.0),          # one neuron past the narrower kernels; a ragged batch group
+    ((2048, 1100), 16, 9, 0.1, 0.5),     # eight units, one per die; row blocks without rows
+    ((2048, 2048, 1026), 4, 1, 0.1, 0.0),  # three units, a single step
+    ((2048, 2048), 20, 7, 0.1, 0.0)])    # ten units: two on some dies
+def test_compressed_row_adjoint_inside_a_die(hidden, B, T, density, window, monkeypatch):
+    """Where the row blocks of a (layer, batch group) fit one die, they exchange through its L2: the same bits as through
+    uncached memory (SNN_WS_KERNEL=uncached) and as the kernel with one workgroup per batch element (=rows_all)."""
+    w = synth.Workload("csrwdie_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=0.8,
+                       rec_density=density, seed=83 + B)
+    d = synth.generate(w)
+    got = {}
+    for mode in ("csrw", "uncached", "rows_all"):
+        monkeypatch.setenv("SNN_WS_KERNEL", mode)
+        net = snn.from_workload(w, d, surr_window=window)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            net.snn_bptt(snn.SNN_CHUNK, 0, min(T, 4))
+            got[mode] = _gpu_grads(net, len(hidden))
+            net.snn_bptt(snn.SNN_CHUNK, 0, min(T, 4))
+            assert _identical(_gpu_grads(net, len(hidden)), got[mode]), mode
+        finally:
+            net.snn_destroy()
+    monkeypatch.delenv("SNN_WS_KERNEL")
+    assert _identical(got["csrw"], got["uncached"]) and _identical(got["csrw"], got["rows_all"])
+
+
 @pytest.mark.parametrize("hidden,B,T,density,window", [((1088,), 5, 14, 1.0, 0.4), ((2048, 1100), 3, 12, 0.15, 0.5),
                                                       ((300, 1026), 4, 10, 1.0, 0.3)])
 def test_event_driven_adjoint_under_the_surrogate_window(hidden, B, T, density, window, monkeypatch):
