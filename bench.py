@@ -494,7 +494,7 @@ def main():
     csr_pol = big and w.rec_density < 1.0 and max(rates) * w.rec_density < 0.01 and np.mean(rates) >= 0.035
     csr_fwd = w.rec_density < 1.0 and min(w.n_hidden) > 1024 and (csr_env == "1" or (csr_env == "" and (csr_pol or (big and np.mean(rates) < 0.035))))
     kernel_of = {"fwd_seq": ("k_layer_seq_gather" if os.environ.get("SNN_SEQ_KERNEL", "") == "gather" else "k_layer_seq_rs") if not wide else ("k_layer_seq_csr_sl" if csr_fwd else
-                            ("k_layer_seq_gather_sl" if nmax > 1024 else "k_layer_seq_gather")),
+                            ("k_layer_seq_gather_sl" if nmax > 1024 else "k_layer_seq_lds")),
                  # (matrices of 32 MB and more: the dense matrix-core version from 3.5 % presynaptic activity, below it
                  # the event-by-event gather k_currents, with k_currents_csr for masked recurrent matrices)
                  "fwd_currents": ("k_currents_dense<4,0>" if np.mean(rates) >= 0.035 else "k_currents") if big else "k_currents_mfma",
