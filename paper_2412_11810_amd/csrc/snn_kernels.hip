@@ -3777,16 +3777,19 @@ k_dw_mfma(DwBatch batch, int B) {
 // (Sixteen wavefronts of 8 rows rather than eight of 16: what bounds the kernel is the round trip LDS read -> add of
 // consecutive events, and four wavefronts per SIMD hide twice as much of it as two.)
 #define DWT_WAVES 16
-template <int BS> // BS = 32 / 64: the batch is 32 (a tile is two whole time steps: the halves of a 64-bit set of rows) or 64
+// RW: rows per wavefront; a launch that 128-row tiles leave short of the chip's compute units (one workgroup each) takes 6 or 7
+// (dw_tile_rows).  The row's spike bits as one word per lane, tested with constants: four layers of 8192, batch 32, 2806 -> 2680 us
+// per launch at 5 %, 3363 -> 3274 at 20 %.
+template <int BS, int RW> // BS = 32 / 64: the batch is 32 (a tile is two whole time steps: the halves of a 64-bit set of rows) or 64
                    // (one time step: the whole set); 0: any batch up to 64
 __global__ void __launch_bounds__(64 * DWT_WAVES)
 k_dw_tile(DwBatch batch, int B) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int PJ = 128, PC = 256, RT = 64, NWV = DWT_WAVES, RW = PJ / NWV, SK = RT / NWV; // rows per wavefront, staging loads per thread
+  constexpr int NWV = DWT_WAVES, PJ = RW * NWV, NWD = PJ % 64 == 0 ? PJ / 64 : PJ / 64 + 2, PC = 256, RT = 64, SK = RT / NWV; // rows per wavefront, staging loads per thread
   // two tile buffers in turn: a tile is written while slower wavefronts still read the one before it, so a tile
   // costs one barrier, not two
   float *const Pb = (float *)smem;                       // [2][RT][PC]
-  uint64_t *const Wb = (uint64_t *)(Pb + 2 * RT * PC);   // [2][2][RT] spike words of the tile's rows
+  uint64_t *const Wb = (uint64_t *)(Pb + 2 * RT * PC);   // [2][NWD][RT] spike words of the tile's rows
   float *P = Pb;
   uint64_t *Wv = Wb;
   int di = 0;
@@ -3794,11 +3797,11 @@ k_dw_tile(DwBatch batch, int B) {
   const DwDesc &d = batch.d[di];
   const int tile = (int)blockIdx.x - d.tile0;
   const int j0 = (tile / d.tiles_n) * PJ, n0 = (tile % d.tiles_n) * PC;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int t0 = d.t0, t1 = d.t1, t_base = d.t_base;
   const int TS = RT / B;                                  // time steps per tile (B <= 64)
   const int jw = j0 + RW * wave;                          // first presynaptic row of this wavefront
-  const int wsel = (RW * wave) >> 6, bitbase = (RW * wave) & 63;
+  const int wsel = (jw >> 6) - (j0 >> 6), bitbase = jw & 63; // where the spike bits of its rows begin
   const int c0 = n0 + 4 * lane;
   // accumulators: continued from HBM
   double acc[RW][4];
@@ -3833,7 +3836,7 @@ k_dw_tile(DwBatch batch, int B) {
   auto tile_store = [&](int t_hi, int nts) {
 #pragma unroll
     for (int k = 0; k < SK; ++k) *reinterpret_cast<float4 *>(P + (size_t)(NWV * k + wave) * PC + 4 * lane) = stg[k];
-    if (tid < 2 * RT) { // spike words of the tile's rows for presynaptic neurons j0 .. j0+127
+    if (tid < NWD * RT) { // spike words of the tile's rows for presynaptic neurons j0 .. j0 + PJ - 1
       const int r = tid & (RT - 1), ws = tid >> 6, ts = r / B, b = r - ts * B;
       uint64_t wv = 0ull;
       if (ts < nts && (j0 >> 6) + ws < d.pre_words) {
@@ -3850,16 +3853,19 @@ k_dw_tile(DwBatch batch, int B) {
     const int nts = t_hi - t0 < TS ? t_hi - t0 : TS;
     // the buffer read two tiles ago: every wavefront has left it, or it would not have passed the barrier of the tile between
     P = Pb + (it & 1) * RT * PC;
-    Wv = Wb + (it & 1) * 2 * RT;
+    Wv = Wb + (it & 1) * NWD * RT;
     tile_store(t_hi, nts);
     __syncthreads();
     const int t_next = t_hi - nts;
     if (t_next > t0) tile_load(t_next, t_next - t0 < TS ? t_next - t0 : TS); // in flight during the adds below
-    const uint64_t wv = Wv[wsel * RT + lane];
+    uint64_t bits = Wv[wsel * RT + lane] >> bitbase; // bit i: the lane's row holds a spike of neuron jw + i
+    if (64 % RW != 0) bits |= (Wv[min(wsel + 1, NWD - 1) * RT + lane] << 1) << (63 - bitbase); // (the last word's rows never go past it)
+    uint32_t own = (uint32_t)bits;
+    asm volatile("" : "+v"(own)); // tested with eight constants, not with eight shifted masks in registers
     if constexpr (BS == 64) { // one time step of 64 rows: the row set as it is
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
-        uint64_t mt = __ballot((wv >> (bitbase + i)) & 1ull); // rows of the tile in which neuron jw + i spiked
+        uint64_t mt = __ballot((own >> i) & 1u); // rows of the tile in which neuron jw + i spiked
         if (mt == 0ull) continue;
         const int k0 = (int)__builtin_ctzll(mt); // the first row starts the sum (see below)
         asm("s_bitset0_b64 %0, %1" : "+s"(mt) : "s"(k0));
@@ -3878,7 +3884,7 @@ k_dw_tile(DwBatch batch, int B) {
     } else if constexpr (BS == 32) { // two time steps of 32 rows: the halves of the row set, no shifts, masks or loop counter (rows past nts hold no spikes)
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
-        const uint64_t m = __ballot((wv >> (bitbase + i)) & 1ull); // rows of the tile in which neuron jw + i spiked
+        const uint64_t m = __ballot((own >> i) & 1u); // rows of the tile in which neuron jw + i spiked
         auto half = [&](uint32_t mt, const float *Ph) {
           // the first row starts the sum (0.0f + x and x differ only for x = -0.0f, and a sum that is -0.0f or +0.0f
           // leaves the fp64 accumulator, which never is -0.0, the same)
@@ -3903,7 +3909,7 @@ k_dw_tile(DwBatch batch, int B) {
     } else {
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
-        const uint64_t m = __ballot((wv >> (bitbase + i)) & 1ull);
+        const uint64_t m = __ballot((own >> i) & 1u);
         if (m == 0ull) continue;
         for (int ts = 0; ts < nts; ++ts) {
           uint64_t mt = (m >> (ts * B)) & bmask;
@@ -5707,6 +5713,23 @@ hipError_t launch_finish_grad_csr(const double *acc, const uint32_t *csr_sub, co
   return hipGetLastError();
 }
 
+// Rows per wavefront of k_dw_tile: a workgroup has a compute unit to itself, so a launch takes as long as its fullest one: rounds
+// times a workgroup's time, which is that of its rows and of staging the adjoint rows (as long as two rows').  512-2x2048-20,
+// batch 16: 176 workgroups of 8 rows a wavefront 75.8 us, 246 of 6 68.2; 700-3x1024-20, batch 64: 192 workgroups of 8, 238
+// of 7, the training step 22.9 -> 22.5 ms.
+static int dw_tile_rows(const DwBatch &batch) {
+  int best = 8;
+  long long least = 0;
+  for (int rw = 8; rw >= 6; --rw) {
+    long long total = 0;
+    for (int i = 0; i < batch.count; ++i)
+      total += (long long)((batch.d[i].n_pre + DWT_WAVES * rw - 1) / (DWT_WAVES * rw)) * ((batch.d[i].n_post + 255) / 256);
+    const long long cost = (total + 255) / 256 * (rw + 2);
+    if (rw == 8 || cost < least) { least = cost; best = rw; }
+  }
+  return best;
+}
+
 hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s) {
   if (batch.count <= 0) return hipSuccess;
   if (B > 64) return hipErrorInvalidValue; // a tile is at least one whole time step of at most 64 rows
@@ -5721,22 +5744,24 @@ hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s) {
       if (batch.count <= 0) return hipSuccess;
     }
   }
+  const int RW = dw_tile_rows(batch);
   int total = 0;
   for (int i = 0; i < batch.count; ++i) {
     if (batch.d[i].t1 <= batch.d[i].t0) return hipErrorInvalidValue;
     batch.d[i].tiles_n = (batch.d[i].n_post + 255) / 256;
     batch.d[i].tile0 = total;
-    total += ((batch.d[i].n_pre + 127) / 128) * batch.d[i].tiles_n;
+    total += ((batch.d[i].n_pre + DWT_WAVES * RW - 1) / (DWT_WAVES * RW)) * batch.d[i].tiles_n;
   }
-  const size_t lds = (size_t)2 * 64 * 256 * sizeof(float) + (size_t)2 * 2 * 64 * sizeof(uint64_t);
-  const void *fn = B == 32 ? reinterpret_cast<const void *>(k_dw_tile<32>)
-                   : B == 64 ? reinterpret_cast<const void *>(k_dw_tile<64>) : reinterpret_cast<const void *>(k_dw_tile<0>);
-  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  if (B == 32) hipLaunchKernelGGL(k_dw_tile<32>, dim3(total), dim3(64 * DWT_WAVES), lds, s, batch, B);
-  else if (B == 64) hipLaunchKernelGGL(k_dw_tile<64>, dim3(total), dim3(64 * DWT_WAVES), lds, s, batch, B);
-  else hipLaunchKernelGGL(k_dw_tile<0>, dim3(total), dim3(64 * DWT_WAVES), lds, s, batch, B);
-  return hipGetLastError();
+  const size_t lds = (size_t)2 * 64 * 256 * sizeof(float) + (size_t)2 * 3 * 64 * sizeof(uint64_t);
+  auto go = [&](auto kern) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(total), dim3(64 * DWT_WAVES), lds, s, batch, B);
+    return hipGetLastError();
+  };
+  if (B == 32) return RW == 8 ? go(k_dw_tile<32, 8>) : RW == 7 ? go(k_dw_tile<32, 7>) : go(k_dw_tile<32, 6>);
+  if (B == 64) return RW == 8 ? go(k_dw_tile<64, 8>) : RW == 7 ? go(k_dw_tile<64, 7>) : go(k_dw_tile<64, 6>);
+  return RW == 8 ? go(k_dw_tile<0, 8>) : RW == 7 ? go(k_dw_tile<0, 7>) : go(k_dw_tile<0, 6>);
 }
 
 hipError_t launch_dw_mfma(DwBatch batch, int B, hipStream_t s) {

@@ -298,6 +298,29 @@ def test_weight_gradient_kernel_follows_the_rates():
         assert lo <= rate < hi, f"gain {gain}: hidden rate {rate:.3f} is outside the regime this case is meant for"
 
 
+@pytest.mark.parametrize("hidden,B,T", [
+    ((97, 300), 5, 9), ((193, 95), 32, 7), ((259, 66), 64, 6),  # 6 rows per wavefront: one past and short of 96-row tiles
+    ((1024, 1024, 1024, 300), 6, 5), ((1024, 1024, 1024, 300), 64, 3),  # 7: more than 256 workgroups of 96 rows, fewer of 112
+    ((1100, 1100, 1100), 3, 5), ((1100, 1100, 1100), 32, 4)])   # 8: more than 256 of 112
+def test_tiled_weight_gradients_at_the_edges_of_tiles(hidden, B, T, monkeypatch):
+    """The event-driven weight-gradient tiles with 6, 7 and 8 rows per wavefront (a wavefront's spike bits may cross a word): the
+    bits of the dense contraction."""
+    w = synth.Workload("dwt_" + "x".join(map(str, hidden)), 70, hidden, 6, T=T, B=B, p_in=0.2, gain=0.8, seed=23 + B)
+    d = synth.generate(w)
+    got = {}
+    for mode in ("mfma", "tile"):
+        monkeypatch.setenv("SNN_DW", mode)
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            net.snn_bptt(snn.SNN_CHUNK, 0, min(T, 3))
+            got[mode] = _gpu_grads(net, len(hidden))
+        finally:
+            net.snn_destroy()
+    monkeypatch.delenv("SNN_DW")
+    assert _identical(got["mfma"], got["tile"])
+
+
 @pytest.mark.parametrize("hidden,B,T", [((520, 300), 20, 12), ((1024,), 32, 10), ((640, 640, 640), 64, 9)])
 def test_chip_wide_adjoint_two_batch_groups_per_workgroup(hidden, B, T, monkeypatch):
     """Layers of 257..1024 neurons with an even number of 16-element batch groups: a workgroup of the chip-wide
