@@ -13,6 +13,7 @@
 //     ascending) that does not depend on where chunk boundaries fall;
 //   * no floating-point atomics anywhere.
 #include "snn_internal.h"
+#include "snn_plan.h"
 #include "snn_split.h"
 #include <algorithm>
 #include <cmath>
@@ -4453,7 +4454,6 @@ static void currents_geometry(const NetDev &net, const CurJobs &jobs, unsigned *
 static size_t currents_lds(int nwv, int ws, int lcap) {
   return (size_t)nwv * 16 * ws * sizeof(uint64_t) + (size_t)nwv * lcap * sizeof(uint32_t);
 }
-#define SNN_LDS_PER_CU (160 * 1024)
 // Matrices of a job: presynaptic widths and the larger product with the postsynaptic width, in bytes.
 static void currents_job_shape(const NetDev &net, const CurJob &j, int *pmax, size_t *wbytes) {
   const bool ro = j.mode == 2;
@@ -4922,7 +4922,6 @@ static int seq_csr_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws
 // The sequential part of layers of 257..1024 neurons with the weights in LDS (k_layer_seq_lds): every job of the stage that
 // wide, units (job, group of batch elements) that fit the dies, one workgroup per compute unit, with as few wavefronts per
 // workgroup as that allows.  SNN_SEQ_SLICES asks for the walk through the L2 (1: unsliced).
-struct SeqLdsPlan { int lpb, waves, groups, slices, units, lcap; size_t lds; };
 static int seq_lds_die_slots(int device) { // workgroups of it that can be resident on a die
   static int cached[16] = {};
   if (device < 0 || device >= 16) return 0;
@@ -4930,7 +4929,7 @@ static int seq_lds_die_slots(int device) { // workgroups of it that can be resid
     hipDeviceProp_t prop;
     int a = 0, b = 0;
     if (hipGetDeviceProperties(&prop, device) != hipSuccess) return 0;
-    const size_t lds = SNN_LDS_PER_CU - 64;
+    const size_t lds = SEQ_LDS_DYNAMIC;
     for (const void *f : {reinterpret_cast<const void *>(k_layer_seq_lds<64>), reinterpret_cast<const void *>(k_layer_seq_lds<32>)})
       if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_layer_seq_lds<64>, 1024, lds) != hipSuccess) return 0;
@@ -4950,22 +4949,7 @@ static bool seq_lds_plan(const NetDev &net, const SeqJobs &ga, const WsArgs *ws,
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess) return false;
   const int slots = seq_lds_die_slots(device);
-  p->lpb = N <= 512 ? 64 : 32;
-  p->slices = (N + p->lpb - 1) / p->lpb;
-  if (p->slices > slots) return false;
-  const int per_wave = 64 / p->lpb, units_max = slots / p->slices * 8;
-  for (p->waves = 4; p->waves <= 16; p->waves *= 2) {
-    p->groups = (net.B + p->waves * per_wave - 1) / (p->waves * per_wave);
-    p->units = ga.count * p->groups;
-    if (p->units > units_max || p->units * p->slices > 64 * SNN_MAXL) continue;
-    const size_t weights = (size_t)(N + 1) * p->lpb * sizeof(float), lists = (size_t)p->waves * per_wave * sizeof(uint16_t);
-    const size_t room = (SNN_LDS_PER_CU - 64 - weights) / lists;
-    p->lcap = (int)((size_t)N + 48 < room ? (size_t)N + 56 : room) & ~7;
-    if (p->lcap < 256 + 48) continue; // a quarter of the widest layer, whole groups, the reads ahead, the spare entry
-    p->lds = weights + lists * p->lcap;
-    return true;
-  }
-  return false;
+  return seq_lds_geometry(N, net.B, ga.count, slots, 64 * SNN_MAXL, p);
 }
 
 hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, float *state, const StoreSpec &st,

@@ -534,6 +534,7 @@ def test_register_stationary_forward_widths(hidden, T):
     ((512, 300), 5, 130, 1.0, 0),              # two widths, a ragged group of batch elements, three tiles
     ((513, 511), 9, 40, 0.7, 0),               # half-word slices, an odd number of them; a narrower layer in the wider class
     ((1000,), 33, 20, 0.5, 0),
+    ((1013,), 65, 6, 0.5, 0),                  # lists that end with the LDS
     ((1024, 1024, 1024, 1024), 64, 12, 1.6, 0),  # sixteen wavefronts, lists shorter than the layer: a quarter of it at a time
     ((640, 640), 3, 2200, 0.5, 1)])            # the ring of spike words
 def test_sequential_forward_with_the_weights_in_lds(hidden, B, T, gain, tier, monkeypatch):

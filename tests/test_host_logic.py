@@ -188,3 +188,41 @@ int main() {
     got = subprocess.run([str(exe)], capture_output=True, text=True)
     assert got.returncode == 0, got.stdout
     assert int(got.stdout) > 0  # shapes that leave blocks without rows are among them
+
+
+def test_lds_of_the_sequential_forward_part(tmp_path):
+    """Every plan of the sequential part of 257..1024 neurons stays within what the launch may ask for, has lists that hold a
+    quarter of the widest layer with the reads ahead, and places its workgroups; widths whose list just reaches the end of
+    the LDS (835, 836, 1013) still have one."""
+    src = tmp_path / "plan.cpp"
+    src.write_text("""
+#include <cstdio>
+#include "snn_plan.h"
+int main() {
+  int plans = 0, tight = 0;
+  for (int N = 257; N <= 1024; ++N)
+    for (int jobs = 1; jobs <= 4; ++jobs)
+      for (int B = 1; B <= 1024; ++B) {
+        SeqLdsPlan p{};
+        if (!seq_lds_geometry(N, B, jobs, 32, 256, &p)) continue;
+        const int per_wave = 64 / p.lpb;
+        const size_t lists = (size_t)p.waves * per_wave * p.lcap * 2, weights = (size_t)(N + 1) * p.lpb * 4;
+        const bool ok = p.lds == weights + lists && p.lds <= SEQ_LDS_DYNAMIC && p.lcap >= 256 + 48 && p.lcap % 8 == 0 &&
+                        p.waves <= 16 && p.groups * p.waves * per_wave >= B && p.units == jobs * p.groups &&
+                        p.slices * p.lpb >= N && (p.units + 7) / 8 * p.slices <= 32 && p.units * p.slices <= 256;
+        if (!ok) { std::printf("N = %d, %d jobs, B = %d: %zu bytes, lists of %d\\n", N, jobs, B, p.lds, p.lcap); return 1; }
+        ++plans;
+        tight += p.lcap < N + 48;
+      }
+  std::printf("%d %d\\n", plans, tight);
+  SeqLdsPlan p{};
+  return seq_lds_geometry(835, 33, 4, 32, 256, &p) && seq_lds_geometry(836, 129, 1, 32, 256, &p) && seq_lds_geometry(1013, 65, 1, 32, 256, &p) ? 0 : 1;
+}
+""")
+    exe = tmp_path / "plan"
+    csrc = os.path.join(ROOT, "paper_2412_11810_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    got = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert got.returncode == 0, got.stdout
+    plans, tight = map(int, got.stdout.split())
+    assert 0 < tight < plans  # lists shorter than their layer are among them
