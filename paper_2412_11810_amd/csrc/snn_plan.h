@@ -31,3 +31,13 @@ inline bool seq_lds_geometry(int N, int B, int jobs, int slots, int posts, SeqLd
   }
   return false;
 }
+
+// ---- register-stationary chain (layers of up to 256 neurons) --------------------------------------
+// Byte offsets of weight [q][i] of an N x N matrix for a buffer load: per lane, and per row in the scalar one.  The chain has
+// NW > N - 1 >= NW - 32 rows and columns; what is not in the matrix has to read 0, and does so by its lane's offset alone
+// and with the scalar one at 0: the hardware's bounds check covers the first, the compiler's contract leaves the second out.
+constexpr uint32_t BUFFER_OUTSIDE = 0x80000000u;
+constexpr uint32_t seq_rs_lane_offset(int N, int NW, int q, int i) {
+  return i < N && (q <= NW - 32 || q < N) ? (uint32_t)i * 4u : BUFFER_OUTSIDE;
+}
+constexpr uint32_t seq_rs_row_offset(int N, int NW, int q) { return q <= NW - 32 || q < N ? (uint32_t)(q * N) * 4u : 0u; }

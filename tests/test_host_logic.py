@@ -226,3 +226,30 @@ int main() {
     assert got.returncode == 0, got.stdout
     plans, tight = map(int, got.stdout.split())
     assert 0 < tight < plans  # lists shorter than their layer are among them
+
+
+def test_weights_of_the_register_stationary_chain_stay_in_the_matrix(tmp_path):
+    """Every load of the chain's prologue is of a weight of the matrix, or its lane's offset alone lies outside the buffer: rows
+    past the layer's width must not count on the scalar offset being part of the bounds check."""
+    src = tmp_path / "rs.cpp"
+    src.write_text("""
+#include <cstdio>
+#include "snn_plan.h"
+int main() {
+  for (int N = 1; N <= 256; ++N) {
+    const int NW = (N + 31) / 32 * 32;
+    for (int q = 0; q < NW; ++q)
+      for (int i = 0; i < 256; ++i) {
+        const uint32_t lane = seq_rs_lane_offset(N, NW, q, i), row = seq_rs_row_offset(N, NW, q), bytes = (uint32_t)(N * N) * 4u;
+        const bool in = q < N && i < N;
+        const bool ok = row < bytes && (in ? (uint64_t)lane + row == (uint64_t)(q * N + i) * 4u : lane >= BUFFER_OUTSIDE);
+        if (!ok) { std::printf("N = %d, row %d, column %d\\n", N, q, i); return 1; }
+      }
+  }
+}
+""")
+    exe = tmp_path / "rs"
+    csrc = os.path.join(ROOT, "paper_2412_11810_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    got = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert got.returncode == 0, got.stdout
