@@ -400,18 +400,17 @@ __device__ __forceinline__ void layer_seq_rs_body(const NetDev &net, const SeqJo
   const bool own = i < N;
   const int ic = own ? i : N - 1;
   float4 *wl = reinterpret_cast<float4 *>(ring + G * 256);             // [lds_rows / 4][256]
-  // (rows and columns past the layer's width read 0, see seq_rs_lane_offset; no load is conditional)
+  // (what lies past the layer's width: see seq_rs_lane_offset; no load is conditional)
   float w[NR];
   {
     const __amdgpu_buffer_rsrc_t wres =
         __builtin_amdgcn_make_buffer_rsrc((void *)net.W_rec[l], 0, (int)((size_t)N * N * sizeof(float)), 0x00027000);
+    const uint32_t col = seq_rs_lane_offset(N, i);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       float m[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        m[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, seq_rs_lane_offset(N, NW, 16 * s + r, i),
-                                                                              seq_rs_row_offset(N, NW, 16 * s + r), 0));
+      for (int r = 0; r < 16; ++r) m[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, col, seq_rs_row_offset(N, NW, 16 * s + r), 0));
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         if (!C::in_lds(s)) w[C::reg_at(s) + r] = m[r];

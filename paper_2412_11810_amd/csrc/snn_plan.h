@@ -33,11 +33,9 @@ inline bool seq_lds_geometry(int N, int B, int jobs, int slots, int posts, SeqLd
 }
 
 // ---- register-stationary chain (layers of up to 256 neurons) --------------------------------------
-// Byte offsets of weight [q][i] of an N x N matrix for a buffer load: per lane, and per row in the scalar one.  The chain has
-// NW > N - 1 >= NW - 32 rows and columns; what is not in the matrix has to read 0, and does so by its lane's offset alone
-// and with the scalar one at 0: the hardware's bounds check covers the first, the compiler's contract leaves the second out.
+// Byte offsets of weight [q][i] of an N x N matrix for a buffer load: per lane, and per row in the scalar one, which the
+// compiler's contract leaves out of the bounds check.  Columns past the layer's width are outside the buffer by their lane's
+// offset and read 0; rows past it are the last row again, their spikes are 0.  (The instance for NW has N > NW - 32.)
 constexpr uint32_t BUFFER_OUTSIDE = 0x80000000u;
-constexpr uint32_t seq_rs_lane_offset(int N, int NW, int q, int i) {
-  return i < N && (q <= NW - 32 || q < N) ? (uint32_t)i * 4u : BUFFER_OUTSIDE;
-}
-constexpr uint32_t seq_rs_row_offset(int N, int NW, int q) { return q <= NW - 32 || q < N ? (uint32_t)(q * N) * 4u : 0u; }
+constexpr uint32_t seq_rs_lane_offset(int N, int i) { return i < N ? (uint32_t)i * 4u : BUFFER_OUTSIDE; }
+constexpr uint32_t seq_rs_row_offset(int N, int NW, int q) { return (uint32_t)((q <= NW - 32 || q < N ? q : N - 1) * N) * 4u; }

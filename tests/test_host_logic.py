@@ -229,8 +229,8 @@ int main() {
 
 
 def test_weights_of_the_register_stationary_chain_stay_in_the_matrix(tmp_path):
-    """Every load of the chain's prologue is of a weight of the matrix, or its lane's offset alone lies outside the buffer: rows
-    past the layer's width must not count on the scalar offset being part of the bounds check."""
+    """Every load of the chain's prologue is of a weight of the matrix (rows past the layer's width: the last one's), or its lane's
+    offset alone lies outside the buffer: nothing may count on the scalar offset being part of the bounds check."""
     src = tmp_path / "rs.cpp"
     src.write_text("""
 #include <cstdio>
@@ -240,9 +240,9 @@ int main() {
     const int NW = (N + 31) / 32 * 32;
     for (int q = 0; q < NW; ++q)
       for (int i = 0; i < 256; ++i) {
-        const uint32_t lane = seq_rs_lane_offset(N, NW, q, i), row = seq_rs_row_offset(N, NW, q), bytes = (uint32_t)(N * N) * 4u;
-        const bool in = q < N && i < N;
-        const bool ok = row < bytes && (in ? (uint64_t)lane + row == (uint64_t)(q * N + i) * 4u : lane >= BUFFER_OUTSIDE);
+        const uint32_t lane = seq_rs_lane_offset(N, i), row = seq_rs_row_offset(N, NW, q), bytes = (uint32_t)(N * N) * 4u;
+        const int r = q < N ? q : N - 1;
+        const bool ok = row < bytes && (i < N ? (uint64_t)lane + row == (uint64_t)(r * N + i) * 4u : lane >= BUFFER_OUTSIDE);
         if (!ok) { std::printf("N = %d, row %d, column %d\\n", N, q, i); return 1; }
       }
   }
