@@ -644,6 +644,10 @@ struct InputFeed {
       if (!c->in_copied[k]) HIPCHK(c, hipEventCreateWithFlags(&c->in_copied[k], hipEventDisableTiming));
       if (!c->in_packed[k]) HIPCHK(c, hipEventCreateWithFlags(&c->in_packed[k], hipEventDisableTiming));
     }
+    // the copy stream follows what the compute stream holds: the caller's own stream may still write the spike trains, and
+    // a call that failed may have left packs of the buffers behind
+    HIPCHK(c, hipEventRecord(c->in_packed[0], c->stream));
+    HIPCHK(c, hipStreamWaitEvent(c->copy_stream, c->in_packed[0], 0));
     return SNN_OK;
   }
   hipError_t steps(int t0, int t1) { // steps t0 + 1 .. t1

@@ -1,0 +1,207 @@
+// The library's host code (snn_api.cpp) over a stand-in for the HIP runtime: device memory is host memory, a stream is a queue
+// whose operations run when something waits for them (the latest moment a GPU may take), allocations and copies can be refused,
+// kernels are replaced by what a check needs of them.  One program, a check per name on the command line (tests/test_host_runtime.py).
+#define __align__(x) __attribute__((aligned(x)))
+#define HIP_SYMBOL(x) (&x)
+#include "snn_api.cpp"
+
+#include <atomic>
+#include <chrono>
+#include <functional>
+#include <map>
+#include <mutex>
+#include <thread>
+
+// ---- the runtime --------------------------------------------------------------------------------
+struct ihipStream_t {
+  std::vector<std::function<void()>> q;
+  size_t done = 0;
+  void drain(size_t upto) { while (done < upto) q[done++](); }
+};
+struct ihipEvent_t { ihipStream_t *s = nullptr; size_t at = 0; };
+static std::mutex g_mem_mutex;
+static std::map<void *, size_t> g_mem;      // device allocations
+static size_t g_largest = ~(size_t)0;       // larger ones are refused
+static int g_mallocs = 0, g_refused = 0;
+static int g_copies_left = -1;              // asynchronous copies until one fails (-1: none does)
+static void put(hipStream_t s, std::function<void()> f) { if (s) s->q.push_back(f); else f(); }
+
+#define HIP(name, ...) extern "C" hipError_t name(__VA_ARGS__)
+static hipError_t device_alloc(void **p, size_t n) {
+  std::lock_guard<std::mutex> hold(g_mem_mutex);
+  if (n > g_largest) { ++g_refused; return hipErrorOutOfMemory; }
+  ++g_mallocs;
+  *p = std::calloc(1, n ? n : 1);
+  g_mem[*p] = n;
+  return hipSuccess;
+}
+HIP(hipMalloc, void **p, size_t n) { return device_alloc(p, n); }
+HIP(hipExtMallocWithFlags, void **p, size_t n, unsigned) { return device_alloc(p, n); }
+HIP(hipFree, void *p) {
+  std::lock_guard<std::mutex> hold(g_mem_mutex);
+  if (p) g_mem.erase(p);
+  return hipSuccess; // (kept: a queued operation may still name it)
+}
+HIP(hipHostMalloc, void **p, size_t n, unsigned) { *p = std::calloc(1, n); return hipSuccess; }
+HIP(hipHostFree, void *p) { std::free(p); return hipSuccess; }
+HIP(hipPointerGetAttributes, hipPointerAttribute_t *a, const void *p) {
+  std::lock_guard<std::mutex> hold(g_mem_mutex);
+  auto it = g_mem.upper_bound(const_cast<void *>(p));
+  const bool dev = it != g_mem.begin() && (--it, static_cast<const char *>(p) < static_cast<const char *>(it->first) + it->second);
+  a->type = dev ? hipMemoryTypeDevice : hipMemoryTypeHost;
+  return hipSuccess;
+}
+HIP(hipMemcpyAsync, void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t st) {
+  if (g_copies_left == 0) return hipErrorUnknown;
+  if (g_copies_left > 0) --g_copies_left;
+  put(st, [=] { std::memcpy(d, s, n); });
+  return hipSuccess;
+}
+HIP(hipMemcpy2DAsync, void *, size_t, const void *, size_t, size_t, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+HIP(hipMemcpy, void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+HIP(hipMemset, void *d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
+HIP(hipMemsetAsync, void *d, int v, size_t n, hipStream_t st) { put(st, [=] { std::memset(d, v, n); }); return hipSuccess; }
+HIP(hipMemGetInfo, size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return hipSuccess; }
+HIP(hipStreamCreateWithFlags, hipStream_t *s, unsigned) { *s = new ihipStream_t(); return hipSuccess; }
+HIP(hipStreamDestroy, hipStream_t) { return hipSuccess; }
+HIP(hipStreamSynchronize, hipStream_t s) { if (s) s->drain(s->q.size()); return hipSuccess; }
+HIP(hipDeviceSynchronize) { return hipSuccess; }
+HIP(hipEventCreate, hipEvent_t *e) { *e = new ihipEvent_t(); return hipSuccess; }
+HIP(hipEventCreateWithFlags, hipEvent_t *e, unsigned) { *e = new ihipEvent_t(); return hipSuccess; }
+HIP(hipEventDestroy, hipEvent_t) { return hipSuccess; }
+HIP(hipEventRecord, hipEvent_t e, hipStream_t s) { e->s = s; e->at = s ? s->q.size() : 0; return hipSuccess; }
+HIP(hipStreamWaitEvent, hipStream_t s, hipEvent_t e, unsigned) {
+  ihipStream_t *from = e->s;
+  const size_t at = e->at;
+  if (from && from != s) put(s, [=] { from->drain(at); });
+  return hipSuccess;
+}
+HIP(hipEventElapsedTime, float *ms, hipEvent_t, hipEvent_t) { *ms = 0.0f; return hipSuccess; }
+HIP(hipStreamBeginCapture, hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; } // (the checks run with SNN_GRAPH=0)
+HIP(hipStreamEndCapture, hipStream_t, hipGraph_t *) { return hipErrorNotSupported; }
+HIP(hipGraphInstantiate, hipGraphExec_t *, hipGraph_t, hipGraphNode_t *, char *, size_t) { return hipErrorNotSupported; }
+HIP(hipGraphLaunch, hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
+HIP(hipGraphDestroy, hipGraph_t) { return hipSuccess; }
+HIP(hipGraphExecDestroy, hipGraphExec_t) { return hipSuccess; }
+HIP(hipGetDeviceCount, int *n) { *n = 1; return hipSuccess; }
+HIP(hipSetDevice, int) { return hipSuccess; }
+HIP(hipGetLastError) { return hipSuccess; }
+HIP(hipGetSymbolAddress, void **p, const void *s) { *p = const_cast<void *>(s); return hipSuccess; }
+extern "C" const char *hipGetErrorString(hipError_t) { return "refused"; }
+
+// ---- the kernels --------------------------------------------------------------------------------
+static double g_rate = 0.0;                              // what launch_count_spikes finds
+static std::function<void(const NetDev &, const WsArgs *)> g_forward; // what a forward pass does on the GPU
+hipError_t launch_pack_inputs(const uint8_t *in, uint64_t *mask, int T, int B, int n_in, int Wd, hipStream_t s) {
+  put(s, [=] { // row 0 of mask is step 0
+    for (size_t r = 0; r < (size_t)T * B; ++r)
+      for (int w = 0; w < Wd; ++w) {
+        uint64_t v = 0;
+        for (int k = 64 * w; k < n_in && k < 64 * w + 64; ++k) v |= (uint64_t)(in[r * n_in + k] != 0) << (k & 63);
+        mask[((size_t)B + r) * Wd + w] = v;
+      }
+  });
+  return hipSuccess;
+}
+hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, float *, const StoreSpec &, double *, int, float *,
+                          hipStream_t s, const SpanHook *, const FwdCallbacks *cb, const WsArgs *ws) {
+  for (int k = 0; k < n_tiles && cb && cb->tile_inputs; ++k) {
+    const hipError_t e = cb->tile_inputs(cb->ctx, bounds[k], bounds[k + 1]);
+    if (e != hipSuccess) return e;
+  }
+  const NetDev *n = &net;
+  if (g_forward) put(s, [=] { g_forward(*n, ws); });
+  return hipSuccess;
+}
+hipError_t launch_count_spikes(const uint64_t *, size_t n_words, unsigned long long *count, hipStream_t s) {
+  put(s, [=] { *count += (unsigned long long)(g_rate * 64.0 * (double)n_words); });
+  return hipSuccess;
+}
+hipError_t launch_fill_zero(void *p, size_t n, hipStream_t s) { put(s, [=] { std::memset(p, 0, n); }); return hipSuccess; }
+hipError_t launch_fill_zero_jobs(ZeroJobs, hipStream_t) { return hipSuccess; }
+hipError_t launch_recompute(const NetDev &, int, int, const float *, float *, int, size_t, int, float *, hipStream_t) { return hipSuccess; }
+hipError_t launch_recompute_currents(const NetDev &, int, int, float *, int, size_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_recompute_scan(const NetDev &, int, int, const float *, float *, int, size_t, int, float *, hipStream_t, const float *,
+                                 int) { return hipSuccess; }
+hipError_t launch_loss(const double *, const int32_t *, int, int, int, float *, float *, float *, hipStream_t) { return hipSuccess; }
+hipError_t launch_adjoint_head(const NetDev &, int, int, int, float *, const float *, float *, int, float *, hipStream_t,
+                               const SpanHook *) { return hipSuccess; }
+hipError_t launch_up_product(const NetDev &, int, int, int, int, const float *, float *, hipStream_t, const SpanHook *) { return hipSuccess; }
+hipError_t launch_adjoint_jobs(const NetDev &, const AdjJobs &, float *, const WsArgs &, hipStream_t, const SpanHook *) { return hipSuccess; }
+int ws_max_resident_groups(int) { return 256; }
+int ws_max_resident_groups_mfma(int) { return 256; }
+int ws_max_resident_groups_mfma8(int) { return 256; }
+void adjoint_prepare(const NetDev &, const WsArgs &) {}
+hipError_t launch_dw(const uint64_t *, int, int, int, const float *, size_t, int, int, int, int, int, int, int, double *, hipStream_t, int) {
+  return hipSuccess;
+}
+hipError_t launch_dw_mfma(DwBatch, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_dw_tile(DwBatch, int, hipStream_t) { return hipSuccess; }
+bool bwd_stage_fusable(const NetDev &, int) { return false; }
+int bwd_pre_placement(const NetDev &) { return 0; }
+hipError_t launch_bwd_stage(const NetDev &, const AdjJobs &, float *, DwBatch, DuJob, const float *, PreJobs, hipStream_t, const SpanHook *) {
+  return hipSuccess;
+}
+hipError_t launch_bwd_inter(const NetDev &, InterJobs, hipStream_t, const SpanHook *) { return hipSuccess; }
+hipError_t launch_transpose(const float *, float *, int, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_csr_count(const uint8_t *, int, uint32_t *, unsigned long long *, hipStream_t) { return hipSuccess; }
+hipError_t launch_csr_fill(const uint8_t *, const float *, int, uint32_t, uint32_t *, uint16_t *, float *, uint64_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_finish_grads(FinishJobs, hipStream_t) { return hipSuccess; }
+hipError_t launch_finish_grad_csr(const double *, const uint32_t *, const uint16_t *, int, float *, hipStream_t) { return hipSuccess; }
+hipError_t launch_unpack_spikes(const uint64_t *, int, int, int, int, uint8_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_copy(const void *, void *, size_t, hipStream_t) { return hipSuccess; }
+bool snn_kernel_shape_ok(const NetDev &, char *, size_t) { return true; }
+static const size_t LIST_ENTRIES = (size_t)1 << 20;
+size_t currents_lists_entries(const NetDev &n) { return n.N[0] > 256 ? LIST_ENTRIES : 0; }
+
+// ---- the checks ---------------------------------------------------------------------------------
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); std::exit(1); } } while (0)
+struct Net {
+  snn_config cfg{};
+  snn_ctx *c = nullptr;
+  std::vector<uint8_t> x;
+  std::vector<int32_t> y;
+  Net(int width, int T, int B, int n_in = 64, hipStream_t stream = nullptr) {
+    cfg.n_in = n_in; cfg.n_layers = 1; cfg.n_hidden[0] = width; cfg.n_out = 8; cfg.T = T; cfg.batch = B;
+    cfg.alpha = cfg.beta_out = 0.9f; cfg.theta = 1.0f; cfg.surr_beta = 10.0f; cfg.stream = stream;
+    if (snn_init(&cfg, &c) != SNN_OK) { std::printf("snn_init: %s\n", snn_last_error(c)); std::exit(1); }
+    fill(0);
+  }
+  void fill(int k) { // batch number k
+    x.assign((size_t)cfg.T * cfg.batch * cfg.n_in, (uint8_t)(k & 1));
+    y.assign((size_t)cfg.batch, k % cfg.n_out);
+  }
+  snn_status bind() { return snn_bind_inputs(c, x.data(), y.data(), cfg.T); }
+  snn_status forward() { return snn_forward(c, x.data(), y.data(), cfg.T, nullptr); }
+  bool holds(int k) const { // the inputs and labels of batch k are the bound ones
+    for (size_t i = (size_t)cfg.batch; i < (size_t)(cfg.T + 1) * cfg.batch; ++i)
+      if (c->net.mask[0][i] != (k & 1 ? ~0ull : 0ull)) return false;
+    for (int b = 0; b < cfg.batch; ++b)
+      if (c->labels[b] != k % cfg.n_out) return false;
+    return true;
+  }
+  ~Net() { snn_destroy(c); }
+};
+
+// Spike trains in host memory that work on the caller's own stream still writes when the library is called
+static void caller_stream() {
+  for (int entry = 0; entry < 2; ++entry) {
+    hipStream_t mine;
+    hipStreamCreateWithFlags(&mine, 0);
+    Net n(64, 20, 4, 64, mine);
+    std::vector<uint8_t> later(n.x.size(), 1);
+    n.y.assign(n.y.size(), 1);
+    hipMemcpyAsync(n.x.data(), later.data(), later.size(), hipMemcpyDeviceToHost, mine);
+    CHECK((entry ? n.forward() : n.bind()) == SNN_OK);
+    CHECK(n.holds(1));
+  }
+}
+
+int main(int argc, char **argv) {
+  setenv("SNN_GRAPH", "0", 1);
+  const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}};
+  const auto it = checks.find(argc > 1 ? argv[1] : "");
+  if (it == checks.end()) return 2;
+  it->second();
+  return 0;
+}
