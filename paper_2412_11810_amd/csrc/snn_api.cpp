@@ -670,8 +670,8 @@ struct InputFeed {
   static hipError_t tile(void *self, int t0, int t1) { return static_cast<InputFeed *>(self)->steps(t0, t1); }
 };
 
-// Arguments of a call that binds inputs, and the labels to the context.
-static snn_status bind_labels(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labels, int32_t T) {
+// Arguments of a call that binds inputs; nothing of the context is touched.
+static snn_status check_batch(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labels, int32_t T) {
   if (!c || !in_spikes || !labels) return fail(c, SNN_E_INVAL, "null argument");
   if (T < 1 || T > c->cfg.T) return fail(c, SNN_E_INVAL, "T out of range for this context");
   HIPCHK(c, hipSetDevice(c->cfg.device));
@@ -690,22 +690,30 @@ static snn_status bind_labels(snn_ctx *c, const uint8_t *in_spikes, const int32_
         return fail(c, SNN_E_INVAL, msg);
       }
   }
-  HIPCHK(c, hipMemcpyAsync(c->labels, labels, (size_t)n.B * 4, hipMemcpyDefault, c->stream));
   return SNN_OK;
 }
 
+// The labels to the context.  From here to the end of a call that binds, nothing is bound: labels and spike trains are of two batches.
+static hipError_t replace_labels(snn_ctx *c, const int32_t *labels) {
+  c->T_bound = c->T_spikes = 0;
+  return hipMemcpyAsync(c->labels, labels, (size_t)c->net.B * 4, hipMemcpyDefault, c->stream);
+}
+
 snn_status snn_bind_inputs(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labels, int32_t T) {
-  snn_status rs = bind_labels(c, in_spikes, labels, T);
+  snn_status rs = check_batch(c, in_spikes, labels, T);
   if (rs != SNN_OK) return rs;
   const NetDev &n = c->net;
-  hipError_t e = hipSuccess;
-  if (is_device_ptr(in_spikes)) {
-    e = launch_pack_inputs(in_spikes, n.mask[0], T, n.B, n.n_in, n.Wd[0], c->stream);
-  } else {
-    InputFeed feed{c, in_spikes};
+  const bool on_device = is_device_ptr(in_spikes);
+  InputFeed feed{c, in_spikes};
+  if (!on_device) {
     rs = feed.init();
     if (rs != SNN_OK) return rs;
-    e = feed.steps(0, T);
+  }
+  hipError_t e = replace_labels(c, labels);
+  if (on_device) {
+    if (e == hipSuccess) e = launch_pack_inputs(in_spikes, n.mask[0], T, n.B, n.n_in, n.Wd[0], c->stream);
+  } else {
+    if (e == hipSuccess) e = feed.steps(0, T);
     const hipError_t ec = hipStreamSynchronize(c->copy_stream); // also after a failure: nothing reads the caller's buffer any more
     if (e == hipSuccess) e = ec;
   }
@@ -850,14 +858,14 @@ static snn_status check_ws_error(snn_ctx *c);
 snn_status snn_forward(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labels, int32_t T, float *loss_out) {
   snn_status s;
   if (c && in_spikes && !is_device_ptr(in_spikes)) { // from host memory: tile by tile, beside the pass itself
-    s = bind_labels(c, in_spikes, labels, T);
+    s = check_batch(c, in_spikes, labels, T);
     if (s != SNN_OK) return s;
     InputFeed feed{c, in_spikes};
     s = feed.init();
     if (s != SNN_OK) return s;
+    HIPCHK(c, replace_labels(c, labels));
     const FwdCallbacks cb{&feed, nullptr, &InputFeed::tile};
     c->T_bound = T;
-    c->T_spikes = 0;
     s = forward_only(c, nullptr, nullptr, &cb);
     const hipError_t ec = hipStreamSynchronize(c->copy_stream); // also after a failure: nothing reads the caller's buffer any more
     if (s == SNN_OK && ec != hipSuccess) s = fail(c, SNN_E_HIP, hipGetErrorString(ec));
@@ -910,10 +918,9 @@ snn_status snn_forward_noalloc(snn_ctx *c, const uint8_t *in_spikes, const int32
       snprintf(msg, sizeof msg, "label %d of batch element %d is outside [0, %d)", (int)lab_host[b], b, n.n_out);
       return fail(c, SNN_E_INVAL, msg);
     }
+  HIPCHK(c, replace_labels(c, labels));
   HIPCHK(c, launch_pack_inputs(in_spikes, n.mask[0], T, n.B, n.n_in, n.Wd[0], s));
-  HIPCHK(c, hipMemcpyAsync(c->labels, labels, (size_t)n.B * 4, hipMemcpyDeviceToDevice, s));
   c->T_bound = T;
-  c->T_spikes = 0;
   // every current the sequential kernels read from the workspace is written earlier in the same call: nothing in
   // it has to start at zero, and what the previous call left there is never read
   const snn_status rs = forward_only(c, nullptr, static_cast<float *>(g_scratch_dev[dev]));

@@ -197,9 +197,41 @@ static void caller_stream() {
   }
 }
 
+// No room for the staging buffers: the batch that was bound stays, whole
+static void no_room_for_staging() {
+  for (int entry = 0; entry < 2; ++entry) {
+    Net n(64, 20, 4);
+    void *x = nullptr;
+    hipMalloc(&x, n.x.size());
+    CHECK(snn_bind_inputs(n.c, (uint8_t *)x, n.y.data(), n.cfg.T) == SNN_OK); // batch 0, from device memory
+    n.fill(1);
+    g_largest = (size_t)1 << 20;
+    CHECK((entry ? n.forward() : n.bind()) != SNN_OK);
+    g_largest = ~(size_t)0;
+    hipStreamSynchronize(n.c->stream);
+    CHECK(n.c->T_bound == n.cfg.T && n.holds(0));
+    CHECK(snn_bptt(n.c, SNN_STANDARD, 0, 0, 0, nullptr) == SNN_OK);
+    CHECK((entry ? n.forward() : n.bind()) == SNN_OK && n.holds(1));
+  }
+}
+
+// A copy that fails leaves labels of one batch and spike trains of another: nothing is bound then
+static void copy_fails() {
+  for (int entry = 0; entry < 2; ++entry) {
+    Net n(64, 20, 4);
+    CHECK(n.bind() == SNN_OK);
+    n.fill(1);
+    g_copies_left = 1; // the labels arrive
+    CHECK((entry ? n.forward() : n.bind()) == SNN_E_HIP);
+    g_copies_left = -1;
+    CHECK(snn_bptt(n.c, SNN_STANDARD, 0, 0, 0, nullptr) == SNN_E_STATE);
+    CHECK(n.bind() == SNN_OK && n.holds(1) && snn_bptt(n.c, SNN_STANDARD, 0, 0, 0, nullptr) == SNN_OK);
+  }
+}
+
 int main(int argc, char **argv) {
   setenv("SNN_GRAPH", "0", 1);
-  const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}};
+  const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

@@ -23,3 +23,8 @@ def checks(tmp_path_factory):
 
 def test_inputs_still_being_written_on_the_callers_stream(checks):
     checks("caller_stream")
+
+
+@pytest.mark.parametrize("name", ["no_room_for_staging", "copy_fails"])
+def test_a_failed_call_never_binds_parts_of_two_batches(checks, name):
+    checks(name)
