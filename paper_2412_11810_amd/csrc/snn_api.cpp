@@ -954,7 +954,7 @@ snn_status snn_debug_states(snn_ctx *c, float *dst) {
   (void)hipFree(traj);
   if (s != SNN_OK) return s;
   if (e != hipSuccess) return fail(c, SNN_E_HIP, hipGetErrorString(e));
-  return SNN_OK;
+  return check_ws_error(c); // as in snn_forward
 }
 
 snn_status snn_get_state(snn_ctx *c, int layer, int32_t t, float *dst) {

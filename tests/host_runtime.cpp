@@ -229,9 +229,27 @@ static void copy_fails() {
   }
 }
 
+// A chip-wide kernel that gave up waiting: the call says so, and the next one starts afresh
+static void time_out_is_reported() {
+  Net n(512, 20, 4);
+  CHECK(n.bind() == SNN_OK);
+  std::vector<float> v((size_t)n.cfg.T * n.cfg.batch * 512);
+  const auto give_up = [](const NetDev &, const WsArgs *ws) { *ws->err = 1u; };
+  for (int entry = 0; entry < 3; ++entry) {
+    const auto call = [&] {
+      return entry == 0 ? n.forward() : entry == 1 ? snn_debug_states(n.c, v.data()) : snn_bptt(n.c, SNN_STANDARD, 0, 0, 0, nullptr);
+    };
+    g_forward = give_up;
+    CHECK(call() == SNN_E_HIP);
+    g_forward = nullptr;
+    CHECK(call() == SNN_OK);
+  }
+}
+
 int main(int argc, char **argv) {
   setenv("SNN_GRAPH", "0", 1);
-  const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails}};
+  const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
+                                              {"time_out_is_reported", time_out_is_reported}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

@@ -28,3 +28,7 @@ def test_inputs_still_being_written_on_the_callers_stream(checks):
 @pytest.mark.parametrize("name", ["no_room_for_staging", "copy_fails"])
 def test_a_failed_call_never_binds_parts_of_two_batches(checks, name):
     checks(name)
+
+
+def test_every_entry_point_reports_a_kernel_that_gave_up_waiting(checks):
+    checks("time_out_is_reported")
