@@ -29,8 +29,11 @@
  * library asks the HIP runtime which); a context on a stream of the library's own waits for
  * the device's default stream before it touches them.  The caller owns every buffer it passes and
  * keeps it alive for the duration of the call.  All calls on one context must come
- * from one thread at a time.  All functions return after the work they queued on the
- * context's stream (and on the library's private copy stream) has completed.
+ * from one thread at a time; different contexts may be driven from different threads.  All functions return after the
+ * work they queued on the context's stream (and on the library's private copy stream) has completed.
+ * Networks with a layer above 256 neurons have kernels whose workgroups wait for each other and need the whole GPU to be
+ * sure of it: forward passes and training steps of such contexts on one GPU take turns within a process.  Between processes
+ * nobody arranges that; a wait that lasts about a second ends the call with SNN_E_HIP and results that do not count.
  */
 #ifndef SNN_H
 #define SNN_H

@@ -6,6 +6,8 @@
 #include <cstdlib>
 #include <cmath>
 #include <cstring>
+#include <mutex>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -128,6 +130,20 @@ bool is_device_ptr(const void *p) {
   }
   return a.type == hipMemoryTypeDevice;
 }
+
+// Kernels whose workgroups wait for each other (the chip-wide adjoint, the sequential forward part of layers above 256 neurons)
+// need all of them resident at once, and a launch may take every compute unit.  Two such launches on one GPU could each
+// hold a part of it and wait for the rest until their polls run out: calls of contexts that have such kernels take turns, from the
+// first launch to the end of the work.  Other contexts' kernels wait for nobody and run beside them.
+std::mutex g_turn[SNN_MAX_DEVICES];
+struct Turn {
+  snn_ctx *c;
+  std::unique_lock<std::mutex> held;
+  explicit Turn(snn_ctx *c) : c(c) {
+    if (c->ws.xg) held = std::unique_lock<std::mutex>(g_turn[c->cfg.device % SNN_MAX_DEVICES]);
+  }
+  ~Turn() { if (held.owns_lock()) (void)hipStreamSynchronize(c->stream); } // also where a call ends early
+};
 
 // Pool of uncached device blocks (never returned to the driver before the process ends).
 struct UncachedBlock { int device; size_t bytes; void *ptr; bool busy; };
@@ -857,6 +873,7 @@ static snn_status forward_only(snn_ctx *c, float *traj_or_null, float *work_or_n
 static snn_status check_ws_error(snn_ctx *c);
 snn_status snn_forward(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labels, int32_t T, float *loss_out) {
   snn_status s;
+  std::optional<Turn> turn;
   if (c && in_spikes && !is_device_ptr(in_spikes)) { // from host memory: tile by tile, beside the pass itself
     s = check_batch(c, in_spikes, labels, T);
     if (s != SNN_OK) return s;
@@ -866,6 +883,7 @@ snn_status snn_forward(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labe
     HIPCHK(c, replace_labels(c, labels));
     const FwdCallbacks cb{&feed, nullptr, &InputFeed::tile};
     c->T_bound = T;
+    turn.emplace(c);
     s = forward_only(c, nullptr, nullptr, &cb);
     const hipError_t ec = hipStreamSynchronize(c->copy_stream); // also after a failure: nothing reads the caller's buffer any more
     if (s == SNN_OK && ec != hipSuccess) s = fail(c, SNN_E_HIP, hipGetErrorString(ec));
@@ -876,6 +894,7 @@ snn_status snn_forward(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labe
   } else {
     s = snn_bind_inputs(c, in_spikes, labels, T);
     if (s != SNN_OK) return s;
+    turn.emplace(c);
     s = forward_only(c, nullptr);
     if (s != SNN_OK) return s;
   }
@@ -923,6 +942,7 @@ snn_status snn_forward_noalloc(snn_ctx *c, const uint8_t *in_spikes, const int32
   c->T_bound = T;
   // every current the sequential kernels read from the workspace is written earlier in the same call: nothing in
   // it has to start at zero, and what the previous call left there is never read
+  Turn turn(c);
   const snn_status rs = forward_only(c, nullptr, static_cast<float *>(g_scratch_dev[dev]));
   if (rs != SNN_OK) return rs;
   float *loss_host = reinterpret_cast<float *>(c->host_small);
@@ -947,6 +967,7 @@ snn_status snn_debug_states(snn_ctx *c, float *dst) {
   float *traj = nullptr;
   const size_t bytes = (size_t)c->T_bound * c->Ms();
   HIPCHK(c, hipMalloc(&traj, bytes));
+  Turn turn(c);
   snn_status s = forward_only(c, traj);
   hipError_t e = hipSuccess;
   if (s == SNN_OK) e = hipMemcpyAsync(dst, traj, bytes, hipMemcpyDeviceToHost, c->stream);
@@ -2118,6 +2139,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
       if (e != hipSuccess) { c->graph_exec = nullptr; return fail(c, SNN_E_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e)); }
       c->graph_key = key;
     }
+    Turn turn(c);
     HIPCHK(c, hipGraphLaunch(c->graph_exec, s));
     if (c->rate_driven || c->dw_rate_driven) {
       snn_status rr = update_current_policy(c, T, nullptr, ring > 0);
@@ -2129,6 +2151,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
     return check_ws_error(c);
   }
 
+  Turn turn(c);
   Timer tm{c, stats != nullptr};
   hipEvent_t ev_start = tm.mark(), ev_fwd = nullptr;
   if (!ev_start) return fail(c, SNN_E_HIP, "hipEventCreate failed");

@@ -246,10 +246,50 @@ static void time_out_is_reported() {
   }
 }
 
+// Two contexts whose kernels wait between workgroups, from two threads on one GPU: never at the same time.  One whose kernels wait
+// for nobody runs beside them.
+static void turns() {
+  static std::atomic<int> inside{0}, overlaps{0}, narrow_runs{0};
+  static std::atomic<bool> alone{true};
+  g_forward = [](const NetDev &n, const WsArgs *) {
+    if (n.N[0] <= 256) { ++narrow_runs; return; }
+    if (++inside > 1) ++overlaps;
+    for (int i = 0; i < 400 && !alone && narrow_runs == 0; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(5));
+    std::this_thread::sleep_for(std::chrono::milliseconds(3));
+    --inside;
+  };
+  Net a(512, 20, 4), b(1100, 20, 4), narrow(64, 20, 4);
+  const auto work = [](Net &n, bool noalloc) {
+    std::vector<float> v((size_t)n.cfg.T * n.cfg.batch * n.c->net.SN);
+    void *x, *y;
+    hipMalloc(&x, n.x.size());
+    hipMalloc(&y, n.y.size() * 4);
+    for (int k = 0; k < 4; ++k) {
+      CHECK(n.forward() == SNN_OK);
+      CHECK(snn_bptt(n.c, SNN_CHUNK, 0, 5, 0, nullptr) == SNN_OK);
+      CHECK(snn_debug_states(n.c, v.data()) == SNN_OK);
+      if (noalloc) CHECK(snn_forward_noalloc(n.c, (uint8_t *)x, (int32_t *)y, n.cfg.T, nullptr) == SNN_OK);
+    }
+  };
+  std::thread ta(work, std::ref(a), true), tb(work, std::ref(b), false);
+  ta.join();
+  tb.join();
+  CHECK(overlaps == 0);
+  alone = false; // the wide pass goes on until the narrow one has run
+  std::thread tw([&] { CHECK(a.forward() == SNN_OK); });
+  while (inside == 0) std::this_thread::yield();
+  const auto t0 = std::chrono::steady_clock::now();
+  CHECK(narrow.forward() == SNN_OK);
+  CHECK(std::chrono::steady_clock::now() - t0 < std::chrono::seconds(1));
+  tw.join();
+  g_forward = nullptr;
+}
+
 int main(int argc, char **argv) {
   setenv("SNN_GRAPH", "0", 1);
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
-                                              {"time_out_is_reported", time_out_is_reported}};
+                                              {"time_out_is_reported", time_out_is_reported},
+                                              {"turns", turns}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

@@ -567,6 +567,43 @@ def test_sequential_forward_with_the_weights_in_lds(hidden, B, T, gain, tier, mo
         _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
 
+def test_two_contexts_from_two_threads():
+    """Evaluation and training of two contexts on one GPU at the same time, both with kernels whose workgroups wait for each
+    other and fill the chip: every call succeeds, every result is the one of the context alone."""
+    import threading
+    nets, want = [], []
+    try:
+        for hidden, B in (((512, 512), 64), ((1024,), 64)):
+            w = synth.Workload("threads_" + "x".join(map(str, hidden)), 60, hidden, 6, T=70, B=B, p_in=0.1, gain=0.6, seed=191)
+            d = synth.generate(w)
+            net = snn.from_workload(w, d)
+            nets.append((net, d, len(hidden)))
+            loss = net.snn_forward(d["in_spikes"], d["labels"], w.T)
+            net.snn_bptt(snn.SNN_CHUNK, 0, 20, want_stats=False)
+            want.append((loss, _gpu_grads(net, len(hidden))))
+        bad = []
+
+        def work(k):
+            net, d, L = nets[k]
+            try:
+                for _ in range(8):
+                    loss = net.snn_forward(d["in_spikes"], d["labels"], 70)
+                    net.snn_bptt(snn.SNN_CHUNK, 0, 20, want_stats=False)
+                    if loss != want[k][0] or not _identical(_gpu_grads(net, L), want[k][1]):
+                        bad.append((k, "results differ"))
+            except Exception as e:  # noqa: BLE001 -- reported by the assertion below
+                bad.append((k, str(e)))
+        threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not bad, bad
+    finally:
+        for net, _, _ in nets:
+            net.snn_destroy()
+
+
 @pytest.mark.parametrize("hidden,B,T,force", [((2048, 2048), 3, 80, "0"), ((3072,), 3, 70, "0"), ((4096, 4096), 2, 20, "0"),
                                               ((512, 512), 5, 150, "8"), ((384,), 4, 100, "2")])
 def test_sliced_sequential_forward_is_bitwise_neutral(hidden, B, T, force, monkeypatch):

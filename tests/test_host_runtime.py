@@ -32,3 +32,7 @@ def test_a_failed_call_never_binds_parts_of_two_batches(checks, name):
 
 def test_every_entry_point_reports_a_kernel_that_gave_up_waiting(checks):
     checks("time_out_is_reported")
+
+
+def test_contexts_whose_kernels_wait_between_workgroups_take_turns(checks):
+    checks("turns")
