@@ -145,11 +145,14 @@ struct Turn {
   ~Turn() { if (held.owns_lock()) (void)hipStreamSynchronize(c->stream); } // also where a call ends early
 };
 
+// What contexts share, whatever thread makes or destroys them: the pool below and g_scratch_dev.
+std::mutex g_shared;
 // Pool of uncached device blocks (never returned to the driver before the process ends).
 struct UncachedBlock { int device; size_t bytes; void *ptr; bool busy; };
 std::vector<UncachedBlock> &uncached_pool() { static std::vector<UncachedBlock> pool; return pool; }
 void *uncached_block(int device, size_t bytes) {
   bytes = (bytes + 320 + 4095) & ~(size_t)4095;
+  std::lock_guard<std::mutex> hold(g_shared);
   for (auto &b : uncached_pool())
     if (!b.busy && b.device == device && b.bytes >= bytes) { b.busy = true; return b.ptr; }
   void *p = nullptr;
@@ -158,6 +161,7 @@ void *uncached_block(int device, size_t bytes) {
   return p;
 }
 void uncached_release(int device, void *ptr) {
+  std::lock_guard<std::mutex> hold(g_shared);
   for (auto &b : uncached_pool())
     if (b.device == device && b.ptr == ptr) b.busy = false;
 }
@@ -453,10 +457,13 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
     c->own_stream = true;
   }
   HIPCHK(c, hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
-  if (cfg->device < SNN_MAX_DEVICES && !g_scratch_dev[cfg->device]) {
-    void *p = nullptr;
-    HIPCHK(c, hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    g_scratch_dev[cfg->device] = p;
+  if (cfg->device < SNN_MAX_DEVICES) {
+    std::lock_guard<std::mutex> hold(g_shared);
+    if (!g_scratch_dev[cfg->device]) {
+      void *p = nullptr;
+      HIPCHK(c, hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
+      g_scratch_dev[cfg->device] = p;
+    }
   }
   NetDev &n = c->net;
   const int L = n.L, B = n.B, O = n.n_out;

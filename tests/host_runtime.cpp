@@ -285,11 +285,31 @@ static void turns() {
   g_forward = nullptr;
 }
 
+// Contexts that come and go on several threads: no uncached block belongs to two of them
+static void blocks() {
+  static std::mutex m;
+  static std::map<void *, int> owner;
+  std::vector<std::thread> ts;
+  for (int k = 0; k < 4; ++k)
+    ts.emplace_back([] {
+      for (int i = 0; i < 400; ++i) {
+        Net n(257, 1, 1);
+        std::unique_lock<std::mutex> hold(m);
+        CHECK(n.c->ws.bar && ++owner[n.c->ws.bar] == 1);
+        hold.unlock();
+        std::this_thread::yield();
+        hold.lock();
+        --owner[n.c->ws.bar];
+      }
+    });
+  for (auto &t : ts) t.join();
+}
+
 int main(int argc, char **argv) {
   setenv("SNN_GRAPH", "0", 1);
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
                                               {"time_out_is_reported", time_out_is_reported},
-                                              {"turns", turns}};
+                                              {"turns", turns}, {"blocks", blocks}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

@@ -9,16 +9,28 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2412_11810_amd", "csrc")
 
 
-@pytest.fixture(scope="module")
-def checks(tmp_path_factory):
-    exe = str(tmp_path_factory.mktemp("host_runtime") / "host_runtime")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-w", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-I", "/opt/rocm/include",
-                    os.path.join(ROOT, "tests", "host_runtime.cpp"), os.path.join(CSRC, "snn_schedule.cpp"), "-o", exe], check=True)
+def _build(folder, *flags):
+    exe = str(folder / "host_runtime")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-w", "-pthread", *flags, "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-I",
+                    "/opt/rocm/include", os.path.join(ROOT, "tests", "host_runtime.cpp"), os.path.join(CSRC, "snn_schedule.cpp"),
+                    "-o", exe], check=True)
 
     def run(name):
         got = subprocess.run([exe, name], capture_output=True, text=True, timeout=120)
-        assert got.returncode == 0, f"{name}: {got.stdout}{got.stderr}"
+        if "unexpected memory mapping" in got.stderr:
+            pytest.skip("the thread sanitizer cannot start on this kernel")
+        assert got.returncode == 0, f"{name}: {got.stdout}{got.stderr[:2000]}"
     return run
+
+
+@pytest.fixture(scope="module")
+def checks(tmp_path_factory):
+    return _build(tmp_path_factory.mktemp("host_runtime"))
+
+
+@pytest.fixture(scope="module")
+def thread_checks(tmp_path_factory):
+    return _build(tmp_path_factory.mktemp("host_runtime_threads"), "-fsanitize=thread")
 
 
 def test_inputs_still_being_written_on_the_callers_stream(checks):
@@ -34,5 +46,9 @@ def test_every_entry_point_reports_a_kernel_that_gave_up_waiting(checks):
     checks("time_out_is_reported")
 
 
-def test_contexts_whose_kernels_wait_between_workgroups_take_turns(checks):
-    checks("turns")
+def test_contexts_whose_kernels_wait_between_workgroups_take_turns(thread_checks):
+    thread_checks("turns")
+
+
+def test_contexts_of_several_threads_share_no_exchange_buffer(thread_checks):
+    thread_checks("blocks")
