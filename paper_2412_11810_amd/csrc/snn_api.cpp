@@ -104,6 +104,7 @@ struct snn_ctx {
   // chunks of several intervals: the least state storage the device had no room for (SNN_STATES_MAX), and what they may
   // take without a budget (an eighth of the device's memory: the rest is the caller's)
   size_t states_max = ~(size_t)0, states_unasked = 0;
+  bool lists_refused = false; // the device had no room for the lists of active neurons behind the workspace
   std::string err;
   size_t Ms() const { return (size_t)cfg.batch * net.SN * sizeof(float); }
 };
@@ -794,10 +795,11 @@ static snn_status ensure_work(snn_ctx *c, size_t bytes) {
 }
 
 // Workspace of `bytes`, and behind it space for the lists of active neurons where `lists` says that this call may use them (they are
-// not part of what snn_bytes_required counts: a budget has room, or there is none) and the device has room for them.
+// not part of what snn_bytes_required counts: a budget has room, or there is none) and the device has room for them: one allocation,
+// and a device without that room is not asked again at every call.
 static size_t lists_bytes(const NetDev &n) { return (currents_lists_entries(n) * sizeof(uint16_t) + 255) & ~(size_t)255; }
 static snn_status ensure_work_lists(snn_ctx *c, size_t bytes, bool lists) {
-  const size_t extra = lists ? lists_bytes(c->net) : 0, work = (bytes + 255) & ~(size_t)255;
+  const size_t extra = lists && !c->lists_refused ? lists_bytes(c->net) : 0, work = (bytes + 255) & ~(size_t)255;
   c->net.lists = nullptr;
   c->net.lists_cap = currents_lists_entries(c->net);
   if (extra) {
@@ -807,12 +809,13 @@ static snn_status ensure_work_lists(snn_ctx *c, size_t bytes, bool lists) {
     }
     (void)hipGetLastError();
     c->err.clear(); // the call goes without
+    c->lists_refused = true;
   }
   return ensure_work(c, bytes);
 }
 
 // State storage of a training step and its workspace, grown on demand.
-static snn_status ensure_states(snn_ctx *c, size_t states, size_t work) {
+static snn_status ensure_states(snn_ctx *c, size_t states, size_t work, bool lists) {
   if (c->arena_bytes < states) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (c->arena) HIPCHK(c, hipFree(c->arena));
@@ -825,7 +828,7 @@ static snn_status ensure_states(snn_ctx *c, size_t states, size_t work) {
     }
     c->arena_bytes = states;
   }
-  return ensure_work(c, work);
+  return ensure_work_lists(c, work, lists);
 }
 
 // The whole-sequence spike arrays in HBM, which the forward-only pass and the accessors work on.  A context with
@@ -2030,6 +2033,9 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   HIPCHK(c, hipSetDevice(c->cfg.device));
   hipStream_t s = c->stream;
   // ---- storage (before anything is queued or recorded) -----------------------------------------
+  // the lists of active neurons are part of the workspace where they are used, and only used where the budget has room
+  const size_t need_lists = lists_bytes(n);
+  auto room_for_lists = [&](size_t states, size_t work) { return !budget || states + work + need_spikes + need_lists <= budget; };
   // Chunks of several fine intervals where what is left of the budget holds them (Chunk, Double, Hierarchical): the
   // backward pass then walks longer chunks from every m-th checkpoint.  Short intervals make it a series of launches
   // that are too small for the chip (a chunk of 10 steps of three 1024-wide layers costs 10 launches of 5-140 us, most
@@ -2047,7 +2053,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
       const size_t states = (size_t)q.local_slots() * Ms, work = work_bytes(n, q.chunk_len);
       if (budget && (q.local_slots() < asked_slots || states + work + need_spikes > budget)) continue;
       if (states >= c->states_max || (!budget && states > c->states_unasked)) continue;
-      if (ensure_states(c, states, work) != SNN_OK) { // not tried again at every call
+      if (ensure_states(c, states, work, room_for_lists(states, work)) != SNN_OK) { // not tried again at every call
         (void)hipGetLastError();
         c->err.clear(); // the call goes on
         c->states_max = states;
@@ -2060,13 +2066,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   const size_t need_states = (size_t)p.local_slots() * Ms;
   const size_t need_work = work_bytes(n, p.chunk_len);
   {
-    snn_status rs = ensure_states(c, need_states, need_work);
-    if (rs != SNN_OK) return rs;
-  }
-  // the lists of active neurons are part of the workspace where they are used, and only used where the budget has room
-  const size_t need_lists = lists_bytes(n);
-  {
-    const snn_status rs = ensure_work_lists(c, need_work, !budget || need_states + need_work + need_spikes + need_lists <= budget);
+    const snn_status rs = ensure_states(c, need_states, need_work, room_for_lists(need_states, need_work));
     if (rs != SNN_OK) return rs;
   }
   const size_t need_host = (size_t)p.n_remote * Ms;

@@ -305,11 +305,45 @@ static void blocks() {
   for (auto &t : ts) t.join();
 }
 
+// A context's first training step allocates its state storage and its workspace, each once; where the device has no room for the
+// lists of active neurons behind the workspace, that is found out once
+static void workspace() {
+  {
+    Net n(512, 40, 4);
+    CHECK(n.bind() == SNN_OK);
+    const int before = g_mallocs;
+    CHECK(snn_bptt(n.c, SNN_CHUNK, 0, 5, 0, nullptr) == SNN_OK);
+    CHECK(n.c->net.lists && g_mallocs == before + 2);
+    CHECK(snn_bptt(n.c, SNN_CHUNK, 0, 5, 0, nullptr) == SNN_OK && n.forward() == SNN_OK);
+    CHECK(n.c->net.lists && g_mallocs == before + 2);
+  }
+  for (int entry = 0; entry < 2; ++entry) {
+    Net n(512, 40, 4);
+    CHECK(n.forward() == SNN_OK); // (a workspace that has to grow)
+    snn_stats st{};
+    const size_t least = snn_bytes_required(&n.cfg, SNN_STANDARD, 40, 0, 0);
+    CHECK(snn_bptt(n.c, SNN_STANDARD, 0, 0, least, &st) == SNN_OK);
+    CHECK(!n.c->net.lists && (size_t)(st.bytes_states + st.bytes_spikes + st.bytes_workspace) == least);
+  }
+  Net n(512, 40, 4);
+  CHECK(n.bind() == SNN_OK);
+  g_largest = LIST_ENTRIES * sizeof(uint16_t);
+  const int refused = g_refused;
+  CHECK(snn_bptt(n.c, SNN_CHUNK, 0, 5, 0, nullptr) == SNN_OK);
+  CHECK(!n.c->net.lists && g_refused == refused + 1);
+  const int before = g_mallocs;
+  CHECK(snn_bptt(n.c, SNN_CHUNK, 0, 5, 0, nullptr) == SNN_OK);
+  CHECK(snn_bptt(n.c, SNN_STANDARD, 0, 0, 0, nullptr) == SNN_OK);
+  CHECK(!n.c->net.lists && g_refused == refused + 1);
+  CHECK(g_mallocs <= before + 1); // (the state storage of the other strategy)
+  g_largest = ~(size_t)0;
+}
+
 int main(int argc, char **argv) {
   setenv("SNN_GRAPH", "0", 1);
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
                                               {"time_out_is_reported", time_out_is_reported},
-                                              {"turns", turns}, {"blocks", blocks}};
+                                              {"turns", turns}, {"blocks", blocks}, {"workspace", workspace}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

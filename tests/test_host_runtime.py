@@ -52,3 +52,7 @@ def test_contexts_whose_kernels_wait_between_workgroups_take_turns(thread_checks
 
 def test_contexts_of_several_threads_share_no_exchange_buffer(thread_checks):
     thread_checks("blocks")
+
+
+def test_workspace_is_allocated_once(checks):
+    checks("workspace")
