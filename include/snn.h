@@ -287,8 +287,10 @@ void snn_destroy(snn_ctx *ctx);
  *     SNN_NO_WS=1                no chip-wide kernels (no exchange buffer is allocated)
  *     SNN_WS_SPIN_LIMIT=n        polls before a chip-wide kernel gives up waiting (0: at once; the error path)
  *   read at the start of every call that launches kernels:
- *     SNN_CURRENTS=gather|mfma|dense   kernel of the synaptic currents (default for matrices below 32 MB in networks with a
- *                                      layer above 256 neurons: lists of active neurons, up to 16 % activity)
+ *     SNN_CURRENTS=gather|mfma|dense|lists
+ *                                      kernel of the synaptic currents (default for matrices below 32 MB: the matrix cores; in
+ *                                      networks with a layer above 256 neurons lists of active neurons where the shapes and the
+ *                                      activity of the last call make that the faster way / lists: wherever they can be walked)
  *     SNN_WS_KERNEL=valu|stream|rows|rows_all|chip|csrw|single|pair|rows64|uncached
  *                                      VALU version of the chip-wide adjoint recurrence / one workgroup per batch
  *                                      element streaming the transposed matrix / the event-driven rows kernel of

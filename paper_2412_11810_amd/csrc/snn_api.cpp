@@ -70,7 +70,7 @@ struct snn_ctx {
   size_t in_slot = 0; // bytes of a buffer
   hipEvent_t in_copied[3]{}, in_packed[3]{};
   int32_t *labels = nullptr;
-  unsigned char *host_small = nullptr; // pinned: 64 bytes (loss, error flag) + B labels, for calls that must not allocate
+  unsigned char *host_small = nullptr; // pinned: 64 bytes (loss, then error flag or spike counts) + B labels
   int T_bound = 0;
   int T_spikes = 0; // length of the sequence whose hidden spike trains are stored (0: none since the inputs were bound)
   double *readout = nullptr;
@@ -86,7 +86,7 @@ struct snn_ctx {
   float *host_ckpt = nullptr;
   size_t host_bytes = 0;
   std::vector<hipEvent_t> ev_pool;
-  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; void *lists; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache && lists == o.lists; } };
+  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; void *lists; float rate[SNN_MAXL + 1]; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache && lists == o.lists && std::equal(rate, rate + SNN_MAXL + 1, o.rate); } };
   GraphKeyT graph_key{};
   hipGraphExec_t graph_exec = nullptr;
   bool graphs_enabled = true;   // SNN_GRAPH=0 turns graph replay off
@@ -221,7 +221,7 @@ void read_kernel_hooks(snn_ctx *c) {
     n.csr_pk[l] = on ? c->csr_pk[l] : nullptr;
   }
   if (const char *e = std::getenv("SNN_CURRENTS"))
-    n.sel_currents = !std::strcmp(e, "gather") ? 1 : !std::strcmp(e, "mfma") ? 2 : !std::strcmp(e, "dense") ? 3 : 0;
+    n.sel_currents = !std::strcmp(e, "gather") ? 1 : !std::strcmp(e, "mfma") ? 2 : !std::strcmp(e, "dense") ? 3 : !std::strcmp(e, "lists") ? 4 : 0;
   if (const char *e = std::getenv("SNN_WS_KERNEL"))
     n.sel_adjoint = !std::strcmp(e, "valu") ? 1 : !std::strcmp(e, "stream") ? 2 : !std::strcmp(e, "rows") ? 3 :
                     !std::strcmp(e, "rows_all") ? 4 : !std::strcmp(e, "chip") ? 5 : !std::strcmp(e, "csrw") ? 6 : !std::strcmp(e, "single") ? 7 : !std::strcmp(e, "pair") ? 8 : !std::strcmp(e, "rows64") ? 9 : !std::strcmp(e, "uncached") ? 10 : 0;
@@ -424,6 +424,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
   if (!valid_cfg(cfg, &why)) return fail(c, SNN_E_INVAL, why);
   c->cfg = *cfg;
   fill_shape(*cfg, &c->net);
+  for (float &r : c->net.rate) r = -1.0f; // not known yet
   if (const char *e = std::getenv("SNN_DW")) c->dw_event_driven = std::strcmp(e, "event") == 0;
   if (const char *e = std::getenv("SNN_HOST_TIER")) {
     if (std::strcmp(e, "dma") == 0) c->host_direct_max = 0;
@@ -508,7 +509,8 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
   HIPCHK(c, hipMalloc(&c->readout, (size_t)B * 2 * O * 8));
   HIPCHK(c, hipMalloc(&c->ubar, (size_t)B * O * 4));
   HIPCHK(c, hipMalloc(&c->g, (size_t)B * O * 4));
-  HIPCHK(c, hipMalloc(&c->loss_dev, 16));
+  HIPCHK(c, hipMalloc(&c->loss_dev, 16 + 8 * (SNN_MAXL + 1)));
+  c->counters = reinterpret_cast<unsigned long long *>(c->loss_dev + 4); // one copy takes the loss and the counts to the host
   HIPCHK(c, hipMalloc(&c->carry, (size_t)B * (n.SN + O) * 4));
   size_t xl_bytes = 0; // exchange inside a die: shares an allocation with cur_state
   {
@@ -547,7 +549,6 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       adjoint_prepare(n, c->ws);
     }
   }
-  HIPCHK(c, hipMalloc(&c->counters, 8 * (SNN_MAXL + 1)));
   for (int l = 0; l < L; ++l) {
     const size_t pmax = (size_t)std::max(l == 0 ? n.n_in : n.N[l - 1], n.N[l]);
     if (pmax * n.N[l] * sizeof(float) >= ((size_t)32 << 20)) c->rate_driven = true;
@@ -589,7 +590,6 @@ void snn_destroy(snn_ctx *c) {
   (void)hipFree(c->labels); (void)hipFree(c->readout); (void)hipFree(c->ubar); (void)hipFree(c->g);
   (void)hipFree(c->loss_dev); (void)hipFree(c->carry); (void)hipFree(c->cur_state);
   if (c->ws.bar) uncached_release(c->cfg.device, c->ws.bar);
-  (void)hipFree(c->counters);
   (void)hipFree(c->arena); (void)hipFree(c->dubuf);
   if (c->host_ckpt) (void)hipHostFree(c->host_ckpt);
   (void)hipFree(c->in_stage);
@@ -854,6 +854,25 @@ static snn_status ensure_full_masks(snn_ctx *c) {
   return SNN_OK;
 }
 
+// Spikes of steps 1..T of the inputs and of hidden layers 1..layers, added to the counters.
+static hipError_t queue_spike_counts(snn_ctx *c, int T, int layers) {
+  const NetDev &n = c->net;
+  CountJobs jobs{};
+  for (int l = 0; l <= layers; ++l)
+    jobs.j[jobs.count++] = CountJob{c->mask_full[l] + (size_t)n.B * n.Wd[l], (size_t)T * n.B * n.Wd[l], c->counters + l};
+  return launch_count_spikes(jobs, c->stream);
+}
+// Activities from the counts into r, and into what the choice of kernels for the currents goes by.  A recorded step holds that
+// choice: a rate stays while the new one is within a quarter of it, so that a step is not recorded again at every call.
+static void set_rates(snn_ctx *c, const unsigned long long *cnt, int T, double *r) {
+  NetDev &n = c->net;
+  for (int l = 0; l <= n.L; ++l) {
+    r[l] = (double)cnt[l] / ((double)T * n.B * (l == 0 ? n.n_in : n.N[l - 1]));
+    const double now = std::max(r[l], 0.01), old = n.rate[l];
+    if (old < 0.0 || std::fabs(now - old) > 0.25 * std::max(now, old)) n.rate[l] = (float)now;
+  }
+}
+
 static snn_status forward_only(snn_ctx *c, float *traj_or_null, float *work_or_null = nullptr, const FwdCallbacks *cb = nullptr) {
   read_kernel_hooks(c);
   c->spikes_on_host = false; // this pass rewrites the hidden spike trains, in HBM
@@ -874,7 +893,10 @@ static snn_status forward_only(snn_ctx *c, float *traj_or_null, float *work_or_n
     if (rs != SNN_OK) return rs;
     work = c->dubuf;
   }
-  HIPCHK(c, launch_fill_zero(c->cur_state, c->Ms(), c->stream));
+  ZeroJobs clear{};
+  clear.add(c->cur_state, c->Ms());
+  clear.add(c->counters, 8 * (SNN_MAXL + 1));
+  HIPCHK(c, launch_fill_zero_jobs(clear, c->stream));
   std::vector<int> bounds = tile_bounds(n, 0, c->T_bound, c->T_bound);
   HIPCHK(c, launch_forward(n, bounds.data(), (int)bounds.size() - 1, c->cur_state, st, c->readout, 1, work, c->stream, nullptr, cb, &c->ws));
   HIPCHK(c, launch_loss(c->readout, c->labels, n.B, n.n_out, c->T_bound, c->ubar, c->g, c->loss_dev, c->stream));
@@ -911,10 +933,15 @@ snn_status snn_forward(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labe
     s = forward_only(c, nullptr);
     if (s != SNN_OK) return s;
   }
-  float loss = 0.f;
-  HIPCHK(c, hipMemcpyAsync(&loss, c->loss_dev, 4, hipMemcpyDeviceToHost, c->stream));
+  // (with the counts that the next call chooses its kernels by, where lists of active neurons may be walked)
+  if (c->net.lists) HIPCHK(c, queue_spike_counts(c, T, c->net.L));
+  HIPCHK(c, hipMemcpyAsync(c->host_small, c->loss_dev, 16 + 8 * (SNN_MAXL + 1), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (loss_out) *loss_out = loss;
+  if (loss_out) std::memcpy(loss_out, c->host_small, sizeof *loss_out);
+  if (c->net.lists) {
+    double r[SNN_MAXL + 1];
+    set_rates(c, reinterpret_cast<const unsigned long long *>(c->host_small + 16), T, r);
+  }
   return check_ws_error(c); // the sliced sequential kernels of wide layers wait for each other, with a bound
 }
 
@@ -1174,22 +1201,18 @@ struct Timer {
 // presynaptic spike, the dense matrix-core version per presynaptic neuron; measured break-even about 3.5 %.
 // (weight gradients of 1024-wide layers, batch 64: tiled kernel 17 / 33 ms at 4.6 / 12 % activity, dense contraction 25.5)
 static constexpr double DW_TILE_MAX_ACTIVITY = 0.08;
-// (currents by lists, 512 -> 512 at batch 16: 33 us per launch at 47 %, matrix-core version 23 at any rate from 15 % on; lists cost
-// about 17 us + 35 us x rate)
-static constexpr double LISTS_MAX_ACTIVITY = 0.16;
 static snn_status update_current_policy(snn_ctx *c, int T, float *rates_out, bool hidden_counted) {
   const NetDev &n = c->net;
-  const int L = n.L, B = n.B;
+  const int L = n.L;
   hipStream_t s = c->stream;
   // with the spike bitmasks on the host tier the step itself counted the hidden layers' spikes, segment by segment
   if (!hidden_counted) HIPCHK(c, launch_fill_zero(c->counters, 8 * (SNN_MAXL + 1), s));
-  for (int l = 0; l <= (hidden_counted ? 0 : L); ++l)
-    HIPCHK(c, launch_count_spikes(c->mask_full[l] + (size_t)B * n.Wd[l], (size_t)T * B * n.Wd[l], c->counters + l, s));
+  HIPCHK(c, queue_spike_counts(c, T, hidden_counted ? 0 : L));
   HIPCHK(c, hipStreamSynchronize(s));
   unsigned long long cnt[SNN_MAXL + 1];
   HIPCHK(c, hipMemcpy(cnt, c->counters, sizeof cnt, hipMemcpyDeviceToHost));
   double r[SNN_MAXL + 1];
-  for (int l = 0; l <= L; ++l) r[l] = (double)cnt[l] / ((double)T * B * (l == 0 ? n.n_in : n.N[l - 1]));
+  set_rates(c, cnt, T, r);
   if (rates_out)
     for (int l = 0; l < L; ++l) rates_out[l] = (float)r[l + 1];
   // presynaptic activity averaged over the weight rows of all layers
@@ -1201,7 +1224,6 @@ static snn_status update_current_policy(snn_ctx *c, int T, float *rates_out, boo
   }
   // weight gradients: measured break-even of the tiled event-driven kernel and the dense contraction
   if (c->dw_rate_driven) c->dw_tile = ev_re < DW_TILE_MAX_ACTIVITY * rows_re;
-  c->net.lists_off = ev_re < LISTS_MAX_ACTIVITY * rows_re ? 0 : 1;
   if (c->rate_driven) {
     // one choice for the whole network (jobs of one launch then stay in one launch)
     for (int l = 0; l < L; ++l) {
@@ -1279,7 +1301,7 @@ struct SpikeOff {
       const size_t rw = (size_t)n.B * n.Wd[l];
       for (int a = r0; a <= r1;) {
         const int pos = a % R, len = std::min(r1 - a + 1, R - pos);
-        const hipError_t e = launch_count_spikes(c->mask_ring[l] + (size_t)pos * rw, (size_t)len * rw, c->counters + l, s);
+        const hipError_t e = launch_count_spikes(CountJobs{{{c->mask_ring[l] + (size_t)pos * rw, (size_t)len * rw, c->counters + l}}, 1}, s);
         if (e != hipSuccess) return e;
         a += len;
       }
@@ -2130,10 +2152,11 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   if (use_graph) {
     unsigned long long pol = 0;
     for (int l = 0; l < L; ++l) pol = pol * 64 + c->net.cur_pol[0][l] * 16 + c->net.cur_pol[1][l] * 2 + c->net.seq_pol[l];
-    pol = (pol * 2 + (c->dw_tile ? 1u : 0u)) * 2 + n.lists_off;
+    pol = pol * 2 + (c->dw_tile ? 1u : 0u);
     const unsigned sel = (unsigned)n.sel_currents | (unsigned)n.sel_adjoint << 8 | (unsigned)n.sel_slices << 16 | (unsigned)n.sel_csr << 24 | (unsigned)n.sel_seq << 28 | (unsigned)n.no_fwd_fuse << 30;
     snn_ctx::GraphKeyT key{(int)strategy, T, p.C, p.F, p.n_chunk_bufs, c->arena, c->dubuf, c->host_ckpt, c->dw_event_driven, pol, sel,
-                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists};
+                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists, {}};
+    if (n.lists) std::copy(n.rate, n.rate + SNN_MAXL + 1, key.rate);
     if (!c->graph_exec || !(key == c->graph_key)) {
       if (c->graph_exec) { (void)hipGraphExecDestroy(c->graph_exec); c->graph_exec = nullptr; }
       Timer tm{c, false};
@@ -2151,7 +2174,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
     }
     Turn turn(c);
     HIPCHK(c, hipGraphLaunch(c->graph_exec, s));
-    if (c->rate_driven || c->dw_rate_driven) {
+    if (c->rate_driven || c->dw_rate_driven || n.lists) {
       snn_status rr = update_current_policy(c, T, nullptr, ring > 0);
       if (rr != SNN_OK) return rr;
     }
@@ -2168,7 +2191,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   snn_status rs = enqueue_step(c, p, st, tm, &ev_fwd);
   if (rs != SNN_OK) { (void)hipStreamSynchronize(c->copy_stream); (void)hipStreamSynchronize(s); return rs; }
   hipEvent_t ev_end = tm.mark();
-  if (stats || c->rate_driven || c->dw_rate_driven) {
+  if (stats || c->rate_driven || c->dw_rate_driven || n.lists) {
     snn_status rr = update_current_policy(c, T, st.firing_rate, ring > 0);
     if (rr != SNN_OK) return rr;
   }

@@ -53,7 +53,8 @@ struct NetDev {
   // (feed-forward part only), [1] recompute (both parts).  Every choice gives the same bits.
   unsigned char cur_pol[2][SNN_MAXL];
   // Kernel selection forced from outside (test hooks; 0 = the library's own choice).  Every choice gives the same
-  // bits.  sel_currents: 1 event-by-event gather, 2 list version on the matrix cores, 3 dense version.
+  // bits.  sel_currents: 1 event-by-event gather, 2 list version on the matrix cores, 3 dense version, 4 the library's choice
+  // but lists of active neurons (k_currents_lists) wherever they can be walked.
   // sel_adjoint: 1 VALU version of the chip-wide recurrence, 2 one-workgroup-per-batch-element streaming kernel,
   // 3 event-driven rows (neurons inside the surrogate window only), 4 the same kernel evaluating every row, 5 the
   // chip-wide kernels over the dense-stored matrix, also under a surrogate window, 6 the chip-wide kernel over
@@ -70,7 +71,9 @@ struct NetDev {
   // Space for the lists of active neurons that k_currents_lists walks (NULL: the matrix-core kernels instead), in entries
   uint16_t *lists;
   size_t lists_cap;
-  unsigned char lists_off; // 1: the measured firing rates are above what the walk pays for (see LISTS_MAX_ACTIVITY)
+  // Activity of layer index l (0: inputs) that the choice between lists and matrix cores goes by: the last measured one, or one
+  // near it (see set_rates); < 0: not known yet
+  float rate[SNN_MAXL + 1];
   unsigned char sel_csr; // compressed rows of masked recurrent matrices: 1 never used (dense-stored walk everywhere),
                          // 2 used wherever a kernel for them exists, 0 the library's choice
 };
@@ -263,7 +266,12 @@ hipError_t launch_finish_grad_csr(const double *acc, const uint32_t *csr_sub, co
                                   hipStream_t s);
 hipError_t launch_unpack_spikes(const uint64_t *mask, int words, int N, int T, int B, uint8_t *dst,
                                 hipStream_t s);
-hipError_t launch_count_spikes(const uint64_t *mask, size_t n_words, unsigned long long *count, hipStream_t s);
+struct CountJob { const uint64_t *mask; size_t n_words; unsigned long long *count; };
+struct CountJobs {
+  CountJob j[SNN_MAXL + 1];
+  int count;
+};
+hipError_t launch_count_spikes(const CountJobs &jobs, hipStream_t s); // adds the set bits of every job to its count
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 struct ZeroJob { void *p; size_t bytes; unsigned first; }; // first: set by the launcher
 struct ZeroJobs {

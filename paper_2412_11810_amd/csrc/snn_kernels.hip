@@ -1339,7 +1339,7 @@ k_currents(NetDev net, CurJobs jobs) {
 // rows (56 % of them at 5 % activity) and multiplies the other fifteen rows by zero.  Sums ascending from 0.0f: the same bits.
 // Bound by the LDS rate (4 rows of 64 bytes per 256-byte access meet the same banks now and then at LPT = 4).
 // 512-2x2048 at 5 %, batch 16, T = 2000: 11.5 -> 5.9 ms of currents per training step, 700-3x1024, batch 64, T = 500: 1.24 -> 0.77
-// per forward pass.  Above 16 % activity the matrix cores are faster (LISTS_MAX_ACTIVITY).
+// per forward pass.  At high activity, and for small launches, the matrix cores are faster (lists_pay).
 // ------------------------------------------------------------------------------------------
 struct ListJob { const uint64_t *mask; int words, ring, t_first, rows, P, lc; uint16_t *lists; }; // rows = steps x B, from step t_first on
 struct ListJobs { ListJob j[SNN_MAXL + 1]; int count; };
@@ -4346,12 +4346,19 @@ __global__ void k_unpack(const uint64_t *__restrict__ mask, int words, int N, si
   dst[i] = (uint8_t)((w >> (n & 63)) & 1ull);
 }
 
-__global__ void k_count(const uint64_t *__restrict__ mask, size_t n_words, unsigned long long *count) {
-  unsigned long long c = 0;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_words; i += (size_t)gridDim.x * blockDim.x)
-    c += __popcll(mask[i]);
+__global__ void __launch_bounds__(256) k_count(CountJobs jobs) { // blockIdx.y: job; one addition per workgroup
+  const uint64_t *__restrict__ mask = jobs.j[blockIdx.y].mask;
+  const size_t n_words = jobs.j[blockIdx.y].n_words;
+  __shared__ unsigned part[4];
+  unsigned c = 0;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_words; i += (size_t)gridDim.x * 256) c += (unsigned)__popcll(mask[i]);
   for (int s = 32; s > 0; s >>= 1) c += __shfl_down(c, s);
-  if (lane_id() == 0 && c) atomicAdd(count, c); // integer atomic: order-independent
+  if (lane_id() == 0) part[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long sum = (unsigned long long)part[0] + part[1] + part[2] + part[3];
+    if (sum) atomicAdd(jobs.j[blockIdx.y].count, sum); // integer atomic: order-independent
+  }
 }
 
 // plain streaming copy of known size (reference for scaling hardware byte counters)
@@ -4540,12 +4547,6 @@ static hipError_t launch_currents(const NetDev &net, const CurJobs &jobs, hipStr
 }
 // Entries per list: the number of groups, as many groups as a layer of P neurons can fill, one group of P alone.
 static int list_entries(int P) { return 8 + ((P + 7) & ~7) + 8; }
-static size_t list_lds(int P, int lpt) { return (size_t)(P + 1) * 4 * lpt * sizeof(float); }
-static int list_lanes(int P) { // the widest slice that fits the LDS
-  for (int lpt = 16; lpt >= 1; lpt /= 2)
-    if (list_lds(P, lpt) + 512 <= SNN_LDS_PER_CU) return lpt;
-  return 0;
-}
 static bool lists_ok(const NetDev &net) { // networks with a layer above 256 neurons and a matrix that fits the L2
   int nmax = 0;
   bool any = false;
@@ -4603,10 +4604,25 @@ static hipError_t launch_lists_walk(const NetDev &net, LstJobs jobs, hipStream_t
   }
   return hipSuccess;
 }
+// Is walking lists the faster way for these jobs (see currents_by_lists)?  Before a rate is known 16 % is assumed, between the 5
+// and 45 % that networks fire at here: the wrong side then costs least.
+static bool lists_pay(const NetDev &net, const CurJobs &jobs, int most) {
+  ListsCost in[SNN_MAXL + 1], rec[SNN_MAXL + 1];
+  int n_in = 0, n_rec = 0;
+  auto rate = [&](int li) { return net.rate[li] < 0.0f ? 0.16 : (double)net.rate[li]; };
+  for (int i = 0; i < jobs.count; ++i) {
+    const CurJob &j = jobs.j[i];
+    const int l = j.lsel, N = j.mode == 2 ? net.n_out : net.N[l];
+    const long long rows = (long long)std::min(j.nsteps, SNN_LIST_STEPS) * net.B;
+    in[n_in++] = ListsCost{l == 0 ? net.n_in : net.N[l - 1], N, rows, rate(l)};
+    if (j.mode == 0) rec[n_rec++] = ListsCost{N, N, rows, rate(l + 1)};
+  }
+  return currents_by_lists(in, n_in, rec, n_rec, (most + SNN_LIST_STEPS - 1) / SNN_LIST_STEPS);
+}
 // Currents by walking lists (a readout job's lsel is the layer index of the spikes it reads, L), SNN_LIST_STEPS steps at a time: the lists of every layer that the jobs
 // read, then the feed-forward parts of all jobs, then the recurrent parts (mode 0), added to them.
 static hipError_t launch_currents_lists(const NetDev &net, CurJobs *jobs, hipStream_t s) {
-  if (!net.lists || net.lists_off || net.sel_currents != 0 || !lists_ok(net)) return hipSuccess;
+  if (!net.lists || (net.sel_currents != 4 && net.sel_currents != 0) || !lists_ok(net)) return hipSuccess;
   CurJobs mine{}, rest{};
   for (int i = 0; i < jobs->count; ++i) {
     const CurJob &j = jobs->j[i];
@@ -4616,6 +4632,7 @@ static hipError_t launch_currents_lists(const NetDev &net, CurJobs *jobs, hipStr
   }
   int most = 0;
   for (int i = 0; i < mine.count; ++i) most = std::max(most, mine.j[i].nsteps);
+  if (net.sel_currents == 0 && !lists_pay(net, mine, most)) return hipSuccess;
   const int B = net.B;
   for (int a = 0; a < most; a += SNN_LIST_STEPS) {
     ListJobs lj{};
@@ -5969,8 +5986,11 @@ hipError_t launch_unpack_spikes(const uint64_t *mask, int words, int N, int T, i
   return hipGetLastError();
 }
 
-hipError_t launch_count_spikes(const uint64_t *mask, size_t n_words, unsigned long long *count, hipStream_t s) {
-  hipLaunchKernelGGL(k_count, dim3(512), dim3(256), 0, s, mask, n_words, count);
+hipError_t launch_count_spikes(const CountJobs &jobs, hipStream_t s) {
+  size_t most = 0;
+  for (int k = 0; k < jobs.count; ++k) most = std::max(most, jobs.j[k].n_words);
+  const unsigned blocks = (unsigned)std::min<size_t>(512, (most + 256 * 8 - 1) / (256 * 8)); // eight words per thread, or more
+  hipLaunchKernelGGL(k_count, dim3(blocks ? blocks : 1, jobs.count), dim3(256), 0, s, jobs);
   return hipGetLastError();
 }
 

@@ -39,3 +39,61 @@ inline bool seq_lds_geometry(int N, int B, int jobs, int slots, int posts, SeqLd
 constexpr uint32_t BUFFER_OUTSIDE = 0x80000000u;
 constexpr uint32_t seq_rs_lane_offset(int N, int i) { return i < N ? (uint32_t)i * 4u : BUFFER_OUTSIDE; }
 constexpr uint32_t seq_rs_row_offset(int N, int NW, int q) { return (uint32_t)((q <= NW - 32 || q < N ? q : N - 1) * N) * 4u; }
+
+// ---- currents by lists of active neurons or on the matrix cores (k_currents_lists, k_currents_mfma) ------------------
+// lanes per row of k_currents_lists (four columns each): the widest slice of columns that fits the LDS for P presynaptic neurons
+constexpr size_t list_lds(int P, int lpt) { return (size_t)(P + 1) * 4 * lpt * sizeof(float); }
+constexpr int list_lanes(int P) {
+  for (int lpt = 16; lpt >= 1; lpt /= 2)
+    if (list_lds(P, lpt) + 512 <= SNN_LDS_PER_CU) return lpt;
+  return 0;
+}
+// One matrix of a launch: presynaptic neurons, columns, (t, b) rows, activity of the presynaptic layer.
+struct ListsCost { int P, N; long long rows; double rate; };
+// Estimated times of a launch over these matrices, in us.  Matrix cores: every presynaptic neuron that is active in any of 16 rows
+// takes part for all of them (29 ns per neuron, 16 rows and 64 columns on each of 1024 SIMDs), a workgroup's chain of them is
+// the least.  Lists: a workgroup per compute unit passes over its rows, 61 ns per active neuron and full pass (the LDS rate; 2 and
+// 2.6 times that for slices of eight and four columns, whose rows meet the same banks) and 3.5 us to begin with.
+inline void currents_mfma_us(const ListsCost *m, int n, int slices, double *work, double *chain) {
+  for (int i = 0; i < n; ++i) {
+    double silent = 1.0 - m[i].rate; // no spike in 16 rows
+    for (int k = 0; k < 4; ++k) silent *= silent;
+    const double some = 1.0 - silent, c = m[i].P * (0.36 + 0.64 * some) * 0.032;
+    *work += (double)m[i].rows * slices * m[i].N * m[i].P * (1.0 + 1.8 * some) * 1e-8;
+    *chain = c > *chain ? c : *chain;
+  }
+}
+inline double currents_lists_walk_us(const ListsCost *m, int n) { // one launch per width of slice
+  double us = 0.0;
+  for (int lpt = 16; lpt >= 1; lpt /= 2) {
+    const long long per_pass = 16 * 64 / lpt;
+    long long units = 0, groups = 0;
+    for (int i = 0; i < n; ++i)
+      if (list_lanes(m[i].P) == lpt) units += (m[i].N + 4 * lpt - 1) / (4 * lpt);
+    if (!units) continue;
+    double longest = 0.0;
+    for (int i = 0; i < n; ++i)
+      if (list_lanes(m[i].P) == lpt) {
+        const long long passes = (m[i].rows + per_pass - 1) / per_pass, most = 256 / units;
+        const long long splits = most < 1 ? 1 : passes < most ? passes : most;
+        groups += (m[i].N + 4 * lpt - 1) / (4 * lpt) * splits;
+        const double lds = lpt == 1 ? 2.6 : lpt == 2 ? 2.0 : 1.0, full = (double)m[i].rows / (double)(passes * per_pass);
+        const double t = (double)((passes + splits - 1) / splits) * (0.061 * m[i].P * m[i].rate * lds * full + 3.5);
+        longest = t > longest ? t : longest;
+      }
+    us += 5.0 + longest * (double)((groups + 255) / 256);
+  }
+  return us;
+}
+// Are lists the faster way for a launch over `in` (the feed-forward parts) and `rec` (the recurrent parts of a recompute), `slices`
+// times those rows?  They have to be a tenth better: over 152 measured launches (one and two layers of 300..2800 neurons, batch
+// 16 to 64, 4..48 % activity) the choice then costs at most 4 % against the better of the two.  One bound on the activity cannot do that:
+// the two meet at 38 % for 2048 neurons, 20 % for 1500, 8 % for 2800, and below 4 % where a launch is too small to pay for its
+// lists (512 neurons at batch 16: 27 us against 54).
+inline bool currents_by_lists(const ListsCost *in, int n_in, const ListsCost *rec, int n_rec, int slices) {
+  const double lists = slices * (5.0 + currents_lists_walk_us(in, n_in) + currents_lists_walk_us(rec, n_rec));
+  double work = 0.0, chain = 0.0; // one launch for both
+  currents_mfma_us(in, n_in, slices, &work, &chain);
+  currents_mfma_us(rec, n_rec, slices, &work, &chain);
+  return 1.1 * lists < 10.0 + (work > chain ? work : chain);
+}

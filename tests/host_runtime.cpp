@@ -113,12 +113,18 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
   if (g_forward) put(s, [=] { g_forward(*n, ws); });
   return hipSuccess;
 }
-hipError_t launch_count_spikes(const uint64_t *, size_t n_words, unsigned long long *count, hipStream_t s) {
-  put(s, [=] { *count += (unsigned long long)(g_rate * 64.0 * (double)n_words); });
+hipError_t launch_count_spikes(const CountJobs &jobs, hipStream_t s) {
+  for (int k = 0; k < jobs.count; ++k) {
+    const CountJob j = jobs.j[k];
+    put(s, [=] { *j.count += (unsigned long long)(g_rate * 64.0 * (double)j.n_words); });
+  }
   return hipSuccess;
 }
 hipError_t launch_fill_zero(void *p, size_t n, hipStream_t s) { put(s, [=] { std::memset(p, 0, n); }); return hipSuccess; }
-hipError_t launch_fill_zero_jobs(ZeroJobs, hipStream_t) { return hipSuccess; }
+hipError_t launch_fill_zero_jobs(ZeroJobs jobs, hipStream_t s) {
+  for (int k = 0; k < jobs.count; ++k) launch_fill_zero(jobs.j[k].p, jobs.j[k].bytes, s);
+  return hipSuccess;
+}
 hipError_t launch_recompute(const NetDev &, int, int, const float *, float *, int, size_t, int, float *, hipStream_t) { return hipSuccess; }
 hipError_t launch_recompute_currents(const NetDev &, int, int, float *, int, size_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_recompute_scan(const NetDev &, int, int, const float *, float *, int, size_t, int, float *, hipStream_t, const float *,
@@ -339,11 +345,37 @@ static void workspace() {
   g_largest = ~(size_t)0;
 }
 
+// The activity that the kernels of the currents are chosen by is that of the last call, whatever the call and the batch size, and
+// stays while the new one is near it (a recorded step holds the choice)
+static void rates() {
+  for (int B : {4, 80})
+    for (int entry = 0; entry < 3; ++entry) {
+      Net n(512, 20, B);
+      const auto call = [&] {
+        if (entry == 0) return n.forward();
+        CHECK(n.bind() == SNN_OK);
+        snn_stats st{};
+        return snn_bptt(n.c, SNN_CHUNK, 0, 5, 0, entry == 1 ? nullptr : &st);
+      };
+      const auto known = [&](double r) { return std::fabs(n.c->net.rate[0] - r) < 1e-3 && std::fabs(n.c->net.rate[1] - r) < 1e-3; };
+      CHECK(n.c->net.rate[0] < 0.0f && n.c->net.rate[1] < 0.0f);
+      g_rate = 0.45;
+      CHECK(call() == SNN_OK && n.c->net.lists && known(0.45));
+      g_rate = 0.40; // within a quarter
+      CHECK(call() == SNN_OK && known(0.45));
+      g_rate = 0.05;
+      CHECK(call() == SNN_OK && known(0.05));
+      g_rate = 0.0;
+      CHECK(call() == SNN_OK && known(0.01));
+    }
+}
+
 int main(int argc, char **argv) {
   setenv("SNN_GRAPH", "0", 1);
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
                                               {"time_out_is_reported", time_out_is_reported},
-                                              {"turns", turns}, {"blocks", blocks}, {"workspace", workspace}};
+                                              {"turns", turns}, {"blocks", blocks}, {"workspace", workspace},
+                                              {"rates", rates}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

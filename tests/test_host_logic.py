@@ -253,3 +253,56 @@ int main() {
     subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)], check=True)
     got = subprocess.run([str(exe)], capture_output=True, text=True)
     assert got.returncode == 0, got.stdout
+
+
+# Recompute currents of 192 steps, measured: inputs (5 % active), layers, batch, activity of the layers, us on the matrix cores, us by lists
+MEASURED_CURRENTS = [
+    (64, (300,), 16, (0.037,), 17, 49),
+    (64, (512,), 16, (0.037,), 27, 54),
+    (64, (1024,), 16, (0.452,), 116, 152),
+    (64, (1500,), 16, (0.046,), 150, 134),
+    (64, (2048,), 16, (0.043,), 290, 152),
+    (64, (2048,), 16, (0.457,), 443, 478),
+    (64, (2800,), 16, (0.044,), 539, 452),
+    (64, (300,), 64, (0.457,), 54, 113),
+    (64, (512,), 64, (0.037,), 76, 74),
+    (64, (512,), 64, (0.428,), 107, 140),
+    (64, (800,), 64, (0.051,), 168, 134),
+    (64, (800,), 64, (0.452,), 234, 367),
+    (64, (1024,), 64, (0.154,), 301, 230),
+    (64, (1024,), 64, (0.452,), 352, 452),
+    (64, (1500,), 64, (0.047,), 525, 323),
+    (64, (1500,), 64, (0.483,), 745, 1257),
+    (64, (2048,), 64, (0.245,), 1303, 985),
+    (64, (2550,), 64, (0.043,), 1572, 763),
+    (64, (2550,), 64, (0.447,), 2412, 3540),
+    (64, (2800,), 64, (0.161,), 2545, 3167),
+    (64, (2800,), 64, (0.451,), 3003, 7806),
+    (64, (1024, 2048), 16, (0.044, 0.046), 428, 261),
+    (64, (1024, 2048), 16, (0.451, 0.471), 675, 796),
+    (2000, (512,), 32, (0.041,), 208, 91),
+    (2000, (512,), 32, (0.435,), 204, 125),
+    (4000, (400,), 32, (0.048,), 591, 144),
+    (4000, (400,), 32, (0.467,), 585, 170),
+]
+
+
+def test_choice_between_lists_and_matrix_cores_follows_the_measured_times(tmp_path):
+    """The estimate that picks the kernel of a launch's currents costs at most 5 % against the better of the two at every measured
+    point, on both sides of where they meet."""
+    calls = []
+    for n_in, hidden, B, rate, _, _ in MEASURED_CURRENTS:
+        pre, r_in = (n_in,) + hidden[:-1], (0.05,) + rate[:-1]
+        mat = lambda P, r: "{" + ", ".join("{%d, %d, %d, %g}" % (p, n, 64 * B, q) for p, n, q in zip(P, hidden, r)) + "}"
+        calls.append("{ const ListsCost a[] = %s, b[] = %s; std::puts(currents_by_lists(a, %d, b, %d, 3) ? \"1\" : \"0\"); }"
+                     % (mat(pre, r_in), mat(hidden, rate), len(hidden), len(hidden)))
+    src = tmp_path / "choice.cpp"
+    src.write_text('#include <cstdio>\n#include "snn_plan.h"\nint main() {\n' + "\n".join(calls) + "\n}\n")
+    exe = tmp_path / "choice"
+    csrc = os.path.join(ROOT, "paper_2412_11810_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    picked = subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split()
+    assert len(picked) == len(MEASURED_CURRENTS) and {"0", "1"} == set(picked)
+    for choice, (n_in, hidden, B, rate, mfma, lists) in zip(picked, MEASURED_CURRENTS):
+        took = lists if choice == "1" else mfma
+        assert took <= 1.05 * min(mfma, lists), (n_in, hidden, B, rate, choice)

@@ -56,3 +56,7 @@ def test_contexts_of_several_threads_share_no_exchange_buffer(thread_checks):
 
 def test_workspace_is_allocated_once(checks):
     checks("workspace")
+
+
+def test_activity_follows_every_call(checks):
+    checks("rates")
