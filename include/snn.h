@@ -219,6 +219,10 @@ snn_status snn_debug_states(snn_ctx *ctx, float *dst);
  * kernel, whose traffic is known (bytes read + bytes written). */
 snn_status snn_debug_copy(snn_ctx *ctx, const void *src, void *dst, size_t bytes);
 
+/* Measurement aid: how many groups of workgroups that exchange with each other every step have found themselves on one die, and
+ * exchanged through its L2, since snn_init (the others went through uncached memory; the results are the same). */
+snn_status snn_debug_die_exchanges(snn_ctx *ctx, int64_t *units);
+
 /* Measurement aid (kernel micro-benchmark at a controlled activity level): replaces the stored
  * spike trains of the hidden layers by the ones given -- hidden[l]: [T][B][N_l] bytes 0/1, host or device, T the
  * length bound by the last snn_forward / snn_bind_inputs call; a NULL entry leaves that layer's spikes as they are
@@ -300,7 +304,7 @@ void snn_destroy(snn_ctx *ctx);
  *                                      the matrix-core version with one batch group per workgroup, never two /
  *                                      with two wherever the batch has an even number of groups of 16 /
  *                                      with workgroups of 64 rows (eight wavefronts) and one batch group /
- *                                      never with its exchange inside one die
+ *                                      never with an exchange inside one die (in the sequential forward part neither)
  *     SNN_CSR=0|1                      compressed rows of masked recurrent matrices never / wherever a kernel
  *                                      for them exists (default: where the firing-rate policy picks a gather)
  *     SNN_SEQ_SLICES=1|2|4|8           workgroups per batch element in the sequential part of wide layers, which then walk

@@ -24,7 +24,7 @@ OP_NAMES = {1: "SAVE_LOCAL", 2: "SAVE_REMOTE", 3: "LOAD_REMOTE", 4: "REFWD1", 5:
 
 EXPORTS = ["snn_init", "snn_set_weights", "snn_forward", "snn_bptt", "snn_bind_inputs", "snn_grads",
            "snn_get_spikes", "snn_get_readout", "snn_debug_states", "snn_bytes_required",
-           "snn_state_slots", "snn_schedule", "snn_last_error", "snn_destroy", "snn_debug_copy",
+           "snn_state_slots", "snn_schedule", "snn_last_error", "snn_destroy", "snn_debug_copy", "snn_debug_die_exchanges",
            "snn_suggest_intervals", "snn_debug_currents", "snn_get_state", "snn_forward_noalloc"]
 
 
@@ -91,6 +91,7 @@ def lib() -> C.CDLL:
         L.snn_debug_states.argtypes = [vp, vp]
         L.snn_get_state.argtypes = [vp, C.c_int, i32, vp]
         L.snn_debug_copy.argtypes = [vp, vp, vp, sz]
+        L.snn_debug_die_exchanges.argtypes = [vp, C.POINTER(i64)]
         L.snn_debug_currents.argtypes = [vp, C.POINTER(vp), i32, i32, C.POINTER(C.c_float)]
         L.snn_bytes_required.argtypes = [C.POINTER(snn_config), C.c_int, i32, i32, i32]
         L.snn_bytes_required.restype = sz
@@ -105,7 +106,7 @@ def lib() -> C.CDLL:
         L.snn_destroy.restype = None
         for name in ("snn_init", "snn_set_weights", "snn_forward", "snn_bptt", "snn_bind_inputs", "snn_grads",
                      "snn_get_spikes", "snn_get_readout", "snn_debug_states", "snn_debug_copy", "snn_debug_currents",
-                     "snn_get_state", "snn_forward_noalloc"):
+                     "snn_get_state", "snn_forward_noalloc", "snn_debug_die_exchanges"):
             getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
@@ -256,6 +257,11 @@ class Snn:
 
     def snn_debug_copy(self, src, dst, nbytes: int):
         self._check(lib().snn_debug_copy(self._h, _ptr(src), _ptr(dst), nbytes))
+
+    def snn_debug_die_exchanges(self) -> int:
+        n = C.c_int64(0)
+        self._check(lib().snn_debug_die_exchanges(self._h, C.byref(n)))
+        return int(n.value)
 
     def snn_debug_currents(self, hidden, chunk: int, reps: int = 1) -> float:
         """hidden: one array / tensor [T][B][N_l] of 0/1 bytes per hidden layer (None: keep the layer's spikes).

@@ -1089,6 +1089,15 @@ snn_status snn_debug_copy(snn_ctx *c, const void *src, void *dst, size_t bytes) 
   return SNN_OK;
 }
 
+snn_status snn_debug_die_exchanges(snn_ctx *c, int64_t *units) {
+  if (!c || !units) return fail(c, SNN_E_INVAL, "null argument");
+  HIPCHK(c, hipSetDevice(c->cfg.device));
+  unsigned n = 0;
+  if (c->ws.err) HIPCHK(c, hipMemcpy(&n, c->ws.err + 1, sizeof n, hipMemcpyDeviceToHost));
+  *units = n;
+  return SNN_OK;
+}
+
 snn_status snn_debug_currents(snn_ctx *c, const uint8_t *const *hidden, int32_t chunk, int32_t reps, float *ms_out) {
   if (!c || !hidden || !ms_out) return fail(c, SNN_E_INVAL, "null argument");
   if (c->T_bound < 1) return fail(c, SNN_E_STATE, "no inputs bound");

@@ -61,7 +61,7 @@ struct NetDev {
   // compressed rows also under a surrogate window, 7 the matrix-core version of the chip-wide recurrence with one
   // batch group per workgroup (never two half a step apart), 8 the same with two groups wherever the batch has an
   // even number of groups, 9 the same with workgroups of 64 rows and one group, 10 the library's choice, but never with
-  // the exchange inside one die.
+  // an exchange inside one die (in the sequential forward part neither).
   // sel_slices: workgroups per batch element in the sequential part of wide layers (1, 2, 4 or 8).
   unsigned char sel_currents, sel_adjoint, sel_slices;
   unsigned char no_fwd_fuse; // 1: the dense currents of wide layers never ride in the launch of the sequential parts
@@ -165,7 +165,7 @@ struct WsArgs {
   float *xl;           // the same for the network's layers in ordinary memory, for workgroups that share a die
   int xg_stride;       // floats between the exchange buffers of two jobs
   unsigned *bar;       // SNN_MAXL x [64] counters, zeroed before every launch
-  unsigned *err;       // raised if a barrier gave up waiting
+  unsigned *err;       // raised if a barrier gave up waiting; err[1] counts the units that exchanged inside one die
   int max_groups;      // workgroups of that kernel that can be resident at once
   int max_groups_m;    // the same for its matrix-core version
   int max_groups_m8;   // ... and for that one's instances for layers of 1025..2048 neurons

@@ -321,6 +321,9 @@ static __device__ __forceinline__ bool unit_on_one_die(unsigned *posts, int me, 
         __builtin_amdgcn_s_sleep(1);
       }
     const bool gave_up = __ballot(late) != 0ull, one = __ballot(got != mine) == 0ull;
+    // (the count of units, see WsArgs::err, is taken here: a branch on the result would make it, and with it every descriptor of the
+    // exchange, differ by lane in the compiler's eyes: 31.3 -> 33.3 ms for a training step of 128-2x512, batch 16, T = 4000)
+    if (i == 0 && me == 0) __hip_atomic_fetch_add(&err[1], one && !gave_up ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (i == 0) s_one_die = gave_up ? 2 : one ? 1 : 0;
   }
   __syncthreads();
@@ -797,7 +800,9 @@ k_layer_seq_lds(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec s
     if (tid < LPB) wl[(size_t)N * LPB + tid] = 0.0f;
   }
   bool dead = false;
-  const bool local = unit_on_one_die(posts + unit * slices, js, (N + LPB - 1) / LPB, err, spin_limit, &dead); // (a barrier: the weights are in)
+  bool local = false;
+  if (xl) local = unit_on_one_die(posts + unit * slices, js, (N + LPB - 1) / LPB, err, spin_limit, &dead);
+  __syncthreads(); // the weights are in
   if (__ballot(bok) == 0ull) return; // no batch element left for this wavefront
   const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)(local ? xl : xg), 0, (int)((size_t)(n_units / groups) * B * 2 * h_max * 8), 0x00027000);
   // this lane's share of the spike words: SB bits from bit sb of half-word h on
@@ -5128,13 +5133,13 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
         // tags of the exchange entries and the posts of the dies start from zero in every launch
         const size_t xbytes = (size_t)ga.count * B * 4 * wd_max * sizeof(uint64_t);
         ZeroJobs clear{};
-        clear.add(ws->xg, xbytes);
-        clear.add(ws->xl, xbytes);
+        uint64_t *xg = reinterpret_cast<uint64_t *>(ws->xg), *xl = net.sel_adjoint == 10 ? nullptr : reinterpret_cast<uint64_t *>(ws->xl);
+        clear.add(xg, xbytes);
+        if (xl) clear.add(xl, xbytes);
         clear.add(ws->bar, (size_t)lp.units * lp.slices * sizeof(unsigned));
         e = launch_fill_zero_jobs(clear, s);
         if (e != hipSuccess) return e;
         const dim3 grid((lp.units + 7) / 8 * 8 * lp.slices), block(64 * lp.waves);
-        uint64_t *xg = reinterpret_cast<uint64_t *>(ws->xg), *xl = reinterpret_cast<uint64_t *>(ws->xl);
         if (lp.lpb == 64)
           hipLaunchKernelGGL(k_layer_seq_lds<64>, grid, block, lp.lds, s, net, ga, state, st, xg, xl, ws->bar, ws->err, ws->spin_limit,
                              lp.slices, lp.groups, lp.units, 2 * wd_max, lp.lcap);

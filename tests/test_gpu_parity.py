@@ -360,16 +360,19 @@ def test_chip_wide_adjoint_inside_a_die(hidden, B, T, monkeypatch):
     w = synth.Workload("die_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=0.6, seed=71 + B)
     first, _ = _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 1)], nthreads=8, check_states=False)
     d = synth.generate(w)
-    for mode in ("uncached", "single"):
+    monkeypatch.setenv("SNN_SEQ_SLICES", "1")  # the forward pass exchanges nothing
+    for mode in ("", "uncached", "single"):
         monkeypatch.setenv("SNN_WS_KERNEL", mode)
         net = snn.from_workload(w, d)
         try:
             net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
             net.snn_bptt(snn.SNN_STANDARD, 0, 0)
             assert _identical(first, _gpu_grads(net, len(hidden))), mode
+            assert (net.snn_debug_die_exchanges() > 0) == (mode != "uncached"), mode
         finally:
             net.snn_destroy()
     monkeypatch.delenv("SNN_WS_KERNEL")
+    monkeypatch.delenv("SNN_SEQ_SLICES")
 
 
 @pytest.mark.parametrize("hidden,B,T", [
@@ -470,21 +473,22 @@ def test_sliced_sequential_forward_at_any_width(hidden, B, T, density, csr, monk
     (40, (300, 300), 17, 66, 1.5),     # lists of nearly every neuron
     (40, (5200, 300), 1, 10, 0.0)])    # 4 columns; no spike at all behind the input
 def test_currents_by_lists(n_in, hidden, B, T, gain, monkeypatch):
-    """Currents from lists of active neurons with the weights in LDS: the bits of the event-by-event gather
-    (SNN_CURRENTS=gather) in spikes, readout and gradients, under full storage and recomputation."""
+    """Currents from lists of active neurons with the weights in LDS, wherever they can be walked (SNN_CURRENTS=lists): the bits of
+    the event-by-event gather (=gather) in spikes, readout and gradients, under full storage and recomputation."""
     w = synth.Workload("lists", n_in, hidden, 5, T=T, B=B, p_in=0.05, gain=gain, seed=191 + B)
     d = synth.generate(w)
     got = []
-    for mode in (None, "gather"):
-        if mode:
-            monkeypatch.setenv("SNN_CURRENTS", mode)
+    for mode in ("lists", "gather"):
+        monkeypatch.setenv("SNN_CURRENTS", mode)
         net = snn.from_workload(w, d)
         try:
             loss = net.snn_forward(d["in_spikes"], d["labels"], T)
             spikes = [net.snn_get_spikes(l, T) for l in range(len(hidden))]
             grads = []
             for strategy, c, f in ((snn.SNN_STANDARD, 0, 0), (snn.SNN_DOUBLE, 10, 3)):
-                net.snn_bptt(strategy, c, f)
+                st = net.snn_bptt(strategy, c, f)
+                # (there is room for the lists, so that "lists" cannot have been something else)
+                assert st.bytes_workspace >= 65 * B * 2 * (n_in + sum(hidden))
                 grads += list(sum((list(g) if isinstance(g, (list, tuple)) else [g] for g in _gpu_grads(net, len(hidden))), []))
             got.append((loss, spikes, grads))
         finally:
@@ -538,31 +542,35 @@ def test_register_stationary_forward_widths(hidden, T):
     ((1024, 1024, 1024, 1024), 64, 12, 1.6, 0),  # sixteen wavefronts, lists shorter than the layer: a quarter of it at a time
     ((640, 640), 3, 2200, 0.5, 1)])            # the ring of spike words
 def test_sequential_forward_with_the_weights_in_lds(hidden, B, T, gain, tier, monkeypatch):
-    """Layers of 257..1024 neurons keep a slice of W_rec in LDS and exchange spike words inside a die: spikes, potentials and
-    gradients of the walk through the L2 (SNN_SEQ_SLICES=1), and of the oracle where that is quick."""
+    """Layers of 257..1024 neurons keep a slice of W_rec in LDS and exchange spike words inside a die, or through uncached memory
+    (SNN_WS_KERNEL=uncached): spikes, potentials and gradients of the walk through the L2 (SNN_SEQ_SLICES=1), and of the oracle
+    where that is quick."""
     w = synth.Workload("lds_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=gain, seed=131 + B)
     d = synth.generate(w)
     L = len(hidden)
     got = {}
-    for slices in (None, "1"):
-        if slices:
-            monkeypatch.setenv("SNN_SEQ_SLICES", slices)
+    for how in ("die", "uncached", "walk"):
+        monkeypatch.setenv("SNN_SEQ_SLICES", "1" if how == "walk" else "0")
+        monkeypatch.setenv("SNN_WS_KERNEL", "uncached" if how == "uncached" else "")
         net = snn.from_workload(w, d, spike_tier=tier) if tier else snn.from_workload(w, d)
         try:
-            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            net.snn_forward(d["in_spikes"], d["labels"], w.T)
+            assert (net.snn_debug_die_exchanges() > 0) == (how == "die"), how
             states = net.snn_debug_states(w.T) if T < 1000 else np.zeros(1)
             net.snn_bptt(snn.SNN_DOUBLE, min(T, 20), 3)
-            got[slices] = _gpu_grads(net, L), [net.snn_get_spikes(l, w.T) for l in range(L)], states
+            got[how] = _gpu_grads(net, L), [net.snn_get_spikes(l, w.T) for l in range(L)], states
         finally:
             net.snn_destroy()
     monkeypatch.delenv("SNN_SEQ_SLICES")
-    assert _identical(got[None][0], got["1"][0])
-    for a, b in zip(got[None][1], got["1"][1]):
-        assert np.array_equal(a, b)
-        assert a.any()
-    assert np.array_equal(got[None][2], got["1"][2])
+    monkeypatch.delenv("SNN_WS_KERNEL")
+    for how in ("die", "uncached"):
+        assert _identical(got[how][0], got["walk"][0]), how
+        for a, b in zip(got[how][1], got["walk"][1]):
+            assert np.array_equal(a, b), how
+            assert a.any()
+        assert np.array_equal(got[how][2], got["walk"][2]), how
     if gain > 1.5:
-        assert max(s.reshape(T, B, -1).sum(2).max() for s in got[None][1]) > 500, "no list was longer than the space for it"
+        assert max(s.reshape(T, B, -1).sum(2).max() for s in got["walk"][1]) > 500, "no list was longer than the space for it"
     if T * B * sum(hidden) < 400_000:
         _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
@@ -1505,12 +1513,15 @@ def test_chip_wide_adjoint_over_compressed_rows(hidden, B, T, density, window, m
         _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_DOUBLE, 8, 3), (snn.SNN_CHUNK, 0, 5)], nthreads=4)
 
 
-@pytest.mark.parametrize("hidden,B,T,density,window", [
-    ((1025,), 5, 11, 0.3, 0.0),          # one neuron past the narrower kernels; a ragged batch group
-    ((2048, 1100), 16, 9, 0.1, 0.5),     # eight units, one per die; row blocks without rows
-    ((2048, 2048, 1026), 4, 1, 0.1, 0.0),  # three units, a single step
-    ((2048, 2048), 20, 7, 0.1, 0.0)])    # ten units: two on some dies
-def test_compressed_row_adjoint_inside_a_die(hidden, B, T, density, window, monkeypatch):
+@pytest.mark.parametrize("hidden,B,T,density,window,die", [
+    ((1025,), 5, 11, 0.3, 0.0, False),           # two units of more row blocks than a die has compute units
+    ((1025,), 29, 11, 0.3, 0.0, True),           # one neuron past the narrower kernels; eight units, a ragged batch group
+    ((2048, 1100), 16, 9, 0.1, 0.5, True),       # eight units, one per die; row blocks without rows
+    ((2048, 2048, 1026), 4, 1, 0.1, 0.0, False),
+    ((2048, 2048, 1026), 32, 1, 0.1, 0.0, True),  # a single step
+    ((2048, 2048), 20, 7, 0.1, 0.0, False),      # five and ten units
+    ((2048, 2048), 45, 7, 0.1, 0.0, True)])      # 12 and 24 units: two and three on a die
+def test_compressed_row_adjoint_inside_a_die(hidden, B, T, density, window, die, monkeypatch):
     """Where the row blocks of a (layer, batch group) fit one die, they exchange through its L2: the same bits as through
     uncached memory (SNN_WS_KERNEL=uncached) and as the kernel with one workgroup per batch element (=rows_all)."""
     w = synth.Workload("csrwdie_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=0.8,
@@ -1526,6 +1537,7 @@ def test_compressed_row_adjoint_inside_a_die(hidden, B, T, density, window, monk
             got[mode] = _gpu_grads(net, len(hidden))
             net.snn_bptt(snn.SNN_CHUNK, 0, min(T, 4))
             assert _identical(_gpu_grads(net, len(hidden)), got[mode]), mode
+            assert (net.snn_debug_die_exchanges() > 0) == (die and mode == "csrw"), mode
         finally:
             net.snn_destroy()
     monkeypatch.delenv("SNN_WS_KERNEL")
