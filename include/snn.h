@@ -126,7 +126,11 @@ typedef struct {
 /* Create a context: validates the configuration, allocates weights, gradients and the
  * spike store for cfg->T steps on cfg->device (the paper's M_others, Section "Standard Checkpointing": weights and
  * the sparse spike trains of the whole sequence, which no strategy recomputes).  No state storage is allocated
- * here.  *out is set even on failure (so that snn_last_error can be read) and must be passed to snn_destroy.
+ * here.  Outside any activation budget a context also holds: for a network with a layer above 256 neurons the buffers its
+ * workgroups exchange through, 16 bytes per batch element (in whole groups of 16) and neuron of the widest layer, four
+ * times and once more per layer (4 x 8192 neurons, batch 32: 34 MB); from the first spike trains in host memory on, three staging
+ * buffers of 2 MiB or one time step of inputs each.
+ * *out is set even on failure (so that snn_last_error can be read) and must be passed to snn_destroy.
  * SNN_E_INVAL for a shape outside the limits noted in snn_config. */
 snn_status snn_init(const snn_config *cfg, snn_ctx **out);
 
@@ -219,8 +223,9 @@ snn_status snn_debug_states(snn_ctx *ctx, float *dst);
  * kernel, whose traffic is known (bytes read + bytes written). */
 snn_status snn_debug_copy(snn_ctx *ctx, const void *src, void *dst, size_t bytes);
 
-/* Measurement aid: how many groups of workgroups that exchange with each other every step have found themselves on one die, and
- * exchanged through its L2, since snn_init (the others went through uncached memory; the results are the same). */
+/* Measurement aid: of the context's last launch that placed groups of workgroups which exchange with each other every step on one die
+ * each, how many groups found themselves there and exchanged through its L2 (the others went through uncached memory; the
+ * results are the same); 0 if there was none. */
 snn_status snn_debug_die_exchanges(snn_ctx *ctx, int64_t *units);
 
 /* Measurement aid (kernel micro-benchmark at a controlled activity level): replaces the stored

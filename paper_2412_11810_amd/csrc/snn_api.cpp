@@ -75,6 +75,7 @@ struct snn_ctx {
   int T_spikes = 0; // length of the sequence whose hidden spike trains are stored (0: none since the inputs were bound)
   double *readout = nullptr;
   WsArgs ws{};                // chip-wide recurrent kernel: exchange buffer, barrier counters, error flag
+  DiePosts die_posts{};       // WsArgs::posted
   float *cur_state = nullptr; // [B][SN] state carried through the forward pass
   float *ubar = nullptr, *g = nullptr, *loss_dev = nullptr, *carry = nullptr;
   unsigned long long *counters = nullptr;
@@ -536,6 +537,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       HIPCHK(c, hipMemsetAsync(c->ws.bar, 0, n_bar * sizeof(unsigned), c->stream));
       xl_bytes = (size_t)L * xg_stride * 4; // (one job per layer at most in a launch)
       c->ws.err = c->ws.bar + 64 * SNN_MAXL;
+      c->ws.posted = &c->die_posts;
       c->ws.max_groups = ws_max_resident_groups(cfg->device);
       c->ws.max_groups_m = ws_max_resident_groups_mfma(cfg->device);
       if (nmax > 1024) c->ws.max_groups_m8 = ws_max_resident_groups_mfma8(cfg->device);
@@ -1092,9 +1094,15 @@ snn_status snn_debug_copy(snn_ctx *c, const void *src, void *dst, size_t bytes) 
 snn_status snn_debug_die_exchanges(snn_ctx *c, int64_t *units) {
   if (!c || !units) return fail(c, SNN_E_INVAL, "null argument");
   HIPCHK(c, hipSetDevice(c->cfg.device));
-  unsigned n = 0;
-  if (c->ws.err) HIPCHK(c, hipMemcpy(&n, c->ws.err + 1, sizeof n, hipMemcpyDeviceToHost));
-  *units = n;
+  *units = 0;
+  const DiePosts &p = c->die_posts;
+  if (!p.posts) return SNN_OK;
+  std::vector<unsigned> die((size_t)p.units * p.slices);
+  HIPCHK(c, hipMemcpy(die.data(), p.posts, die.size() * sizeof(unsigned), hipMemcpyDeviceToHost));
+  for (int u = 0; u < p.units; ++u) { // (slices beyond a narrower layer's width post nothing)
+    const unsigned *d = &die[(size_t)u * p.slices];
+    *units += d[0] != 0u && std::all_of(d, d + p.slices, [&](unsigned x) { return x == 0u || x == d[0]; });
+  }
   return SNN_OK;
 }
 

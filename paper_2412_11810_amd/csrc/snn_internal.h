@@ -12,8 +12,8 @@
 //
 // Weights: fp32, [pre][post] row-major, so the synapses leaving one presynaptic neuron are one
 // contiguous row (one active spike = one coalesced row read).  W_in[l] and W_rec[l] are stacked in
-// one allocation (W_rec[l] = W_in[l] + pre_l * N_l) so that a gather walks one row stream.  *_T are [post][pre] copies used by
-// the adjoint pass (delta_s[j] = sum_n W[j][n] * delta_v[n] becomes a coalesced column walk).
+// one allocation (W_rec[l] = W_in[l] + pre_l * N_l) so that a gather walks one row stream.  *_T are [post][pre] copies: that
+// of W_rec is read by the fallbacks of the adjoint pass (delta_s[j] = sum_n W[j][n] * delta_v[n] as a coalesced column walk).
 // Spikes: one bit per neuron, 64-bit words, mask[l] = [T+1][B][Wd[l]] with row 0 (t = 0) all zero;
 // layer index 0 is the input layer, l >= 1 hidden layer l.
 // States: slots of B*SN floats laid out [B][SN] (all layers of one batch element contiguous).
@@ -134,6 +134,7 @@ struct SeqJobs { SeqJob j[SNN_MAXL]; int count; };
 struct CurJob { int mode, lsel, t0, nsteps, t_base; float *out; size_t slot_stride; };
 struct CurJobs { CurJob j[2 * SNN_MAXL + 1]; int count; };
 struct WsArgs;
+struct DiePosts { const unsigned *posts; int units, slices; }; // where the workgroups of a launch wrote the numbers of their dies
 hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, float *state, const StoreSpec &st,
                           double *readout /*[B][2][O]*/, int readout_init, float *work, hipStream_t s,
                           const SpanHook *hook = nullptr, const FwdCallbacks *cb = nullptr, const WsArgs *ws = nullptr);
@@ -165,11 +166,12 @@ struct WsArgs {
   float *xl;           // the same for the network's layers in ordinary memory, for workgroups that share a die
   int xg_stride;       // floats between the exchange buffers of two jobs
   unsigned *bar;       // SNN_MAXL x [64] counters, zeroed before every launch
-  unsigned *err;       // raised if a barrier gave up waiting; err[1] counts the units that exchanged inside one die
+  unsigned *err;       // raised if a barrier gave up waiting
   int max_groups;      // workgroups of that kernel that can be resident at once
   int max_groups_m;    // the same for its matrix-core version
   int max_groups_m8;   // ... and for that one's instances for layers of 1025..2048 neurons
   unsigned spin_limit; // barrier polls before giving up
+  DiePosts *posted;    // the last launch that placed its units on dies (host memory; for snn_debug_die_exchanges)
 };
 // One recurrence of the adjoint pass: layer l over steps t1, ..., t0+1 of a tile whose states sit in vbuf.
 // up: the inter-layer product of that layer and tile, addressed by absolute slot (row (t - t_base - 1)*B + b,
