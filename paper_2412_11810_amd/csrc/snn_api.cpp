@@ -87,7 +87,7 @@ struct snn_ctx {
   float *host_ckpt = nullptr;
   size_t host_bytes = 0;
   std::vector<hipEvent_t> ev_pool;
-  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; void *lists; float rate[SNN_MAXL + 1]; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache && lists == o.lists && std::equal(rate, rate + SNN_MAXL + 1, o.rate); } };
+  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; void *lists; unsigned choice; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache && lists == o.lists && choice == o.choice; } };
   GraphKeyT graph_key{};
   hipGraphExec_t graph_exec = nullptr;
   bool graphs_enabled = true;   // SNN_GRAPH=0 turns graph replay off
@@ -864,8 +864,8 @@ static hipError_t queue_spike_counts(snn_ctx *c, int T, int layers) {
     jobs.j[jobs.count++] = CountJob{c->mask_full[l] + (size_t)n.B * n.Wd[l], (size_t)T * n.B * n.Wd[l], c->counters + l};
   return launch_count_spikes(jobs, c->stream);
 }
-// Activities from the counts into r, and into what the choice of kernels for the currents goes by.  A recorded step holds that
-// choice: a rate stays while the new one is within a quarter of it, so that a step is not recorded again at every call.
+// Activities from the counts into r, and into what the choice of kernels for the currents goes by.  A recorded step is recorded
+// again when that choice changes: a rate stays while the new one is within a quarter of it, so that it does not go to and fro.
 static void set_rates(snn_ctx *c, const unsigned long long *cnt, int T, double *r) {
   NetDev &n = c->net;
   for (int l = 0; l <= n.L; ++l) {
@@ -2172,8 +2172,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
     pol = pol * 2 + (c->dw_tile ? 1u : 0u);
     const unsigned sel = (unsigned)n.sel_currents | (unsigned)n.sel_adjoint << 8 | (unsigned)n.sel_slices << 16 | (unsigned)n.sel_csr << 24 | (unsigned)n.sel_seq << 28 | (unsigned)n.no_fwd_fuse << 30;
     snn_ctx::GraphKeyT key{(int)strategy, T, p.C, p.F, p.n_chunk_bufs, c->arena, c->dubuf, c->host_ckpt, c->dw_event_driven, pol, sel,
-                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists, {}};
-    if (n.lists) std::copy(n.rate, n.rate + SNN_MAXL + 1, key.rate);
+                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists, currents_choice(n, p.chunk_len)};
     if (!c->graph_exec || !(key == c->graph_key)) {
       if (c->graph_exec) { (void)hipGraphExecDestroy(c->graph_exec); c->graph_exec = nullptr; }
       Timer tm{c, false};

@@ -141,6 +141,7 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
 // Recompute pass over steps t0+1..t1 from state_in = x_{t0}, spikes read from the stored bitmasks:
 // currents of the whole range in parallel into buf (slot of x_t = t - t_base - 1), then a scan that
 // turns them into states in place (store_all) and/or writes x_{t1} to state_out.
+unsigned currents_choice(const NetDev &net, int chunk); // bits: lists for a forward stage, for the recompute of a chunk
 size_t currents_lists_entries(const NetDev &net); // of that space: SNN_LIST_STEPS steps of every layer; 0: never used
 #define SNN_LIST_STEPS 64
 hipError_t launch_recompute(const NetDev &net, int t0, int t1, const float *state_in, float *buf, int t_base,

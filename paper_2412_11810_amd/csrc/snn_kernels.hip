@@ -4623,18 +4623,33 @@ static bool lists_pay(const NetDev &net, const CurJobs &jobs, int most) {
 }
 // Currents by walking lists (a readout job's lsel is the layer index of the spikes it reads, L), SNN_LIST_STEPS steps at a time: the lists of every layer that the jobs
 // read, then the feed-forward parts of all jobs, then the recurrent parts (mode 0), added to them.
-static hipError_t launch_currents_lists(const NetDev &net, CurJobs *jobs, hipStream_t s) {
-  if (!net.lists || (net.sel_currents != 4 && net.sel_currents != 0) || !lists_ok(net)) return hipSuccess;
-  CurJobs mine{}, rest{};
-  for (int i = 0; i < jobs->count; ++i) {
-    const CurJob &j = jobs->j[i];
+static bool lists_run(const NetDev &net, const CurJobs &jobs, CurJobs *mine, CurJobs *rest, int *most) { // which jobs, and whether
+  *most = 0;
+  if (!net.lists || (net.sel_currents != 4 && net.sel_currents != 0) || !lists_ok(net)) return false;
+  for (int i = 0; i < jobs.count; ++i) {
+    const CurJob &j = jobs.j[i];
     const bool ok = list_lanes(j.lsel == 0 ? net.n_in : net.N[j.lsel - 1]) > 0 && (j.mode != 0 || list_lanes(net.N[j.lsel]) > 0);
-    CurJobs &dst = ok ? mine : rest;
+    CurJobs &dst = ok ? *mine : *rest;
     dst.j[dst.count++] = j;
+    if (ok) *most = std::max(*most, j.nsteps);
   }
-  int most = 0;
-  for (int i = 0; i < mine.count; ++i) most = std::max(most, mine.j[i].nsteps);
-  if (net.sel_currents == 0 && !lists_pay(net, mine, most)) return hipSuccess;
+  return net.sel_currents == 4 || lists_pay(net, *mine, *most);
+}
+unsigned currents_choice(const NetDev &net, int chunk) {
+  CurJobs fwd{}, rec{};
+  for (int l = 0; l < net.L; ++l) {
+    const CurJob f{1, l, 0, SNN_FWD_TILE, 0, nullptr, 0}, r{0, l, 0, chunk, 0, nullptr, 0};
+    if (currents_job_kernel(net, f) == 0) fwd.j[fwd.count++] = f;
+    if (currents_job_kernel(net, r) == 0) rec.j[rec.count++] = r;
+  }
+  CurJobs mine{}, rest{}, mine_r{}, rest_r{};
+  int most;
+  return (lists_run(net, fwd, &mine, &rest, &most) ? 1u : 0u) | (lists_run(net, rec, &mine_r, &rest_r, &most) ? 2u : 0u);
+}
+static hipError_t launch_currents_lists(const NetDev &net, CurJobs *jobs, hipStream_t s) {
+  CurJobs mine{}, rest{};
+  int most;
+  if (!lists_run(net, *jobs, &mine, &rest, &most)) return hipSuccess;
   const int B = net.B;
   for (int a = 0; a < most; a += SNN_LIST_STEPS) {
     ListJobs lj{};

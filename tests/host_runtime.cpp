@@ -157,6 +157,7 @@ hipError_t launch_finish_grad_csr(const double *, const uint32_t *, const uint16
 hipError_t launch_unpack_spikes(const uint64_t *, int, int, int, int, uint8_t *, hipStream_t) { return hipSuccess; }
 hipError_t launch_copy(const void *, void *, size_t, hipStream_t) { return hipSuccess; }
 bool snn_kernel_shape_ok(const NetDev &, char *, size_t) { return true; }
+unsigned currents_choice(const NetDev &, int) { return 0; }
 static const size_t LIST_ENTRIES = (size_t)1 << 20;
 size_t currents_lists_entries(const NetDev &n) { return n.N[0] > 256 ? LIST_ENTRIES : 0; }
 

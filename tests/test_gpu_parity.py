@@ -499,6 +499,47 @@ def test_currents_by_lists(n_in, hidden, B, T, gain, monkeypatch):
     assert all(np.array_equal(a, b) for a, b in zip(got[0][2], got[1][2]))
 
 
+@pytest.mark.parametrize("hidden,B,T", [((1024, 300), 64, 40), ((1500,), 16, 30), ((300,), 90, 25)])
+def test_currents_while_the_activity_changes(hidden, B, T, monkeypatch):
+    """One context whose activity goes from nothing known to a few per cent, to tens of per cent and back (the choice between lists and
+    matrix cores with it, the recorded step as well): forward pass and gradients are always those of SNN_CURRENTS=mfma."""
+    n_in, dev = 60, "cuda"
+    import torch
+    g = torch.Generator(device=dev).manual_seed(7 + B)
+    x = (torch.rand((T, B, n_in), generator=g, device=dev) < 0.1).to(torch.uint8)
+    y = torch.zeros(B, dtype=torch.int32, device=dev)
+    pre = (n_in,) + hidden[:-1]
+    w = [[torch.randn((p, n), generator=g, device=dev) / p ** 0.5, torch.randn((n, n), generator=g, device=dev) / n ** 0.5] for p, n in zip(pre, hidden)]
+    w_out = torch.randn((hidden[-1], 7), generator=g, device=dev)
+
+    def steps(net):
+        out = []
+        for gain in (0.5, 0.5, 4.0, 4.0, 0.5):
+            for l, (wi, wr) in enumerate(w):
+                net.snn_set_weights(snn.SNN_W_IN, l, wi * (2.5 * gain))
+                net.snn_set_weights(snn.SNN_W_REC, l, wr * gain)
+            net.snn_set_weights(snn.SNN_W_OUT, 0, w_out)
+            for _ in range(2):
+                loss = net.snn_forward(x, y, T)
+                net.snn_bptt(snn.SNN_DOUBLE, 12, 4, want_stats=False)
+                out.append((loss, [net.snn_get_spikes(l, T) for l in range(len(hidden))], _gpu_grads(net, len(hidden))))
+        return out
+    got = {}
+    for mode in ("", "mfma"):
+        monkeypatch.setenv("SNN_CURRENTS", mode)
+        net = snn.Snn(snn.make_config(n_in, list(hidden), 7, T, B))
+        try:
+            got[mode] = steps(net)
+        finally:
+            net.snn_destroy()
+    monkeypatch.delenv("SNN_CURRENTS")
+    rates = [np.mean([s.mean() for s in spikes]) for _, spikes, _ in got["mfma"]]
+    assert min(rates) < 0.1 and max(rates) > 0.3, rates
+    for k, (a, b) in enumerate(zip(got[""], got["mfma"])):
+        assert a[0] == b[0] and _identical(a[2], b[2]), k
+        assert all(np.array_equal(p, q) for p, q in zip(a[1], b[1])), k
+
+
 @pytest.mark.parametrize("n_in,hidden,B,T", [(1000, (64,), 40, 300), (700, (256, 130), 33, 200), (37, (300,), 3, 9)])
 def test_inputs_from_host_memory_in_pieces(n_in, hidden, B, T):
     """Spike trains in host memory are copied in pieces beside the forward pass (several pieces per tile, buffers used again;
