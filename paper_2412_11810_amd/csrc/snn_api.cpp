@@ -13,8 +13,7 @@
 
 #include "../../include/snn.h"
 #include "snn_internal.h"
-
-#define SNN_BWD_TILE 256 // steps of the adjoint pass per launch group (bounds the per-chunk scratch)
+#include "snn_plan.h"
 
 // Workspace of snn_forward_noalloc: the per-tile currents of the forward pass, which the allocating entry points
 // keep in a buffer they size and hipMalloc on demand.  One copy per GPU the library is loaded on, held until the
@@ -36,7 +35,7 @@ struct snn_ctx {
   // through hipMemcpyAsync on the copy stream, overlapped with compute.  SNN_HOST_TIER=dma|direct forces one.
   size_t host_direct_max = (size_t)1 << 20;
   float *W_in[SNN_MAXL]{}, *W_rec[SNN_MAXL]{}, *W_out = nullptr;
-  float *W_inT[SNN_MAXL]{}, *W_recT[SNN_MAXL]{}, *W_outT = nullptr;
+  float *W_recT[SNN_MAXL]{};
   float *dW_in[SNN_MAXL]{}, *dW_rec[SNN_MAXL]{}, *dW_out = nullptr;
   double *acc_in[SNN_MAXL]{}, *acc_rec[SNN_MAXL]{}, *acc_out = nullptr; // fp64 gradient accumulators
   uint8_t *rec_mask[SNN_MAXL]{};
@@ -479,26 +478,27 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
     const size_t ni = (size_t)pre_of(n, l) * n.N[l], nr = (size_t)n.N[l] * n.N[l];
     HIPCHK(c, hipMalloc(&c->W_in[l], (ni + nr) * 4)); // [W_in ; W_rec] stacked row-wise
     c->W_rec[l] = c->W_in[l] + ni;
-    HIPCHK(c, hipMalloc(&c->W_inT[l], ni * 4));
     HIPCHK(c, hipMalloc(&c->dW_in[l], ni * 4));
     HIPCHK(c, hipMalloc(&c->acc_in[l], ni * 8));
     HIPCHK(c, hipMalloc(&c->acc_rec[l], nr * 8));
     HIPCHK(c, hipMalloc(&c->W_recT[l], nr * 4));
     HIPCHK(c, hipMalloc(&c->dW_rec[l], nr * 4));
     HIPCHK(c, hipMemsetAsync(c->W_in[l], 0, ni * 4, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->W_inT[l], 0, ni * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(c->W_rec[l], 0, nr * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(c->W_recT[l], 0, nr * 4, c->stream));
-    n.W_in[l] = c->W_in[l]; n.W_rec[l] = c->W_rec[l]; n.W_inT[l] = c->W_inT[l]; n.W_recT[l] = c->W_recT[l];
+    n.W_in[l] = c->W_in[l]; n.W_rec[l] = c->W_rec[l]; n.W_recT[l] = c->W_recT[l];
+    if (l > 0 && split_product(n.N[l - 1], n.N[l])) { // filled at the start of every step's backward pass
+      const size_t rows = (size_t)n.N[l - 1];
+      HIPCHK(c, hipMalloc(&n.W_split[l], rows * (split_row_bytes(n.N[l]) + 4)));
+      n.W_scale[l] = reinterpret_cast<float *>(n.W_split[l]) + rows * split_row_bytes(n.N[l]) / 4;
+    }
   }
   const size_t no = (size_t)n.N[L - 1] * O;
   HIPCHK(c, hipMalloc(&c->W_out, no * 4));
-  HIPCHK(c, hipMalloc(&c->W_outT, no * 4));
   HIPCHK(c, hipMalloc(&c->dW_out, no * 4));
   HIPCHK(c, hipMalloc(&c->acc_out, no * 8));
   HIPCHK(c, hipMemsetAsync(c->W_out, 0, no * 4, c->stream));
-  HIPCHK(c, hipMemsetAsync(c->W_outT, 0, no * 4, c->stream));
-  n.W_out = c->W_out; n.W_outT = c->W_outT;
+  n.W_out = c->W_out;
   for (int l = 0; l <= L; ++l) {
     c->mask_words[l] = (size_t)(cfg->T + 1) * B * n.Wd[l];
     if (l > 0 && cfg->spike_tier == 1) continue; // hidden layers: allocated when a call needs the whole sequence in HBM
@@ -512,7 +512,9 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
   HIPCHK(c, hipMalloc(&c->g, (size_t)B * O * 4));
   HIPCHK(c, hipMalloc(&c->loss_dev, 16 + 8 * (SNN_MAXL + 1)));
   c->counters = reinterpret_cast<unsigned long long *>(c->loss_dev + 4); // one copy takes the loss and the counts to the host
-  HIPCHK(c, hipMalloc(&c->carry, (size_t)B * (n.SN + O) * 4));
+  const size_t carry = (size_t)B * (n.SN + O);
+  HIPCHK(c, hipMalloc(&c->carry, (carry + (size_t)L * SNN_BWD_TILE * B) * 4));
+  n.row_scale = c->carry + carry;
   size_t xl_bytes = 0; // exchange inside a die: shares an allocation with cur_state
   {
     int nmax = 0;
@@ -581,14 +583,14 @@ void snn_destroy(snn_ctx *c) {
   (void)hipSetDevice(c->cfg.device);
   (void)hipDeviceSynchronize();
   for (int l = 0; l < SNN_MAXL; ++l) {
-    (void)hipFree(c->W_in[l]); (void)hipFree(c->W_inT[l]); (void)hipFree(c->W_recT[l]);
+    (void)hipFree(c->W_in[l]); (void)hipFree(c->net.W_split[l]); (void)hipFree(c->W_recT[l]);
     (void)hipFree(c->dW_in[l]); (void)hipFree(c->dW_rec[l]); (void)hipFree(c->rec_mask[l]);
     free_csr(c, l);
     (void)hipFree(c->acc_in[l]); (void)hipFree(c->acc_rec[l]);
   }
   for (int l = 0; l <= SNN_MAXL; ++l) { (void)hipFree(c->mask_full[l]); (void)hipFree(c->mask_ring[l]); }
   if (c->host_spk) (void)hipHostFree(c->host_spk);
-  (void)hipFree(c->W_out); (void)hipFree(c->W_outT); (void)hipFree(c->dW_out); (void)hipFree(c->acc_out);
+  (void)hipFree(c->W_out); (void)hipFree(c->dW_out); (void)hipFree(c->acc_out);
   (void)hipFree(c->labels); (void)hipFree(c->readout); (void)hipFree(c->ubar); (void)hipFree(c->g);
   (void)hipFree(c->loss_dev); (void)hipFree(c->carry); (void)hipFree(c->cur_state);
   if (c->ws.bar) uncached_release(c->cfg.device, c->ws.bar);
@@ -611,13 +613,12 @@ snn_status snn_set_weights(snn_ctx *c, int kind, int layer, const float *w, cons
   if (!c || !w) return fail(c, SNN_E_INVAL, "null argument");
   HIPCHK(c, hipSetDevice(c->cfg.device));
   NetDev &n = c->net;
-  float *dst, *dstT;
+  float *dst;
   int rows, cols;
   if (kind == SNN_W_OUT) {
-    dst = c->W_out; dstT = c->W_outT; rows = n.N[n.L - 1]; cols = n.n_out;
+    dst = c->W_out; rows = n.N[n.L - 1]; cols = n.n_out;
   } else if ((kind == SNN_W_IN || kind == SNN_W_REC) && layer >= 0 && layer < n.L) {
     dst = kind == SNN_W_IN ? c->W_in[layer] : c->W_rec[layer];
-    dstT = kind == SNN_W_IN ? c->W_inT[layer] : c->W_recT[layer];
     rows = kind == SNN_W_IN ? pre_of(n, layer) : n.N[layer];
     cols = n.N[layer];
   } else {
@@ -634,7 +635,7 @@ snn_status snn_set_weights(snn_ctx *c, int kind, int layer, const float *w, cons
   // weights and mask may have been produced on the caller's default stream (see snn_bind_inputs)
   if (c->own_stream) HIPCHK(c, hipStreamSynchronize(nullptr));
   HIPCHK(c, hipMemcpyAsync(dst, w, ne * 4, hipMemcpyDefault, c->stream));
-  HIPCHK(c, launch_transpose(dst, dstT, rows, cols, c->stream));
+  if (kind == SNN_W_REC) HIPCHK(c, launch_transpose(dst, c->W_recT[layer], rows, cols, c->stream));
   if (kind == SNN_W_REC) {
     if (mask) {
       if (!c->rec_mask[layer]) HIPCHK(c, hipMalloc(&c->rec_mask[layer], ne));

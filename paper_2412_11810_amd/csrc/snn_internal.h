@@ -6,14 +6,15 @@
 #include <stdint.h>
 
 #define SNN_MAXL 4
+#define SNN_BWD_TILE 256 // steps of the adjoint pass per launch group (bounds the per-chunk scratch)
 #define SNN_CSR_SUBW 512 // postsynaptic neurons per sub-range of a compressed row (one wavefront's share)
 
 // Device-visible description of the network and of where its data lives in HBM.
 //
 // Weights: fp32, [pre][post] row-major, so the synapses leaving one presynaptic neuron are one
 // contiguous row (one active spike = one coalesced row read).  W_in[l] and W_rec[l] are stacked in
-// one allocation (W_rec[l] = W_in[l] + pre_l * N_l) so that a gather walks one row stream.  *_T are [post][pre] copies: that
-// of W_rec is read by the fallbacks of the adjoint pass (delta_s[j] = sum_n W[j][n] * delta_v[n] as a coalesced column walk).
+// one allocation (W_rec[l] = W_in[l] + pre_l * N_l) so that a gather walks one row stream.  W_recT: a [post][pre] copy,
+// read by the fallbacks of the adjoint pass (delta_s[j] = sum_n W[j][n] * delta_v[n] as a coalesced column walk).
 // Spikes: one bit per neuron, 64-bit words, mask[l] = [T+1][B][Wd[l]] with row 0 (t = 0) all zero;
 // layer index 0 is the input layer, l >= 1 hidden layer l.
 // States: slots of B*SN floats laid out [B][SN] (all layers of one batch element contiguous).
@@ -23,7 +24,11 @@ struct NetDev {
   int off[SNN_MAXL + 1];  // offset of layer l inside a state vector
   int Wd[SNN_MAXL + 1];   // 64-bit words per (t, b) of layer index 0..L (0 = input)
   const float *W_in[SNN_MAXL], *W_rec[SNN_MAXL], *W_out;
-  const float *W_inT[SNN_MAXL], *W_recT[SNN_MAXL], *W_outT;
+  const float *W_recT[SNN_MAXL];
+  // W_in of layer l >= 1, every row scaled by a power of two (W_scale) and split into two fp16 values (see k_up_split); NULL: the
+  // products with it go through the fp32 matrix cores.  row_scale: the same scales for the rows of the other operand.
+  uint4 *W_split[SNN_MAXL];
+  float *W_scale[SNN_MAXL], *row_scale;
   uint64_t *mask[SNN_MAXL + 1];
   // > 0: mask[l] holds only a window of the sequence, as a ring of that many steps (row = step modulo the ring);
   // the rest of the spike trains is in pinned host memory and travels per coarse segment.  0: all T + 1 rows.

@@ -2009,25 +2009,18 @@ k_du_scan(const float *__restrict__ g, float *__restrict__ carry, float *__restr
 // element (k ascending in pairs) is fixed and independent of M, i.e. of how time is cut into chunks.
 //   lane layout (verified on the device): A[i][k] in lane i + 32k, B[k][j] in lane j + 32k,
 //   D[8*(r/4) + 4*(lane/32) + r%4][lane%32] in register r.
-template <int WM, int WN, int BM = 1, int BN = 1>
+template <int WM, int WN>
 __device__ __forceinline__ void up_gemm_body(const float *__restrict__ A, int lda, const float *__restrict__ W, int K,
                                              int N, float *__restrict__ C, int ldc, int M, int bx, int by) {
-  // (BM x BN blocks of 32 x 32 per wavefront: every LDS value read feeds BN or BM matrix instructions, and a
-  // tile of 32 WM BM x 32 WN BN needs proportionally fewer operand bytes from the L2 per flop -- what bounds the
-  // 64 x 64 tiles once the matrices are far beyond it.  The operations per element of C are the same.)
-  constexpr int NT = 64 * WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN, KT = 32;
+  constexpr int NT = 64 * WM * WN, TM = 32 * WM, TN = 32 * WN, KT = 32;
   constexpr int LA = TM * KT / NT, LW = TN * KT / NT;
   __shared__ float As[TM][KT + 1], Ws[TN][KT + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WM, wn = wave / WM;
   const int m0 = bx * TM, j0 = by * TN;
-  v16f acc[BM][BN];
+  v16f acc;
 #pragma unroll
-  for (int p = 0; p < BM; ++p)
-#pragma unroll
-    for (int q = 0; q < BN; ++q)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[p][q][r] = 0.0f;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
   float ra[LA], rw[LW];
   auto gload = [&](int k0) {
 #pragma unroll
@@ -2057,29 +2050,17 @@ __device__ __forceinline__ void up_gemm_body(const float *__restrict__ A, int ld
     if (k0 + KT < K) gload(k0 + KT);
 #pragma unroll
     for (int kk = 0; kk < KT; kk += 2) {
-      float a[BM], b[BN];
-#pragma unroll
-      for (int p = 0; p < BM; ++p) a[p] = As[(wm * BM + p) * 32 + (lane & 31)][kk + (lane >> 5)];
-#pragma unroll
-      for (int q = 0; q < BN; ++q) b[q] = Ws[(wn * BN + q) * 32 + (lane & 31)][kk + (lane >> 5)];
-#pragma unroll
-      for (int p = 0; p < BM; ++p)
-#pragma unroll
-        for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[p], b[q], acc[p][q], 0, 0, 0);
+      const float a = As[wm * 32 + (lane & 31)][kk + (lane >> 5)], b = Ws[wn * 32 + (lane & 31)][kk + (lane >> 5)];
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
     }
     __syncthreads();
   }
+  const int j = j0 + wn * 32 + (lane & 31);
 #pragma unroll
-  for (int p = 0; p < BM; ++p)
-#pragma unroll
-    for (int q = 0; q < BN; ++q) {
-      const int j = j0 + (wn * BN + q) * 32 + (lane & 31);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + (wm * BM + p) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (m < M && j < N) C[(size_t)m * ldc + j] = acc[p][q][r];
-      }
-    }
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    if (m < M && j < N) C[(size_t)m * ldc + j] = acc[r];
+  }
 }
 
 // The same product for small weight matrices (N * K <= 65536, K a multiple of 16, 16-byte aligned rows):
@@ -2092,20 +2073,228 @@ __device__ __forceinline__ void up_gemm_body(const float *__restrict__ A, int ld
 // layer shapes only, never on M, so every storage strategy sees the same arithmetic.
 //   lane layout (verified on the device): A[i][k] in lane i + 16k, B[k][j] in lane j + 16k,
 //   D[4*(lane/16) + r][lane%16] in register r.
-template <int WM, int WN, int BM = 1, int BN = 1>
+template <int WM, int WN>
 __global__ void __launch_bounds__(64 * WM * WN)
 k_up_gemm(const float *__restrict__ A, int lda, const float *__restrict__ W, int K, int N, float *__restrict__ C,
           int ldc, int M) {
-  up_gemm_body<WM, WN, BM, BN>(A, lda, W, K, N, C, ldc, M, (int)blockIdx.x, (int)blockIdx.y);
+  up_gemm_body<WM, WN>(A, lda, W, K, N, C, ldc, M, (int)blockIdx.x, (int)blockIdx.y);
 }
-// Tile of a product in front of a large matrix (0: 64 x 64, 1: 128 x 128, 2: 256 x 256): the largest that still gives nearly
-// every compute unit a workgroup.  256 from 192 of them (M = 1600, N = K = 8192: 2263 us, 128: 2362; M = 2048: 54 against 58 ms
-// per step at 1024-4x8192, T = 512; 256 x 128 with 8 wavefronts: 56), 128 from 256 (M = 1024, N = K = 2048, which has 128 of
-// them: 178 us, 64: 94).  The operations per element of the result are the same for every tile, so the choice may look at M.
-static int up_gemm_tile(int M, int N, int K) {
-  if (N < 2048 || K < 2048) return 0;
-  const auto tiles = [&](int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
-  return N >= 4096 && tiles(256) >= 192 ? 2 : tiles(128) >= 256 ? 1 : 0;
+// The same product for large matrices (2048 x 2048 and more) on the fp16 matrix cores.  An fp32 value is the sum of two fp16 ones to
+// within 2^-24 of itself, h = fp16(x) and l = fp16(x - h), as long as neither leaves fp16's range: every row of both operands is
+// scaled by the power of two that brings its largest magnitude to 2^14 ... 2^15 (and the result scaled back exactly), so an
+// element 2^-16 below its row's largest still has all its bits and a smaller one is off by 2^-40 of that largest.  Then
+// a . b = h.h + h.l + l.h with exact products and fp32 sums (l.l is below 2^-24 of h.h).  Three products at sixteen times the
+// fp32 matrix rate, and fewer roundings per element: 16 terms meet in one instruction.  Against 64 bits, 2-norm: 9.9e-7 at K =
+// 8192 (the fp32 matrix cores: 1.6e-6), 5.0e-7 at 2048 (8.1e-7), also for rows that span thirteen decades or sit near the smallest
+// fp32 values.
+// The matrix cores cut the terms they align below an accumulator towards minus infinity: 2.5e-7 of the mean magnitude at K =
+// 8192, always the same way, which sums over thousands of time steps would see.  Every eighth tile of K turns the sign of A and of
+// the accumulators, and what is cut off changes sides: 5e-9.
+//   W comes split (k_split_rows, once per step: 16 bytes hold h and l of four elements, rows padded with zeros to whole tiles of 32),
+//   A is split while it is staged.  The last tile of K comes first: it alone may be ragged, so the loop is straight-line code.
+//   A tile of K costs 3 BM BN matrix instructions per 16 k and wavefront; the share of the next tile's staging (vector work, LDS writes,
+//   the loads of the tile after it) sits between them, group by group: left to the scheduler it ended up behind them, one after
+//   the other (761 -> 706 us at M = 2048, N = K = 8192).  That product took 2180 us in fp32, 126 TFLOP/s; 390 now, 1.17 PFLOP/s of
+//   fp16, where a plain bf16 product of the vendor's library reaches 1.3 here.
+//   Lane layout (checked on the device): A[i][k] in lane i + 32 (k / 8), element k % 8; result as v_mfma_f32_32x32x2.
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+static __device__ __forceinline__ void split_fp16(float x, float y, uint32_t &h, uint32_t &l) {
+  const v2h hv = {(_Float16)x, (_Float16)y};
+  const v2h lv = {(_Float16)__builtin_fmaf((float)hv[0], -1.0f, x), (_Float16)__builtin_fmaf((float)hv[1], -1.0f, y)};
+  h = __builtin_bit_cast(uint32_t, hv);
+  l = __builtin_bit_cast(uint32_t, lv);
+}
+// Scale of a row whose largest magnitude is mx: the power of two that brings it to 2^14 ... 2^15 (a row below 2^-112: 2^127).
+static __device__ __forceinline__ float row_scale(float mx) {
+  const uint32_t e = __float_as_uint(mx) >> 23;
+  return __uint_as_float((e < 14u ? 254u : 268u - e) << 23);
+}
+static __device__ __forceinline__ float row_max(const float *__restrict__ r, int K, int lane) { // over a wavefront
+  float mx = 0.0f;
+  int k = 4 * lane;
+  for (; k + 4 <= K; k += 256) {
+    const f32x4u v = *reinterpret_cast<const f32x4u *>(r + k);
+    mx = fmaxf(fmaxf(mx, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
+  }
+  for (; k < K; ++k) mx = fmaxf(mx, fabsf(r[k])); // (at most three elements, of one lane)
+  for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+  return mx;
+}
+__global__ void __launch_bounds__(256) // a wavefront per row: bound by reading A once (13 us for 67 MB)
+k_row_scales(const float *__restrict__ A, int lda, int K, int M, float *__restrict__ scale) {
+  const int m = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = lane_id();
+  if (m >= M) return;
+  const float mx = row_max(A + (size_t)m * lda, K, lane);
+  if (lane == 0) scale[m] = row_scale(mx);
+}
+__global__ void __launch_bounds__(256) // a wavefront per row; the second look at the row comes from the caches
+k_split_rows(const float *__restrict__ W, int K, int N, uint4 *__restrict__ WS, float *__restrict__ scale) {
+  const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = lane_id(), K4 = (K + 31) / 32 * 8;
+  if (j >= N) return;
+  const float *r = W + (size_t)j * K;
+  const float sc = row_scale(row_max(r, K, lane));
+  if (lane == 0) scale[j] = sc;
+  for (int q = lane; q < K4; q += 64) {
+    float x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = 4 * q + e < K ? r[4 * q + e] * sc : 0.0f;
+    uint4 v;
+    split_fp16(x[0], x[1], v.x, v.z);
+    split_fp16(x[2], x[3], v.y, v.w);
+    WS[(size_t)j * K4 + q] = v;
+  }
+}
+#define UPS_KT 32                      // K per tile
+#define UPS_ROW_BYTES (4 * UPS_KT + 16) // a row of a tile in LDS: h, l; 16 bytes more make its 16-byte reads free of bank conflicts
+#define UPS_FLIP 8                     // K tiles between two turns of the sign
+template <int WM, int WN, int BM, int BN, int WPE> // wavefronts and their blocks of 32 x 32; wavefronts per SIMD
+__global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+k_up_split(const float *__restrict__ A, int lda, const float *__restrict__ sa, const uint4 *__restrict__ WS, const float *__restrict__ sw,
+           int K, int N, float *__restrict__ C, int ldc, int M) {
+  constexpr int NT = 64 * WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN, TPR = UPS_KT / 4, RPP = NT / TPR; // threads per row, rows per pass
+  constexpr int LA = TM / RPP, LW = TN / RPP, LD = LA + LW, NG = UPS_KT / 16 * BM, RB = UPS_ROW_BYTES, BUF = (TM + TN) * RB;
+  static_assert(TM % RPP == 0 && TN % RPP == 0, "whole passes");
+  extern __shared__ __align__(16) unsigned char smem[]; // [2][TM + TN][RB]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave % WM, wn = wave / WM;
+  // a die (workgroup number modulo 8) gets neighbouring tiles, rows fastest: its L2 holds their columns of W for all of them
+  const int mt = (M + TM - 1) / TM, total = (int)gridDim.x, die = (int)blockIdx.x & 7, rest = total & 7;
+  const int tile = die * (total >> 3) + min(die, rest) + (int)(blockIdx.x >> 3);
+  const int m0 = tile % mt * TM, j0 = tile / mt * TN;
+  v16f acc[BM][BN];
+#pragma unroll
+  for (int p = 0; p < BM; ++p)
+#pragma unroll
+    for (int q = 0; q < BN; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[p][q][r] = 0.0f;
+  const int row0 = tid / TPR, c4 = tid % TPR, nk = (K + UPS_KT - 1) / UPS_KT;
+  const float *srcA[LA];
+  float sc[LA];
+  const uint4 *srcW[LW];
+#pragma unroll
+  for (int i = 0; i < LA; ++i) { // rows past the last one: loaded again, not stored
+    const int m = min(m0 + row0 + i * RPP, M - 1);
+    srcA[i] = A + (size_t)m * lda + 4 * c4;
+    sc[i] = sa[m];
+  }
+#pragma unroll
+  for (int i = 0; i < LW; ++i) srcW[i] = WS + (size_t)min(j0 + row0 + i * RPP, N - 1) * (nk * (UPS_KT / 4)) + c4;
+  unsigned char *const dst = smem + row0 * RB + 8 * c4;
+  f32x4u ra[LA];
+  uint4 rw[LW];
+  auto load = [&](int i, int step) { // the tiles in the order nk - 1, 0, 1, ... nk - 2
+    const int kt = min(step, nk - 1) - 1;
+    if (i < LA) ra[i < LA ? i : 0] = *reinterpret_cast<const f32x4u *>(srcA[i < LA ? i : 0] + kt * UPS_KT);
+    else rw[i < LA ? 0 : i - LA] = srcW[i < LA ? 0 : i - LA][kt * (UPS_KT / 4)];
+  };
+  auto put = [&](int i, int buf) {
+    uint2 h, l;
+    if (i < LA) {
+      const int k = i < LA ? i : 0;
+      split_fp16(ra[k][0] * sc[k], ra[k][1] * sc[k], h.x, l.x);
+      split_fp16(ra[k][2] * sc[k], ra[k][3] * sc[k], h.y, l.y);
+    } else {
+      const uint4 v = rw[i < LA ? 0 : i - LA];
+      h = make_uint2(v.x, v.y);
+      l = make_uint2(v.z, v.w);
+    }
+    unsigned char *d = dst + buf * BUF + i * RPP * RB;
+    *reinterpret_cast<uint2 *>(d) = h;
+    *reinterpret_cast<uint2 *>(d + 2 * UPS_KT) = l;
+  };
+  { // the last tile of K
+    const int k0 = (nk - 1) * UPS_KT;
+#pragma unroll
+    for (int i = 0; i < LA; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ra[i][e] = k0 + 4 * c4 + e < K ? srcA[i][k0 + e] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < LW; ++i) rw[i] = srcW[i][(nk - 1) * (UPS_KT / 4)];
+  }
+#pragma unroll
+  for (int i = 0; i < LD; ++i) put(i, 0);
+  if (nk > 1) {
+#pragma unroll
+    for (int i = 0; i < LD; ++i) load(i, 1);
+  }
+  __syncthreads();
+  const unsigned char *const pa = smem + (wm * BM * 32 + (lane & 31)) * RB + 16 * (lane >> 5);
+  const unsigned char *const pb = smem + (TM + wn * BN * 32 + (lane & 31)) * RB + 16 * (lane >> 5);
+  for (int step = 0; step < nk; ++step) {
+    const int cur = step & 1;
+    if (step > 0 && step % UPS_FLIP == 0) {
+#pragma unroll
+      for (int p = 0; p < BM; ++p)
+#pragma unroll
+        for (int q = 0; q < BN; ++q) acc[p][q] = -acc[p][q];
+    }
+    if ((step + 1) % UPS_FLIP == 0) { // the tile staged now is multiplied after the turn
+#pragma unroll
+      for (int i = 0; i < LA; ++i) sc[i] = -sc[i];
+    }
+    v8h a[2][2], b[BN][2], bn[BN][2]; // h and l
+    auto read_a = [&](int g) {
+#pragma unroll
+      for (int z = 0; z < 2; ++z) a[g & 1][z] = *reinterpret_cast<const v8h *>(pa + cur * BUF + g % BM * 32 * RB + 2 * UPS_KT * z + 32 * (g / BM));
+    };
+    auto read_b = [&](int ks, v8h (&dstb)[BN][2]) {
+#pragma unroll
+      for (int q = 0; q < BN; ++q)
+#pragma unroll
+        for (int z = 0; z < 2; ++z) dstb[q][z] = *reinterpret_cast<const v8h *>(pb + cur * BUF + q * 32 * RB + 2 * UPS_KT * z + 32 * ks);
+    };
+    read_b(0, b);
+    read_a(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) { // 16 k of 32 rows against the wavefront's columns
+      const int p = g % BM;
+      const bool turn = p == BM - 1 && g + 1 < NG;
+      if (g + 1 < NG) read_a(g + 1);
+      if (turn) read_b(g / BM + 1, bn);
+      v8h(&x)[2] = a[g & 1];
+#pragma unroll
+      for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], b[q][0], acc[p][q], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], b[q][1], acc[p][q], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], b[q][0], acc[p][q], 0, 0, 0);
+      if (nk > 1) {
+#pragma unroll
+        for (int i = g * LD / NG; i < (g + 1) * LD / NG; ++i) { // (past the last tile: the one before it once more, never read)
+          put(i, cur ^ 1);
+          load(i, step + 2);
+        }
+      }
+      if (turn) {
+#pragma unroll
+        for (int q = 0; q < BN; ++q) { b[q][0] = bn[q][0]; b[q][1] = bn[q][1]; }
+      }
+#pragma unroll
+      for (int z = 0; z < 3 * BN; ++z) { // one matrix instruction, then a share of the vector work
+        __builtin_amdgcn_sched_group_barrier(8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(2, (20 * LD / NG + 3 * BN - 1) / (3 * BN) + 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+  }
+  const uint32_t sign = (nk - 1) / UPS_FLIP % 2 ? 0x80000000u : 0u;
+#pragma unroll
+  for (int p = 0; p < BM; ++p)
+#pragma unroll
+    for (int q = 0; q < BN; ++q) {
+      const int j = j0 + (wn * BN + q) * 32 + (lane & 31);
+      const int ej = 254 - (int)(__float_as_uint(sw[min(j, N - 1)]) >> 23);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + (wm * BM + p) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const float v = ldexpf(acc[p][q][r], ej - (int)(__float_as_uint(sa[min(m, M - 1)]) >> 23));
+        if (m < M && j < N) C[(size_t)m * ldc + j] = __uint_as_float(__float_as_uint(v) ^ sign);
+      }
+    }
 }
 
 __device__ __forceinline__ void up_gemm16_body(const float *__restrict__ A, int lda, const float *__restrict__ W, int K,
@@ -5271,19 +5460,47 @@ static hipError_t launch_up_gemm(const float *A, int lda, const float *W, int K,
                                  hipStream_t s) {
   // Which of the two kernels runs may depend on the layer's shape and on alignments that are the same for every time
   // tile (lda % 4 == 0 makes the alignment of A independent of the slot it starts at), never on M: they add in different
-  // orders.  The tile of the LDS kernel may depend on M: every tile adds in the same order (see up_gemm_tile).
+  // orders.
   const bool aligned16 = K % 16 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
   if (aligned16 && (size_t)N * K <= 65536) {
     const int tiles = ((M + 15) / 16) * ((N + 15) / 16);
     hipLaunchKernelGGL(k_up_gemm16, dim3((tiles + 3) / 4), dim3(256), 0, s, A, lda, W, K, N, C, N, M);
-  } else if (const int tile = up_gemm_tile(M, N, K)) {
-    if (tile == 2)
-      hipLaunchKernelGGL((k_up_gemm<4, 4, 2, 2>), dim3((M + 255) / 256, (N + 255) / 256), dim3(1024), 0, s, A, lda, W, K, N, C, N, M);
-    else
-      hipLaunchKernelGGL((k_up_gemm<2, 2, 2, 2>), dim3((M + 127) / 128, (N + 127) / 128), dim3(256), 0, s, A, lda, W, K, N, C, N, M);
   } else // 64 x 64 tiles: measured faster than 32 x 32 blocks (one wavefront each) and than 128 x 64 up to 1024 x 1024
     hipLaunchKernelGGL((k_up_gemm<2, 2>), dim3((M + 63) / 64, (N + 63) / 64), dim3(256), 0, s, A, lda, W, K, N, C, N, M);
   return hipGetLastError();
+}
+
+// Layer whose W_in is W, if its products go through the split kernel (which by the layer's shape alone: the kernels differ in the
+// last bits, and every way of cutting the time axis must give the same); 0: none.
+static int split_layer(const NetDev &net, const float *W) {
+  for (int l = 1; l < net.L; ++l)
+    if (net.W_split[l] && net.W_in[l] == W) return l;
+  return 0;
+}
+template <int WM, int WN, int BM, int BN, int WPE>
+static hipError_t launch_up_split_t(const float *A, int lda, const float *sa, const NetDev &net, int l, float *C, int M, hipStream_t s) {
+  constexpr int TM = 32 * WM * BM, TN = 32 * WN * BN;
+  constexpr size_t lds = (size_t)2 * (TM + TN) * UPS_ROW_BYTES;
+  const auto kern = k_up_split<WM, WN, BM, BN, WPE>;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const int K = net.N[l], N = net.N[l - 1];
+  hipLaunchKernelGGL(kern, dim3((unsigned)(((M + TM - 1) / TM) * ((N + TN - 1) / TN))), dim3(64 * WM * WN), lds, s, A, lda, sa,
+                     net.W_split[l], net.W_scale[l], K, N, C, N, M);
+  return hipGetLastError();
+}
+// up_{l-1} = dv_l W_in_l^T for M rows.  Tiles as large as still give most compute units one (every tile adds in the same order): M = 2048,
+// N = K = 8192 706 us in tiles of 256 x 256, 957 in 128 x 128; M = 800, N = K = 2048 45 us in 208 tiles of 64 x 128, 60 in 112 of
+// 128 x 128 (the fp32 matrix cores: 57).
+static hipError_t launch_up_split(const NetDev &net, int l, const float *A, int lda, float *C, int M, hipStream_t s) {
+  if (M > SNN_BWD_TILE * net.B) return hipErrorInvalidValue; // what row_scale holds
+  const int N = net.N[l - 1];
+  float *const sa = net.row_scale + (size_t)l * SNN_BWD_TILE * net.B;
+  hipLaunchKernelGGL(k_row_scales, dim3((M + 3) / 4), dim3(256), 0, s, A, lda, net.N[l], M, sa);
+  const auto tiles = [&](int m, int n) { return ((M + m - 1) / m) * ((N + n - 1) / n); };
+  if (tiles(256, 256) >= 192) return launch_up_split_t<2, 4, 4, 2, 2>(A, lda, sa, net, l, C, M, s);
+  if (tiles(128, 128) >= 192) return launch_up_split_t<2, 4, 2, 1, 2>(A, lda, sa, net, l, C, M, s);
+  return launch_up_split_t<2, 4, 1, 1, 4>(A, lda, sa, net, l, C, M, s);
 }
 
 hipError_t launch_adjoint_head(const NetDev &net, int t0, int t1, int t_base, float *dubuf, const float *g,
@@ -5291,6 +5508,11 @@ hipError_t launch_adjoint_head(const NetDev &net, int t0, int t1, int t_base, fl
   if (t1 <= t0) return hipErrorInvalidValue;
   const int B = net.B, O = net.n_out, L = net.L;
   const size_t s0 = (size_t)(t0 - t_base);
+  if (carry_init) // the first tile of a step: the matrices of its products, split
+    for (int l = 1; l < L; ++l)
+      if (net.W_split[l])
+        hipLaunchKernelGGL(k_split_rows, dim3((net.N[l - 1] + 3) / 4), dim3(256), 0, s, net.W_in[l], net.N[l], net.N[l - 1], net.W_split[l],
+                           net.W_scale[l]);
   hipLaunchKernelGGL(k_du_scan, dim3((B * O + 255) / 256), dim3(256), 0, s, g, carry, dubuf, B, O, net.SN, t0, t1,
                      t_base, net.beta, carry_init);
   if (hook) hook->begin(hook->ctx, 6);
@@ -5304,8 +5526,9 @@ hipError_t launch_up_product(const NetDev &net, int l, int t0, int t1, int t_bas
   if (t1 <= t0 || l < 0 || l + 1 >= net.L) return hipErrorInvalidValue;
   const size_t s0 = (size_t)(t0 - t_base);
   if (hook) hook->begin(hook->ctx, 6);
-  const hipError_t e = launch_up_gemm(vbuf + s0 * ((size_t)net.B * net.SN) + net.off[l + 1], net.SN, net.W_in[l + 1],
-                                      net.N[l + 1], net.N[l], up_l, (t1 - t0) * net.B, s);
+  const float *const dv = vbuf + s0 * ((size_t)net.B * net.SN) + net.off[l + 1];
+  const hipError_t e = net.W_split[l + 1] ? launch_up_split(net, l + 1, dv, net.SN, up_l, (t1 - t0) * net.B, s)
+                                          : launch_up_gemm(dv, net.SN, net.W_in[l + 1], net.N[l + 1], net.N[l], up_l, (t1 - t0) * net.B, s);
   if (hook) hook->end(hook->ctx);
   return e;
 }
@@ -5903,10 +6126,6 @@ static void plan_gemm(GemmJob *gj) {
     gj->kind = 0;
     gj->tiles_m = (gj->M + 15) / 16;
     gj->n_blocks = (gj->tiles_m * ((gj->N + 15) / 16) + 3) / 4;
-  } else if (up_gemm_tile(gj->M, gj->N, gj->K)) {
-    gj->kind = 2;
-    gj->tiles_m = (gj->M + 127) / 128;
-    gj->n_blocks = gj->tiles_m * ((gj->N + 127) / 128);
   } else {
     gj->kind = 1;
     gj->tiles_m = (gj->M + 63) / 64;
@@ -5927,19 +6146,16 @@ hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, cons
   }
   if (hook) hook->begin(hook->ctx, 6);
   for (int q = 0; q < ij.n_gemm; ++q) {
-    plan_gemm(&ij.g[q]);
-    if (ij.g[q].kind == 2) {
-      // products of large matrices fill the chip by themselves and want the registers of the 128 x 128 tiles:
-      // launches of their own, the fused launch keeps the rest
-      const GemmJob &gj = ij.g[q];
-      if (up_gemm_tile(gj.M, gj.N, gj.K) == 2)
-        hipLaunchKernelGGL((k_up_gemm<4, 4, 2, 2>), dim3((gj.M + 255) / 256, (gj.N + 255) / 256), dim3(1024), 0, s, gj.A, gj.lda,
-                           gj.W, gj.K, gj.N, gj.C, gj.N, gj.M);
-      else
-        hipLaunchKernelGGL((k_up_gemm<2, 2, 2, 2>), dim3(gj.tiles_m, (gj.N + 127) / 128), dim3(256), 0, s, gj.A, gj.lda, gj.W,
-                           gj.K, gj.N, gj.C, gj.N, gj.M);
+    const GemmJob &gj = ij.g[q];
+    if (const int l = split_layer(net, gj.W)) { // fills the chip by itself: a launch of its own, the fused launch keeps the rest
+      const hipError_t e = launch_up_split(net, l, gj.A, gj.lda, gj.C, gj.M, s);
+      if (e != hipSuccess) {
+        if (hook) hook->end(hook->ctx);
+        return e;
+      }
       continue;
     }
+    plan_gemm(&ij.g[q]);
     grid += ij.g[q].n_blocks;
     ij.g[kept++] = ij.g[q];
   }

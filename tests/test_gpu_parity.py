@@ -428,6 +428,36 @@ def test_streamed_chip_wide_adjoint(hidden, B, T, monkeypatch):
         assert float(np.max(np.abs(a - b))) <= 1e-4 * scale
 
 
+@pytest.mark.parametrize("hidden,B,T,scale", [((2049, 2100), 3, 6, 1.0),  # a ragged last tile of both widths
+                                              ((2048, 2049), 7, 5, 1e-28),  # gradients near the smallest fp32 values
+                                              ((2080, 2048), 40, 21, 1.0),  # tiles of 128 x 128
+                                              ((4160, 4096), 64, 50, 1.0)])  # tiles of 256 x 256
+def test_split_inter_layer_products(hidden, B, T, scale, monkeypatch):
+    """Products of large matrices from fp16 halves on the matrix cores.  The split loses 2^-24 of an element and the sums of 2048 to
+    4160 products round like fp32 ones: an error of 1e-6 of the product in the 2-norm, which the gradients below the product
+    (sums over steps and batch) can only carry on.  Strategies bit-identical, whatever the tiles."""
+    w = synth.Workload("split_" + "x".join(map(str, hidden)), 40, hidden, 7, T=T, B=B, p_in=0.1, gain=0.5, seed=17 + B)
+    d = synth.generate(w)
+    d["W_out"] = (d["W_out"] * np.float32(scale)).astype(np.float32)
+    ref = _oracle(w, d, want_v=True, nthreads=8, backward=False)
+    ref64 = _oracle_f64_on_f32_trajectory(w, d, ref, 8)
+    net = snn.from_workload(w, d)
+    try:
+        net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+        first = None
+        for strat, C, F in [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 3), (snn.SNN_DOUBLE, min(T, 16), 4)]:
+            net.snn_bptt(strat, C, F)
+            g = _gpu_grads(net, 2)
+            assert first is None or _identical(g, first), (strat, C, F)
+            first = g
+    finally:
+        net.snn_destroy()
+    for got, exp in ((first[0][0], ref64.dW_in[0]), (first[1][0], ref64.dW_rec[0])):
+        err = np.linalg.norm(got.astype(np.float64) - exp) / np.linalg.norm(exp)
+        print(hidden, B, T, scale, err)
+        assert err <= 2e-6
+
+
 @pytest.mark.parametrize("hidden,B,T,density,csr", [
     ((1025,), 3, 70, 1.0, None),           # one neuron in the last spike word
     ((1500, 1100), 5, 40, 1.0, None),      # two widths in one launch
