@@ -924,6 +924,52 @@ def test_graph_replay_follows_a_change_of_the_recurrent_mask():
         net.snn_destroy()
 
 
+@pytest.mark.parametrize("hidden,density", [((96, 96), 1.0), ((96, 300), 0.3), ((1100,), 0.2)])
+def test_graph_replay_after_new_weights(hidden, density):
+    """A recorded step is replayed with whatever weights the context holds: after every hand-over (other values; under the same mask;
+    under another mask of as many synapses, one of which fills a row) the gradients of a context that has seen nothing else."""
+    w = synth.Workload("reweigh_" + "x".join(map(str, hidden)), 40, hidden, 5, T=30, B=4, p_in=0.1, gain=0.8, rec_density=density, seed=19)
+    d = synth.generate(w)
+    L = len(hidden)
+    other = {k: ([np.ascontiguousarray(x * np.float32(0.7)) for x in v] if k.startswith("W_") and k != "W_out" else v) for k, v in d.items()}
+    other["W_out"] = d["W_out"] * np.float32(1.3)
+    turned = dict(other)
+    if density < 1.0:
+        turned["rec_mask"] = [np.ascontiguousarray(m[::-1, ::-1]) for m in d["rec_mask"]]
+        for m in turned["rec_mask"]:
+            empty = np.argwhere(m == 0)
+            m[tuple(np.argwhere(m[1:] == 1)[: (m[0] == 0).sum()].T + np.array([[1], [0]]))] = 0
+            m[0] = 1
+            assert len(empty) == (m == 0).sum()
+        turned["W_rec"] = [np.ascontiguousarray(x * m) for x, m in zip(other["W_rec"], turned["rec_mask"])]
+
+    def hand_over(net, d):
+        for l in range(L):
+            net.snn_set_weights(snn.SNN_W_IN, l, d["W_in"][l])
+            net.snn_set_weights(snn.SNN_W_REC, l, d["W_rec"][l], d["rec_mask"][l] if density < 1.0 else None)
+        net.snn_set_weights(snn.SNN_W_OUT, 0, d["W_out"])
+
+    def step(net):
+        net.snn_bptt(snn.SNN_DOUBLE, 12, 4, want_stats=False)
+        return _gpu_grads(net, L)
+    net = snn.from_workload(w, d)
+    try:
+        net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+        step(net)
+        for now in (other, turned, d):
+            hand_over(net, now)
+            got = step(net), step(net)
+            fresh = snn.from_workload(w, now)
+            try:
+                fresh.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+                want = step(fresh)
+            finally:
+                fresh.snn_destroy()
+            assert _identical(got[0], want) and _identical(got[1], want)
+    finally:
+        net.snn_destroy()
+
+
 @pytest.mark.library_chunks
 def test_suggested_intervals_train_within_the_budget():
     """Intervals picked by snn_suggest_intervals for a budget: the step runs inside that budget and gives the
