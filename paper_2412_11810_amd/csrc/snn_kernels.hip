@@ -2079,7 +2079,7 @@ k_up_gemm(const float *__restrict__ A, int lda, const float *__restrict__ W, int
           int ldc, int M) {
   up_gemm_body<WM, WN>(A, lda, W, K, N, C, ldc, M, (int)blockIdx.x, (int)blockIdx.y);
 }
-// The same product for large matrices (2048 x 2048 and more) on the fp16 matrix cores.  An fp32 value is the sum of two fp16 ones to
+// The same product for large matrices (1024 x 1024 and more) on the fp16 matrix cores.  An fp32 value is the sum of two fp16 ones to
 // within 2^-24 of itself, h = fp16(x) and l = fp16(x - h), as long as neither leaves fp16's range: every row of both operands is
 // scaled by the power of two that brings its largest magnitude to 2^14 ... 2^15 (and the result scaled back exactly), so an
 // element 2^-16 below its row's largest still has all its bits and a smaller one is off by 2^-40 of that largest.  Then
@@ -2122,12 +2122,16 @@ static __device__ __forceinline__ float row_max(const float *__restrict__ r, int
   for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
   return mx;
 }
+// The products of a launch (of the layers of a stage, independent of each other): C = A W^T
+struct SplitJob { const float *A; float *sa; const uint4 *WS; const float *sw; float *C; int lda, K, N, M, tile0; };
+struct SplitJobs { SplitJob j[SNN_MAXL]; int count; };
 __global__ void __launch_bounds__(256) // a wavefront per row: bound by reading A once (13 us for 67 MB)
-k_row_scales(const float *__restrict__ A, int lda, int K, int M, float *__restrict__ scale) {
+k_row_scales(SplitJobs jobs) {
+  const SplitJob &jb = jobs.j[blockIdx.y];
   const int m = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = lane_id();
-  if (m >= M) return;
-  const float mx = row_max(A + (size_t)m * lda, K, lane);
-  if (lane == 0) scale[m] = row_scale(mx);
+  if (m >= jb.M) return;
+  const float mx = row_max(jb.A + (size_t)m * jb.lda, jb.K, lane);
+  if (lane == 0) jb.sa[m] = row_scale(mx);
 }
 __global__ void __launch_bounds__(256) // a wavefront per row; the second look at the row comes from the caches
 k_split_rows(const float *__restrict__ W, int K, int N, uint4 *__restrict__ WS, float *__restrict__ scale) {
@@ -2151,16 +2155,22 @@ k_split_rows(const float *__restrict__ W, int K, int N, uint4 *__restrict__ WS, 
 #define UPS_FLIP 8                     // K tiles between two turns of the sign
 template <int WM, int WN, int BM, int BN, int WPE> // wavefronts and their blocks of 32 x 32; wavefronts per SIMD
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-k_up_split(const float *__restrict__ A, int lda, const float *__restrict__ sa, const uint4 *__restrict__ WS, const float *__restrict__ sw,
-           int K, int N, float *__restrict__ C, int ldc, int M) {
+k_up_split(SplitJobs jobs) {
   constexpr int NT = 64 * WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN, TPR = UPS_KT / 4, RPP = NT / TPR; // threads per row, rows per pass
   constexpr int LA = TM / RPP, LW = TN / RPP, LD = LA + LW, NG = UPS_KT / 16 * BM, RB = UPS_ROW_BYTES, BUF = (TM + TN) * RB;
   static_assert(TM % RPP == 0 && TN % RPP == 0, "whole passes");
   extern __shared__ __align__(16) unsigned char smem[]; // [2][TM + TN][RB]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave % WM, wn = wave / WM;
   // a die (workgroup number modulo 8) gets neighbouring tiles, rows fastest: its L2 holds their columns of W for all of them
-  const int mt = (M + TM - 1) / TM, total = (int)gridDim.x, die = (int)blockIdx.x & 7, rest = total & 7;
-  const int tile = die * (total >> 3) + min(die, rest) + (int)(blockIdx.x >> 3);
+  const int total = (int)gridDim.x, die = (int)blockIdx.x & 7, rest = total & 7;
+  int tile = die * (total >> 3) + min(die, rest) + (int)(blockIdx.x >> 3), jq = 0;
+  while (jq + 1 < jobs.count && tile >= jobs.j[jq + 1].tile0) ++jq;
+  const SplitJob &jb = jobs.j[jq];
+  const float *__restrict__ const A = jb.A, *__restrict__ const sa = jb.sa, *__restrict__ const sw = jb.sw;
+  const uint4 *__restrict__ const WS = jb.WS;
+  float *__restrict__ const C = jb.C;
+  const int K = jb.K, N = jb.N, M = jb.M, lda = jb.lda, mt = (M + TM - 1) / TM;
+  tile -= jb.tile0;
   const int m0 = tile % mt * TM, j0 = tile / mt * TN;
   v16f acc[BM][BN];
 #pragma unroll
@@ -2292,7 +2302,7 @@ k_up_split(const float *__restrict__ A, int lda, const float *__restrict__ sa, c
       for (int r = 0; r < 16; ++r) {
         const int m = m0 + (wm * BM + p) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         const float v = ldexpf(acc[p][q][r], ej - (int)(__float_as_uint(sa[min(m, M - 1)]) >> 23));
-        if (m < M && j < N) C[(size_t)m * ldc + j] = __uint_as_float(__float_as_uint(v) ^ sign);
+        if (m < M && j < N) C[(size_t)m * N + j] = __uint_as_float(__float_as_uint(v) ^ sign);
       }
     }
 }
@@ -5477,30 +5487,44 @@ static int split_layer(const NetDev &net, const float *W) {
     if (net.W_split[l] && net.W_in[l] == W) return l;
   return 0;
 }
+static void add_split_job(const NetDev &net, SplitJobs *jobs, int l, const float *A, int lda, float *C, int M) {
+  jobs->j[jobs->count++] = SplitJob{A, net.row_scale + (size_t)l * SNN_BWD_TILE * net.B, net.W_split[l], net.W_scale[l], C, lda, net.N[l],
+                                    net.N[l - 1], M, 0};
+}
 template <int WM, int WN, int BM, int BN, int WPE>
-static hipError_t launch_up_split_t(const float *A, int lda, const float *sa, const NetDev &net, int l, float *C, int M, hipStream_t s) {
+static hipError_t launch_up_split_t(SplitJobs jobs, hipStream_t s) {
   constexpr int TM = 32 * WM * BM, TN = 32 * WN * BN;
   constexpr size_t lds = (size_t)2 * (TM + TN) * UPS_ROW_BYTES;
   const auto kern = k_up_split<WM, WN, BM, BN, WPE>;
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  const int K = net.N[l], N = net.N[l - 1];
-  hipLaunchKernelGGL(kern, dim3((unsigned)(((M + TM - 1) / TM) * ((N + TN - 1) / TN))), dim3(64 * WM * WN), lds, s, A, lda, sa,
-                     net.W_split[l], net.W_scale[l], K, N, C, N, M);
+  int total = 0;
+  for (int k = 0; k < jobs.count; ++k) {
+    jobs.j[k].tile0 = total;
+    total += ((jobs.j[k].M + TM - 1) / TM) * ((jobs.j[k].N + TN - 1) / TN);
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WM * WN), lds, s, jobs);
   return hipGetLastError();
 }
-// up_{l-1} = dv_l W_in_l^T for M rows.  Tiles as large as still give most compute units one (every tile adds in the same order): M = 2048,
+// Tiles as large as still give most compute units one (every tile adds in the same order): M = 2048,
 // N = K = 8192 706 us in tiles of 256 x 256, 957 in 128 x 128; M = 800, N = K = 2048 45 us in 208 tiles of 64 x 128, 60 in 112 of
 // 128 x 128 (the fp32 matrix cores: 57).
-static hipError_t launch_up_split(const NetDev &net, int l, const float *A, int lda, float *C, int M, hipStream_t s) {
-  if (M > SNN_BWD_TILE * net.B) return hipErrorInvalidValue; // what row_scale holds
-  const int N = net.N[l - 1];
-  float *const sa = net.row_scale + (size_t)l * SNN_BWD_TILE * net.B;
-  hipLaunchKernelGGL(k_row_scales, dim3((M + 3) / 4), dim3(256), 0, s, A, lda, net.N[l], M, sa);
-  const auto tiles = [&](int m, int n) { return ((M + m - 1) / m) * ((N + n - 1) / n); };
-  if (tiles(256, 256) >= 192) return launch_up_split_t<2, 4, 4, 2, 2>(A, lda, sa, net, l, C, M, s);
-  if (tiles(128, 128) >= 192) return launch_up_split_t<2, 4, 2, 1, 2>(A, lda, sa, net, l, C, M, s);
-  return launch_up_split_t<2, 4, 1, 1, 4>(A, lda, sa, net, l, C, M, s);
+static hipError_t launch_up_split(const NetDev &net, const SplitJobs &jobs, hipStream_t s) {
+  if (jobs.count <= 0) return hipSuccess;
+  int most = 0;
+  for (int k = 0; k < jobs.count; ++k) {
+    if (jobs.j[k].M > SNN_BWD_TILE * net.B) return hipErrorInvalidValue; // what row_scale holds
+    most = std::max(most, jobs.j[k].M);
+  }
+  hipLaunchKernelGGL(k_row_scales, dim3((unsigned)(most + 3) / 4, jobs.count), dim3(256), 0, s, jobs);
+  const auto tiles = [&](int m, int n) {
+    int sum = 0;
+    for (int k = 0; k < jobs.count; ++k) sum += ((jobs.j[k].M + m - 1) / m) * ((jobs.j[k].N + n - 1) / n);
+    return sum;
+  };
+  if (tiles(256, 256) >= 192) return launch_up_split_t<2, 4, 4, 2, 2>(jobs, s);
+  if (tiles(128, 128) >= 192) return launch_up_split_t<2, 4, 2, 1, 2>(jobs, s);
+  return launch_up_split_t<2, 4, 1, 1, 4>(jobs, s);
 }
 
 hipError_t launch_adjoint_head(const NetDev &net, int t0, int t1, int t_base, float *dubuf, const float *g,
@@ -5527,8 +5551,10 @@ hipError_t launch_up_product(const NetDev &net, int l, int t0, int t1, int t_bas
   const size_t s0 = (size_t)(t0 - t_base);
   if (hook) hook->begin(hook->ctx, 6);
   const float *const dv = vbuf + s0 * ((size_t)net.B * net.SN) + net.off[l + 1];
-  const hipError_t e = net.W_split[l + 1] ? launch_up_split(net, l + 1, dv, net.SN, up_l, (t1 - t0) * net.B, s)
-                                          : launch_up_gemm(dv, net.SN, net.W_in[l + 1], net.N[l + 1], net.N[l], up_l, (t1 - t0) * net.B, s);
+  SplitJobs sj{};
+  if (net.W_split[l + 1]) add_split_job(net, &sj, l + 1, dv, net.SN, up_l, (t1 - t0) * net.B);
+  const hipError_t e = sj.count ? launch_up_split(net, sj, s)
+                                : launch_up_gemm(dv, net.SN, net.W_in[l + 1], net.N[l + 1], net.N[l], up_l, (t1 - t0) * net.B, s);
   if (hook) hook->end(hook->ctx);
   return e;
 }
@@ -6145,14 +6171,11 @@ hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, cons
     if (e != hipSuccess) return e;
   }
   if (hook) hook->begin(hook->ctx, 6);
+  SplitJobs sj{};
   for (int q = 0; q < ij.n_gemm; ++q) {
     const GemmJob &gj = ij.g[q];
-    if (const int l = split_layer(net, gj.W)) { // fills the chip by itself: a launch of its own, the fused launch keeps the rest
-      const hipError_t e = launch_up_split(net, l, gj.A, gj.lda, gj.C, gj.M, s);
-      if (e != hipSuccess) {
-        if (hook) hook->end(hook->ctx);
-        return e;
-      }
+    if (const int l = split_layer(net, gj.W)) { // launches of their own, the fused launch keeps the rest
+      add_split_job(net, &sj, l, gj.A, gj.lda, gj.C, gj.M);
       continue;
     }
     plan_gemm(&ij.g[q]);
@@ -6161,6 +6184,13 @@ hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, cons
   }
   ij.n_gemm = kept;
   grid += pre.cur_gx * pre.cur.count + pre.n_scan;
+  {
+    const hipError_t e = launch_up_split(net, sj, s);
+    if (e != hipSuccess) {
+      if (hook) hook->end(hook->ctx);
+      return e;
+    }
+  }
   if (grid > 0) {
     hipError_t e = hipSuccess;
     if (lds > 32 * 1024)

@@ -7,9 +7,10 @@
 
 // ---- inter-layer products of the adjoint pass -----------------------------------------------------
 // N neurons below, K above: split into fp16 halves (k_up_split) or on the fp32 matrix cores.  The same kernel for every number of
-// rows: they differ in the last bits, and gradients must not depend on how the time axis is cut.  800 rows: 2048 x 2048 45 against
-// 57 us and 4 us for the scales; 1500 x 1100 (1536 rows) 37 against 35.
-inline bool split_product(int N, int K) { return N >= 2048 && K >= 2048; }
+// rows: they differ in the last bits, and gradients must not depend on how the time axis is cut.  From 1024 neurons the split one is
+// never slower (training steps, two layers: 1024 neurons, batch 4 / 16 / 64 3.73 / 4.30 / 6.84 -> 3.74 / 4.30 / 6.54 ms; 1500-1100,
+// batch 8 / 24 3.14 / 3.82 -> 3.14 / 3.73); 512 and 700 neurons gain nothing below batch 64.
+inline bool split_product(int N, int K) { return N >= 1024 && K >= 1024; }
 constexpr size_t split_row_bytes(int K) { return (size_t)(K + 31) / 32 * 128; } // of a split matrix: whole tiles of 32 elements
 
 // ---- sequential forward part of layers of 257..1024 neurons (k_layer_seq_lds) --------------------

@@ -428,12 +428,13 @@ def test_streamed_chip_wide_adjoint(hidden, B, T, monkeypatch):
         assert float(np.max(np.abs(a - b))) <= 1e-4 * scale
 
 
-@pytest.mark.parametrize("hidden,B,T,scale", [((2049, 2100), 3, 6, 1.0),  # a ragged last tile of both widths
+@pytest.mark.parametrize("hidden,B,T,scale", [((1025, 1100, 1030), 3, 6, 1.0),  # ragged last tiles of all widths, two products in a launch
+                                              ((2049, 2100), 3, 6, 1.0),
                                               ((2048, 2049), 7, 5, 1e-28),  # gradients near the smallest fp32 values
                                               ((2080, 2048), 40, 21, 1.0),  # tiles of 128 x 128
                                               ((4160, 4096), 64, 50, 1.0)])  # tiles of 256 x 256
 def test_split_inter_layer_products(hidden, B, T, scale, monkeypatch):
-    """Products of large matrices from fp16 halves on the matrix cores.  The split loses 2^-24 of an element and the sums of 2048 to
+    """Products of large matrices from fp16 halves on the matrix cores.  The split loses 2^-24 of an element and the sums of 1025 to
     4160 products round like fp32 ones: an error of 1e-6 of the product in the 2-norm, which the gradients below the product
     (sums over steps and batch) can only carry on.  Strategies bit-identical, whatever the tiles."""
     w = synth.Workload("split_" + "x".join(map(str, hidden)), 40, hidden, 7, T=T, B=B, p_in=0.1, gain=0.5, seed=17 + B)
@@ -447,7 +448,7 @@ def test_split_inter_layer_products(hidden, B, T, scale, monkeypatch):
         first = None
         for strat, C, F in [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 3), (snn.SNN_DOUBLE, min(T, 16), 4)]:
             net.snn_bptt(strat, C, F)
-            g = _gpu_grads(net, 2)
+            g = _gpu_grads(net, len(hidden))
             assert first is None or _identical(g, first), (strat, C, F)
             first = g
     finally:
