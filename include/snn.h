@@ -316,9 +316,11 @@ void snn_destroy(snn_ctx *ctx);
  *                                      the rows in memory (default up to 1024 neurons: slices of the matrix in LDS)
  *     SNN_FWD_FUSE=0                   wide layers over compressed rows: the dense currents for the next pipeline
  *                                      stage never ride in the launch of a stage's sequential parts
- *     SNN_SEQ_KERNEL=gather|rs         sequential forward part of layers of up to 256 neurons: event-driven gather
+ *     SNN_SEQ_KERNEL=gather|rs|col     sequential forward part of layers of up to 256 neurons: event-driven gather
  *                                      over the rows of the neurons that fired / the register-stationary chain
- *                                      (default: the chain; the gather was measured slower at every firing rate)
+ *                                      (default: the chain; the gather was measured slower at every firing rate); of masked
+ *                                      layers of 32 MB and more: by row (gather, rs) / by column wherever it can run
+ *                                      (default: by the densities and the activity of the last call)
  */
 
 #ifdef __cplusplus

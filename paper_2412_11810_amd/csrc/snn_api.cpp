@@ -44,7 +44,7 @@ struct snn_ctx {
   uint16_t *csr_col[SNN_MAXL]{};
   float *csr_val[SNN_MAXL]{};
   uint64_t *csr_pk[SNN_MAXL]{};
-  size_t csr_nnz[SNN_MAXL]{};
+  size_t csr_nnz[SNN_MAXL]{}, csr_ell[SNN_MAXL]{};
   // fp64 gradient accumulators per existing synapse, in compressed-row order (k_dw_csr); csr_dw_ok: the entries
   // beyond the 64 per row and sub-range that kernel keeps in registers fit its LDS (64 per 16 rows and sub-range)
   double *acc_csr[SNN_MAXL]{};
@@ -208,7 +208,7 @@ bool dw_rec_csr(const snn_ctx *c, int l) {
 void read_kernel_hooks(snn_ctx *c) {
   NetDev &n = c->net;
   n.sel_currents = n.sel_adjoint = n.sel_slices = n.sel_csr = n.sel_seq = 0;
-  if (const char *e = std::getenv("SNN_SEQ_KERNEL")) n.sel_seq = !std::strcmp(e, "gather") ? 1 : !std::strcmp(e, "rs") ? 2 : 0;
+  if (const char *e = std::getenv("SNN_SEQ_KERNEL")) n.sel_seq = !std::strcmp(e, "gather") ? 1 : !std::strcmp(e, "rs") ? 2 : !std::strcmp(e, "col") ? 3 : 0;
   n.no_fwd_fuse = 0;
   if (const char *e = std::getenv("SNN_FWD_FUSE")) n.no_fwd_fuse = !std::strcmp(e, "0") ? 1 : 0;
   if (const char *e = std::getenv("SNN_CSR")) n.sel_csr = !std::strcmp(e, "0") ? 1 : !std::strcmp(e, "1") ? 2 : 0;
@@ -218,6 +218,7 @@ void read_kernel_hooks(snn_ctx *c) {
     n.csr_col[l] = on ? c->csr_col[l] : nullptr;
     n.csr_val[l] = on ? c->csr_val[l] : nullptr;
     n.csr_nnz[l] = on ? (uint32_t)c->csr_nnz[l] : 0u;
+    n.csr_ell[l] = on ? (uint32_t)c->csr_ell[l] : 0u;
     n.csr_pk[l] = on ? c->csr_pk[l] : nullptr;
   }
   if (const char *e = std::getenv("SNN_CURRENTS"))
@@ -283,7 +284,7 @@ size_t spike_bytes(const NetDev &n, int T, int ring = 0) {
 void free_csr(snn_ctx *c, int l) {
   (void)hipFree(c->csr_sub[l]); (void)hipFree(c->csr_col[l]); (void)hipFree(c->csr_val[l]); (void)hipFree(c->acc_csr[l]);
   (void)hipFree(c->csr_pk[l]);
-  c->csr_sub[l] = nullptr; c->csr_col[l] = nullptr; c->csr_val[l] = nullptr; c->csr_pk[l] = nullptr; c->csr_nnz[l] = 0;
+  c->csr_sub[l] = nullptr; c->csr_col[l] = nullptr; c->csr_val[l] = nullptr; c->csr_pk[l] = nullptr; c->csr_nnz[l] = c->csr_ell[l] = 0;
   c->acc_csr[l] = nullptr; c->csr_dw_ok[l] = false;
 }
 
@@ -296,22 +297,23 @@ snn_status build_csr(snn_ctx *c, int l) {
   unsigned long long *out = c->counters; // at least two words
   unsigned long long found[2] = {0, 0};
   hipError_t e = hipSuccess;
-  if (!c->csr_sub[l]) e = hipMalloc(&c->csr_sub[l], (size_t)N * (nsub + 1) * 4);
+  const size_t slices = csr_by_column(N) ? (size_t)(N + 63) / 64 : 0; // of the form by column: their positions follow
+  if (!c->csr_sub[l]) e = hipMalloc(&c->csr_sub[l], ((size_t)N * (nsub + 1) + slices * 257 + 1) * 4);
   if (e == hipSuccess) e = launch_csr_count(c->rec_mask[l], N, c->csr_sub[l], out, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(found, out, sizeof found, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  const size_t nnz = (size_t)found[0];
+  const size_t nnz = (size_t)found[0], ell = slices ? (size_t)(found[1] >> 32) : 0;
   if (e == hipSuccess && nnz > 0x1FF00000ull) {
     free_csr(c, l);
     return fail(c, SNN_E_INVAL, "recurrent matrix has too many synapses for 32-bit byte offsets of its entries");
   }
-  if (e == hipSuccess && (!c->csr_pk[l] || c->csr_nnz[l] != nnz)) {
+  if (e == hipSuccess && (!c->csr_pk[l] || c->csr_nnz[l] != nnz || c->csr_ell[l] != ell)) {
     (void)hipFree(c->csr_col[l]); (void)hipFree(c->csr_val[l]); (void)hipFree(c->csr_pk[l]); (void)hipFree(c->acc_csr[l]);
     c->csr_col[l] = nullptr; c->csr_val[l] = nullptr; c->csr_pk[l] = nullptr; c->acc_csr[l] = nullptr;
     e = hipMalloc(&c->csr_col[l], (nnz + 1) * 2);
     if (e == hipSuccess) e = hipMalloc(&c->csr_val[l], (nnz + 1) * 4);
     if (e == hipSuccess) e = hipMalloc(&c->acc_csr[l], (nnz + 1) * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&c->csr_pk[l], (nnz + (size_t)nsub * 64) * 8);
+    if (e == hipSuccess) e = hipMalloc(&c->csr_pk[l], (nnz + (size_t)nsub * 64 + ell * 8 * 64) * 8);
   }
   if (e == hipSuccess)
     e = launch_csr_fill(c->rec_mask[l], c->W_rec[l], N, (uint32_t)nnz, c->csr_sub[l], c->csr_col[l], c->csr_val[l], c->csr_pk[l], c->stream);
@@ -319,8 +321,9 @@ snn_status build_csr(snn_ctx *c, int l) {
     free_csr(c, l);
     return fail(c, SNN_E_HIP, std::string("compressed rows: ") + hipGetErrorString(e));
   }
-  c->csr_dw_ok[l] = found[1] == 0;
+  c->csr_dw_ok[l] = (uint32_t)found[1] == 0;
   c->csr_nnz[l] = nnz;
+  c->csr_ell[l] = ell;
   return SNN_OK;
 }
 
@@ -528,7 +531,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       const size_t n_bar = (size_t)64 * SNN_MAXL + 16; // counters + error flag, padded to a multiple of 64 bytes
       // (the batch in whole groups of 16; the kernel for layers wider than 1024 takes 1, 2 or 4 of them)
       const size_t bp = nmax > 1024 && B <= 64 ? (size_t)((B + 15) / 16 == 3 ? 4 : (B + 15) / 16) * 16 : (size_t)((B + 15) / 16) * 16;
-      const size_t xg_stride = ((size_t)4 * bp * ((nmax + 3) & ~3) + 15) & ~(size_t)15; // four steps of values in flight, whole 16 bytes
+      const size_t xg_stride = ((size_t)4 * bp * ((nmax + 3) & ~3) + 31) & ~(size_t)31; // four steps of values in flight, whole cache lines
       // (+ 16 KB: the forward pass's exchange of spike words shares the buffer)
       const size_t bytes = n_bar * sizeof(unsigned) + (size_t)SNN_MAXL * xg_stride * 4 + 16384;
       void *blk = uncached_block(cfg->device, bytes);
@@ -949,12 +952,14 @@ snn_status snn_forward(snn_ctx *c, const uint8_t *in_spikes, const int32_t *labe
     s = forward_only(c, nullptr);
     if (s != SNN_OK) return s;
   }
-  // (with the counts that the next call chooses its kernels by, where lists of active neurons may be walked)
-  if (c->net.lists) HIPCHK(c, queue_spike_counts(c, T, c->net.L));
+  // (with the counts that the next call chooses its kernels by, where lists of active neurons or a matrix by column may be walked)
+  bool count = c->net.lists != nullptr;
+  for (int l = 0; l < c->net.L; ++l) count = count || c->net.csr_ell[l] > 0;
+  if (count) HIPCHK(c, queue_spike_counts(c, T, c->net.L));
   HIPCHK(c, hipMemcpyAsync(c->host_small, c->loss_dev, 16 + 8 * (SNN_MAXL + 1), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (loss_out) std::memcpy(loss_out, c->host_small, sizeof *loss_out);
-  if (c->net.lists) {
+  if (count) {
     double r[SNN_MAXL + 1];
     set_rates(c, reinterpret_cast<const unsigned long long *>(c->host_small + 16), T, r);
   }

@@ -49,6 +49,8 @@ struct NetDev {
   // (r + 1) * SNN_CSR_SUBW + k: where a lane has no entry of a row it loads this one, and the add goes to word k of
   // the 64 spare words that follow the SNN_CSR_SUBW accumulators of sub-range r in LDS.
   const uint64_t *csr_pk[SNN_MAXL];
+  // ... and once more by column, behind the packed copy (see k_ell_fill), positions behind csr_sub's: groups of entries in all (0: not kept)
+  uint32_t csr_ell[SNN_MAXL];
   float alpha, beta, theta, k;
   float win;  // surrogate window (<= 0: none)
   // Current kernel for the layers whose weights are far beyond the L2, from the firing rates of the last step
@@ -71,7 +73,8 @@ struct NetDev {
   unsigned char sel_currents, sel_adjoint, sel_slices;
   unsigned char no_fwd_fuse; // 1: the dense currents of wide layers never ride in the launch of the sequential parts
   // Sequential forward part of layers of up to 256 neurons: sel_seq 1 forces the event-driven gather, 2 the
-  // register-stationary chain, 0 follows seq_pol[l] (1: gather; set from the measured firing rates).
+  // register-stationary chain, 0 follows seq_pol[l] (1: gather; set from the measured firing rates).  Of layers kept by column: 1 and 2
+  // the walk over rows, 3 the one over columns, 0 by the activity.
   unsigned char sel_seq, seq_pol[SNN_MAXL];
   // Space for the lists of active neurons that k_currents_lists walks (NULL: the matrix-core kernels instead), in entries
   uint16_t *lists;
@@ -146,7 +149,7 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
 // Recompute pass over steps t0+1..t1 from state_in = x_{t0}, spikes read from the stored bitmasks:
 // currents of the whole range in parallel into buf (slot of x_t = t - t_base - 1), then a scan that
 // turns them into states in place (store_all) and/or writes x_{t1} to state_out.
-unsigned currents_choice(const NetDev &net, int chunk); // bits: lists for a forward stage, for the recompute of a chunk
+unsigned currents_choice(const NetDev &net, int chunk); // bits: lists for a forward stage, for the recompute of a chunk; masked layers by column
 size_t currents_lists_entries(const NetDev &net); // of that space: SNN_LIST_STEPS steps of every layer; 0: never used
 #define SNN_LIST_STEPS 64
 hipError_t launch_recompute(const NetDev &net, int t0, int t1, const float *state_in, float *buf, int t_base,
@@ -261,7 +264,7 @@ hipError_t launch_bwd_stage(const NetDev &net, const AdjJobs &jobs, float *carry
 hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, const SpanHook *hook = nullptr);
 hipError_t launch_transpose(const float *src, float *dst, int rows, int cols, hipStream_t s);
 // Compressed rows of a masked recurrent matrix, in two parts: counts and row ends into sub, {synapses, sub-ranges that are
-// too full for k_dw_csr} into out (device); then, with the arrays sized for them, positions and entries.
+// too full for k_dw_csr (low half) and groups of the form by column (high half)} into out (device); then, with the arrays sized for them, positions and entries.
 hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, hipStream_t s);
 hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t nnz, uint32_t *sub, uint16_t *col, float *val,
                            uint64_t *pk, hipStream_t s);

@@ -1232,6 +1232,196 @@ k_layer_seq_csr_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpe
   layer_seq_csr_sl_body(net, jobs, state, st, S, xw, wd_max, err, spin_limit, smem, (int)blockIdx.x, (int)blockIdx.y);
 }
 
+// The sequential part of layers with compressed rows by column: a wavefront owns 64 postsynaptic neurons, one per lane, and eight batch
+// elements, their sums in registers; it reads the neurons' synapses (NetDev::csr_ell: the entries of a column ascending in the
+// presynaptic index, entry k of the 64 columns side by side) and adds each to the sums of those batch elements whose
+// presynaptic neuron fired.  Per sum the adds of the walk over rows, in its order: the same bits.  The work does not depend on
+// the activity, where the walk over rows costs an LDS read, add and write per active row one after the other (four layers of 8192 at
+// density 0.1, batch 32, alone: 73 us per step at 5 %, 170 at 20 %).
+//   The spikes of the step before sit in LDS as a byte per presynaptic neuron, one bit per batch element: an entry costs one byte read, and
+// per batch element two vector instructions, v_add_co_u32 of the byte with itself -- it shifts, and the carry is the lane mask of
+// that batch element -- and the add under that mask.  Bound by the vector unit (17 instructions per entry and wavefront).
+//   The wavefronts of a layer and eight batch elements exchange a byte per neuron and step: stored through to memory, then a flag per
+// wavefront in uncached memory; who has seen all flags reads the bytes with ordinary loads.  A place is written once per launch
+// and a wavefront's 64 bytes have a cache line to themselves, so no cache can hold an older value of them (one that had been read
+// for its neighbour's sake, say); the readers of a die share one fetch through its L2 (8192 neurons: 32 KB per workgroup and step).
+#define SNN_COL_GROUP 8 // entries per group of loads; columns are padded to whole groups
+#define SNN_COL_AHEAD 4 // groups in registers
+#define SNN_COL_LINE 128 // bytes of a cache line
+static __device__ __forceinline__ void col_add(uint32_t m, float w, float (&acc)[8]) {
+  uint64_t p0, p1, p2, p3, p4, p5, p6, p7;
+  asm volatile("v_lshlrev_b32 %0, 24, %0\n\t"
+               "v_add_co_u32_e64 %0, %1, %0, %0\n\tv_add_co_u32_e64 %0, %2, %0, %0\n\t"
+               "v_add_co_u32_e64 %0, %3, %0, %0\n\tv_add_co_u32_e64 %0, %4, %0, %0\n\t"
+               "v_add_co_u32_e64 %0, %5, %0, %0\n\tv_add_co_u32_e64 %0, %6, %0, %0\n\t"
+               "v_add_co_u32_e64 %0, %7, %0, %0\n\tv_add_co_u32_e64 %0, %8, %0, %0\n\t"
+               "s_mov_b64 exec, %1\n\tv_add_f32 %9, %9, %17\n\ts_mov_b64 exec, %2\n\tv_add_f32 %10, %10, %17\n\t"
+               "s_mov_b64 exec, %3\n\tv_add_f32 %11, %11, %17\n\ts_mov_b64 exec, %4\n\tv_add_f32 %12, %12, %17\n\t"
+               "s_mov_b64 exec, %5\n\tv_add_f32 %13, %13, %17\n\ts_mov_b64 exec, %6\n\tv_add_f32 %14, %14, %17\n\t"
+               "s_mov_b64 exec, %7\n\tv_add_f32 %15, %15, %17\n\ts_mov_b64 exec, %8\n\tv_add_f32 %16, %16, %17\n\t"
+               "s_mov_b64 exec, -1" // (every lane of the wavefront runs)
+               : "+v"(m), "=&s"(p0), "=&s"(p1), "=&s"(p2), "=&s"(p3), "=&s"(p4), "=&s"(p5), "=&s"(p6), "=&s"(p7), "+v"(acc[0]),
+                 "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7])
+               : "v"(w));
+}
+static __device__ __forceinline__ void layer_seq_col_body(const NetDev &net, const SeqJobs &jobs, float *__restrict__ state,
+                                                          const StoreSpec &st, int nq, unsigned char *xl, size_t xl_stride, unsigned *flags,
+                                                          int flags_stride, unsigned *err, unsigned spin_limit, unsigned char *smem, int bx,
+                                                          int jq) {
+  const int l = jobs.j[jq].l, t0 = jobs.j[jq].t0, t1 = jobs.j[jq].t1, t_tile = jobs.j[jq].t_tile;
+  const float *__restrict__ iin = jobs.j[jq].iin;
+  const int N = net.N[l], off = net.off[l], B = net.B, SN = net.SN, Wd = net.Wd[l + 1]; // Wd: slices of 64 neurons
+  const int lane = lane_id(), wave = uniform((int)threadIdx.x >> 6);
+  const int slice = bx * (4 / nq) + wave / nq, q = wave % nq, b0 = 8 * q;
+  if (slice >= Wd || b0 >= B) return; // a narrower layer than the widest of the launch, or no batch elements: nobody waits for it
+  const int c = 64 * slice + lane;
+  const bool in = c < N;
+  unsigned char *const sp = smem + (size_t)wave * (64 * Wd + 64); // [64 Wd] and the byte that padding entries read (64 for alignment)
+  uint64_t *const mbase = net.mask[l + 1];
+  xl += (size_t)jq * xl_stride;
+  flags += (size_t)jq * flags_stride + q * ((Wd + 1) & ~1); // one per slice
+  // spikes of step t0, transposed: a stored word is a lane mask, v_addc of a register with itself and that mask shifts one bit in
+  uint32_t own = 0u;
+  {
+    const __attribute__((address_space(4))) uint64_t *const row =
+        (const __attribute__((address_space(4))) uint64_t *)(mbase + (mrow_of(net, l + 1, t0) * B + b0) * Wd);
+    for (int w = 0; w < Wd; ++w) {
+      uint64_t word[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) word[k] = row[(b0 + k < B ? k : 0) * Wd + w];
+      uint32_t y = 0u;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint64_t x = b0 + k < B ? word[k] : 0ull;
+        asm volatile("v_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(y) : "s"(x) : "vcc");
+      }
+      sp[64 * w + lane] = (unsigned char)y;
+      if (w == slice) own = y;
+    }
+    sp[64 * Wd + lane] = 0;
+  }
+  float v[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = in && b0 + k < B ? state[(size_t)(b0 + k) * SN + off + c] : 0.0f;
+  const uint32_t *const eoff = net.csr_sub[l] + (size_t)N * ((N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW + 1);
+  const int g0 = (int)eoff[slice], ng = (int)eoff[slice + 1] - g0; // groups (>= 1)
+  const uint2 *const ent = reinterpret_cast<const uint2 *>(net.csr_pk[l] + net.csr_nnz[l] + (size_t)((N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW) * 64) +
+                           (size_t)g0 * SNN_COL_GROUP * 64 + lane;
+  const uint32_t spb = (uint32_t)(uintptr_t)(lds_float *)(float *)sp; // LDS byte address
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  uint2 e[SNN_COL_AHEAD][SNN_COL_GROUP];
+  auto issue = [&](uint2 (&x)[SNN_COL_GROUP], int g) { // (past the end: the last group again, not used)
+    const uint2 *p = ent + (size_t)(g < ng ? g : ng - 1) * SNN_COL_GROUP * 64;
+#pragma unroll
+    for (int u = 0; u < SNN_COL_GROUP; ++u) x[u] = p[(size_t)u * 64];
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  StoreCursor sc;
+  sc.init(st, t0 + 1);
+  const size_t istride = (size_t)B * N;
+  const int cc = in ? c : N - 1;
+  unsigned step = 0;
+  bool dead = false;
+  for (int t = t0 + 1; t <= t1; ++t, ++step) {
+    const int store_slot = sc.slot(st, t);
+    sc.next(st);
+    float acc[8], in_t[8];
+    auto consume = [&](const uint2 (&x)[SNN_COL_GROUP]) {
+      uint32_t m[SNN_COL_GROUP];
+#pragma unroll
+      for (int u = 0; u < SNN_COL_GROUP; ++u) m[u] = *(const lds_byte *)(uintptr_t)(spb + x[u].y);
+#pragma unroll
+      for (int u = 0; u < SNN_COL_GROUP; ++u) col_add(m[u], __uint_as_float(x[u].x), acc);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int z = 0; z < SNN_COL_AHEAD; ++z) issue(e[z], z);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      acc[k] = 0.0f;
+      in_t[k] = iin[(size_t)(t - 1 - t_tile) * istride + (size_t)(b0 + k < B ? b0 + k : b0) * N + cc];
+    }
+    for (int g = 0; g < ng; g += SNN_COL_AHEAD)
+#pragma unroll
+      for (int z = 0; z < SNN_COL_AHEAD; ++z) {
+        if (g + z < ng) consume(e[z]);
+        issue(e[z], g + z + SNN_COL_AHEAD);
+      }
+    uint32_t fired = 0u;
+    uint64_t word = 0ull; // lane k: the spike word of batch element b0 + k
+    float it[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      float a = net.alpha * v[k];
+      if ((own >> (7 - k)) & 1u) a = a - net.theta;
+      it[k] = in_t[k] + acc[k];
+      v[k] = a + it[k];
+      const bool f = in && b0 + k < B && v[k] > net.theta;
+      const uint64_t w = __ballot(f);
+      fired = fired * 2u + (f ? 1u : 0u);
+      if (lane == k) word = w;
+    }
+    own = fired;
+    // ---- the layer's spikes of this step, eight batch elements of it ------------------------------------------
+    unsigned char *const xs = xl + ((size_t)step * Wd * nq + q) * SNN_COL_LINE; // [slice][nq][SNN_COL_LINE]
+    const size_t sstride = (size_t)nq * SNN_COL_LINE;
+    __hip_atomic_store(&xs[slice * sstride + lane], (unsigned char)fired, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the bytes are in memory
+    if (lane == 0) __hip_atomic_store(&flags[slice], step + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (!in || b0 + k >= B) continue;
+      const size_t at = (size_t)(b0 + k) * SN + off + c;
+      if (st.cur && t > st.cur_from) st.cur[(size_t)(t - st.cur_from - 1) * st.slot_stride + at] = it[k];
+      if (store_slot >= 0) st.base[(size_t)store_slot * st.slot_stride + at] = v[k];
+    }
+    if (lane < 8 && b0 + lane < B) mbase[(mrow_of(net, l + 1, t) * B + b0 + lane) * Wd + slice] = word;
+    if (t == t1) break;
+    if (spin_limit == 0u && !dead) { // only ever set by a test of this path: give up at once, arrived or not
+      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      dead = true;
+    }
+    for (int f0 = 0; f0 < Wd; f0 += 64) {
+      const unsigned *const fp = &flags[f0 + lane < Wd ? f0 + lane : slice];
+      for (unsigned spins = 0;;) {
+        const unsigned got = __hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__ballot((int)(got - (step + 1u)) < 0) == 0ull || dead) break;
+        if (++spins > spin_limit ||
+            ((spins & 63u) == 0u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          dead = true; // keep going to the end of the tile, never wait again
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    asm volatile("" ::: "memory"); // no byte is read before its flag
+    for (int s0 = 0; s0 < Wd; s0 += 128) {
+      uint4 x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int s = s0 + 16 * u + (lane >> 2);
+        x[u] = *reinterpret_cast<const uint4 *>(xs + (s < Wd ? s : Wd - 1) * sstride + 16 * (lane & 3));
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int s = s0 + 16 * u + (lane >> 2);
+        if (s < Wd) *reinterpret_cast<uint4 *>(sp + 64 * s + 16 * (lane & 3)) = x[u];
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // (LDS instructions of a wavefront execute in order)
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (in && b0 + k < B) state[(size_t)(b0 + k) * SN + off + c] = v[k];
+}
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3)))
+k_layer_seq_col(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpec st, int nq, unsigned char *xl, size_t xl_stride,
+                unsigned *flags, int flags_stride, unsigned *err, unsigned spin_limit) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  layer_seq_col_body(net, jobs, state, st, nq, xl, xl_stride, flags, flags_stride, err, spin_limit, smem, (int)blockIdx.x, (int)blockIdx.y);
+}
+
 // A4: u_t = beta u_{t-1} + I_out,t ; usum += u_t over the steps of a tile (fp64 state: ubar feeds a
 // softmax, which turns an absolute error of ubar into a relative error of the loss gradient).
 __device__ __forceinline__ void readout_scan_body(const float *__restrict__ iout, double *__restrict__ readout, int B,
@@ -1798,6 +1988,24 @@ k_fwd_stage_csr(NetDev net, SeqJobs sj, float *__restrict__ state, StoreSpec st,
   if ((int)blockIdx.x < n_seq) {
     __builtin_amdgcn_s_setprio(3); // the chain goes first wherever both have an instruction ready
     layer_seq_csr_sl_body(net, sj, state, st, S, xw, wd_max, err, spin_limit, smem, (int)blockIdx.x % n_seq_x, (int)blockIdx.x / n_seq_x);
+  } else {
+    const int i = (int)blockIdx.x - n_seq;
+    currents_dense_body<SNN_DENSE_MB_, 0>(net, cj.j[i / cur_gx], i % cur_gx,
+                                          reinterpret_cast<float (*)[16 * SNN_DENSE_MB_][SNN_DENSE_AP]>(smem));
+  }
+}
+
+// The same stage with the sequential parts by column: their vector instructions and the matrix instructions of the currents use
+// different pipes of a SIMD.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+k_fwd_stage_col(NetDev net, SeqJobs sj, float *__restrict__ state, StoreSpec st, int nq, unsigned char *xl, size_t xl_stride,
+                unsigned *flags, int flags_stride, unsigned *err, unsigned spin_limit, CurJobs cj, int n_seq_x, int cur_gx) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int n_seq = n_seq_x * sj.count;
+  if ((int)blockIdx.x < n_seq) {
+    __builtin_amdgcn_s_setprio(3);
+    layer_seq_col_body(net, sj, state, st, nq, xl, xl_stride, flags, flags_stride, err, spin_limit, smem, (int)blockIdx.x % n_seq_x,
+                       (int)blockIdx.x / n_seq_x);
   } else {
     const int i = (int)blockIdx.x - n_seq;
     currents_dense_body<SNN_DENSE_MB_, 0>(net, cj.j[i / cur_gx], i % cur_gx,
@@ -4485,6 +4693,94 @@ k_csr_scan(int N, int nsub, uint32_t *__restrict__ sub, unsigned long long *__re
     out[1] = b;
   }
 }
+// The same synapses by column for k_layer_seq_col: per slice of 64 postsynaptic neurons as many groups of SNN_COL_GROUP entries per
+// column as its fullest column needs, entry k of the 64 columns side by side, a column's entries ascending in the presynaptic index
+// {weight, index}, then padding entries {0, 64 slices}.  A workgroup per slice and quarter of the presynaptic neurons, a wavefront per
+// sixteenth of those; eoff: [slices + 1] first groups, then [slices][4][64] entries per column and quarter.
+#define ELL_QUARTERS 4
+struct EllRows { int j0, j1; };
+static __device__ __forceinline__ EllRows ell_rows(int N) { // of this wavefront
+  const int per = (N + 16 * ELL_QUARTERS - 1) / (16 * ELL_QUARTERS), j0 = ((int)blockIdx.y * 16 + (int)(threadIdx.x >> 6)) * per;
+  return EllRows{min(j0, N), min(j0 + per, N)};
+}
+// Entries of this lane's column in the wavefronts in front of this one (of the workgroup), in all of them: *total.
+static __device__ __forceinline__ uint32_t ell_count(const uint8_t *__restrict__ mask, int N, uint32_t (*cnt)[WAVE], uint32_t *total) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6, c = (int)blockIdx.x * WAVE + lane;
+  const EllRows r = ell_rows(N);
+  uint32_t n = 0;
+#pragma unroll 16
+  for (int j = r.j0; j < r.j1; ++j) n += mask[(size_t)j * N + (c < N ? c : N - 1)] != 0;
+  cnt[wave][lane] = c < N ? n : 0u;
+  __syncthreads();
+  uint32_t before = 0, all = 0;
+  for (int q = 0; q < 16; ++q) {
+    before += q < wave ? cnt[q][lane] : 0u;
+    all += cnt[q][lane];
+  }
+  *total = all;
+  return before;
+}
+__global__ void __launch_bounds__(1024) k_ell_count(const uint8_t *__restrict__ mask, int N, uint32_t *__restrict__ eoff) {
+  __shared__ uint32_t cnt[16][WAVE];
+  uint32_t all;
+  (void)ell_count(mask, N, cnt, &all);
+  if (threadIdx.x < WAVE) eoff[gridDim.x + 1 + (blockIdx.x * ELL_QUARTERS + blockIdx.y) * WAVE + threadIdx.x] = all;
+}
+__global__ void __launch_bounds__(1024) k_ell_scan(int slices, uint32_t *__restrict__ eoff, unsigned long long *__restrict__ out) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  for (int i = wave; i < slices; i += 16) {
+    uint32_t all = 0;
+    for (int q = 0; q < ELL_QUARTERS; ++q) all += eoff[slices + 1 + (i * ELL_QUARTERS + q) * WAVE + lane];
+    for (int d = 1; d < WAVE; d <<= 1) all = max(all, (uint32_t)__shfl_xor((int)all, d));
+    if (lane == 0) eoff[i] = max(1u, (all + SNN_COL_GROUP - 1) / SNN_COL_GROUP);
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  uint32_t sum = 0;
+  for (int i0 = 0; i0 < slices; i0 += WAVE) {
+    const uint32_t n = i0 + lane < slices ? eoff[i0 + lane] : 0u;
+    uint32_t x = n;
+    for (int d = 1; d < WAVE; d <<= 1) {
+      const uint32_t y = (uint32_t)__shfl_up((int)x, d);
+      if (lane >= d) x += y;
+    }
+    if (i0 + lane < slices) eoff[i0 + lane] = sum + x - n;
+    sum += (uint32_t)__shfl((int)x, WAVE - 1);
+  }
+  if (lane == 0) {
+    eoff[slices] = sum;
+    out[1] |= (unsigned long long)sum << 32;
+  }
+}
+__global__ void __launch_bounds__(1024)
+k_ell_fill(const uint8_t *__restrict__ mask, const float *__restrict__ W, int N, const uint32_t *__restrict__ eoff, uint2 *__restrict__ ell) {
+  __shared__ uint32_t cnt[16][WAVE];
+  const int slices = (int)gridDim.x, slice = (int)blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6, c = slice * WAVE + lane;
+  uint32_t mine, k = ell_count(mask, N, cnt, &mine), all = 0;
+  for (int q = 0; q < ELL_QUARTERS; ++q) {
+    const uint32_t n = eoff[slices + 1 + (slice * ELL_QUARTERS + q) * WAVE + lane];
+    k += q < (int)blockIdx.y ? n : 0u;
+    all += n;
+  }
+  uint2 *const e = ell + (size_t)eoff[slice] * SNN_COL_GROUP * WAVE + lane;
+  const uint32_t n = (eoff[slice + 1] - eoff[slice]) * SNN_COL_GROUP;
+  const EllRows r = ell_rows(N);
+  const int cc = c < N ? c : N - 1;
+  for (int j = r.j0; j < r.j1; j += 16) { // sixteen rows' loads at a time, whether a synapse exists or not
+    uint8_t there[16];
+    float w[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const size_t at = (size_t)min(j + u, r.j1 - 1) * N + cc;
+      there[u] = mask[at];
+      w[u] = W[at];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (c < N && j + u < r.j1 && there[u]) e[(size_t)(k++) * WAVE] = make_uint2(__float_as_uint(w[u]), (uint32_t)(j + u));
+  }
+  for (k = all + (uint32_t)((int)blockIdx.y * 16 + wave); k < n; k += 16 * ELL_QUARTERS) e[(size_t)k * WAVE] = make_uint2(0u, slices * WAVE);
+}
 __global__ void __launch_bounds__(256)
 k_csr_fill(const uint8_t *__restrict__ mask, const float *__restrict__ W, int N, int nsub, uint32_t nnz,
            uint32_t *__restrict__ sub, uint16_t *__restrict__ col, float *__restrict__ val, uint64_t *__restrict__ pk) {
@@ -4834,6 +5130,7 @@ static bool lists_run(const NetDev &net, const CurJobs &jobs, CurJobs *mine, Cur
   }
   return net.sel_currents == 4 || lists_pay(net, *mine, *most);
 }
+static bool by_column_pays(const NetDev &net);
 unsigned currents_choice(const NetDev &net, int chunk) {
   CurJobs fwd{}, rec{};
   for (int l = 0; l < net.L; ++l) {
@@ -4843,7 +5140,7 @@ unsigned currents_choice(const NetDev &net, int chunk) {
   }
   CurJobs mine{}, rest{}, mine_r{}, rest_r{};
   int most;
-  return (lists_run(net, fwd, &mine, &rest, &most) ? 1u : 0u) | (lists_run(net, rec, &mine_r, &rest_r, &most) ? 2u : 0u);
+  return (by_column_pays(net) ? 4u : 0u) | (lists_run(net, fwd, &mine, &rest, &most) ? 1u : 0u) | (lists_run(net, rec, &mine_r, &rest_r, &most) ? 2u : 0u);
 }
 static hipError_t launch_currents_lists(const NetDev &net, CurJobs *jobs, hipStream_t s) {
   CurJobs mine{}, rest{};
@@ -5152,6 +5449,49 @@ static int seq_csr_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws
   return S;
 }
 
+// The sequential part by column (k_layer_seq_col): wavefronts per slice of 64 neurons (eight batch elements each); 0 if it cannot run
+// or does not pay.  Its time goes with the synapses of a neuron, that of the walk over rows with the active presynaptic neurons.
+#define SNN_COL_LDS(Wd) ((size_t)4 * (64 * (Wd) + 64))
+static int seq_col_per_cu(int device, int *n_cu) { // workgroups per compute unit, alone and (one more) in the stage launch
+  static int cached[16] = {}, cus[16] = {};
+  if (device < 0 || device >= 16) return 0;
+  if (!cached[device]) {
+    hipDeviceProp_t prop;
+    int a = 0, b = 0;
+    if (hipGetDeviceProperties(&prop, device) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_layer_seq_col, 256, SNN_FWD_STAGE_CSR_LDS) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_fwd_stage_col, 256, SNN_FWD_STAGE_CSR_LDS) != hipSuccess) return 0;
+    cached[device] = a > b - 1 ? b - 1 : a;
+    if (cached[device] < 1) cached[device] = -1;
+    cus[device] = prop.multiProcessorCount;
+  }
+  *n_cu = cus[device];
+  return cached[device] > 0 ? cached[device] : 0;
+}
+static bool by_column_pays(const NetDev &net) { // one choice for the network, whichever of its layers a stage has
+  MaskedLayer m[SNN_MAXL];
+  int n = 0;
+  for (int l = 0; l < net.L; ++l)
+    if (net.csr_ell[l]) m[n++] = MaskedLayer{net.N[l], net.csr_nnz[l], net.rate[l + 1]};
+  return seq_by_column(m, n);
+}
+static int seq_col_waves(const NetDev &net, const SeqJobs &ga, const WsArgs *ws) {
+  if (!ws || !ws->xg || !ws->xl || ga.count < 1 || net.B > 32 || (net.sel_seq != 0 && net.sel_seq != 3) || net.sel_slices != 0) return 0;
+  const int nq = net.B <= 8 ? 1 : net.B <= 16 ? 2 : 4;
+  int Wd = 0;
+  for (int i = 0; i < ga.count; ++i) {
+    const int l = ga.j[i].l;
+    if (!net.csr_ell[l]) return 0;
+    Wd = std::max(Wd, net.Wd[l + 1]);
+    if ((size_t)(ga.j[i].t1 - ga.j[i].t0) * net.Wd[l + 1] * nq * SNN_COL_LINE > (size_t)ws->xg_stride * sizeof(float)) return 0; // a launch's places
+  }
+  if (net.sel_seq == 0 && !by_column_pays(net)) return 0;
+  if (SNN_COL_LDS(Wd) > SNN_FWD_STAGE_CSR_LDS || (size_t)ga.count * 4 * (Wd + 1) > (size_t)ws->xg_stride) return 0;
+  int device = 0, n_cu = 0;
+  if (hipGetDevice(&device) != hipSuccess) return 0;
+  return (Wd * nq + 3) / 4 * ga.count <= seq_col_per_cu(device, &n_cu) * n_cu ? nq : 0; // all resident: they wait for each other
+}
+
 // The sequential part of layers of 257..1024 neurons with the weights in LDS (k_layer_seq_lds): every job of the stage that
 // wide, units (job, group of batch elements) that fit the dies, one workgroup per compute unit, with as few wavefronts per
 // workgroup as that allows.  SNN_SEQ_SLICES asks for the walk through the L2 (1: unsliced).
@@ -5289,19 +5629,20 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
         wd_max = net.Wd[ga.j[i].l + 1] > wd_max ? net.Wd[ga.j[i].l + 1] : wd_max;
         n_max = net.N[ga.j[i].l] > n_max ? net.N[ga.j[i].l] : n_max;
       }
-      const int S_csr = ga.count ? seq_csr_slices(net, ga, ws) : 0;
+      const int by_col = ga.count ? seq_col_waves(net, ga, ws) : 0;
+      const int S_csr = ga.count && !by_col ? seq_csr_slices(net, ga, ws) : 0;
       SeqLdsPlan lp{};
-      const bool in_lds = ga.count && !S_csr && seq_lds_plan(net, ga, ws, &lp);
-      const int S = (ga.count && !S_csr && !in_lds) ? seq_slices(net, ga, ws, &npt_sl, &th_sl) : 1;
+      const bool in_lds = ga.count && !S_csr && !by_col && seq_lds_plan(net, ga, ws, &lp);
+      const int S = (ga.count && !S_csr && !by_col && !in_lds) ? seq_slices(net, ga, ws, &npt_sl, &th_sl) : 1;
       // Wide layers over compressed rows: the dense feed-forward currents for the next stage ride in the launch
       // of this stage's sequential parts (k_fwd_stage_csr) when all sequential workgroups fit beside one current
       // workgroup per compute unit; other current jobs (readout, matrices that fit the L2) go out on their own.
       CurJobs cj_fused{};
-      if (S_csr && !net.no_fwd_fuse && currents_use_mfma(net)) {
+      if ((S_csr || by_col) && !net.no_fwd_fuse && currents_use_mfma(net)) {
         int device = 0, n_cu = 0;
         if (hipGetDevice(&device) != hipSuccess) return hipErrorInvalidDevice;
-        const int per_cu = fwd_stage_csr_per_cu(device, &n_cu);
-        if (per_cu >= 2 && B * S_csr * ga.count <= (per_cu - 1) * n_cu) {
+        const int per_cu = by_col ? 0 : fwd_stage_csr_per_cu(device, &n_cu);
+        if (by_col || (per_cu >= 2 && B * S_csr * ga.count <= (per_cu - 1) * n_cu)) {
           CurJobs rest{};
           for (int i = 0; i < cj.count; ++i) {
             const bool dense = cj.j[i].nsteps > 0 && cj.j[i].mode == 1 && currents_job_kernel(net, cj.j[i]) == 1;
@@ -5321,18 +5662,31 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
         else if (nw <= 128) hipLaunchKernelGGL((k_layer_seq_rs<128>), dim3(B, rs.count), dim3(128), SeqRs<128>::lds_bytes, s, net, rs, state, st);
         else hipLaunchKernelGGL((k_layer_seq_rs<256>), dim3(B, rs.count), dim3(256), SeqRs<256>::lds_bytes, s, net, rs, state, st);
       }
-      if (S_csr) {
+      unsigned gx = 0; // workgroups per job of the currents in the stage launch
+      for (int i = 0; i < cj_fused.count; ++i) {
+        const CurJob &j = cj_fused.j[i];
+        const unsigned g = (unsigned)(((j.nsteps * B + 16 * SNN_DENSE_MB - 1) / (16 * SNN_DENSE_MB)) * ((net.N[j.lsel] + 255) >> 8));
+        gx = g > gx ? g : gx;
+      }
+      if (by_col) {
+        const int flags = 4 * ((wd_max + 1) & ~1), wgs = (wd_max * by_col + 3) / 4;
+        e = launch_fill_zero(ws->xg, (size_t)ga.count * flags * sizeof(unsigned), s); // flags start from zero in every launch
+        if (e != hipSuccess) return e;
+        unsigned char *const xl = reinterpret_cast<unsigned char *>(ws->xl);
+        unsigned *const fl = reinterpret_cast<unsigned *>(ws->xg);
+        const size_t stride = (size_t)ws->xg_stride * sizeof(float);
+        if (cj_fused.count)
+          hipLaunchKernelGGL(k_fwd_stage_col, dim3(wgs * ga.count + gx * cj_fused.count), dim3(256), SNN_FWD_STAGE_CSR_LDS, s, net, ga, state, st,
+                             by_col, xl, stride, fl, flags, ws->err, ws->spin_limit, cj_fused, wgs, (int)gx);
+        else
+          hipLaunchKernelGGL(k_layer_seq_col, dim3(wgs, ga.count), dim3(256), SNN_COL_LDS(wd_max), s, net, ga, state, st, by_col, xl, stride, fl,
+                             flags, ws->err, ws->spin_limit);
+      } else if (S_csr) {
         // tags of the exchange entries start from zero in every launch
         e = launch_fill_zero(ws->xg, (size_t)ga.count * B * 4 * wd_max * sizeof(uint64_t), s);
         if (e != hipSuccess) return e;
         const size_t lds_seq = seq_csr_lds(n_max, wd_max);
         if (cj_fused.count) {
-          unsigned gx = 0;
-          for (int i = 0; i < cj_fused.count; ++i) {
-            const CurJob &j = cj_fused.j[i];
-            const unsigned g = (unsigned)(((j.nsteps * B + 16 * SNN_DENSE_MB - 1) / (16 * SNN_DENSE_MB)) * ((net.N[j.lsel] + 255) >> 8));
-            gx = g > gx ? g : gx;
-          }
           const size_t lds = lds_seq > SNN_FWD_STAGE_CSR_LDS ? lds_seq : SNN_FWD_STAGE_CSR_LDS;
           hipLaunchKernelGGL(k_fwd_stage_csr, dim3(B * S_csr * ga.count + gx * cj_fused.count), dim3(256), lds, s, net, ga, state,
                              st, S_csr, reinterpret_cast<uint64_t *>(ws->xg), wd_max, ws->err, ws->spin_limit, cj_fused, B * S_csr, (int)gx);
@@ -5693,6 +6047,8 @@ void adjoint_prepare(const NetDev &net, const WsArgs &ws) {
       int npt = 0, th = 0;
       (void)seq_slices(net, probe, &ws, &npt, &th);
       (void)seq_csr_slices(net, probe, &ws, false);
+      int n_cu_col = 0, dev_col = 0;
+      if (hipGetDevice(&dev_col) == hipSuccess) (void)seq_col_per_cu(dev_col, &n_cu_col);
       SeqLdsPlan lp{};
       (void)seq_lds_plan(net, probe, &ws, &lp);
       int device = 0, n_cu = 0;
@@ -6214,12 +6570,21 @@ hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned 
   const int nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
   hipLaunchKernelGGL(k_csr_count, dim3(N), dim3(256), 0, s, mask, N, nsub, sub);
   hipLaunchKernelGGL(k_csr_scan, dim3(1), dim3(1024), 0, s, N, nsub, sub, out);
+  if (csr_by_column(N)) {
+    const int slices = (N + WAVE - 1) / WAVE;
+    uint32_t *const eoff = sub + (size_t)N * (nsub + 1);
+    hipLaunchKernelGGL(k_ell_count, dim3(slices, ELL_QUARTERS), dim3(1024), 0, s, mask, N, eoff);
+    hipLaunchKernelGGL(k_ell_scan, dim3(1), dim3(1024), 0, s, slices, eoff, out);
+  }
   return hipGetLastError();
 }
 hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t nnz, uint32_t *sub, uint16_t *col, float *val,
                            uint64_t *pk, hipStream_t s) {
   const int nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
   hipLaunchKernelGGL(k_csr_fill, dim3(N), dim3(256), 0, s, mask, W, N, nsub, nnz, sub, col, val, pk);
+  if (csr_by_column(N))
+    hipLaunchKernelGGL(k_ell_fill, dim3((N + WAVE - 1) / WAVE, ELL_QUARTERS), dim3(1024), 0, s, mask, W, N, sub + (size_t)N * (nsub + 1),
+                       reinterpret_cast<uint2 *>(pk + nnz + (size_t)nsub * 64));
   return hipGetLastError();
 }
 

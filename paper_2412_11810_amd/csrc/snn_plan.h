@@ -5,6 +5,32 @@
 
 #define SNN_LDS_PER_CU (160 * 1024)
 
+// ---- sequential forward part over compressed rows, by row or by column ----------------------------
+// Whether a masked matrix of N x N is also kept by column (k_layer_seq_col): 32 MB dense-stored and more.
+inline bool csr_by_column(int N) { return (size_t)N * N * sizeof(float) >= ((size_t)32 << 20); }
+// Which of the two walks for a network's n masked layers: the one over rows pays per active presynaptic neuron -- and much more where a
+// row's part of a sub-range of 512 columns has more entries than a wavefront has lanes --, the one over columns per synapse of a
+// neuron.  Forward passes over 64 steps, ms by row / by column:
+//   4 x 8192, density 0.1, batch 32   mean activity 5.1 %: 14.6 / 17.4    9.8 %: 21.0 / 17.4    20 %: 31.6 / 17.5
+//   the same, batch 8                               5.1 %: 8.7 / 11.5     9.8 %: 14.6 / 11.6    20 %: 25.6 / 11.6
+//   2 x 8192, density 0.05, batch 32                4.2 %: 5.5 / 6.2      6.0 %: 6.5 / 6.3      9.2 %: 8.4 / 6.3
+//   2 x 8192, density 0.2, batch 32                 5.2 %: 21.7 / 14.6    8.0 %: 31.6 / 14.6    14 %: 46.3 / 14.6
+//   3 x 4096, density 0.1, batch 32                 3.3 %: 5.5 / 8.4      7.9 %: 8.4 / 8.4      14 %: 12.2 / 8.4
+//   8192, density 0.1, batch 32                     4.3 %: 3.3 / 4.9      7.5 %: 4.7 / 4.9
+// (they meet at 5.6 % for density 0.05, 7 to 8 % for 0.1.)  10 % stand in for an activity that is not known (< 0): of the two, the wrong
+// walk over columns costs less.
+struct MaskedLayer { int N; size_t nnz; double rate; };
+inline bool seq_by_column(const MaskedLayer *layers, int n) {
+  double rate = 0.0, density = 0.0;
+  for (int i = 0; i < n; ++i) {
+    rate += (layers[i].rate < 0.0 ? 0.1 : layers[i].rate) / n;
+    density += (double)layers[i].nnz / ((double)layers[i].N * layers[i].N) / n;
+  }
+  if (n <= 0) return false;
+  const double meet = 0.035 + 0.42 * density;
+  return rate >= (512.0 * density > 56.0 ? 0.25 * meet : meet);
+}
+
 // ---- inter-layer products of the adjoint pass -----------------------------------------------------
 // N neurons below, K above: split into fp16 halves (k_up_split) or on the fp32 matrix cores.  The same kernel for every number of
 // rows: they differ in the last bits, and gradients must not depend on how the time axis is cut.  From 1024 neurons the split one is

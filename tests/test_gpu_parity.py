@@ -605,6 +605,63 @@ def test_register_stationary_forward_widths(hidden, T):
     _full_parity(w, [(snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 7), (snn.SNN_DOUBLE, 10, 3)], nthreads=3)
 
 
+@pytest.mark.parametrize("hidden,B,T,density", [((2900,), 3, 40, 0.1),   # a ragged last slice, four slices per workgroup
+                                                ((3000, 2944), 12, 70, 0.3),  # two widths in a launch, batch elements to spare
+                                                ((2900, 2900), 20, 24, 0.05), ((4096,), 32, 33, 0.15)])
+def test_sequential_forward_by_column(hidden, B, T, density, monkeypatch):
+    """Wide layers over compressed rows by column (one neuron per lane, eight batch elements per wavefront): spikes, potentials and
+    gradients of the walk over rows, bit for bit, with the currents of the next stage in the same launch and without, with
+    currents kept, a neuron without synapses and one with all of them; and the oracle's."""
+    w = synth.Workload("col_" + "x".join(map(str, hidden)), 40, hidden, 6, T=T, B=B, p_in=0.1, gain=0.5, rec_density=density, seed=7 + B)
+    d = synth.generate(w)
+    for m, x in zip(d["rec_mask"], d["W_rec"]):
+        m[:, 5] = 0
+        m[:, 70] = 1
+        x[:, 70] = np.abs(x).max() * np.cos(np.arange(len(x)))
+        x *= m
+    got = {}
+    for kernel, fuse in (("rs", None), ("col", None), ("col", "0")):
+        monkeypatch.setenv("SNN_SEQ_KERNEL", kernel)
+        monkeypatch.setenv("SNN_CSR", "1")
+        if fuse:
+            monkeypatch.setenv("SNN_FWD_FUSE", fuse)
+        net = snn.from_workload(w, d)
+        try:
+            loss = net.snn_forward(d["in_spikes"], d["labels"], w.T)
+            spikes = [net.snn_get_spikes(l, w.T) for l in range(len(hidden))]
+            v = net.snn_debug_states(w.T)
+            net.snn_bptt(snn.SNN_DOUBLE, 12, 4)
+            first = _gpu_grads(net, len(hidden))
+            net.snn_bptt(snn.SNN_DOUBLE, 12, 4, want_stats=False)
+            assert _identical(first, _gpu_grads(net, len(hidden)))
+            got[kernel, fuse] = loss, spikes, v, first
+        finally:
+            net.snn_destroy()
+        monkeypatch.delenv("SNN_FWD_FUSE", raising=False)
+    a = got["rs", None]
+    assert all(s.any() for s in a[1])
+    for k in (("col", None), ("col", "0")):
+        b = got[k]
+        assert a[0] == b[0] and all(np.array_equal(x, y) for x, y in zip(a[1], b[1])), k
+        assert np.array_equal(a[2].view(np.uint32), b[2].view(np.uint32)) and _identical(a[3], b[3]), k
+    ref = _oracle(w, d, want_v=True, nthreads=8, backward=False)
+    assert all(np.array_equal(s, r.astype(np.uint8)) for s, r in zip(a[1], ref.spikes))
+
+
+def test_by_column_reports_a_time_out(monkeypatch):
+    """Its wait for the other wavefronts is bounded (forced from the host: give up at once)."""
+    w = synth.Workload("col_timeout", 40, (2900,), 6, T=8, B=4, p_in=0.1, gain=0.5, rec_density=0.1, seed=3)
+    d = synth.generate(w)
+    monkeypatch.setenv("SNN_SEQ_KERNEL", "col")
+    monkeypatch.setenv("SNN_WS_SPIN_LIMIT", "0")
+    net = snn.from_workload(w, d)
+    try:
+        with pytest.raises(snn.SnnError):
+            net.snn_forward(d["in_spikes"], d["labels"], w.T)
+    finally:
+        net.snn_destroy()
+
+
 @pytest.mark.parametrize("hidden,B,T,gain,tier", [
     ((257,), 1, 70, 0.6, 0),                   # one neuron in the last slice; three idle wavefronts per workgroup
     ((512, 300), 5, 130, 1.0, 0),              # two widths, a ragged group of batch elements, three tiles
