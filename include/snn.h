@@ -272,15 +272,17 @@ void snn_destroy(snn_ctx *ctx);
 
 /*
  * Test hooks.  The library chooses its kernels from the layer shapes, the batch size, the state size and the
- * firing rates of the previous step; every choice gives the same bits.  The parity tests force each flavour
- * through environment variables, read by the library at the points noted.  They are not part of the interface
- * proper: a caller never needs them.
+ * firing rates of the previous step; every choice by the rates gives the same bits.  The parity tests force each
+ * flavour through environment variables, read by the library at the points noted.  They are not part of the
+ * interface proper: a caller never needs them.
  *   read by snn_init (fixed for the context's life):
  *     SNN_HOST_TIER=dma|direct   Remote/Double checkpoints by hipMemcpyAsync / written and read by the kernels
  *                                through the mapped pinned block (default: direct up to 1 MiB per state)
  *     SNN_DW=event|tile|mfma     weight gradients by the event-by-event kernel / the event-driven tiled kernel
- *                                (batch <= 64) / the matrix-core contraction (default: tiled when some weight
- *                                matrix has 32 MB or more, else the contraction)
+ *                                (batch <= 64) / the matrix-core contraction (default: split into fp16 for batches of 12
+ *                                to 64 and matrices that fill the chip, which differs in the last bits; else tiled
+ *                                when some weight matrix has 32 MB or more, else the contraction or tiled by the
+ *                                activity)
  *     SNN_RF_CACHE=0             Double: never keep a coarse segment's currents between its two recompute passes
  *     SNN_KEEP_CURRENTS=0        Double: the forward pass never leaves the currents of the last coarse segments in
  *                                that cache (default: as many whole segments as the budget has room for)

@@ -92,6 +92,12 @@ struct snn_ctx {
   bool graphs_enabled = true;   // SNN_GRAPH=0 turns graph replay off
   bool own_stream = false;
   bool dw_event_driven = false; // SNN_DW=event selects the row-by-row kernel instead of the MFMA contraction
+  // k_dw_split: its workspace (NULL: not used), and in it, for a tile of SNN_BWD_TILE steps, the split adjoints and their scales (of every
+  // layer, the readout last) and the spikes (W_in and W_rec of layer l at 2 l and 2 l + 1, W_out last); see DwDesc
+  unsigned char *dw_ws = nullptr;
+  uint4 *dw_split[SNN_MAXL + 1]{};
+  float *dw_scale[SNN_MAXL + 1]{};
+  uint8_t *dw_octets[2 * SNN_MAXL + 1]{};
   bool dw_tile = false;         // the event-driven tiled kernel instead of the dense contraction (batch <= 64; SNN_DW=tile|mfma)
   bool dw_rate_driven = false;  // ... chosen from the firing rates of the previous step (layers wider than 256, no SNN_DW)
   bool bwd_pipeline = true;     // SNN_BWD_PIPE=0: the adjoint pass finishes every layer of a chunk before the next chunk
@@ -201,6 +207,12 @@ int pre_of(const NetDev &n, int l) { return l == 0 ? n.n_in : n.N[l - 1]; }
 bool dw_rec_csr(const snn_ctx *c, int l) {
   return c->dw_tile && c->dw_csr && !c->dw_event_driven && c->net.csr_sub[l] && c->csr_dw_ok[l] && c->acc_csr[l] &&
          c->net.B <= 32;
+}
+
+// Does the recurrent matrix of layer l go through k_dw_split, where the network's matrices do?  Not if its synapses are few enough for
+// k_dw_csr (whether or not that runs in this step: the choice must not follow the activity).
+bool dw_rec_split(const snn_ctx *c, int l) {
+  return c->dw_ws && !(c->csr_sub[l] && c->csr_dw_ok[l] && c->acc_csr[l] && c->net.B <= 32);
 }
 
 // Test hooks that force a kernel flavour (documented in snn.h): read from the environment at the start of every
@@ -560,7 +572,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
     const size_t pmax = (size_t)std::max(l == 0 ? n.n_in : n.N[l - 1], n.N[l]);
     if (pmax * n.N[l] * sizeof(float) >= ((size_t)32 << 20)) c->rate_driven = true;
   }
-  // The weight-gradient kernel (both give the same bits: per time step an fp32 sum over the batch elements in
+  // The weight-gradient kernel where k_dw_split is not used (both give the same bits: per time step an fp32 sum over the batch elements in
   // ascending order, then one fp64 add): the event-driven tiled kernel pays per presynaptic spike, the dense
   // contraction per presynaptic neuron.  Networks with a weight matrix far beyond the L2 always take the tiled kernel
   // (with compressed rows for masked matrices it stays ahead of the dense contraction at 20 % activity as well);
@@ -571,6 +583,27 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
     int nmax = 0;
     for (int l = 0; l < L; ++l) nmax = n.N[l] > nmax ? n.N[l] : nmax;
     c->dw_rate_driven = nmax > 256 && B <= 64 && !c->rate_driven;
+  }
+  {
+    int tiles = dw_split_tiles(n.N[L - 1], n.n_out);
+    for (int l = 0; l < L; ++l) tiles += dw_split_tiles(pre_of(n, l), n.N[l]) + dw_split_tiles(n.N[l], n.N[l]);
+    if (dw_split_pays(tiles, B) && !bwd_stage_fusable(n, dw_wide_tiles(n) ? 1 : 0) && !std::getenv("SNN_DW")) {
+      const size_t octets = (size_t)SNN_BWD_TILE * dw_split_octets(B);
+      size_t at_split[SNN_MAXL + 1], at_scale[SNN_MAXL + 1], at_octets[2 * SNN_MAXL + 1], sum = 0;
+      const auto take = [&](size_t bytes) { const size_t at = sum; sum += (bytes + 255) & ~(size_t)255; return at; };
+      for (int l = 0; l <= L; ++l) {
+        const size_t cols = l < L ? n.N[l] : O;
+        at_split[l] = take(octets * 3 * cols * sizeof(uint4));
+        at_scale[l] = take(octets * cols * sizeof(float));
+      }
+      for (int i = 0; i <= 2 * L; ++i) at_octets[i] = take(octets * 64 * n.Wd[i == 2 * L ? L : (i + 1) / 2]);
+      HIPCHK(c, hipMalloc(&c->dw_ws, sum));
+      for (int l = 0; l <= L; ++l) {
+        c->dw_split[l] = reinterpret_cast<uint4 *>(c->dw_ws + at_split[l]);
+        c->dw_scale[l] = reinterpret_cast<float *>(c->dw_ws + at_scale[l]);
+      }
+      for (int i = 0; i <= 2 * L; ++i) c->dw_octets[i] = c->dw_ws + at_octets[i];
+    }
   }
   if (const char *e = std::getenv("SNN_DW")) {
     c->dw_rate_driven = false;
@@ -593,7 +626,7 @@ void snn_destroy(snn_ctx *c) {
   }
   for (int l = 0; l <= SNN_MAXL; ++l) { (void)hipFree(c->mask_full[l]); (void)hipFree(c->mask_ring[l]); }
   if (c->host_spk) (void)hipHostFree(c->host_spk);
-  (void)hipFree(c->W_out); (void)hipFree(c->dW_out); (void)hipFree(c->acc_out);
+  (void)hipFree(c->dw_ws); (void)hipFree(c->W_out); (void)hipFree(c->dW_out); (void)hipFree(c->acc_out);
   (void)hipFree(c->labels); (void)hipFree(c->readout); (void)hipFree(c->ubar); (void)hipFree(c->g);
   (void)hipFree(c->loss_dev); (void)hipFree(c->carry); (void)hipFree(c->cur_state);
   if (c->ws.bar) uncached_release(c->cfg.device, c->ws.bar);
@@ -1521,12 +1554,12 @@ struct BwdPipe {
     for (const BwdTile &t : done) {
       const int l = t.layer;
       if (l == L - 1)
-        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr};
-      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr};
+        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr, c->dw_split[L], c->dw_scale[L], c->dw_octets[2 * L]};
+      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr, c->dw_split[l], c->dw_scale[l], c->dw_octets[2 * l]};
       if (dw_rec_csr(c, l))
-        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_csr[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], n.csr_sub[l], n.csr_col[l]};
+        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_csr[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], n.csr_sub[l], n.csr_col[l], nullptr, nullptr, nullptr};
       else
-        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr};
+        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr, dw_rec_split(c, l) ? c->dw_split[l] : nullptr, c->dw_scale[l], c->dw_octets[2 * l + 1]};
     }
   }
   snn_status emit_dw() {
@@ -1544,10 +1577,13 @@ struct BwdPipe {
         HIPCHK(c, launch_dw(n.mask[l + 1], n.Wd[l + 1], n.N[l], 1, t.vbuf, slot, SN, n.off[l], n.N[l], B, t.t0, t.t1, t.base, c->acc_rec[l], s, n.mring[l + 1]));
       }
     } else {
-      DwBatch db{};
-      fill_dw_batch(&db);
+      DwBatch all{}, db{}, split{};
+      fill_dw_batch(&all);
+      db.wide = all.wide;
+      for (int i = 0; i < all.count; ++i) (all.d[i].split ? split.d[split.count++] : db.d[db.count++]) = all.d[i];
       if (c->dw_tile) HIPCHK(c, launch_dw_tile(db, B, s));
       else HIPCHK(c, launch_dw_mfma(db, B, s));
+      HIPCHK(c, launch_dw_split(split, B, s));
     }
     tm->end();
     done.clear();

@@ -226,6 +226,11 @@ struct DwDesc {
   // synapse, in the order of the compressed entries (NetDev::csr_sub / csr_col); NULL: dense accumulators
   const uint32_t *csr_sub;
   const uint16_t *csr_col;
+  // k_dw_split: space for the split adjoints and their scales (the same of the matrices of a layer), and for this matrix's
+  // spikes; NULL: the other kernels
+  uint4 *split;             // [steps][dw_split_octets][3][n_post]
+  float *scale;             // [steps][parts][n_post]
+  uint8_t *octets;          // [steps][dw_split_octets][64 pre_words]
 };
 struct DwBatch {
   DwDesc d[2 * SNN_MAXL + 1];
@@ -235,6 +240,8 @@ struct DwBatch {
 hipError_t launch_dw_mfma(DwBatch batch, int B, hipStream_t s);
 // The same update event by event from LDS tiles (see k_dw_tile); batch sizes up to 64.
 hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s);
+// The same update on the fp16 matrix cores (see k_dw_split); batch sizes up to 64.
+hipError_t launch_dw_split(DwBatch batch, int B, hipStream_t s);
 // The recurrences of a stage and the weight-gradient contraction of the previous stage in one launch
 // (see k_bwd_stage).  Only for networks bwd_stage_fusable() accepts; the caller guarantees that the two
 // parts touch different tiles.

@@ -4166,6 +4166,240 @@ __device__ __forceinline__ void dw_mfma_body(const DwBatch &batch, int B, int vb
     }
 }
 
+// B5 for large matrices, whatever the activity: dW += S^T . P on the fp16 matrix cores.  The spikes are exact in fp16 and an adjoint is
+// the sum of three fp16 values (two, as in k_up_split, leave out its last bit half of the time: with them the gradients of the top layer
+// were up to a tenth further from 64 bits than the event-by-event sums), so three products of a part of a time step (at most 32 batch
+// elements), summed in fp32, give its contribution, which goes into the fp64 accumulator.  Parts of odd number run
+// with spikes of -1 (what the matrix cores cut off below an accumulator, always towards minus infinity, changes sides and does not
+// add up over the steps).  Number and scale of a part do not depend on how the time axis is cut: the same bits for every strategy.
+//   k_dw_split_rows lays the adjoints out as the kernel reads them: of the part's values of a column, scaled by the power of two that
+// brings the largest to 2^14 ... 2^15, eight batch elements' high parts in 16 bytes, then the middle and the low ones, zeros past the
+// last.
+// SHORT: a batch of at most 16, a part is a step of 16 rows; else a step is `per` parts of 32.
+static __device__ __forceinline__ void split3_fp16(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) {
+  const v2h hv = {(_Float16)x, (_Float16)y};
+  const float rx = __builtin_fmaf((float)hv[0], -1.0f, x), ry = __builtin_fmaf((float)hv[1], -1.0f, y);
+  h = __builtin_bit_cast(uint32_t, hv);
+  split_fp16(rx, ry, m, l);
+}
+struct DwRows { const float *post; uint4 *split; float *scale; size_t slot_stride; int post_stride, cols, steps; };
+struct DwRowsJobs { DwRows j[SNN_MAXL + 1]; };
+template <bool SHORT>
+__global__ void __launch_bounds__(256)
+k_dw_split_rows(DwRowsJobs jobs, int B, int per) {
+  constexpr int R = SHORT ? 16 : 32;
+  const DwRows &jb = jobs.j[blockIdx.z];
+  const int n = (int)(blockIdx.x * 256 + threadIdx.x), part = (int)blockIdx.y, t = part / per, b0 = R * (part - t * per);
+  if (n >= jb.cols || t >= jb.steps) return;
+  const float *const p = jb.post + (size_t)t * jb.slot_stride + (size_t)b0 * jb.post_stride + n;
+  float x[R], mx = 0.0f;
+#pragma unroll
+  for (int b = 0; b < R; ++b) x[b] = b0 + b < B ? p[(size_t)b * jb.post_stride] : 0.0f;
+#pragma unroll
+  for (int b = 0; b < R; ++b) mx = fmaxf(mx, fabsf(x[b]));
+  const float sc = row_scale(mx);
+  jb.scale[(size_t)part * jb.cols + n] = sc;
+#pragma unroll
+  for (int o = 0; o < R / 8; ++o) {
+    uint4 h, m, l;
+    split3_fp16(x[8 * o] * sc, x[8 * o + 1] * sc, h.x, m.x, l.x);
+    split3_fp16(x[8 * o + 2] * sc, x[8 * o + 3] * sc, h.y, m.y, l.y);
+    split3_fp16(x[8 * o + 4] * sc, x[8 * o + 5] * sc, h.z, m.z, l.z);
+    split3_fp16(x[8 * o + 6] * sc, x[8 * o + 7] * sc, h.w, m.w, l.w);
+    uint4 *const q = jb.split + (size_t)(part * (R / 8) + o) * 3 * jb.cols + n; // [octet][high, middle, low][column]
+    q[0] = h;
+    q[jb.cols] = m;
+    q[2 * (size_t)jb.cols] = l;
+  }
+}
+//   k_dw_octets does the same with the spikes: a byte per presynaptic neuron and eight batch elements, step t0 + 1 + i of a matrix's
+// adjoints with the spikes of t0 + 1 + i - lag.  (As words in scalar registers they had to be waited for with every LDS read.)
+struct DwOctets { const uint64_t *mask; uint8_t *oct; int words, lag, t0, steps, ring; };
+struct DwOctetsJobs { DwOctets j[2 * SNN_MAXL + 1]; };
+__global__ void __launch_bounds__(256)
+k_dw_octets(DwOctetsJobs jobs, int B, int no) { // no: octets per step
+  const DwOctets &jb = jobs.j[blockIdx.z];
+  const int wave = uniform((int)threadIdx.x >> 6), lane = lane_id(), ts = (int)blockIdx.y;
+  const int at = (int)blockIdx.x * 4 + wave, o = at % no, w = at / no; // an octet of 64 neurons per wavefront
+  if (w >= jb.words || ts >= jb.steps) return;
+  const int t = jb.t0 + 1 + ts - jb.lag;
+  const __attribute__((address_space(4))) uint64_t *const m = (const __attribute__((address_space(4))) uint64_t *)jb.mask +
+      (size_t)(jb.ring > 0 ? t % jb.ring : t) * B * jb.words + w;
+  uint32_t y = 0u;
+#pragma unroll
+  for (int k = 7; k >= 0; --k) {
+    const uint64_t x = 8 * o + k < B ? m[(size_t)min(8 * o + k, B - 1) * jb.words] : 0ull;
+    y = 2u * y + (uint32_t)((x >> lane) & 1u);
+  }
+  jb.oct[((size_t)ts * no + o) * (64 * jb.words) + 64 * w + lane] = (uint8_t)y;
+}
+// Workgroup = 256 presynaptic rows x 64 columns of one matrix, four wavefronts of 64 x 64 with the fp64 accumulators in registers for
+// the whole launch; two workgroups per compute unit (256 registers a wavefront).  A stage is 32 rows of (step, batch element): one part, or
+// two steps of a SHORT batch.  The split adjoints go to LDS as they are and the spikes expanded to fp16, one stage ahead.  Parts run
+// from the last to the first.  Lane layouts as in k_up_split.
+//   Bound by the vector unit: an element of the tile costs v_cvt_f64_f32 and v_fma_f64 per part (128 instructions a wavefront and stage,
+// 5 cycles each with two wavefronts), beside 24 matrix instructions of 32 cycles; 1.75 us per stage of two workgroups, 0.9 of them the
+// fp64 additions.  Four layers of 8192, batch 32, per training step of 512 steps at 5 % activity 29.6 (k_dw_tile) -> 22.3 ms, of 200 steps at
+// 20 % 23.0 -> 9.5; three of 1024, batch 64, 1000 steps at 5 % 4.6 + 1.5 (k_dw_mfma) -> 4.2; 1500-1100, batch 24 0.93 (k_dw_mfma) -> 0.32.
+#define DWS_TJ 256
+#define DWS_TN 64
+#define DWS_LDS_A (4 * DWS_TJ * 16)
+#define DWS_LDS_B (4 * DWS_TN * 16)
+#define DWS_LDS_STAGE (DWS_LDS_A + 3 * DWS_LDS_B + 2 * DWS_TN * 4)
+template <bool SHORT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_dw_split(DwBatch batch, int per) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int total = (int)gridDim.x, die = (int)blockIdx.x & 7, rest = total & 7; // a die gets tiles that share columns
+  int tile = die * (total >> 3) + min(die, rest) + (int)(blockIdx.x >> 3), di = 0;
+  while (di + 1 < batch.count && tile >= batch.d[di + 1].tile0) ++di;
+  const DwDesc &d = batch.d[di];
+  tile -= d.tile0;
+  const int n_pre = d.n_pre, n_post = d.n_post, tj = (n_pre + DWS_TJ - 1) / DWS_TJ;
+  const int j0 = tile % tj * DWS_TJ, n0 = tile / tj * DWS_TN;
+  const int lane = lane_id(), wave = uniform((int)threadIdx.x >> 6);
+  const int parts = (d.t1 - d.t0) * per, nst = SHORT ? (parts + 1) / 2 : parts;
+  // ---- staging: a wavefront takes one octet of the stage; a lane its column and four presynaptic neurons
+  const int back = SHORT ? wave >> 1 : 0, first = SHORT ? wave & 1 : wave; // the stage's last part or the one before it; its octet there
+  uint32_t row_b = (uint32_t)n_post * 48u, row_a = 64u * (uint32_t)d.pre_words; // bytes of an octet
+  const unsigned char *const pb = reinterpret_cast<const unsigned char *>(d.split), *const pa = d.octets, *const ps = reinterpret_cast<const unsigned char *>(d.scale);
+  const uint32_t ob = 16u * (uint32_t)min(n0 + lane, n_post - 1), oa = min((uint32_t)(j0 + 4 * lane), row_a - 4u); // (outside the matrix: never stored)
+  uint32_t low = 16u * (uint32_t)n_post;
+  asm volatile("" : "+s"(row_b), "+s"(row_a), "+s"(low)); // (in registers, not read again from the arguments at every stage)
+  int odd = (d.t0 * per) & 1;
+  asm volatile("" : "+s"(odd));
+  uint4 rh, rm, rl;
+  uint32_t so, rs;
+  int part = parts - 1 - back; // of the next load
+  auto load = [&]() {
+    const int g = max(part, 0);
+    const uint32_t o = (SHORT ? 2u : 4u) * (uint32_t)g + (uint32_t)first;
+    const unsigned char *const b = pb + (size_t)o * row_b;
+    rh = *reinterpret_cast<const uint4 *>(b + ob);
+    rm = *reinterpret_cast<const uint4 *>(b + low + ob);
+    rl = *reinterpret_cast<const uint4 *>(b + 2 * (size_t)low + ob);
+    so = *reinterpret_cast<const uint32_t *>(pa + (size_t)o * row_a + oa);
+    rs = *reinterpret_cast<const uint32_t *>(ps + (size_t)(uint32_t)g * (low >> 2) + (ob >> 2));
+    part -= SHORT ? 2 : 1;
+  };
+  auto expand = [&](uint32_t x, uint32_t one) { // bits 0 ... 7 to eight fp16 values; `one` has ten zeros at its end
+    uint4 v;
+    x |= x << 15;
+    v.x = __umul24(x & 0x00010001u, one);
+    v.y = __umul24(x & 0x00040004u, one >> 2);
+    v.z = __umul24(x & 0x00100010u, one >> 4);
+    v.w = __umul24(x & 0x00400040u, one >> 6);
+    return v;
+  };
+  unsigned char *const dst = smem + 16 * lane, *const dst_a = dst + wave * (DWS_TJ * 16), *const dst_b = dst + DWS_LDS_A + wave * (DWS_TN * 16);
+  unsigned char *const dst_s = smem + DWS_LDS_A + 3 * DWS_LDS_B + 4 * (64 * back + lane); // (several wavefronts the same scales)
+  auto put = [&](int buf, int p) { // p: number of the part that was loaded
+    if (SHORT) so = p < 0 ? 0u : so; // (no second step)
+    const uint32_t one = (odd ^ p) & 1 ? 0xBC00u : 0x3C00u;
+    *reinterpret_cast<uint4 *>(dst_b + buf * DWS_LDS_STAGE) = rh;
+    *reinterpret_cast<uint4 *>(dst_b + buf * DWS_LDS_STAGE + DWS_LDS_B) = rm;
+    *reinterpret_cast<uint4 *>(dst_b + buf * DWS_LDS_STAGE + 2 * DWS_LDS_B) = rl;
+    *reinterpret_cast<uint32_t *>(dst_s + buf * DWS_LDS_STAGE) = rs;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) // neuron 4 lane + k of the tile as number 64 k + lane: no bank conflicts, wavefront k's are every fourth
+      *reinterpret_cast<uint4 *>(dst_a + buf * DWS_LDS_STAGE + 64 * 16 * k) = expand((so >> 8 * k) & 0xffu, one);
+  };
+  double acc[2][2][16];
+  double *const out = d.acc;
+  auto row_of = [&](int p, int r) { return j0 + 4 * (32 * p + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) + wave; }; // (see put)
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { // (outside the matrix: an element of it, not stored)
+      const double *const row = out + (size_t)min(row_of(p, r), n_pre - 1) * n_post;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) acc[p][q][r] = row[min(n0 + 32 * q + (lane & 31), n_post - 1)];
+    }
+  v16f sum[2][2];
+  v16f zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+  const unsigned char *const src_a = smem + (lane >> 5) * (DWS_TJ * 16) + (64 * wave + (lane & 31)) * 16;
+  const unsigned char *const src_b = smem + DWS_LDS_A + (lane >> 5) * (DWS_TN * 16) + (lane & 31) * 16;
+  const unsigned char *const src_s = smem + DWS_LDS_A + 3 * DWS_LDS_B + 4 * (lane & 31);
+  load();
+  for (int st = 0; st < nst; ++st) {
+    const int at = (st & 1) * DWS_LDS_STAGE, g0 = parts - 1 - (SHORT ? 2 * st : st); // the stage's (last) part
+    put(st & 1, g0 - back); // (the buffer read two stages ago: every wavefront has passed the barrier of the stage between)
+    load();                 // (after the last stage: the first part, not used)
+    __syncthreads();
+    uint32_t e[SHORT ? 2 : 1][2];
+#pragma unroll
+    for (int i = 0; i < (SHORT ? 2 : 1); ++i)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) e[i][q] = *reinterpret_cast<const uint32_t *>(src_s + at + 4 * (64 * i + 32 * q));
+    v8h a[2], h[2], m[2], l[2]; // one half of the stage's rows at a time
+    auto read = [&](int g) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) a[p] = *reinterpret_cast<const v8h *>(src_a + at + 2 * g * (DWS_TJ * 16) + 32 * 16 * p);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        h[q] = *reinterpret_cast<const v8h *>(src_b + at + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
+        m[q] = *reinterpret_cast<const v8h *>(src_b + at + DWS_LDS_B + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
+        l[q] = *reinterpret_cast<const v8h *>(src_b + at + 2 * DWS_LDS_B + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
+      }
+    };
+    auto multiply = [&](int q, bool fresh) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p], l[q], fresh ? zero : sum[p][q], 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p], m[q], sum[p][q], 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p], h[q], sum[p][q], 0, 0, 0);
+    };
+    auto add = [&](int q, int i) { // the sums of a part, scaled back, into the fp64 accumulators
+      const uint32_t hi = ((1150u - (e[i][q] >> 23)) << 20) | ((uint32_t)(odd ^ (g0 - i)) << 31);
+      const double inv = __hiloint2double((int)hi, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[p][q][r] = __builtin_fma((double)sum[p][q][r], inv, acc[p][q][r]);
+    };
+    // the matrix instructions of one half of the columns run beside the additions of the other
+    read(0);
+    multiply(0, true);
+    multiply(1, true);
+    if constexpr (SHORT) {
+      __builtin_amdgcn_sched_barrier(0);
+      read(1);
+      add(0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(0, true);
+      __builtin_amdgcn_sched_barrier(0);
+      add(1, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(1, true);
+      __builtin_amdgcn_sched_barrier(0);
+      add(0, 1);
+      add(1, 1);
+    } else {
+      read(1);
+      multiply(0, false);
+      multiply(1, false);
+      __builtin_amdgcn_sched_barrier(0);
+      add(0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      add(1, 0);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = row_of(p, r);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int n = n0 + 32 * q + (lane & 31);
+        if (j < n_pre && n < n_post) out[(size_t)j * n_post + n] = acc[p][q][r];
+      }
+    }
+}
+
 template <int NT, int CW>
 __global__ void __launch_bounds__(256 * CW)
 k_dw_mfma(DwBatch batch, int B) {
@@ -6389,6 +6623,41 @@ hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s) {
   if (B == 32) return RW == 8 ? go(k_dw_tile<32, 8>) : RW == 7 ? go(k_dw_tile<32, 7>) : go(k_dw_tile<32, 6>);
   if (B == 64) return RW == 8 ? go(k_dw_tile<64, 8>) : RW == 7 ? go(k_dw_tile<64, 7>) : go(k_dw_tile<64, 6>);
   return RW == 8 ? go(k_dw_tile<0, 8>) : RW == 7 ? go(k_dw_tile<0, 7>) : go(k_dw_tile<0, 6>);
+}
+
+hipError_t launch_dw_split(DwBatch batch, int B, hipStream_t s) {
+  if (batch.count <= 0) return hipSuccess;
+  if (B < 1 || B > 64) return hipErrorInvalidValue;
+  const int no = dw_split_octets(B), per = B <= 16 ? 1 : no / 4;
+  DwRowsJobs rows{};
+  DwOctetsJobs octs{};
+  int n_rows = 0, cols = 0, steps = 0, total = 0, words = 0;
+  for (int i = 0; i < batch.count; ++i) {
+    DwDesc &d = batch.d[i];
+    if (d.t1 <= d.t0 || d.t1 - d.t0 > SNN_BWD_TILE || !d.scale || !d.octets || !d.split) return hipErrorInvalidValue;
+    d.tiles_n = (d.n_post + DWS_TN - 1) / DWS_TN;
+    d.tile0 = total;
+    total += ((d.n_pre + DWS_TJ - 1) / DWS_TJ) * d.tiles_n;
+    octs.j[i] = DwOctets{d.pre_mask, d.octets, d.pre_words, d.lag, d.t0, d.t1 - d.t0, d.pre_ring};
+    words = std::max(words, d.pre_words);
+    steps = std::max(steps, d.t1 - d.t0);
+    bool seen = false; // the matrices of a layer share their adjoints
+    for (int k = 0; k < n_rows; ++k) seen = seen || rows.j[k].scale == d.scale;
+    if (seen) continue;
+    if (n_rows > SNN_MAXL) return hipErrorInvalidValue;
+    rows.j[n_rows++] = DwRows{d.post + (size_t)(d.t0 - d.t_base) * d.slot_stride + d.post_off, d.split, d.scale, d.slot_stride, d.post_stride,
+                              d.n_post, d.t1 - d.t0};
+    cols = std::max(cols, d.n_post);
+  }
+  auto go = [&](auto rows_kern, auto kern) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * DWS_LDS_STAGE);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_dw_octets, dim3((words * no + 3) / 4, steps, batch.count), dim3(256), 0, s, octs, B, no);
+    hipLaunchKernelGGL(rows_kern, dim3((cols + 255) / 256, steps * per, n_rows), dim3(256), 0, s, rows, B, per);
+    hipLaunchKernelGGL(kern, dim3(total), dim3(256), 2 * DWS_LDS_STAGE, s, batch, per);
+    return hipGetLastError();
+  };
+  return B <= 16 ? go(k_dw_split_rows<true>, k_dw_split<true>) : go(k_dw_split_rows<false>, k_dw_split<false>);
 }
 
 hipError_t launch_dw_mfma(DwBatch batch, int B, hipStream_t s) {

@@ -39,6 +39,20 @@ inline bool seq_by_column(const MaskedLayer *layers, int n) {
 inline bool split_product(int N, int K) { return N >= 1024 && K >= 1024; }
 constexpr size_t split_row_bytes(int K) { return (size_t)(K + 31) / 32 * 128; } // of a split matrix: whole tiles of 32 elements
 
+// ---- weight gradients of large matrices -----------------------------------------------------------
+// Tiles of 256 x 64 of a network's matrices (k_dw_split), and where that kernel takes its weight gradients: by the shapes and the batch
+// alone, as it differs from the others in the last bits.  Training steps of 96 steps in chunks of 32, us with the better of k_dw_tile and
+// k_dw_mfma / with k_dw_split, at 3 % and 45 % activity:
+//   3 x 512 (90 tiles)    batch 16 1427 / 1459, 1890 / 1910    32 1606 / 1588, 2046 / 2027
+//   2 x 700 (124)         batch 16 1672 / 1699, 2311 / 2333    32 1800 / 1783, 2455 / 2444
+//   3 x 640 (173)         batch  8 1830 / 1873, 2473 / 2509    12 1918 / 1884, 2569 / 2555    32 2161 / 2053, 2804 / 2697
+//   3 x 1024 (372)        batch  8 2070 / 2092, 3257 / 3202    12 2199 / 2151, 3419 / 3266    32 2532 / 2422, 3958 / 3611
+//   2048 (328)            batch  8 1498 / 1539, 2737 / 2659    12 1560 / 1574, 2881 / 2726    32 1734 / 1713, 3431 / 3077
+inline int dw_split_tiles(int n_pre, int n_post) { return ((n_pre + 255) / 256) * ((n_post + 63) / 64); }
+// octets of batch elements per step: two, or whole parts of four
+constexpr int dw_split_octets(int B) { return B <= 16 ? 2 : (B + 31) / 32 * 4; }
+inline bool dw_split_pays(int tiles, int B) { return tiles >= 150 && B >= 12 && B <= 64; }
+
 // ---- sequential forward part of layers of 257..1024 neurons (k_layer_seq_lds) --------------------
 // Columns per slice, wavefronts per workgroup, groups of batch elements per job, slices per unit, units (job, group); entries of a
 // list of active neurons; dynamic LDS of a workgroup.

@@ -321,6 +321,42 @@ def test_tiled_weight_gradients_at_the_edges_of_tiles(hidden, B, T, monkeypatch)
     assert _identical(got["mfma"], got["tile"])
 
 
+@pytest.mark.parametrize("hidden,n_in,B,T,masked", [
+    ((1024, 1024, 1024), 700, 13, 7, False), ((1024, 1030, 1090), 65, 16, 6, False),   # two steps per stage, odd and even numbers of them
+    ((1100, 1500, 1100), 31, 17, 5, False), ((1024, 1024, 1024), 256, 32, 7, False),  # one part per step
+    ((1025, 1024, 1023), 257, 33, 5, False), ((1024, 1024, 1024), 64, 64, 4, False),  # two
+    ((2048, 2048), 1000, 20, 6, True)])                                               # beside gradients per existing synapse
+def test_weight_gradients_on_the_fp16_matrix_cores(hidden, n_in, B, T, masked, monkeypatch):
+    """Weight gradients of large matrices with the adjoints split into three fp16 values, ragged tiles, steps and batches: bit-identical
+    however the time axis is cut, and the contraction on the fp32 matrix cores but for the rounding of a step's sum (a few times
+    2^-24 of it, of either sign: below 2^-21 in the 2-norm)."""
+    w = synth.Workload("dws_" + "x".join(map(str, hidden)), n_in, hidden, 7, T=T, B=B, p_in=0.2, gain=0.5, seed=B)
+    d = synth.generate(w)
+    got = {}
+    for mode in ("split", "mfma"):
+        if mode == "mfma":
+            monkeypatch.setenv("SNN_DW", mode)
+        net = snn.from_workload(w, d)
+        try:
+            if masked:
+                mask = (np.random.default_rng(3).random((hidden[1], hidden[1])) < 0.1).astype(np.uint8)
+                net.snn_set_weights(snn.SNN_W_REC, 1, d["W_rec"][1] * mask, mask)
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            for strat, C, F in ((snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 1), (snn.SNN_DOUBLE, 4, 3)):
+                net.snn_bptt(strat, C, F)
+                g = _gpu_grads(net, len(hidden))
+                assert mode not in got or _identical(got[mode], g), (mode, strat)
+                got[mode] = g
+        finally:
+            net.snn_destroy()
+    for a, b in zip(got["split"][0] + got["split"][1] + [got["split"][2]], got["mfma"][0] + got["mfma"][1] + [got["mfma"][2]]):
+        assert np.linalg.norm(a.astype(np.float64) - b) < 2.0 ** -21 * np.linalg.norm(b.astype(np.float64))
+    if masked:
+        assert np.array_equal(got["split"][1][1], got["mfma"][1][1]) and not np.array_equal(got["split"][1][0], got["mfma"][1][0])
+    else:
+        assert not _identical(got["split"], got["mfma"])  # the other kernel ran
+
+
 @pytest.mark.parametrize("hidden,B,T", [((520, 300), 20, 12), ((1024,), 32, 10), ((640, 640, 640), 64, 9)])
 def test_chip_wide_adjoint_two_batch_groups_per_workgroup(hidden, B, T, monkeypatch):
     """Layers of 257..1024 neurons with an even number of 16-element batch groups: a workgroup of the chip-wide
