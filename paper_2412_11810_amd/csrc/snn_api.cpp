@@ -201,18 +201,18 @@ void fill_shape(const snn_config &c, NetDev *n) {
 
 int pre_of(const NetDev &n, int l) { return l == 0 ? n.n_in : n.N[l - 1]; }
 
+// Does the recurrent matrix of layer l go through k_dw_split, where the network's matrices do?  Not a wide one whose synapses are few enough
+// for k_dw_csr (whether or not that runs in this step: the choice must not follow the activity).
+bool dw_rec_split(const snn_ctx *c, int l) {
+  return c->dw_ws && (dw_split_masked(c->net.N[l]) || !(c->csr_sub[l] && c->csr_dw_ok[l] && c->acc_csr[l] && c->net.B <= 32));
+}
+
 // Does the recurrent matrix of layer l accumulate its gradient per existing synapse (k_dw_csr)?  Where the tiled
 // event-driven kernel runs, the compressed rows are in use (net.csr_sub follows the SNN_CSR hook), no row is too
 // long for it and a time step fits its tile.  Constant during a training step.
 bool dw_rec_csr(const snn_ctx *c, int l) {
   return c->dw_tile && c->dw_csr && !c->dw_event_driven && c->net.csr_sub[l] && c->csr_dw_ok[l] && c->acc_csr[l] &&
-         c->net.B <= 32;
-}
-
-// Does the recurrent matrix of layer l go through k_dw_split, where the network's matrices do?  Not if its synapses are few enough for
-// k_dw_csr (whether or not that runs in this step: the choice must not follow the activity).
-bool dw_rec_split(const snn_ctx *c, int l) {
-  return c->dw_ws && !(c->csr_sub[l] && c->csr_dw_ok[l] && c->acc_csr[l] && c->net.B <= 32);
+         c->net.B <= 32 && !dw_rec_split(c, l);
 }
 
 // Test hooks that force a kernel flavour (documented in snn.h): read from the environment at the start of every

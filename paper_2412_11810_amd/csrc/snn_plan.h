@@ -52,6 +52,13 @@ inline int dw_split_tiles(int n_pre, int n_post) { return ((n_pre + 255) / 256) 
 // octets of batch elements per step: two, or whole parts of four
 constexpr int dw_split_octets(int B) { return B <= 16 ? 2 : (B + 31) / 32 * 4; }
 inline bool dw_split_pays(int tiles, int B) { return tiles >= 150 && B >= 12 && B <= 64; }
+// Of a masked recurrent matrix of such a network: the dense gradients here rather than the existing synapses' by k_dw_csr, which has few
+// workgroups (256 rows x 512 columns, a compute unit each) where a layer is not wide.  Training steps of 96 steps (64 from 4096
+// neurons, 32 of 8192) in chunks of 32, density 0.1, us by synapse / dense, batch 16, activity about 0, 4 and 15 to 30 %:
+//   3 x 1536 3076 / 2800, 3545 / 3037, 4202 / 3824    2 x 2048 2607 / 2444, 2949 / 2654, 3501 / 3186    4 x 2048 4469 / 4308, 5316 / 4857, 7155 / 6584
+//   2 x 3000 5452 / 5461, 6842 / 6765, 8779 / 8416    2 x 4096 4674 / 4778, 6279 / 6326, 8504 / 8292    8192 2347 / 2745, 2917 / 3302, 4030 / 4336
+// (the same at batch 12 and 32 and at density 0.05: 2 x 3000 4910 / 4930, 5948 / 5888, 6535 / 6236).
+inline bool dw_split_masked(int N) { return N <= 3072; }
 
 // ---- sequential forward part of layers of 257..1024 neurons (k_layer_seq_lds) --------------------
 // Columns per slice, wavefronts per workgroup, groups of batch elements per job, slices per unit, units (job, group); entries of a

@@ -325,7 +325,7 @@ def test_tiled_weight_gradients_at_the_edges_of_tiles(hidden, B, T, monkeypatch)
     ((1024, 1024, 1024), 700, 13, 7, False), ((1024, 1030, 1090), 65, 16, 6, False),   # two steps per stage, odd and even numbers of them
     ((1100, 1500, 1100), 31, 17, 5, False), ((1024, 1024, 1024), 256, 32, 7, False),  # one part per step
     ((1025, 1024, 1023), 257, 33, 5, False), ((1024, 1024, 1024), 64, 64, 4, False),  # two
-    ((2048, 2048), 1000, 20, 6, True)])                                               # beside gradients per existing synapse
+    ((2048, 2048), 1000, 20, 6, True), ((1100, 3200), 100, 20, 4, True)])             # masked: dense, and beside gradients per synapse
 def test_weight_gradients_on_the_fp16_matrix_cores(hidden, n_in, B, T, masked, monkeypatch):
     """Weight gradients of large matrices with the adjoints split into three fp16 values, ragged tiles, steps and batches: bit-identical
     however the time axis is cut, and the contraction on the fp32 matrix cores but for the rounding of a step's sum (a few times
@@ -351,10 +351,8 @@ def test_weight_gradients_on_the_fp16_matrix_cores(hidden, n_in, B, T, masked, m
             net.snn_destroy()
     for a, b in zip(got["split"][0] + got["split"][1] + [got["split"][2]], got["mfma"][0] + got["mfma"][1] + [got["mfma"][2]]):
         assert np.linalg.norm(a.astype(np.float64) - b) < 2.0 ** -21 * np.linalg.norm(b.astype(np.float64))
-    if masked:
-        assert np.array_equal(got["split"][1][1], got["mfma"][1][1]) and not np.array_equal(got["split"][1][0], got["mfma"][1][0])
-    else:
-        assert not _identical(got["split"], got["mfma"])  # the other kernel ran
+    assert not np.array_equal(got["split"][1][0], got["mfma"][1][0])  # the other kernel ran
+    assert np.array_equal(got["split"][1][1], got["mfma"][1][1]) == (hidden[1] == 3200)
 
 
 @pytest.mark.parametrize("hidden,B,T", [((520, 300), 20, 12), ((1024,), 32, 10), ((640, 640, 640), 64, 9)])
