@@ -37,6 +37,7 @@ def progress(msg):
 
 HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 MFMA_F32_PEAK_TF = 157.3  # MI355X published fp32 matrix peak
+MFMA_F16_PEAK_TF = 2516.6 # MI355X published dense fp16 matrix peak
 ALU_F32_PEAK_TF = 157.3   # MI355X published fp32 vector peak (256 CUs x 4 SIMDs x 64 flop/clk x 2.4 GHz)
 
 # strategy parameters per benchmark configuration: (coarse, fine); budgets from the configurations
@@ -454,8 +455,20 @@ def main():
     adj_kernel = ("k_adj_rec_rows" if ws_env in ("rows", "rows_all") or (args.surr_window > 0 and ws_env == "" and not masked_rows) else
                   "k_adj_rec_csrw" if masked_rows else
                   "k_adj_rec_wsm" if nmax <= 2048 and ws_env != "stream" else "k_adj_rec_wide")
-    # inter-layer products of matrices from 2048 x 2048: one launch of the 128 x 128-tile kernel per product
-    gemm_big = L > 1 and min(w.n_hidden) >= 2048
+    # inter-layer products of matrices from 1024 x 1024: split into fp16 halves, three products, one launch per stage
+    gemm_big = L > 1 and min(w.n_hidden) >= 1024
+    if gemm_big:
+        model["up_gemm"] = ("mfma16", 3.0 * model["up_gemm"][1])
+    # weight gradients of networks whose matrices have 150 tiles of 256 x 64 and more, batch 12 to 64: adjoints split into three fp16
+    # values (the time includes the gradients per synapse of masked matrices wider than 3072)
+    pre_n = [w.n_in] + list(w.n_hidden[:-1])
+    mats = [(pre_n[l], w.n_hidden[l]) for l in range(L)] + [(w.n_hidden[-1], w.n_out)]
+    recs = [(n, n) for n in w.n_hidden]
+    dw_split = (not dw_env and 12 <= w.B <= 64 and nmax > 256 and
+                sum(-(-a // 256) * -(-b // 64) for a, b in mats + recs) >= 150)
+    if dw_split:
+        dense = mats + [r for r in recs if not (w.rec_density < 1.0 and w.B <= 32 and r[0] > 3072)]
+        model["dw"] = ("mfma16", 6.0 * w.T * (16 if w.B <= 16 else 32 * -(-w.B // 32)) * sum(float(a) * b for a, b in dense))
     # launches of each kind's main kernel per step (layers that share a width and a pipeline stage share a launch)
     n_stage = n_tiles + 2 * (L - 1)
     n_cur = n_rec
@@ -466,7 +479,7 @@ def main():
         n_cur = len(cached) + sum(1 for o in sched if o[0] == "REFWD2" and o[1] // C not in cached)
     launches = {"fwd_seq": n_stage, "fwd_currents": n_stage, "recompute": max(1, n_cur), "scan": max(1, n_rec),
                 "adjoint": n_bwd * L if (max(w.n_hidden) > 1024 and adj_kernel == "k_adj_rec_wide") else n_bwd + L - 1,
-                "up_gemm": n_bwd * (L - 1) if gemm_big else max(1, n_bwd + L - 2),
+                "up_gemm": max(1, n_bwd + L - 2),
                 "dw": n_bwd + L - 1, "bwd_stage": max(1, n_bwd + L - 1),
                 "fwd_stage": max(1, n_tiles + 2 * L - 2), "bwd_inter": max(1, n_bwd + L - 2)}
     if st.ms_bwd_stage > 0:
@@ -499,17 +512,18 @@ def main():
                  # the event-by-event gather k_currents, with k_currents_csr for masked recurrent matrices)
                  "fwd_currents": ("k_currents_dense<4,0>" if np.mean(rates) >= 0.035 else "k_currents") if big else "k_currents_mfma",
                  "recompute": ("k_currents_dense<4,1>" if np.mean(rates) >= 0.035 else "k_currents") if big else "k_currents_mfma",
-                 "scan": "k_scan", "up_gemm": "k_up_gemm<4,4,2,2>" if gemm_big else ("k_bwd_inter" if L > 2 else "k_up_gemm"), "dw": "k_dw_tile" if dw_tile else "k_dw_mfma", "bwd_stage": "k_bwd_stage", "fwd_stage": "k_fwd_stage_csr" if fwd_fused_wide else "k_fwd_stage",
+                 "scan": "k_scan", "up_gemm": "k_up_split" if gemm_big else ("k_bwd_inter" if L > 2 else "k_up_gemm"), "dw": "k_dw_split" if dw_split else "k_dw_tile" if dw_tile else "k_dw_mfma", "bwd_stage": "k_bwd_stage", "fwd_stage": "k_fwd_stage_csr" if fwd_fused_wide else "k_fwd_stage",
                  "bwd_inter": "k_bwd_inter",
                  "adjoint": "k_adj_rec_rs" if not wide else ("k_adj_rec_wsm" if max(w.n_hidden) <= 1024 else adj_kernel)}
-    peaks = {"hbm": (HBM_PEAK_GBS, "GB/s", 1e9), "alu": (ALU_F32_PEAK_TF, "TFLOP/s", 1e12), "mfma32": (MFMA_F32_PEAK_TF, "TFLOP/s", 1e12)}
+    peaks = {"hbm": (HBM_PEAK_GBS, "GB/s", 1e9), "alu": (ALU_F32_PEAK_TF, "TFLOP/s", 1e12), "mfma32": (MFMA_F32_PEAK_TF, "TFLOP/s", 1e12),
+             "mfma16": (MFMA_F16_PEAK_TF, "TFLOP/s", 1e12)}
     kinds = {}
     for k, (bound, work) in model.items():
         if ms[k] <= 0:
             continue
         peak, unit, scale = peaks[bound]
         ach = work / (ms[k] * 1e-3) / scale
-        kinds[k] = {"kernel": kernel_of[k], "bound": "mfma" if bound == "mfma32" else bound, "ms_per_step": round(ms[k], 3),
+        kinds[k] = {"kernel": kernel_of[k], "bound": "mfma" if bound.startswith("mfma") else bound, "ms_per_step": round(ms[k], 3),
                     "launches_per_step": launches[k], "avg_launch_ms": round(ms[k] / launches[k], 4),
                     "achieved": round(ach, 3), "peak": round(peak, 1), "unit": unit, "frac": round(ach / peak, 5)}
         tr = read_traffic(w.name, args.strategy, kernel_of[k])
