@@ -597,12 +597,15 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
         at_scale[l] = take(octets * cols * sizeof(float));
       }
       for (int i = 0; i <= 2 * L; ++i) at_octets[i] = take(octets * 64 * n.Wd[i == 2 * L ? L : (i + 1) / 2]);
-      HIPCHK(c, hipMalloc(&c->dw_ws, sum));
-      for (int l = 0; l <= L; ++l) {
+      if (hipMalloc(&c->dw_ws, sum) != hipSuccess) { // a device without the room: the kernels that need none
+        (void)hipGetLastError();
+        c->dw_ws = nullptr;
+      }
+      for (int l = 0; c->dw_ws && l <= L; ++l) {
         c->dw_split[l] = reinterpret_cast<uint4 *>(c->dw_ws + at_split[l]);
         c->dw_scale[l] = reinterpret_cast<float *>(c->dw_ws + at_scale[l]);
       }
-      for (int i = 0; i <= 2 * L; ++i) c->dw_octets[i] = c->dw_ws + at_octets[i];
+      for (int i = 0; c->dw_ws && i <= 2 * L; ++i) c->dw_octets[i] = c->dw_ws + at_octets[i];
     }
   }
   if (const char *e = std::getenv("SNN_DW")) {
@@ -1577,13 +1580,10 @@ struct BwdPipe {
         HIPCHK(c, launch_dw(n.mask[l + 1], n.Wd[l + 1], n.N[l], 1, t.vbuf, slot, SN, n.off[l], n.N[l], B, t.t0, t.t1, t.base, c->acc_rec[l], s, n.mring[l + 1]));
       }
     } else {
-      DwBatch all{}, db{}, split{};
-      fill_dw_batch(&all);
-      db.wide = all.wide;
-      for (int i = 0; i < all.count; ++i) (all.d[i].split ? split.d[split.count++] : db.d[db.count++]) = all.d[i];
+      DwBatch db{};
+      fill_dw_batch(&db);
       if (c->dw_tile) HIPCHK(c, launch_dw_tile(db, B, s));
       else HIPCHK(c, launch_dw_mfma(db, B, s));
-      HIPCHK(c, launch_dw_split(split, B, s));
     }
     tm->end();
     done.clear();

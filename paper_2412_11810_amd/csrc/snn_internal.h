@@ -237,11 +237,10 @@ struct DwBatch {
   int count;
   int wide;                 // tile shape, fixed per network (see snn_dw_wide_tiles)
 };
+// (matrices with a workspace for it go through k_dw_split, batch sizes up to 64)
 hipError_t launch_dw_mfma(DwBatch batch, int B, hipStream_t s);
 // The same update event by event from LDS tiles (see k_dw_tile); batch sizes up to 64.
 hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s);
-// The same update on the fp16 matrix cores (see k_dw_split); batch sizes up to 64.
-hipError_t launch_dw_split(DwBatch batch, int B, hipStream_t s);
 // The recurrences of a stage and the weight-gradient contraction of the previous stage in one launch
 // (see k_bwd_stage).  Only for networks bwd_stage_fusable() accepts; the caller guarantees that the two
 // parts touch different tiles.

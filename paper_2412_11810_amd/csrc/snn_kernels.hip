@@ -6591,42 +6591,13 @@ static int dw_tile_rows(const DwBatch &batch) {
   return best;
 }
 
-hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s) {
+// Takes the matrices that go through k_dw_split out of the batch.
+static hipError_t launch_dw_split(DwBatch *all, int B, hipStream_t s) {
+  DwBatch batch{}, others{};
+  others.wide = all->wide;
+  for (int i = 0; i < all->count; ++i) (all->d[i].split ? batch.d[batch.count++] : others.d[others.count++]) = all->d[i];
   if (batch.count <= 0) return hipSuccess;
-  if (B > 64) return hipErrorInvalidValue; // a tile is at least one whole time step of at most 64 rows
-  { // matrices that go through their compressed rows: a launch of their own
-    DwBatch cs{}, dn{};
-    cs.wide = dn.wide = batch.wide;
-    for (int i = 0; i < batch.count; ++i) (batch.d[i].csr_sub ? cs.d[cs.count++] : dn.d[dn.count++]) = batch.d[i];
-    if (cs.count) {
-      const hipError_t e = launch_dw_csr(cs, B, s);
-      if (e != hipSuccess) return e;
-      batch = dn;
-      if (batch.count <= 0) return hipSuccess;
-    }
-  }
-  const int RW = dw_tile_rows(batch);
-  int total = 0;
-  for (int i = 0; i < batch.count; ++i) {
-    if (batch.d[i].t1 <= batch.d[i].t0) return hipErrorInvalidValue;
-    batch.d[i].tiles_n = (batch.d[i].n_post + 255) / 256;
-    batch.d[i].tile0 = total;
-    total += ((batch.d[i].n_pre + DWT_WAVES * RW - 1) / (DWT_WAVES * RW)) * batch.d[i].tiles_n;
-  }
-  const size_t lds = (size_t)2 * 64 * 256 * sizeof(float) + (size_t)2 * 3 * 64 * sizeof(uint64_t);
-  auto go = [&](auto kern) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(total), dim3(64 * DWT_WAVES), lds, s, batch, B);
-    return hipGetLastError();
-  };
-  if (B == 32) return RW == 8 ? go(k_dw_tile<32, 8>) : RW == 7 ? go(k_dw_tile<32, 7>) : go(k_dw_tile<32, 6>);
-  if (B == 64) return RW == 8 ? go(k_dw_tile<64, 8>) : RW == 7 ? go(k_dw_tile<64, 7>) : go(k_dw_tile<64, 6>);
-  return RW == 8 ? go(k_dw_tile<0, 8>) : RW == 7 ? go(k_dw_tile<0, 7>) : go(k_dw_tile<0, 6>);
-}
-
-hipError_t launch_dw_split(DwBatch batch, int B, hipStream_t s) {
-  if (batch.count <= 0) return hipSuccess;
+  *all = others;
   if (B < 1 || B > 64) return hipErrorInvalidValue;
   const int no = dw_split_octets(B), per = B <= 16 ? 1 : no / 4;
   DwRowsJobs rows{};
@@ -6660,7 +6631,49 @@ hipError_t launch_dw_split(DwBatch batch, int B, hipStream_t s) {
   return B <= 16 ? go(k_dw_split_rows<true>, k_dw_split<true>) : go(k_dw_split_rows<false>, k_dw_split<false>);
 }
 
+hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s) {
+  {
+    const hipError_t e = launch_dw_split(&batch, B, s);
+    if (e != hipSuccess) return e;
+  }
+  if (batch.count <= 0) return hipSuccess;
+  if (B > 64) return hipErrorInvalidValue; // a tile is at least one whole time step of at most 64 rows
+  { // matrices that go through their compressed rows: a launch of their own
+    DwBatch cs{}, dn{};
+    cs.wide = dn.wide = batch.wide;
+    for (int i = 0; i < batch.count; ++i) (batch.d[i].csr_sub ? cs.d[cs.count++] : dn.d[dn.count++]) = batch.d[i];
+    if (cs.count) {
+      const hipError_t e = launch_dw_csr(cs, B, s);
+      if (e != hipSuccess) return e;
+      batch = dn;
+      if (batch.count <= 0) return hipSuccess;
+    }
+  }
+  const int RW = dw_tile_rows(batch);
+  int total = 0;
+  for (int i = 0; i < batch.count; ++i) {
+    if (batch.d[i].t1 <= batch.d[i].t0) return hipErrorInvalidValue;
+    batch.d[i].tiles_n = (batch.d[i].n_post + 255) / 256;
+    batch.d[i].tile0 = total;
+    total += ((batch.d[i].n_pre + DWT_WAVES * RW - 1) / (DWT_WAVES * RW)) * batch.d[i].tiles_n;
+  }
+  const size_t lds = (size_t)2 * 64 * 256 * sizeof(float) + (size_t)2 * 3 * 64 * sizeof(uint64_t);
+  auto go = [&](auto kern) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(total), dim3(64 * DWT_WAVES), lds, s, batch, B);
+    return hipGetLastError();
+  };
+  if (B == 32) return RW == 8 ? go(k_dw_tile<32, 8>) : RW == 7 ? go(k_dw_tile<32, 7>) : go(k_dw_tile<32, 6>);
+  if (B == 64) return RW == 8 ? go(k_dw_tile<64, 8>) : RW == 7 ? go(k_dw_tile<64, 7>) : go(k_dw_tile<64, 6>);
+  return RW == 8 ? go(k_dw_tile<0, 8>) : RW == 7 ? go(k_dw_tile<0, 7>) : go(k_dw_tile<0, 6>);
+}
+
 hipError_t launch_dw_mfma(DwBatch batch, int B, hipStream_t s) {
+  {
+    const hipError_t e = launch_dw_split(&batch, B, s);
+    if (e != hipSuccess) return e;
+  }
   if (batch.count <= 0) return hipSuccess;
   for (int i = 0; i < batch.count; ++i)
     if (batch.d[i].t1 <= batch.d[i].t0) return hipErrorInvalidValue;
