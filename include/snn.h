@@ -279,7 +279,7 @@ void snn_destroy(snn_ctx *ctx);
  *     SNN_HOST_TIER=dma|direct   Remote/Double checkpoints by hipMemcpyAsync / written and read by the kernels
  *                                through the mapped pinned block (default: direct up to 1 MiB per state)
  *     SNN_DW=event|tile|mfma     weight gradients by the event-by-event kernel / the event-driven tiled kernel
- *                                (batch <= 64) / the matrix-core contraction (default: split into fp16 for batches of 12
+ *                                (batch <= 64) / the matrix-core contraction (default: in three bf16 parts for batches of 12
  *                                to 64 and matrices that fill the chip, which differs in the last bits; else tiled
  *                                when some weight matrix has 32 MB or more, else the contraction or tiled by the
  *                                activity)

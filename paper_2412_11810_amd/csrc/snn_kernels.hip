@@ -4166,21 +4166,29 @@ __device__ __forceinline__ void dw_mfma_body(const DwBatch &batch, int B, int vb
     }
 }
 
-// B5 for large matrices, whatever the activity: dW += S^T . P on the fp16 matrix cores.  The spikes are exact in fp16 and an adjoint is
-// the sum of three fp16 values (two, as in k_up_split, leave out its last bit half of the time: with them the gradients of the top layer
-// were up to a tenth further from 64 bits than the event-by-event sums), so three products of a part of a time step (at most 32 batch
-// elements), summed in fp32, give its contribution, which goes into the fp64 accumulator.  Parts of odd number run
+// B5 for large matrices, whatever the activity: dW += S^T . P on the 16-bit matrix cores.  The spikes are exact in bf16, and a 32-bit
+// value is the sum of three bf16 ones, exactly (8 bits each; bf16 has the exponents of fp32, so that holds for every element of a
+// column, however far below its largest).  Three products of a part of a time step (at most 32 batch
+// elements), summed in fp32, give its contribution, which goes into the fp64 accumulator: of a single spike, the adjoint itself.  Parts of odd number run
 // with spikes of -1 (what the matrix cores cut off below an accumulator, always towards minus infinity, changes sides and does not
 // add up over the steps).  Number and scale of a part do not depend on how the time axis is cut: the same bits for every strategy.
 //   k_dw_split_rows lays the adjoints out as the kernel reads them: of the part's values of a column, scaled by the power of two that
-// brings the largest to 2^14 ... 2^15, eight batch elements' high parts in 16 bytes, then the middle and the low ones, zeros past the
-// last.
+// brings the largest to 2^100 ... 2^101 (at most by 2^127: so the low parts of values down to the smallest fp32 ones stay normal
+// numbers), eight batch elements' high parts in 16 bytes, then the middle and the low ones, zeros past the last.
 // SHORT: a batch of at most 16, a part is a step of 16 rows; else a step is `per` parts of 32.
-static __device__ __forceinline__ void split3_fp16(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) {
-  const v2h hv = {(_Float16)x, (_Float16)y};
-  const float rx = __builtin_fmaf((float)hv[0], -1.0f, x), ry = __builtin_fmaf((float)hv[1], -1.0f, y);
-  h = __builtin_bit_cast(uint32_t, hv);
-  split_fp16(rx, ry, m, l);
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+static __device__ __forceinline__ uint32_t round_bf16(float &x, float &y) { // both in 16 bits, what is left of them in 32 (exactly)
+  const v2b v = {(__bf16)x, (__bf16)y};
+  const uint32_t h = __builtin_bit_cast(uint32_t, v);
+  x = x - __uint_as_float(h << 16);
+  y = y - __uint_as_float(h & 0xffff0000u);
+  return h;
+}
+static __device__ __forceinline__ void split3_bf16(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) {
+  h = round_bf16(x, y);
+  m = round_bf16(x, y);
+  l = round_bf16(x, y);
 }
 struct DwRows { const float *post; uint4 *split; float *scale; size_t slot_stride; int post_stride, cols, steps; };
 struct DwRowsJobs { DwRows j[SNN_MAXL + 1]; };
@@ -4197,15 +4205,16 @@ k_dw_split_rows(DwRowsJobs jobs, int B, int per) {
   for (int b = 0; b < R; ++b) x[b] = b0 + b < B ? p[(size_t)b * jb.post_stride] : 0.0f;
 #pragma unroll
   for (int b = 0; b < R; ++b) mx = fmaxf(mx, fabsf(x[b]));
-  const float sc = row_scale(mx);
+  const uint32_t e = __float_as_uint(mx) >> 23;
+  const float sc = __uint_as_float((e < 100u ? 254u : 354u - e) << 23);
   jb.scale[(size_t)part * jb.cols + n] = sc;
 #pragma unroll
   for (int o = 0; o < R / 8; ++o) {
     uint4 h, m, l;
-    split3_fp16(x[8 * o] * sc, x[8 * o + 1] * sc, h.x, m.x, l.x);
-    split3_fp16(x[8 * o + 2] * sc, x[8 * o + 3] * sc, h.y, m.y, l.y);
-    split3_fp16(x[8 * o + 4] * sc, x[8 * o + 5] * sc, h.z, m.z, l.z);
-    split3_fp16(x[8 * o + 6] * sc, x[8 * o + 7] * sc, h.w, m.w, l.w);
+    split3_bf16(x[8 * o] * sc, x[8 * o + 1] * sc, h.x, m.x, l.x);
+    split3_bf16(x[8 * o + 2] * sc, x[8 * o + 3] * sc, h.y, m.y, l.y);
+    split3_bf16(x[8 * o + 4] * sc, x[8 * o + 5] * sc, h.z, m.z, l.z);
+    split3_bf16(x[8 * o + 6] * sc, x[8 * o + 7] * sc, h.w, m.w, l.w);
     uint4 *const q = jb.split + (size_t)(part * (R / 8) + o) * 3 * jb.cols + n; // [octet][high, middle, low][column]
     q[0] = h;
     q[jb.cols] = m;
@@ -4235,7 +4244,7 @@ k_dw_octets(DwOctetsJobs jobs, int B, int no) { // no: octets per step
 }
 // Workgroup = 256 presynaptic rows x 64 columns of one matrix, four wavefronts of 64 x 64 with the fp64 accumulators in registers for
 // the whole launch; two workgroups per compute unit (256 registers a wavefront).  A stage is 32 rows of (step, batch element): one part, or
-// two steps of a SHORT batch.  The split adjoints go to LDS as they are and the spikes expanded to fp16, one stage ahead.  Parts run
+// two steps of a SHORT batch.  The split adjoints go to LDS as they are and the spikes expanded to bf16, one stage ahead.  Parts run
 // from the last to the first.  Lane layouts as in k_up_split.
 //   Bound by the vector unit: an element of the tile costs v_cvt_f64_f32 and v_fma_f64 per part (128 instructions a wavefront and stage,
 // 5 cycles each with two wavefronts), beside 24 matrix instructions of 32 cycles; 1.75 us per stage of two workgroups, 0.9 of them the
@@ -4282,7 +4291,7 @@ k_dw_split(DwBatch batch, int per) {
     rs = *reinterpret_cast<const uint32_t *>(ps + (size_t)(uint32_t)g * (low >> 2) + (ob >> 2));
     part -= SHORT ? 2 : 1;
   };
-  auto expand = [&](uint32_t x, uint32_t one) { // bits 0 ... 7 to eight fp16 values; `one` has ten zeros at its end
+  auto expand = [&](uint32_t x, uint32_t one) { // bits 0 ... 7 to eight bf16 values; `one` has seven zeros at its end
     uint4 v;
     x |= x << 15;
     v.x = __umul24(x & 0x00010001u, one);
@@ -4295,7 +4304,7 @@ k_dw_split(DwBatch batch, int per) {
   unsigned char *const dst_s = smem + DWS_LDS_A + 3 * DWS_LDS_B + 4 * (64 * back + lane); // (several wavefronts the same scales)
   auto put = [&](int buf, int p) { // p: number of the part that was loaded
     if (SHORT) so = p < 0 ? 0u : so; // (no second step)
-    const uint32_t one = (odd ^ p) & 1 ? 0xBC00u : 0x3C00u;
+    const uint32_t one = (odd ^ p) & 1 ? 0xBF80u : 0x3F80u;
     *reinterpret_cast<uint4 *>(dst_b + buf * DWS_LDS_STAGE) = rh;
     *reinterpret_cast<uint4 *>(dst_b + buf * DWS_LDS_STAGE + DWS_LDS_B) = rm;
     *reinterpret_cast<uint4 *>(dst_b + buf * DWS_LDS_STAGE + 2 * DWS_LDS_B) = rl;
@@ -4333,24 +4342,24 @@ k_dw_split(DwBatch batch, int per) {
     for (int i = 0; i < (SHORT ? 2 : 1); ++i)
 #pragma unroll
       for (int q = 0; q < 2; ++q) e[i][q] = *reinterpret_cast<const uint32_t *>(src_s + at + 4 * (64 * i + 32 * q));
-    v8h a[2], h[2], m[2], l[2]; // one half of the stage's rows at a time
+    v8b a[2], h[2], m[2], l[2]; // one half of the stage's rows at a time
     auto read = [&](int g) {
 #pragma unroll
-      for (int p = 0; p < 2; ++p) a[p] = *reinterpret_cast<const v8h *>(src_a + at + 2 * g * (DWS_TJ * 16) + 32 * 16 * p);
+      for (int p = 0; p < 2; ++p) a[p] = *reinterpret_cast<const v8b *>(src_a + at + 2 * g * (DWS_TJ * 16) + 32 * 16 * p);
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        h[q] = *reinterpret_cast<const v8h *>(src_b + at + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
-        m[q] = *reinterpret_cast<const v8h *>(src_b + at + DWS_LDS_B + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
-        l[q] = *reinterpret_cast<const v8h *>(src_b + at + 2 * DWS_LDS_B + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
+        h[q] = *reinterpret_cast<const v8b *>(src_b + at + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
+        m[q] = *reinterpret_cast<const v8b *>(src_b + at + DWS_LDS_B + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
+        l[q] = *reinterpret_cast<const v8b *>(src_b + at + 2 * DWS_LDS_B + 2 * g * (DWS_TN * 16) + 32 * 16 * q);
       }
     };
     auto multiply = [&](int q, bool fresh) {
 #pragma unroll
-      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p], l[q], fresh ? zero : sum[p][q], 0, 0, 0);
+      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], l[q], fresh ? zero : sum[p][q], 0, 0, 0);
 #pragma unroll
-      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p], m[q], sum[p][q], 0, 0, 0);
+      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], m[q], sum[p][q], 0, 0, 0);
 #pragma unroll
-      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p], h[q], sum[p][q], 0, 0, 0);
+      for (int p = 0; p < 2; ++p) sum[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], h[q], sum[p][q], 0, 0, 0);
     };
     auto add = [&](int q, int i) { // the sums of a part, scaled back, into the fp64 accumulators
       const uint32_t hi = ((1150u - (e[i][q] >> 23)) << 20) | ((uint32_t)(odd ^ (g0 - i)) << 31);

@@ -355,6 +355,38 @@ def test_weight_gradients_on_the_fp16_matrix_cores(hidden, n_in, B, T, masked, m
     assert np.array_equal(got["split"][1][1], got["mfma"][1][1]) == (hidden[1] == 3200)
 
 
+@pytest.mark.parametrize("B", [12, 32, 64])
+def test_weight_gradients_of_samples_far_apart(B, monkeypatch):
+    """Adjoints of one batch element that are 2^-24 and less of another's (well-classified samples beside wrong ones), and inputs that fire
+    in one sample each: a gradient is then the fp64 sum of single adjoints, the same bits whether the matrix cores take them in three
+    parts or the event-driven tiles as they are."""
+    w = synth.Workload("apart", 64, (1024, 1024), 10, T=3, B=B, p_in=0.9, gain=0.7, seed=B)
+    d = synth.generate(w)
+    d["in_spikes"] *= (np.arange(64)[None, None, :] % B == np.arange(B)[None, :, None]).astype(np.uint8)
+    d["W_in"][0] *= 8.0  # one to six inputs per sample
+    d["W_out"] *= 30.0
+    got = {}
+    for mode in ("split", "tile"):
+        if mode == "tile":
+            monkeypatch.setenv("SNN_DW", mode)
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_forward(d["in_spikes"], d["labels"], w.T)
+            ubar, _ = net.snn_get_readout()
+            labels = np.where(np.arange(B) % 2 == 0, ubar.argmax(1), ubar.argmin(1)).astype(np.int32)
+            net.snn_bind_inputs(d["in_spikes"], labels, w.T)
+            net.snn_bptt(snn.SNN_STANDARD)
+            got[mode] = _gpu_grads(net, 2)
+        finally:
+            net.snn_destroy()
+    a, b = got["split"][0][0], got["tile"][0][0]
+    largest = np.abs(b).max(1)
+    print(B, "rows", largest.min(), largest.max(), "differ", int((a != b).sum()))
+    assert 0.0 < largest[largest > 0].min() < 2.0 ** -24 * largest.max()
+    assert not np.array_equal(got["split"][1][1], got["tile"][1][1])  # the other kernel ran
+    assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("hidden,B,T", [((520, 300), 20, 12), ((1024,), 32, 10), ((640, 640, 640), 64, 9)])
 def test_chip_wide_adjoint_two_batch_groups_per_workgroup(hidden, B, T, monkeypatch):
     """Layers of 257..1024 neurons with an even number of 16-element batch groups: a workgroup of the chip-wide
