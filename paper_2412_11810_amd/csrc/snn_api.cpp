@@ -98,6 +98,7 @@ struct snn_ctx {
   uint4 *dw_split[SNN_MAXL + 1]{};
   float *dw_scale[SNN_MAXL + 1]{};
   uint8_t *dw_octets[2 * SNN_MAXL + 1]{};
+  unsigned *dw_special = nullptr; // [SNN_MAXL + 1]
   bool dw_tile = false;         // the event-driven tiled kernel instead of the dense contraction (batch <= 64; SNN_DW=tile|mfma)
   bool dw_rate_driven = false;  // ... chosen from the firing rates of the previous step (layers wider than 256, no SNN_DW)
   bool bwd_pipeline = true;     // SNN_BWD_PIPE=0: the adjoint pass finishes every layer of a chunk before the next chunk
@@ -597,6 +598,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
         at_scale[l] = take(octets * cols * sizeof(float));
       }
       for (int i = 0; i <= 2 * L; ++i) at_octets[i] = take(octets * 64 * n.Wd[i == 2 * L ? L : (i + 1) / 2]);
+      const size_t at_special = take((SNN_MAXL + 1) * sizeof(unsigned));
       if (hipMalloc(&c->dw_ws, sum) != hipSuccess) { // a device without the room: the kernels that need none
         (void)hipGetLastError();
         c->dw_ws = nullptr;
@@ -606,6 +608,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
         c->dw_scale[l] = reinterpret_cast<float *>(c->dw_ws + at_scale[l]);
       }
       for (int i = 0; c->dw_ws && i <= 2 * L; ++i) c->dw_octets[i] = c->dw_ws + at_octets[i];
+      if (c->dw_ws) c->dw_special = reinterpret_cast<unsigned *>(c->dw_ws + at_special);
     }
   }
   if (const char *e = std::getenv("SNN_DW")) {
@@ -1557,12 +1560,12 @@ struct BwdPipe {
     for (const BwdTile &t : done) {
       const int l = t.layer;
       if (l == L - 1)
-        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr, c->dw_split[L], c->dw_scale[L], c->dw_octets[2 * L]};
-      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr, c->dw_split[l], c->dw_scale[l], c->dw_octets[2 * l]};
+        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr, c->dw_split[L], c->dw_scale[L], c->dw_octets[2 * L], c->dw_special + L};
+      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr, c->dw_split[l], c->dw_scale[l], c->dw_octets[2 * l], c->dw_special + l};
       if (dw_rec_csr(c, l))
-        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_csr[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], n.csr_sub[l], n.csr_col[l], nullptr, nullptr, nullptr};
+        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_csr[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], n.csr_sub[l], n.csr_col[l], nullptr, nullptr, nullptr, nullptr};
       else
-        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr, dw_rec_split(c, l) ? c->dw_split[l] : nullptr, c->dw_scale[l], c->dw_octets[2 * l + 1]};
+        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr, dw_rec_split(c, l) ? c->dw_split[l] : nullptr, c->dw_scale[l], c->dw_octets[2 * l + 1], c->dw_special + l};
     }
   }
   snn_status emit_dw() {

@@ -231,6 +231,7 @@ struct DwDesc {
   uint4 *split;             // [steps][dw_split_octets][3][n_post]
   float *scale;             // [steps][parts][n_post]
   uint8_t *octets;          // [steps][dw_split_octets][64 pre_words]
+  unsigned *special;        // a word per layer: some of its adjoints are not finite
 };
 struct DwBatch {
   DwDesc d[2 * SNN_MAXL + 1];

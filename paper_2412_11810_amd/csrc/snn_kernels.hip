@@ -4175,6 +4175,8 @@ __device__ __forceinline__ void dw_mfma_body(const DwBatch &batch, int B, int vb
 //   k_dw_split_rows lays the adjoints out as the kernel reads them: of the part's values of a column, scaled by the power of two that
 // brings the largest to 2^100 ... 2^101 (at most by 2^127: so the low parts of values down to the smallest fp32 ones stay normal
 // numbers), eight batch elements' high parts in 16 bytes, then the middle and the low ones, zeros past the last.
+//   An adjoint that is infinite or not a number would meet the zeros of the silent neurons in a product.  It is left out of the split, its
+// layer's word `special` says that there are such values, and k_dw_split adds them to the rows of the neurons that fired.
 // SHORT: a batch of at most 16, a part is a step of 16 rows; else a step is `per` parts of 32.
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 typedef __bf16 v2b __attribute__((ext_vector_type(2)));
@@ -4190,7 +4192,7 @@ static __device__ __forceinline__ void split3_bf16(float x, float y, uint32_t &h
   m = round_bf16(x, y);
   l = round_bf16(x, y);
 }
-struct DwRows { const float *post; uint4 *split; float *scale; size_t slot_stride; int post_stride, cols, steps; };
+struct DwRows { const float *post; uint4 *split; float *scale; unsigned *special; size_t slot_stride; int post_stride, cols, steps; };
 struct DwRowsJobs { DwRows j[SNN_MAXL + 1]; };
 template <bool SHORT>
 __global__ void __launch_bounds__(256)
@@ -4203,8 +4205,15 @@ k_dw_split_rows(DwRowsJobs jobs, int B, int per) {
   float x[R], mx = 0.0f;
 #pragma unroll
   for (int b = 0; b < R; ++b) x[b] = b0 + b < B ? p[(size_t)b * jb.post_stride] : 0.0f;
+  bool special = false;
 #pragma unroll
-  for (int b = 0; b < R; ++b) mx = fmaxf(mx, fabsf(x[b]));
+  for (int b = 0; b < R; ++b) {
+    const bool finite = fabsf(x[b]) < __builtin_inff();
+    special = special || !finite;
+    x[b] = finite ? x[b] : 0.0f;
+    mx = fmaxf(mx, fabsf(x[b]));
+  }
+  if (special) *jb.special = 1u;
   const uint32_t e = __float_as_uint(mx) >> 23;
   const float sc = __uint_as_float((e < 100u ? 254u : 354u - e) << 23);
   jb.scale[(size_t)part * jb.cols + n] = sc;
@@ -4223,13 +4232,14 @@ k_dw_split_rows(DwRowsJobs jobs, int B, int per) {
 }
 //   k_dw_octets does the same with the spikes: a byte per presynaptic neuron and eight batch elements, step t0 + 1 + i of a matrix's
 // adjoints with the spikes of t0 + 1 + i - lag.  (As words in scalar registers they had to be waited for with every LDS read.)
-struct DwOctets { const uint64_t *mask; uint8_t *oct; int words, lag, t0, steps, ring; };
+struct DwOctets { const uint64_t *mask; uint8_t *oct; unsigned *special; int words, lag, t0, steps, ring; };
 struct DwOctetsJobs { DwOctets j[2 * SNN_MAXL + 1]; };
 __global__ void __launch_bounds__(256)
 k_dw_octets(DwOctetsJobs jobs, int B, int no) { // no: octets per step
   const DwOctets &jb = jobs.j[blockIdx.z];
   const int wave = uniform((int)threadIdx.x >> 6), lane = lane_id(), ts = (int)blockIdx.y;
   const int at = (int)blockIdx.x * 4 + wave, o = at % no, w = at / no; // an octet of 64 neurons per wavefront
+  if (blockIdx.x + blockIdx.y + threadIdx.x == 0) *jb.special = 0u; // (of the same layer's other matrix as well; k_dw_split_rows follows)
   if (w >= jb.words || ts >= jb.steps) return;
   const int t = jb.t0 + 1 + ts - jb.lag;
   const __attribute__((address_space(4))) uint64_t *const m = (const __attribute__((address_space(4))) uint64_t *)jb.mask +
@@ -4257,7 +4267,7 @@ k_dw_octets(DwOctetsJobs jobs, int B, int no) { // no: octets per step
 #define DWS_LDS_STAGE (DWS_LDS_A + 3 * DWS_LDS_B + 2 * DWS_TN * 4)
 template <bool SHORT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_dw_split(DwBatch batch, int per) {
+k_dw_split(DwBatch batch, int B, int per) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int total = (int)gridDim.x, die = (int)blockIdx.x & 7, rest = total & 7; // a die gets tiles that share columns
   int tile = die * (total >> 3) + min(die, rest) + (int)(blockIdx.x >> 3), di = 0;
@@ -4407,6 +4417,33 @@ k_dw_split(DwBatch batch, int per) {
         if (j < n_pre && n < n_post) out[(size_t)j * n_post + n] = acc[p][q][r];
       }
     }
+  if (*d.special == 0u) return;
+  // ---- adjoints that are not finite: 64 rows (a spike word) to a wavefront, a column to a lane; a row gets an infinity or, from both
+  // or from what is not a number, NaN
+  __syncthreads(); // (the tile is written)
+  const int w = j0 / 64 + wave;
+  int n; // (computed here, not kept in a register since the loads)
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0\n\tv_add_u32 %0, %0, %1" : "=&v"(n) : "s"(n0));
+  if (w >= d.pre_words) return;
+  const float *const post = d.post + d.post_off + min(n, n_post - 1);
+  uint64_t up = 0ull, down = 0ull;
+  for (int t = d.t0 + 1; t <= d.t1; ++t) {
+    const uint64_t *const m = d.pre_mask + (size_t)(d.pre_ring > 0 ? (t - d.lag) % d.pre_ring : t - d.lag) * B * d.pre_words + w;
+    for (int b = 0; b < B; ++b) {
+      const float x = post[(size_t)(t - d.t_base - 1) * d.slot_stride + (size_t)b * d.post_stride];
+      if (fabsf(x) < __builtin_inff()) continue;
+      const uint64_t fired = m[(size_t)b * d.pre_words];
+      if (!(x < 0.0f)) up |= fired;
+      if (!(x > 0.0f)) down |= fired;
+    }
+  }
+  if (n >= n_post) return;
+  for (int r = 0; r < 64 && 64 * w + r < n_pre; ++r) {
+    if (((up | down) >> r & 1u) == 0u) continue;
+    double *const at = out + (size_t)(64 * w + r) * n_post + n;
+    if (up >> r & 1u) *at += __builtin_inf();
+    if (down >> r & 1u) *at -= __builtin_inf();
+  }
 }
 
 template <int NT, int CW>
@@ -6614,18 +6651,18 @@ static hipError_t launch_dw_split(DwBatch *all, int B, hipStream_t s) {
   int n_rows = 0, cols = 0, steps = 0, total = 0, words = 0;
   for (int i = 0; i < batch.count; ++i) {
     DwDesc &d = batch.d[i];
-    if (d.t1 <= d.t0 || d.t1 - d.t0 > SNN_BWD_TILE || !d.scale || !d.octets || !d.split) return hipErrorInvalidValue;
+    if (d.t1 <= d.t0 || d.t1 - d.t0 > SNN_BWD_TILE || !d.scale || !d.octets || !d.split || !d.special) return hipErrorInvalidValue;
     d.tiles_n = (d.n_post + DWS_TN - 1) / DWS_TN;
     d.tile0 = total;
     total += ((d.n_pre + DWS_TJ - 1) / DWS_TJ) * d.tiles_n;
-    octs.j[i] = DwOctets{d.pre_mask, d.octets, d.pre_words, d.lag, d.t0, d.t1 - d.t0, d.pre_ring};
+    octs.j[i] = DwOctets{d.pre_mask, d.octets, d.special, d.pre_words, d.lag, d.t0, d.t1 - d.t0, d.pre_ring};
     words = std::max(words, d.pre_words);
     steps = std::max(steps, d.t1 - d.t0);
     bool seen = false; // the matrices of a layer share their adjoints
     for (int k = 0; k < n_rows; ++k) seen = seen || rows.j[k].scale == d.scale;
     if (seen) continue;
     if (n_rows > SNN_MAXL) return hipErrorInvalidValue;
-    rows.j[n_rows++] = DwRows{d.post + (size_t)(d.t0 - d.t_base) * d.slot_stride + d.post_off, d.split, d.scale, d.slot_stride, d.post_stride,
+    rows.j[n_rows++] = DwRows{d.post + (size_t)(d.t0 - d.t_base) * d.slot_stride + d.post_off, d.split, d.scale, d.special, d.slot_stride, d.post_stride,
                               d.n_post, d.t1 - d.t0};
     cols = std::max(cols, d.n_post);
   }
@@ -6634,7 +6671,7 @@ static hipError_t launch_dw_split(DwBatch *all, int B, hipStream_t s) {
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_dw_octets, dim3((words * no + 3) / 4, steps, batch.count), dim3(256), 0, s, octs, B, no);
     hipLaunchKernelGGL(rows_kern, dim3((cols + 255) / 256, steps * per, n_rows), dim3(256), 0, s, rows, B, per);
-    hipLaunchKernelGGL(kern, dim3(total), dim3(256), 2 * DWS_LDS_STAGE, s, batch, per);
+    hipLaunchKernelGGL(kern, dim3(total), dim3(256), 2 * DWS_LDS_STAGE, s, batch, B, per);
     return hipGetLastError();
   };
   return B <= 16 ? go(k_dw_split_rows<true>, k_dw_split<true>) : go(k_dw_split_rows<false>, k_dw_split<false>);

@@ -387,6 +387,54 @@ def test_weight_gradients_of_samples_far_apart(B, monkeypatch):
     assert np.array_equal(a, b)
 
 
+def _same_values(got, want, rel):
+    """Infinities and NaN in the same places, the other values within `rel` in the 2-norm."""
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), fin) and np.array_equal(got[~fin], want[~fin], equal_nan=True)
+    g, x = got[fin].astype(np.float64), want[fin].astype(np.float64)
+    assert np.linalg.norm(g - x) <= rel * np.linalg.norm(x)
+
+
+def _with_an_infinite_adjoint(d, layer=-1):
+    """An infinite weight to readout 0 of a top neuron that never fires: finite logits, an infinite adjoint at that neuron."""
+    j = 7
+    d["W_in"][layer][:, j] = -np.abs(d["W_in"][layer][:, j]) - np.float32(1e-3)
+    d["W_rec"][layer][:, j] = -np.abs(d["W_rec"][layer][:, j]) - np.float32(1e-3)
+    d["W_out"][j, 0] = np.inf
+    return j
+
+
+@pytest.mark.parametrize("n_in,N,B,T", [(1000, 1990, 12, 3), (1025, 2048, 20, 3), (900, 2048, 40, 4)])
+def test_weight_gradients_of_infinite_adjoints(n_in, N, B, T, monkeypatch):
+    """At the last step the adjoint of one neuron is infinite, at the steps before it those of all neurons are: the gradients of the
+    event-driven tiles, infinite where a presynaptic neuron fired, NaN where both signs meet, as they were where none did."""
+    w = synth.Workload("inf", n_in, (N,), 10, T=T, B=B, p_in=0.03, gain=0.8, seed=B)
+    d = synth.generate(w)
+    j = _with_an_infinite_adjoint(d)
+    d["in_spikes"][:, :, 3] = 0  # an input that is silent, and one that fires at the last step only
+    d["in_spikes"][:, :, 5] = 0
+    d["in_spikes"][T - 1, 4, 5] = 1
+    got = {}
+    for mode in ("split", "tile"):
+        if mode == "tile":
+            monkeypatch.setenv("SNN_DW", mode)
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], T)
+            net.snn_bptt(snn.SNN_STANDARD)
+            got[mode] = _gpu_grads(net, 1)
+            net.snn_bptt(snn.SNN_CHUNK, 0, 1)
+            again = _gpu_grads(net, 1)
+            assert all(np.array_equal(x, y, equal_nan=True) for x, y in zip((again[0][0], again[1][0]), (got[mode][0][0], got[mode][1][0])))
+        finally:
+            net.snn_destroy()
+    a, b = got["split"], got["tile"]
+    assert not a[0][0][3].any() and np.array_equal(~np.isfinite(a[0][0][5]), np.arange(N) == j)
+    assert np.isinf(b[0][0]).any() and np.isnan(b[0][0]).any() and not np.isfinite(b[1][0]).all()
+    _same_values(a[0][0], b[0][0], 2.0 ** -21)
+    _same_values(a[1][0], b[1][0], 2.0 ** -21)
+
+
 @pytest.mark.parametrize("hidden,B,T", [((520, 300), 20, 12), ((1024,), 32, 10), ((640, 640, 640), 64, 9)])
 def test_chip_wide_adjoint_two_batch_groups_per_workgroup(hidden, B, T, monkeypatch):
     """Layers of 257..1024 neurons with an even number of 16-element batch groups: a workgroup of the chip-wide
