@@ -25,7 +25,7 @@ struct NetDev {
   int Wd[SNN_MAXL + 1];   // 64-bit words per (t, b) of layer index 0..L (0 = input)
   const float *W_in[SNN_MAXL], *W_rec[SNN_MAXL], *W_out;
   const float *W_recT[SNN_MAXL];
-  // W_in of layer l >= 1, every row scaled by a power of two (W_scale) and split into two fp16 values (see k_up_split); NULL: the
+  // W_in of layer l >= 1, every row scaled by a power of two (W_scale) and split into three bf16 values (see k_up_split); NULL: the
   // products with it go through the fp32 matrix cores.  row_scale: the same scales for the rows of the other operand.
   uint4 *W_split[SNN_MAXL];
   float *W_scale[SNN_MAXL], *row_scale;

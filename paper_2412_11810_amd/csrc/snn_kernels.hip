@@ -2287,37 +2287,43 @@ k_up_gemm(const float *__restrict__ A, int lda, const float *__restrict__ W, int
           int ldc, int M) {
   up_gemm_body<WM, WN>(A, lda, W, K, N, C, ldc, M, (int)blockIdx.x, (int)blockIdx.y);
 }
-// The same product for large matrices (1024 x 1024 and more) on the fp16 matrix cores.  An fp32 value is the sum of two fp16 ones to
-// within 2^-24 of itself, h = fp16(x) and l = fp16(x - h), as long as neither leaves fp16's range: every row of both operands is
-// scaled by the power of two that brings its largest magnitude to 2^14 ... 2^15 (and the result scaled back exactly), so an
-// element 2^-16 below its row's largest still has all its bits and a smaller one is off by 2^-40 of that largest.  Then
-// a . b = h.h + h.l + l.h with exact products and fp32 sums (l.l is below 2^-24 of h.h).  Three products at sixteen times the
-// fp32 matrix rate, and fewer roundings per element: 16 terms meet in one instruction.  Against 64 bits, 2-norm: 9.9e-7 at K =
-// 8192 (the fp32 matrix cores: 1.6e-6), 5.0e-7 at 2048 (8.1e-7), also for rows that span thirteen decades or sit near the smallest
-// fp32 values.
-// The matrix cores cut the terms they align below an accumulator towards minus infinity: 2.5e-7 of the mean magnitude at K =
-// 8192, always the same way, which sums over thousands of time steps would see.  Every eighth tile of K turns the sign of A and of
-// the accumulators, and what is cut off changes sides: 5e-9.
-//   W comes split (k_split_rows, once per step: 16 bytes hold h and l of four elements, rows padded with zeros to whole tiles of 32),
-//   A is split while it is staged.  The last tile of K comes first: it alone may be ragged, so the loop is straight-line code.
-//   A tile of K costs 3 BM BN matrix instructions per 16 k and wavefront; the share of the next tile's staging (vector work, LDS writes,
+// The same product for large matrices (1024 x 1024 and more) on the 16-bit matrix cores.  An fp32 value is the sum of three bf16 ones,
+// h, m and l, exactly (8 bits each, and the exponents of fp32).  a . b = m.m + l.h + h.l + m.h + h.m + h.h with exact products and
+// fp32 sums: what is left out is 2^-26 of a product at most, a quarter of what rounding it to fp32 loses, whatever its size beside the others.
+// Every row of both operands is scaled by the power of two that brings its largest magnitude to 2^50 ... 2^51 (at most by 2^127; the result
+// scaled back exactly): values near the smallest fp32 ones stay clear of the end of the range.
+// Against 64 bits, 2-norm: 1.4e-6 at K = 8192 (the fp32 matrix cores: 1.6e-6), 6.8e-7 at 2048 (8.0e-7), 4.9e-7 at 1024 (5.7e-7); of single
+// values, 1.7e-7 of the sum of the terms' magnitudes at most (2.0e-7), also where the elements of a row span six decades.
+// The matrix cores cut the terms they align below an accumulator towards minus infinity, always the same way, which sums over
+// thousands of time steps would see.  Every 256 k turn the sign of A and of the accumulators, and what is cut off changes sides.
+//   W comes split (k_split_rows, once per step: by slabs of 16 k, of a row 32 bytes each of h, m and l, so that the rows of a tile lie one
+//   after the other; padded with zeros to whole blocks of 32), A is split while it is staged.  The last block of 32 comes first: it alone may be
+//   ragged, so the loop is straight-line code.
+//   A slab costs 6 BM BN matrix instructions per wavefront; the share of the next tile's staging (vector work, LDS writes,
 //   the loads of the tile after it) sits between them, group by group: left to the scheduler it ended up behind them, one after
-//   the other (761 -> 706 us at M = 2048, N = K = 8192).  That product took 2180 us in fp32, 126 TFLOP/s; 390 now, 1.17 PFLOP/s of
-//   fp16, where a plain bf16 product of the vendor's library reaches 1.3 here.
+//   the other.  M = 2048, N = K = 8192, the scales of A included: 1300 us (the fp32 matrix cores in tiles as large 2180), 1.27 PFLOP/s of
+//   bf16, where a plain bf16 product of the vendor's library reaches 1.3 here; 800, 2048: 69 (114); 320, 1024: 33 (35).
 //   Lane layout (checked on the device): A[i][k] in lane i + 32 (k / 8), element k % 8; result as v_mfma_f32_32x32x2.
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-static __device__ __forceinline__ void split_fp16(float x, float y, uint32_t &h, uint32_t &l) {
-  const v2h hv = {(_Float16)x, (_Float16)y};
-  const v2h lv = {(_Float16)__builtin_fmaf((float)hv[0], -1.0f, x), (_Float16)__builtin_fmaf((float)hv[1], -1.0f, y)};
-  h = __builtin_bit_cast(uint32_t, hv);
-  l = __builtin_bit_cast(uint32_t, lv);
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+static __device__ __forceinline__ uint32_t round_bf16(float &x, float &y) { // both in 16 bits, what is left of them in 32 (exactly)
+  const v2b v = {(__bf16)x, (__bf16)y};
+  const uint32_t h = __builtin_bit_cast(uint32_t, v);
+  x = x - __uint_as_float(h << 16);
+  y = y - __uint_as_float(h & 0xffff0000u);
+  return h;
 }
-// Scale of a row whose largest magnitude is mx: the power of two that brings it to 2^14 ... 2^15 (a row below 2^-112: 2^127).
+static __device__ __forceinline__ void split3_bf16(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) {
+  h = round_bf16(x, y);
+  m = round_bf16(x, y);
+  l = round_bf16(x, y);
+}
+// Scale of a row whose largest magnitude is mx: the power of two that brings it to 2^50 ... 2^51 (a row below 2^-76: 2^127).
 static __device__ __forceinline__ float row_scale(float mx) {
   const uint32_t e = __float_as_uint(mx) >> 23;
-  return __uint_as_float((e < 14u ? 254u : 268u - e) << 23);
+  return __uint_as_float((e < 50u ? 254u : 304u - e) << 23);
 }
 static __device__ __forceinline__ float row_max(const float *__restrict__ r, int K, int lane) { // over a wavefront
   float mx = 0.0f;
@@ -2343,30 +2349,35 @@ k_row_scales(SplitJobs jobs) {
 }
 __global__ void __launch_bounds__(256) // a wavefront per row; the second look at the row comes from the caches
 k_split_rows(const float *__restrict__ W, int K, int N, uint4 *__restrict__ WS, float *__restrict__ scale) {
-  const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = lane_id(), K4 = (K + 31) / 32 * 8;
+  const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = lane_id(), K8 = (K + 31) / 32 * 4;
   if (j >= N) return;
   const float *r = W + (size_t)j * K;
   const float sc = row_scale(row_max(r, K, lane));
   if (lane == 0) scale[j] = sc;
-  for (int q = lane; q < K4; q += 64) {
-    float x[4];
+  for (int q = lane; q < K8; q += 64) { // half a slab
+    float x[8];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = 4 * q + e < K ? r[4 * q + e] * sc : 0.0f;
-    uint4 v;
-    split_fp16(x[0], x[1], v.x, v.z);
-    split_fp16(x[2], x[3], v.y, v.w);
-    WS[(size_t)j * K4 + q] = v;
+    for (int e = 0; e < 8; ++e) x[e] = 8 * q + e < K ? r[8 * q + e] * sc : 0.0f;
+    uint4 h, m, l;
+    split3_bf16(x[0], x[1], h.x, m.x, l.x);
+    split3_bf16(x[2], x[3], h.y, m.y, l.y);
+    split3_bf16(x[4], x[5], h.z, m.z, l.z);
+    split3_bf16(x[6], x[7], h.w, m.w, l.w);
+    uint4 *const d = WS + ((size_t)(q >> 1) * N + j) * (UPS_SLAB_BYTES / 16) + (q & 1);
+    d[0] = h;
+    d[2] = m;
+    d[4] = l;
   }
 }
-#define UPS_KT 32                      // K per tile
-#define UPS_ROW_BYTES (4 * UPS_KT + 16) // a row of a tile in LDS: h, l; 16 bytes more make its 16-byte reads free of bank conflicts
-#define UPS_FLIP 8                     // K tiles between two turns of the sign
-template <int WM, int WN, int BM, int BN, int WPE> // wavefronts and their blocks of 32 x 32; wavefronts per SIMD
+// KS: slabs per tile of K; a row of a tile in LDS has 16 bytes more, which make its 16-byte reads free of bank conflicts
+constexpr int ups_row_bytes(int KS) { return KS * UPS_SLAB_BYTES + 16; }
+template <int WM, int WN, int BM, int BN, int WPE, int KS> // wavefronts and their blocks of 32 x 32; wavefronts per SIMD
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 k_up_split(SplitJobs jobs) {
-  constexpr int NT = 64 * WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN, TPR = UPS_KT / 4, RPP = NT / TPR; // threads per row, rows per pass
-  constexpr int LA = TM / RPP, LW = TN / RPP, LD = LA + LW, NG = UPS_KT / 16 * BM, RB = UPS_ROW_BYTES, BUF = (TM + TN) * RB;
-  static_assert(TM % RPP == 0 && TN % RPP == 0, "whole passes");
+  constexpr int NT = 64 * WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN, TPR = 4 * KS, RPP = NT / TPR; // threads per row of A, rows per pass
+  constexpr int WCH = UPS_SLAB_BYTES / 16, LA = TM / RPP, LW = TN * WCH * KS / NT, LD = LA + LW, NG = KS * BM;
+  constexpr int RB = ups_row_bytes(KS), BUF = (TM + TN) * RB, HEAD = 2 / KS, FLIP = 8 * HEAD; // steps of the last block; between two turns of the sign
+  static_assert(TM % RPP == 0 && TN * WCH * KS % NT == 0, "whole passes");
   extern __shared__ __align__(16) unsigned char smem[]; // [2][TM + TN][RB]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave % WM, wn = wave / WM;
   // a die (workgroup number modulo 8) gets neighbouring tiles, rows fastest: its L2 holds their columns of W for all of them
@@ -2387,10 +2398,11 @@ k_up_split(SplitJobs jobs) {
     for (int q = 0; q < BN; ++q)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[p][q][r] = 0.0f;
-  const int row0 = tid / TPR, c4 = tid % TPR, nk = (K + UPS_KT - 1) / UPS_KT;
+  const int row0 = tid / TPR, c4 = tid % TPR, nk = (K + 31) / 32 * HEAD; // steps
   const float *srcA[LA];
   float sc[LA];
-  const uint4 *srcW[LW];
+  uint32_t srcW[LW]; // bytes from the start of the tile's first slab
+  int dstW[LW];
 #pragma unroll
   for (int i = 0; i < LA; ++i) { // rows past the last one: loaded again, not stored
     const int m = min(m0 + row0 + i * RPP, M - 1);
@@ -2398,70 +2410,74 @@ k_up_split(SplitJobs jobs) {
     sc[i] = sa[m];
   }
 #pragma unroll
-  for (int i = 0; i < LW; ++i) srcW[i] = WS + (size_t)min(j0 + row0 + i * RPP, N - 1) * (nk * (UPS_KT / 4)) + c4;
-  unsigned char *const dst = smem + row0 * RB + 8 * c4;
+  for (int i = 0; i < LW; ++i) {
+    const int id = tid + i * NT, slab = id / (TN * WCH), row = id % (TN * WCH) / WCH, part = id % WCH;
+    srcW[i] = ((uint32_t)(slab * N + min(j0 + row, N - 1)) * WCH + part) * 16u;
+    dstW[i] = (TM + row) * RB + slab * UPS_SLAB_BYTES + 16 * part;
+  }
+  const size_t stepW = (size_t)N * WCH * KS;
+  unsigned char *const dst = smem + row0 * RB + c4 / 4 * UPS_SLAB_BYTES + 8 * (c4 % 4);
   f32x4u ra[LA];
-  uint4 rw[LW];
-  auto load = [&](int i, int step) { // the tiles in the order nk - 1, 0, 1, ... nk - 2
-    const int kt = min(step, nk - 1) - 1;
-    if (i < LA) ra[i < LA ? i : 0] = *reinterpret_cast<const f32x4u *>(srcA[i < LA ? i : 0] + kt * UPS_KT);
-    else rw[i < LA ? 0 : i - LA] = srcW[i < LA ? 0 : i - LA][kt * (UPS_KT / 4)];
-  };
-  auto put = [&](int i, int buf) {
-    uint2 h, l;
-    if (i < LA) {
-      const int k = i < LA ? i : 0;
-      split_fp16(ra[k][0] * sc[k], ra[k][1] * sc[k], h.x, l.x);
-      split_fp16(ra[k][2] * sc[k], ra[k][3] * sc[k], h.y, l.y);
-    } else {
-      const uint4 v = rw[i < LA ? 0 : i - LA];
-      h = make_uint2(v.x, v.y);
-      l = make_uint2(v.z, v.w);
-    }
-    unsigned char *d = dst + buf * BUF + i * RPP * RB;
-    *reinterpret_cast<uint2 *>(d) = h;
-    *reinterpret_cast<uint2 *>(d + 2 * UPS_KT) = l;
-  };
-  { // the last tile of K
-    const int k0 = (nk - 1) * UPS_KT;
+  u32x4 rw[LW];
+  auto load_w = [&](int i, int kt) { rw[i] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const unsigned char *>(WS + kt * stepW) + srcW[i]); };
+  auto load_a = [&](int i, int kt) { ra[i] = *reinterpret_cast<const f32x4u *>(srcA[i] + kt * (16 * KS)); };
+  auto tile_of = [&](int step) { return min(step, nk - 1) - HEAD; }; // the tiles in the order nk - HEAD ... nk - 1, 0, 1, ...
+  auto load_last = [&](int step) { // of the last block: the first HEAD steps
+    const int kt = nk - HEAD + step;
 #pragma unroll
     for (int i = 0; i < LA; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ra[i][e] = k0 + 4 * c4 + e < K ? srcA[i][k0 + e] : 0.0f;
+      for (int e = 0; e < 4; ++e) ra[i][e] = kt * (16 * KS) + 4 * c4 + e < K ? srcA[i][kt * (16 * KS) + e] : 0.0f;
 #pragma unroll
-    for (int i = 0; i < LW; ++i) rw[i] = srcW[i][(nk - 1) * (UPS_KT / 4)];
-  }
+    for (int i = 0; i < LW; ++i) load_w(i, kt);
+  };
+  auto put_a = [&](int i, int buf) {
+    uint2 h, m, l;
+    split3_bf16(ra[i][0] * sc[i], ra[i][1] * sc[i], h.x, m.x, l.x);
+    split3_bf16(ra[i][2] * sc[i], ra[i][3] * sc[i], h.y, m.y, l.y);
+    unsigned char *d = dst + buf * BUF + i * RPP * RB;
+    *reinterpret_cast<uint2 *>(d) = h;
+    *reinterpret_cast<uint2 *>(d + 32) = m;
+    *reinterpret_cast<uint2 *>(d + 64) = l;
+  };
+  auto put_w = [&](int i, int buf) { *reinterpret_cast<u32x4 *>(smem + buf * BUF + dstW[i]) = rw[i]; };
+  load_last(0);
 #pragma unroll
-  for (int i = 0; i < LD; ++i) put(i, 0);
-  if (nk > 1) {
+  for (int i = 0; i < LA; ++i) put_a(i, 0);
 #pragma unroll
-    for (int i = 0; i < LD; ++i) load(i, 1);
+  for (int i = 0; i < LW; ++i) put_w(i, 0);
+  if constexpr (HEAD == 2) load_last(1);
+  else {
+#pragma unroll
+    for (int i = 0; i < LA; ++i) load_a(i, 0);
+#pragma unroll
+    for (int i = 0; i < LW; ++i) load_w(i, 0);
   }
   __syncthreads();
   const unsigned char *const pa = smem + (wm * BM * 32 + (lane & 31)) * RB + 16 * (lane >> 5);
   const unsigned char *const pb = smem + (TM + wn * BN * 32 + (lane & 31)) * RB + 16 * (lane >> 5);
   for (int step = 0; step < nk; ++step) {
     const int cur = step & 1;
-    if (step > 0 && step % UPS_FLIP == 0) {
+    if (step > 0 && step % FLIP == 0) {
 #pragma unroll
       for (int p = 0; p < BM; ++p)
 #pragma unroll
         for (int q = 0; q < BN; ++q) acc[p][q] = -acc[p][q];
     }
-    if ((step + 1) % UPS_FLIP == 0) { // the tile staged now is multiplied after the turn
+    if ((step + 1) % FLIP == 0) { // the tile staged now is multiplied after the turn
 #pragma unroll
       for (int i = 0; i < LA; ++i) sc[i] = -sc[i];
     }
-    v8h a[2][2], b[BN][2], bn[BN][2]; // h and l
+    v8b a[2][3], b[BN][3], bn[KS > 1 ? BN : 1][3]; // h, m and l
     auto read_a = [&](int g) {
 #pragma unroll
-      for (int z = 0; z < 2; ++z) a[g & 1][z] = *reinterpret_cast<const v8h *>(pa + cur * BUF + g % BM * 32 * RB + 2 * UPS_KT * z + 32 * (g / BM));
+      for (int z = 0; z < 3; ++z) a[g & 1][z] = *reinterpret_cast<const v8b *>(pa + cur * BUF + g % BM * 32 * RB + 32 * z + UPS_SLAB_BYTES * (g / BM));
     };
-    auto read_b = [&](int ks, v8h (&dstb)[BN][2]) {
+    auto read_b = [&](int ks, v8b (*dstb)[3]) {
 #pragma unroll
       for (int q = 0; q < BN; ++q)
 #pragma unroll
-        for (int z = 0; z < 2; ++z) dstb[q][z] = *reinterpret_cast<const v8h *>(pb + cur * BUF + q * 32 * RB + 2 * UPS_KT * z + 32 * ks);
+        for (int z = 0; z < 3; ++z) dstb[q][z] = *reinterpret_cast<const v8b *>(pb + cur * BUF + q * 32 * RB + 32 * z + UPS_SLAB_BYTES * ks);
     };
     read_b(0, b);
     read_a(0);
@@ -2472,34 +2488,41 @@ k_up_split(SplitJobs jobs) {
       const bool turn = p == BM - 1 && g + 1 < NG;
       if (g + 1 < NG) read_a(g + 1);
       if (turn) read_b(g / BM + 1, bn);
-      v8h(&x)[2] = a[g & 1];
+      v8b(&x)[3] = a[g & 1];
 #pragma unroll
-      for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], b[q][0], acc[p][q], 0, 0, 0);
+      for (int z = 0; z < 6; ++z) { // m.m, l.h, h.l, m.h, h.m, h.h
+        constexpr int ZA[6] = {1, 2, 0, 1, 0, 0}, ZB[6] = {1, 0, 2, 0, 1, 0};
 #pragma unroll
-      for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], b[q][1], acc[p][q], 0, 0, 0);
-#pragma unroll
-      for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], b[q][0], acc[p][q], 0, 0, 0);
-      if (nk > 1) {
-#pragma unroll
-        for (int i = g * LD / NG; i < (g + 1) * LD / NG; ++i) { // (past the last tile: the one before it once more, never read)
-          put(i, cur ^ 1);
-          load(i, step + 2);
-        }
+        for (int q = 0; q < BN; ++q) acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ZA[z]], b[q][ZB[z]], acc[p][q], 0, 0, 0);
       }
+#pragma unroll
+      for (int i = 0; i < LA; ++i) // (past the last tile: the one before it once more, never read)
+        if (i * NG / LD == g) {
+          put_a(i, cur ^ 1);
+          load_a(i, tile_of(step + 2));
+        }
+#pragma unroll
+      for (int i = 0; i < LW; ++i)
+        if ((LA + i) * NG / LD == g) {
+          put_w(i, cur ^ 1);
+          load_w(i, tile_of(step + 2));
+        }
       if (turn) {
 #pragma unroll
-        for (int q = 0; q < BN; ++q) { b[q][0] = bn[q][0]; b[q][1] = bn[q][1]; }
+        for (int q = 0; q < BN; ++q)
+#pragma unroll
+          for (int z = 0; z < 3; ++z) b[q][z] = bn[KS > 1 ? q : 0][z];
       }
 #pragma unroll
-      for (int z = 0; z < 3 * BN; ++z) { // one matrix instruction, then a share of the vector work
+      for (int z = 0; z < 6 * BN; ++z) { // one matrix instruction, then a share of the vector work
         __builtin_amdgcn_sched_group_barrier(8, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(2, (20 * LD / NG + 3 * BN - 1) / (3 * BN) + 1, 0);
+        __builtin_amdgcn_sched_group_barrier(2, (30 * LA / NG + 6 * BN - 1) / (6 * BN) + 1, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
   }
-  const uint32_t sign = (nk - 1) / UPS_FLIP % 2 ? 0x80000000u : 0u;
+  const uint32_t sign = (nk - 1) / FLIP % 2 ? 0x80000000u : 0u;
 #pragma unroll
   for (int p = 0; p < BM; ++p)
 #pragma unroll
@@ -4173,25 +4196,10 @@ __device__ __forceinline__ void dw_mfma_body(const DwBatch &batch, int B, int vb
 // with spikes of -1 (what the matrix cores cut off below an accumulator, always towards minus infinity, changes sides and does not
 // add up over the steps).  Number and scale of a part do not depend on how the time axis is cut: the same bits for every strategy.
 //   k_dw_split_rows lays the adjoints out as the kernel reads them: of the part's values of a column, scaled by the power of two that
-// brings the largest to 2^100 ... 2^101 (at most by 2^127: so the low parts of values down to the smallest fp32 ones stay normal
-// numbers), eight batch elements' high parts in 16 bytes, then the middle and the low ones, zeros past the last.
+// brings the largest to 2^50 ... 2^51 (so the low parts of values down to the smallest fp32 ones stay normal numbers), eight batch elements' high parts in 16 bytes, then the middle and the low ones, zeros past the last.
 //   An adjoint that is infinite or not a number would meet the zeros of the silent neurons in a product.  It is left out of the split, its
 // layer's word `special` says that there are such values, and k_dw_split adds them to the rows of the neurons that fired.
 // SHORT: a batch of at most 16, a part is a step of 16 rows; else a step is `per` parts of 32.
-typedef __bf16 v8b __attribute__((ext_vector_type(8)));
-typedef __bf16 v2b __attribute__((ext_vector_type(2)));
-static __device__ __forceinline__ uint32_t round_bf16(float &x, float &y) { // both in 16 bits, what is left of them in 32 (exactly)
-  const v2b v = {(__bf16)x, (__bf16)y};
-  const uint32_t h = __builtin_bit_cast(uint32_t, v);
-  x = x - __uint_as_float(h << 16);
-  y = y - __uint_as_float(h & 0xffff0000u);
-  return h;
-}
-static __device__ __forceinline__ void split3_bf16(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) {
-  h = round_bf16(x, y);
-  m = round_bf16(x, y);
-  l = round_bf16(x, y);
-}
 struct DwRows { const float *post; uint4 *split; float *scale; unsigned *special; size_t slot_stride; int post_stride, cols, steps; };
 struct DwRowsJobs { DwRows j[SNN_MAXL + 1]; };
 template <bool SHORT>
@@ -4214,8 +4222,7 @@ k_dw_split_rows(DwRowsJobs jobs, int B, int per) {
     mx = fmaxf(mx, fabsf(x[b]));
   }
   if (special) *jb.special = 1u;
-  const uint32_t e = __float_as_uint(mx) >> 23;
-  const float sc = __uint_as_float((e < 100u ? 254u : 354u - e) << 23);
+  const float sc = row_scale(mx);
   jb.scale[(size_t)part * jb.cols + n] = sc;
 #pragma unroll
   for (int o = 0; o < R / 8; ++o) {
@@ -6125,11 +6132,11 @@ static void add_split_job(const NetDev &net, SplitJobs *jobs, int l, const float
   jobs->j[jobs->count++] = SplitJob{A, net.row_scale + (size_t)l * SNN_BWD_TILE * net.B, net.W_split[l], net.W_scale[l], C, lda, net.N[l],
                                     net.N[l - 1], M, 0};
 }
-template <int WM, int WN, int BM, int BN, int WPE>
+template <int WM, int WN, int BM, int BN, int WPE, int KS>
 static hipError_t launch_up_split_t(SplitJobs jobs, hipStream_t s) {
   constexpr int TM = 32 * WM * BM, TN = 32 * WN * BN;
-  constexpr size_t lds = (size_t)2 * (TM + TN) * UPS_ROW_BYTES;
-  const auto kern = k_up_split<WM, WN, BM, BN, WPE>;
+  constexpr size_t lds = (size_t)2 * (TM + TN) * ups_row_bytes(KS);
+  const auto kern = k_up_split<WM, WN, BM, BN, WPE, KS>;
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int total = 0;
@@ -6140,14 +6147,14 @@ static hipError_t launch_up_split_t(SplitJobs jobs, hipStream_t s) {
   hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WM * WN), lds, s, jobs);
   return hipGetLastError();
 }
-// Tiles as large as still give most compute units one (every tile adds in the same order): M = 2048,
-// N = K = 8192 706 us in tiles of 256 x 256, 957 in 128 x 128; M = 800, N = K = 2048 45 us in 208 tiles of 64 x 128, 60 in 112 of
-// 128 x 128 (the fp32 matrix cores: 57).
+// Tiles as large as still give most compute units one (every tile adds in the same order).  us in tiles of 256 x 256 / 128 x 128 /
+// 64 x 128: M = 2048, N = K = 8192 1188 / 1467 / 1638; 800, 8192 915 (128 tiles) / 693 / 761; two of 1600, 1024 135 / 52 (208) / 55; 800, 2048
+// 241 / 86 (112) / 63.
 static hipError_t launch_up_split(const NetDev &net, const SplitJobs &jobs, hipStream_t s) {
   if (jobs.count <= 0) return hipSuccess;
   int most = 0;
   for (int k = 0; k < jobs.count; ++k) {
-    if (jobs.j[k].M > SNN_BWD_TILE * net.B) return hipErrorInvalidValue; // what row_scale holds
+    if (jobs.j[k].M > SNN_BWD_TILE * net.B || jobs.j[k].K <= 64) return hipErrorInvalidValue; // (what row_scale holds; more than two blocks)
     most = std::max(most, jobs.j[k].M);
   }
   hipLaunchKernelGGL(k_row_scales, dim3((unsigned)(most + 3) / 4, jobs.count), dim3(256), 0, s, jobs);
@@ -6156,9 +6163,9 @@ static hipError_t launch_up_split(const NetDev &net, const SplitJobs &jobs, hipS
     for (int k = 0; k < jobs.count; ++k) sum += ((jobs.j[k].M + m - 1) / m) * ((jobs.j[k].N + n - 1) / n);
     return sum;
   };
-  if (tiles(256, 256) >= 192) return launch_up_split_t<2, 4, 4, 2, 2>(jobs, s);
-  if (tiles(128, 128) >= 192) return launch_up_split_t<2, 4, 2, 1, 2>(jobs, s);
-  return launch_up_split_t<2, 4, 1, 1, 4>(jobs, s);
+  if (tiles(256, 256) >= 192) return launch_up_split_t<2, 4, 4, 2, 2, 1>(jobs, s);
+  if (tiles(128, 128) >= 192) return launch_up_split_t<2, 4, 2, 1, 2, 2>(jobs, s);
+  return launch_up_split_t<2, 4, 1, 1, 4, 2>(jobs, s);
 }
 
 hipError_t launch_adjoint_head(const NetDev &net, int t0, int t1, int t_base, float *dubuf, const float *g,

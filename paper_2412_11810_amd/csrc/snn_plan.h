@@ -32,12 +32,13 @@ inline bool seq_by_column(const MaskedLayer *layers, int n) {
 }
 
 // ---- inter-layer products of the adjoint pass -----------------------------------------------------
-// N neurons below, K above: split into fp16 halves (k_up_split) or on the fp32 matrix cores.  The same kernel for every number of
+// N neurons below, K above: split into three bf16 parts (k_up_split) or on the fp32 matrix cores.  The same kernel for every number of
 // rows: they differ in the last bits, and gradients must not depend on how the time axis is cut.  From 1024 neurons the split one is
 // never slower (training steps, two layers: 1024 neurons, batch 4 / 16 / 64 3.73 / 4.30 / 6.84 -> 3.74 / 4.30 / 6.54 ms; 1500-1100,
 // batch 8 / 24 3.14 / 3.82 -> 3.14 / 3.73); 512 and 700 neurons gain nothing below batch 64.
 inline bool split_product(int N, int K) { return N >= 1024 && K >= 1024; }
-constexpr size_t split_row_bytes(int K) { return (size_t)(K + 31) / 32 * 128; } // of a split matrix: whole tiles of 32 elements
+#define UPS_SLAB_BYTES 96 // 16 elements of a row of a split matrix: the high, the middle and the low parts
+constexpr size_t split_row_bytes(int K) { return (size_t)(K + 31) / 32 * (2 * UPS_SLAB_BYTES); } // whole blocks of 32 elements
 
 // ---- weight gradients of large matrices -----------------------------------------------------------
 // Tiles of 256 x 64 of a network's matrices (k_dw_split), and where that kernel takes its weight gradients: by the shapes and the batch

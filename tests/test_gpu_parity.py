@@ -327,7 +327,7 @@ def test_tiled_weight_gradients_at_the_edges_of_tiles(hidden, B, T, monkeypatch)
     ((1025, 1024, 1023), 257, 33, 5, False), ((1024, 1024, 1024), 64, 64, 4, False),  # two
     ((2048, 2048), 1000, 20, 6, True), ((1100, 3200), 100, 20, 4, True)])             # masked: dense, and beside gradients per synapse
 def test_weight_gradients_on_the_fp16_matrix_cores(hidden, n_in, B, T, masked, monkeypatch):
-    """Weight gradients of large matrices with the adjoints split into three fp16 values, ragged tiles, steps and batches: bit-identical
+    """Weight gradients of large matrices with the adjoints split into three 16-bit values, ragged tiles, steps and batches: bit-identical
     however the time axis is cut, and the contraction on the fp32 matrix cores but for the rounding of a step's sum (a few times
     2^-24 of it, of either sign: below 2^-21 in the 2-norm)."""
     w = synth.Workload("dws_" + "x".join(map(str, hidden)), n_in, hidden, 7, T=T, B=B, p_in=0.2, gain=0.5, seed=B)
@@ -548,7 +548,7 @@ def test_streamed_chip_wide_adjoint(hidden, B, T, monkeypatch):
                                               ((2080, 2048), 40, 21, 1.0),  # tiles of 128 x 128
                                               ((4160, 4096), 64, 50, 1.0)])  # tiles of 256 x 256
 def test_split_inter_layer_products(hidden, B, T, scale, monkeypatch):
-    """Products of large matrices from fp16 halves on the matrix cores.  The split loses 2^-24 of an element and the sums of 1025 to
+    """Products of large matrices from three bf16 parts on the matrix cores.  What is left out is 2^-26 of a product and the sums of 1025 to
     4160 products round like fp32 ones: an error of 1e-6 of the product in the 2-norm, which the gradients below the product
     (sums over steps and batch) can only carry on.  Strategies bit-identical, whatever the tiles."""
     w = synth.Workload("split_" + "x".join(map(str, hidden)), 40, hidden, 7, T=T, B=B, p_in=0.1, gain=0.5, seed=17 + B)
@@ -571,6 +571,33 @@ def test_split_inter_layer_products(hidden, B, T, scale, monkeypatch):
         err = np.linalg.norm(got.astype(np.float64) - exp) / np.linalg.norm(exp)
         print(hidden, B, T, scale, err)
         assert err <= 2e-6
+
+
+@pytest.mark.parametrize("hidden,B,factor", [((1024, 1040), 5, 2.0 ** 40), ((1100, 1030), 40, 2.0 ** 60), ((2050, 2048), 260, 2.0 ** 50)])
+def test_inter_layer_products_of_values_far_apart(hidden, B, factor):
+    """One adjoint of the upper layer far above the others, and neurons below that have no synapse to its neuron: their products hold the
+    small adjoints only, to fp32's accuracy as with any other kernel (1e-6 in the 2-norm, and every value: a single step, no recurrence)."""
+    w = synth.Workload("far", 40, hidden, 7, T=1, B=B, p_in=0.3, gain=0.5, seed=B)
+    d = synth.generate(w)
+    j = 9  # never fires
+    d["W_in"][1][:, j] = -np.abs(d["W_in"][1][:, j])
+    d["W_in"][1][::2, j] = 0.0
+    d["W_out"][j] *= np.float32(factor)
+    ref = _oracle(w, d, want_v=True, nthreads=8, backward=False)
+    ref64 = _oracle_f64_on_f32_trajectory(w, d, ref, 8)
+    net = snn.from_workload(w, d)
+    try:
+        net.snn_bind_inputs(d["in_spikes"], d["labels"], 1)
+        net.snn_bptt(snn.SNN_STANDARD)
+        got = net.snn_grads(snn.SNN_W_IN, 0).astype(np.float64)
+    finally:
+        net.snn_destroy()
+    exp = ref64.dW_in[0]
+    assert np.abs(exp[:, 1::2]).max() > 2.0 ** 24 * np.abs(exp[:, ::2]).max()
+    for k in (0, 1):
+        err = got[:, k::2] - exp[:, k::2]
+        print(hidden, B, factor, k, np.linalg.norm(err) / np.linalg.norm(exp[:, k::2]), np.abs(err).max() / np.abs(exp[:, k::2]).max())
+        assert np.linalg.norm(err) <= 2e-6 * np.linalg.norm(exp[:, k::2])
 
 
 @pytest.mark.parametrize("hidden,B,T,density,csr", [
