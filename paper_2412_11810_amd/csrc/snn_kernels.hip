@@ -2296,6 +2296,8 @@ k_up_gemm(const float *__restrict__ A, int lda, const float *__restrict__ W, int
 // values, 1.7e-7 of the sum of the terms' magnitudes at most (2.0e-7), also where the elements of a row span six decades.
 // The matrix cores cut the terms they align below an accumulator towards minus infinity, always the same way, which sums over
 // thousands of time steps would see.  Every 256 k turn the sign of A and of the accumulators, and what is cut off changes sides.
+//   A row with an infinity or NaN cannot be split.  Its scale is negative, and the elements of C that it takes part in are computed again at the
+// end, in fp32 from the terms that are not finite (0 * inf among them).
 //   W comes split (k_split_rows, once per step: by slabs of 16 k, of a row 32 bytes each of h, m and l, so that the rows of a tile lie one
 //   after the other; padded with zeros to whole blocks of 32), A is split while it is staged.  The last block of 32 comes first: it alone may be
 //   ragged, so the loop is straight-line code.
@@ -2325,34 +2327,38 @@ static __device__ __forceinline__ float row_scale(float mx) {
   const uint32_t e = __float_as_uint(mx) >> 23;
   return __uint_as_float((e < 50u ? 254u : 304u - e) << 23);
 }
-static __device__ __forceinline__ float row_max(const float *__restrict__ r, int K, int lane) { // over a wavefront
-  float mx = 0.0f;
+// The same for the bits of the largest magnitude of a row, infinities and NaN above all; a scale below zero: there are some.
+#define BITS_INF 0x7f800000u
+static __device__ __forceinline__ float row_scale_of_bits(uint32_t mx) { return mx >= BITS_INF ? -1.0f : row_scale(__uint_as_float(mx)); }
+static __device__ __forceinline__ uint32_t row_max(const float *__restrict__ r, int K, int lane) { // over a wavefront
+  const auto bits = [](float x) { return __float_as_uint(x) & 0x7fffffffu; };
+  uint32_t mx = 0u;
   int k = 4 * lane;
   for (; k + 4 <= K; k += 256) {
     const f32x4u v = *reinterpret_cast<const f32x4u *>(r + k);
-    mx = fmaxf(fmaxf(mx, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
+    mx = max(max(mx, max(bits(v[0]), bits(v[1]))), max(bits(v[2]), bits(v[3])));
   }
-  for (; k < K; ++k) mx = fmaxf(mx, fabsf(r[k])); // (at most three elements, of one lane)
-  for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+  for (; k < K; ++k) mx = max(mx, bits(r[k])); // (at most three elements, of one lane)
+  for (int d = 32; d > 0; d >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, d));
   return mx;
 }
 // The products of a launch (of the layers of a stage, independent of each other): C = A W^T
-struct SplitJob { const float *A; float *sa; const uint4 *WS; const float *sw; float *C; int lda, K, N, M, tile0; };
+struct SplitJob { const float *A; float *sa; const uint4 *WS; const float *W, *sw; float *C; int lda, K, N, M, tile0; };
 struct SplitJobs { SplitJob j[SNN_MAXL]; int count; };
 __global__ void __launch_bounds__(256) // a wavefront per row: bound by reading A once (13 us for 67 MB)
 k_row_scales(SplitJobs jobs) {
   const SplitJob &jb = jobs.j[blockIdx.y];
   const int m = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = lane_id();
   if (m >= jb.M) return;
-  const float mx = row_max(jb.A + (size_t)m * jb.lda, jb.K, lane);
-  if (lane == 0) jb.sa[m] = row_scale(mx);
+  const uint32_t mx = row_max(jb.A + (size_t)m * jb.lda, jb.K, lane);
+  if (lane == 0) jb.sa[m] = row_scale_of_bits(mx);
 }
 __global__ void __launch_bounds__(256) // a wavefront per row; the second look at the row comes from the caches
 k_split_rows(const float *__restrict__ W, int K, int N, uint4 *__restrict__ WS, float *__restrict__ scale) {
   const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = lane_id(), K8 = (K + 31) / 32 * 4;
   if (j >= N) return;
   const float *r = W + (size_t)j * K;
-  const float sc = row_scale(row_max(r, K, lane));
+  const float sc = row_scale_of_bits(row_max(r, K, lane));
   if (lane == 0) scale[j] = sc;
   for (int q = lane; q < K8; q += 64) { // half a slab
     float x[8];
@@ -2523,19 +2529,37 @@ k_up_split(SplitJobs jobs) {
     __syncthreads();
   }
   const uint32_t sign = (nk - 1) / FLIP % 2 ? 0x80000000u : 0u;
+  int special = 0; // below zero: a row that is not finite
 #pragma unroll
   for (int p = 0; p < BM; ++p)
 #pragma unroll
     for (int q = 0; q < BN; ++q) {
       const int j = j0 + (wn * BN + q) * 32 + (lane & 31);
-      const int ej = 254 - (int)(__float_as_uint(sw[min(j, N - 1)]) >> 23);
+      const int bj = __float_as_int(sw[min(j, N - 1)]), ej = 254 - (bj >> 23);
+      special |= bj;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int m = m0 + (wm * BM + p) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const float v = ldexpf(acc[p][q][r], ej - (int)(__float_as_uint(sa[min(m, M - 1)]) >> 23));
+        const int bm = __float_as_int(sa[min(m, M - 1)]);
+        special |= bm;
+        const float v = ldexpf(acc[p][q][r], ej - (bm >> 23));
         if (m < M && j < N) C[(size_t)m * N + j] = __uint_as_float(__float_as_uint(v) ^ sign);
       }
     }
+  if (special >= 0) return;
+#pragma unroll 1
+  for (int i = 0; i < BM * BN * 16; ++i) {
+    const int p = i / (16 * BN), q = i / 16 % BN, r = i % 16;
+    const int j = j0 + (wn * BN + q) * 32 + (lane & 31), m = m0 + (wm * BM + p) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    if (m >= M || j >= N || (__float_as_int(sa[m]) | __float_as_int(sw[j])) >= 0) continue;
+    const float *const a = A + (size_t)m * lda, *const w = jb.W + (size_t)j * K;
+    float v = 0.0f;
+    for (int k = 0; k < K && v == v; ++k) {
+      const float x = a[k] * w[k];
+      if (!(fabsf(x) < __builtin_inff())) v += x;
+    }
+    C[(size_t)m * N + j] = v;
+  }
 }
 
 __device__ __forceinline__ void up_gemm16_body(const float *__restrict__ A, int lda, const float *__restrict__ W, int K,
@@ -6129,7 +6153,7 @@ static int split_layer(const NetDev &net, const float *W) {
   return 0;
 }
 static void add_split_job(const NetDev &net, SplitJobs *jobs, int l, const float *A, int lda, float *C, int M) {
-  jobs->j[jobs->count++] = SplitJob{A, net.row_scale + (size_t)l * SNN_BWD_TILE * net.B, net.W_split[l], net.W_scale[l], C, lda, net.N[l],
+  jobs->j[jobs->count++] = SplitJob{A, net.row_scale + (size_t)l * SNN_BWD_TILE * net.B, net.W_split[l], net.W_in[l], net.W_scale[l], C, lda, net.N[l],
                                     net.N[l - 1], M, 0};
 }
 template <int WM, int WN, int BM, int BN, int WPE, int KS>

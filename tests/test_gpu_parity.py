@@ -600,6 +600,39 @@ def test_inter_layer_products_of_values_far_apart(hidden, B, factor):
         assert np.linalg.norm(err) <= 2e-6 * np.linalg.norm(exp[:, k::2])
 
 
+@pytest.mark.parametrize("hidden,B,T", [((1024, 1030), 16, 1), ((1500, 1100), 40, 2), ((2050, 2048), 200, 1), ((4100, 4096), 250, 2)])
+def test_inter_layer_products_of_infinite_values(hidden, B, T, monkeypatch):
+    """An infinite adjoint in the upper layer and an infinite weight (of neurons that never fire), together and the weight alone: the
+    products are those of fp32 arithmetic, infinite of either sign, NaN where an infinity meets a zero, finite everywhere else."""
+    monkeypatch.setenv("SNN_CURRENTS", "gather")  # currents of the neurons that fire alone (a weight of infinity meets no silent one)
+    w = synth.Workload("inf_up", B, hidden, 7, T=T, B=B, p_in=1.0, gain=0.5, seed=B)
+    d = synth.generate(w)
+    d["in_spikes"] *= np.eye(B, dtype=np.uint8)  # an input per sample: gradients of single adjoints
+    d["W_in"][0] *= np.float32(np.sqrt(B))
+    j = _with_an_infinite_adjoint(d)
+    d["W_in"][1][::3, j] = 0.0
+    d["W_in"][0][:, 11] = -np.abs(d["W_in"][0][:, 11])
+    d["W_rec"][0][:, 11] = -np.abs(d["W_rec"][0][:, 11])
+    d["W_in"][1][11, 20] = -np.inf
+    for both in (True, False):
+        if not both:
+            d["W_out"][j, 0] = 1.0
+        ref = _oracle(w, d, want_v=True, nthreads=8, backward=False)
+        ref64 = _oracle_f64_on_f32_trajectory(w, d, ref, 8)
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], T)
+            net.snn_bptt(snn.SNN_STANDARD)
+            got = net.snn_grads(snn.SNN_W_IN, 0)
+        finally:
+            net.snn_destroy()
+        exp = ref64.dW_in[0]
+        print(hidden, B, T, both, "inf", int(np.isinf(exp).sum()), "nan", int(np.isnan(exp).sum()), "of", exp.size)
+        if T == 1:
+            assert np.isinf(exp).any() and np.isnan(exp).any() == both and (both or np.isfinite(np.delete(exp, 11, 1)).all())
+        _same_values(got, exp, 2e-6)
+
+
 @pytest.mark.parametrize("hidden,B,T,density,csr", [
     ((1025,), 3, 70, 1.0, None),           # one neuron in the last spike word
     ((1500, 1100), 5, 40, 1.0, None),      # two widths in one launch
