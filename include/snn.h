@@ -283,6 +283,7 @@ void snn_destroy(snn_ctx *ctx);
  *                                to 64 and matrices that fill the chip, which differs in the last bits; else tiled
  *                                when some weight matrix has 32 MB or more, else the contraction or tiled by the
  *                                activity)
+ *     SNN_DW_STEPS=n             workspace of those bf16 parts for at most n steps, as if the device had no room for more
  *     SNN_RF_CACHE=0             Double: never keep a coarse segment's currents between its two recompute passes
  *     SNN_KEEP_CURRENTS=0        Double: the forward pass never leaves the currents of the last coarse segments in
  *                                that cache (default: as many whole segments as the budget has room for)

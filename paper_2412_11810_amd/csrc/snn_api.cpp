@@ -92,9 +92,11 @@ struct snn_ctx {
   bool graphs_enabled = true;   // SNN_GRAPH=0 turns graph replay off
   bool own_stream = false;
   bool dw_event_driven = false; // SNN_DW=event selects the row-by-row kernel instead of the MFMA contraction
-  // k_dw_split: its workspace (NULL: not used), and in it, for a tile of SNN_BWD_TILE steps, the split adjoints and their scales (of every
+  bool dw_by_split = false; // weight gradients by k_dw_split (fixed by the shapes, the batch and SNN_DW)
+  // its workspace, and in it, for dw_steps steps, the split adjoints and their scales (of every
   // layer, the readout last) and the spikes (W_in and W_rec of layer l at 2 l and 2 l + 1, W_out last); see DwDesc
   unsigned char *dw_ws = nullptr;
+  int dw_steps = 0, dw_steps_max = SNN_BWD_TILE; // (SNN_DW_STEPS; less where the device had no room for more)
   uint4 *dw_split[SNN_MAXL + 1]{};
   float *dw_scale[SNN_MAXL + 1]{};
   uint8_t *dw_octets[2 * SNN_MAXL + 1]{};
@@ -205,7 +207,7 @@ int pre_of(const NetDev &n, int l) { return l == 0 ? n.n_in : n.N[l - 1]; }
 // Does the recurrent matrix of layer l go through k_dw_split, where the network's matrices do?  Not a wide one whose synapses are few enough
 // for k_dw_csr (whether or not that runs in this step: the choice must not follow the activity).
 bool dw_rec_split(const snn_ctx *c, int l) {
-  return c->dw_ws && (dw_split_masked(c->net.N[l]) || !(c->csr_sub[l] && c->csr_dw_ok[l] && c->acc_csr[l] && c->net.B <= 32));
+  return c->dw_by_split && (dw_split_masked(c->net.N[l]) || !(c->csr_sub[l] && c->csr_dw_ok[l] && c->acc_csr[l] && c->net.B <= 32));
 }
 
 // Does the recurrent matrix of layer l accumulate its gradient per existing synapse (k_dw_csr)?  Where the tiled
@@ -292,6 +294,48 @@ size_t spike_bytes(const NetDev &n, int T, int ring = 0) {
   size_t w = (size_t)(T + 1) * n.B * n.Wd[0];
   for (int l = 1; l <= n.L; ++l) w += (size_t)(ring > 0 ? ring : T + 1) * n.B * n.Wd[l];
   return w * 8;
+}
+
+// Workspace of k_dw_split for `steps` steps: its bytes, and where its parts are (at: NULL, or where it starts).
+size_t dw_workspace(snn_ctx *c, int steps, unsigned char *at) {
+  const NetDev &n = c->net;
+  const size_t octets = (size_t)steps * dw_split_octets(n.B);
+  size_t sum = 0;
+  const auto take = [&](size_t bytes) {
+    unsigned char *const p = at ? at + sum : nullptr;
+    sum += (bytes + 255) & ~(size_t)255;
+    return p;
+  };
+  c->dw_special = reinterpret_cast<unsigned *>(take((SNN_MAXL + 1) * sizeof(unsigned)));
+  for (int l = 0; l <= n.L; ++l) {
+    const size_t cols = l < n.L ? n.N[l] : n.n_out;
+    c->dw_split[l] = reinterpret_cast<uint4 *>(take(octets * 3 * cols * sizeof(uint4)));
+    c->dw_scale[l] = reinterpret_cast<float *>(take(octets * cols * sizeof(float)));
+  }
+  for (int i = 0; i <= 2 * n.L; ++i) c->dw_octets[i] = take(octets * 64 * n.Wd[i == 2 * n.L ? n.L : (i + 1) / 2]);
+  return sum;
+}
+// That workspace for `steps` steps, or for as many as the device has room for (not asked again for more): a tile then takes several
+// ranges of steps, and the gradients are the same bits.
+snn_status ensure_dw(snn_ctx *c, int steps) {
+  const int most = c->dw_steps_max;
+  for (steps = std::min(steps, most); c->dw_steps < steps; c->dw_steps_max = steps /= 2) {
+    if (c->dw_ws) {
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+      (void)hipFree(c->dw_ws);
+      c->dw_ws = nullptr; c->dw_steps = 0;
+    }
+    if (hipMalloc(&c->dw_ws, dw_workspace(c, steps, nullptr)) == hipSuccess) {
+      c->dw_steps = steps;
+      (void)dw_workspace(c, steps, c->dw_ws);
+      return SNN_OK;
+    }
+    (void)hipGetLastError();
+    c->dw_ws = nullptr;
+  }
+  if (c->dw_ws) return SNN_OK;
+  c->dw_steps_max = most;
+  return fail(c, SNN_E_HIP, "no room for the workspace of the weight gradients");
 }
 
 void free_csr(snn_ctx *c, int l) {
@@ -588,27 +632,11 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
   {
     int tiles = dw_split_tiles(n.N[L - 1], n.n_out);
     for (int l = 0; l < L; ++l) tiles += dw_split_tiles(pre_of(n, l), n.N[l]) + dw_split_tiles(n.N[l], n.N[l]);
-    if (dw_split_pays(tiles, B) && !bwd_stage_fusable(n, dw_wide_tiles(n) ? 1 : 0) && !std::getenv("SNN_DW")) {
-      const size_t octets = (size_t)SNN_BWD_TILE * dw_split_octets(B);
-      size_t at_split[SNN_MAXL + 1], at_scale[SNN_MAXL + 1], at_octets[2 * SNN_MAXL + 1], sum = 0;
-      const auto take = [&](size_t bytes) { const size_t at = sum; sum += (bytes + 255) & ~(size_t)255; return at; };
-      for (int l = 0; l <= L; ++l) {
-        const size_t cols = l < L ? n.N[l] : O;
-        at_split[l] = take(octets * 3 * cols * sizeof(uint4));
-        at_scale[l] = take(octets * cols * sizeof(float));
-      }
-      for (int i = 0; i <= 2 * L; ++i) at_octets[i] = take(octets * 64 * n.Wd[i == 2 * L ? L : (i + 1) / 2]);
-      const size_t at_special = take((SNN_MAXL + 1) * sizeof(unsigned));
-      if (hipMalloc(&c->dw_ws, sum) != hipSuccess) { // a device without the room: the kernels that need none
-        (void)hipGetLastError();
-        c->dw_ws = nullptr;
-      }
-      for (int l = 0; c->dw_ws && l <= L; ++l) {
-        c->dw_split[l] = reinterpret_cast<uint4 *>(c->dw_ws + at_split[l]);
-        c->dw_scale[l] = reinterpret_cast<float *>(c->dw_ws + at_scale[l]);
-      }
-      for (int i = 0; c->dw_ws && i <= 2 * L; ++i) c->dw_octets[i] = c->dw_ws + at_octets[i];
-      if (c->dw_ws) c->dw_special = reinterpret_cast<unsigned *>(c->dw_ws + at_special);
+    c->dw_by_split = dw_split_pays(tiles, B) && !bwd_stage_fusable(n, dw_wide_tiles(n) ? 1 : 0) && !std::getenv("SNN_DW");
+    if (const char *e = std::getenv("SNN_DW_STEPS")) c->dw_steps_max = std::max(1, std::min(SNN_BWD_TILE, std::atoi(e)));
+    if (c->dw_by_split) {
+      const snn_status rs = ensure_dw(c, SNN_BWD_TILE);
+      if (rs != SNN_OK) return rs;
     }
   }
   if (const char *e = std::getenv("SNN_DW")) {
@@ -1557,6 +1585,7 @@ struct BwdPipe {
     const int B = n.B, O = n.n_out, L = n.L, SN = n.SN;
     const size_t slot = (size_t)B * SN;
     db->wide = dw_wide ? 1 : 0;
+    db->split_steps = c->dw_steps;
     for (const BwdTile &t : done) {
       const int l = t.layer;
       if (l == L - 1)

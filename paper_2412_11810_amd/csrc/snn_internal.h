@@ -237,6 +237,7 @@ struct DwBatch {
   DwDesc d[2 * SNN_MAXL + 1];
   int count;
   int wide;                 // tile shape, fixed per network (see snn_dw_wide_tiles)
+  int split_steps;          // steps that the workspace of k_dw_split holds
 };
 // (matrices with a workspace for it go through k_dw_split, batch sizes up to 64)
 hipError_t launch_dw_mfma(DwBatch batch, int B, hipStream_t s);

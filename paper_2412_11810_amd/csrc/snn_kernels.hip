@@ -6668,21 +6668,15 @@ static int dw_tile_rows(const DwBatch &batch) {
   return best;
 }
 
-// Takes the matrices that go through k_dw_split out of the batch.
-static hipError_t launch_dw_split(DwBatch *all, int B, hipStream_t s) {
-  DwBatch batch{}, others{};
-  others.wide = all->wide;
-  for (int i = 0; i < all->count; ++i) (all->d[i].split ? batch.d[batch.count++] : others.d[others.count++]) = all->d[i];
-  if (batch.count <= 0) return hipSuccess;
-  *all = others;
-  if (B < 1 || B > 64) return hipErrorInvalidValue;
+// One range of steps, of every matrix no more than the workspace holds.
+static hipError_t launch_dw_split_range(DwBatch batch, int B, hipStream_t s) {
   const int no = dw_split_octets(B), per = B <= 16 ? 1 : no / 4;
   DwRowsJobs rows{};
   DwOctetsJobs octs{};
   int n_rows = 0, cols = 0, steps = 0, total = 0, words = 0;
   for (int i = 0; i < batch.count; ++i) {
     DwDesc &d = batch.d[i];
-    if (d.t1 <= d.t0 || d.t1 - d.t0 > SNN_BWD_TILE || !d.scale || !d.octets || !d.split || !d.special) return hipErrorInvalidValue;
+    if (d.t1 <= d.t0 || d.t1 - d.t0 > batch.split_steps || !d.scale || !d.octets || !d.split || !d.special) return hipErrorInvalidValue;
     d.tiles_n = (d.n_post + DWS_TN - 1) / DWS_TN;
     d.tile0 = total;
     total += ((d.n_pre + DWS_TJ - 1) / DWS_TJ) * d.tiles_n;
@@ -6706,6 +6700,35 @@ static hipError_t launch_dw_split(DwBatch *all, int B, hipStream_t s) {
     return hipGetLastError();
   };
   return B <= 16 ? go(k_dw_split_rows<true>, k_dw_split<true>) : go(k_dw_split_rows<false>, k_dw_split<false>);
+}
+// Takes the matrices that go through k_dw_split out of the batch.  A workspace of fewer steps than a tile takes its steps in several
+// ranges, the last ones first: the same additions in the same order.
+static hipError_t launch_dw_split(DwBatch *all, int B, hipStream_t s) {
+  DwBatch batch{}, others{};
+  others.wide = all->wide;
+  batch.split_steps = all->split_steps;
+  int longest = 0;
+  for (int i = 0; i < all->count; ++i) {
+    const DwDesc &d = all->d[i];
+    (d.split ? batch.d[batch.count++] : others.d[others.count++]) = d;
+    if (d.split) longest = std::max(longest, d.t1 - d.t0);
+  }
+  if (batch.count <= 0) return hipSuccess;
+  *all = others;
+  if (B < 1 || B > 64 || batch.split_steps < 1 || longest < 1) return hipErrorInvalidValue;
+  for (int from = 0; from < longest; from += batch.split_steps) { // steps from the end of the tile
+    DwBatch range{};
+    range.split_steps = batch.split_steps;
+    for (int i = 0; i < batch.count; ++i) {
+      DwDesc d = batch.d[i];
+      d.t1 -= from;
+      d.t0 = std::max(d.t0, d.t1 - batch.split_steps);
+      if (d.t1 > d.t0) range.d[range.count++] = d;
+    }
+    const hipError_t e = launch_dw_split_range(range, B, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_dw_tile(DwBatch batch, int B, hipStream_t s) {

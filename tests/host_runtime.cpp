@@ -141,8 +141,9 @@ void adjoint_prepare(const NetDev &, const WsArgs &) {}
 hipError_t launch_dw(const uint64_t *, int, int, int, const float *, size_t, int, int, int, int, int, int, int, double *, hipStream_t, int) {
   return hipSuccess;
 }
-hipError_t launch_dw_mfma(DwBatch, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_dw_tile(DwBatch, int, hipStream_t) { return hipSuccess; }
+static DwBatch g_dw; // the last one
+hipError_t launch_dw_mfma(DwBatch b, int, hipStream_t) { g_dw = b; return hipSuccess; }
+hipError_t launch_dw_tile(DwBatch b, int, hipStream_t) { g_dw = b; return hipSuccess; }
 bool bwd_stage_fusable(const NetDev &, int) { return false; }
 int bwd_pre_placement(const NetDev &) { return 0; }
 hipError_t launch_bwd_stage(const NetDev &, const AdjJobs &, float *, DwBatch, DuJob, const float *, PreJobs, hipStream_t, const SpanHook *) {
@@ -346,6 +347,29 @@ static void workspace() {
   g_largest = ~(size_t)0;
 }
 
+// Which kernel takes the weight gradients never follows the memory that is free: where there is no room for its workspace it walks
+// shorter ranges of steps
+static void split_room() {
+  const auto by_split = [](const Net &n) {
+    CHECK(g_dw.count == 3 && g_dw.split_steps >= 1 && g_dw.split_steps <= SNN_BWD_TILE);
+    for (int i = 0; i < 3; ++i) CHECK(g_dw.d[i].split && g_dw.d[i].scale && g_dw.d[i].octets);
+  };
+  for (size_t room : {~(size_t)0, (size_t)150 << 20, (size_t)75 << 20}) {
+    g_largest = room;
+    Net n(2048, 300, 64);
+    CHECK(n.bind() == SNN_OK);
+    for (int k = 0; k < 2; ++k) {
+      const int refused = g_refused;
+      CHECK(snn_bptt(n.c, SNN_CHUNK, 0, 5, 0, nullptr) == SNN_OK);
+      by_split(n);
+      CHECK(k == 0 || g_refused == refused);
+    }
+    CHECK(room != ~(size_t)0 || g_dw.split_steps == n.c->dw_steps);
+    CHECK(room == ~(size_t)0 || n.c->dw_steps < SNN_BWD_TILE);
+  }
+  g_largest = ~(size_t)0;
+}
+
 // The activity that the kernels of the currents are chosen by is that of the last call, whatever the call and the batch size, and
 // stays while the new one is near it (a recorded step holds the choice)
 static void rates() {
@@ -376,7 +400,7 @@ int main(int argc, char **argv) {
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
                                               {"time_out_is_reported", time_out_is_reported},
                                               {"turns", turns}, {"blocks", blocks}, {"workspace", workspace},
-                                              {"rates", rates}};
+                                              {"rates", rates}, {"split_room", split_room}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

@@ -387,6 +387,26 @@ def test_weight_gradients_of_samples_far_apart(B, monkeypatch):
     assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("B,steps", [(16, (1, 7, 32)), (40, (1, 5, 16))])
+def test_weight_gradients_in_ranges_of_steps(B, steps, monkeypatch):
+    """A workspace of fewer steps than a tile has (no room for more): the gradients of one that holds it, bit for bit."""
+    w = synth.Workload("ranges", 100, (1024, 1030), 7, T=33, B=B, p_in=0.2, gain=0.5, seed=B)
+    d = synth.generate(w)
+    got = []
+    for n in (None,) + steps:
+        if n:
+            monkeypatch.setenv("SNN_DW_STEPS", str(n))
+        net = snn.from_workload(w, d)
+        try:
+            net.snn_bind_inputs(d["in_spikes"], d["labels"], w.T)
+            for strat, C, F in ((snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 9)):
+                net.snn_bptt(strat, C, F)
+                got.append(_gpu_grads(net, 2))
+        finally:
+            net.snn_destroy()
+    assert all(np.any(g) for g in got[0][0] + got[0][1]) and all(_identical(got[0], g) for g in got[1:])
+
+
 def _same_values(got, want, rel):
     """Infinities and NaN in the same places, the other values within `rel` in the 2-norm."""
     fin = np.isfinite(want)

@@ -60,3 +60,7 @@ def test_workspace_is_allocated_once(checks):
 
 def test_activity_follows_every_call(checks):
     checks("rates")
+
+
+def test_gradients_do_not_follow_the_memory_that_is_free(checks):
+    checks("split_room")
