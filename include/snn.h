@@ -129,7 +129,9 @@ typedef struct {
  * here.  Outside any activation budget a context also holds: for a network with a layer above 256 neurons the buffers its
  * workgroups exchange through, 16 bytes per batch element (in whole groups of 16) and neuron of the widest layer, four
  * times and once more per layer (4 x 8192 neurons, batch 32: 34 MB); from the first spike trains in host memory on, three staging
- * buffers of 2 MiB or one time step of inputs each.
+ * buffers of 2 MiB or one time step of inputs each; for batches of 12 to 64 and matrices that fill the chip, from a training
+ * step on whose workspace and budget have no room for it, the workspace of 16 steps of the weight gradients, about 6.7 bytes per
+ * batch element (in whole groups of 16, above that of 32), neuron and step (4 x 8192 neurons, batch 32: 110 MB).
  * *out is set even on failure (so that snn_last_error can be read) and must be passed to snn_destroy.
  * SNN_E_INVAL for a shape outside the limits noted in snn_config. */
 snn_status snn_init(const snn_config *cfg, snn_ctx **out);
@@ -173,7 +175,9 @@ snn_status snn_forward_noalloc(snn_ctx *ctx, const uint8_t *in_spikes, const int
  *   snn_bytes_required is the least the strategy can run in (one chunk buffer: the paper's state
  *   count); below it -> SNN_E_BUDGET before anything is allocated.  Where the budget has room (or none is set), networks with a
  *   layer above 256 neurons also keep lists of active neurons for 65 steps in the workspace (2 bytes per neuron, step and batch
- *   element); stats counts them.  With room to spare (or no budget)
+ *   element); stats counts them.  Where the weight gradients take a workspace of their own (see snn_init) it is one of a quarter of what
+ *   the budget leaves at most, for the steps of one tile of the backward pass; stats counts it unless the step's workspace has the room.
+ *   With room to spare (or no budget)
  *   the call takes up to n_layers + 2 more chunk buffers, which let the layers of the adjoint pass and
  *   the recompute of the next chunks overlap; DOUBLE then takes coarse_interval more state slots to keep the
  *   synaptic currents of a coarse segment between its two recompute passes (Section "Double Checkpointing":

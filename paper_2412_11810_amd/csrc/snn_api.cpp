@@ -24,6 +24,10 @@ static __device__ __align__(256) unsigned char scratch[SNN_NOALLOC_SCRATCH_BYTES
 #define SNN_MAX_DEVICES 64
 static void *g_scratch_dev[SNN_MAX_DEVICES]; // per device ordinal, filled by snn_init with that device current
 
+// Workspace of k_dw_split: the split adjoints and their scales (of every layer, the readout last) and the spikes (W_in and W_rec of layer l
+// at 2 l and 2 l + 1, W_out last) of some steps; see DwDesc.
+struct DwSpace { unsigned *special; uint4 *split[SNN_MAXL + 1]; float *scale[SNN_MAXL + 1]; uint8_t *octets[2 * SNN_MAXL + 1]; };
+
 struct snn_ctx {
   snn_config cfg{};
   NetDev net{};
@@ -86,21 +90,18 @@ struct snn_ctx {
   float *host_ckpt = nullptr;
   size_t host_bytes = 0;
   std::vector<hipEvent_t> ev_pool;
-  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; void *lists; unsigned choice; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache && lists == o.lists && choice == o.choice; } };
+  struct GraphKeyT { int strategy, T, C, F, n_chunk_bufs; void *arena, *work, *host; bool dw_event; unsigned long long cur_pol; unsigned sel; void *ring, *host_spk, *mask1; int cache; void *lists; unsigned choice; void *dw; int dw_steps; bool operator==(const GraphKeyT &o) const { return strategy == o.strategy && T == o.T && C == o.C && F == o.F && n_chunk_bufs == o.n_chunk_bufs && arena == o.arena && work == o.work && host == o.host && dw_event == o.dw_event && cur_pol == o.cur_pol && sel == o.sel && ring == o.ring && host_spk == o.host_spk && mask1 == o.mask1 && cache == o.cache && lists == o.lists && choice == o.choice && dw == o.dw && dw_steps == o.dw_steps; } };
   GraphKeyT graph_key{};
   hipGraphExec_t graph_exec = nullptr;
   bool graphs_enabled = true;   // SNN_GRAPH=0 turns graph replay off
   bool own_stream = false;
   bool dw_event_driven = false; // SNN_DW=event selects the row-by-row kernel instead of the MFMA contraction
   bool dw_by_split = false; // weight gradients by k_dw_split (fixed by the shapes, the batch and SNN_DW)
-  // its workspace, and in it, for dw_steps steps, the split adjoints and their scales (of every
-  // layer, the readout last) and the spikes (W_in and W_rec of layer l at 2 l and 2 l + 1, W_out last); see DwDesc
+  // its workspace of a training step, for dw_steps steps: behind what the adjoint pass takes of the step's workspace, or
+  // an allocation of its own for dw_held steps, no more than dw_steps_max (SNN_DW_STEPS; what the device had room for)
+  DwSpace dw{};
   unsigned char *dw_ws = nullptr;
-  int dw_steps = 0, dw_steps_max = SNN_BWD_TILE; // (SNN_DW_STEPS; less where the device had no room for more)
-  uint4 *dw_split[SNN_MAXL + 1]{};
-  float *dw_scale[SNN_MAXL + 1]{};
-  uint8_t *dw_octets[2 * SNN_MAXL + 1]{};
-  unsigned *dw_special = nullptr; // [SNN_MAXL + 1]
+  int dw_steps = 0, dw_held = 0, dw_steps_max = SNN_BWD_TILE;
   bool dw_tile = false;         // the event-driven tiled kernel instead of the dense contraction (batch <= 64; SNN_DW=tile|mfma)
   bool dw_rate_driven = false;  // ... chosen from the firing rates of the previous step (layers wider than 256, no SNN_DW)
   bool bwd_pipeline = true;     // SNN_BWD_PIPE=0: the adjoint pass finishes every layer of a chunk before the next chunk
@@ -250,8 +251,11 @@ void read_kernel_hooks(snn_ctx *c) {
 // per-tile scratch of the adjoint pass: readout adjoints 3 x [tile][B][O] (three tiles alive) + one inter-layer product per layer
 // [tile][B][N_l] (the layers run one tile apart, so every layer's product is alive at once); the forward pass
 // uses the same scratch for the currents of one time tile
+size_t adjoint_work_bytes(const NetDev &n, int chunk_len) {
+  return (size_t)std::min(chunk_len, SNN_BWD_TILE) * n.B * (3 * n.n_out + n.SN) * sizeof(float);
+}
 size_t work_bytes(const NetDev &n, int chunk_len) {
-  const size_t bwd = (size_t)std::min(chunk_len, SNN_BWD_TILE) * n.B * (3 * n.n_out + n.SN) * sizeof(float);
+  const size_t bwd = adjoint_work_bytes(n, chunk_len);
   // currents of two tiles of every layer (double-buffered) + readout currents of SNN_RO_TILES tiles
   const size_t fwd = (size_t)SNN_FWD_TILE * n.B * (SNN_RO_TILES * n.n_out + 2 * n.SN) * sizeof(float);
   return bwd > fwd ? bwd : fwd;
@@ -296,46 +300,58 @@ size_t spike_bytes(const NetDev &n, int T, int ring = 0) {
   return w * 8;
 }
 
-// Workspace of k_dw_split for `steps` steps: its bytes, and where its parts are (at: NULL, or where it starts).
-size_t dw_workspace(snn_ctx *c, int steps, unsigned char *at) {
-  const NetDev &n = c->net;
-  const size_t octets = (size_t)steps * dw_split_octets(n.B);
+// Workspace of k_dw_split for `steps` steps: its bytes, and where its parts are if it starts at `at`.
+size_t dw_bytes(const NetDev &n, int steps, unsigned char *at = nullptr, DwSpace *d = nullptr) {
+  const size_t per = n.B <= 16 ? 1 : (size_t)dw_split_octets(n.B) / 4, octets = (size_t)steps * dw_split_octets(n.B);
   size_t sum = 0;
-  const auto take = [&](size_t bytes) {
-    unsigned char *const p = at ? at + sum : nullptr;
+  const auto take = [&](auto **p, size_t bytes) {
+    if (d) *p = reinterpret_cast<std::remove_reference_t<decltype(**p)> *>(at + sum);
     sum += (bytes + 255) & ~(size_t)255;
-    return p;
   };
-  c->dw_special = reinterpret_cast<unsigned *>(take((SNN_MAXL + 1) * sizeof(unsigned)));
+  DwSpace none;
+  DwSpace &o = d ? *d : none;
+  take(&o.special, (SNN_MAXL + 1) * sizeof(unsigned));
   for (int l = 0; l <= n.L; ++l) {
     const size_t cols = l < n.L ? n.N[l] : n.n_out;
-    c->dw_split[l] = reinterpret_cast<uint4 *>(take(octets * 3 * cols * sizeof(uint4)));
-    c->dw_scale[l] = reinterpret_cast<float *>(take(octets * cols * sizeof(float)));
+    take(&o.split[l], octets * 3 * cols * sizeof(uint4));
+    take(&o.scale[l], (size_t)steps * per * cols * sizeof(float));
   }
-  for (int i = 0; i <= 2 * n.L; ++i) c->dw_octets[i] = take(octets * 64 * n.Wd[i == 2 * n.L ? n.L : (i + 1) / 2]);
+  for (int i = 0; i <= 2 * n.L; ++i) take(&o.octets[i], octets * 64 * n.Wd[i == 2 * n.L ? n.L : (i + 1) / 2]);
   return sum;
 }
-// That workspace for `steps` steps, or for as many as the device has room for (not asked again for more): a tile then takes several
+// The most steps, up to `most`, whose workspace fits `room` bytes.
+int dw_steps_in(const NetDev &n, size_t room, int most) {
+  int lo = 0;
+  for (int hi = most; lo < hi;) {
+    const int mid = (lo + hi + 1) / 2;
+    if (dw_bytes(n, mid) <= room) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+// An allocation of its own for `steps` steps, or for as many as the device has room for (not asked again for more): a tile then takes several
 // ranges of steps, and the gradients are the same bits.
 snn_status ensure_dw(snn_ctx *c, int steps) {
   const int most = c->dw_steps_max;
-  for (steps = std::min(steps, most); c->dw_steps < steps; c->dw_steps_max = steps /= 2) {
+  for (steps = std::min(steps, most); c->dw_held < steps; c->dw_steps_max = steps /= 2) {
     if (c->dw_ws) {
       HIPCHK(c, hipStreamSynchronize(c->stream));
       (void)hipFree(c->dw_ws);
-      c->dw_ws = nullptr; c->dw_steps = 0;
+      c->dw_ws = nullptr; c->dw_held = 0;
     }
-    if (hipMalloc(&c->dw_ws, dw_workspace(c, steps, nullptr)) == hipSuccess) {
-      c->dw_steps = steps;
-      (void)dw_workspace(c, steps, c->dw_ws);
-      return SNN_OK;
+    if (hipMalloc(&c->dw_ws, dw_bytes(c->net, steps)) == hipSuccess) {
+      c->dw_held = steps;
+      break;
     }
     (void)hipGetLastError();
     c->dw_ws = nullptr;
   }
-  if (c->dw_ws) return SNN_OK;
-  c->dw_steps_max = most;
-  return fail(c, SNN_E_HIP, "no room for the workspace of the weight gradients");
+  if (!c->dw_ws) {
+    c->dw_steps_max = most;
+    return fail(c, SNN_E_HIP, "no room for the workspace of the weight gradients");
+  }
+  c->dw_steps = std::min(steps, c->dw_held);
+  (void)dw_bytes(c->net, c->dw_steps, c->dw_ws, &c->dw);
+  return SNN_OK;
 }
 
 void free_csr(snn_ctx *c, int l) {
@@ -634,10 +650,6 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
     for (int l = 0; l < L; ++l) tiles += dw_split_tiles(pre_of(n, l), n.N[l]) + dw_split_tiles(n.N[l], n.N[l]);
     c->dw_by_split = dw_split_pays(tiles, B) && !bwd_stage_fusable(n, dw_wide_tiles(n) ? 1 : 0) && !std::getenv("SNN_DW");
     if (const char *e = std::getenv("SNN_DW_STEPS")) c->dw_steps_max = std::max(1, std::min(SNN_BWD_TILE, std::atoi(e)));
-    if (c->dw_by_split) {
-      const snn_status rs = ensure_dw(c, SNN_BWD_TILE);
-      if (rs != SNN_OK) return rs;
-    }
   }
   if (const char *e = std::getenv("SNN_DW")) {
     c->dw_rate_driven = false;
@@ -1589,12 +1601,12 @@ struct BwdPipe {
     for (const BwdTile &t : done) {
       const int l = t.layer;
       if (l == L - 1)
-        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr, c->dw_split[L], c->dw_scale[L], c->dw_octets[2 * L], c->dw_special + L};
-      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr, c->dw_split[l], c->dw_scale[l], c->dw_octets[2 * l], c->dw_special + l};
+        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr, c->dw_by_split ? c->dw.split[L] : nullptr, c->dw.scale[L], c->dw.octets[2 * L], c->dw.special + L};
+      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr, c->dw_by_split ? c->dw.split[l] : nullptr, c->dw.scale[l], c->dw.octets[2 * l], c->dw.special + l};
       if (dw_rec_csr(c, l))
         db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_csr[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], n.csr_sub[l], n.csr_col[l], nullptr, nullptr, nullptr, nullptr};
       else
-        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr, dw_rec_split(c, l) ? c->dw_split[l] : nullptr, c->dw_scale[l], c->dw_octets[2 * l + 1], c->dw_special + l};
+        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr, dw_rec_split(c, l) ? c->dw.split[l] : nullptr, c->dw.scale[l], c->dw.octets[2 * l + 1], c->dw.special + l};
     }
   }
   snn_status emit_dw() {
@@ -2107,6 +2119,20 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   const size_t Ms = c->Ms();
   const int ring = spike_ring_steps(c->cfg, (int)strategy, T, p.C); // > 0: the hidden spike bitmasks live on the host tier
   const int asked_slots = p.local_slots();
+  // The workspace of k_dw_split for a tile of the adjoint pass, or for as many steps as a quarter of what the budget leaves holds; the
+  // rest of the budget is for states.  (Where that is next to nothing: see below.)
+  int dw_own = 0;
+  size_t need_dw = 0;
+  const int dw_tile_steps = std::min(T, L > 1 && c->bwd_pipeline ? bwd_tile_target(n, T) : SNN_BWD_TILE);
+  if (c->dw_by_split) {
+    dw_own = std::min(dw_tile_steps, c->dw_steps_max);
+    if (budget) {
+      const size_t least = (size_t)asked_slots * Ms + work_bytes(n, p.chunk_len) + spike_bytes(n, T, ring);
+      dw_own = dw_steps_in(n, budget > least ? (budget - least) / 4 : 0, dw_own);
+      need_dw = dw_own ? dw_bytes(n, dw_own) : 0;
+      budget -= need_dw;
+    }
+  }
   // One chunk buffer per layer lets the adjoint pass run its layers one chunk apart (see BwdPipe).  The extra
   // (L - 1) * chunk_len state slots are taken only if the budget has room for them; the results are the same
   // bit for bit either way.
@@ -2198,6 +2224,22 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
     const snn_status rs = ensure_states(c, need_states, need_work, room_for_lists(need_states, need_work));
     if (rs != SNN_OK) return rs;
   }
+  if (c->dw_by_split) {
+    // Short chunks leave room in the step's workspace, which is as large as the forward pass needs it.  Where neither that nor
+    // the budget holds SNN_DW_STEPS_LEAST, those are the context's, outside the budget.
+    const size_t from = (adjoint_work_bytes(n, p.chunk_len) + 255) & ~(size_t)255;
+    const int inside = dw_steps_in(n, need_work > from ? need_work - from : 0, std::min(dw_tile_steps, c->dw_steps_max));
+    if (inside >= dw_own && inside >= std::min(SNN_DW_STEPS_LEAST, dw_tile_steps)) {
+      need_dw = 0;
+      c->dw_steps = inside;
+      (void)dw_bytes(n, inside, reinterpret_cast<unsigned char *>(c->dubuf) + from, &c->dw);
+    } else {
+      if (dw_own < std::min(SNN_DW_STEPS_LEAST, dw_tile_steps)) need_dw = 0;
+      const snn_status rs = ensure_dw(c, std::max(dw_own, std::min(SNN_DW_STEPS_LEAST, dw_tile_steps)));
+      if (rs != SNN_OK) return rs;
+      if (need_dw || !budget) need_dw = dw_bytes(n, c->dw_steps);
+    }
+  }
   const size_t need_host = (size_t)p.n_remote * Ms;
   if (c->host_bytes < need_host) {
     HIPCHK(c, hipStreamSynchronize(s));
@@ -2245,7 +2287,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
   }
 
   snn_stats st{};
-  st.bytes_states = (int64_t)need_states; st.bytes_spikes = (int64_t)need_spikes; st.bytes_workspace = (int64_t)(need_work + (n.lists ? need_lists : 0));
+  st.bytes_states = (int64_t)need_states; st.bytes_spikes = (int64_t)need_spikes; st.bytes_workspace = (int64_t)(need_work + (n.lists ? need_lists : 0) + need_dw);
   st.bytes_host = (int64_t)need_host; st.local_state_slots = p.local_slots(); st.remote_state_slots = p.n_remote;
   st.bytes_host_spikes = (int64_t)need_host_spk;
 
@@ -2259,7 +2301,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
     pol = pol * 2 + (c->dw_tile ? 1u : 0u);
     const unsigned sel = (unsigned)n.sel_currents | (unsigned)n.sel_adjoint << 8 | (unsigned)n.sel_slices << 16 | (unsigned)n.sel_csr << 24 | (unsigned)n.sel_seq << 28 | (unsigned)n.no_fwd_fuse << 30;
     snn_ctx::GraphKeyT key{(int)strategy, T, p.C, p.F, p.n_chunk_bufs, c->arena, c->dubuf, c->host_ckpt, c->dw_event_driven, pol, sel,
-                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists, currents_choice(n, p.chunk_len)};
+                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists, currents_choice(n, p.chunk_len), (void *)c->dw.special, c->dw_steps};
     if (!c->graph_exec || !(key == c->graph_key)) {
       if (c->graph_exec) { (void)hipGraphExecDestroy(c->graph_exec); c->graph_exec = nullptr; }
       Timer tm{c, false};

@@ -52,6 +52,7 @@ constexpr size_t split_row_bytes(int K) { return (size_t)(K + 31) / 32 * (2 * UP
 inline int dw_split_tiles(int n_pre, int n_post) { return ((n_pre + 255) / 256) * ((n_post + 63) / 64); }
 // octets of batch elements per step: two, or whole parts of four
 constexpr int dw_split_octets(int B) { return B <= 16 ? 2 : (B + 31) / 32 * 4; }
+#define SNN_DW_STEPS_LEAST 16 // steps of its workspace that a context has whatever the budget (see snn_bptt)
 inline bool dw_split_pays(int tiles, int B) { return tiles >= 150 && B >= 12 && B <= 64; }
 // Of a masked recurrent matrix of such a network: the dense gradients here rather than the existing synapses' by k_dw_csr, which has few
 // workgroups (256 rows x 512 columns, a compute unit each) where a layer is not wide.  Training steps of 96 steps (64 from 4096

@@ -349,6 +349,11 @@ static void workspace() {
 
 // Which kernel takes the weight gradients never follows the memory that is free: where there is no room for its workspace it walks
 // shorter ranges of steps
+static size_t device_bytes() {
+  size_t sum = 0;
+  for (const auto &m : g_mem) sum += m.second;
+  return sum;
+}
 static void split_room() {
   const auto by_split = [](const Net &n) {
     CHECK(g_dw.count == 3 && g_dw.split_steps >= 1 && g_dw.split_steps <= SNN_BWD_TILE);
@@ -364,10 +369,55 @@ static void split_room() {
       by_split(n);
       CHECK(k == 0 || g_refused == refused);
     }
-    CHECK(room != ~(size_t)0 || g_dw.split_steps == n.c->dw_steps);
-    CHECK(room == ~(size_t)0 || n.c->dw_steps < SNN_BWD_TILE);
+    CHECK(g_dw.split_steps == n.c->dw_steps);
+    CHECK((room == ~(size_t)0) == (n.c->dw_steps == SNN_BWD_TILE));
   }
   g_largest = ~(size_t)0;
+}
+
+// That workspace is one of training steps, inside their budget but for SNN_DW_STEPS_LEAST steps
+static void split_workspace() {
+  size_t evaluation[3]; // (the first context of that size leaves its uncached block to the next)
+  for (int k = 0; k < 3; ++k) {
+    k == 1 ? setenv("SNN_DW", "mfma", 1) : unsetenv("SNN_DW");
+    const size_t before = device_bytes();
+    Net n(2048, 300, 64);
+    CHECK(n.bind() == SNN_OK && n.forward() == SNN_OK);
+    evaluation[k] = device_bytes() - before;
+  }
+  CHECK(evaluation[1] == evaluation[2]);
+  for (int strategy : {SNN_STANDARD, SNN_CHUNK, SNN_DOUBLE, SNN_HIER})
+    for (int F : {5, 100, 200})
+      for (double more : {1.0, 1.02, 1.3, 3.0, 0.0}) {
+        const int C = strategy == SNN_HIER ? 2 : 200;
+        Net n(2048, 300, 64);
+        CHECK(n.bind() == SNN_OK);
+        const size_t least = snn_bytes_required(&n.cfg, (snn_strategy)strategy, 300, C, F), budget = (size_t)(more * (double)least);
+        const size_t before = device_bytes();
+        snn_stats st{};
+        CHECK(snn_bptt(n.c, (snn_strategy)strategy, C, F, budget, &st) == SNN_OK);
+        const size_t counted = (size_t)(st.bytes_states + st.bytes_spikes + st.bytes_workspace), spikes = (size_t)st.bytes_spikes; // (held since snn_init)
+        CHECK(!budget || counted <= budget);
+        CHECK(more != 1.0 || counted == least);
+        CHECK(device_bytes() - before <= counted - spikes + dw_bytes(n.c->net, SNN_DW_STEPS_LEAST) + 512);
+        CHECK(g_dw.split_steps >= SNN_DW_STEPS_LEAST && (more > 0.0 || g_dw.split_steps == SNN_BWD_TILE));
+        // whatever the plan, the parts lie inside one of the two allocations and do not meet
+        std::vector<std::pair<const unsigned char *, const unsigned char *>> parts;
+        const size_t octets = (size_t)n.c->dw_steps * dw_split_octets(64);
+        for (int l = 0; l < 2; ++l) {
+          const size_t cols = l ? 8 : 2048;
+          const auto add = [&](const void *p, size_t bytes) { parts.push_back({(const unsigned char *)p, (const unsigned char *)p + bytes}); };
+          add(n.c->dw.split[l], octets * 48 * cols);
+          add(n.c->dw.scale[l], octets / 4 * 4 * cols);
+          for (int i = l; i < 3; i += 2) add(n.c->dw.octets[i], octets * 64 * n.c->net.Wd[i ? 1 : 0]);
+          if (l) add(n.c->dw.special, 4 * (SNN_MAXL + 1));
+        }
+        std::sort(parts.begin(), parts.end());
+        for (size_t i = 1; i < parts.size(); ++i) CHECK(parts[i - 1].second <= parts[i].first);
+        const bool own = n.c->dw_ws && parts[0].first == n.c->dw_ws;
+        const unsigned char *const base = own ? n.c->dw_ws : (const unsigned char *)n.c->dubuf;
+        CHECK(parts[0].first >= base + (own ? 0 : adjoint_work_bytes(n.c->net, F > n.cfg.T ? n.cfg.T : F)) && parts.back().second <= base + g_mem[(void *)base]);
+      }
 }
 
 // The activity that the kernels of the currents are chosen by is that of the last call, whatever the call and the batch size, and
@@ -400,7 +450,7 @@ int main(int argc, char **argv) {
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
                                               {"time_out_is_reported", time_out_is_reported},
                                               {"turns", turns}, {"blocks", blocks}, {"workspace", workspace},
-                                              {"rates", rates}, {"split_room", split_room}};
+                                              {"rates", rates}, {"split_room", split_room}, {"split_workspace", split_workspace}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

@@ -64,3 +64,7 @@ def test_activity_follows_every_call(checks):
 
 def test_gradients_do_not_follow_the_memory_that_is_free(checks):
     checks("split_room")
+
+
+def test_workspace_of_the_weight_gradients_is_part_of_the_step(checks):
+    checks("split_workspace")
