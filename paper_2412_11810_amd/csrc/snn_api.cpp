@@ -613,7 +613,9 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       c->ws.xg = (float *)((char *)blk + n_bar * sizeof(unsigned));
       c->ws.xg_stride = (int)xg_stride;
       HIPCHK(c, hipMemsetAsync(c->ws.bar, 0, n_bar * sizeof(unsigned), c->stream));
-      xl_bytes = (size_t)L * xg_stride * 4; // (one job per layer at most in a launch)
+      for (int l = 0; l < L; ++l) // (from 9 batch elements on as much as the adjoint's exchange where N is a multiple of 64, more elsewhere)
+        if (csr_by_column(n.N[l]) && B <= 32) c->ws.xl_col = std::max(c->ws.xl_col, seq_col_places(n.N[l], B, SNN_FWD_TILE));
+      xl_bytes = (size_t)L * std::max(xg_stride * 4, c->ws.xl_col); // (one job per layer at most in a launch)
       c->ws.err = c->ws.bar + 64 * SNN_MAXL;
       c->ws.posted = &c->die_posts;
       c->ws.max_groups = ws_max_resident_groups(cfg->device);

@@ -172,7 +172,9 @@ hipError_t launch_loss(const double *readout, const int32_t *labels, int B, int 
 // kernel (see k_adj_rec_ws); xg == NULL disables that kernel.
 struct WsArgs {
   float *xg;           // SNN_MAXL x [4][B in whole groups of 16][max N_l], one per job of a launch
-  float *xl;           // the same for the network's layers in ordinary memory, for workgroups that share a die
+  float *xl;           // the same for the network's layers in ordinary memory, for workgroups that share a die; and for
+                       // the sequential forward part by column, xl_col bytes per job of a launch of SNN_FWD_TILE steps
+  size_t xl_col;
   int xg_stride;       // floats between the exchange buffers of two jobs
   unsigned *bar;       // SNN_MAXL x [64] counters, zeroed before every launch
   unsigned *err;       // raised if a barrier gave up waiting

@@ -1247,7 +1247,6 @@ k_layer_seq_csr_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpe
 // for its neighbour's sake, say); the readers of a die share one fetch through its L2 (8192 neurons: 32 KB per workgroup and step).
 #define SNN_COL_GROUP 8 // entries per group of loads; columns are padded to whole groups
 #define SNN_COL_AHEAD 4 // groups in registers
-#define SNN_COL_LINE 128 // bytes of a cache line
 static __device__ __forceinline__ void col_add(uint32_t m, float w, float (&acc)[8]) {
   uint64_t p0, p1, p2, p3, p4, p5, p6, p7;
   asm volatile("v_lshlrev_b32 %0, 24, %0\n\t"
@@ -5762,7 +5761,6 @@ static int seq_csr_slices(const NetDev &net, const SeqJobs &ga, const WsArgs *ws
 
 // The sequential part by column (k_layer_seq_col): wavefronts per slice of 64 neurons (eight batch elements each); 0 if it cannot run
 // or does not pay.  Its time goes with the synapses of a neuron, that of the walk over rows with the active presynaptic neurons.
-#define SNN_COL_LDS(Wd) ((size_t)4 * (64 * (Wd) + 64))
 static int seq_col_per_cu(int device, int *n_cu) { // workgroups per compute unit, alone and (one more) in the stage launch
   static int cached[16] = {}, cus[16] = {};
   if (device < 0 || device >= 16) return 0;
@@ -5788,16 +5786,16 @@ static bool by_column_pays(const NetDev &net) { // one choice for the network, w
 }
 static int seq_col_waves(const NetDev &net, const SeqJobs &ga, const WsArgs *ws) {
   if (!ws || !ws->xg || !ws->xl || ga.count < 1 || net.B > 32 || (net.sel_seq != 0 && net.sel_seq != 3) || net.sel_slices != 0) return 0;
-  const int nq = net.B <= 8 ? 1 : net.B <= 16 ? 2 : 4;
+  const int nq = seq_col_waves_of(net.B);
   int Wd = 0;
   for (int i = 0; i < ga.count; ++i) {
     const int l = ga.j[i].l;
     if (!net.csr_ell[l]) return 0;
     Wd = std::max(Wd, net.Wd[l + 1]);
-    if ((size_t)(ga.j[i].t1 - ga.j[i].t0) * net.Wd[l + 1] * nq * SNN_COL_LINE > (size_t)ws->xg_stride * sizeof(float)) return 0; // a launch's places
+    if (seq_col_places(net.N[l], net.B, ga.j[i].t1 - ga.j[i].t0) > ws->xl_col) return 0;
   }
   if (net.sel_seq == 0 && !by_column_pays(net)) return 0;
-  if (SNN_COL_LDS(Wd) > SNN_FWD_STAGE_CSR_LDS || (size_t)ga.count * 4 * (Wd + 1) > (size_t)ws->xg_stride) return 0;
+  if (seq_col_lds(64 * Wd) > SNN_FWD_STAGE_CSR_LDS || (size_t)ga.count * 4 * (Wd + 1) > (size_t)ws->xg_stride) return 0;
   int device = 0, n_cu = 0;
   if (hipGetDevice(&device) != hipSuccess) return 0;
   return (Wd * nq + 3) / 4 * ga.count <= seq_col_per_cu(device, &n_cu) * n_cu ? nq : 0; // all resident: they wait for each other
@@ -5985,12 +5983,12 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
         if (e != hipSuccess) return e;
         unsigned char *const xl = reinterpret_cast<unsigned char *>(ws->xl);
         unsigned *const fl = reinterpret_cast<unsigned *>(ws->xg);
-        const size_t stride = (size_t)ws->xg_stride * sizeof(float);
+        const size_t stride = ws->xl_col;
         if (cj_fused.count)
           hipLaunchKernelGGL(k_fwd_stage_col, dim3(wgs * ga.count + gx * cj_fused.count), dim3(256), SNN_FWD_STAGE_CSR_LDS, s, net, ga, state, st,
                              by_col, xl, stride, fl, flags, ws->err, ws->spin_limit, cj_fused, wgs, (int)gx);
         else
-          hipLaunchKernelGGL(k_layer_seq_col, dim3(wgs, ga.count), dim3(256), SNN_COL_LDS(wd_max), s, net, ga, state, st, by_col, xl, stride, fl,
+          hipLaunchKernelGGL(k_layer_seq_col, dim3(wgs, ga.count), dim3(256), seq_col_lds(64 * wd_max), s, net, ga, state, st, by_col, xl, stride, fl,
                              flags, ws->err, ws->spin_limit);
       } else if (S_csr) {
         // tags of the exchange entries start from zero in every launch

@@ -8,6 +8,12 @@
 // ---- sequential forward part over compressed rows, by row or by column ----------------------------
 // Whether a masked matrix of N x N is also kept by column (k_layer_seq_col): 32 MB dense-stored and more.
 inline bool csr_by_column(int N) { return (size_t)N * N * sizeof(float) >= ((size_t)32 << 20); }
+// Wavefronts per slice of 64 neurons (eight batch elements each), the places of the spikes that a launch of `steps` steps
+// exchanges, a cache line per step, slice and wavefront (bytes), and the LDS of a workgroup.
+#define SNN_COL_LINE 128 // bytes of a cache line
+constexpr int seq_col_waves_of(int B) { return B <= 8 ? 1 : B <= 16 ? 2 : 4; }
+constexpr size_t seq_col_places(int N, int B, int steps) { return (size_t)steps * ((N + 63) / 64) * seq_col_waves_of(B) * SNN_COL_LINE; }
+constexpr size_t seq_col_lds(int N) { return (size_t)4 * (64 * ((N + 63) / 64) + 64); }
 // Which of the two walks for a network's n masked layers: the one over rows pays per active presynaptic neuron -- and much more where a
 // row's part of a sub-range of 512 columns has more entries than a wavefront has lanes --, the one over columns per synapse of a
 // neuron.  Forward passes over 64 steps, ms by row / by column:

@@ -420,6 +420,18 @@ static void split_workspace() {
       }
 }
 
+// A launch of the sequential forward part by column has places for its spikes whatever the width: for the longest tile of every layer
+static void column_places() {
+  for (int N : {2897, 2900, 3000, 4095, 4096, 8100, 8192})
+    for (int B : {1, 8, 9, 16, 20, 32}) {
+      Net n(N, 2, B, 1);
+      const size_t state = ((size_t)B * N * 4 + 255) & ~(size_t)255, slices = (N + 63) / 64, waves = B <= 8 ? 1 : B <= 16 ? 2 : 4;
+      CHECK(g_mem[n.c->cur_state] >= state + SNN_FWD_TILE * slices * waves * 128);
+      CHECK(n.c->ws.xl_col >= SNN_FWD_TILE * slices * waves * 128 && n.c->ws.xl_col % 128 == 0);
+      CHECK(g_mem[n.c->cur_state] >= state + n.c->ws.xl_col && g_mem[n.c->cur_state] >= state + (size_t)n.c->ws.xg_stride * 4);
+    }
+}
+
 // The activity that the kernels of the currents are chosen by is that of the last call, whatever the call and the batch size, and
 // stays while the new one is near it (a recorded step holds the choice)
 static void rates() {
@@ -450,7 +462,7 @@ int main(int argc, char **argv) {
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
                                               {"time_out_is_reported", time_out_is_reported},
                                               {"turns", turns}, {"blocks", blocks}, {"workspace", workspace},
-                                              {"rates", rates}, {"split_room", split_room}, {"split_workspace", split_workspace}};
+                                              {"rates", rates}, {"split_room", split_room}, {"split_workspace", split_workspace}, {"column_places", column_places}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

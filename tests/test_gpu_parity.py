@@ -801,7 +801,8 @@ def test_register_stationary_forward_widths(hidden, T):
 
 @pytest.mark.parametrize("hidden,B,T,density", [((2900,), 3, 40, 0.1),   # a ragged last slice, four slices per workgroup
                                                 ((3000, 2944), 12, 70, 0.3),  # two widths in a launch, batch elements to spare
-                                                ((2900, 2900), 20, 24, 0.05), ((4096,), 32, 33, 0.15)])
+                                                ((2900, 2900), 20, 24, 0.05), ((4096,), 32, 33, 0.15),
+                                                ((2900,), 20, 64, 0.1), ((3000,), 16, 64, 0.2)])  # the longest tile, widths between multiples of 64
 def test_sequential_forward_by_column(hidden, B, T, density, monkeypatch):
     """Wide layers over compressed rows by column (one neuron per lane, eight batch elements per wavefront): spikes, potentials and
     gradients of the walk over rows, bit for bit, with the currents of the next stage in the same launch and without, with

@@ -68,3 +68,7 @@ def test_gradients_do_not_follow_the_memory_that_is_free(checks):
 
 def test_workspace_of_the_weight_gradients_is_part_of_the_step(checks):
     checks("split_workspace")
+
+
+def test_exchange_of_the_forward_part_by_column_holds_the_longest_tile(checks):
+    checks("column_places")
