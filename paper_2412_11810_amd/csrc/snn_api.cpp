@@ -48,7 +48,7 @@ struct snn_ctx {
   uint16_t *csr_col[SNN_MAXL]{};
   float *csr_val[SNN_MAXL]{};
   uint64_t *csr_pk[SNN_MAXL]{};
-  size_t csr_nnz[SNN_MAXL]{}, csr_ell[SNN_MAXL]{};
+  size_t csr_nnz[SNN_MAXL]{}, csr_ell[SNN_MAXL]{}, csr_longest[SNN_MAXL]{}, csr_refused[SNN_MAXL]{};
   // fp64 gradient accumulators per existing synapse, in compressed-row order (k_dw_csr); csr_dw_ok: the entries
   // beyond the 64 per row and sub-range that kernel keeps in registers fit its LDS (64 per 16 rows and sub-range)
   double *acc_csr[SNN_MAXL]{};
@@ -235,6 +235,7 @@ void read_kernel_hooks(snn_ctx *c) {
     n.csr_val[l] = on ? c->csr_val[l] : nullptr;
     n.csr_nnz[l] = on ? (uint32_t)c->csr_nnz[l] : 0u;
     n.csr_ell[l] = on ? (uint32_t)c->csr_ell[l] : 0u;
+    n.csr_longest[l] = (uint32_t)c->csr_longest[l];
     n.csr_pk[l] = on ? c->csr_pk[l] : nullptr;
   }
   if (const char *e = std::getenv("SNN_CURRENTS"))
@@ -364,18 +365,22 @@ void free_csr(snn_ctx *c, int l) {
 // Compressed rows of a masked recurrent matrix (layout: NetDev::csr_sub).  An entry exists where the mask says a
 // synapse exists, whatever its weight; its order inside a row is the ascending postsynaptic index.  Built on the GPU
 // from the context's own copies of mask and weights; the arrays stay while the number of synapses does (a training loop
-// that hands over new weights under the same mask).  A matrix that cannot be compressed is left without the form.
+// that hands over new weights under the same mask).  A matrix that cannot be compressed is left without the form.  Masks of few synapses
+// that are spread over the columns are also kept by column (csr_column_form), where the device has the room.
 snn_status build_csr(snn_ctx *c, int l) {
   const int N = c->net.N[l], nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
-  unsigned long long *out = c->counters; // at least two words
-  unsigned long long found[2] = {0, 0};
+  unsigned long long *out = c->counters; // at least four words
+  unsigned long long found[4] = {0, 0, 0, 0};
   hipError_t e = hipSuccess;
-  const size_t slices = csr_by_column(N) ? (size_t)(N + 63) / 64 : 0; // of the form by column: their positions follow
+  // the form by column, where the kernel for it can run: its positions follow
+  const bool columns = c->ws.xl && csr_by_column(N, c->net.B);
+  const size_t slices = columns ? (size_t)(N + 63) / 64 : 0;
   if (!c->csr_sub[l]) e = hipMalloc(&c->csr_sub[l], ((size_t)N * (nsub + 1) + slices * 257 + 1) * 4);
-  if (e == hipSuccess) e = launch_csr_count(c->rec_mask[l], N, c->csr_sub[l], out, c->stream);
+  if (e == hipSuccess) e = launch_csr_count(c->rec_mask[l], N, c->csr_sub[l], out, columns, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(found, out, sizeof found, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  const size_t nnz = (size_t)found[0], ell = slices ? (size_t)(found[1] >> 32) : 0;
+  const size_t nnz = (size_t)found[0];
+  size_t ell = columns && csr_column_form(N, nnz, (size_t)found[2]) && c->csr_refused[l] != nnz + 1 ? (size_t)found[2] : 0;
   if (e == hipSuccess && nnz > 0x1FF00000ull) {
     free_csr(c, l);
     return fail(c, SNN_E_INVAL, "recurrent matrix has too many synapses for 32-bit byte offsets of its entries");
@@ -383,20 +388,28 @@ snn_status build_csr(snn_ctx *c, int l) {
   if (e == hipSuccess && (!c->csr_pk[l] || c->csr_nnz[l] != nnz || c->csr_ell[l] != ell)) {
     (void)hipFree(c->csr_col[l]); (void)hipFree(c->csr_val[l]); (void)hipFree(c->csr_pk[l]); (void)hipFree(c->acc_csr[l]);
     c->csr_col[l] = nullptr; c->csr_val[l] = nullptr; c->csr_pk[l] = nullptr; c->acc_csr[l] = nullptr;
+    const size_t packed = (nnz + (size_t)nsub * 64) * 8;
     e = hipMalloc(&c->csr_col[l], (nnz + 1) * 2);
     if (e == hipSuccess) e = hipMalloc(&c->csr_val[l], (nnz + 1) * 4);
     if (e == hipSuccess) e = hipMalloc(&c->acc_csr[l], (nnz + 1) * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&c->csr_pk[l], (nnz + (size_t)nsub * 64 + ell * 8 * 64) * 8);
+    if (e == hipSuccess) e = hipMalloc(&c->csr_pk[l], packed + ell * SNN_COL_GROUP * 64 * 8);
+    if (e != hipSuccess && ell && c->acc_csr[l]) { // no room for the form by column: without it, while the mask has as many synapses
+      (void)hipGetLastError();
+      c->csr_refused[l] = nnz + 1;
+      ell = 0;
+      e = hipMalloc(&c->csr_pk[l], packed);
+    }
   }
   if (e == hipSuccess)
-    e = launch_csr_fill(c->rec_mask[l], c->W_rec[l], N, (uint32_t)nnz, c->csr_sub[l], c->csr_col[l], c->csr_val[l], c->csr_pk[l], c->stream);
+    e = launch_csr_fill(c->rec_mask[l], c->W_rec[l], N, (uint32_t)nnz, c->csr_sub[l], c->csr_col[l], c->csr_val[l], c->csr_pk[l], ell != 0, c->stream);
   if (e != hipSuccess) {
     free_csr(c, l);
     return fail(c, SNN_E_HIP, std::string("compressed rows: ") + hipGetErrorString(e));
   }
-  c->csr_dw_ok[l] = (uint32_t)found[1] == 0;
+  c->csr_dw_ok[l] = found[1] == 0;
   c->csr_nnz[l] = nnz;
   c->csr_ell[l] = ell;
+  c->csr_longest[l] = ell ? (size_t)found[3] * SNN_COL_GROUP : 0;
   return SNN_OK;
 }
 
@@ -614,7 +627,7 @@ snn_status snn_init(const snn_config *cfg, snn_ctx **out) {
       c->ws.xg_stride = (int)xg_stride;
       HIPCHK(c, hipMemsetAsync(c->ws.bar, 0, n_bar * sizeof(unsigned), c->stream));
       for (int l = 0; l < L; ++l) // (from 9 batch elements on as much as the adjoint's exchange where N is a multiple of 64, more elsewhere)
-        if (csr_by_column(n.N[l]) && B <= 32) c->ws.xl_col = std::max(c->ws.xl_col, seq_col_places(n.N[l], B, SNN_FWD_TILE));
+        if (csr_by_column(n.N[l], B)) c->ws.xl_col = std::max(c->ws.xl_col, seq_col_places(n.N[l], B, SNN_FWD_TILE));
       xl_bytes = (size_t)L * std::max(xg_stride * 4, c->ws.xl_col); // (one job per layer at most in a launch)
       c->ws.err = c->ws.bar + 64 * SNN_MAXL;
       c->ws.posted = &c->die_posts;

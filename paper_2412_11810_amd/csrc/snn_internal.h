@@ -50,7 +50,7 @@ struct NetDev {
   // the 64 spare words that follow the SNN_CSR_SUBW accumulators of sub-range r in LDS.
   const uint64_t *csr_pk[SNN_MAXL];
   // ... and once more by column, behind the packed copy (see k_ell_fill), positions behind csr_sub's: groups of entries in all (0: not kept)
-  uint32_t csr_ell[SNN_MAXL];
+  uint32_t csr_ell[SNN_MAXL], csr_longest[SNN_MAXL]; // and entries of the fullest slice
   float alpha, beta, theta, k;
   float win;  // surrogate window (<= 0: none)
   // Current kernel for the layers whose weights are far beyond the L2, from the firing rates of the last step
@@ -149,7 +149,7 @@ hipError_t launch_forward(const NetDev &net, const int *bounds, int n_tiles, flo
 // Recompute pass over steps t0+1..t1 from state_in = x_{t0}, spikes read from the stored bitmasks:
 // currents of the whole range in parallel into buf (slot of x_t = t - t_base - 1), then a scan that
 // turns them into states in place (store_all) and/or writes x_{t1} to state_out.
-unsigned currents_choice(const NetDev &net, int chunk); // bits: lists for a forward stage, for the recompute of a chunk; masked layers by column
+unsigned currents_choice(const NetDev &net, int chunk); // bits: lists for a forward stage, for the recompute of a chunk; layers of a stage by column
 size_t currents_lists_entries(const NetDev &net); // of that space: SNN_LIST_STEPS steps of every layer; 0: never used
 #define SNN_LIST_STEPS 64
 hipError_t launch_recompute(const NetDev &net, int t0, int t1, const float *state_in, float *buf, int t_base,
@@ -274,10 +274,10 @@ hipError_t launch_bwd_stage(const NetDev &net, const AdjJobs &jobs, float *carry
 hipError_t launch_bwd_inter(const NetDev &net, InterJobs ij, hipStream_t s, const SpanHook *hook = nullptr);
 hipError_t launch_transpose(const float *src, float *dst, int rows, int cols, hipStream_t s);
 // Compressed rows of a masked recurrent matrix, in two parts: counts and row ends into sub, {synapses, sub-ranges that are
-// too full for k_dw_csr (low half) and groups of the form by column (high half)} into out (device); then, with the arrays sized for them, positions and entries.
-hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, hipStream_t s);
+// too full for k_dw_csr, groups of the form by column and of its fullest slice (columns: else as they were)} into out (device); then, with the arrays sized for them, positions and entries.
+hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, bool columns, hipStream_t s);
 hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t nnz, uint32_t *sub, uint16_t *col, float *val,
-                           uint64_t *pk, hipStream_t s);
+                           uint64_t *pk, bool columns, hipStream_t s);
 // dW = the accumulators rounded to fp32, zero where a mask says so, for every matrix of a step in one launch
 struct FinishJob { const double *acc; const uint8_t *mask; float *dW; size_t n; unsigned first; }; // first: set by the launcher
 struct FinishJobs { FinishJob j[2 * SNN_MAXL + 1]; int count; };

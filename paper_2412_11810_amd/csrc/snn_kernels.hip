@@ -1245,7 +1245,6 @@ k_layer_seq_csr_sl(NetDev net, SeqJobs jobs, float *__restrict__ state, StoreSpe
 // wavefront in uncached memory; who has seen all flags reads the bytes with ordinary loads.  A place is written once per launch
 // and a wavefront's 64 bytes have a cache line to themselves, so no cache can hold an older value of them (one that had been read
 // for its neighbour's sake, say); the readers of a die share one fetch through its L2 (8192 neurons: 32 KB per workgroup and step).
-#define SNN_COL_GROUP 8 // entries per group of loads; columns are padded to whole groups
 #define SNN_COL_AHEAD 4 // groups in registers
 static __device__ __forceinline__ void col_add(uint32_t m, float w, float (&acc)[8]) {
   uint64_t p0, p1, p2, p3, p4, p5, p6, p7;
@@ -5036,7 +5035,7 @@ __global__ void __launch_bounds__(1024) k_ell_count(const uint8_t *__restrict__ 
   (void)ell_count(mask, N, cnt, &all);
   if (threadIdx.x < WAVE) eoff[gridDim.x + 1 + (blockIdx.x * ELL_QUARTERS + blockIdx.y) * WAVE + threadIdx.x] = all;
 }
-__global__ void __launch_bounds__(1024) k_ell_scan(int slices, uint32_t *__restrict__ eoff, unsigned long long *__restrict__ out) {
+__global__ void __launch_bounds__(1024) k_ell_scan(int slices, uint32_t *__restrict__ eoff, unsigned long long *__restrict__ out) { // {groups, of the fullest slice}
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   for (int i = wave; i < slices; i += 16) {
     uint32_t all = 0;
@@ -5046,9 +5045,10 @@ __global__ void __launch_bounds__(1024) k_ell_scan(int slices, uint32_t *__restr
   }
   __syncthreads();
   if (wave != 0) return;
-  uint32_t sum = 0;
+  uint32_t sum = 0, most = 0;
   for (int i0 = 0; i0 < slices; i0 += WAVE) {
     const uint32_t n = i0 + lane < slices ? eoff[i0 + lane] : 0u;
+    most = max(most, n);
     uint32_t x = n;
     for (int d = 1; d < WAVE; d <<= 1) {
       const uint32_t y = (uint32_t)__shfl_up((int)x, d);
@@ -5057,9 +5057,11 @@ __global__ void __launch_bounds__(1024) k_ell_scan(int slices, uint32_t *__restr
     if (i0 + lane < slices) eoff[i0 + lane] = sum + x - n;
     sum += (uint32_t)__shfl((int)x, WAVE - 1);
   }
+  for (int d = 1; d < WAVE; d <<= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d));
   if (lane == 0) {
     eoff[slices] = sum;
-    out[1] |= (unsigned long long)sum << 32;
+    out[0] = sum;
+    out[1] = most;
   }
 }
 __global__ void __launch_bounds__(1024)
@@ -5795,7 +5797,8 @@ static int seq_col_waves(const NetDev &net, const SeqJobs &ga, const WsArgs *ws)
     if (seq_col_places(net.N[l], net.B, ga.j[i].t1 - ga.j[i].t0) > ws->xl_col) return 0;
   }
   if (net.sel_seq == 0 && !by_column_pays(net)) return 0;
-  if (seq_col_lds(64 * Wd) > SNN_FWD_STAGE_CSR_LDS || (size_t)ga.count * 4 * (Wd + 1) > (size_t)ws->xg_stride) return 0;
+  static_assert(SNN_COL_LDS_MAX == SNN_FWD_STAGE_CSR_LDS, "what the stage launch asks for");
+  if (seq_col_lds(64 * Wd) > SNN_COL_LDS_MAX || (size_t)ga.count * 4 * (Wd + 1) > (size_t)ws->xg_stride) return 0;
   int device = 0, n_cu = 0;
   if (hipGetDevice(&device) != hipSuccess) return 0;
   return (Wd * nq + 3) / 4 * ga.count <= seq_col_per_cu(device, &n_cu) * n_cu ? nq : 0; // all resident: they wait for each other
@@ -6946,23 +6949,23 @@ hipError_t launch_transpose(const float *src, float *dst, int rows, int cols, hi
   return hipGetLastError();
 }
 
-hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, hipStream_t s) {
+hipError_t launch_csr_count(const uint8_t *mask, int N, uint32_t *sub, unsigned long long *out, bool columns, hipStream_t s) {
   const int nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
   hipLaunchKernelGGL(k_csr_count, dim3(N), dim3(256), 0, s, mask, N, nsub, sub);
   hipLaunchKernelGGL(k_csr_scan, dim3(1), dim3(1024), 0, s, N, nsub, sub, out);
-  if (csr_by_column(N)) {
+  if (columns) {
     const int slices = (N + WAVE - 1) / WAVE;
     uint32_t *const eoff = sub + (size_t)N * (nsub + 1);
     hipLaunchKernelGGL(k_ell_count, dim3(slices, ELL_QUARTERS), dim3(1024), 0, s, mask, N, eoff);
-    hipLaunchKernelGGL(k_ell_scan, dim3(1), dim3(1024), 0, s, slices, eoff, out);
+    hipLaunchKernelGGL(k_ell_scan, dim3(1), dim3(1024), 0, s, slices, eoff, out + 2);
   }
   return hipGetLastError();
 }
 hipError_t launch_csr_fill(const uint8_t *mask, const float *W, int N, uint32_t nnz, uint32_t *sub, uint16_t *col, float *val,
-                           uint64_t *pk, hipStream_t s) {
+                           uint64_t *pk, bool columns, hipStream_t s) {
   const int nsub = (N + SNN_CSR_SUBW - 1) / SNN_CSR_SUBW;
   hipLaunchKernelGGL(k_csr_fill, dim3(N), dim3(256), 0, s, mask, W, N, nsub, nnz, sub, col, val, pk);
-  if (csr_by_column(N))
+  if (columns)
     hipLaunchKernelGGL(k_ell_fill, dim3((N + WAVE - 1) / WAVE, ELL_QUARTERS), dim3(1024), 0, s, mask, W, N, sub + (size_t)N * (nsub + 1),
                        reinterpret_cast<uint2 *>(pk + nnz + (size_t)nsub * 64));
   return hipGetLastError();

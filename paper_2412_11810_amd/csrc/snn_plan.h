@@ -5,15 +5,24 @@
 
 #define SNN_LDS_PER_CU (160 * 1024)
 
-// ---- sequential forward part over compressed rows, by row or by column ----------------------------
-// Whether a masked matrix of N x N is also kept by column (k_layer_seq_col): 32 MB dense-stored and more.
-inline bool csr_by_column(int N) { return (size_t)N * N * sizeof(float) >= ((size_t)32 << 20); }
+// ---- sequential forward part of masked layers, by column (k_layer_seq_col) ------------------------
 // Wavefronts per slice of 64 neurons (eight batch elements each), the places of the spikes that a launch of `steps` steps
 // exchanges, a cache line per step, slice and wavefront (bytes), and the LDS of a workgroup.
 #define SNN_COL_LINE 128 // bytes of a cache line
+#define SNN_COL_GROUP 8  // entries per group of loads; columns are padded to whole groups
+#define SNN_COL_LDS_MAX ((size_t)34816) // of the stage launch (k_fwd_stage_col), whose currents want as much
 constexpr int seq_col_waves_of(int B) { return B <= 8 ? 1 : B <= 16 ? 2 : 4; }
 constexpr size_t seq_col_places(int N, int B, int steps) { return (size_t)steps * ((N + 63) / 64) * seq_col_waves_of(B) * SNN_COL_LINE; }
 constexpr size_t seq_col_lds(int N) { return (size_t)4 * (64 * ((N + 63) / 64) + 64); }
+// Whether a masked matrix of N x N is also kept by column: 32 MB dense-stored and more, where the kernel can run, ...
+inline bool csr_by_column(int N, int B) {
+  return (size_t)N * N * sizeof(float) >= ((size_t)32 << 20) && B <= 32 && seq_col_lds(N) <= SNN_COL_LDS_MAX;
+}
+// ... and with `groups` groups of 64 columns in all: no more than two of five synapses exist (beyond, the walk over the dense-stored matrix is
+// ahead but for a few percent) and padding takes no more than the entries do.
+inline bool csr_column_form(int N, size_t nnz, size_t groups) {
+  return nnz * 5 <= (size_t)N * N * 2 && groups * SNN_COL_GROUP * 64 <= 2 * nnz + (size_t)((N + 63) / 64) * SNN_COL_GROUP * 64;
+}
 // Which of the two walks for a network's n masked layers: the one over rows pays per active presynaptic neuron -- and much more where a
 // row's part of a sub-range of 512 columns has more entries than a wavefront has lanes --, the one over columns per synapse of a
 // neuron.  Forward passes over 64 steps, ms by row / by column:

@@ -151,8 +151,17 @@ hipError_t launch_bwd_stage(const NetDev &, const AdjJobs &, float *, DwBatch, D
 }
 hipError_t launch_bwd_inter(const NetDev &, InterJobs, hipStream_t, const SpanHook *) { return hipSuccess; }
 hipError_t launch_transpose(const float *, float *, int, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_csr_count(const uint8_t *, int, uint32_t *, unsigned long long *, hipStream_t) { return hipSuccess; }
-hipError_t launch_csr_fill(const uint8_t *, const float *, int, uint32_t, uint32_t *, uint16_t *, float *, uint64_t *, hipStream_t) { return hipSuccess; }
+static unsigned long long g_mask[3]; // synapses, groups by column, of the fullest slice
+static int g_column_counts = 0, g_column_fills = 0;
+hipError_t launch_csr_count(const uint8_t *, int, uint32_t *, unsigned long long *out, bool columns, hipStream_t s) {
+  g_column_counts += columns;
+  put(s, [=] { out[0] = g_mask[0]; out[1] = 0; if (columns) { out[2] = g_mask[1]; out[3] = g_mask[2]; } });
+  return hipSuccess;
+}
+hipError_t launch_csr_fill(const uint8_t *, const float *, int, uint32_t, uint32_t *, uint16_t *, float *, uint64_t *, bool columns, hipStream_t) {
+  g_column_fills += columns;
+  return hipSuccess;
+}
 hipError_t launch_finish_grads(FinishJobs, hipStream_t) { return hipSuccess; }
 hipError_t launch_finish_grad_csr(const double *, const uint32_t *, const uint16_t *, int, float *, hipStream_t) { return hipSuccess; }
 hipError_t launch_unpack_spikes(const uint64_t *, int, int, int, int, uint8_t *, hipStream_t) { return hipSuccess; }
@@ -432,6 +441,40 @@ static void column_places() {
     }
 }
 
+// The form by column of a masked matrix is kept where its kernel can run, the mask suits it and the device has the room; handing weights over
+// does not fail for it
+static void column_form() {
+  const auto kept = [](int N, int B, double density, double groups_per_slice, size_t room = ~(size_t)0) {
+    Net n(N, 2, B, 1);
+    g_mask[0] = (unsigned long long)(density * N * N);
+    g_mask[1] = (unsigned long long)(groups_per_slice * ((N + 63) / 64));
+    g_mask[2] = (unsigned long long)groups_per_slice;
+    std::vector<float> w((size_t)N * N);
+    std::vector<uint8_t> mask((size_t)N * N, 1);
+    g_largest = room;
+    int fills[2];
+    for (int k = 0; k < 2; ++k) { // handed over once more
+      g_column_fills = 0;
+      CHECK(snn_set_weights(n.c, SNN_W_REC, 0, w.data(), mask.data()) == SNN_OK);
+      fills[k] = g_column_fills;
+    }
+    g_largest = ~(size_t)0;
+    CHECK(n.c->csr_pk[0] && n.c->csr_nnz[0] == g_mask[0] && fills[0] == fills[1] && fills[0] == (n.c->csr_ell[0] > 0));
+    CHECK(n.c->csr_longest[0] == (n.c->csr_ell[0] ? 8 * g_mask[2] : 0));
+    return n.c->csr_ell[0] > 0;
+  };
+  const int N = 4096;
+  CHECK(kept(N, 32, 0.1, 58) && kept(N, 1, 0.01, 8) && kept(2897, 16, 0.3, 115) && kept(8192, 8, 0.002, 4));
+  g_column_counts = 0;
+  CHECK(!kept(2800, 32, 0.1, 40) && !kept(N, 33, 0.1, 58) && !kept(8700, 8, 0.002, 5) && g_column_counts == 0);
+  CHECK(!kept(N, 32, 0.5, 260) && !kept(N, 32, 0.1, 512)); // the dense-stored walk is ahead; a full column in every slice
+  setenv("SNN_NO_WS", "1", 1);
+  g_column_counts = 0;
+  CHECK(!kept(N, 32, 0.1, 58) && g_column_counts == 0);
+  unsetenv("SNN_NO_WS");
+  CHECK(!kept(N, 32, 0.2, 115, (size_t)(0.2 * N * N) * 8 + (1 << 20))); // room for the packed rows alone
+}
+
 // The activity that the kernels of the currents are chosen by is that of the last call, whatever the call and the batch size, and
 // stays while the new one is near it (a recorded step holds the choice)
 static void rates() {
@@ -462,7 +505,7 @@ int main(int argc, char **argv) {
   const std::map<std::string, void (*)()> checks{{"caller_stream", caller_stream}, {"no_room_for_staging", no_room_for_staging}, {"copy_fails", copy_fails},
                                               {"time_out_is_reported", time_out_is_reported},
                                               {"turns", turns}, {"blocks", blocks}, {"workspace", workspace},
-                                              {"rates", rates}, {"split_room", split_room}, {"split_workspace", split_workspace}, {"column_places", column_places}};
+                                              {"rates", rates}, {"split_room", split_room}, {"split_workspace", split_workspace}, {"column_places", column_places}, {"column_form", column_form}};
   const auto it = checks.find(argc > 1 ? argv[1] : "");
   if (it == checks.end()) return 2;
   it->second();

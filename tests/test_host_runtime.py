@@ -72,3 +72,7 @@ def test_workspace_of_the_weight_gradients_is_part_of_the_step(checks):
 
 def test_exchange_of_the_forward_part_by_column_holds_the_longest_tile(checks):
     checks("column_places")
+
+
+def test_form_by_column_only_where_it_can_be_used(checks):
+    checks("column_form")
