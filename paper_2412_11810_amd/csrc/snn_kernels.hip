@@ -5442,7 +5442,7 @@ static bool lists_run(const NetDev &net, const CurJobs &jobs, CurJobs *mine, Cur
   }
   return net.sel_currents == 4 || lists_pay(net, *mine, *most);
 }
-static bool by_column_pays(const NetDev &net);
+static bool by_column_pays(const NetDev &net, unsigned layers, bool rows);
 unsigned currents_choice(const NetDev &net, int chunk) {
   CurJobs fwd{}, rec{};
   for (int l = 0; l < net.L; ++l) {
@@ -5452,7 +5452,10 @@ unsigned currents_choice(const NetDev &net, int chunk) {
   }
   CurJobs mine{}, rest{}, mine_r{}, rest_r{};
   int most;
-  return (by_column_pays(net) ? 4u : 0u) | (lists_run(net, fwd, &mine, &rest, &most) ? 1u : 0u) | (lists_run(net, rec, &mine_r, &rest_r, &most) ? 2u : 0u);
+  unsigned cols = 0u;
+  for (unsigned layers = 1; layers < 1u << SNN_MAXL; ++layers) // every set of layers that a stage may have
+    cols |= ((by_column_pays(net, layers, true) ? 1u : 0u) | (by_column_pays(net, layers, false) ? 2u : 0u)) << (2 * layers);
+  return cols | (lists_run(net, fwd, &mine, &rest, &most) ? 1u : 0u) | (lists_run(net, rec, &mine_r, &rest_r, &most) ? 2u : 0u);
 }
 static hipError_t launch_currents_lists(const NetDev &net, CurJobs *jobs, hipStream_t s) {
   CurJobs mine{}, rest{};
@@ -5779,24 +5782,29 @@ static int seq_col_per_cu(int device, int *n_cu) { // workgroups per compute uni
   *n_cu = cus[device];
   return cached[device] > 0 ? cached[device] : 0;
 }
-static bool by_column_pays(const NetDev &net) { // one choice for the network, whichever of its layers a stage has
+static bool by_column_pays(const NetDev &net, unsigned layers, bool rows) { // layers: a bit each; rows: the walk that else runs
   MaskedLayer m[SNN_MAXL];
   int n = 0;
-  for (int l = 0; l < net.L; ++l)
-    if (net.csr_ell[l]) m[n++] = MaskedLayer{net.N[l], net.csr_nnz[l], net.rate[l + 1]};
-  return seq_by_column(m, n);
+  for (int l = 0; l < SNN_MAXL; ++l)
+    if (layers >> l & 1u) {
+      if (l >= net.L || !net.csr_ell[l]) return false;
+      m[n++] = MaskedLayer{net.N[l], net.csr_nnz[l], (int)net.csr_longest[l], net.rate[l + 1]};
+    }
+  return seq_by_column(m, n, net.B, rows);
 }
 static int seq_col_waves(const NetDev &net, const SeqJobs &ga, const WsArgs *ws) {
   if (!ws || !ws->xg || !ws->xl || ga.count < 1 || net.B > 32 || (net.sel_seq != 0 && net.sel_seq != 3) || net.sel_slices != 0) return 0;
   const int nq = seq_col_waves_of(net.B);
   int Wd = 0;
+  unsigned layers = 0u;
   for (int i = 0; i < ga.count; ++i) {
     const int l = ga.j[i].l;
     if (!net.csr_ell[l]) return 0;
+    layers |= 1u << l;
     Wd = std::max(Wd, net.Wd[l + 1]);
     if (seq_col_places(net.N[l], net.B, ga.j[i].t1 - ga.j[i].t0) > ws->xl_col) return 0;
   }
-  if (net.sel_seq == 0 && !by_column_pays(net)) return 0;
+  if (net.sel_seq == 0 && !by_column_pays(net, layers, seq_csr_slices(net, ga, ws) > 0)) return 0;
   static_assert(SNN_COL_LDS_MAX == SNN_FWD_STAGE_CSR_LDS, "what the stage launch asks for");
   if (seq_col_lds(64 * Wd) > SNN_COL_LDS_MAX || (size_t)ga.count * 4 * (Wd + 1) > (size_t)ws->xg_stride) return 0;
   int device = 0, n_cu = 0;

@@ -23,27 +23,40 @@ inline bool csr_by_column(int N, int B) {
 inline bool csr_column_form(int N, size_t nnz, size_t groups) {
   return nnz * 5 <= (size_t)N * N * 2 && groups * SNN_COL_GROUP * 64 <= 2 * nnz + (size_t)((N + 63) / 64) * SNN_COL_GROUP * 64;
 }
-// Which of the two walks for a network's n masked layers: the one over rows pays per active presynaptic neuron -- and much more where a
-// row's part of a sub-range of 512 columns has more entries than a wavefront has lanes --, the one over columns per synapse of a
-// neuron.  Forward passes over 64 steps, ms by row / by column:
-//   4 x 8192, density 0.1, batch 32   mean activity 5.1 %: 14.6 / 17.4    9.8 %: 21.0 / 17.4    20 %: 31.6 / 17.5
-//   the same, batch 8                               5.1 %: 8.7 / 11.5     9.8 %: 14.6 / 11.6    20 %: 25.6 / 11.6
-//   2 x 8192, density 0.05, batch 32                4.2 %: 5.5 / 6.2      6.0 %: 6.5 / 6.3      9.2 %: 8.4 / 6.3
-//   2 x 8192, density 0.2, batch 32                 5.2 %: 21.7 / 14.6    8.0 %: 31.6 / 14.6    14 %: 46.3 / 14.6
-//   3 x 4096, density 0.1, batch 32                 3.3 %: 5.5 / 8.4      7.9 %: 8.4 / 8.4      14 %: 12.2 / 8.4
-//   8192, density 0.1, batch 32                     4.3 %: 3.3 / 4.9      7.5 %: 4.7 / 4.9
-// (they meet at 5.6 % for density 0.05, 7 to 8 % for 0.1.)  10 % stand in for an activity that is not known (< 0): of the two, the wrong
-// walk over columns costs less.
-struct MaskedLayer { int N; size_t nnz; double rate; };
-inline bool seq_by_column(const MaskedLayer *layers, int n) {
-  double rate = 0.0, density = 0.0;
+// The layers of a launch: synapses, entries of the fullest slice of 64 columns (whole groups), activity (< 0: not known).
+struct MaskedLayer { int N; size_t nnz; int longest; double rate; };
+// Is the walk by column the faster one for a launch over these layers?  Estimates of a step, in us.  By column every wavefront passes
+// its slice's entries whatever the activity, and all wait for the fullest slice.  By row (`rows`, or else the walk over the dense-stored
+// matrix, whichever would run) a workgroup passes the active presynaptic neurons, over compressed rows one entry per lane and sub-range of 512 columns
+// at a time -- a row with more entries there costs much more --, over the dense-stored matrix bound by its bytes, of all layers and
+// batch elements, where it is larger than the caches (13 TB/s, 27 where the batch elements share its rows), or by its rows one after the other.
+// Forward passes over 64 steps, ms by column / rows /
+// dense-stored:
+//   8192, batch 32       density 0.05  4 %  2.7 / 2.3 / 2.6    19 %  2.9 / 6.8 / 9.2     0.1  8 %  4.5 / 4.6 / 4.9    18 %  4.7 / 8.8 / 9.1
+//                        0.3           8 % 11.7 /  31 / 4.8    38 % 11.9 / 103 / 8.1     0.9  4 %  32 / 65 / 2.6
+//   4 x 8192, batch 32   0.1           4 %   17 / 12 / 18      19 %   17 / 31 / 43       0.3 19 %  35 / 176 / 44       0.5 34 %  52 / 455 / 49
+//   2 x 8192, batch 8    0.1           4 %  6.8 / 4.4 / 5.1    11 %  6.9 / 9.7 / 8.5     0.3 11 %  18 / 73 / 8.4
+//   3 x 4096, batch 32   0.1           4 %  8.3 / 5.8 / 2.6    15 %  8.4 / 13 / 4.3      0.3 15 %  19 / 74 / 4.3
+//   3 x 4096, batch 32, density 0.1 and one neuron with every synapse  15 %  53 / 13 / 4.3
+// An activity that is not known: the walk by row.
+inline bool seq_by_column(const MaskedLayer *layers, int n, int B, bool rows) {
+  double col = 0.0, row = 0.0, dense = 0.0, rows_of_one = 0.0;
   for (int i = 0; i < n; ++i) {
-    rate += (layers[i].rate < 0.0 ? 0.1 : layers[i].rate) / n;
-    density += (double)layers[i].nnz / ((double)layers[i].N * layers[i].N) / n;
+    const MaskedLayer &l = layers[i];
+    if (l.rate < 0.0 || l.longest <= 0) return false;
+    const double active = l.rate * l.N, e = 512.0 * (double)l.nnz / ((double)l.N * l.N); // a row's entries in a sub-range
+    const double per_row = e <= 40.0 ? 0.06 : e <= 60.0 ? 0.06 + 0.002 * (e - 40.0) : 0.0054 * e - 0.15;
+    const double c = 0.065 * l.longest, r = 3.0 + active * (per_row < 0.06 ? 0.06 : per_row);
+    col = c > col ? c : col;
+    row = r > row ? r : row;
+    const double bytes = (double)l.N * sizeof(float), rate = l.rate < 0.2 ? 0.0 : l.rate - 0.2;
+    const double tb_s = bytes * l.N < 2e8 ? 100.0 : rate > 0.18 ? 27.0 : 13.0 + 75.0 * rate;
+    const double chain = active * (l.N > 4096 ? 0.04 : 0.015);
+    dense += active * bytes * B / (1e6 * tb_s);
+    rows_of_one = chain > rows_of_one ? chain : rows_of_one;
   }
-  if (n <= 0) return false;
-  const double meet = 0.035 + 0.42 * density;
-  return rate >= (512.0 * density > 56.0 ? 0.25 * meet : meet);
+  if (dense < rows_of_one) dense = rows_of_one;
+  return n > 0 && 11.0 + col < 0.95 * (rows ? 11.0 + row : 8.0 + dense);
 }
 
 // ---- inter-layer products of the adjoint pass -----------------------------------------------------
