@@ -723,19 +723,21 @@ snn_status snn_set_weights(snn_ctx *c, int kind, int layer, const float *w, cons
   }
   if (mask && kind != SNN_W_REC) return fail(c, SNN_E_INVAL, "mask only for recurrent matrices");
   // A recorded step reads the weights where they always are, so new values need no new recording (700-2x256-20, 38 launches:
-  // 2.73 -> 2.61 ms per pass with a hand-over; 90-200-75-11, 75 launches and copies: 1.71 -> 1.30; 512-2x2048-20 over 2000 steps: 40.9 -> 38.5).  What it holds of a recurrent matrix's form -- the mask, the compressed rows, how many synapses, whether
-  // their gradients go by them -- does: the recording is dropped when any of it has changed, also if the call fails.
+  // 2.73 -> 2.61 ms per pass with a hand-over; 90-200-75-11, 75 launches and copies: 1.71 -> 1.30; 512-2x2048-20 over 2000 steps:
+  // 40.9 -> 38.5).  What it holds of a recurrent matrix's form -- the mask, the compressed rows, how many synapses, whether
+  // their gradients go by them, the form by column -- does: the recording is dropped when any of it has changed, also if the call fails.
   struct Form {
     snn_ctx *c; int l;
-    const void *p[6]; size_t nnz; bool dw;
+    const void *p[6]; size_t nnz, ell; bool dw;
     static Form of(snn_ctx *c, int l) {
-      if (l < 0) return Form{c, l, {}, 0, false};
-      return Form{c, l, {c->rec_mask[l], c->csr_sub[l], c->csr_col[l], c->csr_val[l], c->csr_pk[l], c->acc_csr[l]}, c->csr_nnz[l], c->csr_dw_ok[l]};
+      if (l < 0) return Form{c, l, {}, 0, 0, false};
+      return Form{c, l, {c->rec_mask[l], c->csr_sub[l], c->csr_col[l], c->csr_val[l], c->csr_pk[l], c->acc_csr[l]}, c->csr_nnz[l], c->csr_ell[l],
+                  c->csr_dw_ok[l]};
     }
     ~Form() {
       if (l < 0 || !c->graph_exec) return;
       const void *const now[6] = {c->rec_mask[l], c->csr_sub[l], c->csr_col[l], c->csr_val[l], c->csr_pk[l], c->acc_csr[l]};
-      if (std::equal(p, p + 6, now) && nnz == c->csr_nnz[l] && dw == c->csr_dw_ok[l]) return;
+      if (std::equal(p, p + 6, now) && nnz == c->csr_nnz[l] && ell == c->csr_ell[l] && dw == c->csr_dw_ok[l]) return;
       (void)hipStreamSynchronize(c->stream);
       (void)hipGraphExecDestroy(c->graph_exec);
       c->graph_exec = nullptr;

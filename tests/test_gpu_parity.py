@@ -1177,11 +1177,16 @@ def test_graph_replay_follows_a_change_of_the_recurrent_mask():
         net.snn_destroy()
 
 
-@pytest.mark.parametrize("hidden,density", [((96, 96), 1.0), ((96, 300), 0.3), ((1100,), 0.2)])
-def test_graph_replay_after_new_weights(hidden, density):
+@pytest.mark.parametrize("hidden,density,B,kernel", [((96, 96), 1.0, 4, None), ((96, 300), 0.3, 4, None), ((1100,), 0.2, 4, None),
+                                                     ((2900,), 0.1, 4, "col"),          # entries and positions by column
+                                                     ((1100, 1030, 1100), 1.0, 16, None)])  # split matrices, split adjoints
+def test_graph_replay_after_new_weights(hidden, density, B, kernel, monkeypatch):
     """A recorded step is replayed with whatever weights the context holds: after every hand-over (other values; under the same mask;
     under another mask of as many synapses, one of which fills a row) the gradients of a context that has seen nothing else."""
-    w = synth.Workload("reweigh_" + "x".join(map(str, hidden)), 40, hidden, 5, T=30, B=4, p_in=0.1, gain=0.8, rec_density=density, seed=19)
+    if kernel:
+        monkeypatch.setenv("SNN_SEQ_KERNEL", kernel)
+        monkeypatch.setenv("SNN_CSR", "1")
+    w = synth.Workload("reweigh_" + "x".join(map(str, hidden)), 40, hidden, 5, T=30, B=B, p_in=0.1, gain=0.8, rec_density=density, seed=19)
     d = synth.generate(w)
     L = len(hidden)
     other = {k: ([np.ascontiguousarray(x * np.float32(0.7)) for x in v] if k.startswith("W_") and k != "W_out" else v) for k, v in d.items()}
