@@ -62,8 +62,9 @@ inline bool seq_by_column(const MaskedLayer *layers, int n, int B, bool rows) {
 // ---- inter-layer products of the adjoint pass -----------------------------------------------------
 // N neurons below, K above: split into three bf16 parts (k_up_split) or on the fp32 matrix cores.  The same kernel for every number of
 // rows: they differ in the last bits, and gradients must not depend on how the time axis is cut.  From 1024 neurons the split one is
-// never slower (training steps, two layers: 1024 neurons, batch 4 / 16 / 64 3.73 / 4.30 / 6.84 -> 3.74 / 4.30 / 6.54 ms; 1500-1100,
-// batch 8 / 24 3.14 / 3.82 -> 3.14 / 3.73); 512 and 700 neurons gain nothing below batch 64.
+// not slower by more than a percent (training steps of 96 steps, two layers, fp32 / split: 1024 neurons, batch 4 / 16 / 64 1.89 / 2.00 / 2.49 and
+// 1.89 / 2.00 / 2.43 ms; 1500-1100, batch 8 / 24 2.41 / 2.69 and 2.42 / 2.64; 2048, batch 64 5.54 and 5.27; 4096, batch 4, 48 steps
+// 4.76 and 4.82); with two fp16 parts, half the products, 512 and 700 neurons gained nothing below batch 64.
 inline bool split_product(int N, int K) { return N >= 1024 && K >= 1024; }
 #define UPS_SLAB_BYTES 96 // 16 elements of a row of a split matrix: the high, the middle and the low parts
 constexpr size_t split_row_bytes(int K) { return (size_t)(K + 31) / 32 * (2 * UPS_SLAB_BYTES); } // whole blocks of 32 elements
@@ -74,9 +75,9 @@ constexpr size_t split_row_bytes(int K) { return (size_t)(K + 31) / 32 * (2 * UP
 // k_dw_mfma / with k_dw_split, at 3 % and 45 % activity:
 //   3 x 512 (90 tiles)    batch 16 1427 / 1459, 1890 / 1910    32 1606 / 1588, 2046 / 2027
 //   2 x 700 (124)         batch 16 1672 / 1699, 2311 / 2333    32 1800 / 1783, 2455 / 2444
-//   3 x 640 (173)         batch  8 1830 / 1873, 2473 / 2509    12 1918 / 1884, 2569 / 2555    32 2161 / 2053, 2804 / 2697
-//   3 x 1024 (372)        batch  8 2070 / 2092, 3257 / 3202    12 2199 / 2151, 3419 / 3266    32 2532 / 2422, 3958 / 3611
-//   2048 (328)            batch  8 1498 / 1539, 2737 / 2659    12 1560 / 1574, 2881 / 2726    32 1734 / 1713, 3431 / 3077
+//   3 x 640 (173)         batch  8 1830 / 1873, 2473 / 2509    12 1918 / 1903, 2571 / 2548    32 2163 / 2058, 2811 / 2704
+//   3 x 1024 (372)        batch  8 2070 / 2092, 3257 / 3202    12 2234 / 2200, 3456 / 3306    32 2577 / 2471, 4019 / 3666
+//   2048 (328)            batch  8 1498 / 1539, 2737 / 2659    12 1566 / 1577, 2882 / 2735    32 1727 / 1712, 3437 / 3079
 inline int dw_split_tiles(int n_pre, int n_post) { return ((n_pre + 255) / 256) * ((n_post + 63) / 64); }
 // octets of batch elements per step: two, or whole parts of four
 constexpr int dw_split_octets(int B) { return B <= 16 ? 2 : (B + 31) / 32 * 4; }
@@ -85,9 +86,9 @@ inline bool dw_split_pays(int tiles, int B) { return tiles >= 150 && B >= 12 && 
 // Of a masked recurrent matrix of such a network: the dense gradients here rather than the existing synapses' by k_dw_csr, which has few
 // workgroups (256 rows x 512 columns, a compute unit each) where a layer is not wide.  Training steps of 96 steps (64 from 4096
 // neurons, 32 of 8192) in chunks of 32, density 0.1, us by synapse / dense, batch 16, activity about 0, 4 and 15 to 30 %:
-//   3 x 1536 3076 / 2800, 3545 / 3037, 4202 / 3824    2 x 2048 2607 / 2444, 2949 / 2654, 3501 / 3186    4 x 2048 4469 / 4308, 5316 / 4857, 7155 / 6584
-//   2 x 3000 5452 / 5461, 6842 / 6765, 8779 / 8416    2 x 4096 4674 / 4778, 6279 / 6326, 8504 / 8292    8192 2347 / 2745, 2917 / 3302, 4030 / 4336
-// (the same at batch 12 and 32 and at density 0.05: 2 x 3000 4910 / 4930, 5948 / 5888, 6535 / 6236).
+//   3 x 1536 3126 / 2826, 3606 / 3066, 4262 / 3873    2 x 2048 2640 / 2473, 2976 / 2666, 3535 / 3212    4 x 2048 4471 / 4290, 5330 / 4845, 7155 / 6575
+//   2 x 3000 5508 / 5483, 6861 / 6765, 8895 / 8570    2 x 4096 4737 / 4826, 6347 / 6335, 8577 / 8441    8192 2337 / 2754, 2922 / 3269, 4091 / 4399
+// (the same at batch 12 and 32 and at density 0.05: 2 x 3000 4934 / 4934, 6006 / 5892, 6545 / 6242).
 inline bool dw_split_masked(int N) { return N <= 3072; }
 
 // ---- sequential forward part of layers of 257..1024 neurons (k_layer_seq_lds) --------------------
