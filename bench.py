@@ -37,7 +37,7 @@ def progress(msg):
 
 HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 MFMA_F32_PEAK_TF = 157.3  # MI355X published fp32 matrix peak
-MFMA_F16_PEAK_TF = 2516.6 # MI355X published dense fp16 matrix peak
+MFMA_BF16_PEAK_TF = 2516.6 # MI355X published dense bf16 matrix peak
 ALU_F32_PEAK_TF = 157.3   # MI355X published fp32 vector peak (256 CUs x 4 SIMDs x 64 flop/clk x 2.4 GHz)
 
 # strategy parameters per benchmark configuration: (coarse, fine); budgets from the configurations
@@ -455,11 +455,10 @@ def main():
     adj_kernel = ("k_adj_rec_rows" if ws_env in ("rows", "rows_all") or (args.surr_window > 0 and ws_env == "" and not masked_rows) else
                   "k_adj_rec_csrw" if masked_rows else
                   "k_adj_rec_wsm" if nmax <= 2048 and ws_env != "stream" else "k_adj_rec_wide")
-    # inter-layer products of matrices from 1024 x 1024: split into fp16 halves, three products, one launch per stage
+    # inter-layer products of matrices from 1024 x 1024: split into three bf16 parts, six products, one launch per stage
     gemm_big = L > 1 and min(w.n_hidden) >= 1024
-    if gemm_big:
-        model["up_gemm"] = ("mfma16", 3.0 * model["up_gemm"][1])
-    # weight gradients of networks whose matrices have 150 tiles of 256 x 64 and more, batch 12 to 64: adjoints split into three fp16
+    split_flops = {"up_gemm": 6.0 * model["up_gemm"][1]} if gemm_big else {}
+    # weight gradients of networks whose matrices have 150 tiles of 256 x 64 and more, batch 12 to 64: adjoints split into three bf16
     # values (the time includes the gradients per synapse of masked matrices wider than 3072)
     pre_n = [w.n_in] + list(w.n_hidden[:-1])
     mats = [(pre_n[l], w.n_hidden[l]) for l in range(L)] + [(w.n_hidden[-1], w.n_out)]
@@ -468,7 +467,7 @@ def main():
                 sum(-(-a // 256) * -(-b // 64) for a, b in mats + recs) >= 150)
     if dw_split:
         dense = mats + [r for r in recs if not (w.rec_density < 1.0 and w.B <= 32 and r[0] > 3072)]
-        model["dw"] = ("mfma16", 6.0 * w.T * (16 if w.B <= 16 else 32 * -(-w.B // 32)) * sum(float(a) * b for a, b in dense))
+        split_flops["dw"] = (6.0 * w.T * (16 if w.B <= 16 else 32 * -(-w.B // 32)) * sum(float(a) * b for a, b in dense))
     # launches of each kind's main kernel per step (layers that share a width and a pipeline stage share a launch)
     n_stage = n_tiles + 2 * (L - 1)
     n_cur = n_rec
@@ -515,8 +514,7 @@ def main():
                  "scan": "k_scan", "up_gemm": "k_up_split" if gemm_big else ("k_bwd_inter" if L > 2 else "k_up_gemm"), "dw": "k_dw_split" if dw_split else "k_dw_tile" if dw_tile else "k_dw_mfma", "bwd_stage": "k_bwd_stage", "fwd_stage": "k_fwd_stage_csr" if fwd_fused_wide else "k_fwd_stage",
                  "bwd_inter": "k_bwd_inter",
                  "adjoint": "k_adj_rec_rs" if not wide else ("k_adj_rec_wsm" if max(w.n_hidden) <= 1024 else adj_kernel)}
-    peaks = {"hbm": (HBM_PEAK_GBS, "GB/s", 1e9), "alu": (ALU_F32_PEAK_TF, "TFLOP/s", 1e12), "mfma32": (MFMA_F32_PEAK_TF, "TFLOP/s", 1e12),
-             "mfma16": (MFMA_F16_PEAK_TF, "TFLOP/s", 1e12)}
+    peaks = {"hbm": (HBM_PEAK_GBS, "GB/s", 1e9), "alu": (ALU_F32_PEAK_TF, "TFLOP/s", 1e12), "mfma32": (MFMA_F32_PEAK_TF, "TFLOP/s", 1e12)}
     kinds = {}
     for k, (bound, work) in model.items():
         if ms[k] <= 0:
@@ -533,8 +531,12 @@ def main():
             kinds[k]["traffic_bytes_per_launch"] = int(tr)
             if bound == "hbm":
                 kinds[k]["own_bytes_per_launch"] = int(work / launches[k])
-        what = None
-        if k == "fwd_stage" and fwd_fused_wide:
+        what, matrix_peak = None, MFMA_F32_PEAK_TF
+        if k in split_flops:
+            what, fl, matrix_peak = {"up_gemm": "bf16 matrix operations of the six products of the operands' parts",
+                                     "dw": "bf16 matrix operations of the three parts of the adjoints over every (t, b) row, a step's in whole "
+                                           "parts of 16 or 32, spikes as 0/1 operands"}[k], split_flops[k], MFMA_BF16_PEAK_TF
+        elif k == "fwd_stage" and fwd_fused_wide:
             what, fl = ("dense K=1 fp32 matrix operations of the feed-forward currents, one per presynaptic neuron; the "
                         "sequential chain over compressed rows runs beside them in the same launch"), dense_flops["fwd_currents"]
         elif kernel_of[k].startswith("k_currents_dense") and k in dense_flops:
@@ -550,9 +552,9 @@ def main():
             # compressed rows that serves its recurrent part, so its fraction is a lower bound for the dense kernel.)
             tf = fl / (ms[k] * 1e-3) / 1e12
             own = {f: kinds[k][f] for f in ("bound", "achieved", "peak", "unit", "frac")}
-            kinds[k].update({"bound": "mfma", "achieved": round(tf, 3), "peak": MFMA_F32_PEAK_TF, "unit": "TFLOP/s",
-                             "frac": round(tf / MFMA_F32_PEAK_TF, 5), "what": what, "own_work": own})
-            model[k] = ("mfma32", fl)
+            kinds[k].update({"bound": "mfma", "achieved": round(tf, 3), "peak": matrix_peak, "unit": "TFLOP/s",
+                             "frac": round(tf / matrix_peak, 5), "what": what, "own_work": own})
+            model[k] = ("mfma", fl)
     dom = max(kinds, key=lambda k: kinds[k]["ms_per_step"])
     dk = kinds[dom]
     work_per_launch = model[dom][1] / launches[dom]
@@ -564,7 +566,8 @@ def main():
                 "note": "work = the event-driven method's own work per kind (bytes of the weight rows of active presynaptic "
                         "neurons -- existing synapses only for masked matrices -- for hbm kinds; adds of those rows plus the "
                         "dense recurrent product of the adjoint for alu kinds; dense inter-layer products for mfma kinds), "
-                        "never the dense-equivalent work of a kernel; durations from HIP events on the compute stream of an "
+                        "except for the kinds with a \"what\": the matrix operations their kernel executes, the own work beside "
+                        "them (own_work); durations from HIP events on the compute stream of an "
                         "eager step; traffic = HBM bytes per launch of that kernel (FETCH_SIZE + WRITE_SIZE, scaled by the "
                         "copy kernel) from the committed rocprofv3 --pmc summary of this workload at the same launch shape "
                         "(profiles/pmc_traffic_<workload>_<strategy>.txt; null if none)",
