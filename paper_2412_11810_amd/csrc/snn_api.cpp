@@ -26,7 +26,7 @@ static void *g_scratch_dev[SNN_MAX_DEVICES]; // per device ordinal, filled by sn
 
 // Workspace of k_dw_split: the split adjoints and their scales (of every layer, the readout last) and the spikes (W_in and W_rec of layer l
 // at 2 l and 2 l + 1, W_out last) of some steps; see DwDesc.
-struct DwSpace { unsigned *special; uint4 *split[SNN_MAXL + 1]; float *scale[SNN_MAXL + 1]; uint8_t *octets[2 * SNN_MAXL + 1]; };
+struct DwSpace { uint4 *split[SNN_MAXL + 1]; float *scale[SNN_MAXL + 1]; uint8_t *octets[2 * SNN_MAXL + 1]; };
 
 struct snn_ctx {
   snn_config cfg{};
@@ -234,8 +234,7 @@ void read_kernel_hooks(snn_ctx *c) {
     n.csr_col[l] = on ? c->csr_col[l] : nullptr;
     n.csr_val[l] = on ? c->csr_val[l] : nullptr;
     n.csr_nnz[l] = on ? (uint32_t)c->csr_nnz[l] : 0u;
-    n.csr_ell[l] = on ? (uint32_t)c->csr_ell[l] : 0u;
-    n.csr_longest[l] = (uint32_t)c->csr_longest[l];
+    n.csr_ell[l] = on ? (uint32_t)c->csr_longest[l] : 0u;
     n.csr_pk[l] = on ? c->csr_pk[l] : nullptr;
   }
   if (const char *e = std::getenv("SNN_CURRENTS"))
@@ -311,11 +310,11 @@ size_t dw_bytes(const NetDev &n, int steps, unsigned char *at = nullptr, DwSpace
   };
   DwSpace none;
   DwSpace &o = d ? *d : none;
-  take(&o.special, (SNN_MAXL + 1) * sizeof(unsigned));
   for (int l = 0; l <= n.L; ++l) {
     const size_t cols = l < n.L ? n.N[l] : n.n_out;
     take(&o.split[l], octets * 3 * cols * sizeof(uint4));
-    take(&o.scale[l], (size_t)steps * per * cols * sizeof(float));
+    take(&o.scale[l], (SNN_DW_SPECIAL + (size_t)steps * per * cols) * sizeof(float));
+    if (d) o.scale[l] += SNN_DW_SPECIAL;
   }
   for (int i = 0; i <= 2 * n.L; ++i) take(&o.octets[i], octets * 64 * n.Wd[i == 2 * n.L ? n.L : (i + 1) / 2]);
   return sum;
@@ -1614,16 +1613,16 @@ struct BwdPipe {
     const int B = n.B, O = n.n_out, L = n.L, SN = n.SN;
     const size_t slot = (size_t)B * SN;
     db->wide = dw_wide ? 1 : 0;
-    db->split_steps = c->dw_steps;
+    db->split_steps = (short)c->dw_steps;
     for (const BwdTile &t : done) {
       const int l = t.layer;
       if (l == L - 1)
-        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr, c->dw_by_split ? c->dw.split[L] : nullptr, c->dw.scale[L], c->dw.octets[2 * L], c->dw.special + L};
-      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr, c->dw_by_split ? c->dw.split[l] : nullptr, c->dw.scale[l], c->dw.octets[2 * l], c->dw.special + l};
+        db->d[db->count++] = DwDesc{n.mask[L], n.Wd[L], 0, n.N[L - 1], O, t.du, (size_t)B * O, O, 0, c->acc_out, t.t0, t.t1, t.base, 0, 0, 0, n.mring[L], nullptr, nullptr, c->dw_by_split ? c->dw.split[L] : nullptr, c->dw.scale[L], c->dw.octets[2 * L]};
+      db->d[db->count++] = DwDesc{n.mask[l], n.Wd[l], 0, pre_of(n, l), n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_in[l], t.t0, t.t1, t.base, l == 0 ? 1 : 0, 0, 0, n.mring[l], nullptr, nullptr, c->dw_by_split ? c->dw.split[l] : nullptr, c->dw.scale[l], c->dw.octets[2 * l]};
       if (dw_rec_csr(c, l))
-        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_csr[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], n.csr_sub[l], n.csr_col[l], nullptr, nullptr, nullptr, nullptr};
+        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_csr[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], n.csr_sub[l], n.csr_col[l], nullptr, nullptr, nullptr};
       else
-        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr, dw_rec_split(c, l) ? c->dw.split[l] : nullptr, c->dw.scale[l], c->dw.octets[2 * l + 1], c->dw.special + l};
+        db->d[db->count++] = DwDesc{n.mask[l + 1], n.Wd[l + 1], 1, n.N[l], n.N[l], t.vbuf, slot, SN, n.off[l], c->acc_rec[l], t.t0, t.t1, t.base, 0, 0, 0, n.mring[l + 1], nullptr, nullptr, dw_rec_split(c, l) ? c->dw.split[l] : nullptr, c->dw.scale[l], c->dw.octets[2 * l + 1]};
     }
   }
   snn_status emit_dw() {
@@ -2318,7 +2317,7 @@ snn_status snn_bptt(snn_ctx *c, snn_strategy strategy, int32_t C_in, int32_t F_i
     pol = pol * 2 + (c->dw_tile ? 1u : 0u);
     const unsigned sel = (unsigned)n.sel_currents | (unsigned)n.sel_adjoint << 8 | (unsigned)n.sel_slices << 16 | (unsigned)n.sel_csr << 24 | (unsigned)n.sel_seq << 28 | (unsigned)n.no_fwd_fuse << 30;
     snn_ctx::GraphKeyT key{(int)strategy, T, p.C, p.F, p.n_chunk_bufs, c->arena, c->dubuf, c->host_ckpt, c->dw_event_driven, pol, sel,
-                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists, currents_choice(n, p.chunk_len), (void *)c->dw.special, c->dw_steps};
+                           ring > 0 ? (void *)c->mask_ring[1] : nullptr, ring > 0 ? (void *)c->host_spk : nullptr, (void *)c->mask_full[1], p.n_cache_slots, (void *)n.lists, currents_choice(n, p.chunk_len), (void *)c->dw.split[0], c->dw_steps};
     if (!c->graph_exec || !(key == c->graph_key)) {
       if (c->graph_exec) { (void)hipGraphExecDestroy(c->graph_exec); c->graph_exec = nullptr; }
       Timer tm{c, false};

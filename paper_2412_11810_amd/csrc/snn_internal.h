@@ -49,8 +49,8 @@ struct NetDev {
   // (r + 1) * SNN_CSR_SUBW + k: where a lane has no entry of a row it loads this one, and the add goes to word k of
   // the 64 spare words that follow the SNN_CSR_SUBW accumulators of sub-range r in LDS.
   const uint64_t *csr_pk[SNN_MAXL];
-  // ... and once more by column, behind the packed copy (see k_ell_fill), positions behind csr_sub's: groups of entries in all (0: not kept)
-  uint32_t csr_ell[SNN_MAXL], csr_longest[SNN_MAXL]; // and entries of the fullest slice
+  // ... and once more by column, behind the packed copy (see k_ell_fill), positions behind csr_sub's: entries of the fullest slice of 64 columns (0: not kept)
+  uint32_t csr_ell[SNN_MAXL];
   float alpha, beta, theta, k;
   float win;  // surrogate window (<= 0: none)
   // Current kernel for the layers whose weights are far beyond the L2, from the firing rates of the last step
@@ -231,15 +231,16 @@ struct DwDesc {
   // k_dw_split: space for the split adjoints and their scales (the same of the matrices of a layer), and for this matrix's
   // spikes; NULL: the other kernels
   uint4 *split;             // [steps][dw_split_octets][3][n_post]
-  float *scale;             // [steps][parts][n_post]
+  float *scale;             // [steps][parts][n_post]; SNN_DW_SPECIAL words in front of it a word that is raised where some
+                            // of the layer's adjoints are not finite
   uint8_t *octets;          // [steps][dw_split_octets][64 pre_words]
-  unsigned *special;        // a word per layer: some of its adjoints are not finite
 };
+#define SNN_DW_SPECIAL 64
 struct DwBatch {
   DwDesc d[2 * SNN_MAXL + 1];
   int count;
-  int wide;                 // tile shape, fixed per network (see snn_dw_wide_tiles)
-  int split_steps;          // steps that the workspace of k_dw_split holds
+  short wide;               // tile shape, fixed per network (see snn_dw_wide_tiles)
+  short split_steps;        // steps that the workspace of k_dw_split holds
 };
 // (matrices with a workspace for it go through k_dw_split, batch sizes up to 64)
 hipError_t launch_dw_mfma(DwBatch batch, int B, hipStream_t s);

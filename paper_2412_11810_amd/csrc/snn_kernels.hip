@@ -4446,7 +4446,7 @@ k_dw_split(DwBatch batch, int B, int per) {
         if (j < n_pre && n < n_post) out[(size_t)j * n_post + n] = acc[p][q][r];
       }
     }
-  if (*d.special == 0u) return;
+  if (*(reinterpret_cast<const unsigned *>(d.scale) - SNN_DW_SPECIAL) == 0u) return;
   // ---- adjoints that are not finite: 64 rows (a spike word) to a wavefront, a column to a lane; a row gets an infinity or, from both
   // or from what is not a number, NaN
   __syncthreads(); // (the tile is written)
@@ -5788,7 +5788,7 @@ static bool by_column_pays(const NetDev &net, unsigned layers, bool rows) { // l
   for (int l = 0; l < SNN_MAXL; ++l)
     if (layers >> l & 1u) {
       if (l >= net.L || !net.csr_ell[l]) return false;
-      m[n++] = MaskedLayer{net.N[l], net.csr_nnz[l], (int)net.csr_longest[l], net.rate[l + 1]};
+      m[n++] = MaskedLayer{net.N[l], net.csr_nnz[l], (int)net.csr_ell[l], net.rate[l + 1]};
     }
   return seq_by_column(m, n, net.B, rows);
 }
@@ -6685,18 +6685,19 @@ static hipError_t launch_dw_split_range(DwBatch batch, int B, hipStream_t s) {
   int n_rows = 0, cols = 0, steps = 0, total = 0, words = 0;
   for (int i = 0; i < batch.count; ++i) {
     DwDesc &d = batch.d[i];
-    if (d.t1 <= d.t0 || d.t1 - d.t0 > batch.split_steps || !d.scale || !d.octets || !d.split || !d.special) return hipErrorInvalidValue;
+    if (d.t1 <= d.t0 || d.t1 - d.t0 > batch.split_steps || !d.scale || !d.octets || !d.split) return hipErrorInvalidValue;
+    unsigned *const special = reinterpret_cast<unsigned *>(d.scale) - SNN_DW_SPECIAL;
     d.tiles_n = (d.n_post + DWS_TN - 1) / DWS_TN;
     d.tile0 = total;
     total += ((d.n_pre + DWS_TJ - 1) / DWS_TJ) * d.tiles_n;
-    octs.j[i] = DwOctets{d.pre_mask, d.octets, d.special, d.pre_words, d.lag, d.t0, d.t1 - d.t0, d.pre_ring};
+    octs.j[i] = DwOctets{d.pre_mask, d.octets, special, d.pre_words, d.lag, d.t0, d.t1 - d.t0, d.pre_ring};
     words = std::max(words, d.pre_words);
     steps = std::max(steps, d.t1 - d.t0);
     bool seen = false; // the matrices of a layer share their adjoints
     for (int k = 0; k < n_rows; ++k) seen = seen || rows.j[k].scale == d.scale;
     if (seen) continue;
     if (n_rows > SNN_MAXL) return hipErrorInvalidValue;
-    rows.j[n_rows++] = DwRows{d.post + (size_t)(d.t0 - d.t_base) * d.slot_stride + d.post_off, d.split, d.scale, d.special, d.slot_stride, d.post_stride,
+    rows.j[n_rows++] = DwRows{d.post + (size_t)(d.t0 - d.t_base) * d.slot_stride + d.post_off, d.split, d.scale, special, d.slot_stride, d.post_stride,
                               d.n_post, d.t1 - d.t0};
     cols = std::max(cols, d.n_post);
   }

@@ -417,9 +417,8 @@ static void split_workspace() {
           const size_t cols = l ? 8 : 2048;
           const auto add = [&](const void *p, size_t bytes) { parts.push_back({(const unsigned char *)p, (const unsigned char *)p + bytes}); };
           add(n.c->dw.split[l], octets * 48 * cols);
-          add(n.c->dw.scale[l], octets / 4 * 4 * cols);
+          add(n.c->dw.scale[l] - SNN_DW_SPECIAL, (SNN_DW_SPECIAL + octets / 4 * cols) * 4);
           for (int i = l; i < 3; i += 2) add(n.c->dw.octets[i], octets * 64 * n.c->net.Wd[i ? 1 : 0]);
-          if (l) add(n.c->dw.special, 4 * (SNN_MAXL + 1));
         }
         std::sort(parts.begin(), parts.end());
         for (size_t i = 1; i < parts.size(); ++i) CHECK(parts[i - 1].second <= parts[i].first);
