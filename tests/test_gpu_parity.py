@@ -407,6 +407,28 @@ def test_weight_gradients_in_ranges_of_steps(B, steps, monkeypatch):
     assert all(np.any(g) for g in got[0][0] + got[0][1]) and all(_identical(got[0], g) for g in got[1:])
 
 
+@pytest.mark.parametrize("hidden,B,T", [((1024, 1030), 16, 150), ((1100, 1024), 64, 140)])
+def test_weight_gradients_within_the_smallest_budget(hidden, B, T):
+    """Their workspace in what a short chunk leaves of the step's, in the few steps a context has with chunks that leave nothing, and in an
+    allocation under a budget with room: the same bits, and no more than the budget counted."""
+    w = synth.Workload("tight", 60, hidden, 7, T=T, B=B, p_in=0.1, gain=0.3, seed=B)
+    d = synth.generate(w)
+    net = snn.from_workload(w, d)
+    got = []
+    try:
+        net.snn_bind_inputs(d["in_spikes"], d["labels"], T)
+        for strat, C, F in ((snn.SNN_STANDARD, 0, 0), (snn.SNN_CHUNK, 0, 8), (snn.SNN_DOUBLE, T, 130), (snn.SNN_HIER, 2, 40)):
+            need = snn.snn_bytes_required(net.cfg, strat, T, C, F)
+            for budget in (need, need + need // 50, 3 * need, 0):
+                st = net.snn_bptt(strat, C, F, budget)
+                total = st.bytes_states + st.bytes_spikes + st.bytes_workspace
+                assert total == need if budget == need else total <= (budget or total)
+                got.append(_gpu_grads(net, 2))
+    finally:
+        net.snn_destroy()
+    assert np.any(got[0][1][1]) and all(_identical(got[0], g) for g in got[1:])
+
+
 def _same_values(got, want, rel):
     """Infinities and NaN in the same places, the other values within `rel` in the 2-norm."""
     fin = np.isfinite(want)
